@@ -143,7 +143,10 @@ int rnnd_update_neighbors_blocks(const void *X, int64_t N, int32_t d, int dtype,
 /* Bytes of device workspace a build of `rounds` = T1 * T2 UpdateNeighbors rounds (times the runs per pass for
  * rnnd_build_blocks; at most 131072) needs for these sizes (an upper bound; for rnnd_build_wide pass M as R).
  * The library allocates it at the first call that needs it and keeps it, per device, for later calls (a
- * larger request replaces it); rnnd_release_workspace hands it back. */
+ * larger request replaces it); rnnd_release_workspace hands it back.  Where the matrix-core scan needs rows of another
+ * length than X has (see rnnd_set_kernel_variant), a call also keeps a padded copy of X in the block -- N rows of d
+ * coordinates rounded up to a multiple of 128 bytes (uint8: to 32, 64, 128 or a multiple of 64) -- if the device has
+ * room for it; without room it does with the bytes reported here, slower. */
 int rnnd_workspace_bytes(int64_t N, int32_t d, int dtype, int32_t R, int64_t rounds, size_t *bytes);
 
 /* Frees the workspace block the library keeps on the current device between calls (no-op if there is none
@@ -255,11 +258,13 @@ int rnnd_probe_gather_map(const void *X, int64_t n_rows, int64_t row_bytes, int6
  * kernel for every input, 2 = automatic, but the float matrix-core scan works in double precision
  * throughout.  Automatic uses the dense Gram-block kernels on the matrix cores where they apply
  * and the generic kernel otherwise:
- *   uint8 rows with d = 32, 64 or 128: int8 MFMA;
+ *   uint8 rows: int8 MFMA (d = 32, 64 or 128 as they are, other lengths on a padded copy);
  *   float32 rows with d a multiple of 16, 16-bit rows with d a multiple of 32: a single-precision
  *   Gram block first (fp32 MFMA on float32 rows; f16 / bf16 MFMA on 16-bit rows as stored), every
  *   pair whose outcome lies within that block's error bound decided by the exact distance, and
- *   vertices with very many such pairs redone on the f64 MFMA.
+ *   vertices with very many such pairs redone on the f64 MFMA.  Float rows of other lengths, or not 16-byte
+ *   aligned, on a padded copy if there are enough of them (4,096; 16,384 if d < 16) and every coordinate is finite.
+ *   rnnd_update_neighbors on fewer than 2,048 vertices makes no copy.
  * All give identical graphs; this exists for testing and profiling.  Process-wide, not thread-safe. */
 int rnnd_set_kernel_variant(int variant);
 

@@ -43,7 +43,8 @@ struct RoundCtr {
     u32 n_touched[NMRG];  // distinct targets of the redirected edges, by size of the merge they need
     u32 bin_cursor;       // space handed out in the bin array
     u32 has_surplus;      // some vertex received more than INBOX_CAP edges this round
-    u32 pad[2];
+    u32 nonfinite;        // slot 0: k_prepare_rows met a coordinate that is NaN or infinite
+    u32 pad;
     u32 n_redo[NDEG];     // float scan: vertices the single-precision form left to the double-precision one
     // ticks of the device's constant-rate clock (0 = not taken): the round's first scan launch starts, its scatter
     // starts (= the scan has ended: launches of one stream run back to back), the round's last kernel has ended
@@ -1427,7 +1428,7 @@ struct Workspace {
     u64 *bins = nullptr;    // [N*R]   surplus of the inboxes; AddReverseEdges' bins
     u64 *thr = nullptr;     // [N]
     int *cnt = nullptr, *binoff = nullptr, *fill = nullptr, *touched = nullptr, *hubs = nullptr, *nprop = nullptr;
-    int8_t *xs = nullptr;     // X - 128 as int8 (uint8 MFMA scan)
+    int8_t *xs = nullptr;     // copy of X (see ScanPlan): X - 128 as int8 for the uint8 MFMA scan, or padded rows
     int *lists = nullptr;   // [NDEG*N] active lists by degree class
     int8_t *vcls = nullptr, *tcls = nullptr;   // [N], [NMRG*N]
     RoundCtr *ctr = nullptr;   // [n_ctr]
@@ -1521,16 +1522,65 @@ static int vec_ok_for(const void *X, int d, int dtype)
     return (rowbytes % 16 == 0) && (((uintptr_t)X) % 16 == 0);
 }
 
-// How UpdateNeighbors scans for this input: 1 = generic kernel, 2 = int8 MFMA Gram kernel (uint8 rows),
-// 3 = matrix-core Gram kernel for float or half rows (fp32 MFMA first, f64 MFMA for what it leaves).
-static int scan_variant_for(const void *X, int d, int dtype)
+// How UpdateNeighbors scans for this input.
+//   variant   1 = generic kernel, 2 = int8 MFMA Gram kernel (uint8 rows), 3 = matrix-core Gram kernel for float or 16-bit
+//             rows (fp32 / f16 / bf16 MFMA first, f64 MFMA for what it leaves)
+//   copy      what the workspace's copy of X holds: nothing (the scan reads X), the bytes minus 128 of uint8 rows that
+//             fit the tiles, or rows padded to a length the tiles take (dp coordinates; see k_prepare_*_rows)
+// The first two are what a call needs; padded rows are an extra a call does without (generic kernel) where there is
+// no room for them.
+enum CopyKind { COPY_NONE = 0, COPY_U8, COPY_U8_ROWS, COPY_ROWS, COPY_ROWS_PERMUTED };
+struct ScanPlan {
+    int variant = 1, dp = 0;
+    CopyKind copy = COPY_NONE;
+    size_t copy_bytes = 0;
+    int classes() const { return variant == 2 ? 2 : variant == 3 ? 1 : 0; }
+    bool extra() const { return copy > COPY_U8; }
+};
+
+// From how many vertices on padded rows are worth their copy, measured on whole builds (generic kernel against padded
+// rows, S = 20, R = 96, 60 rounds):
+//   uint8   always: d = 8: 1.8 -> 1.6 ms at 300 vertices, 4.8 -> 2.2 ms at 20,000; d = 100: 3.5 -> 1.6 and 15.7 -> 2.7 ms
+//   float   the matrix-core scan has eight launches per round, which small inputs wait for: d = 100: 3.0 -> 3.3 ms at 300
+//           vertices, 7.2 -> 5.7 at 4,096, 13.4 -> 9.1 at 20,000; d = 7: 2.7 -> 3.3 ms at 4,096, 4.9 -> 4.6 at 20,000
+#define PAD_MIN_N_FLOAT 4096
+#define PAD_MIN_N_SHORT_FLOAT 16384     // rows of fewer than 16 coordinates
+#define PAD_MIN_N_STEP 2048     // UpdateNeighbors by itself: a call on fewer vertices scans X as it is, with no copy made for it
+#define PAD_MAX_D 65536         // (row lengths in bytes stay far below 2^31)
+
+static bool worth_padding(long long N, int d, int dtype, bool step)
 {
+    if (d > PAD_MAX_D || (step && N < PAD_MIN_N_STEP)) return false;
+    return dtype == RNND_U8 || N >= (d < 16 ? PAD_MIN_N_SHORT_FLOAT : PAD_MIN_N_FLOAT);
+}
+
+static ScanPlan scan_plan_for(const void *X, long long N, int d, int dtype, bool may_pad)
+{
+    ScanPlan p;
+    p.dp = d;
+    if (g_kernel_variant == 1) return p;
     const bool aligned = (((uintptr_t)X) % 16 == 0);
-    if (g_kernel_variant == 1 || !aligned) return 1;
-    if (dtype == RNND_U8 && (d == 32 || d == 64 || d == 128)) return 2;
-    if (dtype == RNND_F32 && d % 16 == 0) return 3;
-    if ((dtype == RNND_F16 || dtype == RNND_BF16) && d % 32 == 0) return 3;      // rows of a multiple of 64 bytes
-    return 1;
+    if (aligned && dtype == RNND_U8 && (d == 32 || d == 64 || d == 128)) {
+        p.variant = 2;
+        p.copy = COPY_U8;
+        p.copy_bytes = (size_t)N * d;
+    } else if (aligned && ((dtype == RNND_F32 && d % 16 == 0) || ((dtype == RNND_F16 || dtype == RNND_BF16) && d % 32 == 0))) {
+        p.variant = 3;      // rows of a multiple of 64 bytes, as they are
+    } else if (may_pad) {
+        if (dtype == RNND_U8) {
+            p.variant = 2;
+            p.copy = COPY_U8_ROWS;
+            p.dp = d <= 32 ? 32 : d <= 64 ? 64 : d <= 128 ? 128 : (d + 63) / 64 * 64;
+            p.copy_bytes = (size_t)N * p.dp;
+        } else {
+            const int per = 128 / dt_size(dtype);
+            p.variant = 3;
+            p.copy = vec_ok_for(X, d, dtype) ? COPY_ROWS : COPY_ROWS_PERMUTED;
+            p.dp = (int)(((long long)d + per - 1) / per * per);
+            p.copy_bytes = (size_t)N * p.dp * dt_size(dtype);
+        }
+    }
+    return p;
 }
 
 static int cu_count()
@@ -1579,28 +1629,75 @@ struct RoundEvents {
 };
 
 template <int NG, int KS>
-static void launch_mfma_scan(const Workspace &w, int R, u64 *keys, int *deg, long long N, RoundCtr *c,
+static void launch_mfma_scan(const Workspace &w, int d, int R, u64 *keys, int *deg, long long N, RoundCtr *c,
                              hipStream_t st, hipEvent_t e_stop)
 {
     static const int per_cu = resident_blocks_per_cu(k_update_scan_mfma_u8<NG, KS>, NG == 2 ? 3 : 2);
     hipExtLaunchKernelGGL((k_update_scan_mfma_u8<NG, KS>), dim3(capped(cu_count() * per_cu, N)), dim3(256), 0, st, nullptr,
-                          e_stop, 0, (const int8_t *)w.xs, R, keys, deg, w.lists + (size_t)(NG + 1) * N,
+                          e_stop, 0, (const int8_t *)w.xs, d, R, keys, deg, w.lists + (size_t)(NG + 1) * N,
                           &c->n_active[NG + 1], w.props, w.nprop, c);
 }
 
-// Fills w.xs for the uint8 MFMA scan (d = 32, 64 or 128; X is 16-byte aligned).
-static void launch_prepare_u8(const Workspace &w, const void *X, long long N, int d, hipStream_t st)
+// Fills w.xs, the copy of X the plan asks for.
+static void launch_prepare(const Workspace &w, const ScanPlan &p, const void *X, long long N, int d, int dtype, hipStream_t st)
 {
-    const size_t n = (size_t)N * d;
-    hipLaunchKernelGGL(k_prepare_u8, dim3((unsigned)((n / 16 + 255) / 256)), dim3(256), 0, st, (const uint8_t *)X, n,
-                       w.xs);
+    const u32 exponent = dtype == RNND_F32 ? 0x7F800000u : dtype == RNND_F16 ? 0x7C00u : 0x7F80u;
+    if (p.copy == COPY_NONE) return;
+    if (p.copy == COPY_U8) {
+        const size_t n = (size_t)N * d;
+        hipLaunchKernelGGL(k_prepare_u8, dim3((unsigned)((n / 16 + 255) / 256)), dim3(256), 0, st, (const uint8_t *)X, n, w.xs);
+        return;
+    }
+    const size_t threads = p.copy == COPY_U8_ROWS ? p.copy_bytes / 4 : p.copy_bytes / 16;
+    const size_t need = (threads + 255) / 256, most = (size_t)cu_count() * 32;
+    const dim3 grid((unsigned)(need < most ? need : most));
+    const u32 rb = (u32)((size_t)p.dp * dt_size(dtype));
+    const int permute = p.copy == COPY_ROWS_PERMUTED;
+    if (p.copy == COPY_U8_ROWS)
+        hipLaunchKernelGGL(k_prepare_u8_rows, grid, dim3(256), 0, st, (const uint8_t *)X, N, d, p.dp, w.xs);
+    else if (dtype == RNND_F32)
+        hipLaunchKernelGGL(k_prepare_rows<u32>, grid, dim3(256), 0, st, (const u32 *)X, N, d, rb, permute, exponent,
+                           (uint4 *)w.xs, &w.ctr->nonfinite);
+    else
+        hipLaunchKernelGGL(k_prepare_rows<unsigned short>, grid, dim3(256), 0, st, (const unsigned short *)X, N, d, rb, permute,
+                           exponent, (uint4 *)w.xs, &w.ctr->nonfinite);
 }
 
-// Bytes of the int8 copy of X that the uint8 MFMA scan works on (0 for every other scan).
-static size_t xs_bytes_for(long long N, int d, int variant) { return variant == 2 ? (size_t)N * d : 0; }
+// The rows every kernel but the uint8 matrix-core scan reads: X, or the padded copy of float or 16-bit rows.
+struct RowsView {
+    const void *X = nullptr;
+    int d = 0, vec_ok = 0;
+};
+
+// Makes the copy the plan asks for and says what the kernels are to read.  Padded float rows are for finite
+// coordinates: where X holds a NaN or an infinity the plan falls back to the generic kernel on X itself, whose
+// comparisons treat such distances in their own way.  That answer is waited for (about 20 us; rows that need no
+// padding pay nothing).
+static hipError_t prepare_rows(const Workspace &w, ScanPlan &p, const void *X, long long N, int d, int dtype, hipStream_t st, RowsView *rv)
+{
+    rv->X = X;
+    rv->d = d;
+    rv->vec_ok = vec_ok_for(X, d, dtype);
+    launch_prepare(w, p, X, N, d, dtype, st);
+    if (p.copy != COPY_ROWS && p.copy != COPY_ROWS_PERMUTED) return hipGetLastError();
+    u32 nonfinite = 0;
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipMemcpyAsync(&nonfinite, &w.ctr->nonfinite, sizeof nonfinite, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return e;
+    if (nonfinite) {
+        p = ScanPlan();
+        p.dp = d;
+    } else {
+        rv->X = w.xs;
+        rv->d = p.dp;
+        rv->vec_ok = 1;
+    }
+    return hipSuccess;
+}
 
 template <int KS>
-static void launch_mfma_scan_classes(const Workspace &w, int R, u64 *keys, int *deg, long long N, RoundCtr *c,
+static void launch_mfma_scan_classes(const Workspace &w, int d, int R, u64 *keys, int *deg, long long N, RoundCtr *c,
                                      hipStream_t st, const RoundEvents &re)
 {
     static const int per_cu = resident_blocks_per_cu(k_update_scan_mfma_u8_small<KS>, 4);
@@ -1611,18 +1708,18 @@ static void launch_mfma_scan_classes(const Workspace &w, int R, u64 *keys, int *
         if (gx < 8) gx = 8;      // a block at least for every class
         if (n_big == 1)
             hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, 4>), dim3(gx), dim3(256), 0, st, re.scan_start, re.scan_stop, 0,
-                                  (const int8_t *)w.xs, R, keys, deg, w.lists, N, w.props, w.nprop, c);
+                                  (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, w.props, w.nprop, c);
         else if (n_big == 2)
             hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, 5>), dim3(gx), dim3(256), 0, st, re.scan_start, re.scan_stop, 0,
-                                  (const int8_t *)w.xs, R, keys, deg, w.lists, N, w.props, w.nprop, c);
+                                  (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, w.props, w.nprop, c);
         else
             hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, 6>), dim3(gx), dim3(256), 0, st, re.scan_start, re.scan_stop, 0,
-                                  (const int8_t *)w.xs, R, keys, deg, w.lists, N, w.props, w.nprop, c);
+                                  (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, w.props, w.nprop, c);
         return;
     }
     const int ny = 1 + (R > 8) + (R > 16);
     hipExtLaunchKernelGGL((k_update_scan_mfma_u8_small<KS>), dim3(capped(cu_count() * per_cu, N), ny), dim3(256), 0, st,
-                          re.scan_start, n_big == 0 ? re.scan_stop : nullptr, 0, (const int8_t *)w.xs, R, keys, deg,
+                          re.scan_start, n_big == 0 ? re.scan_stop : nullptr, 0, (const int8_t *)w.xs, d, R, keys, deg,
                           w.lists, N, w.props, w.nprop, c);
     // large inputs: the short-list launch above, then the longer classes in one launch
     if (n_big >= 2 && (g_scan_launches == 3 || (g_scan_launches == 0 && N <= LONG_SHARED_MAX_N))) {
@@ -1630,15 +1727,15 @@ static void launch_mfma_scan_classes(const Workspace &w, int R, u64 *keys, int *
         if (gx < 8) gx = 8;      // a block at least for every class
         if (n_big == 2)
             hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, 5, 3>), dim3(gx), dim3(256), 0, st, nullptr, re.scan_stop, 0,
-                                  (const int8_t *)w.xs, R, keys, deg, w.lists, N, w.props, w.nprop, c);
+                                  (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, w.props, w.nprop, c);
         else
             hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, 6, 3>), dim3(gx), dim3(256), 0, st, nullptr, re.scan_stop, 0,
-                                  (const int8_t *)w.xs, R, keys, deg, w.lists, N, w.props, w.nprop, c);
+                                  (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, w.props, w.nprop, c);
         return;
     }
-    if (R > 32) launch_mfma_scan<2, KS>(w, R, keys, deg, N, c, st, n_big == 1 ? re.scan_stop : nullptr);
-    if (R > 64) launch_mfma_scan<3, KS>(w, R, keys, deg, N, c, st, n_big == 2 ? re.scan_stop : nullptr);
-    if (R > 96) launch_mfma_scan<4, KS>(w, R, keys, deg, N, c, st, n_big == 3 ? re.scan_stop : nullptr);
+    if (R > 32) launch_mfma_scan<2, KS>(w, d, R, keys, deg, N, c, st, n_big == 1 ? re.scan_stop : nullptr);
+    if (R > 64) launch_mfma_scan<3, KS>(w, d, R, keys, deg, N, c, st, n_big == 2 ? re.scan_stop : nullptr);
+    if (R > 96) launch_mfma_scan<4, KS>(w, d, R, keys, deg, N, c, st, n_big == 3 ? re.scan_stop : nullptr);
 }
 
 // Float scan of degree class cls: the single-precision form over the class's active list.  Vertices it
@@ -1705,12 +1802,14 @@ struct VertexRun {
 // One synchronous round over the active lists of counter slot t (run == nullptr), or one run of a
 // block-sequential pass: the run's active lists are taken from vcls[] first, and the classes of the
 // vertices its merge touched go back to vcls[] instead of into the next slot's lists.
-static hipError_t launch_update_round(const Workspace &w, const void *X, long long N, int d, int dtype,
-                                      int vec_ok, int variant, int R, u64 *keys, int *deg, int t,
+static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, long long N, int dp, int dtype,
+                                      int variant, int R, u64 *keys, int *deg, int t,
                                       hipStream_t st, const RoundEvents &re = RoundEvents(),
                                       const VertexRun *run = nullptr)
 {
     const unsigned pb = capped(persistent_blocks(), N);
+    const void *X = rv.X;
+    const int d = variant == 2 ? dp : rv.d, vec_ok = rv.vec_ok;
     RoundCtr *c = w.ctr + t;
     const int use_classes = variant == 2 ? 2 : variant == 3 ? 1 : 0;
     if (run) {
@@ -1720,9 +1819,10 @@ static hipError_t launch_update_round(const Workspace &w, const void *X, long lo
                            run->first, w.vcls);
     }
     if (variant == 2) {
-        if (d == 32) launch_mfma_scan_classes<1>(w, R, keys, deg, N, c, st, re);
-        else if (d == 64) launch_mfma_scan_classes<2>(w, R, keys, deg, N, c, st, re);
-        else launch_mfma_scan_classes<4>(w, R, keys, deg, N, c, st, re);
+        if (d == 32) launch_mfma_scan_classes<1>(w, d, R, keys, deg, N, c, st, re);
+        else if (d == 64) launch_mfma_scan_classes<2>(w, d, R, keys, deg, N, c, st, re);
+        else if (d == 128) launch_mfma_scan_classes<4>(w, d, R, keys, deg, N, c, st, re);
+        else launch_mfma_scan_classes<0>(w, d, R, keys, deg, N, c, st, re);
     } else if (variant == 3) {
         // degree classes 0..6: lists of at most 8, 16, 32, 48, 64, 80, 96 entries = 1, 1, 2, 3, 4, 5, 6 groups of 16
         // rows; class 7 (97..128 entries: too many accumulator tiles) goes to the generic kernel
@@ -1801,8 +1901,8 @@ static hipError_t launch_update_round(const Workspace &w, const void *X, long lo
 
 // One block-sequential pass: `blocks` runs of ceil(N / blocks) consecutive ids, in id order, counter slots
 // t0, t0 + 1, ...  Returns the number of slots used through *used.
-static hipError_t launch_update_pass_blocks(const Workspace &w, const void *X, long long N, int d, int dtype,
-                                            int vec_ok, int variant, int R, u64 *keys, int *deg, int t0,
+static hipError_t launch_update_pass_blocks(const Workspace &w, const RowsView &rv, long long N, int dp, int dtype,
+                                            int variant, int R, u64 *keys, int *deg, int t0,
                                             long long blocks, hipStream_t st, int *used)
 {
     const long long bs = (N + blocks - 1) / blocks;
@@ -1811,7 +1911,7 @@ static hipError_t launch_update_pass_blocks(const Workspace &w, const void *X, l
         VertexRun run;
         run.first = (u32)lo;
         run.count = (u32)(lo + bs < N ? bs : N - lo);
-        hipError_t e = launch_update_round(w, X, N, d, dtype, vec_ok, variant, R, keys, deg, t0 + k, st, RoundEvents(),
+        hipError_t e = launch_update_round(w, rv, N, dp, dtype, variant, R, keys, deg, t0 + k, st, RoundEvents(),
                                            &run);
         if (e != hipSuccess) return e;
     }
@@ -1990,6 +2090,24 @@ done:
     return rc;
 }
 
+// Lays out and acquires the workspace of a build or of UpdateNeighbors calls.  Where there is no room for the padded
+// copy of X the plan does without it.
+static int ws_open(Workspace &w, WsLease *lease, ScanPlan &plan, const void *X, long long N, int R, int d, int dtype, int n_ctr,
+                   bool own_graph, bool static_only, hipStream_t st)
+{
+    w.bytes = ws_layout(w, N, R, n_ctr, own_graph, plan.copy_bytes);
+    int rc = ws_acquire(w.bytes, static_only, st, lease);
+    if ((rc == RNND_ERR_OOM || rc == RNND_ERR_SCRATCH) && plan.extra()) {
+        plan = scan_plan_for(X, N, d, dtype, false);
+        w.bytes = ws_layout(w, N, R, n_ctr, own_graph, plan.copy_bytes);
+        rc = ws_acquire(w.bytes, static_only, st, lease);
+    }
+    if (rc) return rc;
+    w.base = lease->base;
+    ws_layout(w, N, R, n_ctr, own_graph, plan.copy_bytes);
+    return RNND_OK;
+}
+
 static void ws_release(WsLease *l)
 {
     if (l->src == WS_FRESH) {
@@ -2092,8 +2210,9 @@ static int build_impl(const void *X, int64_t N, int32_t d, int dtype, int metric
     const long long per_pass = blocks ? runs_per_pass(N, blocks) : 1;
     if ((long long)T1 * T2 * per_pass > RNND_MAX_RUN_SLOTS) return RNND_ERR_BAD_PARAM;
     hipStream_t st = (hipStream_t)stream;
-    const int rounds = T1 * T2, n_ctr = (int)(rounds * per_pass) + 2, vec_ok = vec_ok_for(X, d, dtype);
-    const int variant = scan_variant_for(X, d, dtype), use_classes = variant == 2 ? 2 : variant == 3 ? 1 : 0;
+    const int rounds = T1 * T2, n_ctr = (int)(rounds * per_pass) + 2;
+    // (padded float rows read a flag back: not in a call that may not allocate)
+    ScanPlan plan = scan_plan_for(X, N, d, dtype, worth_padding(N, d, dtype, false) && (!fixed || dtype == RNND_U8));
     // events (only when statistics are wanted): 0 start, 1 end of init, last: the end.  Per-round times come from the
     // device clock (RoundCtr::t_*), which costs nothing; with rnnd_set_event_timing(1), and for block-sequential
     // passes, from events as well: 2 + 3t .. 4 + 3t = scan start, scan stop, end of round t (block-sequential passes
@@ -2105,11 +2224,8 @@ static int build_impl(const void *X, int64_t N, int32_t d, int dtype, int metric
     hipEvent_t *ev = nullptr;
     RoundCtr *hctr = nullptr;
     int n_ev_made = 0;
-    w.bytes = ws_layout(w, N, M, n_ctr, true, xs_bytes_for(N, d, variant));
-    rc = ws_acquire(w.bytes, fixed, st, &lease);
+    rc = ws_open(w, &lease, plan, X, N, M, d, dtype, n_ctr, true, fixed, st);
     if (rc) return rc;
-    w.base = lease.base;
-    ws_layout(w, N, M, n_ctr, true, xs_bytes_for(N, d, variant));
     if (stats) {
         ev = (hipEvent_t *)calloc(n_ev + 1, sizeof(hipEvent_t));
         hctr = (RoundCtr *)calloc(n_ctr, sizeof(RoundCtr));
@@ -2121,8 +2237,10 @@ static int build_impl(const void *X, int64_t N, int32_t d, int dtype, int metric
         int t = 0;
         if (stats) HIPCHK(hipEventRecord(ev[0], st));
         ws_clear(w, st);
-        if (variant == 2) launch_prepare_u8(w, X, N, d, st);
-        launch_random_graph(X, N, d, dtype, vec_ok, S, M, (u64)seed, w.keys, w.deg, w.vcls, use_classes, st);
+        RowsView rows;
+        HIPCHK(prepare_rows(w, plan, X, N, d, dtype, st, &rows));
+        const int variant = plan.variant, use_classes = plan.classes();
+        launch_random_graph(rows.X, N, rows.d, dtype, rows.vec_ok, S, M, (u64)seed, w.keys, w.deg, w.vcls, use_classes, st);
         if (!blocks) launch_compact_all(w, N, 0, st, stats ? ev[1] : nullptr);
         else if (stats) HIPCHK(hipEventRecord(ev[1], st));
         HIPCHK(hipGetLastError());
@@ -2130,7 +2248,7 @@ static int build_impl(const void *X, int64_t N, int32_t d, int dtype, int metric
             for (int t2 = 0; t2 < T2; ++t2, ++t) {
                 if (blocks) {
                     int used = 0;
-                    HIPCHK(launch_update_pass_blocks(w, X, N, d, dtype, vec_ok, variant, M, w.keys, w.deg,
+                    HIPCHK(launch_update_pass_blocks(w, rows, N, plan.dp, dtype, variant, M, w.keys, w.deg,
                                                      (int)(t * per_pass), blocks, st, &used));
                     if (stats) HIPCHK(hipEventRecord(ev[4 + 3 * t], st));
                     continue;
@@ -2143,7 +2261,7 @@ static int build_impl(const void *X, int64_t N, int32_t d, int dtype, int metric
                     re.scan_stop = ev[3 + 3 * t];
                     if (t2 == T2 - 1) re.round_stop = ev[4 + 3 * t];
                 }
-                HIPCHK(launch_update_round(w, X, N, d, dtype, vec_ok, variant, M, w.keys, w.deg, t, st, re));
+                HIPCHK(launch_update_round(w, rows, N, plan.dp, dtype, variant, M, w.keys, w.deg, t, st, re));
                 if (stats && !ev_rounds && t2 == T2 - 1)
                     hipLaunchKernelGGL(k_stamp, dim3(1), dim3(64), 0, st, &w.ctr[t].t_round_stop);
             }
@@ -2282,22 +2400,22 @@ static int update_impl(const void *X, int64_t N, int32_t d, int dtype, int metri
     const long long per_pass = blocks ? runs_per_pass(N, blocks) : 1;
     if ((long long)n_rounds * per_pass > RNND_MAX_RUN_SLOTS) return RNND_ERR_BAD_PARAM;
     hipStream_t st = (hipStream_t)stream;
-    const int n_ctr = (int)(n_rounds * per_pass) + 2, vec_ok = vec_ok_for(X, d, dtype);
-    const int variant = scan_variant_for(X, d, dtype), use_classes = variant == 2 ? 2 : variant == 3 ? 1 : 0;
+    const int n_ctr = (int)(n_rounds * per_pass) + 2;
+    ScanPlan plan = scan_plan_for(X, N, d, dtype, worth_padding(N, d, dtype, true));
     Workspace w;
     WsLease lease;
     RoundCtr *hctr = nullptr;
-    w.bytes = ws_layout(w, N, R, n_ctr, false, xs_bytes_for(N, d, variant));
-    rc = ws_acquire(w.bytes, false, st, &lease);
+    RowsView rows;
+    int variant = 1, use_classes = 0;
+    rc = ws_open(w, &lease, plan, X, N, R, d, dtype, n_ctr, false, false, st);
     if (rc) return rc;
-    w.base = lease.base;
-    ws_layout(w, N, R, n_ctr, false, xs_bytes_for(N, d, variant));
     if (stats) {
         hctr = (RoundCtr *)calloc(n_ctr, sizeof(RoundCtr));
         if (!hctr) { rc = RNND_ERR_OOM; goto done; }
     }
     ws_clear(w, st);
-    if (variant == 2) launch_prepare_u8(w, X, N, d, st);
+    HIPCHK(prepare_rows(w, plan, X, N, d, dtype, st, &rows));
+    variant = plan.variant, use_classes = plan.classes();
     hipLaunchKernelGGL(k_classify, dim3(vertex_blocks(N)), dim3(BLOCK), 0, st, (long long)N, R, (const u64 *)keys,
                        deg, w.vcls, use_classes);
     if (!blocks) launch_compact_all(w, N, 0, st);
@@ -2305,10 +2423,10 @@ static int update_impl(const void *X, int64_t N, int32_t d, int dtype, int metri
     for (int t = 0; t < n_rounds; ++t) {
         if (blocks) {
             int used = 0;
-            HIPCHK(launch_update_pass_blocks(w, X, N, d, dtype, vec_ok, variant, R, (u64 *)keys, deg,
+            HIPCHK(launch_update_pass_blocks(w, rows, N, plan.dp, dtype, variant, R, (u64 *)keys, deg,
                                              (int)(t * per_pass), blocks, st, &used));
         } else {
-            HIPCHK(launch_update_round(w, X, N, d, dtype, vec_ok, variant, R, (u64 *)keys, deg, t, st));
+            HIPCHK(launch_update_round(w, rows, N, plan.dp, dtype, variant, R, (u64 *)keys, deg, t, st));
         }
     }
     if (stats) {

@@ -93,6 +93,25 @@ __global__ __launch_bounds__(256) void k_prepare_u8(const uint8_t *__restrict__ 
     }
 }
 
+// The same for rows the tiles do not fit: row u of Xs is dp bytes (dp >= d, a multiple of 4): the d bytes of x_u minus
+// 128, then zeros, which add nothing to a product of two rows.  X may have any alignment, so it is read by single
+// bytes, a wavefront taking 256 consecutive ones of a row.
+__global__ __launch_bounds__(256) void k_prepare_u8_rows(const uint8_t *__restrict__ X, long long N, int d, int dp,
+                                                         int8_t *__restrict__ Xs)
+{
+    const u32 words = (u32)dp / 4u;
+    for (u64 i = (u64)blockIdx.x * 256u + threadIdx.x; i < (u64)N * words; i += (u64)gridDim.x * 256u) {
+        const u64 u = i / words;
+        const int e = 4 * (int)(i - u * words);
+        const uint8_t *x = X + u * (u64)d + e;
+        u32 w = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (e + k < d) w |= ((u32)x[k] ^ 0x80u) << (8 * k);
+        *(u32 *)(Xs + 4 * i) = w;
+    }
+}
+
 // What a trip has in flight for the trips after it: the rows of the next vertex (or group) and the
 // list of the one after.  The memory counter of a wavefront is in order and counts stores as well, so a
 // wait for these loads that stood after the trip's stores would also wait for the stores to be
@@ -102,13 +121,91 @@ __device__ __forceinline__ void arrived(const v4i &x) { asm volatile("" ::"v"(x)
 __device__ __forceinline__ void arrived(u64 x) { asm volatile("" ::"v"(x)); }
 __device__ __forceinline__ void arrived(int x) { asm volatile("" ::"v"(x)); }
 
-// The body of Alg. 4's vertex loop for the vertex in `cur`, whose rows are in A and whose norms are in nr.
+// Where a vertex's Gram tiles come from: formed on demand from rows that are held whole in registers (rows of 32 KS
+// bytes) ...
 template <int NG, int KS>
-__device__ __forceinline__ void scan_vertex_u8(const ScanItem &cur, v4i (&A)[NG][KS], MfmaScanSmem<NG> &sm, int R, u64 *__restrict__ keys,
+struct RowsGram {
+    const v4i (&A)[NG][KS];
+    __device__ __forceinline__ v16i tile(int I, int J) const
+    {
+        v16i G = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) G = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[J][s], A[I][s], G, 0, 0, 0);
+        return G;
+    }
+};
+// ... or accumulated beforehand while longer rows were streamed through the registers (stream_gram)
+template <int NG>
+struct StreamedGram {
+    const v16i (&G)[NG * (NG + 1) / 2];
+    __device__ __forceinline__ v16i tile(int I, int J) const { return G[I * (I + 1) / 2 + J]; }
+};
+
+// Rows of more than 128 bytes (padded with zeros to d = a multiple of 64) do not fit in registers whole: they are
+// streamed through them 32 CH bytes at a time, three buffers in rotation, while the accumulators of all the
+// vertex's tiles stay (16 registers per tile).  While the matrix cores work on one chunk the loads of the next two are
+// in flight; chunks past the end re-read the last one (a cache hit).  A list of this class fills all its NG groups,
+// and a tile costs 32 cycles per 32 bytes of its rows, a sixth of what its rows cost in memory time, so every tile is
+// formed, needed or not.  Measured on whole builds, S = 20, R = 96, 60 rounds, against the pair-at-a-time kernel these
+// rows went to before (bound by its dependent trips to memory): 60,000 x 784 36.1 -> 5.6 ms, 20,000 x 200 23.2 -> 3.0 ms.
+template <int NG, int CH>
+__device__ __forceinline__ void stream_fetch(const int8_t *const (&rp)[NG], int c, v4i (&x)[NG][CH])
+{
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int s = 0; s < CH; ++s) x[g][s] = *(const v4i *)(rp[g] + (c * CH + s) * 32);
+}
+
+template <int NG, int CH>
+__device__ __forceinline__ void stream_tiles(const v4i (&x)[NG][CH], v16i (&G)[NG * (NG + 1) / 2])
+{
+#pragma unroll
+    for (int s = 0; s < CH; ++s)
+#pragma unroll
+        for (int I = 0; I < NG; ++I)
+#pragma unroll
+            for (int J = 0; J <= I; ++J)
+                G[I * (I + 1) / 2 + J] = __builtin_amdgcn_mfma_i32_32x32x32_i8(x[J][s], x[I][s], G[I * (I + 1) / 2 + J], 0, 0, 0);
+}
+
+// Chunks 0 and 1 (in x0, x1) have been asked for; the buffers are free afterwards.
+template <int NG, int CH>
+__device__ __forceinline__ void stream_gram(const int8_t *const (&rp)[NG], int nchunk, v4i (&x0)[NG][CH], v4i (&x1)[NG][CH],
+                                            v16i (&G)[NG * (NG + 1) / 2])
+{
+    v4i x2[NG][CH];
+    const int last = nchunk - 1;
+#pragma unroll
+    for (int t = 0; t < NG * (NG + 1) / 2; ++t) G[t] = (v16i)(0);
+#pragma unroll 1
+    for (int c = 0; c < nchunk; c += 3) {
+        stream_fetch<NG, CH>(rp, c + 2 < last ? c + 2 : last, x2);
+        __builtin_amdgcn_sched_barrier(0);      // the loads first, then the matrix instructions they travel behind
+        stream_tiles<NG, CH>(x0, G);
+        __builtin_amdgcn_sched_barrier(0);
+        if (c + 1 < nchunk) {
+            stream_fetch<NG, CH>(rp, c + 3 < last ? c + 3 : last, x0);
+            __builtin_amdgcn_sched_barrier(0);
+            stream_tiles<NG, CH>(x1, G);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (c + 2 < nchunk) {
+            stream_fetch<NG, CH>(rp, c + 4 < last ? c + 4 : last, x1);
+            __builtin_amdgcn_sched_barrier(0);
+            stream_tiles<NG, CH>(x2, G);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
+// The body of Alg. 4's vertex loop for the vertex in `cur`, whose Gram tiles `gram` yields.  hold() names the
+// registers in flight for the trips after this one (see arrived).
+template <int NG, typename GRAM, typename HOLD>
+__device__ __forceinline__ void scan_vertex_u8(const ScanItem &cur, const GRAM &gram, MfmaScanSmem<NG> &sm, int R, u64 *__restrict__ keys,
                                                int *__restrict__ deg, Prop *__restrict__ props,
                                                int *__restrict__ nprop, int lane, u64 &tiles, u64 &rows,
-                                               u64 &nprops_total, u32 &ev_lane, const v4i (&An)[NG][KS],
-                                               const ScanItem &aft, int u_after)
+                                               u64 &nprops_total, u32 &ev_lane, HOLD hold)
 {
     const int l32 = lane & 31, half = lane >> 5;
     const int u = __builtin_amdgcn_readfirstlane(cur.u);      // same in every lane: keep it scalar
@@ -143,9 +240,7 @@ __device__ __forceinline__ void scan_vertex_u8(const ScanItem &cur, v4i (&A)[NG]
         if (32 * I < m) {                   // wave-uniform
             // the Gram tile of the block with itself; n of its rows is the diagonal, read back through
             // LDS (rows past the list hold row 0 of X; no mask ever selects them)
-            v16i G = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-            for (int s = 0; s < KS; ++s) G = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[I][s], A[I][s], G, 0, 0, 0);
+            const v16i G = gram.tile(I, I);
             {
                 int4 *gt = (int4 *)(sm.gt + (32 * I + l32) * GT_STRIDE + 4 * half);
                 gt[0] = make_int4(G[0], G[1], G[2], G[3]);
@@ -181,12 +276,7 @@ __device__ __forceinline__ void scan_vertex_u8(const ScanItem &cur, v4i (&A)[NG]
                 E[J] = e & hm;
                 // lane: row l32 of block I; acc[a]: column 8(a/4) + 4 half + a%4 of block J
                 v16i acc = G;
-                if (J < I) {
-                    acc = (v16i){0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-                    for (int s = 0; s < KS; ++s)
-                        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[J][s], A[I][s], acc, 0, 0, 0);
-                }
+                if (J < I) acc = gram.tile(I, J);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int4 nj = ((const int4 *)sm.nrm)[8 * J + 2 * q + half];
@@ -263,13 +353,7 @@ __device__ __forceinline__ void scan_vertex_u8(const ScanItem &cur, v4i (&A)[NG]
         }
     }
     }
-    // every store of the trip comes after this point
-#pragma unroll
-    for (int g = 0; g < NG; ++g)
-#pragma unroll
-        for (int s = 0; s < KS; ++s) arrived(An[g][s]);
-    arrived(aft.k[0]), arrived(aft.m), arrived(u_after);
-    if (NG > 2) arrived(aft.k[1]);
+    hold();     // every store of the trip comes after this point
 #pragma unroll
     for (int I = 0; I < NG; ++I)
         if (eslot[I] >= 0) emit_redirect(ekey[I], etgt[I], props + (size_t)u * R + eslot[I]);
@@ -315,6 +399,14 @@ __device__ __forceinline__ void scan_list_body(const int8_t *__restrict__ X, int
 #pragma unroll
         for (int s = 0; s < KS; ++s) arrived(A0[g][s]);
     arrived(nxt.k[0]), arrived(nxt.k[1]), arrived(nxt.m), arrived(u_after);
+    auto hold = [&](const v4i (&An)[NG][KS], const ScanItem &aft) {
+#pragma unroll
+        for (int g = 0; g < NG; ++g)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) arrived(An[g][s]);
+        arrived(aft.k[0]), arrived(aft.m), arrived(u_after);
+        if (NG > 2) arrived(aft.k[1]);
+    };
 
     u32 it = gw;
     while (true) {
@@ -325,8 +417,8 @@ __device__ __forceinline__ void scan_list_body(const int8_t *__restrict__ X, int
             const unsigned long long j = (unsigned long long)it + 3ull * nw;
             u_after = j < n_active ? list[j] : -1;
         }
-        scan_vertex_u8<NG, KS>(cur, A0, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total,
-                               ev_lane, A1, aft, u_after);
+        scan_vertex_u8<NG>(cur, RowsGram<NG, KS>{A0}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total,
+                           ev_lane, [&] { hold(A1, aft); });
         cur = nxt;
         nxt = aft;
         if ((unsigned long long)it + nw >= n_active) break;
@@ -338,8 +430,8 @@ __device__ __forceinline__ void scan_list_body(const int8_t *__restrict__ X, int
             const unsigned long long j = (unsigned long long)it + 3ull * nw;
             u_after = j < n_active ? list[j] : -1;
         }
-        scan_vertex_u8<NG, KS>(cur, A1, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total,
-                               ev_lane, A0, aft, u_after);
+        scan_vertex_u8<NG>(cur, RowsGram<NG, KS>{A1}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total,
+                           ev_lane, [&] { hold(A0, aft); });
         cur = nxt;
         nxt = aft;
         if ((unsigned long long)it + nw >= n_active) break;
@@ -351,14 +443,91 @@ __device__ __forceinline__ void scan_list_body(const int8_t *__restrict__ X, int
     if (lane == 0 && rows) add_round_stats(ctr, evals_algo, tiles * 1024ull, rows, nprops_total);
 }
 
+// The same walk for rows of d > 128 bytes (d a multiple of 64).  The first two chunks of the next vertex's rows are
+// asked for as soon as the current one's matrix work is done, so they travel during its prune test and its stores.
+template <int NG>
+__device__ __forceinline__ void scan_list_stream_body(const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
+                                                      int *__restrict__ deg, const int *__restrict__ list, u32 n_active,
+                                                      Prop *__restrict__ props, int *__restrict__ nprop,
+                                                      RoundCtr *__restrict__ ctr, MfmaScanSmem<NG> &sm, u32 block, u32 nblocks)
+{
+    constexpr int CH = NG <= 2 ? 2 : 1;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+    const u32 gw = block * 4 + wave, nw = nblocks * 4;
+    const int nchunk = d / (32 * CH);
+    u64 tiles = 0, rows = 0, nprops_total = 0;
+    u32 ev_lane = 0;
+
+    if (gw >= n_active) return;
+    auto row_pointers = [&](const ScanItem &it, const int8_t *(&rp)[NG]) {
+        const int m = it.m < 32 * NG ? it.m : 32 * NG;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const int id = __shfl((int)key_id(it.k[g >> 1]), 32 * (g & 1) + l32);
+            const bool valid = it.u >= 0 && 32 * g + l32 < m;      // else row 0 (see scan_gather)
+            rp[g] = X + (size_t)(valid ? id : 0) * (size_t)d + half * 16;
+        }
+    };
+    ScanItem cur = scan_item_load<NG>(list[gw], keys, deg, R, lane);
+    ScanItem nxt = scan_item_load<NG>(gw + nw < n_active ? list[gw + nw] : -1, keys, deg, R, lane);
+    int u_after = gw + 2 * nw < n_active ? list[gw + 2 * nw] : -1;
+    const int8_t *rp[NG];
+    v4i x0[NG][CH], x1[NG][CH];
+    row_pointers(cur, rp);
+    stream_fetch<NG, CH>(rp, 0, x0);
+    stream_fetch<NG, CH>(rp, 1, x1);
+
+    for (u32 it = gw;; it += nw) {
+        v16i G[NG * (NG + 1) / 2];
+        stream_gram<NG, CH>(rp, nchunk, x0, x1, G);
+        row_pointers(nxt, rp);
+        stream_fetch<NG, CH>(rp, 0, x0);
+        stream_fetch<NG, CH>(rp, 1, x1);
+        ScanItem aft = scan_item_load<NG>(u_after, keys, deg, R, lane);
+        {
+            const unsigned long long j = (unsigned long long)it + 3ull * nw;
+            u_after = j < n_active ? list[j] : -1;
+        }
+        scan_vertex_u8<NG>(cur, StreamedGram<NG>{G}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total,
+                           ev_lane, [&] {
+#pragma unroll
+                               for (int g = 0; g < NG; ++g)
+#pragma unroll
+                                   for (int s = 0; s < CH; ++s) arrived(x0[g][s]), arrived(x1[g][s]);
+                               arrived(aft.k[0]), arrived(aft.m), arrived(u_after);
+                               if (NG > 2) arrived(aft.k[1]);
+                           });
+        cur = nxt;
+        nxt = aft;
+        if ((unsigned long long)it + nw >= n_active) break;
+    }
+    u64 evals_algo = ev_lane;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) evals_algo += shfl_xor_u64(evals_algo, o);
+    if (lane == 0 && rows) add_round_stats(ctr, evals_algo, tiles * 1024ull, rows, nprops_total);
+}
+
+// KS = 0: rows of d > 128 bytes, streamed
 template <int NG, int KS>
-__global__ __launch_bounds__(256, (NG == 1 ? 5 : NG == 2 ? 3 : 2)) void k_update_scan_mfma_u8(
-    const int8_t *__restrict__ X, int R, u64 *__restrict__ keys,
+__device__ __forceinline__ void scan_list_any(const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
+                                              int *__restrict__ deg, const int *__restrict__ list, u32 n_active,
+                                              Prop *__restrict__ props, int *__restrict__ nprop,
+                                              RoundCtr *__restrict__ ctr, MfmaScanSmem<NG> &sm, u32 block, u32 nblocks)
+{
+    if constexpr (KS == 0) scan_list_stream_body<NG>(X, d, R, keys, deg, list, n_active, props, nprop, ctr, sm, block, nblocks);
+    else scan_list_body<NG, KS>(X, R, keys, deg, list, n_active, props, nprop, ctr, sm, block, nblocks);
+}
+
+// (four groups of streamed rows: 160 accumulator registers, so one block per CU)
+template <int NG, int KS>
+__global__ __launch_bounds__(256, (NG == 1 ? 5 : NG == 2 ? 3 : KS == 0 && NG == 4 ? 1 : 2)) void k_update_scan_mfma_u8(
+    const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
     int *__restrict__ deg, const int *__restrict__ list, const u32 *__restrict__ n_list,
     Prop *__restrict__ props, int *__restrict__ nprop, RoundCtr *__restrict__ ctr)
 {
     __shared__ MfmaScanSmem<NG> smem[4];
-    scan_list_body<NG, KS>(X, R, keys, deg, list, *n_list, props, nprop, ctr, smem[threadIdx.x >> 6], blockIdx.x, gridDim.x);
+    scan_list_any<NG, KS>(X, d, R, keys, deg, list, *n_list, props, nprop, ctr, smem[threadIdx.x >> 6], blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -388,22 +557,21 @@ __device__ __forceinline__ PackItem pack_item_load(int u, const u64 *__restrict_
 
 template <int P, int KS>
 __device__ __forceinline__ void pack_gather(const int8_t *__restrict__ X, const PackItem &it, int pos,
-                                            int half, v4i (&A)[KS])
+                                            int half, v4i (&A)[1][KS])
 {
     constexpr int d = KS * 32, W = 32 / P;
     // a lane without a list entry reads row 0 of X (see scan_gather)
     const bool valid = it.u >= 0 && pos < (it.m < W ? it.m : W);
     const int8_t *p = X + (size_t)(valid ? key_id(it.k) : 0u) * d + half * 16;
 #pragma unroll
-    for (int s = 0; s < KS; ++s) A[s] = *(const v4i *)(p + s * 32);
+    for (int s = 0; s < KS; ++s) A[0][s] = *(const v4i *)(p + s * 32);
 }
 
-template <int P, int KS>
-__device__ __forceinline__ void pack_vertices_u8(const PackItem &cur, v4i (&A)[KS], MfmaScanSmem<1> &sm, int R,
+template <int P, typename GRAM, typename HOLD>
+__device__ __forceinline__ void pack_vertices_u8(const PackItem &cur, const GRAM &gram, MfmaScanSmem<1> &sm, int R,
                                                  u64 *__restrict__ keys, int *__restrict__ deg,
                                                  Prop *__restrict__ props, int *__restrict__ nprop, int lane,
-                                                 u32 &tiles, u32 &rows, u32 &nprops_total, u32 &ev_lane,
-                                                 const v4i (&An)[KS], const PackItem &aft, int u_after)
+                                                 u32 &tiles, u32 &rows, u32 &nprops_total, u32 &ev_lane, HOLD hold)
 {
     constexpr int W = 32 / P;
     const int l32 = lane & 31, half = lane >> 5, seg = l32 / W, pos = l32 % W;
@@ -429,9 +597,7 @@ __device__ __forceinline__ void pack_vertices_u8(const PackItem &cur, v4i (&A)[K
         // n of every row: the diagonal of the Gram tile, through LDS (rows past a list hold row 0 of X;
         // no mask ever selects them)
         // lane: row l32; G[a]: <x_row, x_col> for column 8(a/4) + 4 half + a%4
-        v16i G = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-        for (int s = 0; s < KS; ++s) G = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[s], A[s], G, 0, 0, 0);
+        const v16i G = gram.tile(0, 0);
         {
             int4 *gt = (int4 *)(sm.gt + l32 * GT_STRIDE + 4 * half);
             gt[0] = make_int4(G[0], G[1], G[2], G[3]);
@@ -511,10 +677,7 @@ __device__ __forceinline__ void pack_vertices_u8(const PackItem &cur, v4i (&A)[K
         }
         nprops_total += __popc(pm);
     }
-    // every store of the trip comes after this point
-#pragma unroll
-    for (int s = 0; s < KS; ++s) arrived(An[s]);
-    arrived(aft.k), arrived(aft.m), arrived(u_after);
+    hold();     // every store of the trip comes after this point
     // the redirect: v enters w's list
     if (pruned) emit_redirect(make_key(dvw, key_id(kb), 1u), tgt_id, props + (size_t)u * R + __popc(pm & segmask & below));
     // kept entries, flag old, compacted back into the row
@@ -551,12 +714,17 @@ __device__ __forceinline__ void scan_packed_body(const int8_t *__restrict__ X, i
     PackItem cur = pack_item_load<P>(vertex_of(gw), keys, deg, R, pos);
     PackItem nxt = pack_item_load<P>(vertex_of((unsigned long long)gw + nw), keys, deg, R, pos);
     int u_after = vertex_of((unsigned long long)gw + 2ull * nw);
-    v4i A0[KS], A1[KS];
+    v4i A0[1][KS], A1[1][KS];
     pack_gather<P, KS>(X, cur, pos, half, A0);
     // once per wavefront: the loop starts with nothing in flight
 #pragma unroll
-    for (int s = 0; s < KS; ++s) arrived(A0[s]);
+    for (int s = 0; s < KS; ++s) arrived(A0[0][s]);
     arrived(nxt.k), arrived(nxt.m), arrived(u_after);
+    auto hold = [&](const v4i (&An)[1][KS], const PackItem &aft) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s) arrived(An[0][s]);
+        arrived(aft.k), arrived(aft.m), arrived(u_after);
+    };
 
     u32 it = gw;
     while (true) {
@@ -564,8 +732,8 @@ __device__ __forceinline__ void scan_packed_body(const int8_t *__restrict__ X, i
         pack_gather<P, KS>(X, nxt, pos, half, A1);
         PackItem aft = pack_item_load<P>(u_after, keys, deg, R, pos);
         u_after = vertex_of((unsigned long long)it + 3ull * nw);
-        pack_vertices_u8<P, KS>(cur, A0, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total, ev_lane,
-                                A1, aft, u_after);
+        pack_vertices_u8<P>(cur, RowsGram<1, KS>{A0}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total, ev_lane,
+                            [&] { hold(A1, aft); });
         cur = nxt;
         nxt = aft;
         if ((unsigned long long)it + nw >= n_groups) break;
@@ -574,8 +742,8 @@ __device__ __forceinline__ void scan_packed_body(const int8_t *__restrict__ X, i
         pack_gather<P, KS>(X, nxt, pos, half, A0);
         aft = pack_item_load<P>(u_after, keys, deg, R, pos);
         u_after = vertex_of((unsigned long long)it + 3ull * nw);
-        pack_vertices_u8<P, KS>(cur, A1, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total, ev_lane,
-                                A0, aft, u_after);
+        pack_vertices_u8<P>(cur, RowsGram<1, KS>{A1}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total, ev_lane,
+                            [&] { hold(A0, aft); });
         cur = nxt;
         nxt = aft;
         if ((unsigned long long)it + nw >= n_groups) break;
@@ -587,11 +755,81 @@ __device__ __forceinline__ void scan_packed_body(const int8_t *__restrict__ X, i
     if (lane == 0 && rows) add_round_stats(ctr, evals_algo, (u64)tiles * 1024ull, rows, nprops_total);
 }
 
+// The same for rows of d > 128 bytes (see scan_list_stream_body).
+template <int P>
+__device__ __forceinline__ void scan_packed_stream_body(const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
+                                                        int *__restrict__ deg, const int *__restrict__ list,
+                                                        u32 n_active, Prop *__restrict__ props,
+                                                        int *__restrict__ nprop, RoundCtr *__restrict__ ctr,
+                                                        MfmaScanSmem<1> &sm, u32 block, u32 nblocks)
+{
+    constexpr int W = 32 / P, CH = 2;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+    const int seg = l32 / W, pos = l32 % W;
+    const u32 gw = block * 4 + wave, nw = nblocks * 4;
+    const u32 n_groups = (n_active + (u32)P - 1u) / (u32)P;
+    const int nchunk = d / (32 * CH);
+    u32 tiles = 0, rows = 0, nprops_total = 0;
+    u32 ev_lane = 0;
+
+    if (gw >= n_groups) return;
+    auto vertex_of = [&](unsigned long long g) -> int {
+        const unsigned long long idx = g * P + (unsigned)seg;
+        return (g < n_groups && idx < n_active) ? list[idx] : -1;
+    };
+    auto row_pointer = [&](const PackItem &it, const int8_t *(&rp)[1]) {
+        const bool valid = it.u >= 0 && pos < (it.m < W ? it.m : W);      // else row 0 (see scan_gather)
+        rp[0] = X + (size_t)(valid ? key_id(it.k) : 0u) * (size_t)d + half * 16;
+    };
+    PackItem cur = pack_item_load<P>(vertex_of(gw), keys, deg, R, pos);
+    PackItem nxt = pack_item_load<P>(vertex_of((unsigned long long)gw + nw), keys, deg, R, pos);
+    int u_after = vertex_of((unsigned long long)gw + 2ull * nw);
+    const int8_t *rp[1];
+    v4i x0[1][CH], x1[1][CH];
+    row_pointer(cur, rp);
+    stream_fetch<1, CH>(rp, 0, x0);
+    stream_fetch<1, CH>(rp, 1, x1);
+
+    for (u32 it = gw;; it += nw) {
+        v16i G[1];
+        stream_gram<1, CH>(rp, nchunk, x0, x1, G);
+        row_pointer(nxt, rp);
+        stream_fetch<1, CH>(rp, 0, x0);
+        stream_fetch<1, CH>(rp, 1, x1);
+        PackItem aft = pack_item_load<P>(u_after, keys, deg, R, pos);
+        u_after = vertex_of((unsigned long long)it + 3ull * nw);
+        pack_vertices_u8<P>(cur, StreamedGram<1>{G}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total, ev_lane,
+                            [&] {
+#pragma unroll
+                                for (int s = 0; s < CH; ++s) arrived(x0[0][s]), arrived(x1[0][s]);
+                                arrived(aft.k), arrived(aft.m), arrived(u_after);
+                            });
+        cur = nxt;
+        nxt = aft;
+        if ((unsigned long long)it + nw >= n_groups) break;
+    }
+    u64 evals_algo = ev_lane;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) evals_algo += shfl_xor_u64(evals_algo, o);
+    if (lane == 0 && rows) add_round_stats(ctr, evals_algo, (u64)tiles * 1024ull, rows, nprops_total);
+}
+
+template <int P, int KS>
+__device__ __forceinline__ void scan_packed_any(const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
+                                                int *__restrict__ deg, const int *__restrict__ list, u32 n_active,
+                                                Prop *__restrict__ props, int *__restrict__ nprop,
+                                                RoundCtr *__restrict__ ctr, MfmaScanSmem<1> &sm, u32 block, u32 nblocks)
+{
+    if constexpr (KS == 0) scan_packed_stream_body<P>(X, d, R, keys, deg, list, n_active, props, nprop, ctr, sm, block, nblocks);
+    else scan_packed_body<P, KS>(X, R, keys, deg, list, n_active, props, nprop, ctr, sm, block, nblocks);
+}
+
 // The three short-list classes in one launch: blockIdx.y = degree class (lists of at most 8, 16, 32
 // entries: 4, 2, 1 vertices per wavefront).  Each class is walked by the gridDim.x blocks of its row.
 template <int KS>
 __global__ __launch_bounds__(256, 4) void k_update_scan_mfma_u8_small(
-    const int8_t *__restrict__ X, int R, u64 *__restrict__ keys, int *__restrict__ deg,
+    const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
     const int *__restrict__ lists, long long N, Prop *__restrict__ props, int *__restrict__ nprop,
     RoundCtr *__restrict__ ctr)
 {
@@ -601,9 +839,9 @@ __global__ __launch_bounds__(256, 4) void k_update_scan_mfma_u8_small(
     const int *list = lists + (size_t)y * N;
     const u32 n = ctr->n_active[y];
     stamp_scan_start(ctr);
-    if (y == 0) scan_packed_body<4, KS>(X, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
-    else if (y == 1) scan_packed_body<2, KS>(X, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
-    else scan_packed_body<1, KS>(X, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
+    if (y == 0) scan_packed_any<4, KS>(X, d, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
+    else if (y == 1) scan_packed_any<2, KS>(X, d, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
+    else scan_packed_any<1, KS>(X, d, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
 }
 
 // Classes C0 .. NC - 1 in one launch, all of them resident together: the grid's blocks are divided among the
@@ -615,8 +853,8 @@ __global__ __launch_bounds__(256, 4) void k_update_scan_mfma_u8_small(
 // (the short-list classes lose occupancy: with many active lists their own launch is faster).  C0 = 3, the
 // long-list classes only, next to k_update_scan_mfma_u8_small: for large inputs.
 template <int KS, int NC, int C0 = 0>
-__global__ __launch_bounds__(256, 2) void k_update_scan_mfma_u8_all(
-    const int8_t *__restrict__ X, int R, u64 *__restrict__ keys, int *__restrict__ deg,
+__global__ __launch_bounds__(256, (KS == 0 && NC == 6 ? 1 : 2)) void k_update_scan_mfma_u8_all(
+    const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
     const int *__restrict__ lists, long long N, Prop *__restrict__ props, int *__restrict__ nprop,
     RoundCtr *__restrict__ ctr)
 {
@@ -628,7 +866,8 @@ __global__ __launch_bounds__(256, 2) void k_update_scan_mfma_u8_all(
     // tiles (3 : 6 : 10; the division is sensitive there: 3 : 4.5 or 3 : 8 costs the 1M build 4 % of its scan time),
     // and a 64-entry list weighted 2.25 short tiles (measured on 100,000 vertices: 1.5 -> 1.60 ms, 2 -> 1.51, 2.25 ->
     // 1.49, 3 -> 1.53, 4 -> 1.70 ms of scan time per build)
-    constexpr u32 weight[6] = {4u, 8u, 16u, 36u, 72u, 120u};
+    // streamed rows (KS = 0): the rows' bytes dominate, and a list of a class holds 6, 12, 24, 46, 78, 112 of them or so
+    constexpr u32 weight[6] = {4u, 8u, 16u, KS ? 36u : 30u, KS ? 72u : 50u, KS ? 120u : 72u};
     u32 n[NC];
     u64 total = 0;
     u32 nonempty = 0;
@@ -664,13 +903,13 @@ __global__ __launch_bounds__(256, 2) void k_update_scan_mfma_u8_all(
     const int *list = lists + (size_t)cls * N;
     const int wave = threadIdx.x >> 6;
     MfmaScanSmem<1> &sm1 = *reinterpret_cast<MfmaScanSmem<1> *>(&smem[wave]);
-    if (C0 == 0 && cls == 0) scan_packed_body<4, KS>(X, R, keys, deg, list, n[0], props, nprop, ctr, sm1, block, mine);
-    else if (C0 == 0 && cls == 1) scan_packed_body<2, KS>(X, R, keys, deg, list, n[1], props, nprop, ctr, sm1, block, mine);
-    else if (C0 == 0 && cls == 2) scan_packed_body<1, KS>(X, R, keys, deg, list, n[2], props, nprop, ctr, sm1, block, mine);
+    if (C0 == 0 && cls == 0) scan_packed_any<4, KS>(X, d, R, keys, deg, list, n[0], props, nprop, ctr, sm1, block, mine);
+    else if (C0 == 0 && cls == 1) scan_packed_any<2, KS>(X, d, R, keys, deg, list, n[1], props, nprop, ctr, sm1, block, mine);
+    else if (C0 == 0 && cls == 2) scan_packed_any<1, KS>(X, d, R, keys, deg, list, n[2], props, nprop, ctr, sm1, block, mine);
     else if (cls == 3)
-        scan_list_body<2, KS>(X, R, keys, deg, list, n[3], props, nprop, ctr, *reinterpret_cast<MfmaScanSmem<2> *>(&smem[wave]), block, mine);
+        scan_list_any<2, KS>(X, d, R, keys, deg, list, n[3], props, nprop, ctr, *reinterpret_cast<MfmaScanSmem<2> *>(&smem[wave]), block, mine);
     else if (NC > 4 && cls == 4)
-        scan_list_body<3, KS>(X, R, keys, deg, list, n[NC > 4 ? 4 : 0], props, nprop, ctr, *reinterpret_cast<MfmaScanSmem<3> *>(&smem[wave]), block, mine);
+        scan_list_any<3, KS>(X, d, R, keys, deg, list, n[NC > 4 ? 4 : 0], props, nprop, ctr, *reinterpret_cast<MfmaScanSmem<3> *>(&smem[wave]), block, mine);
     else if (NC > 5 && cls == 5)
-        scan_list_body<4, KS>(X, R, keys, deg, list, n[NC > 5 ? 5 : 0], props, nprop, ctr, *reinterpret_cast<MfmaScanSmem<4> *>(&smem[wave]), block, mine);
+        scan_list_any<4, KS>(X, d, R, keys, deg, list, n[NC > 5 ? 5 : 0], props, nprop, ctr, *reinterpret_cast<MfmaScanSmem<4> *>(&smem[wave]), block, mine);
 }
