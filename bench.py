@@ -214,7 +214,7 @@ def measure(rn, cfg, X, Xd, esz, st16, steps, warmup, args, with_search=True, wi
     kv = s["kernel_variant"]
     kname = {1: "k_update_scan",
              2: u8_scan_kernels(cfg),
-             3: "k_update_scan_mfma_f32<NG,CH,NRC,fast> (one launch per degree class, back to back per round; "
+             3: "k_update_scan_mfma_f32_all<NRC,C0,CH,DT> (a round's scan launches, back to back; "
                 "%s MFMA Gram tiles, undecided pairs by exact distances)" % (st16 if half else "fp32")}[kv]
     traffic = None if half or args.merge_cap or args.blocks else TRAFFIC_PER_LAUNCH.get((cfg.name, kv))
     if kv == 3:

@@ -1411,6 +1411,13 @@ static int g_scan_launches = 0;    // uint8 matrix-core scan: 0 by size, 1 short
                                    // launches per class: 0.75 x at 50,000 vertices, 0.78 x at 100,000, 0.90 x at 300,000, 0.955 x
                                    // at 500,000; 1.02 x at 1M, where it wins only in rounds with fewer than 250,000 active lists).
                                    // Above: the short-list launch and one launch for all longer classes (0.99 x at 1M)
+// Float scan: up to here one launch for all classes, which costs the shorter lists their occupancy.  Whole builds, three
+// launches -> one, S = 20, 60 rounds, float32 d = 96 / 304, bfloat16 d = 768: R = 64: 20,000 vertices 4.10 -> 3.78 / 6.56
+// -> 5.98 / 7.83 -> 7.01 ms, 70,000: 9.97 -> 9.88 / 19.6 -> 19.1 / 24.0 -> 23.3, 100,000: 13.6 -> 13.8 / 28.0 -> 27.8 /
+// 34.1 -> 33.5; R = 96: 20,000: 4.27 -> 4.12 / 6.88 -> 6.65 / 8.10 -> 7.47, 50,000: 8.03 -> 8.45 / 15.0 -> 15.5 / 18.1 -> 17.6
+#define SMALL_FLOAT_MAX_N_64 65536      // R <= 64
+#define SMALL_FLOAT_MAX_N_96 32768      // R > 64
+#define SMALL_FLOAT_MAX_N_32 131072     // float32: lists of up to 32 entries in one launch (see k_update_scan_mfma_f32_all)
 #define LONG_SHARED_MAX_N 2097152  // ... up to here (1.00 x at 2M, 1.01 x at 4M, 1.00 x at 8M, 1.01 x at 20M: no start-up left to
                                    // share, and each class alone gets the occupancy that suits it); above: a launch per class
                                    // (bench.py names the round's scan launches by the same rule; include/rnnd.h states it)
@@ -1541,10 +1548,9 @@ struct ScanPlan {
 // From how many vertices on padded rows are worth their copy, measured on whole builds (generic kernel against padded
 // rows, S = 20, R = 96, 60 rounds):
 //   uint8   always: d = 8: 1.8 -> 1.6 ms at 300 vertices, 4.8 -> 2.2 ms at 20,000; d = 100: 3.5 -> 1.6 and 15.7 -> 2.7 ms
-//   float   the matrix-core scan has eight launches per round, which small inputs wait for: d = 100: 3.0 -> 3.3 ms at 300
-//           vertices, 7.2 -> 5.7 at 4,096, 13.4 -> 9.1 at 20,000; d = 7: 2.7 -> 3.3 ms at 4,096, 4.9 -> 4.6 at 20,000
-#define PAD_MIN_N_FLOAT 4096
-#define PAD_MIN_N_SHORT_FLOAT 16384     // rows of fewer than 16 coordinates
+//   float   d = 33: 2.2 -> 1.9 ms at 300 vertices, d = 100: 3.0 -> 1.9; d = 7: 1.8 -> 1.9 ms at 300, 2.4 -> 2.0 at 2,048
+#define PAD_MIN_N_FLOAT 256
+#define PAD_MIN_N_SHORT_FLOAT 2048      // rows of fewer than 16 coordinates
 #define PAD_MIN_N_STEP 2048     // UpdateNeighbors by itself: a call on fewer vertices scans X as it is, with no copy made for it
 #define PAD_MAX_D 65536         // (row lengths in bytes stay far below 2^31)
 
@@ -1738,60 +1744,106 @@ static void launch_mfma_scan_classes(const Workspace &w, int d, int R, u64 *keys
     if (R > 96) launch_mfma_scan<4, KS>(w, d, R, keys, deg, N, c, st, n_big == 3 ? re.scan_stop : nullptr);
 }
 
-// Float scan of degree class cls: the single-precision form over the class's active list.  Vertices it
-// leaves alone (ties in bulk) go to one redo list for all classes, which launch_f32_redo hands to the
-// double-precision form.  The redo list lives in the bin array, which nothing else uses until the
-// scatter that follows the scans.  Kernel variant 2: the double-precision form on the active list itself.
+// Float scan.  The single-precision form takes the active lists; vertices it leaves alone (ties in bulk) go to one redo
+// list for all classes, which launch_f32_redo hands to the double-precision form.  The redo list lives in the bin
+// array, which nothing else uses until the scatter that follows the scans.
+template <int NRCMAX, int C0, int CH, int DT>
+static void launch_f32_classes(const Workspace &w, const void *X, int d, int R, u64 *keys, int *deg, long long N, RoundCtr *c,
+                               hipStream_t st, hipEvent_t e_start)
+{
+    static const int per_cu = resident_blocks_per_cu(k_update_scan_mfma_f32_all<NRCMAX, C0, CH, DT>, 2);
+    unsigned gx = capped((long long)cu_count() * per_cu, N);
+    if (gx < 8) gx = 8;      // a block at least for every class
+    hipExtLaunchKernelGGL((k_update_scan_mfma_f32_all<NRCMAX, C0, CH, DT>), dim3(gx), dim3(256), 0, st, e_start, nullptr, 0,
+                          (const char *)X, d, R, keys, deg, w.lists, N, w.props, w.nprop, c, (int *)w.bins, &c->n_redo[0]);
+}
+
+template <int DT>
+static void launch_f32_scan(const Workspace &w, const void *X, int d, int R, u64 *keys, int *deg, long long N, RoundCtr *c,
+                            hipStream_t st, hipEvent_t e_start)
+{
+    const bool wide = ((size_t)d * dt_size(DT)) % 128 == 0;     // two 64-byte chunks per iteration
+    if (R > 32 && N <= (R <= 64 ? SMALL_FLOAT_MAX_N_64 : SMALL_FLOAT_MAX_N_96)) {
+        if (R <= 64) {
+            if (wide) launch_f32_classes<4, 0, 2, DT>(w, X, d, R, keys, deg, N, c, st, e_start);
+            else launch_f32_classes<4, 0, 1, DT>(w, X, d, R, keys, deg, N, c, st, e_start);
+        } else {
+            if (wide) launch_f32_classes<6, 0, 2, DT>(w, X, d, R, keys, deg, N, c, st, e_start);
+            else launch_f32_classes<6, 0, 1, DT>(w, X, d, R, keys, deg, N, c, st, e_start);
+        }
+        return;
+    }
+    if (DT == DT_F32 && N > SMALL_FLOAT_MAX_N_32) {
+        if (wide) launch_f32_classes<1, 0, 2, DT>(w, X, d, R, keys, deg, N, c, st, e_start);
+        else launch_f32_classes<1, 0, 1, DT>(w, X, d, R, keys, deg, N, c, st, e_start);
+        if (R > 16) {
+            if (wide) launch_f32_classes<2, 2, 2, DT>(w, X, d, R, keys, deg, N, c, st, nullptr);
+            else launch_f32_classes<2, 2, 1, DT>(w, X, d, R, keys, deg, N, c, st, nullptr);
+        }
+    } else {
+        if (wide) launch_f32_classes<2, 0, 2, DT>(w, X, d, R, keys, deg, N, c, st, e_start);
+        else launch_f32_classes<2, 0, 1, DT>(w, X, d, R, keys, deg, N, c, st, e_start);
+    }
+    if (R > 32) launch_f32_classes<4, 3, 1, DT>(w, X, d, R, keys, deg, N, c, st, nullptr);
+    if (R > 64) launch_f32_classes<6, 5, 1, DT>(w, X, d, R, keys, deg, N, c, st, nullptr);
+}
+
+// Kernel variant 2: the double-precision form on the active list of degree class cls.
 template <int NG, int CH, int NRC, int DT>
-static void launch_f32_scan_dt(const Workspace &w, const void *X, int d, int R, u64 *keys, int *deg, long long N,
-                               RoundCtr *c, int cls, hipStream_t st, hipEvent_t e_start, hipEvent_t e_stop)
+static void launch_f64_class_dt(const Workspace &w, const void *X, int d, int R, u64 *keys, int *deg, long long N,
+                                RoundCtr *c, int cls, hipStream_t st, hipEvent_t e_start, hipEvent_t e_stop)
 {
     // wavefronts that fit per SIMD: about 4 for NG = 1, 2 for NG = 2, 1 for NG = 3 (21 accumulator tiles)
-    static const int per_cu_fast = resident_blocks_per_cu(k_update_scan_mfma_f32<NG, CH, NRC, true, DT>, NG == 1 ? 4 : 2);
-    static const int per_cu = resident_blocks_per_cu(k_update_scan_mfma_f32<NG, CH, NRC, false, DT>, NG == 1 ? 4 : NG == 2 ? 2 : 1);
-    if (g_kernel_variant != 2)
-        hipExtLaunchKernelGGL((k_update_scan_mfma_f32<NG, CH, NRC, true, DT>), dim3(capped(cu_count() * per_cu_fast, N)), dim3(256), 0,
-                              st, e_start, e_stop, 0, (const char *)X, d, R, keys, deg, w.lists + (size_t)cls * N,
-                              &c->n_active[cls], w.props, w.nprop, c, (int *)w.bins, &c->n_redo[0]);
-    else
-        hipExtLaunchKernelGGL((k_update_scan_mfma_f32<NG, CH, NRC, false, DT>), dim3(capped(cu_count() * per_cu, N)), dim3(256), 0,
-                              st, e_start, e_stop, 0, (const char *)X, d, R, keys, deg, w.lists + (size_t)cls * N,
-                              &c->n_active[cls], w.props, w.nprop, c, (int *)nullptr, (u32 *)nullptr);
+    static const int per_cu = resident_blocks_per_cu(k_update_scan_f64<NG, CH, NRC, DT>, NG == 1 ? 4 : NG == 2 ? 2 : 1);
+    hipExtLaunchKernelGGL((k_update_scan_f64<NG, CH, NRC, DT>), dim3(capped(cu_count() * per_cu, N)), dim3(256), 0,
+                          st, e_start, e_stop, 0, (const char *)X, d, R, keys, deg, w.lists + (size_t)cls * N,
+                          &c->n_active[cls], w.props, w.nprop, c);
 }
 
 template <int NG, int CH, int NRC>
-static void launch_f32_scan(const Workspace &w, const void *X, int d, int dtype, int R, u64 *keys, int *deg,
-                            long long N, RoundCtr *c, int cls, hipStream_t st, hipEvent_t e_start, hipEvent_t e_stop)
+static void launch_f64_class(const Workspace &w, const void *X, int d, int dtype, int R, u64 *keys, int *deg,
+                             long long N, RoundCtr *c, int cls, hipStream_t st, hipEvent_t e_start, hipEvent_t e_stop)
 {
-    // (the three-group shape compiles badly -- with some versions of this code to thousands of spilled
-    // registers -- so lists of 33..48 entries take the four-group kernel, which skips the tiles of the empty
-    // group; the shape is not instantiated at all)
-    constexpr int NRK = NRC == 3 ? 4 : NRC;
-    if (dtype == RNND_F16)
-        launch_f32_scan_dt<NG, CH, NRK, DT_F16>(w, X, d, R, keys, deg, N, c, cls, st, e_start, e_stop);
-    else if (dtype == RNND_BF16)
-        launch_f32_scan_dt<NG, CH, NRK, DT_BF16>(w, X, d, R, keys, deg, N, c, cls, st, e_start, e_stop);
-    else
-        launch_f32_scan_dt<NG, CH, NRK, DT_F32>(w, X, d, R, keys, deg, N, c, cls, st, e_start, e_stop);
+    if (dtype == RNND_F16) launch_f64_class_dt<NG, CH, NRC, DT_F16>(w, X, d, R, keys, deg, N, c, cls, st, e_start, e_stop);
+    else if (dtype == RNND_BF16) launch_f64_class_dt<NG, CH, NRC, DT_BF16>(w, X, d, R, keys, deg, N, c, cls, st, e_start, e_stop);
+    else launch_f64_class_dt<NG, CH, NRC, DT_F32>(w, X, d, R, keys, deg, N, c, cls, st, e_start, e_stop);
 }
 
 // The double-precision form (in its widest shape: lists of up to 96 entries) over the round's redo list.
 template <int DT>
-static void launch_f32_redo_dt(const Workspace &w, const void *X, int d, int R, u64 *keys, int *deg, RoundCtr *c,
+static void launch_f32_redo_dt(const Workspace &w, const void *X, int d, int R, u64 *keys, int *deg, long long N, RoundCtr *c,
                                hipStream_t st, hipEvent_t e_stop)
 {
-    static const int per_cu = resident_blocks_per_cu(k_update_scan_mfma_f32<3, 1, 6, false, DT>, 1);
-    hipExtLaunchKernelGGL((k_update_scan_mfma_f32<3, 1, 6, false, DT>), dim3(cu_count() * per_cu), dim3(256), 0, st,
+    static const int per_cu = resident_blocks_per_cu(k_update_scan_f64<3, 1, 6, DT>, 1);
+    hipExtLaunchKernelGGL((k_update_scan_f64<3, 1, 6, DT>), dim3(capped(cu_count() * per_cu, N)), dim3(256), 0, st,
                           nullptr, e_stop, 0, (const char *)X, d, R, keys, deg, (const int *)w.bins,
-                          (const u32 *)&c->n_redo[0], w.props, w.nprop, c, (int *)nullptr, (u32 *)nullptr);
+                          (const u32 *)&c->n_redo[0], w.props, w.nprop, c);
 }
 
 static void launch_f32_redo(const Workspace &w, const void *X, int d, int dtype, int R, u64 *keys, int *deg,
-                            RoundCtr *c, hipStream_t st, hipEvent_t e_stop)
+                            long long N, RoundCtr *c, hipStream_t st, hipEvent_t e_stop)
 {
-    if (dtype == RNND_F16) launch_f32_redo_dt<DT_F16>(w, X, d, R, keys, deg, c, st, e_stop);
-    else if (dtype == RNND_BF16) launch_f32_redo_dt<DT_BF16>(w, X, d, R, keys, deg, c, st, e_stop);
-    else launch_f32_redo_dt<DT_F32>(w, X, d, R, keys, deg, c, st, e_stop);
+    if (dtype == RNND_F16) launch_f32_redo_dt<DT_F16>(w, X, d, R, keys, deg, N, c, st, e_stop);
+    else if (dtype == RNND_BF16) launch_f32_redo_dt<DT_BF16>(w, X, d, R, keys, deg, N, c, st, e_stop);
+    else launch_f32_redo_dt<DT_F32>(w, X, d, R, keys, deg, N, c, st, e_stop);
+}
+
+template <int DT>
+static void launch_generic_scan_dt(const Workspace &w, const void *X, int d, int vec_ok, int R, u64 *keys, int *deg, long long N,
+                                   int cls, unsigned blocks, RoundCtr *c, hipStream_t st, hipEvent_t e_start, hipEvent_t e_stop)
+{
+    hipExtLaunchKernelGGL(k_update_scan<DT>, dim3(blocks), dim3(BLOCK), 0, st, e_start, e_stop, 0, X, d, vec_ok, R, keys, deg,
+                          w.lists + (size_t)cls * N, &c->n_active[cls], w.props, w.nprop, c);
+}
+
+// The generic scan over the active list of class cls.
+static void launch_generic_scan(const Workspace &w, const void *X, int d, int dtype, int vec_ok, int R, u64 *keys, int *deg,
+                                long long N, int cls, unsigned blocks, RoundCtr *c, hipStream_t st, hipEvent_t e_start, hipEvent_t e_stop)
+{
+    if (dtype == RNND_U8) launch_generic_scan_dt<DT_U8>(w, X, d, vec_ok, R, keys, deg, N, cls, blocks, c, st, e_start, e_stop);
+    else if (dtype == RNND_F16) launch_generic_scan_dt<DT_F16>(w, X, d, vec_ok, R, keys, deg, N, cls, blocks, c, st, e_start, e_stop);
+    else if (dtype == RNND_BF16) launch_generic_scan_dt<DT_BF16>(w, X, d, vec_ok, R, keys, deg, N, cls, blocks, c, st, e_start, e_stop);
+    else launch_generic_scan_dt<DT_F32>(w, X, d, vec_ok, R, keys, deg, N, cls, blocks, c, st, e_start, e_stop);
 }
 
 // One run of consecutive vertex ids of a block-sequential pass: ids first .. first + count - 1.
@@ -1826,53 +1878,27 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
     } else if (variant == 3) {
         // degree classes 0..6: lists of at most 8, 16, 32, 48, 64, 80, 96 entries = 1, 1, 2, 3, 4, 5, 6 groups of 16
         // rows; class 7 (97..128 entries: too many accumulator tiles) goes to the generic kernel
-        const int n_more = (R > 8) + (R > 16) + (R > 32) + (R > 48) + (R > 64) + (R > 80) + (R > 96);
-        // the round's scan ends with its last launch: the redo pass, or the generic kernel when R > 96
-        const bool redo_pass = g_kernel_variant != 2, generic_tail = R > 96;
-        int k = 0;
-        auto stop_for = [&](void) {
-            const bool last = k++ == n_more;
-            return (last && (generic_tail || !redo_pass)) ? re.scan_stop : (hipEvent_t) nullptr;
-        };
-        const bool wide = ((size_t)d * dt_size(dtype)) % 128 == 0;     // two 64-byte chunks per iteration
-        if (wide) launch_f32_scan<1, 2, 1>(w, X, d, dtype, R, keys, deg, N, c, 0, st, re.scan_start, stop_for());
-        else launch_f32_scan<1, 1, 1>(w, X, d, dtype, R, keys, deg, N, c, 0, st, re.scan_start, stop_for());
-        if (R > 8) {
-            if (wide) launch_f32_scan<1, 2, 1>(w, X, d, dtype, R, keys, deg, N, c, 1, st, nullptr, stop_for());
-            else launch_f32_scan<1, 1, 1>(w, X, d, dtype, R, keys, deg, N, c, 1, st, nullptr, stop_for());
+        const bool generic_tail = R > 96;
+        if (g_kernel_variant != 2) {
+            if (dtype == RNND_F16) launch_f32_scan<DT_F16>(w, X, d, R, keys, deg, N, c, st, re.scan_start);
+            else if (dtype == RNND_BF16) launch_f32_scan<DT_BF16>(w, X, d, R, keys, deg, N, c, st, re.scan_start);
+            else launch_f32_scan<DT_F32>(w, X, d, R, keys, deg, N, c, st, re.scan_start);
+            launch_f32_redo(w, X, d, dtype, R, keys, deg, N, c, st, generic_tail ? (hipEvent_t) nullptr : re.scan_stop);
+        } else {
+            const int n_more = (R > 8) + (R > 16) + (R > 32) + (R > 48) + (R > 64) + (R > 80);
+            int k = 0;
+            auto stop_for = [&](void) { return (k++ == n_more && !generic_tail) ? re.scan_stop : (hipEvent_t) nullptr; };
+            launch_f64_class<1, 1, 1>(w, X, d, dtype, R, keys, deg, N, c, 0, st, re.scan_start, stop_for());
+            if (R > 8) launch_f64_class<1, 1, 1>(w, X, d, dtype, R, keys, deg, N, c, 1, st, nullptr, stop_for());
+            if (R > 16) launch_f64_class<1, 1, 2>(w, X, d, dtype, R, keys, deg, N, c, 2, st, nullptr, stop_for());
+            if (R > 32) launch_f64_class<2, 1, 4>(w, X, d, dtype, R, keys, deg, N, c, 3, st, nullptr, stop_for());
+            if (R > 48) launch_f64_class<2, 1, 4>(w, X, d, dtype, R, keys, deg, N, c, 4, st, nullptr, stop_for());
+            if (R > 64) launch_f64_class<3, 1, 5>(w, X, d, dtype, R, keys, deg, N, c, 5, st, nullptr, stop_for());
+            if (R > 80) launch_f64_class<3, 1, 6>(w, X, d, dtype, R, keys, deg, N, c, 6, st, nullptr, stop_for());
         }
-        if (R > 16) {
-            if (wide) launch_f32_scan<1, 2, 2>(w, X, d, dtype, R, keys, deg, N, c, 2, st, nullptr, stop_for());
-            else launch_f32_scan<1, 1, 2>(w, X, d, dtype, R, keys, deg, N, c, 2, st, nullptr, stop_for());
-        }
-        if (R > 32) launch_f32_scan<2, 1, 3>(w, X, d, dtype, R, keys, deg, N, c, 3, st, nullptr, stop_for());
-        if (R > 48) launch_f32_scan<2, 1, 4>(w, X, d, dtype, R, keys, deg, N, c, 4, st, nullptr, stop_for());
-        if (R > 64) launch_f32_scan<3, 1, 5>(w, X, d, dtype, R, keys, deg, N, c, 5, st, nullptr, stop_for());
-        if (R > 80) launch_f32_scan<3, 1, 6>(w, X, d, dtype, R, keys, deg, N, c, 6, st, nullptr, stop_for());
-        if (redo_pass) launch_f32_redo(w, X, d, dtype, R, keys, deg, c, st, generic_tail ? (hipEvent_t) nullptr : re.scan_stop);
-        if (R > 96) {
-            if (dtype == RNND_F16)
-                hipExtLaunchKernelGGL(k_update_scan<DT_F16>, dim3(pb), dim3(BLOCK), 0, st, nullptr, stop_for(), 0, X, d,
-                                      vec_ok, R, keys, deg, w.lists + (size_t)7 * N, &c->n_active[7], w.props, w.nprop, c);
-            else if (dtype == RNND_BF16)
-                hipExtLaunchKernelGGL(k_update_scan<DT_BF16>, dim3(pb), dim3(BLOCK), 0, st, nullptr, stop_for(), 0, X, d,
-                                      vec_ok, R, keys, deg, w.lists + (size_t)7 * N, &c->n_active[7], w.props, w.nprop, c);
-            else
-                hipExtLaunchKernelGGL(k_update_scan<DT_F32>, dim3(pb), dim3(BLOCK), 0, st, nullptr, stop_for(), 0, X, d,
-                                      vec_ok, R, keys, deg, w.lists + (size_t)7 * N, &c->n_active[7], w.props, w.nprop, c);
-        }
-    } else if (dtype == RNND_U8) {
-        hipExtLaunchKernelGGL(k_update_scan<DT_U8>, dim3(pb), dim3(BLOCK), 0, st, re.scan_start, re.scan_stop, 0, X, d,
-                              vec_ok, R, keys, deg, w.lists, &c->n_active[0], w.props, w.nprop, c);
-    } else if (dtype == RNND_F16) {
-        hipExtLaunchKernelGGL(k_update_scan<DT_F16>, dim3(pb), dim3(BLOCK), 0, st, re.scan_start, re.scan_stop, 0, X, d,
-                              vec_ok, R, keys, deg, w.lists, &c->n_active[0], w.props, w.nprop, c);
-    } else if (dtype == RNND_BF16) {
-        hipExtLaunchKernelGGL(k_update_scan<DT_BF16>, dim3(pb), dim3(BLOCK), 0, st, re.scan_start, re.scan_stop, 0, X, d,
-                              vec_ok, R, keys, deg, w.lists, &c->n_active[0], w.props, w.nprop, c);
+        if (generic_tail) launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, 7, pb, c, st, nullptr, re.scan_stop);
     } else {
-        hipExtLaunchKernelGGL(k_update_scan<DT_F32>, dim3(pb), dim3(BLOCK), 0, st, re.scan_start, re.scan_stop, 0, X, d,
-                              vec_ok, R, keys, deg, w.lists, &c->n_active[0], w.props, w.nprop, c);
+        launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, 0, pb, c, st, re.scan_start, re.scan_stop);
     }
     // from here on `fill` plays the role of the per-target count of this round
     const int ncl = use_classes ? NDEG : 1;

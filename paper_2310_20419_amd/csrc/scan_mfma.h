@@ -844,6 +844,45 @@ __global__ __launch_bounds__(256, 4) void k_update_scan_mfma_u8_small(
     else scan_packed_any<1, KS>(X, d, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
 }
 
+// Divides the grid's blocks among NC classes in proportion to their work, n[c] lists of weight[c] each; the grid has
+// more blocks than there are classes (and < 2^24).  Returns the class of this block, which is number `block` of the
+// `mine` blocks that class got, or -1 if there is no work at all.
+// A class gets one block plus its share of the rest: the shares are differences of one non-decreasing
+// function of the running sum that ends at `spare` exactly (total / total = 1), so they add up to the grid
+// whatever the rounding of the single-precision quotient; every block computes the same numbers.
+template <int NC, int NWEIGHT>
+__device__ __forceinline__ int share_blocks(const u32 (&n)[NC], const u32 (&weight)[NWEIGHT], u32 &block, u32 &mine)
+{
+    u64 total = 0;
+    u32 nonempty = 0;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        total += (u64)n[c] * weight[c];
+        nonempty += n[c] != 0u;
+    }
+    if (total == 0) return -1;
+    const u32 spare = gridDim.x - nonempty;
+    const float scale = (float)spare, ftotal = (float)total;
+    u32 first = 0, below = 0;
+    int cls = -1;
+    u64 cum = 0;
+    mine = 0;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        cum += (u64)n[c] * weight[c];
+        const u32 upto = (u32)(scale * ((float)cum / ftotal));
+        const u32 nb = n[c] ? 1u + upto - below : 0u;
+        below = upto;
+        if (cls < 0 && blockIdx.x < first + nb) {
+            cls = c;
+            mine = nb;
+        }
+        if (cls < 0) first += nb;
+    }
+    block = blockIdx.x - first;
+    return cls;      // (-1 cannot happen here: the shares add up to the grid)
+}
+
 // Classes C0 .. NC - 1 in one launch, all of them resident together: the grid's blocks are divided among the
 // classes in proportion to their work (active lists x matrix tiles per list), one block at least for a class
 // that has any; every block derives the same division from the round's counters.  The classes then share the
@@ -869,37 +908,11 @@ __global__ __launch_bounds__(256, (KS == 0 && NC == 6 ? 1 : 2)) void k_update_sc
     // streamed rows (KS = 0): the rows' bytes dominate, and a list of a class holds 6, 12, 24, 46, 78, 112 of them or so
     constexpr u32 weight[6] = {4u, 8u, 16u, KS ? 36u : 30u, KS ? 72u : 50u, KS ? 120u : 72u};
     u32 n[NC];
-    u64 total = 0;
-    u32 nonempty = 0;
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        n[c] = c >= C0 ? ctr->n_active[c] : 0u;
-        total += (u64)n[c] * weight[c];
-        nonempty += n[c] != 0u;
-    }
-    if (total == 0) return;
-    // A class gets one block plus its share of the rest: the shares are differences of one non-decreasing
-    // function of the running sum that ends at `spare` exactly (total / total = 1), so they add up to the grid
-    // whatever the rounding of the single-precision quotient; every block computes the same numbers.
-    const u32 spare = gridDim.x - nonempty;      // the grid has more blocks than there are classes (and < 2^24)
-    const float scale = (float)spare, ftotal = (float)total;
-    u32 first = 0, mine = 0, below = 0;
-    int cls = -1;
-    u64 cum = 0;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        cum += (u64)n[c] * weight[c];
-        const u32 upto = (u32)(scale * ((float)cum / ftotal));
-        const u32 nb = n[c] ? 1u + upto - below : 0u;
-        below = upto;
-        if (cls < 0 && blockIdx.x < first + nb) {
-            cls = c;
-            mine = nb;
-        }
-        if (cls < 0) first += nb;
-    }
-    if (cls < 0) return;      // cannot happen: the shares add up to the grid
-    const u32 block = blockIdx.x - first;
+    for (int c = 0; c < NC; ++c) n[c] = c >= C0 ? ctr->n_active[c] : 0u;
+    u32 block, mine;
+    const int cls = share_blocks<NC>(n, weight, block, mine);
+    if (cls < 0) return;
     const int *list = lists + (size_t)cls * N;
     const int wave = threadIdx.x >> 6;
     MfmaScanSmem<1> &sm1 = *reinterpret_cast<MfmaScanSmem<1> *>(&smem[wave]);

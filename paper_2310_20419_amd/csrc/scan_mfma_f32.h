@@ -308,11 +308,14 @@ __device__ __forceinline__ int popc_below_w(u64 m0, u64 m1, int p)
 // against double precision stays below 2.3 x 2^-24 per instruction, also for operands spread over 20
 // binades, and shows that subnormal halves count), G and either norm are off by at most
 // (d / 4) 2^-24 of sqrt(n_i n_j) resp. n, hence eps_ij = (0.5 d + 20) 2^-24 (n_i + n_j).
-template <int NG, int CH, int NRC = 2 * NG, bool FAST = false, int DT = DT_F32>
-__global__ __launch_bounds__(64 * 4, (FAST ? (NRC <= 2 ? 4 : NRC <= 4 ? 3 : 2) : (NRC <= 2 ? 4 : NRC <= 5 ? 2 : 1))) void k_update_scan_mfma_f32(
+//
+// The work list: entries 0 .. n_first - 1 are list[0 ..], entries n_first .. n_active - 1 follow `skip` places further on
+// (a second degree class that the same shape serves).
+template <int NG, int CH, int NRC, bool FAST, int DT>
+__device__ __forceinline__ void f32_scan_body(
     const char *__restrict__ X, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
-    const int *__restrict__ list, const u32 *__restrict__ n_list, Prop *__restrict__ props,
-    int *__restrict__ nprop, RoundCtr *__restrict__ ctr, int *__restrict__ redo, u32 *__restrict__ n_redo)
+    const int *__restrict__ list, u32 n_first, size_t skip, u32 n_active, Prop *__restrict__ props, int *__restrict__ nprop,
+    RoundCtr *__restrict__ ctr, int *__restrict__ redo, u32 *__restrict__ n_redo, F32ScanSmem<NRC> &sm, u32 block, u32 nblocks)
 {
     typedef typename GramAcc<FAST>::type acc_t;
     // 16-bit rows in the single-precision form: the matrix instruction takes them as they are
@@ -323,28 +326,23 @@ __global__ __launch_bounds__(64 * 4, (FAST ? (NRC <= 2 ? 4 : NRC <= 4 ? 3 : 2) :
     constexpr int NWD = (NRC + 1) / 2;        // 32-bit words of a mask over slots
     constexpr int NSET = NRC > 4 ? 2 : 1;     // lane (r16, q) owns rows 16 q + r16 and, if NRC > 4, 64 + 16 q + r16
     static_assert(NRC >= 1 && NRC <= 6 && (NRC == 2 * NG || NRC == 2 * NG - 1), "lists of at most 96 entries");
-    __shared__ F32ScanSmem<NRC> smem[4];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int r16 = lane & 15, q = lane >> 4, sub = lane & 7, grp = lane >> 3;
-    const u32 gw = blockIdx.x * 4 + wave, nw = gridDim.x * 4;
-    const u32 n_active = *n_list;
-    F32ScanSmem<NRC> &sm = smem[wave];
+    const u32 gw = block * 4 + wave, nw = nblocks * 4;
     const u32 rowbytes = (u32)d * (u32)dt_size(DT);     // at most a few hundred KB
     const int nchunk = (int)(rowbytes / (64u * CH));
     u64 tiles = 0, rows = 0, nprops_total = 0;
     u32 ev_lane = 0;
 
-    stamp_scan_start(ctr);
     if (gw >= n_active) return;
-    ScanItem cur = scan_item_load<NG>(list[gw], keys, deg, R, lane);
-    ScanItem nxt = scan_item_load<NG>(gw + nw < n_active ? list[gw + nw] : -1, keys, deg, R, lane);
+    auto vertex_at = [&](unsigned long long i) -> int {
+        return i < n_active ? list[i < n_first ? i : i + skip] : -1;
+    };
+    ScanItem cur = scan_item_load<NG>(vertex_at(gw), keys, deg, R, lane);
+    ScanItem nxt = scan_item_load<NG>(vertex_at((unsigned long long)gw + nw), keys, deg, R, lane);
 
     for (u32 it = gw; it < n_active; it += nw) {
-        int u_after = -1;
-        {
-            const unsigned long long j = (unsigned long long)it + 2ull * nw;
-            if (j < n_active) u_after = list[j];
-        }
+        const int u_after = vertex_at((unsigned long long)it + 2ull * nw);
         ScanItem aft = scan_item_load<NG>(u_after, keys, deg, R, lane);
 
         const int u = __builtin_amdgcn_readfirstlane(cur.u);      // same in every lane: keep it scalar
@@ -754,4 +752,71 @@ __global__ __launch_bounds__(64 * 4, (FAST ? (NRC <= 2 ? 4 : NRC <= 4 ? 3 : 2) :
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) evals_algo += shfl_xor_u64(evals_algo, o);
     if (lane == 0 && rows) add_round_stats(ctr, evals_algo, tiles * 256ull, rows, nprops_total);
+}
+
+// The double-precision form over one list: the redo list, or (kernel variant 2) the active list of a degree class.
+template <int NG, int CH, int NRC, int DT>
+__global__ __launch_bounds__(64 * 4, (NRC <= 2 ? 4 : NRC <= 5 ? 2 : 1)) void k_update_scan_f64(
+    const char *__restrict__ X, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
+    const int *__restrict__ list, const u32 *__restrict__ n_list, Prop *__restrict__ props,
+    int *__restrict__ nprop, RoundCtr *__restrict__ ctr)
+{
+    __shared__ F32ScanSmem<NRC> smem[4];
+    stamp_scan_start(ctr);
+    const u32 n = *n_list;
+    f32_scan_body<NG, CH, NRC, false, DT>(X, d, R, keys, deg, list, n, 0, n, props, nprop, ctr, nullptr, nullptr,
+                                          smem[threadIdx.x >> 6], blockIdx.x, gridDim.x);
+}
+
+// The single-precision form of the degree classes from C0 on, up to lists of 16 NRCMAX entries, in one launch, the
+// grid's blocks divided among them in proportion to their work (share_blocks).  All classes together (C0 = 0): for
+// inputs so small that no class fills the chip by itself and a round waits for one short launch after the other; every
+// block then has the registers of the longest shape.  Larger inputs take the classes that need about the same number
+// of registers together: up to 32 entries (C0 = 0; float32 rows: up to 16 entries, and 17 .. 32 with C0 = 2, because the
+// two shapes side by side need a few registers more than four wavefronts per SIMD leave: 1M x 96 152.5 against 146.5
+// ms), 33 .. 64 (C0 = 3), 65 .. 96 (C0 = 5).
+template <int NRCMAX, int C0, int CH, int DT>
+__global__ __launch_bounds__(64 * 4, (NRCMAX <= 2 ? 4 : NRCMAX <= 4 ? 3 : 2)) void k_update_scan_mfma_f32_all(
+    const char *__restrict__ X, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
+    const int *__restrict__ lists, long long N, Prop *__restrict__ props, int *__restrict__ nprop,
+    RoundCtr *__restrict__ ctr, int *__restrict__ redo, u32 *__restrict__ n_redo)
+{
+    static_assert(NRCMAX == 1 || NRCMAX == 2 || NRCMAX == 4 || NRCMAX == 6, "lists of at most 16, 32, 64, 96 entries");
+    __shared__ F32ScanSmem<NRCMAX> smem[4];
+    if (C0 == 0) stamp_scan_start(ctr);
+    // the shapes and the classes they serve: 1 group (classes 0, 1), 2 (2), 4 (3, 4: the three-group shape compiles badly --
+    // with some versions of this code to thousands of spilled registers -- and the four-group one skips the tiles of an
+    // empty group), 5 (5), 6 (6); work per list: its rows, plus what a list costs whatever its length (60-round builds of
+    // 20,000 x 96 / x 304 float32: 4.05 / 6.45 ms; 12 : 24 : 52 : 72 : 88 4.24 / 6.99, 8 : 24 : 56 : 90 : 110 4.98 / 8.24,
+    // 24 : 26 : 40 : 50 : 60 4.19 / 6.92)
+    constexpr int NS = NRCMAX == 1 ? 1 : NRCMAX == 2 ? 2 : NRCMAX == 4 ? 3 : 5;
+    constexpr int first_class[5] = {0, 2, 3, 5, 6};
+    constexpr u32 weight[5] = {16u, 24u, 44u, 60u, 72u};
+    u32 n[NS], n1[NS];
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+        const int c = first_class[k];
+        const bool on = c >= C0, two = k == 0 || k == 2;
+        n1[k] = on ? ctr->n_active[c] : 0u;
+        n[k] = n1[k] + (on && two ? ctr->n_active[c + 1] : 0u);
+    }
+    u32 block, mine;
+    const int k = share_blocks<NS>(n, weight, block, mine);
+    if (k < 0) return;
+    const int wave = threadIdx.x >> 6;
+#define RNND_F32_SHAPE(K_, NG_, CH_, NRC_)                                                                            \
+    f32_scan_body<NG_, CH_, NRC_, true, DT>(X, d, R, keys, deg, lists + (size_t)first_class[K_] * N, n1[K_],           \
+                                            (size_t)N - n1[K_], n[K_], props, nprop, ctr, redo, n_redo,                \
+                                            *reinterpret_cast<F32ScanSmem<NRC_> *>(&smem[wave]), block, mine)
+    if constexpr (C0 == 0)
+        if (k == 0) RNND_F32_SHAPE(0, 1, CH, 1);
+    if constexpr (NRCMAX >= 2 && C0 <= 2)
+        if (k == 1) RNND_F32_SHAPE(1, 1, CH, 2);
+    if constexpr (NRCMAX >= 4 && C0 <= 3)
+        if (k == 2) RNND_F32_SHAPE(2, 2, 1, 4);
+    if constexpr (NRCMAX >= 6) {
+        if (k == 3) RNND_F32_SHAPE(3, 3, 1, 5);
+        if (k == 4) RNND_F32_SHAPE(4, 3, 1, 6);
+    }
+#undef RNND_F32_SHAPE
 }

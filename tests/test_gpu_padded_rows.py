@@ -9,9 +9,7 @@ from gpu_util import assert_snapshot_equal
 
 pytestmark = pytest.mark.gpu
 
-def _n(dtype, d):
-    """Just past the number of vertices from which rows of this kind are padded."""
-    return 2304 if dtype == "u8" else 4160 if d >= 16 else 16500
+N = 2304      # past the 2,048 vertices from which the step-wise call pads too
 
 
 @pytest.fixture(scope="module")
@@ -63,7 +61,6 @@ def _params(i):
 def test_build_equals_oracle_and_generic_kernel(rn, oracle_mod, i, dtype, d, offset):
     import torch
     S, R, T1, T2 = _params(i)
-    N = _n(dtype, d)
     X = _u8(N, d, i) if dtype == "u8" else _float(N, d, i)
     if dtype in ("f16", "bf16"):
         X = torch.from_numpy(X).to(getattr(torch, {"f16": "float16", "bf16": "bfloat16"}[dtype])).float().numpy()
@@ -96,7 +93,7 @@ def test_build_equals_oracle_and_generic_kernel(rn, oracle_mod, i, dtype, d, off
 def test_every_launch_form_of_the_long_uint8_rows(rn, oracle_mod, mode):
     """One launch for all classes, the short-list launch plus one, a launch per class."""
     import torch
-    X = _u8(2304, 200, 77, k=3, spread=9)            # tight clusters: lists of every length up to 128
+    X = _u8(N, 200, 77, k=3, spread=9)            # tight clusters: lists of every length up to 128
     want = oracle_mod.build_sync(X, 60, 128, 2, 3, 11)
     try:
         rn.rnnd_set_scan_launches(mode)
@@ -107,12 +104,30 @@ def test_every_launch_form_of_the_long_uint8_rows(rn, oracle_mod, mode):
     assert list(st.algo_evals[:6]) == want.round_evals.tolist()
 
 
+@pytest.mark.parametrize("dtype,d", [("u8", 100), ("f32", 33), ("bf16", 65)])
+@pytest.mark.parametrize("n,R", [(300, 128), (300, 32), (40_000, 96), (70_000, 64), (140_000, 48)])
+def test_launch_forms_by_size(rn, dtype, d, n, R):
+    """Sizes on either side of the rules that choose how many launches a scan takes: the generic kernel's graph."""
+    import torch
+    X = torch.from_numpy(_u8(n, d, 2, k=40, spread=30) if dtype == "u8" else _float(n, d, 2)).cuda()
+    X = X.to(torch.bfloat16) if dtype == "bf16" else X
+    got = rn.rnnd_build_ex(X, 20, R, 2, 3, 4)
+    assert got[3].kernel_variant == (2 if dtype == "u8" else 3)
+    try:
+        rn.rnnd_set_kernel_variant(1)
+        want = rn.rnnd_build_ex(X, 20, R, 2, 3, 4)
+    finally:
+        rn.rnnd_set_kernel_variant(0)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    assert list(got[3].algo_evals[:6]) == list(want[3].algo_evals[:6])
+
+
 @pytest.mark.parametrize("bad", [np.nan, np.inf])
 @pytest.mark.parametrize("d", [33, 100])
 def test_nan_and_infinity_go_to_the_generic_kernel(rn, bad, d):
     """A coordinate that is not finite: the same graph as the generic kernel gives on X."""
     import torch
-    X = _float(_n("f32", d), d, 5)
+    X = _float(N, d, 5)
     X[[3, 700, 701, 2000], [0, 1, d - 1, d // 2]] = bad
     Xd = torch.from_numpy(X).cuda()
     got = rn.rnnd_build_ex(Xd, 20, 64, 2, 3, 4)
