@@ -2042,6 +2042,7 @@ static void fill_round_stats(rnnd_stats *s, const RoundCtr *h, int rounds)
 // 2. a fresh allocation, freed when the call ends, if another thread's call holds that block;
 // 3. for rnnd_build_static only: the file-scope array below, which needs no allocation at all.
 #define RNND_MAX_DEVICES 64
+#define SEARCH_MAX_BLOCKS 16384     // queries a search has in flight at most
 
 static __device__ __align__(256) unsigned char scratch[RNND_STATIC_SCRATCH_BYTES];
 
@@ -2050,6 +2051,7 @@ struct DeviceSlot {
     size_t cached_bytes = 0;
     bool busy = false;             // a call is using it
     char *static_ptr = nullptr;    // this device's copy of `scratch` (hipGetSymbolAddress, once per device)
+    unsigned long long *counts = nullptr;   // pinned host memory, kept like the block: SEARCH_MAX_BLOCKS evaluation counts
 };
 static std::mutex g_ws_mu;
 static DeviceSlot g_dev[RNND_MAX_DEVICES];
@@ -2158,9 +2160,33 @@ extern "C" int rnnd_release_workspace(void)
             d.cached = nullptr;
             d.cached_bytes = 0;
         }
+        if (d.counts && !d.busy) {
+            HIPCHK(hipHostFree(d.counts));
+            d.counts = nullptr;
+        }
     }
 done:
     return rc;
+}
+
+// Where the blocks of a search put their evaluation counts: the kept buffer if the lease holds the kept block, else one
+// of its own (freed by counts_release).
+static int counts_acquire(const WsLease &l, unsigned long long **out)
+{
+    int rc = RNND_OK;
+    if (l.src == WS_CACHED) {       // busy: no other call touches the slot's buffer
+        DeviceSlot &d = g_dev[l.dev];
+        if (!d.counts) HIPCHK(hipHostMalloc((void **)&d.counts, SEARCH_MAX_BLOCKS * sizeof(unsigned long long), hipHostMallocDefault));
+        *out = d.counts;
+    } else {
+        HIPCHK(hipHostMalloc((void **)out, SEARCH_MAX_BLOCKS * sizeof(unsigned long long), hipHostMallocDefault));
+    }
+done:
+    return rc;
+}
+static void counts_release(const WsLease &l, unsigned long long *p)
+{
+    if (p && l.src != WS_CACHED) (void)hipHostFree(p);
 }
 
 extern "C" int rnnd_set_workspace_poison(int on)
@@ -2558,47 +2584,85 @@ extern "C" int rnnd_search(const void *X, int64_t N, int32_t d, int dtype, int m
     if (nq == 0) return RNND_OK;
     const size_t rowbytes = (size_t)d * dt_size(dtype);
     const int vec_ok = (rowbytes % 16 == 0) && (((uintptr_t)X) % 16 == 0) && (((uintptr_t)Q) % 16 == 0);
-    // one bitmap of N bits per wavefront in flight; at most 1 GiB of them, at most 8 wavefronts per SIMD
+    // few queries: a team of four wavefronts for each (rows of up to 128 bytes: one, which evaluates while the table answers),
+    // and the LDS is free for larger tables (fewer collisions)
+    const bool few = nq <= 4ll * cu_count();
+    // The table of evaluated vertices.  A query evaluates about 21 vertices per place of its candidate list, 27 with wide
+    // rows.  Few queries have the LDS for 4,096 slots, alone for 8,192.  Many queries at once need the wavefronts that the LDS of larger tables
+    // would cost (32 per CU without a table, 17 with 2,048 slots): a table must not get fuller than two thirds for rows of
+    // up to 128 bytes, which also do without where the bitmap is small (10,000 queries, L = 64, K = 32, 128-byte rows: 1M
+    // vertices 1.33 ms with the bitmap, 0.90 with the table; 32-byte rows, 200,000 vertices: 0.66 and 0.74), or seven
+    // eighths for longer ones (L = 90, K = 96, 1M vertices: 2.04 with the bitmap, 2.54 ms with a table that overflows).
+    const bool short_rows = vec_ok && rowbytes <= 128;
+    const u32 expect = (u32)((K > 40 ? 27 : 21) * L);
+    u32 slots = 512;
+    while (few ? slots < (short_rows && expect > 1792u ? 8192u : 4096u) : slots < expect) slots *= 2;
+    if (!few && (slots > 2048u || (short_rows && (expect > 1365u || N <= 262144)))) slots = 0;
+    const size_t q_bytes = ((dtype == RNND_U8 ? rowbytes : (size_t)d * 8) + 15) / 16 * 16;
+    const bool q_lds = (size_t)slots * 4 + q_bytes <= (60u << 10);
+    const int shape = (!vec_ok ? EVAL_SINGLE : rowbytes <= 128 ? EVAL_SHORT : rowbytes <= 512 ? EVAL_MID : EVAL_LONG) + (q_lds ? 0 : EVAL_GLOBAL);
+    const size_t dyn_lds = (size_t)slots * 4 + (q_lds ? q_bytes : 0);
+    // queries in flight: what the LDS of a CU holds, at most 8 wavefronts per SIMD; one bitmap of N bits each (for queries
+    // that outgrow the table), at most 1 GiB of them
     const size_t bitmap_words = (((size_t)N + 31) / 32 + 63) / 64 * 64;
-    long long waves = (long long)cu_count() * 32;
+    long long per_cu = (long long)((160u << 10) / (dyn_lds + sizeof(SearchSmem)));
+    if (per_cu > (few ? 8 : 32)) per_cu = few ? 8 : 32;
+    long long waves = (long long)cu_count() * per_cu;
     const long long by_mem = (long long)((1ull << 30) / (bitmap_words * 4));
     if (waves > by_mem) waves = by_mem;
     if (waves > nq) waves = nq;
+    if (waves > SEARCH_MAX_BLOCKS) waves = SEARCH_MAX_BLOCKS;
     if (waves < 1) waves = 1;
-    const unsigned blocks = (unsigned)((waves + 3) / 4);
-    const size_t bm_bytes = (size_t)blocks * 4 * bitmap_words * 4;
-    char *base = nullptr;
-    unsigned long long h_evals = 0;
+    const unsigned blocks = (unsigned)waves;
+    const size_t bm_bytes = (size_t)blocks * bitmap_words * 4;
+    unsigned long long *counts = nullptr;
     WsLease lease;
-    rc = ws_acquire(bm_bytes + 256, false, st, &lease);      // the block kept between calls, like the builds' workspace
+    rc = ws_acquire(bm_bytes, false, st, &lease);      // the block kept between calls, like the builds' workspace
     if (rc) return rc;
-    base = lease.base;
-    // the evaluation counter; the bitmaps are cleared by their wavefronts before every query
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, (u32 *)(base + bm_bytes), (size_t)64);
+    rc = counts_acquire(lease, &counts);
+    if (rc) {
+        ws_release(&lease);
+        return rc;
+    }
     {
-        u32 *bitmaps = (u32 *)base;
-        unsigned long long *d_evals = (unsigned long long *)(base + bm_bytes);
-#define RNND_SEARCH_LAUNCH(DT, E)                                                                            \
-    hipLaunchKernelGGL((k_search<DT, E>), dim3(blocks), dim3(256), 0, st, X, (long long)N, d, vec_ok, graph, \
-                       degree, row_stride, Q, (long long)nq, L, K, k, (u64)seed, bitmaps, bitmap_words,      \
-                       out_ids, out_dist_bits, d_evals)
-        if (dtype == RNND_U8) {
-            if (L <= 64) RNND_SEARCH_LAUNCH(DT_U8, 1); else RNND_SEARCH_LAUNCH(DT_U8, 2);
-        } else if (dtype == RNND_F16) {
-            if (L <= 64) RNND_SEARCH_LAUNCH(DT_F16, 1); else RNND_SEARCH_LAUNCH(DT_F16, 2);
-        } else if (dtype == RNND_BF16) {
-            if (L <= 64) RNND_SEARCH_LAUNCH(DT_BF16, 1); else RNND_SEARCH_LAUNCH(DT_BF16, 2);
-        } else {
-            if (L <= 64) RNND_SEARCH_LAUNCH(DT_F32, 1); else RNND_SEARCH_LAUNCH(DT_F32, 2);
-        }
+        // (the bitmaps are cleared by the queries that need them)
+        u32 *bitmaps = (u32 *)lease.base;
+#define RNND_SEARCH_TEAM(DT, E, SHAPE, TEAM)                                                                          \
+    hipLaunchKernelGGL((k_search<DT, E, SHAPE, TEAM>), dim3(blocks), dim3(64 * TEAM), dyn_lds, st, X, (long long)N, d, graph, \
+                       degree, row_stride, Q, (long long)nq, L, K, k, (u64)seed, bitmaps, bitmap_words, slots,        \
+                       out_ids, out_dist_bits, counts)
+#define RNND_SEARCH_ALONE(DT, E, SHAPE) RNND_SEARCH_TEAM(DT, E, SHAPE, 1)
+#define RNND_SEARCH_LAUNCH(DT, E, SHAPE)          \
+    if (few) RNND_SEARCH_TEAM(DT, E, SHAPE, 4);   \
+    else RNND_SEARCH_TEAM(DT, E, SHAPE, 1)
+#define RNND_SEARCH_E(DT, E)                                            \
+    if (shape == EVAL_SHORT) { RNND_SEARCH_ALONE(DT, E, EVAL_SHORT); }  \
+    else if (shape == EVAL_MID) { RNND_SEARCH_LAUNCH(DT, E, EVAL_MID); } \
+    else if (shape == EVAL_LONG) { RNND_SEARCH_LAUNCH(DT, E, EVAL_LONG); } \
+    else if (shape == EVAL_SINGLE) { RNND_SEARCH_LAUNCH(DT, E, EVAL_SINGLE); } \
+    else if (shape == EVAL_LONG_GLOBAL) { RNND_SEARCH_LAUNCH(DT, E, EVAL_LONG_GLOBAL); } \
+    else { RNND_SEARCH_LAUNCH(DT, E, EVAL_SINGLE_GLOBAL); }
+#define RNND_SEARCH_DT(DT)                \
+    if (L <= 64) { RNND_SEARCH_E(DT, 1) } \
+    else { RNND_SEARCH_E(DT, 2) }
+        if (dtype == RNND_U8) { RNND_SEARCH_DT(DT_U8) }
+        else if (dtype == RNND_F16) { RNND_SEARCH_DT(DT_F16) }
+        else if (dtype == RNND_BF16) { RNND_SEARCH_DT(DT_BF16) }
+        else { RNND_SEARCH_DT(DT_F32) }
+#undef RNND_SEARCH_DT
+#undef RNND_SEARCH_E
+#undef RNND_SEARCH_ALONE
+#undef RNND_SEARCH_TEAM
 #undef RNND_SEARCH_LAUNCH
         HIPCHK(hipGetLastError());
-        HIPCHK(hipMemcpyAsync(&h_evals, d_evals, sizeof h_evals, hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
-        if (dist_evals) *dist_evals = (int64_t)h_evals;
+        int64_t sum = 0;
+        for (unsigned b = 0; b < blocks; ++b) sum += (int64_t)counts[b];
+        if (dist_evals) *dist_evals = sum;
     }
 done:
     if (rc == RNND_ERR_HIP || rc == RNND_ERR_OOM) (void)hipStreamSynchronize(st);
+    counts_release(lease, counts);
     ws_release(&lease);
     return rc;
 }
