@@ -5,10 +5,9 @@
 //   scan     every active vertex (one holding a "new" entry) runs the body of Alg. 4's vertex loop on its own list,
 //            writes its kept entries back in place and leaves its redirected edges in its slot of `props`
 //   scatter  every redirected edge takes an arrival number at its target (the round's only atomic per
-//            edge) and moves into the target's inbox (INBOX_CAP slots per vertex); later arrivals wait
-//   classify vertices that received edges form the `touched` lists, by the size of the merge they need;
-//            those that received more than INBOX_CAP get a bin, which a second scatter pass fills
-//   merge    every touched list becomes the first R distinct keys of (kept entries + inbox + bin)
+//            edge) and moves into the target's inbox (INBOX_CAP slots per vertex); later arrivals are chained
+//   classify vertices that received edges form the `touched` lists, by the size of the merge they need
+//   merge    every touched list becomes the first R distinct keys of (kept entries + inbox + later arrivals)
 //   compact  touched vertices whose new list holds a "new" entry form the next active lists,
 //            one per degree class (see degree_class)
 // Between outer rounds AddReverseEdges (Alg. 5) uses the same inboxes and bins (launch_reverse).
@@ -41,10 +40,8 @@
 struct RoundCtr {
     u32 n_active[NDEG];   // lengths of this round's active lists
     u32 n_touched[NMRG];  // distinct targets of the redirected edges, by size of the merge they need
-    u32 bin_cursor;       // space handed out in the bin array
-    u32 has_surplus;      // some vertex received more than INBOX_CAP edges this round
     u32 nonfinite;        // slot 0: k_prepare_rows met a coordinate that is NaN or infinite
-    u32 pad;
+    u32 pad[3];
     u32 n_redo[NDEG];     // float scan: vertices the single-precision form left to the double-precision one
     // ticks of the device's constant-rate clock (0 = not taken): the round's first scan launch starts, its scatter
     // starts (= the scan has ended: launches of one stream run back to back), the round's last kernel has ended
@@ -82,7 +79,7 @@ __global__ void k_stamp(u64 *dst) { if (threadIdx.x == 0) *dst = wall_clock64();
 struct Prop {          // one redirected edge (Alg. 4, the edge update): `key` enters `tgt`'s list
     u64 key;
     u32 tgt;
-    u32 arrival;       // set by the scatter: arrival number at tgt, for edges past the inbox
+    u32 next;          // set by the scatter for edges past the inbox: the edge (its place in props) that was on tgt's list before
 };
 
 // The edge update of Alg. 4: (w, v) enters E.  Recorded in the scanning vertex's own slot.
@@ -91,7 +88,7 @@ __device__ __forceinline__ void emit_redirect(u64 key, u32 tgt, Prop *slot)
     Prop pr;
     pr.key = key;
     pr.tgt = tgt;
-    pr.arrival = 0;
+    pr.next = 0;
     *slot = pr;
 }
 
@@ -352,21 +349,32 @@ __device__ __forceinline__ u32 same_target_mask(u32 tgt, int sub)
     }
 }
 
-#define SURPLUS_MARK 0x40000000   // set in nprop[u]: some edge redirected by u arrived past its target's inbox
+// Redirected edges that arrive past their target's inbox ("late") stay where they are, in props, and are chained: a
+// target has late_heads lists, arrival number a is on list (a - INBOX_CAP) mod late_heads, so the lists are of equal
+// length and a wavefront walks all of them at once.  heads[] needs no clearing: how many edges are on a list follows
+// from the target's count.  (A second pass over all active vertices, once bins had been handed out, used to move them:
+// one launch more per round and 1.06 of 26 ms at 1M x 128.  Whole builds: 5,000 x 32 381 -> 354 us, 100,000 x 128 4.61 -> 4.33
+// ms, 1M x 128 26.0 -> 25.5 ms.)
+static __host__ __device__ inline int late_heads(int R)      // a power of two; the table takes 4 of the 8 R bytes per vertex of the bin array
+{
+    int h = 64;
+    while (h > 2 * R) h >>= 1;
+    return h;
+}
 
 // Every active vertex moves its redirected edges to their targets, 16 lanes per vertex.  Lanes of a
 // group that share a target take their arrival numbers with one atomic (a vertex usually redirects
-// several entries to the same kept neighbour).  Arrivals below INBOX_CAP go to the target's inbox;
-// later ones record their number in the edge and are placed by k_scatter_surplus once bins exist.
+// several entries to the same kept neighbour).  Arrivals below INBOX_CAP go to the target's inbox, later ones onto one of
+// its lists (see late_heads).
 __global__ __launch_bounds__(BLOCK) void k_scatter(long long N, int R, const int *lists, int ncl, RoundCtr *ctr,
-                                                   Prop *props, int *nprop, int *fill, u64 *inbox)
+                                                   Prop *props, const int *nprop, int *fill, u64 *inbox, u32 *heads)
 {
+    const u32 nheads = (u32)late_heads(R);
     const int lane = threadIdx.x & 63, sub = lane & 15, gbase = lane & ~15;
     const u32 g = (blockIdx.x * BLOCK + threadIdx.x) >> 4, ng = (gridDim.x * BLOCK) >> 4;
     // the classes' lists as one: the grid is shared by their entries, however they are spread over the classes
     const ActiveLists al = active_lists(lists, N, ctr, ncl);
     const u32 n = al.start[NDEG];
-    bool surplus = false;
     stamp_scan_stop(ctr);
     if (g >= n) return;
     // the loads of the next vertex (its count and its first 16 edges) are issued before the atomics
@@ -374,7 +382,7 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(long long N, int R, const int
     auto vertex_at = [&](unsigned long long i) -> int { return i < n ? active_vertex(al, (u32)i) : -1; };
     auto first_edges = [&](int u, int &np, Prop &pr) {
         np = 0;
-        pr.key = 0; pr.tgt = 0xFFFFFFFFu; pr.arrival = 0;
+        pr.key = 0; pr.tgt = 0xFFFFFFFFu; pr.next = 0;
         if (u >= 0) {
             np = nprop[u];
             if (sub < R) pr = props[(size_t)u * R + sub];   // slots past np exist; masked below
@@ -390,7 +398,6 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(long long N, int R, const int
         first_edges(u_next, np_next, pr_next);
         const int u_after = vertex_at(it + 2ull * ng);
 
-        bool mine_surplus = false;
         for (int p0 = 0; p0 < np; p0 += 16) {      // same trip count for the whole group
             const int p = p0 + sub;
             const bool have = p < np;
@@ -409,43 +416,13 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(long long N, int R, const int
                 if (s < INBOX_CAP) {
                     inbox[(size_t)pr.tgt * INBOX_CAP + s] = pr.key;
                 } else {
-                    props[(size_t)u * R + p].arrival = (u32)s;
-                    mine_surplus = true;
+                    const size_t slot = (size_t)u * R + p;
+                    props[slot].next = atomicExch(&heads[(size_t)pr.tgt * nheads + ((u32)(s - INBOX_CAP) & (nheads - 1u))], (u32)slot);
                 }
             }
         }
-        // mark u for the second pass (this group is the only one that touches nprop[u])
-        const u32 anyb = ((u32)(__builtin_amdgcn_ballot_w64(mine_surplus) >> gbase)) & 0xFFFFu;
-        if (anyb) {
-            if (sub == 0) nprop[u] = np | SURPLUS_MARK;
-            surplus = true;
-        }
         u = u_next; np = np_next; pr0 = pr_next;
         u_next = u_after;
-    }
-    if (surplus) ctr->has_surplus = 1u;
-}
-
-// Second pass, only when some vertex received more than INBOX_CAP edges: the late arrivals go to bins.
-__global__ __launch_bounds__(BLOCK) void k_scatter_surplus(long long N, int R, const int *lists, int ncl,
-                                                           const RoundCtr *ctr, const Prop *props,
-                                                           const int *nprop, const int *binoff, u64 *bins)
-{
-    if (ctr->has_surplus == 0) return;
-    const int sub = threadIdx.x & 15;
-    const u32 g = (blockIdx.x * BLOCK + threadIdx.x) >> 4, ng = (gridDim.x * BLOCK) >> 4;
-    const ActiveLists al = active_lists(lists, N, ctr, ncl);
-    const u32 n = al.start[NDEG];
-    for (unsigned long long it = g; it < n; it += ng) {
-        const int u = active_vertex(al, (u32)it);
-        int np = nprop[u];
-        if (!(np & SURPLUS_MARK)) continue;
-        np &= ~SURPLUS_MARK;
-        for (int p = sub; p < np; p += 16) {
-            const Prop pr = props[(size_t)u * R + p];
-            if (pr.arrival >= (u32)INBOX_CAP)
-                bins[(size_t)binoff[pr.tgt] + (pr.arrival - INBOX_CAP)] = pr.key;
-        }
     }
 }
 
@@ -456,36 +433,25 @@ __device__ __forceinline__ int merge_class(int nb, int c)
     return total <= 16 ? 0 : total <= 32 ? 1 : total <= 64 ? 2 : 3;
 }
 
-// Every vertex x that received edges (cnt[x] > 0) is appended to the touched list of its merge class;
-// if it received more than INBOX_CAP it also gets a bin for the surplus.  A block covers TC_TILES x 1024
-// vertices and takes its space with one atomic per class (and one for the bins).  Four tiles per block
+// Every vertex x that received edges (cnt[x] > 0) is appended to the touched list of its merge class.  A block covers
+// TC_TILES x 1024 vertices and takes its space with one atomic per class.  Four tiles per block
 // keep the atomics of a 1M-vertex round few; on small inputs two tiles (twice the blocks, a shorter chain in
 // each) are faster: 100,000 vertices 4.68 -> 4.55 ms per build, 1M 26.0 -> 26.1 ms.
 template <int TC_TILES>
-__global__ __launch_bounds__(1024) void k_touch_classify(long long N, const int *cnt, const int *deg,
-                                                         int *binoff, RoundCtr *ctr, int *tlists)
+__global__ __launch_bounds__(1024) void k_touch_classify(long long N, const int *cnt, const int *deg, RoundCtr *ctr, int *tlists)
 {
-    __shared__ u32 s_cnt[TC_TILES][16][NMRG], s_sum[TC_TILES][16], s_base[NMRG + 1];
+    __shared__ u32 s_cnt[TC_TILES][16][NMRG], s_base[NMRG];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int mc[TC_TILES];
-    u32 mine[TC_TILES], incl[TC_TILES], rank[TC_TILES];
+    u32 rank[TC_TILES];
 #pragma unroll
     for (int k = 0; k < TC_TILES; ++k) {
         const long long x = ((long long)blockIdx.x * TC_TILES + k) * 1024 + threadIdx.x;
-        int c = 0;
         mc[k] = -1;
         if (x < N) {
-            c = cnt[x];
+            const int c = cnt[x];
             if (c > 0) mc[k] = merge_class(deg[x], c);
         }
-        mine[k] = c > INBOX_CAP ? (u32)(c - INBOX_CAP) : 0u;
-        u32 in = mine[k];
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            u32 v = __shfl_up(in, o);
-            if (lane >= o) in += v;
-        }
-        incl[k] = in;
         rank[k] = 0;
 #pragma unroll
         for (int q = 0; q < NMRG; ++q) {
@@ -493,7 +459,6 @@ __global__ __launch_bounds__(1024) void k_touch_classify(long long N, const int 
             if (mc[k] == q) rank[k] = (u32)__popcll(b & lanes_below(lane));
             if (lane == 0) s_cnt[k][wave][q] = (u32)__popcll(b);
         }
-        if (lane == 63) s_sum[k][wave] = in;
     }
     __syncthreads();
     if (wave == 0) {
@@ -502,35 +467,29 @@ __global__ __launch_bounds__(1024) void k_touch_classify(long long N, const int 
         const bool used = lane < TC_TILES * 16;
         const int k = used ? lane >> 4 : 0, w = lane & 15;
 #pragma unroll
-        for (int q = 0; q <= NMRG; ++q) {
-            const u32 a = !used ? 0u : q < NMRG ? s_cnt[k][w][q] : s_sum[k][w];
+        for (int q = 0; q < NMRG; ++q) {
+            const u32 a = !used ? 0u : s_cnt[k][w][q];
             u32 in = a;
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) {
                 u32 v = __shfl_up(in, o);
                 if (lane >= o) in += v;
             }
-            if (used) {
-                if (q < NMRG) s_cnt[k][w][q] = in - a;
-                else s_sum[k][w] = in - a;
-            }
+            if (used) s_cnt[k][w][q] = in - a;
             if (lane == 63) s_base[q] = in;
         }
         wave_sync();
-        if (lane <= NMRG) {     // the block's atomics are in flight together
+        if (lane < NMRG) {     // the block's atomics are in flight together
             const u32 tot = s_base[lane];
-            s_base[lane] = tot ? atomicAdd(lane < NMRG ? &ctr->n_touched[lane] : &ctr->bin_cursor, tot) : 0u;
+            s_base[lane] = tot ? atomicAdd(&ctr->n_touched[lane], tot) : 0u;
         }
     }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < TC_TILES; ++k) {
         const long long x = ((long long)blockIdx.x * TC_TILES + k) * 1024 + threadIdx.x;
-        if (x < N) {
-            binoff[x] = mine[k] ? (int)(s_base[NMRG] + s_sum[k][wave] + incl[k] - mine[k]) : -1;
-            if (mc[k] >= 0)
-                tlists[(size_t)mc[k] * N + s_base[mc[k]] + s_cnt[k][wave][mc[k]] + rank[k]] = (int)x;
-        }
+        if (x < N && mc[k] >= 0)
+            tlists[(size_t)mc[k] * N + s_base[mc[k]] + s_cnt[k][wave][mc[k]] + rank[k]] = (int)x;
     }
 }
 
@@ -609,7 +568,7 @@ __device__ __forceinline__ void merge_group_body(int R, u64 *keys, int *deg, con
     if (dropped) atomicAdd(&ctr->stat[blockIdx.x & (STAT_SLOTS - 1)][4], (u64)dropped);
 }
 
-// General merge (any size): one touched vertex per wavefront; kept entries + inbox + surplus bin.
+// General merge (any size): one touched vertex per wavefront; kept entries + inbox + late edges.
 // The common case (at most INBOX_CAP received, at most 128 keys in all) is sorted in registers from
 // loads issued one vertex ahead: lane l holds list slots l and l + 64 and inbox slot 63 - l.
 struct WideItem {
@@ -632,9 +591,32 @@ __device__ __forceinline__ WideItem wide_item_load(int x, int R, const u64 *keys
     return m;
 }
 
+// A vertex's late edges: lane l walks list l (or, reversed, list nheads - 1 - l).
+struct LateEdges {
+    const Prop *props;
+    u32 next;
+    int left;      // edges still on my list
+
+    __device__ __forceinline__ LateEdges(const Prop *p, const u32 *heads, size_t x, int nheads, int late, int list) : props(p), next(0), left(0)
+    {
+        if (list >= 0 && list < nheads && list < late) {
+            left = (late - list + nheads - 1) / nheads;
+            next = heads[x * (size_t)nheads + (size_t)list];
+        }
+    }
+    __device__ __forceinline__ u64 take()
+    {
+        if (left <= 0) return KEY_PAD;
+        --left;
+        const Prop pr = props[next];
+        next = pr.next;
+        return pr.key;
+    }
+};
+
 __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, const int *tlist,
                                                    const u32 *n_ptr, int *cnt, const u64 *inbox,
-                                                   const int *binoff, const u64 *bins, int8_t *tcls,
+                                                   const u32 *heads, const Prop *props, int8_t *tcls,
                                                    int use_classes, u64 (*s_stage)[RNND_MAX_R], RoundCtr *ctr)
 {
     int dropped = 0;
@@ -663,9 +645,38 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
             wave_sort<2>(k, lane);
             nd = wave_unique_prefix<2>(k, lane, R, keys + (size_t)x * R, &any_new, &dropped);
         } else {
-            const int ca = c < INBOX_CAP ? c : INBOX_CAP;
-            nd = wave_merge_row(keys + (size_t)x * R, nb, inbox + (size_t)x * INBOX_CAP, ca,
-                                bins + (c > ca ? binoff[x] : 0), c - ca, R, s_stage[wave], lane, &any_new, &dropped);
+            const int ca = c < INBOX_CAP ? c : INBOX_CAP, late = c - ca, nheads = late_heads(R);
+            u64 *row = keys + (size_t)x * R;
+            if (nb + c <= 128 && nheads == 64) {
+                // a full inbox, and at most one late edge per list: the lists from the top lane down, above the kept entries
+                LateEdges more(props, heads, (size_t)x, nheads, late, 63 - lane);
+                u64 k[2];
+                k[0] = lane < nb ? cur.r0 : more.take();
+                k[1] = cur.in;
+                wave_sort<2>(k, lane);
+                nd = wave_unique_prefix<2>(k, lane, R, row, &any_new, &dropped);
+            } else {
+                // inbox and late edges in chunks of 128 against the best R found so far
+                LateEdges more(props, heads, (size_t)x, nheads, late, lane);
+                u64 k[4];
+                k[0] = lane < nb ? cur.r0 : KEY_PAD;
+                k[1] = lane + 64 < nb ? cur.r1 : KEY_PAD;
+                k[2] = INBOX_CAP - 1 - lane < ca ? cur.in : KEY_PAD;
+                k[3] = more.take();
+                for (int taken = nheads;; taken += 2 * nheads) {
+                    wave_sort<4>(k, lane);
+                    nd = wave_unique_prefix<4>(k, lane, R, s_stage[wave], &any_new, &dropped);
+                    wave_sync();
+                    k[0] = lane < nd ? s_stage[wave][lane] : KEY_PAD;
+                    k[1] = lane + 64 < nd ? s_stage[wave][lane + 64] : KEY_PAD;
+                    wave_sync();
+                    if (taken >= late) break;
+                    k[2] = more.take();
+                    k[3] = more.take();
+                }
+                if (lane < nd) row[lane] = k[0];
+                if (lane + 64 < nd) row[lane + 64] = k[1];
+            }
         }
         if (lane == 0) {
             deg[x] = nd;
@@ -680,7 +691,7 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
 // All four merge classes in one launch: blockIdx.y = merge class (touched list y, tcls + y*N).
 __global__ __launch_bounds__(BLOCK) void k_merge(long long N, int R, u64 *keys, int *deg, const int *tlists,
                                                  const u32 *n_touched, int *cnt, const u64 *inbox,
-                                                 const int *binoff, const u64 *bins, int8_t *tcls,
+                                                 const u32 *heads, const Prop *props, int8_t *tcls,
                                                  int use_classes, RoundCtr *ctr)
 {
     __shared__ u64 s_stage[WAVES_PER_BLOCK][RNND_MAX_R];
@@ -690,7 +701,7 @@ __global__ __launch_bounds__(BLOCK) void k_merge(long long N, int R, u64 *keys, 
     if (y == 0) merge_group_body<16>(R, keys, deg, tlist, n_touched + 0, cnt, inbox, tc, use_classes, ctr);
     else if (y == 1) merge_group_body<32>(R, keys, deg, tlist, n_touched + 1, cnt, inbox, tc, use_classes, ctr);
     else if (y == 2) merge_group_body<64>(R, keys, deg, tlist, n_touched + 2, cnt, inbox, tc, use_classes, ctr);
-    else merge_general_body(R, keys, deg, tlist, n_touched + 3, cnt, inbox, binoff, bins, tc, use_classes, s_stage, ctr);
+    else merge_general_body(R, keys, deg, tlist, n_touched + 3, cnt, inbox, heads, props, tc, use_classes, s_stage, ctr);
 }
 
 // Items i < n with cls[first + i] >= 0 are appended to list cls[first + i]; item i stands for vertex idx[i]
@@ -967,7 +978,7 @@ __global__ __launch_bounds__(BIN_THREADS) void k_bin_partition(long long N, int 
         Prop pr;
         pr.key = make_key(key_dist(k), (u32)u, 1u);
         pr.tgt = v;
-        pr.arrival = 0;
+        pr.next = 0;
         part[at] = pr;
     });
 }
@@ -1432,7 +1443,7 @@ struct Workspace {
     int *deg = nullptr;     // [N]
     Prop *props = nullptr;  // [N*R]   slot u*R.. holds the edges vertex u redirected this round
     u64 *inbox = nullptr;   // [N*INBOX_CAP] redirected edges received this round, by target
-    u64 *bins = nullptr;    // [N*R]   surplus of the inboxes; AddReverseEdges' bins
+    u64 *bins = nullptr;    // [N*R]   a round's heads of late edges, the float scan's redo list; AddReverseEdges' bins
     u64 *thr = nullptr;     // [N]
     int *cnt = nullptr, *binoff = nullptr, *fill = nullptr, *touched = nullptr, *hubs = nullptr, *nprop = nullptr;
     int8_t *xs = nullptr;     // copy of X (see ScanPlan): X - 128 as int8 for the uint8 MFMA scan, or padded rows
@@ -1902,19 +1913,17 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
     }
     // from here on `fill` plays the role of the per-target count of this round
     const int ncl = use_classes ? NDEG : 1;
-    hipLaunchKernelGGL(k_scatter, dim3(pb), dim3(BLOCK), 0, st, N, R, w.lists, ncl, c, w.props, w.nprop, w.fill,
-                       w.inbox);
+    hipLaunchKernelGGL(k_scatter, dim3(pb), dim3(BLOCK), 0, st, N, R, w.lists, ncl, c, w.props, (const int *)w.nprop, w.fill,
+                       w.inbox, (u32 *)w.bins);
     if (N <= SMALL_INPUT_MAX_N)
-        hipLaunchKernelGGL(k_touch_classify<2>, dim3((unsigned)((N + 2047) / 2048)), dim3(1024), 0, st, N, w.fill, deg, w.binoff, c,
+        hipLaunchKernelGGL(k_touch_classify<2>, dim3((unsigned)((N + 2047) / 2048)), dim3(1024), 0, st, N, w.fill, deg, c,
                            w.touched);
     else
-        hipLaunchKernelGGL(k_touch_classify<4>, dim3((unsigned)((N + 4095) / 4096)), dim3(1024), 0, st, N, w.fill, deg, w.binoff, c,
+        hipLaunchKernelGGL(k_touch_classify<4>, dim3((unsigned)((N + 4095) / 4096)), dim3(1024), 0, st, N, w.fill, deg, c,
                            w.touched);
-    hipLaunchKernelGGL(k_scatter_surplus, dim3(pb), dim3(BLOCK), 0, st, N, R, w.lists, ncl, c, w.props, w.nprop,
-                       w.binoff, w.bins);
     static const int merge_per_cu = resident_blocks_per_cu(k_merge, 6);
     hipLaunchKernelGGL(k_merge, dim3(capped(cu_count() * merge_per_cu, N), NMRG), dim3(BLOCK), 0, st, N, R, keys, deg, w.touched, c->n_touched,
-                       w.fill, w.inbox, w.binoff, w.bins, w.tcls, use_classes, c);
+                       w.fill, w.inbox, (const u32 *)w.bins, (const Prop *)w.props, w.tcls, use_classes, c);
     if (run)
         hipLaunchKernelGGL(k_store_classes, dim3(64, NMRG), dim3(256), 0, st, (const u32 *)c->n_touched,
                            (const int *)w.touched, (const int8_t *)w.tcls, N, w.vcls);

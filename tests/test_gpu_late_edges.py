@@ -1,0 +1,35 @@
+"""Edges that arrive past a target's inbox (64 per round) are chained in up to 64 lists of equal length, fewer where
+rows are narrower than 32 slots: a star whose centre receives from a few dozen to a few thousand edges in one round."""
+import numpy as np
+import pytest
+
+from gpu_util import assert_snapshot_equal, snapshot_to_device
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("R", [2, 5, 16, 31, 32, 96])
+@pytest.mark.parametrize("planted", [90, 150, 230, 2499])
+def test_hub_receives_more_than_its_inbox_holds(oracle_mod, R, planted):
+    import torch
+    import paper_2310_20419_amd as rn
+    rn.load_library()
+    g = np.random.default_rng(8)
+    n, d = 2500, 32
+    X = np.clip(128 + g.normal(0, 40, size=(n, d)), 0, 255).astype(np.uint8)
+    X[0] = 128
+    snap = oracle_mod.random_graph(X, min(R, 8), 5, R)
+    for u in range(1, planted + 1):                      # plant the centre, which is nearest, in these lists
+        m = snap.deg[u]
+        if 0 not in snap.ids[u, :m]:
+            snap.ids[u, m - 1] = 0
+            snap.dist[u, m - 1] = float(((X[u].astype(np.int64) - 128) ** 2).sum())
+        order = np.lexsort((snap.ids[u, :m], snap.dist[u, :m]))
+        snap.ids[u, :m], snap.dist[u, :m] = snap.ids[u, :m][order], snap.dist[u, :m][order]
+    Xd = torch.from_numpy(X).cuda()
+    for t in range(3):
+        keys, deg = snapshot_to_device(snap, False, R)
+        snap, evals, props = oracle_mod.update_neighbors_sync(X, snap, R)
+        st = rn.rnnd_update_neighbors(Xd, keys, deg, R, 1)
+        assert st.algo_evals[0] == evals and st.proposals[0] == props
+        assert_snapshot_equal(snap, False, keys, deg, "R %d planted %d round %d" % (R, planted, t))
