@@ -149,8 +149,8 @@ int rnnd_update_neighbors_blocks(const void *X, int64_t N, int32_t d, int dtype,
  * room for it; without room it does with the bytes reported here, slower. */
 int rnnd_workspace_bytes(int64_t N, int32_t d, int dtype, int32_t R, int64_t rounds, size_t *bytes);
 
-/* Frees the workspace block the library keeps on the current device between calls (no-op if there is none
- * or a call is using it). */
+/* Frees the workspace block (and the small pinned buffer of rnnd_search) the library keeps on the current device
+ * between calls (no-op if there is none or a call is using it). */
 int rnnd_release_workspace(void);
 
 /* rnnd_build for callers that cannot allocate device memory (code that runs under HIP graph capture
@@ -225,7 +225,7 @@ int rnnd_export_graph(int64_t N, int32_t R, const uint64_t *keys, const int32_t 
  *              uint8 data, the float's bit pattern for float32); 0xFFFFFFFF where out_ids is -1.
  *   dist_evals host, or NULL: number of delta(q, .) evaluations over all queries.
  * Work is enqueued on `stream` and the call returns after it has completed; a bitmap of N bits per
- * wavefront in flight (at most 1 GiB in all) lives in the workspace block the library keeps between calls
+ * query in flight (at most 1 GiB in all) lives in the workspace block the library keeps between calls
  * (see rnnd_workspace_bytes).  Caller keeps ownership of every buffer.  Errors as for rnnd_build (RNND_ERR_BAD_PARAM for L, K, k, row_stride). */
 int rnnd_search(const void *X, int64_t N, int32_t d, int dtype, int metric, const int32_t *graph,
                 const int32_t *degree, int32_t row_stride, const void *Q, int64_t nq, int32_t L,
