@@ -94,6 +94,7 @@ __device__ __forceinline__ void emit_redirect(u64 key, u32 tgt, Prop *slot)
 
 #include "dist.h"
 #include "scan_mfma.h"
+#include "scan_pairs.h"
 #include "scan_mfma_f32.h"
 #include "search.h"
 
@@ -157,10 +158,7 @@ __global__ __launch_bounds__(BLOCK) void k_random_graph(const void *X, long long
 }
 
 // ------------------------------------------------- UpdateNeighbors: scan (generic kernel)
-// The body of Alg. 4's vertex loop for one vertex per wavefront, in the algorithm's own order: v runs over the
-// sorted list; the kept set U' so far is a bit mask; the delta(v,w) of up to 8 eligible w (kept,
-// not old/old) are evaluated at once by 8-lane groups in ascending w, and the first failing one
-// prunes v and redirects it.  Kept entries are written back in place with the flag cleared.
+// The body of Alg. 4's vertex loop (scan_vertex_pairs) for one vertex per wavefront.
 template <int DT>
 __global__ __launch_bounds__(BLOCK) void k_update_scan(const void *X, int d, int vec_ok, int R,
                                                        u64 *keys, int *deg, const int *list,
@@ -170,11 +168,9 @@ __global__ __launch_bounds__(BLOCK) void k_update_scan(const void *X, int d, int
     __shared__ u64 s_key[WAVES_PER_BLOCK][RNND_MAX_R];
     __shared__ u64 s_pkey[WAVES_PER_BLOCK][RNND_MAX_R];
     __shared__ u32 s_ptgt[WAVES_PER_BLOCK][RNND_MAX_R];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, sub = lane & 7, grp = lane >> 3;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const u32 gw = blockIdx.x * WAVES_PER_BLOCK + wave, nw = gridDim.x * WAVES_PER_BLOCK;
     const u32 n_active = *n_list;
-    const size_t rowbytes = (size_t)d * dt_size(DT);
-    u64 *sk = s_key[wave];
     stamp_scan_start(ctr);
     u64 evals_algo = 0, evals_exec = 0, rows = 0, nprops_total = 0;
     for (u32 it = gw; it < n_active; it += nw) {
@@ -184,73 +180,10 @@ __global__ __launch_bounds__(BLOCK) void k_update_scan(const void *X, int d, int
         u64 *row = keys + (size_t)u * R;
         u64 k0 = lane < m ? row[lane] : KEY_PAD;
         u64 k1 = lane + 64 < m ? row[lane + 64] : KEY_PAD;
-        wave_sync();
-        sk[lane] = k0;
-        sk[lane + 64] = k1;
-        const u64 new0 = __builtin_amdgcn_ballot_w64(lane < m && (k0 & 1ull));
-        const u64 new1 = __builtin_amdgcn_ballot_w64(lane + 64 < m && (k1 & 1ull));
-        wave_sync();
-        if ((new0 | new1) == 0) {
-            if (lane == 0) nprop[u] = 0;
-            continue;
-        }
+        const int np = scan_vertex_pairs<DT>(X, d, vec_ok, R, u, m, k0, k1, row, deg, props, nprop, s_key[wave], s_pkey[wave], s_ptgt[wave],
+                                             lane, evals_algo, evals_exec);
+        if (np < 0) continue;
         rows += m;
-        u64 K0 = 0, K1 = 0;   // U' as positions in the sorted list
-        int np = 0;
-        for (int i = 0; i < m; ++i) {
-            const u64 ki = sk[i];
-            const u32 di = key_dist(ki), idv = key_id(ki);
-            const bool newv = ki & 1ull;
-            u64 e0 = newv ? K0 : (K0 & new0);   // old/old pairs are skipped
-            u64 e1 = newv ? K1 : (K1 & new1);
-            bool pruned = false;
-            const char *xv = (const char *)X + (size_t)idv * rowbytes;
-            while ((e0 | e1) != 0 && !pruned) {
-                int mypos = -1, nb = 0;
-#pragma unroll
-                for (int g = 0; g < 8; ++g) {
-                    int p = -1;
-                    if (e0) { p = __builtin_ctzll(e0); e0 &= e0 - 1; }
-                    else if (e1) { p = 64 + __builtin_ctzll(e1); e1 &= e1 - 1; }
-                    if (p >= 0) ++nb;
-                    if (grp == g) mypos = p;
-                }
-                const u32 idw = key_id(sk[mypos >= 0 ? mypos : 0]);
-                u32 db = 0;
-                if (mypos >= 0)
-                    db = group8_dist_bits<DT>(xv, (const char *)X + (size_t)idw * rowbytes, d, vec_ok, sub);
-                const bool fail = mypos >= 0 && di >= db;   // the prune test
-                const u64 fm = __builtin_amdgcn_ballot_w64(fail && sub == 0);
-                if (fm) {
-                    const int fl = __builtin_ctzll(fm);     // first failing w in list order
-                    const u32 fdb = __shfl(db, fl), fidw = __shfl(idw, fl);
-                    if (lane == 0) {                        // the edge update: (u,v) leaves, (w,v) enters
-                        s_pkey[wave][np] = make_key(fdb, idv, 1u);
-                        s_ptgt[wave][np] = fidw;
-                    }
-                    ++np;
-                    evals_algo += (fl >> 3) + 1;
-                    pruned = true;
-                } else {
-                    evals_algo += nb;
-                }
-                evals_exec += nb;
-            }
-            if (!pruned) {
-                if (i < 64) K0 |= 1ull << i; else K1 |= 1ull << (i - 64);   // v joins U'
-            }
-        }
-        // kept entries, flag old, compacted back into the row
-        const int nk0 = __popcll(K0);
-        if ((K0 >> lane) & 1ull) row[__popcll(K0 & lanes_below(lane))] = k0 & ~1ull;
-        if ((K1 >> lane) & 1ull) row[nk0 + __popcll(K1 & lanes_below(lane))] = k1 & ~1ull;
-        if (lane == 0) {
-            deg[u] = nk0 + __popcll(K1);
-            nprop[u] = np;
-        }
-        wave_sync();
-        for (int p = lane; p < np; p += 64)
-            emit_redirect(s_pkey[wave][p], s_ptgt[wave][p], props + (size_t)u * R + p);
         nprops_total += np;
     }
     if (lane == 0 && rows) add_round_stats(ctr, evals_algo, evals_exec, rows, nprops_total);

@@ -5,12 +5,12 @@
 // floats of row l%16 of every group, widens them to double, and for each of the 4 it feeds
 // v_mfma_f64_16x16x4_f64 for every needed 16x16 tile (I >= J) of the Gram block G = A A^T.  The A and B
 // operand of a tile come from the same loads with the same lane -> dimension mapping, so the products
-// pair up whatever that mapping is.  Products of floats are exact in double, so with n_i = sum_k x_ik^2
-//     delta(v_i, v_j) ~= float(n_i + n_j - 2 G_ij)
-// differs from the reference value (double accumulation of (a-b)^2, rounded once) only when the two
-// doubles straddle a rounding boundary of float, about 1e-8 of the time; it is used for the DECISION of
-// the prune test only.  Every distance that is STORED (the delta(v,w) of a redirected edge) is recomputed by
-// the one routine all stored distances come from (dist.h), so equal edges always carry equal keys.
+// pair up whatever that mapping is.  With n_i = sum_k x_ik^2
+//     delta(v_i, v_j) ~= n_i + n_j - 2 G_ij ,
+// which loses as many leading digits as the distance is smaller than the norms.  It is used for the DECISION of the
+// prune test only, and only where its error bound leaves no doubt; the other pairs are decided by the one routine all
+// stored distances come from (dist.h).  Every distance that is STORED (the delta(v,w) of a redirected edge) comes from
+// that routine, so equal edges always carry equal keys.
 //
 // Alg. 4 never tests two old entries against each other (the old/old skip), so only pairs with a new member need a
 // distance.  The list is therefore laid out in SLOTS: its new entries first, then its old ones, each in
@@ -26,12 +26,14 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "scan_pairs.h"
 #include "wave_prims.h"
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-#define F32_AMB_CAP 256   // pairs of one vertex that the single-precision form may leave undecided
+#define F32_AMB_CAP 256   // pairs of one vertex that the single-precision form may leave undecided; that the other resolves at a time
+#define F64_AMB_PER_ROW 12   // pairs per list entry that the double-precision form may leave undecided
 
 template <int NRC>
 struct alignas(16) F32ScanSmem {
@@ -300,8 +302,17 @@ __device__ __forceinline__ int popc_below_w(u64 m0, u64 m1, int p)
 // of delta(v,w) to float on either side (delta <= 2 (n_i + n_j)); the few undecided pairs get the exact
 // delta(v,w) from the routine every stored distance comes from, so the decisions are those of the
 // reference arithmetic.  A vertex with more than F32_AMB_CAP undecided pairs (ties in bulk: duplicates,
-// lattices) is left untouched and appended to `redo`, which the double-precision form (FAST = false)
-// takes afterwards.
+// lattices; rows far from the origin) is left untouched and appended to `redo`, which the double-precision form
+// (FAST = false) takes afterwards.
+// The double-precision form decides in the same way: its block is off by at most (1.01 d + d / 4 + 6) 2^-53 (n_i + n_j)
+// (products of floats are exact in double), the double that the exact routine rounds by (d / 8 + 6) 2^-53 delta, hence
+// E_ij = (2 d + 24) 2^-53 (n_i + n_j).  Rounding to float is monotone, so delta(v,w) as a float lies between those of the
+// block's value -/+ E_ij; what delta(u,v) does not decide against both goes to the exact routine.  A vertex with more than
+// F64_AMB_PER_ROW such pairs per list entry (rows so far out that no block helps) is scanned pair by pair, which evaluates
+// only what the outcome depends on, one entry after the other: 20,000 x 100 of unit variance, 8 rounds, around 10^7 17.2 ms
+// with every pair resolved, 8.2 pair by pair, around 10^6 (few pairs each) 4.6 and 7.0.
+// (Without the bound 8,319 of 20,000 lists differed from the exact decisions for 100 coordinates of unit variance around
+// 10^6, 6,889 where every row occurs 100 times.)
 // FAST with 16-bit rows: the block comes from v_mfma_f32_16x16x32_{f16,bf16} on the rows as stored (exact
 // products), norms included (diagonals of the diagonal tiles).  One instruction sums 32 products and the
 // accumulator; taking its error as at most 8 x 2^-24 of the sum of their magnitudes (an in-bounds probe
@@ -322,6 +333,7 @@ __device__ __forceinline__ void f32_scan_body(
     constexpr bool NATIVE16 = FAST && (DT == DT_F16 || DT == DT_BF16);
     const double epsk = NATIVE16 ? (0.5 * (double)d + 20.0) * 5.9604644775390625e-08
                                  : (1.5 * (double)d + 20.0) * 5.9604644775390625e-08;
+    const double epsk64 = (2.0 * (double)d + 24.0) * 1.1102230246251565e-16;      // double-precision form
     constexpr int NT = NRC * (NRC + 1) / 2;
     constexpr int NWD = (NRC + 1) / 2;        // 32-bit words of a mask over slots
     constexpr int NSET = NRC > 4 ? 2 : 1;     // lane (r16, q) owns rows 16 q + r16 and, if NRC > 4, 64 + 16 q + r16
@@ -331,7 +343,7 @@ __device__ __forceinline__ void f32_scan_body(
     const u32 gw = block * 4 + wave, nw = nblocks * 4;
     const u32 rowbytes = (u32)d * (u32)dt_size(DT);     // at most a few hundred KB
     const int nchunk = (int)(rowbytes / (64u * CH));
-    u64 tiles = 0, rows = 0, nprops_total = 0;
+    u64 tiles = 0, rows = 0, nprops_total = 0, pair_evals = 0;
     u32 ev_lane = 0;
 
     if (gw >= n_active) return;
@@ -509,11 +521,13 @@ __device__ __forceinline__ void f32_scan_body(
                             for (int v = 0; v < 4; ++v) {
                                 const int rsel = 4 * v + q;
                                 const int si = 16 * I + rsel;
-                                const double dvwd = sm.nrm[si] + nr[J] - 2.0 * (double)acc[t][v];
-                                const float dvw = (float)dvwd;
+                                const double nsum = sm.nrm[si] + nr[J], dvw = nsum - 2.0 * (double)acc[t][v];
+                                const float lo = (float)(dvw - epsk64 * nsum), hi = (float)(dvw + epsk64 * nsum);
                                 const float di = __uint_as_float(key_dist(sm.key[si]));
-                                fa |= (di >= dvw) ? (1u << rsel) : 0u;
-                                fb |= (dj >= dvw) ? (1u << rsel) : 0u;
+                                fa |= (di >= hi) ? (1u << rsel) : 0u;
+                                fa |= !(di >= hi || di < lo) ? (0x10000u << rsel) : 0u;      // also when not a number
+                                fb |= (dj >= hi) ? (1u << rsel) : 0u;
+                                fb |= !(dj >= hi || dj < lo) ? (0x10000u << rsel) : 0u;
                             }
                         }
                         if constexpr (FAST) {
@@ -521,12 +535,12 @@ __device__ __forceinline__ void f32_scan_body(
                         } else {
                             fa |= (u32)__shfl_xor((int)fa, 16);
                             fa |= (u32)__shfl_xor((int)fa, 32);
-                            FA[t] = transpose16_bits(fa, lane);
+                            FA[t] = transpose16_bits(fa & 0xFFFFu, lane) | (transpose16_bits(fa >> 16, lane) << 16);
                         }
                         if (I != J) {
                             fb |= (u32)__shfl_xor((int)fb, 16);
                             fb |= (u32)__shfl_xor((int)fb, 32);
-                            FB[t] = FAST ? fb : (fb & 0xFFFFu);
+                            FB[t] = fb;
                         }
                     }
                 }
@@ -566,14 +580,14 @@ __device__ __forceinline__ void f32_scan_body(
                     const u32 bnew = range_word(0, a, c), bold = range_word(n_new, n_new + b, c);
                     Bw[e][c] = bnew | bold;
                     Ew[e][c] = valid[e] ? (snew ? (bnew | bold) : bnew) : 0u;
-                    Aw[e][c] = FAST ? (wa & Ew[e][c]) : 0u;
+                    Aw[e][c] = wa & Ew[e][c];
                     Fw[e][c] = w & Ew[e][c] & ~Aw[e][c];
                 }
             }
 
-            // ---- single precision only: the undecided pairs get the exact delta(v,w)
+            // ---- the undecided pairs get the exact delta(v,w)
             bool defer = false;
-            if (FAST) {
+            {
                 int mine = 0;
 #pragma unroll
                 for (int e = 0; e < NSET; ++e)
@@ -588,12 +602,23 @@ __device__ __forceinline__ void f32_scan_body(
                     }
                     total = __shfl(incl, 63);
                 }
-                if (total > F32_AMB_CAP) {
+                if (total > (FAST ? F32_AMB_CAP : F64_AMB_PER_ROW * m)) {
                     defer = true;
-                    if (lane == 0) redo[atomicAdd(n_redo, 1u)] = u;
-                } else if (total > 0) {
+                    if (FAST) {
+                        if (lane == 0) redo[atomicAdd(n_redo, 1u)] = u;
+                    } else {
+                        u64 ea = 0, ee = 0;
+                        nprops_total += scan_vertex_pairs<DT>(X, d, 1, R, u, m, kreg[0], kreg[1], row, deg, props, nprop, sm.key,
+                                                              (u64 *)sm.nrm, sm.pv, lane, ea, ee);
+                        ev_lane += lane == 0 ? (u32)ea : 0u;
+                        pair_evals += ee;
+                    }
+                    total = 0;
+                }
+                for (int first = 0; first < total; first += F32_AMB_CAP) {      // (single precision: once)
+                    const int now = FAST ? total : (total - first < F32_AMB_CAP ? total - first : F32_AMB_CAP);
                     wave_sync();
-                    int o = incl - mine;
+                    int o = incl - mine - first;
 #pragma unroll
                     for (int e = 0; e < NSET; ++e) {
                         const int s = 16 * (4 * e + q) + r16;
@@ -603,14 +628,15 @@ __device__ __forceinline__ void f32_scan_body(
                             while (bits) {
                                 const int b = __builtin_ctz(bits);
                                 bits &= bits - 1u;
-                                sm.amb[o++] = (uint16_t)((s << 8) | (32 * c + b));
+                                if (FAST || (u32)o < (u32)F32_AMB_CAP) sm.amb[o] = (uint16_t)((s << 8) | (32 * c + b));
+                                ++o;
                             }
                         }
                     }
                     wave_sync();
-                    for (int base = 0; base < total; base += 8) {
+                    for (int base = 0; base < now; base += 8) {
                         const int p = base + grp;
-                        const bool have = p < total;
+                        const bool have = p < now;
                         const u32 pair = sm.amb[have ? p : 0];
                         const u32 sv0 = (pair >> 8) & 0x7Fu, sw0 = pair & 0xFFu;
                         const u32 sv = sv0 < 16u * NRC ? sv0 : 0u, sw = sw0 < 16u * NRC ? sw0 : 0u;
@@ -618,12 +644,13 @@ __device__ __forceinline__ void f32_scan_body(
                         u32 db = 0;
                         if (have) db = group8_dist_bits<DT>(X + (size_t)idv * rowbytes, X + (size_t)idw * rowbytes, d, 1, sub);
                         if (have && sub == 0) {
-                            const bool fails = __uint_as_float(key_dist(sm.key[sv])) >= __uint_as_float(db);
+                            // as bits, like the pair-at-a-time kernel: the same order for numbers, a defined one for NaN
+                            const bool fails = key_dist(sm.key[sv]) >= db;
                             sm.amb[p] = (uint16_t)(pair | (fails ? 0x8000u : 0u));
                         }
                     }
                     wave_sync();
-                    o = incl - mine;
+                    o = incl - mine - first;
 #pragma unroll
                     for (int e = 0; e < NSET; ++e)
 #pragma unroll
@@ -632,9 +659,11 @@ __device__ __forceinline__ void f32_scan_body(
                             while (bits) {
                                 const int b = __builtin_ctz(bits);
                                 bits &= bits - 1u;
-                                if (sm.amb[o++] & 0x8000u) Fw[e][c] |= 1u << b;
+                                if ((FAST || (u32)o < (u32)F32_AMB_CAP) && (sm.amb[o] & 0x8000u)) Fw[e][c] |= 1u << b;
+                                ++o;
                             }
                         }
+                    if (FAST) break;
                 }
             }
             if (!defer) {
@@ -751,7 +780,7 @@ __device__ __forceinline__ void f32_scan_body(
     u64 evals_algo = ev_lane;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) evals_algo += shfl_xor_u64(evals_algo, o);
-    if (lane == 0 && rows) add_round_stats(ctr, evals_algo, tiles * 256ull, rows, nprops_total);
+    if (lane == 0 && rows) add_round_stats(ctr, evals_algo, tiles * 256ull + pair_evals, rows, nprops_total);
 }
 
 // The double-precision form over one list: the redo list, or (kernel variant 2) the active list of a degree class.
