@@ -1,6 +1,6 @@
 """Rows on which the prune test of the float scan is delicate: far from the origin every Gram-form distance loses its
-leading digits, copies of a row differ by nothing at all.  The matrix-core scans (automatic, and in double precision throughout)
-must take the decisions the pair-at-a-time kernel takes: the same graphs, the same stored distances, the same counts."""
+leading digits, copies of a row differ by nothing at all, very small coordinates have squares that single precision cannot
+hold.  The matrix-core scans (automatic, and in double precision throughout) must take the decisions the pair-at-a-time kernel takes: the same graphs, the same stored distances, the same counts."""
 import numpy as np
 import pytest
 
@@ -23,6 +23,8 @@ def _rows(kind, d, seed):
     X = (g.normal(size=(8, d))[g.integers(0, 8, size=N)] + 0.5 * g.normal(size=(N, d))).astype(np.float32)
     if kind.startswith("centre"):
         X = X + np.float32(kind.split()[1])
+    elif kind.startswith("scale"):
+        X = X * np.float32(kind.split()[1])
     elif kind == "copies":                        # 24 rows, 100 times each
         X = X[g.permutation(np.repeat(np.arange(24), N // 24))]
     elif kind == "zeros":                         # half the rows are the origin
@@ -32,6 +34,8 @@ def _rows(kind, d, seed):
 
 FAR = [("f32", k, d) for k in ("centre 1e3", "centre 1e5", "centre 1e6", "centre 1e7", "copies", "zeros") for d in (96, 100, 33)] + \
       [(t, k, d) for t in ("f16", "bf16") for k in ("centre 200", "copies") for d in (64, 100)]
+SMALL = [("f32", k, d) for k in ("scale 1e-19", "scale 1e-20", "scale 1e-21", "scale 1e-22", "scale 1e-23", "scale 1e-38") for d in (96, 100)] + \
+        [("bf16", k, d) for k in ("scale 1e-20", "scale 1e-22", "scale 1e-23") for d in (64, 100)] + [("f16", "scale 1e-4", 64)]
 
 
 def _compare(rn, X, S, R, T1, T2, seed, label):
@@ -64,4 +68,11 @@ def _device(X, dtype):
 def test_rows_far_from_the_origin_and_copies(rn, dtype, kind, d):
     X = _device(_rows(kind, d, 7), dtype)
     for S, R in ((20, 96), (40, 128), (10, 24)):
+        _compare(rn, X, S, R, 2, 3, 5, "%s %s d %d R %d" % (dtype, kind, d, R))
+
+
+@pytest.mark.parametrize("dtype,kind,d", SMALL)
+def test_squares_too_small_for_single_precision(rn, dtype, kind, d):
+    X = _device(_rows(kind, d, 7), dtype)
+    for S, R in ((20, 96), (10, 24)):
         _compare(rn, X, S, R, 2, 3, 5, "%s %s d %d R %d" % (dtype, kind, d, R))
