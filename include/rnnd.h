@@ -143,14 +143,15 @@ int rnnd_update_neighbors_blocks(const void *X, int64_t N, int32_t d, int dtype,
 /* Bytes of device workspace a build of `rounds` = T1 * T2 UpdateNeighbors rounds (times the runs per pass for
  * rnnd_build_blocks; at most 131072) needs for these sizes (an upper bound; for rnnd_build_wide pass M as R).
  * The library allocates it at the first call that needs it and keeps it, per device, for later calls (a
- * larger request replaces it); rnnd_release_workspace hands it back.  Where the matrix-core scan needs rows of another
- * length than X has (see rnnd_set_kernel_variant), a call also keeps a padded copy of X in the block -- N rows of d
- * coordinates rounded up to a multiple of 128 bytes (uint8: to 32, 64, 128 or a multiple of 64) -- if the device has
- * room for it; without room it does with the bytes reported here, slower. */
+ * larger request replaces it); rnnd_release_workspace hands it back.  Not counted here: where the matrix-core scan needs
+ * rows of another length than X has (see rnnd_set_kernel_variant), a call also keeps a padded copy of X in a block of its
+ * own -- N rows of d coordinates rounded up to a multiple of 128 bytes (uint8: to 32, 64, 128 or a multiple of 64) -- if the
+ * device has room for it.  Without room the call works on X itself, slower; the copy's block is given up where the
+ * workspace itself could not be had otherwise. */
 int rnnd_workspace_bytes(int64_t N, int32_t d, int dtype, int32_t R, int64_t rounds, size_t *bytes);
 
-/* Frees the workspace block (and the small pinned buffer of rnnd_search) the library keeps on the current device
- * between calls (no-op if there is none or a call is using it). */
+/* Frees the workspace block, the block for padded rows and the small pinned buffer of rnnd_search that the library keeps
+ * on the current device between calls (no-op if there is none or a call is using them). */
 int rnnd_release_workspace(void);
 
 /* rnnd_build for callers that cannot allocate device memory (code that runs under HIP graph capture

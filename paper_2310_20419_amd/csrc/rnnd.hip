@@ -1983,6 +1983,8 @@ static void fill_round_stats(rnnd_stats *s, const RoundCtr *h, int rounds)
 //    when a later call needs more, handed back by rnnd_release_workspace): repeated builds pay no allocation;
 // 2. a fresh allocation, freed when the call ends, if another thread's call holds that block;
 // 3. for rnnd_build_static only: the file-scope array below, which needs no allocation at all.
+// The padded copy of X has a block of its own (1. and 2.), because a call can do without it: asking for it must not cost
+// the block the call cannot do without, and it is the first to go when that block cannot be had.
 #define RNND_MAX_DEVICES 64
 #define SEARCH_MAX_BLOCKS 16384     // queries a search has in flight at most
 
@@ -1991,7 +1993,9 @@ static __device__ __align__(256) unsigned char scratch[RNND_STATIC_SCRATCH_BYTES
 struct DeviceSlot {
     char *cached = nullptr;        // the kept block
     size_t cached_bytes = 0;
-    bool busy = false;             // a call is using it
+    char *copy = nullptr;          // the kept block for padded rows
+    size_t copy_bytes = 0;
+    bool busy = false;             // a call is using them
     char *static_ptr = nullptr;    // this device's copy of `scratch` (hipGetSymbolAddress, once per device)
     unsigned long long *counts = nullptr;   // pinned host memory, kept like the block: SEARCH_MAX_BLOCKS evaluation counts
 };
@@ -2001,7 +2005,7 @@ static int g_poison = 0;           // testing aid: every workspace is filled wit
 
 enum WsSource { WS_NONE = 0, WS_CACHED, WS_FRESH, WS_STATIC };
 struct WsLease {
-    char *base = nullptr;
+    char *base = nullptr, *copy = nullptr;
     int dev = -1;
     WsSource src = WS_NONE;
 };
@@ -2043,7 +2047,14 @@ static int ws_acquire(size_t bytes, bool static_only, hipStream_t st, WsLease *o
                 d.cached_bytes = 0;
             }
             if (!d.cached) {
-                HIPCHK(hipMalloc((void **)&d.cached, bytes));
+                if (d.copy && hipMalloc((void **)&d.cached, bytes) != hipSuccess) {
+                    (void)hipGetLastError();
+                    d.cached = nullptr;
+                    (void)hipFree(d.copy);
+                    d.copy = nullptr;
+                    d.copy_bytes = 0;
+                }
+                if (!d.cached) HIPCHK(hipMalloc((void **)&d.cached, bytes));
                 d.cached_bytes = bytes;
             }
             d.busy = true;
@@ -2060,21 +2071,47 @@ done:
     return rc;
 }
 
+// A block for padded rows next to the one the lease holds; false where there is no room for it.
+static bool ws_acquire_copy(WsLease *l, size_t bytes, hipStream_t st)
+{
+    if (bytes > RNND_WS_HARD_LIMIT) return false;
+    if (l->src == WS_CACHED) {
+        std::lock_guard<std::mutex> lock(g_ws_mu);
+        DeviceSlot &d = g_dev[l->dev];       // busy: no other call touches the slot's blocks
+        if (d.copy_bytes < bytes) {
+            if (d.copy) (void)hipFree(d.copy);
+            d.copy = nullptr;
+            d.copy_bytes = 0;
+            if (hipMalloc((void **)&d.copy, bytes) != hipSuccess) d.copy = nullptr;
+            else d.copy_bytes = bytes;
+        }
+        l->copy = d.copy;
+    } else if (hipMalloc((void **)&l->copy, bytes) != hipSuccess) {
+        l->copy = nullptr;
+    }
+    if (!l->copy) (void)hipGetLastError();      // not an error of the call
+    else if (g_poison) hipLaunchKernelGGL(k_fill_u32, dim3(2048), dim3(256), 0, st, (u32 *)l->copy, bytes / 4, 0xA5A5A5A5u);
+    return l->copy != nullptr;
+}
+
 // Lays out and acquires the workspace of a build or of UpdateNeighbors calls.  Where there is no room for the padded
-// copy of X the plan does without it.
+// copy of X the plan does without it.  (The static array holds the copy as well, if it is large enough.)
 static int ws_open(Workspace &w, WsLease *lease, ScanPlan &plan, const void *X, long long N, int R, int d, int dtype, int n_ctr,
                    bool own_graph, bool static_only, hipStream_t st)
 {
-    w.bytes = ws_layout(w, N, R, n_ctr, own_graph, plan.copy_bytes);
+    const bool apart = plan.extra() && !static_only;
+    w.bytes = ws_layout(w, N, R, n_ctr, own_graph, apart ? 0 : plan.copy_bytes);
     int rc = ws_acquire(w.bytes, static_only, st, lease);
-    if ((rc == RNND_ERR_OOM || rc == RNND_ERR_SCRATCH) && plan.extra()) {
-        plan = scan_plan_for(X, N, d, dtype, false);
+    const bool no_copy = rc ? rc == RNND_ERR_SCRATCH && plan.extra() : apart && !ws_acquire_copy(lease, plan.copy_bytes, st);
+    if (no_copy) plan = scan_plan_for(X, N, d, dtype, false);
+    if (no_copy && rc) {
         w.bytes = ws_layout(w, N, R, n_ctr, own_graph, plan.copy_bytes);
         rc = ws_acquire(w.bytes, static_only, st, lease);
     }
     if (rc) return rc;
     w.base = lease->base;
-    ws_layout(w, N, R, n_ctr, own_graph, plan.copy_bytes);
+    ws_layout(w, N, R, n_ctr, own_graph, apart ? 0 : plan.copy_bytes);
+    if (lease->copy) w.xs = (int8_t *)lease->copy;
     return RNND_OK;
 }
 
@@ -2082,12 +2119,13 @@ static void ws_release(WsLease *l)
 {
     if (l->src == WS_FRESH) {
         (void)hipFree(l->base);
+        if (l->copy) (void)hipFree(l->copy);
     } else if (l->src == WS_CACHED) {
         std::lock_guard<std::mutex> lock(g_ws_mu);
         g_dev[l->dev].busy = false;
     }
     l->src = WS_NONE;
-    l->base = nullptr;
+    l->base = l->copy = nullptr;
 }
 
 extern "C" int rnnd_release_workspace(void)
@@ -2101,6 +2139,11 @@ extern "C" int rnnd_release_workspace(void)
             HIPCHK(hipFree(d.cached));
             d.cached = nullptr;
             d.cached_bytes = 0;
+        }
+        if (d.copy && !d.busy) {
+            HIPCHK(hipFree(d.copy));
+            d.copy = nullptr;
+            d.copy_bytes = 0;
         }
         if (d.counts && !d.busy) {
             HIPCHK(hipHostFree(d.counts));
@@ -2144,7 +2187,7 @@ extern "C" int rnnd_workspace_bytes(int64_t N, int32_t d, int dtype, int32_t R, 
     if (N < 2 || N > 2147483646LL || d < 1) return RNND_ERR_BAD_SHAPE;
     if (R < 1 || R > RNND_MAX_R || rounds < 1 || rounds > RNND_MAX_RUN_SLOTS) return RNND_ERR_BAD_PARAM;
     Workspace w;
-    // upper bound: the int8 copy exists only for uint8 rows of 32, 64 or 128 bytes
+    // what no call can do without: the int8 copy of uint8 rows of 32, 64 or 128 bytes, but no padded copy (see ScanPlan)
     *bytes = ws_layout(w, N, R, (int)rounds + 2, true,
                        (dtype == RNND_U8 && (d == 32 || d == 64 || d == 128)) ? (size_t)N * d : 0);
     return RNND_OK;
