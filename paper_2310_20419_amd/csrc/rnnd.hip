@@ -2572,18 +2572,32 @@ extern "C" int rnnd_search(const void *X, int64_t N, int32_t d, int dtype, int m
     // few queries: a team of four wavefronts for each (rows of up to 128 bytes: one, which evaluates while the table answers),
     // and the LDS is free for larger tables (fewer collisions)
     const bool few = nq <= 4ll * cu_count();
-    // The table of evaluated vertices.  A query evaluates about 21 vertices per place of its candidate list, 27 with wide
-    // rows.  Few queries have the LDS for 4,096 slots, alone for 8,192.  Many queries at once need the wavefronts that the LDS of larger tables
-    // would cost (32 per CU without a table, 17 with 2,048 slots): a table must not get fuller than two thirds for rows of
-    // up to 128 bytes, which also do without where the bitmap is small (10,000 queries, L = 64, K = 32, 128-byte rows: 1M
-    // vertices 1.33 ms with the bitmap, 0.90 with the table; 32-byte rows, 200,000 vertices: 0.66 and 0.74), or seven
-    // eighths for longer ones (L = 90, K = 96, 1M vertices: 2.04 with the bitmap, 2.54 ms with a table that overflows).
+    // The table of evaluated vertices takes LDS that wavefronts need, holds 7/8 of its slots - 64 vertices (384, 832, 1,728,
+    // 3,520; see SeenSet) and costs most when it overflows: then the bitmap has to be cleared all the same.  A query evaluates
+    // about 300 vertices + 12 per place of its candidate list, 15 with wide rows (K > 40); on rows of up to 128 bytes 20 and 28 (100,000
+    // to 1M vertices, eight kinds of rows).  Few queries have the LDS for 4,096 slots, alone for 8,192.  The others:
+    //   rounds of queries   the smallest table that holds what is expected: 10,000 queries on 1M x 128 uint8, K = 32, bitmap
+    //     follow each other / 1,024 / 2,048 / 4,096 slots: L = 16 (571 evaluated) 728 / 314 / 333 / 408 us, L = 24 (717) 841 /
+    //                       490 / 408 / 477, L = 64 (1,348) 1,313 / 1,845 / 887 / 993, L = 90 (1,711) 1,629 / 2,148 / 1,516 / 1,404, L = 128
+    //                       (2,196) 2,029 / 2,603 / 2,526 / 1,914; beyond 1,728 expected the bitmap alone, as 4,096 slots are
+    //                       twice as slow on rows of 384 bytes (300,000 x 96 float32, L = 90: 1,345 / 1,623 / 1,027 / 2,249).  Rows of
+    //                       more than 128 bytes have fewer wavefronts per CU anyway: 2,048 slots at least (L = 32: 656 / 472 / 437).
+    //                       Short rows of a small index, whose bitmaps stay in cache: 200,000 x 128 uint8, L = 16 296 / 253 / 283,
+    //                       L = 64 (1,049) 763 / 946 / 778, L = 90 961 / 1,278 / 1,144: bitmap beyond 1,024 slots
+    //   all at once         as many slots, up to 4,096, as leave all queries resident: 1,500 queries, 1M x 128, L = 64 bitmap / 2,048
+    //                       / 4,096: 322 / 370 / 266 us, L = 128 523 / 716 / 471; 1M x 32 uint8, L = 90 (2,225) 320 / 467 / 311, L = 128
+    //                       (3,003) 414 / 683 / 435; 4,000 queries, 1M x 128, L = 16 349 / 171 / 221 (1,024 slots 224)
     const bool short_rows = vec_ok && rowbytes <= 128;
-    const u32 expect = (u32)((K > 40 ? 27 : 21) * L);
-    u32 slots = 512;
-    while (few ? slots < (short_rows && expect > 1792u ? 8192u : 4096u) : slots < expect) slots *= 2;
-    if (!few && (slots > 2048u || (short_rows && (expect > 1365u || N <= 262144)))) slots = 0;
+    const u32 expect = 300u + (u32)L * (short_rows ? (K > 40 ? 28u : 20u) : (K > 40 ? 15u : 12u));
     const size_t q_bytes = ((dtype == RNND_U8 ? rowbytes : (size_t)d * 8) + 15) / 16 * 16;
+    auto all_resident = [&](u32 sl) { return (size_t)((nq + cu_count() - 1) / cu_count()) * (sl * 4 + q_bytes + sizeof(SearchSmem)) <= (160u << 10); };
+    u32 slots;
+    if (few) slots = short_rows && expect > 2000u ? 8192u : 4096u;
+    else if (expect <= 2400u && all_resident(4096u)) slots = 4096u;
+    else if (expect <= 1728u && all_resident(2048u)) slots = 2048u;
+    else if ((short_rows || !vec_ok) && expect <= 700u) slots = 1024u;
+    else if (short_rows && N <= 262144) slots = 0;
+    else slots = expect <= 1728u ? 2048u : 0u;
     const bool q_lds = (size_t)slots * 4 + q_bytes <= (60u << 10);
     const int shape = (!vec_ok ? EVAL_SINGLE : rowbytes <= 128 ? EVAL_SHORT : rowbytes <= 512 ? EVAL_MID : EVAL_LONG) + (q_lds ? 0 : EVAL_GLOBAL);
     const size_t dyn_lds = (size_t)slots * 4 + (q_lds ? q_bytes : 0);
