@@ -5,7 +5,7 @@
 //   scan     every active vertex (one holding a "new" entry) runs the body of Alg. 4's vertex loop on its own list,
 //            writes its kept entries back in place and leaves its redirected edges in its slot of `props`
 //   scatter  every redirected edge takes an arrival number at its target (the round's only atomic per
-//            edge) and moves into the target's inbox (INBOX_CAP slots per vertex); later arrivals are chained
+//            edge) and moves into the target's inbox (up to INBOX_CAP slots per vertex); later arrivals are chained
 //   classify vertices that received edges form the `touched` lists, by the size of the merge they need
 //   merge    every touched list becomes the first R distinct keys of (kept entries + inbox + later arrivals)
 //   compact  touched vertices whose new list holds a "new" entry form the next active lists,
@@ -283,26 +283,39 @@ __device__ __forceinline__ u32 same_target_mask(u32 tgt, int sub)
 }
 
 // Redirected edges that arrive past their target's inbox ("late") stay where they are, in props, and are chained: a
-// target has late_heads lists, arrival number a is on list (a - INBOX_CAP) mod late_heads, so the lists are of equal
-// length and a wavefront walks all of them at once.  heads[] needs no clearing: how many edges are on a list follows
-// from the target's count.  (A second pass over all active vertices, once bins had been handed out, used to move them:
-// one launch more per round and 1.06 of 26 ms at 1M x 128.  Whole builds: 5,000 x 32 381 -> 354 us, 100,000 x 128 4.61 -> 4.33
-// ms, 1M x 128 26.0 -> 25.5 ms.)
-static __host__ __device__ inline int late_heads(int R)      // a power of two; the table takes 4 of the 8 R bytes per vertex of the bin array
+// target has LATE_LISTS lists, arrival number a is on list (a - inbox) mod LATE_LISTS, so the lists are of equal
+// length and a wavefront walks all of them at once.  The heads need no clearing: how many edges are on a list follows
+// from the target's count.  They lie in the bin array (8 R bytes per vertex, 4 LATE_LISTS needed); rows of fewer than 32
+// slots have no room for them there and receive fewer edges, so they use 32 of their 64 inbox slots and keep the heads in the
+// other 32.  (A second pass over all active vertices, once bins had been handed out, used to move them: one launch more
+// per round and 1.06 of 26 ms at 1M x 128.  Whole builds: 5,000 x 32 381 -> 354 us, 100,000 x 128 4.61 -> 4.33
+// ms, 1M x 128 26.0 -> 25.5 ms.  A round in which one vertex receives 700,000 edges, second pass / as many lists as fit 4 R
+// bytes / now: rows of 8 slots 19.5 / 78.6 / 19.7 ms, of 16 19.5 / 40.4 / 19.7, of 96 19.5 / 20.8 / 19.8, the last because the links
+// of a chunk are asked for while the one before it is sorted; 7,000 edges, 8 slots: 0.29 / 0.87 / 0.28.)
+#define LATE_LISTS 64
+static __host__ __device__ inline int round_inbox(int R) { return R < 32 ? 32 : INBOX_CAP; }
+
+// list head l of vertex x is at [x * stride + l]
+struct LateHeads {
+    u32 *base;
+    u32 stride;
+};
+static __host__ __device__ inline LateHeads late_heads(u64 *inbox, u64 *bins, int R)
 {
-    int h = 64;
-    while (h > 2 * R) h >>= 1;
+    LateHeads h;
+    h.base = R < 32 ? (u32 *)(inbox + 32) : (u32 *)bins;
+    h.stride = R < 32 ? 2u * INBOX_CAP : (u32)LATE_LISTS;
     return h;
 }
 
 // Every active vertex moves its redirected edges to their targets, 16 lanes per vertex.  Lanes of a
 // group that share a target take their arrival numbers with one atomic (a vertex usually redirects
-// several entries to the same kept neighbour).  Arrivals below INBOX_CAP go to the target's inbox, later ones onto one of
-// its lists (see late_heads).
+// several entries to the same kept neighbour).  Arrivals below round_inbox(R) go to the target's inbox, later ones onto
+// one of its lists (see LATE_LISTS).
 __global__ __launch_bounds__(BLOCK) void k_scatter(long long N, int R, const int *lists, int ncl, RoundCtr *ctr,
-                                                   Prop *props, const int *nprop, int *fill, u64 *inbox, u32 *heads)
+                                                   Prop *props, const int *nprop, int *fill, u64 *inbox, LateHeads heads)
 {
-    const u32 nheads = (u32)late_heads(R);
+    const int cap = round_inbox(R);
     const int lane = threadIdx.x & 63, sub = lane & 15, gbase = lane & ~15;
     const u32 g = (blockIdx.x * BLOCK + threadIdx.x) >> 4, ng = (gridDim.x * BLOCK) >> 4;
     // the classes' lists as one: the grid is shared by their entries, however they are spread over the classes
@@ -346,11 +359,11 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(long long N, int R, const int
             base = __shfl(base, gbase + leader);
             if (have) {
                 const int s = base + rank;
-                if (s < INBOX_CAP) {
+                if (s < cap) {
                     inbox[(size_t)pr.tgt * INBOX_CAP + s] = pr.key;
                 } else {
                     const size_t slot = (size_t)u * R + p;
-                    props[slot].next = atomicExch(&heads[(size_t)pr.tgt * nheads + ((u32)(s - INBOX_CAP) & (nheads - 1u))], (u32)slot);
+                    props[slot].next = atomicExch(&heads.base[(size_t)pr.tgt * heads.stride + ((u32)(s - cap) & (LATE_LISTS - 1u))], (u32)slot);
                 }
             }
         }
@@ -359,11 +372,12 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(long long N, int R, const int
     }
 }
 
-// Merge class of a vertex that holds nb entries and received c: how wide a sort its merge needs.
-__device__ __forceinline__ int merge_class(int nb, int c)
+// Merge class of a vertex that holds nb entries and received c: how wide a sort its merge needs.  cap = round_inbox(R):
+// the first three read received edges from the inbox only.
+__device__ __forceinline__ int merge_class(int nb, int c, int cap)
 {
     const int total = nb + c;
-    return total <= 16 ? 0 : total <= 32 ? 1 : total <= 64 ? 2 : 3;
+    return c > cap ? 3 : total <= 16 ? 0 : total <= 32 ? 1 : total <= 64 ? 2 : 3;
 }
 
 // Every vertex x that received edges (cnt[x] > 0) is appended to the touched list of its merge class.  A block covers
@@ -371,7 +385,7 @@ __device__ __forceinline__ int merge_class(int nb, int c)
 // keep the atomics of a 1M-vertex round few; on small inputs two tiles (twice the blocks, a shorter chain in
 // each) are faster: 100,000 vertices 4.68 -> 4.55 ms per build, 1M 26.0 -> 26.1 ms.
 template <int TC_TILES>
-__global__ __launch_bounds__(1024) void k_touch_classify(long long N, const int *cnt, const int *deg, RoundCtr *ctr, int *tlists)
+__global__ __launch_bounds__(1024) void k_touch_classify(long long N, int cap, const int *cnt, const int *deg, RoundCtr *ctr, int *tlists)
 {
     __shared__ u32 s_cnt[TC_TILES][16][NMRG], s_base[NMRG];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -383,7 +397,7 @@ __global__ __launch_bounds__(1024) void k_touch_classify(long long N, const int 
         mc[k] = -1;
         if (x < N) {
             const int c = cnt[x];
-            if (c > 0) mc[k] = merge_class(deg[x], c);
+            if (c > 0) mc[k] = merge_class(deg[x], c, cap);
         }
         rank[k] = 0;
 #pragma unroll
@@ -502,7 +516,7 @@ __device__ __forceinline__ void merge_group_body(int R, u64 *keys, int *deg, con
 }
 
 // General merge (any size): one touched vertex per wavefront; kept entries + inbox + late edges.
-// The common case (at most INBOX_CAP received, at most 128 keys in all) is sorted in registers from
+// The common case (no late edges, at most 128 keys in all) is sorted in registers from
 // loads issued one vertex ahead: lane l holds list slots l and l + 64 and inbox slot 63 - l.
 struct WideItem {
     int x, nb, c;
@@ -524,36 +538,31 @@ __device__ __forceinline__ WideItem wide_item_load(int x, int R, const u64 *keys
     return m;
 }
 
-// A vertex's late edges: lane l walks list l (or, reversed, list nheads - 1 - l).
-struct LateEdges {
-    const Prop *props;
+// The edge at props[at] of one of a vertex's late lists (see LATE_LISTS), if there is one.
+struct LateEdge {
+    u64 key;
     u32 next;
-    int left;      // edges still on my list
-
-    __device__ __forceinline__ LateEdges(const Prop *p, const u32 *heads, size_t x, int nheads, int late, int list) : props(p), next(0), left(0)
-    {
-        if (list >= 0 && list < nheads && list < late) {
-            left = (late - list + nheads - 1) / nheads;
-            next = heads[x * (size_t)nheads + (size_t)list];
-        }
-    }
-    __device__ __forceinline__ u64 take()
-    {
-        if (left <= 0) return KEY_PAD;
-        --left;
-        const Prop pr = props[next];
-        next = pr.next;
-        return pr.key;
-    }
 };
+__device__ __forceinline__ LateEdge late_edge(const Prop *props, u32 at, bool have)
+{
+    LateEdge e;
+    e.key = KEY_PAD;
+    e.next = 0;
+    if (have) {
+        e.key = props[at].key;
+        e.next = props[at].next;
+    }
+    return e;
+}
 
 __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, const int *tlist,
                                                    const u32 *n_ptr, int *cnt, const u64 *inbox,
-                                                   const u32 *heads, const Prop *props, int8_t *tcls,
+                                                   LateHeads heads, const Prop *props, int8_t *tcls,
                                                    int use_classes, u64 (*s_stage)[RNND_MAX_R], RoundCtr *ctr)
 {
     int dropped = 0;
-    static_assert(INBOX_CAP == 64, "lane l prefetches inbox slot 63 - l");
+    static_assert(INBOX_CAP == 64 && LATE_LISTS == 64, "lane l prefetches inbox slot 63 - l and walks list l");
+    const int cap = round_inbox(R);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const u32 gw = blockIdx.x * WAVES_PER_BLOCK + wave, nw = gridDim.x * WAVES_PER_BLOCK;
     const u32 n = *n_ptr;
@@ -571,41 +580,45 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
         const int nb = __builtin_amdgcn_readfirstlane(cur.nb), c = __builtin_amdgcn_readfirstlane(cur.c);
         bool any_new = false;
         int nd;
-        if (c <= INBOX_CAP && nb + c <= 128) {
+        if (c <= cap && nb + c <= 128) {
             u64 k[2];
             k[0] = lane < nb ? cur.r0 : KEY_PAD;
             k[1] = lane + 64 < nb ? cur.r1 : (63 - lane < c ? cur.in : KEY_PAD);
             wave_sort<2>(k, lane);
             nd = wave_unique_prefix<2>(k, lane, R, keys + (size_t)x * R, &any_new, &dropped);
         } else {
-            const int ca = c < INBOX_CAP ? c : INBOX_CAP, late = c - ca, nheads = late_heads(R);
+            const int ca = c < cap ? c : cap, late = c - ca;
+            const u32 *head = heads.base + (size_t)x * heads.stride;
             u64 *row = keys + (size_t)x * R;
-            if (nb + c <= 128 && nheads == 64) {
+            if (nb + late <= 64) {
                 // a full inbox, and at most one late edge per list: the lists from the top lane down, above the kept entries
-                LateEdges more(props, heads, (size_t)x, nheads, late, 63 - lane);
                 u64 k[2];
-                k[0] = lane < nb ? cur.r0 : more.take();
-                k[1] = cur.in;
+                k[0] = lane < nb ? cur.r0 : late_edge(props, 63 - lane < late ? head[63 - lane] : 0u, 63 - lane < late).key;
+                k[1] = 63 - lane < ca ? cur.in : KEY_PAD;
                 wave_sort<2>(k, lane);
                 nd = wave_unique_prefix<2>(k, lane, R, row, &any_new, &dropped);
             } else {
-                // inbox and late edges in chunks of 128 against the best R found so far
-                LateEdges more(props, heads, (size_t)x, nheads, late, lane);
+                // inbox and late edges in chunks of 128 against the best R found so far; lane l walks list l, and the two
+                // records of the next chunk travel while this one is sorted and cut
+                const LateEdge first = late_edge(props, lane < late ? head[lane] : 0u, lane < late);
                 u64 k[4];
                 k[0] = lane < nb ? cur.r0 : KEY_PAD;
                 k[1] = lane + 64 < nb ? cur.r1 : KEY_PAD;
-                k[2] = INBOX_CAP - 1 - lane < ca ? cur.in : KEY_PAD;
-                k[3] = more.take();
-                for (int taken = nheads;; taken += 2 * nheads) {
+                k[2] = 63 - lane < ca ? cur.in : KEY_PAD;
+                k[3] = first.key;
+                LateEdge a = late_edge(props, first.next, LATE_LISTS + lane < late);
+                for (int at = LATE_LISTS;; at += 2 * LATE_LISTS) {      // edges taken so far; `a` is the next one of my list
                     wave_sort<4>(k, lane);
+                    const LateEdge b = late_edge(props, a.next, at + LATE_LISTS + lane < late);
                     nd = wave_unique_prefix<4>(k, lane, R, s_stage[wave], &any_new, &dropped);
                     wave_sync();
                     k[0] = lane < nd ? s_stage[wave][lane] : KEY_PAD;
                     k[1] = lane + 64 < nd ? s_stage[wave][lane + 64] : KEY_PAD;
                     wave_sync();
-                    if (taken >= late) break;
-                    k[2] = more.take();
-                    k[3] = more.take();
+                    if (at >= late) break;
+                    k[2] = a.key;
+                    k[3] = b.key;
+                    a = late_edge(props, b.next, at + 2 * LATE_LISTS + lane < late);
                 }
                 if (lane < nd) row[lane] = k[0];
                 if (lane + 64 < nd) row[lane + 64] = k[1];
@@ -624,7 +637,7 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
 // All four merge classes in one launch: blockIdx.y = merge class (touched list y, tcls + y*N).
 __global__ __launch_bounds__(BLOCK) void k_merge(long long N, int R, u64 *keys, int *deg, const int *tlists,
                                                  const u32 *n_touched, int *cnt, const u64 *inbox,
-                                                 const u32 *heads, const Prop *props, int8_t *tcls,
+                                                 LateHeads heads, const Prop *props, int8_t *tcls,
                                                  int use_classes, RoundCtr *ctr)
 {
     __shared__ u64 s_stage[WAVES_PER_BLOCK][RNND_MAX_R];
@@ -1847,16 +1860,16 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
     // from here on `fill` plays the role of the per-target count of this round
     const int ncl = use_classes ? NDEG : 1;
     hipLaunchKernelGGL(k_scatter, dim3(pb), dim3(BLOCK), 0, st, N, R, w.lists, ncl, c, w.props, (const int *)w.nprop, w.fill,
-                       w.inbox, (u32 *)w.bins);
+                       w.inbox, late_heads(w.inbox, w.bins, R));
     if (N <= SMALL_INPUT_MAX_N)
-        hipLaunchKernelGGL(k_touch_classify<2>, dim3((unsigned)((N + 2047) / 2048)), dim3(1024), 0, st, N, w.fill, deg, c,
+        hipLaunchKernelGGL(k_touch_classify<2>, dim3((unsigned)((N + 2047) / 2048)), dim3(1024), 0, st, N, round_inbox(R), w.fill, deg, c,
                            w.touched);
     else
-        hipLaunchKernelGGL(k_touch_classify<4>, dim3((unsigned)((N + 4095) / 4096)), dim3(1024), 0, st, N, w.fill, deg, c,
+        hipLaunchKernelGGL(k_touch_classify<4>, dim3((unsigned)((N + 4095) / 4096)), dim3(1024), 0, st, N, round_inbox(R), w.fill, deg, c,
                            w.touched);
     static const int merge_per_cu = resident_blocks_per_cu(k_merge, 6);
     hipLaunchKernelGGL(k_merge, dim3(capped(cu_count() * merge_per_cu, N), NMRG), dim3(BLOCK), 0, st, N, R, keys, deg, w.touched, c->n_touched,
-                       w.fill, w.inbox, (const u32 *)w.bins, (const Prop *)w.props, w.tcls, use_classes, c);
+                       w.fill, w.inbox, late_heads(w.inbox, w.bins, R), (const Prop *)w.props, w.tcls, use_classes, c);
     if (run)
         hipLaunchKernelGGL(k_store_classes, dim3(64, NMRG), dim3(256), 0, st, (const u32 *)c->n_touched,
                            (const int *)w.touched, (const int8_t *)w.tcls, N, w.vcls);

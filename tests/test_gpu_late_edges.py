@@ -1,5 +1,5 @@
-"""Edges that arrive past a target's inbox (64 per round) are chained in up to 64 lists of equal length, fewer where
-rows are narrower than 32 slots: a star whose centre receives from a few dozen to a few thousand edges in one round."""
+"""Edges that arrive past a target's inbox (64 per round, 32 where rows are narrower than 32 slots) are chained in 64 lists
+of equal length: a star whose centre receives from a few dozen to a few thousand edges in one round."""
 import numpy as np
 import pytest
 
