@@ -269,6 +269,42 @@ __device__ __forceinline__ int active_vertex(const ActiveLists &a, u32 i)
     return a.lists[(size_t)c * (size_t)a.N + off];
 }
 
+// The padded copy for a single round (see k_prepare_rows).  Where fewer than one vertex in LISTED_SHARE is active only the
+// rows their lists name are copied, by one wavefront for 8 entries; a row named twice is written twice, with the same bytes.
+// On a snapshot that is nearly converged the copy of all rows costs more than the round: 200,000 x 100 float32, 690
+// vertices active, call with all rows / these rows / no copy and the generic kernel: 197 / 148 / 149 us; 1M x 100, 9,251
+// active: 590 / 450 / 464; 28,399 active, where either copy reads about as much: 640 / - / 612; 100,000 x 901, 252: 315 / 173 / 512.
+#define LISTED_SHARE 64
+#define LISTED_MIN_N 32768       // below, the copy of all rows is a launch's worth of time
+template <typename T>
+__global__ __launch_bounds__(256) void k_prepare_listed_rows(const T *__restrict__ X, long long N, int d, u32 rb, int permute,
+                                                             uint4 *__restrict__ Xp, const int *lists, const RoundCtr *ctr,
+                                                             const u64 *__restrict__ keys, const int *__restrict__ deg, int R)
+{
+    const ActiveLists al = active_lists(lists, N, ctr, NDEG);
+    const u32 n = al.start[NDEG], pieces = rb / 16u;
+    if ((u64)n * LISTED_SHARE >= (u64)N) {
+        (void)pad_all_rows<T>(X, N, d, rb, permute, 0u, Xp);
+        return;
+    }
+    const u32 parts = ((u32)R + 7u) / 8u;
+    const int lane = threadIdx.x & 63;
+    for (u64 w = ((u64)blockIdx.x * 256u + threadIdx.x) >> 6; w < (u64)n * parts; w += (u64)gridDim.x * 4u) {
+        const int u = active_vertex(al, (u32)(w / parts)), first = 8 * (int)(w % parts);
+        int m = deg[u] - first;
+        if (first + m > R) m = R - first;
+        if (m > 8) m = 8;
+        if (m <= 0) continue;
+        const u32 mine = key_id(keys[(size_t)u * R + first + (lane < m ? lane : 0)]), total = (u32)m * pieces;
+        bool odd = false;
+        for (u32 base = 0; base < total; base += 64u) {
+            const u32 i = base + (u32)lane, e = i < total ? i / pieces : 0u;
+            const size_t id = (u32)__shfl((int)mine, (int)e);      // (every lane takes part)
+            if (i < total) Xp[id * pieces + (i - e * pieces)] = padded_piece<T>(X + id * (size_t)d, (int)(i - e * pieces), d, permute, 0u, odd);
+        }
+    }
+}
+
 // Bit j set iff lane j of this lane's row of 16 holds the same value, for the lanes reached by rotations R .. 15.
 template <int R>
 __device__ __forceinline__ u32 same_target_mask(u32 tgt, int sub)
@@ -1508,7 +1544,10 @@ struct ScanPlan {
 //   float   d = 33: 2.2 -> 1.9 ms at 300 vertices, d = 100: 3.0 -> 1.9; d = 7: 1.8 -> 1.9 ms at 300, 2.4 -> 2.0 at 2,048
 #define PAD_MIN_N_FLOAT 256
 #define PAD_MIN_N_SHORT_FLOAT 2048      // rows of fewer than 16 coordinates
-#define PAD_MIN_N_STEP 2048     // UpdateNeighbors by itself: a call on fewer vertices scans X as it is, with no copy made for it
+// UpdateNeighbors by itself: a call on fewer vertices scans X as it is, with no copy made for it.  A copy pays where there is
+// work (2,000 x 100 float32, generic / padded: 170 / 111 us with 1,976 vertices active; 500 x 100: 152 / 107 with 493) and costs a launch
+// or two where there is none (75 / 90 us), which small snapshots reach soonest.
+#define PAD_MIN_N_STEP 2048
 #define PAD_MAX_D 65536         // (row lengths in bytes stay far below 2^31)
 
 static bool worth_padding(long long N, int d, int dtype, bool step)
@@ -1602,7 +1641,14 @@ static void launch_mfma_scan(const Workspace &w, int d, int R, u64 *keys, int *d
 }
 
 // Fills w.xs, the copy of X the plan asks for.
-static void launch_prepare(const Workspace &w, const ScanPlan &p, const void *X, long long N, int d, int dtype, hipStream_t st)
+// `round` (one round on this snapshot, its active lists made): padded float rows may be copied for its lists only.
+struct SnapshotRound {
+    const u64 *keys;
+    const int *deg;
+    int R;
+};
+static void launch_prepare(const Workspace &w, const ScanPlan &p, const void *X, long long N, int d, int dtype, const SnapshotRound *round,
+                           hipStream_t st)
 {
     const u32 exponent = dtype == RNND_F32 ? 0x7F800000u : dtype == RNND_F16 ? 0x7C00u : 0x7F80u;
     if (p.copy == COPY_NONE) return;
@@ -1618,6 +1664,12 @@ static void launch_prepare(const Workspace &w, const ScanPlan &p, const void *X,
     const int permute = p.copy == COPY_ROWS_PERMUTED;
     if (p.copy == COPY_U8_ROWS)
         hipLaunchKernelGGL(k_prepare_u8_rows, grid, dim3(256), 0, st, (const uint8_t *)X, N, d, p.dp, w.xs);
+    else if (round && dtype == RNND_F32)
+        hipLaunchKernelGGL(k_prepare_listed_rows<u32>, grid, dim3(256), 0, st, (const u32 *)X, N, d, rb, permute, (uint4 *)w.xs,
+                           (const int *)w.lists, (const RoundCtr *)w.ctr, round->keys, round->deg, round->R);
+    else if (round)
+        hipLaunchKernelGGL(k_prepare_listed_rows<unsigned short>, grid, dim3(256), 0, st, (const unsigned short *)X, N, d, rb, permute,
+                           (uint4 *)w.xs, (const int *)w.lists, (const RoundCtr *)w.ctr, round->keys, round->deg, round->R);
     else if (dtype == RNND_F32)
         hipLaunchKernelGGL(k_prepare_rows<u32>, grid, dim3(256), 0, st, (const u32 *)X, N, d, rb, permute, exponent,
                            (uint4 *)w.xs, &w.ctr->nonfinite);
@@ -1632,21 +1684,24 @@ struct RowsView {
     int d = 0, vec_ok = 0;
 };
 
-// Makes the copy the plan asks for and says what the kernels are to read.  Padded float rows are for finite
-// coordinates: where X holds a NaN or an infinity the plan falls back to the generic kernel on X itself, whose
-// comparisons treat such distances in their own way.  That answer is waited for (about 20 us; rows that need no
-// padding pay nothing).
-static hipError_t prepare_rows(const Workspace &w, ScanPlan &p, const void *X, long long N, int d, int dtype, hipStream_t st, RowsView *rv)
+// Makes the copy the plan asks for and says what the kernels are to read.  The matrix-core scan leaves every pair of rows
+// that are not finite to the exact routine, so it gives the generic kernel's graph for them too, slowly where there are many.
+// A build asks: where padded float rows hold a NaN or an infinity the plan falls back to the generic kernel on X.  That
+// answer is waited for, about 20 us; UpdateNeighbors by itself (step), where a round may take no longer than that, does without it
+// (20,000 x 40 float32, a call with two active vertices: 97 -> 86 us, 77 with no copy and the generic kernel; 1,625 active:
+// 105 -> 92, 102).
+static hipError_t prepare_rows(const Workspace &w, ScanPlan &p, const void *X, long long N, int d, int dtype, hipStream_t st, bool step,
+                               const SnapshotRound *round, RowsView *rv)
 {
     rv->X = X;
     rv->d = d;
     rv->vec_ok = vec_ok_for(X, d, dtype);
-    launch_prepare(w, p, X, N, d, dtype, st);
+    launch_prepare(w, p, X, N, d, dtype, round, st);
     if (p.copy != COPY_ROWS && p.copy != COPY_ROWS_PERMUTED) return hipGetLastError();
     u32 nonfinite = 0;
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(&nonfinite, &w.ctr->nonfinite, sizeof nonfinite, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e == hipSuccess && !step) e = hipMemcpyAsync(&nonfinite, &w.ctr->nonfinite, sizeof nonfinite, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess && !step) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return e;
     if (nonfinite) {
         p = ScanPlan();
@@ -2288,7 +2343,7 @@ static int build_impl(const void *X, int64_t N, int32_t d, int dtype, int metric
         if (stats) HIPCHK(hipEventRecord(ev[0], st));
         ws_clear(w, st);
         RowsView rows;
-        HIPCHK(prepare_rows(w, plan, X, N, d, dtype, st, &rows));
+        HIPCHK(prepare_rows(w, plan, X, N, d, dtype, st, false, nullptr, &rows));
         const int variant = plan.variant, use_classes = plan.classes();
         launch_random_graph(rows.X, N, rows.d, dtype, rows.vec_ok, S, M, (u64)seed, w.keys, w.deg, w.vcls, use_classes, st);
         if (!blocks) launch_compact_all(w, N, 0, st, stats ? ev[1] : nullptr);
@@ -2456,27 +2511,29 @@ static int update_impl(const void *X, int64_t N, int32_t d, int dtype, int metri
     WsLease lease;
     RoundCtr *hctr = nullptr;
     RowsView rows;
-    int variant = 1, use_classes = 0;
+    const SnapshotRound round = {(const u64 *)keys, deg, R};
+    bool listed = false;
     rc = ws_open(w, &lease, plan, X, N, R, d, dtype, n_ctr, false, false, st);
     if (rc) return rc;
     if (stats) {
         hctr = (RoundCtr *)calloc(n_ctr, sizeof(RoundCtr));
         if (!hctr) { rc = RNND_ERR_OOM; goto done; }
     }
+    listed = (plan.copy == COPY_ROWS || plan.copy == COPY_ROWS_PERMUTED) && !blocks && n_rounds == 1 && N >= LISTED_MIN_N;
     ws_clear(w, st);
-    HIPCHK(prepare_rows(w, plan, X, N, d, dtype, st, &rows));
-    variant = plan.variant, use_classes = plan.classes();
+    // (the copy first, where it does not depend on the lists: it runs while the other launches are submitted)
+    if (!listed) HIPCHK(prepare_rows(w, plan, X, N, d, dtype, st, true, nullptr, &rows));
     hipLaunchKernelGGL(k_classify, dim3(vertex_blocks(N)), dim3(BLOCK), 0, st, (long long)N, R, (const u64 *)keys,
-                       deg, w.vcls, use_classes);
+                       deg, w.vcls, plan.classes());
     if (!blocks) launch_compact_all(w, N, 0, st);
-    HIPCHK(hipGetLastError());
+    if (listed) HIPCHK(prepare_rows(w, plan, X, N, d, dtype, st, true, &round, &rows));
     for (int t = 0; t < n_rounds; ++t) {
         if (blocks) {
             int used = 0;
-            HIPCHK(launch_update_pass_blocks(w, rows, N, plan.dp, dtype, variant, R, (u64 *)keys, deg,
+            HIPCHK(launch_update_pass_blocks(w, rows, N, plan.dp, dtype, plan.variant, R, (u64 *)keys, deg,
                                              (int)(t * per_pass), blocks, st, &used));
         } else {
-            HIPCHK(launch_update_round(w, rows, N, plan.dp, dtype, variant, R, (u64 *)keys, deg, t, st));
+            HIPCHK(launch_update_round(w, rows, N, plan.dp, dtype, plan.variant, R, (u64 *)keys, deg, t, st));
         }
     }
     if (stats) {
@@ -2488,7 +2545,7 @@ static int update_impl(const void *X, int64_t N, int32_t d, int dtype, int metri
         memset(stats, 0, sizeof *stats);
         if (blocks) fill_pass_stats(stats, hctr, n_rounds, (int)per_pass);
         else fill_round_stats(stats, hctr, n_rounds);
-        stats->kernel_variant = variant;
+        stats->kernel_variant = plan.variant;
         if (!blocks) {      // per-round times from the device clock (see build_impl)
             int dev = 0, khz = 0;
             (void)hipGetDevice(&dev);

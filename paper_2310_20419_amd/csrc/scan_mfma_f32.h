@@ -238,33 +238,41 @@ __device__ __forceinline__ void gram_f32_loop(const char *const (&rp)[NR], int n
 // depend on the order of the coordinates otherwise.  The copy streams (200,000 x 100: about 60 us); the build it makes
 // possible: 200,000 x 100 float 95.7 -> 34.0 ms, S = 20, R = 96, 60 rounds.
 template <typename T>      // uint32_t: float rows, unsigned short: 16-bit rows
+__device__ __forceinline__ uint4 padded_piece(const T *x, int c, int d, int permute, u32 exponent, bool &odd)     // piece c of the copy of row x
+{
+    constexpr int V = 16 / (int)sizeof(T);      // coordinates per piece
+    const int e0 = permute ? 8 * V * (c >> 3) + (c & 7) : V * c, step = permute ? 8 : 1;
+    T t[V];
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+        const int e = e0 + k * step;
+        t[k] = e < d ? x[e] : (T)0;
+        odd = odd || ((u32)t[k] & exponent) == exponent;       // exponent bits all set: NaN or infinity
+    }
+    if constexpr (sizeof(T) == 4)
+        return make_uint4(t[0], t[1], t[2], t[3]);
+    else
+        return make_uint4((u32)t[0] | (u32)t[1] << 16, (u32)t[2] | (u32)t[3] << 16, (u32)t[V - 4] | (u32)t[V - 3] << 16,
+                          (u32)t[V - 2] | (u32)t[V - 1] << 16);
+}
+
+template <typename T>
+__device__ __forceinline__ bool pad_all_rows(const T *__restrict__ X, long long N, int d, u32 rb, int permute, u32 exponent, uint4 *__restrict__ Xp)
+{
+    const u32 pieces = rb / 16u;
+    bool odd = false;
+    for (u64 i = (u64)blockIdx.x * 256u + threadIdx.x; i < (u64)N * pieces; i += (u64)gridDim.x * 256u) {
+        const u64 u = i / pieces;
+        Xp[i] = padded_piece<T>(X + u * (u64)d, (int)(i - u * pieces), d, permute, exponent, odd);
+    }
+    return odd;
+}
+
+template <typename T>
 __global__ __launch_bounds__(256) void k_prepare_rows(const T *__restrict__ X, long long N, int d, u32 rb, int permute,
                                                       u32 exponent, uint4 *__restrict__ Xp, u32 *__restrict__ nonfinite)
 {
-    constexpr int V = 16 / (int)sizeof(T);      // coordinates per piece
-    const u32 pieces = rb / 16u;
-    bool odd = false;       // exponent bits all set: NaN or infinity
-    for (u64 i = (u64)blockIdx.x * 256u + threadIdx.x; i < (u64)N * pieces; i += (u64)gridDim.x * 256u) {
-        const u64 u = i / pieces;
-        const int c = (int)(i - u * pieces);
-        const T *x = X + u * (u64)d;
-        const int e0 = permute ? 8 * V * (c >> 3) + (c & 7) : V * c, step = permute ? 8 : 1;
-        T t[V];
-#pragma unroll
-        for (int k = 0; k < V; ++k) {
-            const int e = e0 + k * step;
-            t[k] = e < d ? x[e] : (T)0;
-            odd = odd || ((u32)t[k] & exponent) == exponent;
-        }
-        uint4 o;
-        if constexpr (sizeof(T) == 4)
-            o = make_uint4(t[0], t[1], t[2], t[3]);
-        else
-            o = make_uint4((u32)t[0] | (u32)t[1] << 16, (u32)t[2] | (u32)t[3] << 16, (u32)t[V - 4] | (u32)t[V - 3] << 16,
-                           (u32)t[V - 2] | (u32)t[V - 1] << 16);
-        Xp[i] = o;
-    }
-    if (odd) *nonfinite = 1u;
+    if (pad_all_rows<T>(X, N, d, rb, permute, exponent, Xp)) *nonfinite = 1u;
 }
 
 // bits [lo, hi) of a 96-bit mask, as word c (bits 32c .. 32c+31)
