@@ -2662,14 +2662,15 @@ extern "C" int rnnd_search(const void *X, int64_t N, int32_t d, int dtype, int m
     const size_t q_bytes = ((dtype == RNND_U8 ? rowbytes : (size_t)d * 8) + 15) / 16 * 16;
     auto all_resident = [&](u32 sl) { return (size_t)((nq + cu_count() - 1) / cu_count()) * (sl * 4 + q_bytes + sizeof(SearchSmem)) <= (160u << 10); };
     u32 slots;
-    if (few) slots = short_rows && expect > 2000u ? 8192u : 4096u;
+    if (few) slots = short_rows && expect > 2000u ? SEARCH_MAX_SLOTS : SEARCH_MAX_SLOTS / 2u;
     else if (expect <= 2400u && all_resident(4096u)) slots = 4096u;
     else if (expect <= 1728u && all_resident(2048u)) slots = 2048u;
     else if ((short_rows || !vec_ok) && expect <= 700u) slots = 1024u;
     else if (short_rows && N <= 262144) slots = 0;
     else slots = expect <= 1728u ? 2048u : 0u;
-    const bool q_lds = (size_t)slots * 4 + q_bytes <= (60u << 10);
-    const int shape = (!vec_ok ? EVAL_SINGLE : rowbytes <= 128 ? EVAL_SHORT : rowbytes <= 512 ? EVAL_MID : EVAL_LONG) + (q_lds ? 0 : EVAL_GLOBAL);
+    const bool q_lds = (size_t)slots * 4 + q_bytes <= SEARCH_MAX_DYN_LDS;
+    const EvalShape shape = !q_lds ? (vec_ok ? EVAL_LONG_GLOBAL : EVAL_SINGLE_GLOBAL)
+                                   : !vec_ok ? EVAL_SINGLE : rowbytes <= 128 ? EVAL_SHORT : rowbytes <= 512 ? EVAL_MID : EVAL_LONG;
     const size_t dyn_lds = (size_t)slots * 4 + (q_lds ? q_bytes : 0);
     // queries in flight: what the LDS of a CU holds, at most 8 wavefronts per SIMD; one bitmap of N bits each (for queries
     // that outgrow the table), at most 1 GiB of them
@@ -2708,17 +2709,21 @@ extern "C" int rnnd_search(const void *X, int64_t N, int32_t d, int dtype, int m
     if (shape == EVAL_SHORT) { RNND_SEARCH_ALONE(DT, E, EVAL_SHORT); }  \
     else if (shape == EVAL_MID) { RNND_SEARCH_LAUNCH(DT, E, EVAL_MID); } \
     else if (shape == EVAL_LONG) { RNND_SEARCH_LAUNCH(DT, E, EVAL_LONG); } \
-    else if (shape == EVAL_SINGLE) { RNND_SEARCH_LAUNCH(DT, E, EVAL_SINGLE); } \
+    else if (shape == EVAL_SINGLE) { RNND_SEARCH_LAUNCH(DT, E, EVAL_SINGLE); }
+#define RNND_SEARCH_FLOAT_E(DT, E)                                      \
+    RNND_SEARCH_E(DT, E)                                                \
     else if (shape == EVAL_LONG_GLOBAL) { RNND_SEARCH_LAUNCH(DT, E, EVAL_LONG_GLOBAL); } \
     else { RNND_SEARCH_LAUNCH(DT, E, EVAL_SINGLE_GLOBAL); }
-#define RNND_SEARCH_DT(DT)                \
-    if (L <= 64) { RNND_SEARCH_E(DT, 1) } \
-    else { RNND_SEARCH_E(DT, 2) }
-        if (dtype == RNND_U8) { RNND_SEARCH_DT(DT_U8) }
-        else if (dtype == RNND_F16) { RNND_SEARCH_DT(DT_F16) }
-        else if (dtype == RNND_BF16) { RNND_SEARCH_DT(DT_BF16) }
-        else { RNND_SEARCH_DT(DT_F32) }
-#undef RNND_SEARCH_DT
+#define RNND_SEARCH_FLOAT(DT)                   \
+    if (L <= 64) { RNND_SEARCH_FLOAT_E(DT, 1) } \
+    else { RNND_SEARCH_FLOAT_E(DT, 2) }
+        if (dtype == RNND_U8 && L <= 64) { RNND_SEARCH_E(DT_U8, 1) }
+        else if (dtype == RNND_U8) { RNND_SEARCH_E(DT_U8, 2) }
+        else if (dtype == RNND_F16) { RNND_SEARCH_FLOAT(DT_F16) }
+        else if (dtype == RNND_BF16) { RNND_SEARCH_FLOAT(DT_BF16) }
+        else { RNND_SEARCH_FLOAT(DT_F32) }
+#undef RNND_SEARCH_FLOAT
+#undef RNND_SEARCH_FLOAT_E
 #undef RNND_SEARCH_E
 #undef RNND_SEARCH_ALONE
 #undef RNND_SEARCH_TEAM

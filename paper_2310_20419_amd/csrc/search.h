@@ -301,9 +301,13 @@ __device__ __forceinline__ void eval_rows_single(const void *X, QUERY qs, int d,
 //   EVAL_MID     up to 512 bytes: up to four pieces per lane
 //   EVAL_LONG    longer: 16 pieces in flight per lane
 //   EVAL_SINGLE  rows that cannot be read in 16-byte pieces
-// and the last two with a query too long for LDS (EVAL_GLOBAL added; float and 16-bit rows only)
-enum EvalShape { EVAL_SHORT = 0, EVAL_MID, EVAL_LONG, EVAL_SINGLE, EVAL_GLOBAL = 2, EVAL_LONG_GLOBAL = EVAL_LONG + EVAL_GLOBAL,
-                 EVAL_SINGLE_GLOBAL = EVAL_SINGLE + EVAL_GLOBAL };
+// and the last two with a query too long for LDS (float and 16-bit rows only)
+enum EvalShape { EVAL_SHORT = 0, EVAL_MID, EVAL_LONG, EVAL_SINGLE, EVAL_LONG_GLOBAL, EVAL_SINGLE_GLOBAL };
+#define SEARCH_MAX_DYN_LDS (60u << 10)      // table and query; with SearchSmem below the 64 KB a launch may ask for without more ado
+#define SEARCH_MAX_SLOTS 8192u              // of the table: alone; 4,096 for rows of more than 128 bytes
+static_assert(SEARCH_MAX_SLOTS * 4u + 128u * 8u <= SEARCH_MAX_DYN_LDS && SEARCH_MAX_SLOTS / 2u * 4u + 256u * 8u <= SEARCH_MAX_DYN_LDS,
+              "queries of up to 128 bytes (128 doubles), and of up to 512 (256), always lie in LDS");
+static_assert(SEARCH_MAX_SLOTS / 2u * 4u + 33040u <= SEARCH_MAX_DYN_LDS, "uint8 queries (d <= 33025) always do");
 
 // delta(q, ids[first .. cnt)) -> dist, the part of wavefront `wave` of a team of TEAM: eight vertices at a time each, or
 // (alone) as many as there are, so that no lane works on vertices that are not there.
@@ -465,7 +469,7 @@ __global__ __launch_bounds__(64 * TEAM, 4) void k_search(const void *X, long lon
                                                       unsigned long long *evals)
 {
     constexpr bool in_lds = SHAPE_ < EVAL_LONG_GLOBAL;
-    constexpr int SHAPE = in_lds ? SHAPE_ : SHAPE_ - EVAL_GLOBAL;
+    constexpr int SHAPE = SHAPE_ == EVAL_LONG_GLOBAL ? EVAL_LONG : SHAPE_ == EVAL_SINGLE_GLOBAL ? EVAL_SINGLE : SHAPE_;
     static_assert(SHAPE != EVAL_SHORT || TEAM == 1, "short rows are evaluated by the searching wavefront itself");
     constexpr bool AT_ONCE = SHAPE == EVAL_SHORT;      // neighbours are evaluated before the table has answered
     extern __shared__ uint4 s_dyn[];
