@@ -484,12 +484,13 @@ __device__ __forceinline__ void f32_scan_body(
 #pragma unroll
             for (int I = 0; I < NRC; ++I) {
                 // single-precision form: the rows of group I that this lane's accumulators stand for
-                float nIf[4], dIf[4];
+                float nIf[4], dIf[4], tIf[4];     // n, delta(u, .), n's part of the bound
                 if (FAST) {
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         nIf[v] = sm.nrmf[16 * I + 4 * q + v];
                         dIf[v] = sm.distf[16 * I + 4 * q + v];
+                        tIf[v] = epskf * nIf[v];
                     }
                 }
 #pragma unroll
@@ -505,7 +506,7 @@ __device__ __forceinline__ void f32_scan_body(
                             // all in float: the evaluation adds at most 4 x 2^-24 (n_i + n_j) to the error of
                             // delta(v,w), which the bound's constant covers
                             const float dj = sm.distf[16 * J + r16];
-                            const float nJf = (float)nr[J];
+                            const float nJf = (float)nr[J], tJf = fmaf(epskf, nJf, epsaf);
                             // The outcomes with group I's slot as the tested row are taken as wavefront-wide masks:
                             // accumulator v of lane (r16, q) is (row 4q + v, column r16), so bit 16q + c of the mask
                             // of accumulator v is (row 4q + v, column c), and the row a lane stands for, r16, finds
@@ -516,7 +517,7 @@ __device__ __forceinline__ void f32_scan_body(
                                 const int rsel = 4 * q + v;
                                 const float nsum = nIf[v] + nJf;
                                 const float dvw = fmaf(-2.f, acc[t][v], nsum);
-                                const float tol = fmaf(epskf, nsum, epsaf);
+                                const float tol = tIf[v] + tJf;
                                 const float ta = dIf[v] - dvw, tb = dj - dvw;
                                 fire_m[v] = __builtin_amdgcn_ballot_w64(ta >= 0.f);
                                 amb_m[v] = __builtin_amdgcn_ballot_w64(!(fabsf(ta) > tol));      // also when not finite
