@@ -1404,13 +1404,28 @@ static int g_scan_launches = 0;    // uint8 matrix-core scan: 0 by size, 1 short
                                    // launches per class: 0.75 x at 50,000 vertices, 0.78 x at 100,000, 0.90 x at 300,000, 0.955 x
                                    // at 500,000; 1.02 x at 1M, where it wins only in rounds with fewer than 250,000 active lists).
                                    // Above: the short-list launch and one launch for all longer classes (0.99 x at 1M)
-// Float scan: up to here one launch for all classes, which costs the shorter lists their occupancy.  Whole builds, three
-// launches -> one, S = 20, 60 rounds, float32 d = 96 / 304, bfloat16 d = 768: R = 64: 20,000 vertices 4.10 -> 3.78 / 6.56
-// -> 5.98 / 7.83 -> 7.01 ms, 70,000: 9.97 -> 9.88 / 19.6 -> 19.1 / 24.0 -> 23.3, 100,000: 13.6 -> 13.8 / 28.0 -> 27.8 /
-// 34.1 -> 33.5; R = 96: 20,000: 4.27 -> 4.12 / 6.88 -> 6.65 / 8.10 -> 7.47, 50,000: 8.03 -> 8.45 / 15.0 -> 15.5 / 18.1 -> 17.6
+// Float scan: up to here one launch for all classes, which costs the shorter lists their occupancy; above, a launch for each of
+// lists of up to 32, 64 and 96 entries.  Whole builds, S = 20, 60 rounds, three launches / one, ms:
+//   R = 96          20,000        32,000        50,000         70,000         100,000         200,000
+//   float32   96    4.05 / 3.83   5.33 / 5.49   7.61 / 8.11    9.97 / 11.0    13.7 / 16.1     27.4 / 34.4
+//   float32  304    6.63 / 6.28   9.62 / 9.41   14.7 / 14.8    20.3 / 21.0    29.3 / 31.4     61.4 / 69.4
+//   float16  320    5.12 / 4.80   6.99 / 6.91   9.90 / 10.3    13.1 / 14.2    18.1 / 20.4     35.8 / 42.5
+//   bfloat16 128    3.87 / 3.62   5.04 / 5.01   7.08 / 7.28    9.16 / 9.75    12.6 / 14.0     24.1 / 29.1
+//   bfloat16 768    9.83 / 7.88   12.4 / 11.1   17.0 / 16.2    22.2 / 22.1    30.5 / 31.2     60.9 / 67.5
+//   R = 64
+//   float32   96    3.85 / 3.55   5.07 / 4.88   7.08 / 7.01    9.36 / 9.42    12.8 / 13.2     25.2 / 26.4
+//   float32  304    6.27 / 5.72   9.18 / 8.55   13.8 / 13.0    19.1 / 18.3    27.3 / 26.4     55.6 / 53.9
+//   float16  320    4.89 / 4.42   6.64 / 6.22   9.36 / 9.06    12.4 / 12.3    17.0 / 17.2     32.6 / 34.0
+//   bfloat16 128    3.71 / 3.38   4.76 / 4.51   6.63 / 6.34    8.63 / 8.39    11.7 / 11.6     22.0 / 22.6
+//   bfloat16 768    6.76 / 5.94   8.89 / 8.11   12.5 / 11.8    16.9 / 16.2    23.4 / 22.8     46.9 / 47.1
+// The lines suit rows of up to about 1 KB; longer ones would gain up to 5 % from later lines.
 #define SMALL_FLOAT_MAX_N_64 65536      // R <= 64
 #define SMALL_FLOAT_MAX_N_96 32768      // R > 64
-#define SMALL_FLOAT_MAX_N_32 131072     // float32: lists of up to 32 entries in one launch (see k_update_scan_mfma_f32_all)
+// Lists of up to 32 entries of long float32 rows: two launches (up to 16, 17 .. 32).  Two / one: 60-round builds of 96 coordinates 70,000
+// vertices 10.5 / 10.0 ms, 200,000 27.5 / 26.8, 1M 144.3 / 143.2, of 304 1M 312.5 / 310.6; of 960 150,000 113.0 / 112.0, 500,000 423.2 /
+// 424.9, 1M 917.4 / 924.1.  (16-bit rows always take one.)
+#define SPLIT_SHORT_LISTS_MIN_N 262144
+#define SPLIT_SHORT_LISTS_MIN_D 512
 #define LONG_SHARED_MAX_N 2097152  // ... up to here (1.00 x at 2M, 1.01 x at 4M, 1.00 x at 8M, 1.01 x at 20M: no start-up left to
                                    // share, and each class alone gets the occupancy that suits it); above: a launch per class
                                    // (bench.py names the round's scan launches by the same rule; include/rnnd.h states it)
@@ -1785,7 +1800,7 @@ static void launch_f32_scan(const Workspace &w, const void *X, int d, int R, u64
         }
         return;
     }
-    if (DT == DT_F32 && N > SMALL_FLOAT_MAX_N_32) {
+    if (DT == DT_F32 && N > SPLIT_SHORT_LISTS_MIN_N && d > SPLIT_SHORT_LISTS_MIN_D) {
         if (wide) launch_f32_classes<1, 0, 2, DT>(w, X, d, R, keys, deg, N, c, st, e_start);
         else launch_f32_classes<1, 0, 1, DT>(w, X, d, R, keys, deg, N, c, st, e_start);
         if (R > 16) {

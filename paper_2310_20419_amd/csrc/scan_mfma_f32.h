@@ -814,9 +814,8 @@ __global__ __launch_bounds__(64 * 4, (NRC <= 2 ? 4 : NRC <= 5 ? 2 : 1)) void k_u
 // grid's blocks divided among them in proportion to their work (share_blocks).  All classes together (C0 = 0): for
 // inputs so small that no class fills the chip by itself and a round waits for one short launch after the other; every
 // block then has the registers of the longest shape.  Larger inputs take the classes that need about the same number
-// of registers together: up to 32 entries (C0 = 0; float32 rows: up to 16 entries, and 17 .. 32 with C0 = 2, because the
-// two shapes side by side need a few registers more than four wavefronts per SIMD leave: 1M x 96 152.5 against 146.5
-// ms), 33 .. 64 (C0 = 3), 65 .. 96 (C0 = 5).
+// of registers together: up to 32 entries (C0 = 0), 33 .. 64 (C0 = 3), 65 .. 96 (C0 = 5); many long float32 rows the first of these
+// in two parts, up to 16 and (C0 = 2) 17 .. 32.
 template <int NRCMAX, int C0, int CH, int DT>
 __global__ __launch_bounds__(64 * 4, (NRCMAX <= 2 ? 4 : NRCMAX <= 4 ? 3 : 2)) void k_update_scan_mfma_f32_all(
     const char *__restrict__ X, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
