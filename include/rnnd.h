@@ -264,9 +264,8 @@ int rnnd_probe_gather_map(const void *X, int64_t n_rows, int64_t row_bytes, int6
  *   Gram block first (fp32 MFMA on float32 rows; f16 / bf16 MFMA on 16-bit rows as stored), every
  *   pair whose outcome lies within that block's error bound decided by the exact distance, and
  *   vertices with very many such pairs redone on the f64 MFMA.  Float rows of other lengths, or not 16-byte
- *   aligned, on a padded copy if there are enough of them (256; 2,048 if d < 16) and every coordinate is finite.
- *   rnnd_update_neighbors on fewer than 2,048 vertices
- *   makes no copy and on more takes rows that are not finite as well.
+ *   aligned, on a padded copy if there are enough of them (256; 2,048 if d < 16) and every coordinate is finite
+ *   (rnnd_update_neighbors: 2,048, finite or not).
  * All give identical graphs; this exists for testing and profiling.  Process-wide, not thread-safe. */
 int rnnd_set_kernel_variant(int variant);
 
