@@ -1443,6 +1443,7 @@ struct Workspace {
     u64 *bins = nullptr;    // [N*R]   a round's heads of late edges, the float scan's redo list; AddReverseEdges' bins
     u64 *thr = nullptr;     // [N]
     int *cnt = nullptr, *binoff = nullptr, *fill = nullptr, *touched = nullptr, *hubs = nullptr, *nprop = nullptr;
+    char *half = nullptr;     // half-precision copy of float32 rows
     int8_t *xs = nullptr;     // copy of X (see ScanPlan): X - 128 as int8 for the uint8 MFMA scan, or padded rows
     int *lists = nullptr;   // [NDEG*N] active lists by degree class
     int8_t *vcls = nullptr, *tcls = nullptr;   // [N], [NMRG*N]
@@ -1544,13 +1545,21 @@ static int vec_ok_for(const void *X, int d, int dtype)
 //             fit the tiles, or rows padded to a length the tiles take (dp coordinates; see k_prepare_*_rows)
 // The first two are what a call needs; padded rows are an extra a call does without (generic kernel) where there is
 // no room for them.
+// Row length in bytes of the half-precision copy of d coordinates: a multiple of 128, so that no row shares a cache line.
+static u32 half_row_bytes(int d) { return ((u32)d + 63u) / 64u * 128u; }
+// From how many vertices on a build's float32 scans take their Gram block from that copy (with / without it, 60-round builds: 1M x
+// 960 604 / 915 ms, half the bytes per gathered row; 200,000 x 100 27.1 / 31.5, 1M x 96 139.4 / 143.3; 20,000 x 96, where
+// launches and latency count, 3.89 / 3.87 and two launches more).
+#define HALF_MIN_N 32768
 enum CopyKind { COPY_NONE = 0, COPY_U8, COPY_U8_ROWS, COPY_ROWS, COPY_ROWS_PERMUTED };
 struct ScanPlan {
     int variant = 1, dp = 0;
     CopyKind copy = COPY_NONE;
     size_t copy_bytes = 0;
+    u32 half_rb = 0;            // row length of the half-precision copy of float32 rows (see HalfRows), 0 = none
+    size_t half_bytes = 0;      // what it takes: rows, centre, sums, parameters
     int classes() const { return variant == 2 ? 2 : variant == 3 ? 1 : 0; }
-    bool extra() const { return copy > COPY_U8; }
+    bool extra() const { return copy > COPY_U8 || half_rb; }
 };
 
 // From how many vertices on padded rows are worth their copy, measured on whole builds (generic kernel against padded
@@ -1571,7 +1580,8 @@ static bool worth_padding(long long N, int d, int dtype, bool step)
     return dtype == RNND_U8 || N >= (d < 16 ? PAD_MIN_N_SHORT_FLOAT : PAD_MIN_N_FLOAT);
 }
 
-static ScanPlan scan_plan_for(const void *X, long long N, int d, int dtype, bool may_pad)
+static size_t half_layout(char *base, long long N, int d, u32 rb, struct HalfLayout *l);
+static ScanPlan scan_plan_for(const void *X, long long N, int d, int dtype, bool may_pad, bool may_half = false)
 {
     ScanPlan p;
     p.dp = d;
@@ -1596,6 +1606,10 @@ static ScanPlan scan_plan_for(const void *X, long long N, int d, int dtype, bool
             p.dp = (int)(((long long)d + per - 1) / per * per);
             p.copy_bytes = (size_t)N * p.dp * dt_size(dtype);
         }
+    }
+    if (may_half && N > HALF_MIN_N && p.variant == 3 && dtype == RNND_F32 && g_kernel_variant == 0) {
+        p.half_rb = half_row_bytes(d);
+        p.half_bytes = half_layout(nullptr, N, d, p.half_rb, nullptr);
     }
     return p;
 }
@@ -1693,11 +1707,47 @@ static void launch_prepare(const Workspace &w, const ScanPlan &p, const void *X,
                            exponent, (uint4 *)w.xs, &w.ctr->nonfinite);
 }
 
-// The rows every kernel but the uint8 matrix-core scan reads: X, or the padded copy of float or 16-bit rows.
+// The rows every kernel but the uint8 matrix-core scan reads: X, or the padded copy of float or 16-bit rows; and the
+// half-precision copy of float32 rows, if there is one.
 struct RowsView {
     const void *X = nullptr;
     int d = 0, vec_ok = 0;
+    HalfRows half;
 };
+
+// Where the parts of a half-precision copy lie.
+struct HalfLayout {
+    char *rows;
+    float *centre, *square;
+    HalfPar *par;
+};
+static size_t half_layout(char *base, long long N, int d, u32 rb, HalfLayout *l)
+{
+    size_t off = 0;
+    auto take = [&](size_t b) { size_t o = off; off += align_up(b); return o; };
+    const size_t o_rows = take((size_t)N * rb), o_centre = take((size_t)d * 4 + 32), o_square = take(((size_t)d + 63) / 64 * 4), o_par = take(sizeof(HalfPar));
+    if (l) *l = HalfLayout{base + o_rows, (float *)(base + o_centre), (float *)(base + o_square), (HalfPar *)(base + o_par)};
+    return off;
+}
+
+static void launch_half_rows(char *base, const void *X, long long N, int d, int vec_ok, u32 rb, hipStream_t st, HalfRows *out)
+{
+    HalfLayout l;
+    half_layout(base, N, d, rb, &l);
+    hipLaunchKernelGGL(k_half_centre, dim3((unsigned)((d + 63) / 64)), dim3(256), 0, st, (const float *)X, N, d, l.centre, l.square, l.par);
+    const int lanes = rb <= 512 ? 16 : 64;
+    const size_t need = ((size_t)N * lanes + 255) / 256, most = (size_t)persistent_blocks();
+    const dim3 grid((unsigned)(need < most ? need : most));
+    if (lanes == 16)
+        hipLaunchKernelGGL(k_half_rows<16>, grid, dim3(256), 0, st, (const float *)X, N, d, vec_ok, rb, (const float *)l.centre,
+                           (const float *)l.square, l.rows, l.par);
+    else
+        hipLaunchKernelGGL(k_half_rows<64>, grid, dim3(256), 0, st, (const float *)X, N, d, vec_ok, rb, (const float *)l.centre,
+                           (const float *)l.square, l.rows, l.par);
+    out->rows = l.rows;
+    out->rowbytes = rb;
+    out->par = l.par;
+}
 
 // Makes the copy the plan asks for and says what the kernels are to read.  The matrix-core scan leaves every pair of rows
 // that are not finite to the exact routine, so it gives the generic kernel's graph for them too, slowly where there are many.
@@ -1711,6 +1761,7 @@ static hipError_t prepare_rows(const Workspace &w, ScanPlan &p, const void *X, l
     rv->X = X;
     rv->d = d;
     rv->vec_ok = vec_ok_for(X, d, dtype);
+    if (p.half_rb) launch_half_rows(w.half, X, N, d, rv->vec_ok, p.half_rb, st, &rv->half);
     launch_prepare(w, p, X, N, d, dtype, round, st);
     if (p.copy != COPY_ROWS && p.copy != COPY_ROWS_PERMUTED) return hipGetLastError();
     u32 nonfinite = 0;
@@ -1721,6 +1772,7 @@ static hipError_t prepare_rows(const Workspace &w, ScanPlan &p, const void *X, l
     if (nonfinite) {
         p = ScanPlan();
         p.dp = d;
+        rv->half = HalfRows();
     } else {
         rv->X = w.xs;
         rv->d = p.dp;
@@ -1774,45 +1826,45 @@ static void launch_mfma_scan_classes(const Workspace &w, int d, int R, u64 *keys
 // Float scan.  The single-precision form takes the active lists; vertices it leaves alone (ties in bulk) go to one redo
 // list for all classes, which launch_f32_redo hands to the double-precision form.  The redo list lives in the bin
 // array, which nothing else uses until the scatter that follows the scans.
-template <int NRCMAX, int C0, int CH, int DT>
-static void launch_f32_classes(const Workspace &w, const void *X, int d, int R, u64 *keys, int *deg, long long N, RoundCtr *c,
+template <int NRCMAX, int C0, int CH, int DT, bool HALF>
+static void launch_f32_classes(const Workspace &w, const void *X, const HalfRows &half, int d, int R, u64 *keys, int *deg, long long N, RoundCtr *c,
                                hipStream_t st, hipEvent_t e_start)
 {
-    static const int per_cu = resident_blocks_per_cu(k_update_scan_mfma_f32_all<NRCMAX, C0, CH, DT>, 2);
+    static const int per_cu = resident_blocks_per_cu(k_update_scan_mfma_f32_all<NRCMAX, C0, CH, DT, HALF>, 2);
     unsigned gx = capped((long long)cu_count() * per_cu, N);
     if (gx < 8) gx = 8;      // a block at least for every class
-    hipExtLaunchKernelGGL((k_update_scan_mfma_f32_all<NRCMAX, C0, CH, DT>), dim3(gx), dim3(256), 0, st, e_start, nullptr, 0,
-                          (const char *)X, d, R, keys, deg, w.lists, N, w.props, w.nprop, c, (int *)w.bins, &c->n_redo[0]);
+    hipExtLaunchKernelGGL((k_update_scan_mfma_f32_all<NRCMAX, C0, CH, DT, HALF>), dim3(gx), dim3(256), 0, st, e_start, nullptr, 0,
+                          (const char *)X, half, d, R, keys, deg, w.lists, N, w.props, w.nprop, c, (int *)w.bins, &c->n_redo[0]);
 }
 
-template <int DT>
-static void launch_f32_scan(const Workspace &w, const void *X, int d, int R, u64 *keys, int *deg, long long N, RoundCtr *c,
+template <int DT, bool HALF = false>
+static void launch_f32_scan(const Workspace &w, const void *X, const HalfRows &half, int d, int R, u64 *keys, int *deg, long long N, RoundCtr *c,
                             hipStream_t st, hipEvent_t e_start)
 {
-    const bool wide = ((size_t)d * dt_size(DT)) % 128 == 0;     // two 64-byte chunks per iteration
+    const bool wide = (HALF ? half.rowbytes : (size_t)d * dt_size(DT)) % 128 == 0;     // two 64-byte chunks per iteration
     if (R > 32 && N <= (R <= 64 ? SMALL_FLOAT_MAX_N_64 : SMALL_FLOAT_MAX_N_96)) {
         if (R <= 64) {
-            if (wide) launch_f32_classes<4, 0, 2, DT>(w, X, d, R, keys, deg, N, c, st, e_start);
-            else launch_f32_classes<4, 0, 1, DT>(w, X, d, R, keys, deg, N, c, st, e_start);
+            if (wide) launch_f32_classes<4, 0, 2, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, e_start);
+            else launch_f32_classes<4, 0, 1, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, e_start);
         } else {
-            if (wide) launch_f32_classes<6, 0, 2, DT>(w, X, d, R, keys, deg, N, c, st, e_start);
-            else launch_f32_classes<6, 0, 1, DT>(w, X, d, R, keys, deg, N, c, st, e_start);
+            if (wide) launch_f32_classes<6, 0, 2, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, e_start);
+            else launch_f32_classes<6, 0, 1, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, e_start);
         }
         return;
     }
     if (DT == DT_F32 && N > SPLIT_SHORT_LISTS_MIN_N && d > SPLIT_SHORT_LISTS_MIN_D) {
-        if (wide) launch_f32_classes<1, 0, 2, DT>(w, X, d, R, keys, deg, N, c, st, e_start);
-        else launch_f32_classes<1, 0, 1, DT>(w, X, d, R, keys, deg, N, c, st, e_start);
+        if (wide) launch_f32_classes<1, 0, 2, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, e_start);
+        else launch_f32_classes<1, 0, 1, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, e_start);
         if (R > 16) {
-            if (wide) launch_f32_classes<2, 2, 2, DT>(w, X, d, R, keys, deg, N, c, st, nullptr);
-            else launch_f32_classes<2, 2, 1, DT>(w, X, d, R, keys, deg, N, c, st, nullptr);
+            if (wide) launch_f32_classes<2, 2, 2, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, nullptr);
+            else launch_f32_classes<2, 2, 1, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, nullptr);
         }
     } else {
-        if (wide) launch_f32_classes<2, 0, 2, DT>(w, X, d, R, keys, deg, N, c, st, e_start);
-        else launch_f32_classes<2, 0, 1, DT>(w, X, d, R, keys, deg, N, c, st, e_start);
+        if (wide) launch_f32_classes<2, 0, 2, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, e_start);
+        else launch_f32_classes<2, 0, 1, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, e_start);
     }
-    if (R > 32) launch_f32_classes<4, 3, 1, DT>(w, X, d, R, keys, deg, N, c, st, nullptr);
-    if (R > 64) launch_f32_classes<6, 5, 1, DT>(w, X, d, R, keys, deg, N, c, st, nullptr);
+    if (R > 32) launch_f32_classes<4, 3, 1, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, nullptr);
+    if (R > 64) launch_f32_classes<6, 5, 1, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, nullptr);
 }
 
 // Kernel variant 2: the double-precision form on the active list of degree class cls.
@@ -1907,9 +1959,10 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
         // rows; class 7 (97..128 entries: too many accumulator tiles) goes to the generic kernel
         const bool generic_tail = R > 96;
         if (g_kernel_variant != 2) {
-            if (dtype == RNND_F16) launch_f32_scan<DT_F16>(w, X, d, R, keys, deg, N, c, st, re.scan_start);
-            else if (dtype == RNND_BF16) launch_f32_scan<DT_BF16>(w, X, d, R, keys, deg, N, c, st, re.scan_start);
-            else launch_f32_scan<DT_F32>(w, X, d, R, keys, deg, N, c, st, re.scan_start);
+            if (dtype == RNND_F16) launch_f32_scan<DT_F16>(w, X, rv.half, d, R, keys, deg, N, c, st, re.scan_start);
+            else if (dtype == RNND_BF16) launch_f32_scan<DT_BF16>(w, X, rv.half, d, R, keys, deg, N, c, st, re.scan_start);
+            else if (rv.half.rows) launch_f32_scan<DT_F32, true>(w, X, rv.half, d, R, keys, deg, N, c, st, re.scan_start);
+            else launch_f32_scan<DT_F32>(w, X, rv.half, d, R, keys, deg, N, c, st, re.scan_start);
             launch_f32_redo(w, X, d, dtype, R, keys, deg, N, c, st, generic_tail ? (hipEvent_t) nullptr : re.scan_stop);
         } else {
             const int n_more = (R > 8) + (R > 16) + (R > 32) + (R > 48) + (R > 64) + (R > 80);
@@ -2185,7 +2238,12 @@ static int ws_open(Workspace &w, WsLease *lease, ScanPlan &plan, const void *X, 
     const bool apart = plan.extra() && !static_only;
     w.bytes = ws_layout(w, N, R, n_ctr, own_graph, apart ? 0 : plan.copy_bytes);
     int rc = ws_acquire(w.bytes, static_only, st, lease);
-    const bool no_copy = rc ? rc == RNND_ERR_SCRATCH && plan.extra() : apart && !ws_acquire_copy(lease, plan.copy_bytes, st);
+    bool no_copy = rc ? rc == RNND_ERR_SCRATCH && plan.extra() : apart && !ws_acquire_copy(lease, align_up(plan.copy_bytes) + plan.half_bytes, st);
+    if (no_copy && !rc && plan.half_rb) {      // no room for the half-precision rows: do without these first
+        plan.half_rb = 0;
+        plan.half_bytes = 0;
+        no_copy = plan.extra() && !ws_acquire_copy(lease, plan.copy_bytes, st);
+    }
     if (no_copy) plan = scan_plan_for(X, N, d, dtype, false);
     if (no_copy && rc) {
         w.bytes = ws_layout(w, N, R, n_ctr, own_graph, plan.copy_bytes);
@@ -2194,7 +2252,10 @@ static int ws_open(Workspace &w, WsLease *lease, ScanPlan &plan, const void *X, 
     if (rc) return rc;
     w.base = lease->base;
     ws_layout(w, N, R, n_ctr, own_graph, apart ? 0 : plan.copy_bytes);
-    if (lease->copy) w.xs = (int8_t *)lease->copy;
+    if (lease->copy) {
+        w.xs = (int8_t *)lease->copy;
+        w.half = lease->copy + align_up(plan.copy_bytes);
+    }
     return RNND_OK;
 }
 
@@ -2332,7 +2393,7 @@ static int build_impl(const void *X, int64_t N, int32_t d, int dtype, int metric
     hipStream_t st = (hipStream_t)stream;
     const int rounds = T1 * T2, n_ctr = (int)(rounds * per_pass) + 2;
     // (padded float rows read a flag back: not in a call that may not allocate)
-    ScanPlan plan = scan_plan_for(X, N, d, dtype, worth_padding(N, d, dtype, false) && (!fixed || dtype == RNND_U8));
+    ScanPlan plan = scan_plan_for(X, N, d, dtype, worth_padding(N, d, dtype, false) && (!fixed || dtype == RNND_U8), !fixed);
     // events (only when statistics are wanted): 0 start, 1 end of init, last: the end.  Per-round times come from the
     // device clock (RoundCtr::t_*), which costs nothing; with rnnd_set_event_timing(1), and for block-sequential
     // passes, from events as well: 2 + 3t .. 4 + 3t = scan start, scan stop, end of round t (block-sequential passes

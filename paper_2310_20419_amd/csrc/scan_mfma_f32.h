@@ -275,6 +275,131 @@ __global__ __launch_bounds__(256) void k_prepare_rows(const T *__restrict__ X, l
     if (pad_all_rows<T>(X, N, d, rb, permute, exponent, Xp)) *nonfinite = 1u;
 }
 
+
+// The half-precision copy of float32 rows that the first form's Gram block is computed from: row i is h_i, the binary16
+// rounding of (x_i - centre) 2^exponent, zeros up to rowbytes.  Distances do not depend on the centre, the mean of a
+// sample of rows, which keeps the rounding small for rows far from the origin; the exponent puts the sample's root mean
+// square near 2^-4, so that coordinates a million times larger still fit (what does not, or is not finite, becomes a NaN,
+// and every pair of its row is left to the exact routine).  With r_i = |(x_i - centre) 2^exponent - h_i|, a Euclidean norm
+// measured for every row in double precision, r_i <= share |h_i| + rest holds for all rows.
+struct HalfPar {
+    u32 share_bits, rest_bits;     // bits of non-negative floats order like the floats
+    int exponent, pad;
+};
+struct HalfRows {
+    const char *rows = nullptr;
+    u32 rowbytes = 0;
+    const HalfPar *par = nullptr;
+};
+#define HALF_SAMPLE 512          // rows the centre is the mean of
+
+// centre[c] = mean of coordinate c over the sample, square[b] = sum of the squared deviations of the 64 coordinates of block b.
+__global__ __launch_bounds__(256) void k_half_centre(const float *__restrict__ X, long long N, int d, float *__restrict__ centre,
+                                                     float *__restrict__ square, HalfPar *__restrict__ par)
+{
+    __shared__ float s[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c = blockIdx.x * 64 + lane, n = (int)(N < HALF_SAMPLE ? N : HALF_SAMPLE);
+    const float *col = X + (c < d ? c : d - 1);
+    if (blockIdx.x == 0 && threadIdx.x == 0) par->share_bits = par->rest_bits = 0u;
+    float sum = 0.f;
+#pragma unroll 16
+    for (int i = wave; i < n; i += 4) {
+        const float x = col[(size_t)(i * N / n) * d];
+        sum += fabsf(x) <= 3.0e38f ? x * (1.f / HALF_SAMPLE) : 0.f;
+    }
+    s[wave][lane] = sum;
+    __syncthreads();
+    const float mean = (s[0][lane] + s[1][lane] + s[2][lane] + s[3][lane]) * ((float)HALF_SAMPLE / (float)n);
+    __syncthreads();
+    sum = 0.f;
+#pragma unroll 16
+    for (int i = wave; i < n; i += 4) {
+        const float x = col[(size_t)(i * N / n) * d] - mean;
+        sum += fabsf(x) <= 1.0e16f ? x * x : 0.f;
+    }
+    s[wave][lane] = c < d ? sum : 0.f;
+    __syncthreads();
+    if (wave == 0) {
+        if (c < d) centre[c] = mean;
+        sum = s[0][lane] + s[1][lane] + s[2][lane] + s[3][lane];
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+        if (lane == 0) square[blockIdx.x] = sum;
+    }
+}
+
+// L lanes per row, 8 coordinates (16 bytes of the copy) per lane and trip.
+template <int L>
+__global__ __launch_bounds__(256) void k_half_rows(const float *__restrict__ X, long long N, int d, int vec_ok, u32 rowbytes,
+                                                   const float *__restrict__ centre, const float *__restrict__ square,
+                                                   char *__restrict__ H, HalfPar *__restrict__ par)
+{
+    __shared__ float s[4][2];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = lane & (L - 1);
+    const int n = (int)(N < HALF_SAMPLE ? N : HALF_SAMPLE), nsq = (d + 63) / 64;
+    double tot = 0.0;
+    for (int k = lane; k < nsq; k += 64) tot += (double)square[k];
+    for (int o = 32; o > 0; o >>= 1) tot += __builtin_bit_cast(double, shfl_xor_u64(__builtin_bit_cast(u64, tot), o));
+    const float ms = (float)(tot / ((double)n * (double)d));
+    int e = ms > 0.f && ms < 3.0e38f ? -4 - (ilogbf(ms) >> 1) : 0;
+    e = e < -60 ? -60 : e > 60 ? 60 : e;
+    if (blockIdx.x == 0 && threadIdx.x == 0) par->exponent = e;
+    const float scale = ldexpf(1.f, e);
+    const int pieces = (int)(rowbytes / 16u);
+    const float small = (float)d * 0x1p-18f;
+    float share = 0.f, rest = 0.f;
+    for (u64 row = ((u64)blockIdx.x * 256u + threadIdx.x) / L; row < (u64)N; row += (u64)gridDim.x * (256u / L)) {
+        const float *x = X + row * (u64)d;
+        double err = 0.0;
+        float nrm = 0.f;
+        for (int p = sub; p < pieces; p += L) {
+            v8h h;
+            float v[8], m[8];
+            if (vec_ok && 8 * p + 8 <= d) {
+                *(float4 *)&v[0] = ((const float4 *)(x + 8 * p))[0];
+                *(float4 *)&v[4] = ((const float4 *)(x + 8 * p))[1];
+                *(float4 *)&m[0] = ((const float4 *)(centre + 8 * p))[0];
+                *(float4 *)&m[4] = ((const float4 *)(centre + 8 * p))[1];
+            } else {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const int c = 8 * p + k;
+                    v[k] = c < d ? x[c] : 0.f;
+                    m[k] = c < d ? centre[c] : 0.f;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const float t = (v[k] - m[k]) * scale;
+                h[k] = fabsf(t) <= 65504.f ? (_Float16)t : (_Float16)__uint_as_float(0x7FC00000u);
+                const float hf = (float)h[k];
+                const double r = ((double)v[k] - (double)m[k]) * (double)scale - (double)hf;
+                err = fma(r, r, err);
+                nrm = fmaf(hf, hf, nrm);
+            }
+            *(v8h *)(H + row * (u64)rowbytes + 16u * (u32)p) = h;
+        }
+#pragma unroll
+        for (int o = L / 2; o > 0; o >>= 1) {
+            err += __builtin_bit_cast(double, shfl_xor_u64(__builtin_bit_cast(u64, err), o));
+            nrm += __shfl_xor(nrm, o);
+        }
+        // a row of NaN compares false and counts for neither
+        if (nrm >= small) share = fmaxf(share, (float)sqrt(err / (double)nrm));
+        else if (nrm < small) rest = fmaxf(rest, (float)sqrt(err));
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        share = fmaxf(share, __shfl_xor(share, o));
+        rest = fmaxf(rest, __shfl_xor(rest, o));
+    }
+    if (lane == 0) { s[wave][0] = share; s[wave][1] = rest; }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        float m = fmaxf(fmaxf(s[0][threadIdx.x], s[1][threadIdx.x]), fmaxf(s[2][threadIdx.x], s[3][threadIdx.x]));
+        if (m > 0.f) atomicMax(threadIdx.x ? &par->rest_bits : &par->share_bits, __float_as_uint(m));
+    }
+}
+
 // bits [lo, hi) of a 96-bit mask, as word c (bits 32c .. 32c+31)
 __device__ __forceinline__ u32 range_word(int lo, int hi, int c)
 {
@@ -334,17 +459,20 @@ __device__ __forceinline__ int popc_below_w(u64 m0, u64 m1, int p)
 //
 // The work list: entries 0 .. n_first - 1 are list[0 ..], entries n_first .. n_active - 1 follow `skip` places further on
 // (a second degree class that the same shape serves).
-template <int NG, int CH, int NRC, bool FAST, int DT>
+template <int NG, int CH, int NRC, bool FAST, int DT, bool HALF = false>
 __device__ __forceinline__ void f32_scan_body(
-    const char *__restrict__ X, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
+    const char *__restrict__ X, const HalfRows &half, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
     const int *__restrict__ list, u32 n_first, size_t skip, u32 n_active, Prop *__restrict__ props, int *__restrict__ nprop,
     RoundCtr *__restrict__ ctr, int *__restrict__ redo, u32 *__restrict__ n_redo, F32ScanSmem<NRC> &sm, u32 block, u32 nblocks)
 {
     typedef typename GramAcc<FAST>::type acc_t;
     // 16-bit rows in the single-precision form: the matrix instruction takes them as they are
-    constexpr bool NATIVE16 = FAST && (DT == DT_F16 || DT == DT_BF16);
-    const double epsk = NATIVE16 ? (0.5 * (double)d + 20.0) * 5.9604644775390625e-08
-                                 : (1.5 * (double)d + 20.0) * 5.9604644775390625e-08;
+    static_assert(!HALF || (FAST && DT == DT_F32), "the half-precision copy serves the first form on float32 rows");
+    constexpr int GDT = HALF ? DT_F16 : DT;       // what the Gram block is computed from
+    constexpr bool NATIVE16 = FAST && (GDT == DT_F16 || GDT == DT_BF16);
+    const int dg = HALF ? (int)(half.rowbytes / 2u) : d;
+    const double epsk = NATIVE16 ? (0.5 * (double)dg + 20.0) * 5.9604644775390625e-08
+                                 : (1.5 * (double)dg + 20.0) * 5.9604644775390625e-08;
     const double epsk64 = (2.0 * (double)d + 24.0) * 1.1102230246251565e-16;      // double-precision form
     constexpr int NT = NRC * (NRC + 1) / 2;
     constexpr int NWD = (NRC + 1) / 2;        // 32-bit words of a mask over slots
@@ -354,7 +482,12 @@ __device__ __forceinline__ void f32_scan_body(
     const int r16 = lane & 15, q = lane >> 4, sub = lane & 7, grp = lane >> 3;
     const u32 gw = block * 4 + wave, nw = nblocks * 4;
     const u32 rowbytes = (u32)d * (u32)dt_size(DT);     // at most a few hundred KB
-    const int nchunk = (int)(rowbytes / (64u * CH));
+    const char *__restrict__ G = HALF ? half.rows : X;      // rows of the Gram block
+    const u32 growbytes = HALF ? half.rowbytes : rowbytes;
+    const int nchunk = (int)(growbytes / (64u * CH));
+    // rounded up: what the sums of k_half_rows and the square roots here may have lost
+    const float gam = HALF ? 1.0001f * __uint_as_float(half.par->share_bits) : 0.f, bet = HALF ? 1.0001f * __uint_as_float(half.par->rest_bits) : 0.f;
+    const int e2 = HALF ? 2 * half.par->exponent : 0;
     u64 tiles = 0, rows = 0, nprops_total = 0, pair_evals = 0;
     u32 ev_lane = 0;
 
@@ -400,7 +533,8 @@ __device__ __forceinline__ void f32_scan_body(
                     const int s = in ? (isnew ? sn : so) : p;
                     sm.key[s] = in ? kreg[h] : 0ull;
                     sm.pos[s] = p;
-                    sm.distf[s] = in ? __uint_as_float(key_dist(kreg[h])) : 0.f;
+                    const float du = in ? __uint_as_float(key_dist(kreg[h])) : 0.f;
+                    sm.distf[s] = HALF ? ldexpf(du, e2) : du;
                 }
             }
             rows += m;
@@ -412,7 +546,7 @@ __device__ __forceinline__ void f32_scan_body(
             for (int g = 0; g < NRC; ++g) {
                 const int s = 16 * g + r16;
                 const int id = s < m ? (int)key_id(sm.key[s]) : 0;      // lanes without a row read row 0
-                rp[g] = X + (size_t)id * rowbytes + 16 * q;
+                rp[g] = G + (size_t)id * growbytes + 16 * q;
             }
             // ---- Gram block over d in chunks of 16 dimensions: the tiles whose column group holds a new slot
             acc_t acc[NT];
@@ -439,12 +573,12 @@ __device__ __forceinline__ void f32_scan_body(
             }
             if constexpr (FAST) {
                 if (NRC == 1) {
-                    gram_f32_loop<NRC, CH, 1u, DT>(rp, nchunk, acc, nr, need_g);
+                    gram_f32_loop<NRC, CH, 1u, GDT>(rp, nchunk, acc, nr, need_g);
                 } else if (NRC == 2) {
-                    if (NATIVE16 || need == 7u) gram_f32_loop<NRC, CH, 7u, DT>(rp, nchunk, acc, nr, need_g);
-                    else gram_f32_loop<NRC, CH, 3u, DT>(rp, nchunk, acc, nr, need_g);
+                    if (NATIVE16 || need == 7u) gram_f32_loop<NRC, CH, 7u, GDT>(rp, nchunk, acc, nr, need_g);
+                    else gram_f32_loop<NRC, CH, 3u, GDT>(rp, nchunk, acc, nr, need_g);
                 } else {
-                    gram_f32_loop<NRC, CH, 0u, DT>(rp, nchunk, acc, nr, need_g);
+                    gram_f32_loop<NRC, CH, 0u, GDT>(rp, nchunk, acc, nr, need_g);
                 }
             } else {
                 if (NRC == 1) {
@@ -480,17 +614,23 @@ __device__ __forceinline__ void f32_scan_body(
             // group I as the tested row, bit c = column slot c of group J.  FB[t] (I != J): lane r16 = slot r16
             // of group J as the tested row, bit c = column slot c of group I.  (Same in all quarter-waves.)
             u32 FA[NT], FB[NT];
-            const float epskf = (float)epsk, epsaf = (float)(8 * d + 8) * 1.17549435e-38f;
+            const float epskf = (float)epsk;
+            const float epsaf = HALF ? ldexpf(1.f, -120 + (e2 > 0 ? e2 : 0)) : (float)(8 * d + 8) * 1.17549435e-38f;
 #pragma unroll
             for (int I = 0; I < NRC; ++I) {
                 // single-precision form: the rows of group I that this lane's accumulators stand for
                 float nIf[4], dIf[4], tIf[4];     // n, delta(u, .), n's part of the bound
+                float qIf[4], rIf[4];             // half-precision copy: 2 sqrt(delta(u, .)), distance of the row from its copy
                 if (FAST) {
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         nIf[v] = sm.nrmf[16 * I + 4 * q + v];
                         dIf[v] = sm.distf[16 * I + 4 * q + v];
                         tIf[v] = epskf * nIf[v];
+                        if constexpr (HALF) {
+                            qIf[v] = 2.000002f * __builtin_amdgcn_sqrtf(dIf[v]);
+                            rIf[v] = fmaf(gam, __builtin_amdgcn_sqrtf(nIf[v]), bet);
+                        }
                     }
                 }
 #pragma unroll
@@ -507,6 +647,8 @@ __device__ __forceinline__ void f32_scan_body(
                             // delta(v,w), which the bound's constant covers
                             const float dj = sm.distf[16 * J + r16];
                             const float nJf = (float)nr[J], tJf = fmaf(epskf, nJf, epsaf);
+                            const float qJf = HALF ? 2.000002f * __builtin_amdgcn_sqrtf(dj) : 0.f;
+                            const float rJf = HALF ? fmaf(gam, __builtin_amdgcn_sqrtf(nJf), bet) : 0.f;
                             // The outcomes with group I's slot as the tested row are taken as wavefront-wide masks:
                             // accumulator v of lane (r16, q) is (row 4q + v, column r16), so bit 16q + c of the mask
                             // of accumulator v is (row 4q + v, column c), and the row a lane stands for, r16, finds
@@ -517,12 +659,18 @@ __device__ __forceinline__ void f32_scan_body(
                                 const int rsel = 4 * q + v;
                                 const float nsum = nIf[v] + nJf;
                                 const float dvw = fmaf(-2.f, acc[t][v], nsum);
-                                const float tol = tIf[v] + tJf;
+                                float tol = tIf[v] + tJf, tolb = tol;
+                                if constexpr (HALF) {
+                                    const float rs = rIf[v] + rJf;
+                                    tol = fmaf(rs, rs, tol);
+                                    tolb = fmaf(qJf, rs, tol);
+                                    tol = fmaf(qIf[v], rs, tol);
+                                }
                                 const float ta = dIf[v] - dvw, tb = dj - dvw;
                                 fire_m[v] = __builtin_amdgcn_ballot_w64(ta >= 0.f);
                                 amb_m[v] = __builtin_amdgcn_ballot_w64(!(fabsf(ta) > tol));      // also when not finite
                                 fb |= (tb >= 0.f) ? (1u << rsel) : 0u;
-                                fb |= !(fabsf(tb) > tol) ? (0x10000u << rsel) : 0u;
+                                fb |= !(fabsf(tb) > tolb) ? (0x10000u << rsel) : 0u;
                             }
                             const int vs = r16 & 3, sh = 16 * (r16 >> 2);
                             const u64 mf = vs == 0 ? fire_m[0] : vs == 1 ? fire_m[1] : vs == 2 ? fire_m[2] : fire_m[3];
@@ -601,13 +749,70 @@ __device__ __forceinline__ void f32_scan_body(
             // ---- the undecided pairs get the exact delta(v,w)
             bool defer = false;
             {
+                u32 some = 0;
+#pragma unroll
+                for (int e = 0; e < NSET; ++e)
+#pragma unroll
+                    for (int c = 0; c < NWD; ++c) some |= Aw[e][c];
+                const bool undecided = __builtin_amdgcn_ballot_w64(some != 0) != 0ull;     // most vertices have no undecided pair at all
+                if (undecided) {
+                    // Only pairs that can matter are resolved.  `lo`: rows kept however the undecided pairs turn out, `hi`:
+                    // rows not pruned for certain; row s is settled after rank(s) + 1 sweeps.  A pair (s, t) is without effect if
+                    // t is not in hi, or comes after a column of lo that s fails against for certain.
+                    u64 lo0 = 0, hi0 = val0, lo1 = 0, hi1 = val1;
+                    for (int sweep = 0; sweep < 16 * NRC + 1; ++sweep) {
+                        bool may0 = false, may1 = false, must0 = false, must1 = false;
+#pragma unroll
+                        for (int c = 0; c < NWD; ++c) {
+                            const u32 hc = c == 0 ? (u32)hi0 : c == 1 ? (u32)(hi0 >> 32) : (u32)hi1;
+                            may0 = may0 || (((Fw[0][c] | Aw[0][c]) & hc) != 0);
+                            if (NSET > 1) may1 = may1 || (((Fw[NSET - 1][c] | Aw[NSET - 1][c]) & hc) != 0);
+                        }
+                        lo0 = val0 & ~__builtin_amdgcn_ballot_w64(may0);
+                        if (NSET > 1) lo1 = val1 & ~__builtin_amdgcn_ballot_w64(may1);
+#pragma unroll
+                        for (int c = 0; c < NWD; ++c) {
+                            const u32 lc = c == 0 ? (u32)lo0 : c == 1 ? (u32)(lo0 >> 32) : (u32)lo1;
+                            must0 = must0 || ((Fw[0][c] & lc) != 0);
+                            if (NSET > 1) must1 = must1 || ((Fw[NSET - 1][c] & lc) != 0);
+                        }
+                        const u64 h0 = val0 & ~__builtin_amdgcn_ballot_w64(must0);
+                        const u64 h1 = NSET > 1 ? val1 & ~__builtin_amdgcn_ballot_w64(must1) : 0ull;
+                        if (h0 == hi0 && h1 == hi1) break;
+                        hi0 = h0;
+                        hi1 = h1;
+                    }
+                    const u32 lov[3] = {(u32)lo0, (u32)(lo0 >> 32), (u32)lo1}, hiv[3] = {(u32)hi0, (u32)(hi0 >> 32), (u32)hi1};
+#pragma unroll
+                    for (int e = 0; e < NSET; ++e) {
+                        int tn = -1, to = -1;
+#pragma unroll
+                        for (int c = NWD - 1; c >= 0; --c) {
+                            const u32 fk = Fw[e][c] & lov[c];
+                            const u32 fn = fk & range_word(0, n_new, c), fo = fk & ~range_word(0, n_new, c);
+                            if (fn) tn = 32 * c + __builtin_ctz(fn);
+                            if (fo) to = 32 * c + __builtin_ctz(fo);
+                        }
+                        const int tgt = (tn >= 0 && to >= 0) ? (sm.pos[tn] < sm.pos[to] ? tn : to) : (tn >= 0 ? tn : to);
+                        const int tl = tgt >= 0 ? (tgt & 15) + 16 * ((tgt >> 4) & 3) : lane;
+#pragma unroll
+                        for (int c = 0; c < NWD; ++c) {
+                            u32 upto = (u32)__shfl((int)Bw[0][c], tl);
+                            if (NSET > 1) {
+                                const u32 hi = (u32)__shfl((int)Bw[NSET - 1][c], tl);
+                                upto = (tgt >> 6) ? hi : upto;
+                            }
+                            Aw[e][c] &= hiv[c] & (tgt < 0 ? 0xFFFFFFFFu : upto);
+                        }
+                    }
+                }
                 int mine = 0;
 #pragma unroll
                 for (int e = 0; e < NSET; ++e)
 #pragma unroll
                     for (int c = 0; c < NWD; ++c) mine += __popc(Aw[e][c]);
                 int incl = mine, total = 0;
-                if (__builtin_amdgcn_ballot_w64(mine != 0) != 0ull) {     // most vertices have no undecided pair at all
+                if (undecided) {
 #pragma unroll
                     for (int o = 1; o < 64; o <<= 1) {
                         const int up = __shfl_up(incl, o);
@@ -806,7 +1011,7 @@ __global__ __launch_bounds__(64 * 4, (NRC <= 2 ? 4 : NRC <= 5 ? 2 : 1)) void k_u
     __shared__ F32ScanSmem<NRC> smem[4];
     stamp_scan_start(ctr);
     const u32 n = *n_list;
-    f32_scan_body<NG, CH, NRC, false, DT>(X, d, R, keys, deg, list, n, 0, n, props, nprop, ctr, nullptr, nullptr,
+    f32_scan_body<NG, CH, NRC, false, DT>(X, HalfRows(), d, R, keys, deg, list, n, 0, n, props, nprop, ctr, nullptr, nullptr,
                                           smem[threadIdx.x >> 6], blockIdx.x, gridDim.x);
 }
 
@@ -816,9 +1021,9 @@ __global__ __launch_bounds__(64 * 4, (NRC <= 2 ? 4 : NRC <= 5 ? 2 : 1)) void k_u
 // block then has the registers of the longest shape.  Larger inputs take the classes that need about the same number
 // of registers together: up to 32 entries (C0 = 0), 33 .. 64 (C0 = 3), 65 .. 96 (C0 = 5); many long float32 rows the first of these
 // in two parts, up to 16 and (C0 = 2) 17 .. 32.
-template <int NRCMAX, int C0, int CH, int DT>
+template <int NRCMAX, int C0, int CH, int DT, bool HALF = false>
 __global__ __launch_bounds__(64 * 4, (NRCMAX <= 2 ? 4 : NRCMAX <= 4 ? 3 : 2)) void k_update_scan_mfma_f32_all(
-    const char *__restrict__ X, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
+    const char *__restrict__ X, HalfRows half, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
     const int *__restrict__ lists, long long N, Prop *__restrict__ props, int *__restrict__ nprop,
     RoundCtr *__restrict__ ctr, int *__restrict__ redo, u32 *__restrict__ n_redo)
 {
@@ -846,7 +1051,7 @@ __global__ __launch_bounds__(64 * 4, (NRCMAX <= 2 ? 4 : NRCMAX <= 4 ? 3 : 2)) vo
     if (k < 0) return;
     const int wave = threadIdx.x >> 6;
 #define RNND_F32_SHAPE(K_, NG_, CH_, NRC_)                                                                            \
-    f32_scan_body<NG_, CH_, NRC_, true, DT>(X, d, R, keys, deg, lists + (size_t)first_class[K_] * N, n1[K_],           \
+    f32_scan_body<NG_, CH_, NRC_, true, DT, HALF>(X, half, d, R, keys, deg, lists + (size_t)first_class[K_] * N, n1[K_],           \
                                             (size_t)N - n1[K_], n[K_], props, nprop, ctr, redo, n_redo,                \
                                             *reinterpret_cast<F32ScanSmem<NRC_> *>(&smem[wave]), block, mine)
     if constexpr (C0 == 0)
