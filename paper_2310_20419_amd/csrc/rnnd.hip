@@ -22,86 +22,30 @@
 
 #include "../../include/rnnd.h"
 #include "wave_prims.h"
+#include "round.h"
 
 #define WAVES_PER_BLOCK 4
 #define BLOCK (64 * WAVES_PER_BLOCK)
 #define GOLDEN64 0x9E3779B97F4A7C15ull
 #define RNND_MAX_SLOTS 0x7FFFFF00ull   // N * (slots per row): bin offsets are ints, -1 = no bin
 #define RNND_MAX_RUN_SLOTS 131072      // rounds (x runs per pass): one small counter block each
-#define NDEG 8   // degree classes of the active lists (see degree_class)
-#define NMRG 4   // merge classes of the touched lists: kept + received at most 16, 32, 64, more
 #ifndef INBOX_CAP
 #define INBOX_CAP 64   // redirected edges a vertex can receive per round without the overflow path
 #endif
 
-// Per-round device counters.  Round t reads ctr[t].n_active[] and fills the rest; its compact step
-// writes ctr[t+1].n_active[].  Zeroed once per call, never reset, so they double as statistics.
-#define STAT_SLOTS 64
-struct RoundCtr {
-    u32 n_active[NDEG];   // lengths of this round's active lists
-    u32 n_touched[NMRG];  // distinct targets of the redirected edges, by size of the merge they need
-    u32 nonfinite;        // slot 0: k_prepare_rows met a coordinate that is NaN or infinite
-    u32 pad[3];
-    u32 n_redo[NDEG];     // float scan: vertices the single-precision form left to the double-precision one
-    // ticks of the device's constant-rate clock (0 = not taken): the round's first scan launch starts, its scatter
-    // starts (= the scan has ended: launches of one stream run back to back), the round's last kernel has ended
-    // (taken by k_stamp after the last round before an AddReverseEdges call or the export, only where statistics
-    // ask for it; every other round, and an AddReverseEdges call, ends where the next round's scan starts)
-    u64 t_scan_start, t_scan_stop, t_round_stop;
-    // statistics, spread over STAT_SLOTS addresses so that the adds of many blocks do not queue up
-    // on one: [slot][0..4] = algorithmic evals, executed evals, rows gathered, edges redirected, entries a merge
-    // dropped because the list was full
-    u64 stat[STAT_SLOTS][5];
-};
-
-// One add per wavefront into the slot of its block.
-__device__ __forceinline__ void add_round_stats(RoundCtr *ctr, u64 algo, u64 exec, u64 rows, u64 props)
-{
-    u64 *s = ctr->stat[blockIdx.x & (STAT_SLOTS - 1)];
-    atomicAdd(&s[0], algo);
-    atomicAdd(&s[1], exec);
-    atomicAdd(&s[2], rows);
-    atomicAdd(&s[3], props);
-}
-
-// Statistics take the scan time of a round from the device's own clock instead of events attached to the launches:
-// an event costs 4-7 microseconds of idle queue after its kernel, three per round used to add 1 ms to a 27 ms build.
-__device__ __forceinline__ void stamp_scan_start(RoundCtr *ctr)
-{   // the first scan launch of a round that comes by fills the field
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && ctr->t_scan_start == 0ull) ctr->t_scan_start = wall_clock64();
-}
-__device__ __forceinline__ void stamp_scan_stop(RoundCtr *ctr)
-{
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) ctr->t_scan_stop = wall_clock64();
-}
-__global__ void k_stamp(u64 *dst) { if (threadIdx.x == 0) *dst = wall_clock64(); }
-
-struct Prop {          // one redirected edge (Alg. 4, the edge update): `key` enters `tgt`'s list
-    u64 key;
-    u32 tgt;
-    u32 next;          // set by the scatter for edges past the inbox: the edge (its place in props) that was on tgt's list before
-};
-
-// The edge update of Alg. 4: (w, v) enters E.  Recorded in the scanning vertex's own slot.
-__device__ __forceinline__ void emit_redirect(u64 key, u32 tgt, Prop *slot)
-{
-    Prop pr;
-    pr.key = key;
-    pr.tgt = tgt;
-    pr.next = 0;
-    *slot = pr;
-}
-
 #include "dist.h"
-#include "scan_mfma.h"
+#include "scan_u8.h"
 #include "scan_pairs.h"
-#include "scan_mfma_f32.h"
+#include "padded_rows.h"
+#include "launch.h"
 #include "search.h"
 
+__global__ void k_stamp(u64 *dst) { if (threadIdx.x == 0) *dst = wall_clock64(); }
+
 // Degree class of a list of m entries: which scan kernel takes it.  use_classes 0: one list for all
-// (generic scan).  2 (uint8 matrix-core scan): classes 0, 1, 2 = at most 8, 16, 32 entries (four, two,
+// (generic scan).  2 (uint8 and 16-bit matrix-core scans): classes 0, 1, 2 = at most 8, 16, 32 entries (four, two,
 // one vertex per wavefront), 3, 4, 5 = at most 64, 96, 128 (two, three, four 32-row blocks).
-// 1 (float matrix-core scan, 16-row groups): classes 0..6 = at most 8, 16, 32, 48, 64, 80, 96 entries
+// 1 (scan of whole float32 rows, 16-row groups): classes 0..6 = at most 8, 16, 32, 48, 64, 80, 96 entries
 // (1, 1, 2, 3, 4, 5, 6 groups), 7 = more (generic scan).
 __device__ __forceinline__ int degree_class(int m, int use_classes)
 {
@@ -329,6 +273,7 @@ __device__ __forceinline__ u32 same_target_mask(u32 tgt, int sub)
 // bytes / now: rows of 8 slots 19.5 / 78.6 / 19.7 ms, of 16 19.5 / 40.4 / 19.7, of 96 19.5 / 20.8 / 19.8, the last because the links
 // of a chunk are asked for while the one before it is sorted; 7,000 edges, 8 slots: 0.29 / 0.87 / 0.28.)
 #define LATE_LISTS 64
+#define LATE_OPEN 512     // float rows: late edges of a vertex whose distances its merge computes
 static __host__ __device__ inline int round_inbox(int R) { return R < 32 ? 32 : INBOX_CAP; }
 
 // list head l of vertex x is at [x * stride + l]
@@ -342,6 +287,41 @@ static __host__ __device__ inline LateHeads late_heads(u64 *inbox, u64 *bins, in
     h.base = R < 32 ? (u32 *)(inbox + 32) : (u32 *)bins;
     h.stride = R < 32 ? 2u * INBOX_CAP : (u32)LATE_LISTS;
     return h;
+}
+
+// Redirected edges of the float scans arrive without their distances (OPEN_DIST).  Computes them for the lanes whose key (of a
+// vertex in the list of vertex x) is open, in 8-lane groups, in the order the wavefront holds them; every lane of the
+// wavefront takes part.  DT_U8: nothing is ever open.
+struct OpenEdges {
+    uint2 edge[64];
+    u32 dist[64];
+};
+template <int DT>
+__device__ __forceinline__ u64 close_keys(u64 key, int x, bool have, OpenEdges *s, const char *__restrict__ X, int d, int lane)
+{
+    if constexpr (DT == DT_U8) {
+        return key;
+    } else {
+        const bool open = have && key_dist(key) == OPEN_DIST;
+        const u64 om = __builtin_amdgcn_ballot_w64(open);
+        const int total = __popcll(om);
+        if (total == 0) return key;
+        const size_t rb = (size_t)d * dt_size(DT);
+        const int mine = __popcll(om & lanes_below(lane)), grp = lane >> 3, sub = lane & 7;
+        wave_sync();
+        if (open) s->edge[mine] = make_uint2(key_id(key), (u32)x);
+        wave_sync();
+        for (int b = 0; b < total; b += 8) {
+            const int e = b + grp;
+            if (e < total) {
+                const uint2 vw = s->edge[e];
+                const u32 db = group8_dist_bits<DT, 3>(X + (size_t)vw.x * rb, X + (size_t)vw.y * rb, d, 1, sub);
+                if (sub == 0) s->dist[e] = db;
+            }
+        }
+        wave_sync();
+        return open ? make_key(s->dist[mine], key_id(key), 1u) : key;
+    }
 }
 
 // Every active vertex moves its redirected edges to their targets, 16 lanes per vertex.  Lanes of a
@@ -408,6 +388,26 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(long long N, int R, const int
     }
 }
 
+// Computes the open distances of the late edges of vertex x; group g of 8 lanes of the block walks list g.
+template <int DT>
+__device__ __attribute__((noinline)) void close_late(long long x, int late, LateHeads heads, Prop *props, const char *X, int d)
+{
+    const u32 l = threadIdx.x >> 3;
+    const int sub = threadIdx.x & 7;
+    if (l >= LATE_LISTS) return;
+    const size_t rb = (size_t)d * dt_size(DT);
+    u32 at = heads.base[(size_t)x * heads.stride + l];
+    for (int left = (late - (int)l + LATE_LISTS - 1) / LATE_LISTS; left > 0; --left) {
+        const u64 key = props[at].key;
+        const u32 next = props[at].next;
+        if (key_dist(key) == OPEN_DIST) {
+            const u32 db = group8_dist_bits<DT, 2>(X + (size_t)key_id(key) * rb, X + (size_t)x * rb, d, 1, sub);
+            if (sub == 0) props[at].key = make_key(db, key_id(key), 1u);
+        }
+        at = next;
+    }
+}
+
 // Merge class of a vertex that holds nb entries and received c: how wide a sort its merge needs.  cap = round_inbox(R):
 // the first three read received edges from the inbox only.
 __device__ __forceinline__ int merge_class(int nb, int c, int cap)
@@ -420,10 +420,14 @@ __device__ __forceinline__ int merge_class(int nb, int c, int cap)
 // TC_TILES x 1024 vertices and takes its space with one atomic per class.  Four tiles per block
 // keep the atomics of a 1M-vertex round few; on small inputs two tiles (twice the blocks, a shorter chain in
 // each) are faster: 100,000 vertices 4.68 -> 4.55 ms per build, 1M 26.0 -> 26.1 ms.
-template <int TC_TILES>
-__global__ __launch_bounds__(1024) void k_touch_classify(long long N, int cap, const int *cnt, const int *deg, RoundCtr *ctr, int *tlists)
+// Float rows: a hub's merge walks its late edges with one wavefront, which would also compute their open distances; for hubs
+// of more than LATE_OPEN late edges the block does that here, 8 lanes for each of the hub's lists.
+template <int TC_TILES, int DT>
+__global__ __launch_bounds__(1024) void k_touch_classify(long long N, int cap, const int *cnt, const int *deg, RoundCtr *ctr, int *tlists,
+                                                         LateHeads heads, Prop *props, const char *__restrict__ X, int d)
 {
     __shared__ u32 s_cnt[TC_TILES][16][NMRG], s_base[NMRG];
+    bool hub = false;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int mc[TC_TILES];
     u32 rank[TC_TILES];
@@ -434,6 +438,7 @@ __global__ __launch_bounds__(1024) void k_touch_classify(long long N, int cap, c
         if (x < N) {
             const int c = cnt[x];
             if (c > 0) mc[k] = merge_class(deg[x], c, cap);
+            if (DT != DT_U8) hub = hub || c > cap + LATE_OPEN;
         }
         rank[k] = 0;
 #pragma unroll
@@ -474,6 +479,20 @@ __global__ __launch_bounds__(1024) void k_touch_classify(long long N, int cap, c
         if (x < N && mc[k] >= 0)
             tlists[(size_t)mc[k] * N + s_base[mc[k]] + s_cnt[k][wave][mc[k]] + rank[k]] = (int)x;
     }
+    if constexpr (DT != DT_U8) {
+        __shared__ int s_hub[TC_TILES * 1024], s_hubs;
+        if (__syncthreads_or(hub) == 0) return;
+        if (threadIdx.x == 0) s_hubs = 0;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < TC_TILES; ++k) {
+            const long long x = ((long long)blockIdx.x * TC_TILES + k) * 1024 + threadIdx.x;
+            if (x < N && cnt[x] > cap + LATE_OPEN) s_hub[atomicAdd(&s_hubs, 1)] = (int)x;
+        }
+        __syncthreads();
+        const int n = s_hubs;
+        for (int h = 0; h < n; ++h) close_late<DT>(s_hub[h], cnt[s_hub[h]] - cap, heads, props, X, d);
+    }
 }
 
 // Merge of the touched vertices whose kept entries + received edges number at most G: one vertex per
@@ -503,24 +522,32 @@ __device__ __forceinline__ MergeItem merge_item_load(int x, int R, const u64 *ke
     return m;
 }
 
-template <int G>
+template <int G, int DT>
 __device__ __forceinline__ void merge_group_body(int R, u64 *keys, int *deg, const int *tlist,
                                                  const u32 *n_ptr, int *cnt, const u64 *inbox,
-                                                 int8_t *tcls, int use_classes, RoundCtr *ctr)
+                                                 int8_t *tcls, int use_classes, RoundCtr *ctr, OpenEdges *s_open,
+                                                 const char *__restrict__ X, int d)
 {
     int dropped = 0;
     static_assert(G <= INBOX_CAP, "a group merge reads the received edges from the inbox only");
-    const int lane = threadIdx.x & 63, sub = lane & (G - 1), shift = lane & ~(G - 1);
+    int lane = threadIdx.x & 63, sub = lane & (G - 1), shift = lane & ~(G - 1);
     const u64 gmask = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1ull);
     const u32 gid = (blockIdx.x * BLOCK + threadIdx.x) / G, ngrp = (gridDim.x * BLOCK) / G;
     const u32 n = *n_ptr;
-    if (gid >= n) return;
+    if (gid - (DT == DT_U8 ? 0u : (u32)(lane / G)) >= n) return;
     // list indices fit 32 bits with room to spare: n <= 2^31 and three strides of the grid are far below 2^31
     auto vertex_at = [&](u32 i) -> int { const int v = tlist[i < n ? i : n - 1u]; return i < n ? v : -1; };
     MergeItem cur = merge_item_load<G>(vertex_at(gid), R, keys, deg, cnt, inbox, sub);
     int x_next = vertex_at(gid + ngrp);
     int x_after = vertex_at(gid + 2u * ngrp);
-    for (u32 it = gid; it < n; it += ngrp) {
+    // (open distances are computed by the whole wavefront: it leaves the loop as one, groups past the end hold no vertex)
+    const u32 lead = DT == DT_U8 ? 0u : (u32)(lane / G);
+    for (u32 it = gid; it - lead < n; it += ngrp) {
+        if constexpr (DT != DT_U8) {
+            lane = afresh(lane);
+            sub = lane & (G - 1);
+            shift = lane & ~(G - 1);
+        }
         const MergeItem nxt = merge_item_load<G>(x_next, R, keys, deg, cnt, inbox, sub);
         x_next = x_after;
         x_after = vertex_at(it + 3u * ngrp);
@@ -530,6 +557,7 @@ __device__ __forceinline__ void merge_group_body(int R, u64 *keys, int *deg, con
         u64 k = KEY_PAD;
         if (sub < nb) k = cur.kr;
         else if (G - 1 - sub < c) k = cur.ki;
+        k = close_keys<DT>(k, x, sub >= nb && G - 1 - sub < c, s_open, X, d, lane);
         k = group_sort<G>(k, lane);
         u64 prev = shfl_up1_u64(k);
         if (sub == 0) prev = KEY_PAD;
@@ -539,7 +567,7 @@ __device__ __forceinline__ void merge_group_body(int R, u64 *keys, int *deg, con
         const bool w = keep && pos < R;
         if (w) row[pos] = k;
         const u64 nm = (__builtin_amdgcn_ballot_w64(w && (k & 1ull)) >> shift) & gmask;
-        if (sub == 0) {
+        if (sub == 0 && (DT == DT_U8 || x >= 0)) {
             int nd = __popcll(m);
             if (nd > R) { dropped += nd - R; nd = R; }
             deg[x] = nd;
@@ -591,15 +619,18 @@ __device__ __forceinline__ LateEdge late_edge(const Prop *props, u32 at, bool ha
     return e;
 }
 
+template <int DT>
 __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, const int *tlist,
                                                    const u32 *n_ptr, int *cnt, const u64 *inbox,
                                                    LateHeads heads, const Prop *props, int8_t *tcls,
-                                                   int use_classes, u64 (*s_stage)[RNND_MAX_R], RoundCtr *ctr)
+                                                   int use_classes, u64 (*s_stage)[RNND_MAX_R], RoundCtr *ctr,
+                                                   OpenEdges *s_open, const char *__restrict__ X, int d)
 {
     int dropped = 0;
     static_assert(INBOX_CAP == 64 && LATE_LISTS == 64, "lane l prefetches inbox slot 63 - l and walks list l");
     const int cap = round_inbox(R);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    int lane = threadIdx.x & 63;
     const u32 gw = blockIdx.x * WAVES_PER_BLOCK + wave, nw = gridDim.x * WAVES_PER_BLOCK;
     const u32 n = *n_ptr;
     if (gw >= n) return;
@@ -608,12 +639,14 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
     int x_next = vertex_at(gw + nw);
     int x_after = vertex_at(gw + 2u * nw);
     for (u32 it = gw; it < n; it += nw) {
+        if constexpr (DT != DT_U8) lane = afresh(lane);
         const WideItem nxt = wide_item_load(x_next, R, keys, deg, cnt, inbox, lane);
         x_next = x_after;
         x_after = vertex_at(it + 3u * nw);
 
         const int x = __builtin_amdgcn_readfirstlane(cur.x);
         const int nb = __builtin_amdgcn_readfirstlane(cur.nb), c = __builtin_amdgcn_readfirstlane(cur.c);
+        cur.in = close_keys<DT>(cur.in, x, 63 - lane < (c < cap ? c : cap), s_open, X, d, lane);
         bool any_new = false;
         int nd;
         if (c <= cap && nb + c <= 128) {
@@ -630,6 +663,7 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
                 // a full inbox, and at most one late edge per list: the lists from the top lane down, above the kept entries
                 u64 k[2];
                 k[0] = lane < nb ? cur.r0 : late_edge(props, 63 - lane < late ? head[63 - lane] : 0u, 63 - lane < late).key;
+                k[0] = close_keys<DT>(k[0], x, lane >= nb && 63 - lane < late, s_open, X, d, lane);
                 k[1] = 63 - lane < ca ? cur.in : KEY_PAD;
                 wave_sort<2>(k, lane);
                 nd = wave_unique_prefix<2>(k, lane, R, row, &any_new, &dropped);
@@ -641,7 +675,7 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
                 k[0] = lane < nb ? cur.r0 : KEY_PAD;
                 k[1] = lane + 64 < nb ? cur.r1 : KEY_PAD;
                 k[2] = 63 - lane < ca ? cur.in : KEY_PAD;
-                k[3] = first.key;
+                k[3] = close_keys<DT>(first.key, x, lane < late, s_open, X, d, lane);
                 LateEdge a = late_edge(props, first.next, LATE_LISTS + lane < late);
                 for (int at = LATE_LISTS;; at += 2 * LATE_LISTS) {      // edges taken so far; `a` is the next one of my list
                     wave_sort<4>(k, lane);
@@ -652,8 +686,8 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
                     k[1] = lane + 64 < nd ? s_stage[wave][lane + 64] : KEY_PAD;
                     wave_sync();
                     if (at >= late) break;
-                    k[2] = a.key;
-                    k[3] = b.key;
+                    k[2] = close_keys<DT>(a.key, x, at + lane < late, s_open, X, d, lane);
+                    k[3] = close_keys<DT>(b.key, x, at + LATE_LISTS + lane < late, s_open, X, d, lane);
                     a = late_edge(props, b.next, at + 2 * LATE_LISTS + lane < late);
                 }
                 if (lane < nd) row[lane] = k[0];
@@ -671,19 +705,22 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
 }
 
 // All four merge classes in one launch: blockIdx.y = merge class (touched list y, tcls + y*N).
-__global__ __launch_bounds__(BLOCK) void k_merge(long long N, int R, u64 *keys, int *deg, const int *tlists,
+template <int DT>
+__global__ __launch_bounds__(BLOCK, (DT == DT_U8 ? 1 : 5)) void k_merge(long long N, int R, u64 *keys, int *deg, const int *tlists,
                                                  const u32 *n_touched, int *cnt, const u64 *inbox,
                                                  LateHeads heads, const Prop *props, int8_t *tcls,
-                                                 int use_classes, RoundCtr *ctr)
+                                                 int use_classes, RoundCtr *ctr, const char *__restrict__ X, int d)
 {
     __shared__ u64 s_stage[WAVES_PER_BLOCK][RNND_MAX_R];
+    static_assert(sizeof(OpenEdges) <= sizeof(u64) * RNND_MAX_R, "the open edges lie in the stage, which is free until they are closed");
+    OpenEdges *so = reinterpret_cast<OpenEdges *>(&s_stage[threadIdx.x >> 6]);
     const int y = blockIdx.y;
     const int *tlist = tlists + (size_t)y * N;
     int8_t *tc = tcls + (size_t)y * N;
-    if (y == 0) merge_group_body<16>(R, keys, deg, tlist, n_touched + 0, cnt, inbox, tc, use_classes, ctr);
-    else if (y == 1) merge_group_body<32>(R, keys, deg, tlist, n_touched + 1, cnt, inbox, tc, use_classes, ctr);
-    else if (y == 2) merge_group_body<64>(R, keys, deg, tlist, n_touched + 2, cnt, inbox, tc, use_classes, ctr);
-    else merge_general_body(R, keys, deg, tlist, n_touched + 3, cnt, inbox, heads, props, tc, use_classes, s_stage, ctr);
+    if (y == 0) merge_group_body<16, DT>(R, keys, deg, tlist, n_touched + 0, cnt, inbox, tc, use_classes, ctr, so, X, d);
+    else if (y == 1) merge_group_body<32, DT>(R, keys, deg, tlist, n_touched + 1, cnt, inbox, tc, use_classes, ctr, so, X, d);
+    else if (y == 2) merge_group_body<64, DT>(R, keys, deg, tlist, n_touched + 2, cnt, inbox, tc, use_classes, ctr, so, X, d);
+    else merge_general_body<DT>(R, keys, deg, tlist, n_touched + 3, cnt, inbox, heads, props, tc, use_classes, s_stage, ctr, so, X, d);
 }
 
 // Items i < n with cls[first + i] >= 0 are appended to list cls[first + i]; item i stands for vertex idx[i]
@@ -1404,28 +1441,6 @@ static int g_scan_launches = 0;    // uint8 matrix-core scan: 0 by size, 1 short
                                    // launches per class: 0.75 x at 50,000 vertices, 0.78 x at 100,000, 0.90 x at 300,000, 0.955 x
                                    // at 500,000; 1.02 x at 1M, where it wins only in rounds with fewer than 250,000 active lists).
                                    // Above: the short-list launch and one launch for all longer classes (0.99 x at 1M)
-// Float scan: up to here one launch for all classes, which costs the shorter lists their occupancy; above, a launch for each of
-// lists of up to 32, 64 and 96 entries.  Whole builds, S = 20, 60 rounds, three launches / one, ms:
-//   R = 96          20,000        32,000        50,000         70,000         100,000         200,000
-//   float32   96    4.05 / 3.83   5.33 / 5.49   7.61 / 8.11    9.97 / 11.0    13.7 / 16.1     27.4 / 34.4
-//   float32  304    6.63 / 6.28   9.62 / 9.41   14.7 / 14.8    20.3 / 21.0    29.3 / 31.4     61.4 / 69.4
-//   float16  320    5.12 / 4.80   6.99 / 6.91   9.90 / 10.3    13.1 / 14.2    18.1 / 20.4     35.8 / 42.5
-//   bfloat16 128    3.87 / 3.62   5.04 / 5.01   7.08 / 7.28    9.16 / 9.75    12.6 / 14.0     24.1 / 29.1
-//   bfloat16 768    9.83 / 7.88   12.4 / 11.1   17.0 / 16.2    22.2 / 22.1    30.5 / 31.2     60.9 / 67.5
-//   R = 64
-//   float32   96    3.85 / 3.55   5.07 / 4.88   7.08 / 7.01    9.36 / 9.42    12.8 / 13.2     25.2 / 26.4
-//   float32  304    6.27 / 5.72   9.18 / 8.55   13.8 / 13.0    19.1 / 18.3    27.3 / 26.4     55.6 / 53.9
-//   float16  320    4.89 / 4.42   6.64 / 6.22   9.36 / 9.06    12.4 / 12.3    17.0 / 17.2     32.6 / 34.0
-//   bfloat16 128    3.71 / 3.38   4.76 / 4.51   6.63 / 6.34    8.63 / 8.39    11.7 / 11.6     22.0 / 22.6
-//   bfloat16 768    6.76 / 5.94   8.89 / 8.11   12.5 / 11.8    16.9 / 16.2    23.4 / 22.8     46.9 / 47.1
-// The lines suit rows of up to about 1 KB; longer ones would gain up to 5 % from later lines.
-#define SMALL_FLOAT_MAX_N_64 65536      // R <= 64
-#define SMALL_FLOAT_MAX_N_96 32768      // R > 64
-// Lists of up to 32 entries of long float32 rows: two launches (up to 16, 17 .. 32).  Two / one: 60-round builds of 96 coordinates 70,000
-// vertices 10.5 / 10.0 ms, 200,000 27.5 / 26.8, 1M 144.3 / 143.2, of 304 1M 312.5 / 310.6; of 960 150,000 113.0 / 112.0, 500,000 423.2 /
-// 424.9, 1M 917.4 / 924.1.  (16-bit rows always take one.)
-#define SPLIT_SHORT_LISTS_MIN_N 262144
-#define SPLIT_SHORT_LISTS_MIN_D 512
 #define LONG_SHARED_MAX_N 2097152  // ... up to here (1.00 x at 2M, 1.01 x at 4M, 1.00 x at 8M, 1.01 x at 20M: no start-up left to
                                    // share, and each class alone gets the occupancy that suits it); above: a launch per class
                                    // (bench.py names the round's scan launches by the same rule; include/rnnd.h states it)
@@ -1545,12 +1560,13 @@ static int vec_ok_for(const void *X, int d, int dtype)
 //             fit the tiles, or rows padded to a length the tiles take (dp coordinates; see k_prepare_*_rows)
 // The first two are what a call needs; padded rows are an extra a call does without (generic kernel) where there is
 // no room for them.
-// Row length in bytes of the half-precision copy of d coordinates: a multiple of 128, so that no row shares a cache line.
-static u32 half_row_bytes(int d) { return ((u32)d + 63u) / 64u * 128u; }
-// From how many vertices on a build's float32 scans take their Gram block from that copy (with / without it, 60-round builds: 1M x
-// 960 604 / 915 ms, half the bytes per gathered row; 200,000 x 100 27.1 / 31.5, 1M x 96 139.4 / 143.3; 20,000 x 96, where
-// launches and latency count, 3.89 / 3.87 and two launches more).
-#define HALF_MIN_N 32768
+// Row length in bytes of the half-precision copy of d coordinates: a multiple of 128, so that no row shares a cache line; 192 for 65
+// .. 96 coordinates, where a third of 256 would be padding.
+static u32 half_row_bytes(int d) { return d <= 64 ? 128u : d <= 128 ? ((u32)d + 31u) / 32u * 64u : ((u32)d + 63u) / 64u * 128u; }
+// From how many vertices on a build's float32 scans take their Gram blocks from that copy: always but for the smallest inputs,
+// whose lists the two launches that make it would hold up (60-round builds without / with it, R = 96: 300 x 96 1.64 / 1.21 ms, 2,000 x 33
+// 1.60 / 1.55, 20,000 x 96 3.87 / 3.15, 1M x 960 915 / 526).
+#define HALF_MIN_N 256
 enum CopyKind { COPY_NONE = 0, COPY_U8, COPY_U8_ROWS, COPY_ROWS, COPY_ROWS_PERMUTED };
 struct ScanPlan {
     int variant = 1, dp = 0;
@@ -1558,7 +1574,9 @@ struct ScanPlan {
     size_t copy_bytes = 0;
     u32 half_rb = 0;            // row length of the half-precision copy of float32 rows (see HalfRows), 0 = none
     size_t half_bytes = 0;      // what it takes: rows, centre, sums, parameters
-    int classes() const { return variant == 2 ? 2 : variant == 3 ? 1 : 0; }
+    bool tiles16 = false;       // variant 3: 16-bit rows go to the 16-bit matrix instructions as they are
+    // which degree classes the scan works by (see degree_class)
+    int classes() const { return variant == 2 ? 2 : variant == 3 ? (tiles16 || half_rb ? 2 : 1) : 0; }
     bool extra() const { return copy > COPY_U8 || half_rb; }
 };
 
@@ -1607,49 +1625,15 @@ static ScanPlan scan_plan_for(const void *X, long long N, int d, int dtype, bool
             p.copy_bytes = (size_t)N * p.dp * dt_size(dtype);
         }
     }
-    if (may_half && N > HALF_MIN_N && p.variant == 3 && dtype == RNND_F32 && g_kernel_variant == 0) {
+    p.tiles16 = p.variant == 3 && dtype != RNND_F32 && g_kernel_variant == 0;
+    if (may_half && N >= HALF_MIN_N && p.variant == 3 && dtype == RNND_F32 && g_kernel_variant == 0) {
         p.half_rb = half_row_bytes(d);
         p.half_bytes = half_layout(nullptr, N, d, p.half_rb, nullptr);
     }
     return p;
 }
 
-static int cu_count()
-{
-    static int cus = 0;
-    if (!cus) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-            cus = 256;
-    }
-    return cus;
-}
-
-static int persistent_blocks() { return cu_count() * 8; }   // 32 wavefronts per CU
-
-// A grid that walks a list of at most N vertices, one or more per wavefront of a 4-wavefront block, needs no more
-// than N / 4 blocks: small inputs get small grids (a launch costs by its workgroups even when they find no work).
-static unsigned capped(long long blocks, long long N)
-{
-    const long long need = (N + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK;
-    return (unsigned)(blocks < need ? blocks : (need < 1 ? 1 : need));
-}
-
 static inline int vertex_blocks(long long N) { return (int)((N + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK); }
-
-// Blocks of `kernel` (256 threads, static LDS only) that one CU keeps resident; the persistent
-// scans launch exactly that many per CU so that every wavefront starts at once.
-template <typename K>
-static int resident_blocks_per_cu(K kernel, int fallback)
-{
-    int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, 256, 0) != hipSuccess || nb < 1) {
-        (void)hipGetLastError();
-        nb = fallback;
-    }
-    return nb;
-}
 
 // Events tied to kernels of one round (null: not wanted).  They are attached to the launches
 // themselves, which costs no extra packet on the stream.
@@ -1823,106 +1807,55 @@ static void launch_mfma_scan_classes(const Workspace &w, int d, int R, u64 *keys
     if (R > 96) launch_mfma_scan<4, KS>(w, d, R, keys, deg, N, c, st, n_big == 3 ? re.scan_stop : nullptr);
 }
 
-// Float scan.  The single-precision form takes the active lists; vertices it leaves alone (ties in bulk) go to one redo
-// list for all classes, which launch_f32_redo hands to the double-precision form.  The redo list lives in the bin
-// array, which nothing else uses until the scatter that follows the scans.
-template <int NRCMAX, int C0, int CH, int DT, bool HALF>
-static void launch_f32_classes(const Workspace &w, const void *X, const HalfRows &half, int d, int R, u64 *keys, int *deg, long long N, RoundCtr *c,
-                               hipStream_t st, hipEvent_t e_start)
-{
-    static const int per_cu = resident_blocks_per_cu(k_update_scan_mfma_f32_all<NRCMAX, C0, CH, DT, HALF>, 2);
-    unsigned gx = capped((long long)cu_count() * per_cu, N);
-    if (gx < 8) gx = 8;      // a block at least for every class
-    hipExtLaunchKernelGGL((k_update_scan_mfma_f32_all<NRCMAX, C0, CH, DT, HALF>), dim3(gx), dim3(256), 0, st, e_start, nullptr, 0,
-                          (const char *)X, half, d, R, keys, deg, w.lists, N, w.props, w.nprop, c, (int *)w.bins, &c->n_redo[0]);
-}
-
-template <int DT, bool HALF = false>
-static void launch_f32_scan(const Workspace &w, const void *X, const HalfRows &half, int d, int R, u64 *keys, int *deg, long long N, RoundCtr *c,
-                            hipStream_t st, hipEvent_t e_start)
-{
-    const bool wide = (HALF ? half.rowbytes : (size_t)d * dt_size(DT)) % 128 == 0;     // two 64-byte chunks per iteration
-    if (R > 32 && N <= (R <= 64 ? SMALL_FLOAT_MAX_N_64 : SMALL_FLOAT_MAX_N_96)) {
-        if (R <= 64) {
-            if (wide) launch_f32_classes<4, 0, 2, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, e_start);
-            else launch_f32_classes<4, 0, 1, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, e_start);
-        } else {
-            if (wide) launch_f32_classes<6, 0, 2, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, e_start);
-            else launch_f32_classes<6, 0, 1, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, e_start);
-        }
-        return;
-    }
-    if (DT == DT_F32 && N > SPLIT_SHORT_LISTS_MIN_N && d > SPLIT_SHORT_LISTS_MIN_D) {
-        if (wide) launch_f32_classes<1, 0, 2, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, e_start);
-        else launch_f32_classes<1, 0, 1, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, e_start);
-        if (R > 16) {
-            if (wide) launch_f32_classes<2, 2, 2, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, nullptr);
-            else launch_f32_classes<2, 2, 1, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, nullptr);
-        }
-    } else {
-        if (wide) launch_f32_classes<2, 0, 2, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, e_start);
-        else launch_f32_classes<2, 0, 1, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, e_start);
-    }
-    if (R > 32) launch_f32_classes<4, 3, 1, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, nullptr);
-    if (R > 64) launch_f32_classes<6, 5, 1, DT, HALF>(w, X, half, d, R, keys, deg, N, c, st, nullptr);
-}
-
-// Kernel variant 2: the double-precision form on the active list of degree class cls.
-template <int NG, int CH, int NRC, int DT>
-static void launch_f64_class_dt(const Workspace &w, const void *X, int d, int R, u64 *keys, int *deg, long long N,
-                                RoundCtr *c, int cls, hipStream_t st, hipEvent_t e_start, hipEvent_t e_stop)
-{
-    // wavefronts that fit per SIMD: about 4 for NG = 1, 2 for NG = 2, 1 for NG = 3 (21 accumulator tiles)
-    static const int per_cu = resident_blocks_per_cu(k_update_scan_f64<NG, CH, NRC, DT>, NG == 1 ? 4 : NG == 2 ? 2 : 1);
-    hipExtLaunchKernelGGL((k_update_scan_f64<NG, CH, NRC, DT>), dim3(capped(cu_count() * per_cu, N)), dim3(256), 0,
-                          st, e_start, e_stop, 0, (const char *)X, d, R, keys, deg, w.lists + (size_t)cls * N,
-                          &c->n_active[cls], w.props, w.nprop, c);
-}
-
-template <int NG, int CH, int NRC>
-static void launch_f64_class(const Workspace &w, const void *X, int d, int dtype, int R, u64 *keys, int *deg,
-                             long long N, RoundCtr *c, int cls, hipStream_t st, hipEvent_t e_start, hipEvent_t e_stop)
-{
-    if (dtype == RNND_F16) launch_f64_class_dt<NG, CH, NRC, DT_F16>(w, X, d, R, keys, deg, N, c, cls, st, e_start, e_stop);
-    else if (dtype == RNND_BF16) launch_f64_class_dt<NG, CH, NRC, DT_BF16>(w, X, d, R, keys, deg, N, c, cls, st, e_start, e_stop);
-    else launch_f64_class_dt<NG, CH, NRC, DT_F32>(w, X, d, R, keys, deg, N, c, cls, st, e_start, e_stop);
-}
-
-// The double-precision form (in its widest shape: lists of up to 96 entries) over the round's redo list.
-template <int DT>
-static void launch_f32_redo_dt(const Workspace &w, const void *X, int d, int R, u64 *keys, int *deg, long long N, RoundCtr *c,
-                               hipStream_t st, hipEvent_t e_stop)
-{
-    static const int per_cu = resident_blocks_per_cu(k_update_scan_f64<3, 1, 6, DT>, 1);
-    hipExtLaunchKernelGGL((k_update_scan_f64<3, 1, 6, DT>), dim3(capped(cu_count() * per_cu, N)), dim3(256), 0, st,
-                          nullptr, e_stop, 0, (const char *)X, d, R, keys, deg, (const int *)w.bins,
-                          (const u32 *)&c->n_redo[0], w.props, w.nprop, c);
-}
-
-static void launch_f32_redo(const Workspace &w, const void *X, int d, int dtype, int R, u64 *keys, int *deg,
-                            long long N, RoundCtr *c, hipStream_t st, hipEvent_t e_stop)
-{
-    if (dtype == RNND_F16) launch_f32_redo_dt<DT_F16>(w, X, d, R, keys, deg, N, c, st, e_stop);
-    else if (dtype == RNND_BF16) launch_f32_redo_dt<DT_BF16>(w, X, d, R, keys, deg, N, c, st, e_stop);
-    else launch_f32_redo_dt<DT_F32>(w, X, d, R, keys, deg, N, c, st, e_stop);
-}
-
 template <int DT>
 static void launch_generic_scan_dt(const Workspace &w, const void *X, int d, int vec_ok, int R, u64 *keys, int *deg, long long N,
-                                   int cls, unsigned blocks, RoundCtr *c, hipStream_t st, hipEvent_t e_start, hipEvent_t e_stop)
+                                   const int *list, const u32 *n_list, unsigned blocks, RoundCtr *c, hipStream_t st, hipEvent_t e_start, hipEvent_t e_stop)
 {
     hipExtLaunchKernelGGL(k_update_scan<DT>, dim3(blocks), dim3(BLOCK), 0, st, e_start, e_stop, 0, X, d, vec_ok, R, keys, deg,
-                          w.lists + (size_t)cls * N, &c->n_active[cls], w.props, w.nprop, c);
+                          list, n_list, w.props, w.nprop, c);
 }
 
-// The generic scan over the active list of class cls.
+// The generic scan over one list.
 static void launch_generic_scan(const Workspace &w, const void *X, int d, int dtype, int vec_ok, int R, u64 *keys, int *deg,
-                                long long N, int cls, unsigned blocks, RoundCtr *c, hipStream_t st, hipEvent_t e_start, hipEvent_t e_stop)
+                                long long N, const int *list, const u32 *n_list, unsigned blocks, RoundCtr *c, hipStream_t st, hipEvent_t e_start,
+                                hipEvent_t e_stop)
 {
-    if (dtype == RNND_U8) launch_generic_scan_dt<DT_U8>(w, X, d, vec_ok, R, keys, deg, N, cls, blocks, c, st, e_start, e_stop);
-    else if (dtype == RNND_F16) launch_generic_scan_dt<DT_F16>(w, X, d, vec_ok, R, keys, deg, N, cls, blocks, c, st, e_start, e_stop);
-    else if (dtype == RNND_BF16) launch_generic_scan_dt<DT_BF16>(w, X, d, vec_ok, R, keys, deg, N, cls, blocks, c, st, e_start, e_stop);
-    else launch_generic_scan_dt<DT_F32>(w, X, d, vec_ok, R, keys, deg, N, cls, blocks, c, st, e_start, e_stop);
+    if (dtype == RNND_U8) launch_generic_scan_dt<DT_U8>(w, X, d, vec_ok, R, keys, deg, N, list, n_list, blocks, c, st, e_start, e_stop);
+    else if (dtype == RNND_F16) launch_generic_scan_dt<DT_F16>(w, X, d, vec_ok, R, keys, deg, N, list, n_list, blocks, c, st, e_start, e_stop);
+    else if (dtype == RNND_BF16) launch_generic_scan_dt<DT_BF16>(w, X, d, vec_ok, R, keys, deg, N, list, n_list, blocks, c, st, e_start, e_stop);
+    else launch_generic_scan_dt<DT_F32>(w, X, d, vec_ok, R, keys, deg, N, list, n_list, blocks, c, st, e_start, e_stop);
+}
+
+// dt (here and below): the type of the rows that open distances are computed from, DT_U8 where none are open
+template <int DT>
+static void launch_classify_dt(hipStream_t st, long long N, int R, const Workspace &w, const int *deg, RoundCtr *c, const void *X, int d)
+{
+    const LateHeads heads = late_heads(w.inbox, w.bins, R);
+    if (N <= SMALL_INPUT_MAX_N)
+        hipLaunchKernelGGL((k_touch_classify<2, DT>), dim3((unsigned)((N + 2047) / 2048)), dim3(1024), 0, st, N, round_inbox(R), w.fill, deg, c,
+                           w.touched, heads, w.props, (const char *)X, d);
+    else
+        hipLaunchKernelGGL((k_touch_classify<4, DT>), dim3((unsigned)((N + 4095) / 4096)), dim3(1024), 0, st, N, round_inbox(R), w.fill, deg, c,
+                           w.touched, heads, w.props, (const char *)X, d);
+}
+
+template <int DT>
+static void launch_merge_dt(hipStream_t st, long long N, int R, const Workspace &w, u64 *keys, int *deg, int use_classes, RoundCtr *c, const void *X, int d)
+{
+    static const int per_cu = resident_blocks_per_cu(k_merge<DT>, 6);
+    hipLaunchKernelGGL(k_merge<DT>, dim3(capped(cu_count() * per_cu, N), NMRG), dim3(BLOCK), 0, st, N, R, keys, deg, w.touched, c->n_touched,
+                       w.fill, w.inbox, late_heads(w.inbox, w.bins, R), (const Prop *)w.props, w.tcls, use_classes, c, (const char *)X, d);
+}
+
+static void launch_classify(int dt, hipStream_t st, long long N, int R, const Workspace &w, const int *deg, RoundCtr *c, const void *X, int d)
+{
+    const auto go = dt == RNND_F32 ? launch_classify_dt<DT_F32> : dt == RNND_F16 ? launch_classify_dt<DT_F16> : dt == RNND_BF16 ? launch_classify_dt<DT_BF16> : launch_classify_dt<DT_U8>;
+    go(st, N, R, w, deg, c, X, d);
+}
+static void launch_merge(int dt, hipStream_t st, long long N, int R, const Workspace &w, u64 *keys, int *deg, int use_classes, RoundCtr *c, const void *X, int d)
+{
+    const auto go = dt == RNND_F32 ? launch_merge_dt<DT_F32> : dt == RNND_F16 ? launch_merge_dt<DT_F16> : dt == RNND_BF16 ? launch_merge_dt<DT_BF16> : launch_merge_dt<DT_U8>;
+    go(st, N, R, w, keys, deg, use_classes, c, X, d);
 }
 
 // One run of consecutive vertex ids of a block-sequential pass: ids first .. first + count - 1.
@@ -1933,16 +1866,16 @@ struct VertexRun {
 // One synchronous round over the active lists of counter slot t (run == nullptr), or one run of a
 // block-sequential pass: the run's active lists are taken from vcls[] first, and the classes of the
 // vertices its merge touched go back to vcls[] instead of into the next slot's lists.
-static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, long long N, int dp, int dtype,
-                                      int variant, int R, u64 *keys, int *deg, int t,
+static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, long long N, const ScanPlan &plan, int dtype,
+                                      int R, u64 *keys, int *deg, int t,
                                       hipStream_t st, const RoundEvents &re = RoundEvents(),
                                       const VertexRun *run = nullptr)
 {
     const unsigned pb = capped(persistent_blocks(), N);
     const void *X = rv.X;
-    const int d = variant == 2 ? dp : rv.d, vec_ok = rv.vec_ok;
+    const int variant = plan.variant, use_classes = plan.classes();
+    const int d = variant == 2 ? plan.dp : rv.d, vec_ok = rv.vec_ok;
     RoundCtr *c = w.ctr + t;
-    const int use_classes = variant == 2 ? 2 : variant == 3 ? 1 : 0;
     if (run) {
         const unsigned cb = (run->count + 1023u) / 1024u;
         hipLaunchKernelGGL(k_compact_classes, dim3(cb < 256u ? cb : 256u, 1), dim3(1024), 0, st, (const u32 *)nullptr,
@@ -1955,44 +1888,35 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
         else if (d == 128) launch_mfma_scan_classes<4>(w, d, R, keys, deg, N, c, st, re);
         else launch_mfma_scan_classes<0>(w, d, R, keys, deg, N, c, st, re);
     } else if (variant == 3) {
-        // degree classes 0..6: lists of at most 8, 16, 32, 48, 64, 80, 96 entries = 1, 1, 2, 3, 4, 5, 6 groups of 16
-        // rows; class 7 (97..128 entries: too many accumulator tiles) goes to the generic kernel
         const bool generic_tail = R > 96;
-        if (g_kernel_variant != 2) {
-            if (dtype == RNND_F16) launch_f32_scan<DT_F16>(w, X, rv.half, d, R, keys, deg, N, c, st, re.scan_start);
-            else if (dtype == RNND_BF16) launch_f32_scan<DT_BF16>(w, X, rv.half, d, R, keys, deg, N, c, st, re.scan_start);
-            else if (rv.half.rows) launch_f32_scan<DT_F32, true>(w, X, rv.half, d, R, keys, deg, N, c, st, re.scan_start);
-            else launch_f32_scan<DT_F32>(w, X, rv.half, d, R, keys, deg, N, c, st, re.scan_start);
-            launch_f32_redo(w, X, d, dtype, R, keys, deg, N, c, st, generic_tail ? (hipEvent_t) nullptr : re.scan_stop);
+        ScanLaunch l = {X, d, R, keys, deg, N, w.lists, w.props, w.nprop, c, (int *)w.bins, st, re.scan_start, generic_tail ? (hipEvent_t) nullptr : re.scan_stop};
+        if (use_classes == 2) {
+            // lists of up to 128 entries; what the redo list of the longest holds goes to the generic kernel
+            const bool copy = rv.half.rows != nullptr;
+            launch_float_scan(l, dtype, copy ? rv.half.rows : X, copy ? rv.half.rowbytes : (u32)(d * dt_size(dtype)), rv.half.par);
+            launch_f64_redo(l, dtype);
+            if (generic_tail) launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, l.redo + N, &c->n_redo[1], pb, c, st, nullptr, re.scan_stop);
         } else {
-            const int n_more = (R > 8) + (R > 16) + (R > 32) + (R > 48) + (R > 64) + (R > 80);
-            int k = 0;
-            auto stop_for = [&](void) { return (k++ == n_more && !generic_tail) ? re.scan_stop : (hipEvent_t) nullptr; };
-            launch_f64_class<1, 1, 1>(w, X, d, dtype, R, keys, deg, N, c, 0, st, re.scan_start, stop_for());
-            if (R > 8) launch_f64_class<1, 1, 1>(w, X, d, dtype, R, keys, deg, N, c, 1, st, nullptr, stop_for());
-            if (R > 16) launch_f64_class<1, 1, 2>(w, X, d, dtype, R, keys, deg, N, c, 2, st, nullptr, stop_for());
-            if (R > 32) launch_f64_class<2, 1, 4>(w, X, d, dtype, R, keys, deg, N, c, 3, st, nullptr, stop_for());
-            if (R > 48) launch_f64_class<2, 1, 4>(w, X, d, dtype, R, keys, deg, N, c, 4, st, nullptr, stop_for());
-            if (R > 64) launch_f64_class<3, 1, 5>(w, X, d, dtype, R, keys, deg, N, c, 5, st, nullptr, stop_for());
-            if (R > 80) launch_f64_class<3, 1, 6>(w, X, d, dtype, R, keys, deg, N, c, 6, st, nullptr, stop_for());
+            // degree classes 0..6: lists of at most 8, 16, 32, 48, 64, 80, 96 entries = 1, 1, 2, 3, 4, 5, 6 groups of 16
+            // rows; class 7 (97..128 entries: too many accumulator tiles) goes to the generic kernel
+            if (g_kernel_variant != 2) {
+                launch_f32_scan(l);
+                launch_f64_redo(l, dtype);
+            } else {
+                launch_f64_classes(l, dtype);
+            }
+            if (generic_tail) launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, w.lists + (size_t)7 * N, &c->n_active[7], pb, c, st, nullptr, re.scan_stop);
         }
-        if (generic_tail) launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, 7, pb, c, st, nullptr, re.scan_stop);
     } else {
-        launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, 0, pb, c, st, re.scan_start, re.scan_stop);
+        launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, w.lists, &c->n_active[0], pb, c, st, re.scan_start, re.scan_stop);
     }
     // from here on `fill` plays the role of the per-target count of this round
     const int ncl = use_classes ? NDEG : 1;
+    const int open_dt = variant == 3 && use_classes == 2 ? dtype : RNND_U8;      // whose redirected edges come without distances
     hipLaunchKernelGGL(k_scatter, dim3(pb), dim3(BLOCK), 0, st, N, R, w.lists, ncl, c, w.props, (const int *)w.nprop, w.fill,
                        w.inbox, late_heads(w.inbox, w.bins, R));
-    if (N <= SMALL_INPUT_MAX_N)
-        hipLaunchKernelGGL(k_touch_classify<2>, dim3((unsigned)((N + 2047) / 2048)), dim3(1024), 0, st, N, round_inbox(R), w.fill, deg, c,
-                           w.touched);
-    else
-        hipLaunchKernelGGL(k_touch_classify<4>, dim3((unsigned)((N + 4095) / 4096)), dim3(1024), 0, st, N, round_inbox(R), w.fill, deg, c,
-                           w.touched);
-    static const int merge_per_cu = resident_blocks_per_cu(k_merge, 6);
-    hipLaunchKernelGGL(k_merge, dim3(capped(cu_count() * merge_per_cu, N), NMRG), dim3(BLOCK), 0, st, N, R, keys, deg, w.touched, c->n_touched,
-                       w.fill, w.inbox, late_heads(w.inbox, w.bins, R), (const Prop *)w.props, w.tcls, use_classes, c);
+    launch_classify(open_dt, st, N, R, w, deg, c, X, d);
+    launch_merge(open_dt, st, N, R, w, keys, deg, use_classes, c, X, d);
     if (run)
         hipLaunchKernelGGL(k_store_classes, dim3(64, NMRG), dim3(256), 0, st, (const u32 *)c->n_touched,
                            (const int *)w.touched, (const int8_t *)w.tcls, N, w.vcls);
@@ -2005,8 +1929,8 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
 
 // One block-sequential pass: `blocks` runs of ceil(N / blocks) consecutive ids, in id order, counter slots
 // t0, t0 + 1, ...  Returns the number of slots used through *used.
-static hipError_t launch_update_pass_blocks(const Workspace &w, const RowsView &rv, long long N, int dp, int dtype,
-                                            int variant, int R, u64 *keys, int *deg, int t0,
+static hipError_t launch_update_pass_blocks(const Workspace &w, const RowsView &rv, long long N, const ScanPlan &plan, int dtype,
+                                            int R, u64 *keys, int *deg, int t0,
                                             long long blocks, hipStream_t st, int *used)
 {
     const long long bs = (N + blocks - 1) / blocks;
@@ -2015,7 +1939,7 @@ static hipError_t launch_update_pass_blocks(const Workspace &w, const RowsView &
         VertexRun run;
         run.first = (u32)lo;
         run.count = (u32)(lo + bs < N ? bs : N - lo);
-        hipError_t e = launch_update_round(w, rv, N, dp, dtype, variant, R, keys, deg, t0 + k, st, RoundEvents(),
+        hipError_t e = launch_update_round(w, rv, N, plan, dtype, R, keys, deg, t0 + k, st, RoundEvents(),
                                            &run);
         if (e != hipSuccess) return e;
     }
@@ -2429,7 +2353,7 @@ static int build_impl(const void *X, int64_t N, int32_t d, int dtype, int metric
             for (int t2 = 0; t2 < T2; ++t2, ++t) {
                 if (blocks) {
                     int used = 0;
-                    HIPCHK(launch_update_pass_blocks(w, rows, N, plan.dp, dtype, variant, M, w.keys, w.deg,
+                    HIPCHK(launch_update_pass_blocks(w, rows, N, plan, dtype, M, w.keys, w.deg,
                                                      (int)(t * per_pass), blocks, st, &used));
                     if (stats) HIPCHK(hipEventRecord(ev[4 + 3 * t], st));
                     continue;
@@ -2442,7 +2366,7 @@ static int build_impl(const void *X, int64_t N, int32_t d, int dtype, int metric
                     re.scan_stop = ev[3 + 3 * t];
                     if (t2 == T2 - 1) re.round_stop = ev[4 + 3 * t];
                 }
-                HIPCHK(launch_update_round(w, rows, N, plan.dp, dtype, variant, M, w.keys, w.deg, t, st, re));
+                HIPCHK(launch_update_round(w, rows, N, plan, dtype, M, w.keys, w.deg, t, st, re));
                 if (stats && !ev_rounds && t2 == T2 - 1)
                     hipLaunchKernelGGL(k_stamp, dim3(1), dim3(64), 0, st, &w.ctr[t].t_round_stop);
             }
@@ -2606,10 +2530,10 @@ static int update_impl(const void *X, int64_t N, int32_t d, int dtype, int metri
     for (int t = 0; t < n_rounds; ++t) {
         if (blocks) {
             int used = 0;
-            HIPCHK(launch_update_pass_blocks(w, rows, N, plan.dp, dtype, plan.variant, R, (u64 *)keys, deg,
+            HIPCHK(launch_update_pass_blocks(w, rows, N, plan, dtype, R, (u64 *)keys, deg,
                                              (int)(t * per_pass), blocks, st, &used));
         } else {
-            HIPCHK(launch_update_round(w, rows, N, plan.dp, dtype, plan.variant, R, (u64 *)keys, deg, t, st));
+            HIPCHK(launch_update_round(w, rows, N, plan, dtype, R, (u64 *)keys, deg, t, st));
         }
     }
     if (stats) {

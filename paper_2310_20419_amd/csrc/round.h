@@ -1,0 +1,70 @@
+// What the kernels of a round share: the counters, the clock marks, the record of a redirected edge.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "wave_prims.h"
+
+#define NDEG 8   // degree classes of the active lists (see degree_class)
+#define NMRG 4   // merge classes of the touched lists: kept + received at most 16, 32, 64, more
+
+// Per-round device counters.  Round t reads ctr[t].n_active[] and fills the rest; its compact step
+// writes ctr[t+1].n_active[].  Zeroed once per call, never reset, so they double as statistics.
+#define STAT_SLOTS 64
+struct RoundCtr {
+    u32 n_active[NDEG];   // lengths of this round's active lists
+    u32 n_touched[NMRG];  // distinct targets of the redirected edges, by size of the merge they need
+    u32 nonfinite;        // slot 0: k_prepare_rows met a coordinate that is NaN or infinite
+    u32 pad[3];
+    u32 n_redo[NDEG];     // float scan: vertices the single-precision form left to the double-precision one
+    // ticks of the device's constant-rate clock (0 = not taken): the round's first scan launch starts, its scatter
+    // starts (= the scan has ended: launches of one stream run back to back), the round's last kernel has ended
+    // (taken by k_stamp after the last round before an AddReverseEdges call or the export, only where statistics
+    // ask for it; every other round, and an AddReverseEdges call, ends where the next round's scan starts)
+    u64 t_scan_start, t_scan_stop, t_round_stop;
+    // statistics, spread over STAT_SLOTS addresses so that the adds of many blocks do not queue up
+    // on one: [slot][0..4] = algorithmic evals, executed evals, rows gathered, edges redirected, entries a merge
+    // dropped because the list was full
+    u64 stat[STAT_SLOTS][5];
+};
+
+// One add per wavefront into the slot of its block.
+__device__ __forceinline__ void add_round_stats(RoundCtr *ctr, u64 algo, u64 exec, u64 rows, u64 props)
+{
+    u64 *s = ctr->stat[blockIdx.x & (STAT_SLOTS - 1)];
+    atomicAdd(&s[0], algo);
+    atomicAdd(&s[1], exec);
+    atomicAdd(&s[2], rows);
+    atomicAdd(&s[3], props);
+}
+
+// Statistics take the scan time of a round from the device's own clock instead of events attached to the launches:
+// an event costs 4-7 microseconds of idle queue after its kernel, three per round used to add 1 ms to a 27 ms build.
+__device__ __forceinline__ void stamp_scan_start(RoundCtr *ctr)
+{   // the first scan launch of a round that comes by fills the field
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && ctr->t_scan_start == 0ull) ctr->t_scan_start = wall_clock64();
+}
+__device__ __forceinline__ void stamp_scan_stop(RoundCtr *ctr)
+{
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) ctr->t_scan_stop = wall_clock64();
+}
+
+struct Prop {          // one redirected edge (Alg. 4, the edge update): `key` enters `tgt`'s list
+    u64 key;
+    u32 tgt;
+    u32 next;          // set by the scatter for edges past the inbox: the edge (its place in props) that was on tgt's list before
+};
+
+// A key whose distance is still to be computed (by the merge, see close_keys): these bits in place of the distance.  A NaN can
+// have them too; computing it once more gives the same bits.
+#define OPEN_DIST 0xFFFFFFFFu
+
+// The edge update of Alg. 4: (w, v) enters E.  Recorded in the scanning vertex's own slot.
+__device__ __forceinline__ void emit_redirect(u64 key, u32 tgt, Prop *slot)
+{
+    Prop pr;
+    pr.key = key;
+    pr.tgt = tgt;
+    pr.next = 0;
+    *slot = pr;
+}

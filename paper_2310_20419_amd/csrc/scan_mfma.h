@@ -1,42 +1,20 @@
-// UpdateNeighbors scan (Alg. 4, the body of the vertex loop) for uint8 rows on the matrix cores.
-//
-// One wavefront owns one vertex u with m <= 32*NG list entries.  The rows x_v of its whole list are
-// gathered straight into MFMA operand registers (lane l: row l%32 of a 32-row group, bytes
-// [32s + 16(l/32), +16) of K-step s) from a copy of X made once per build in which every byte is
-// the int8 x-128 (this leaves every difference, hence every delta, unchanged).  n_v = |x_v - 128|^2
-// is read off the diagonal of the Gram tile of v's block with itself.
-// For a block I of 32 list positions (rows v_i) and a block J <= I (candidates w_j) the tile
-//     T_ij = 2 <x_i, x_j> - n_j - t_i ,   t_i = n_i - delta(u, v_i)
-// is formed from the Gram tile G(I, J) of v_mfma_i32_32x32x32_i8 (for J = I the one that gave the norms) by
-// one shift-add per entry.  The first operand is block J, the second block I, so a lane holds ROW i = l%32 of the tile
-// and 16 of its columns, j = 8(a/4) + 4(l/32) + a%4: by the symmetry of the Gram matrix no transpose
-// is needed.  Both operands use the same byte order, so however the hardware pairs the K bytes, the
-// two sides pair alike.  With delta(v_i, w_j) = n_i + n_j - 2<x_i, x_j> (exact in int32):
-//     the prune test fires  <=>  delta(u, v_i) >= delta(v_i, w_j)  <=>  T_ij >= 0 ,
-// Each half-wave collects the outcomes for its 16 columns as bits of one word per row.  The loop over v
-// then run on bit masks: the kept set U' is the unique solution K of
-//     K_i = not exists j < i : F_ij and K_j
-// (F already masked by the old/old skip), found per 32-row block by iterating
-// K <- Phi(K) from "all kept" until it stops changing (row i is final after i+1 sweeps).  A pruned
-// row's redirect target is the first set bit of F_i & K, and delta(v,w) for the new edge comes from
-// the tile kept in LDS:  delta(v_i, w_j) = delta(u, v_i) - T_ij.
+// The walk of the matrix-core scans over a round's active lists, and how a list's rows reach the matrix instructions: lane l of
+// a wavefront holds 16 bytes, piece 2 s + l / 32, of row l % 32 of each group of 32 list entries, for step s of an instruction
+// that takes 32 bytes of every row.  What is done with a vertex's Gram tiles is the business of the class OP (uint8 rows:
+// scan_u8.h, float rows: scan_float.h):
+//     tile_t, mac           accumulator of a 32 x 32 tile and the matrix instruction
+//     Smem<NG>              LDS of a wavefront; its gt, of 4 KB per 32 rows at least, is free until the Gram tiles are complete
+//     list<NG>, pack<P>     the body of Alg. 4's vertex loop for one vertex of up to 32 NG entries, for P vertices of up to 32 / P
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "round.h"
 #include "wave_prims.h"
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 
 #define GT_STRIDE 36   // dwords per row of a tile in LDS (32 + 4: conflict-free b128 stores)
-
-template <int NG>
-struct alignas(16) MfmaScanSmem {
-    int gt[NG * 32 * GT_STRIDE];   // tiles T(I, J) of the current block I: [(32J + i) * GT_STRIDE + j]
-    int nrm[32 * NG];              // n_j by list position
-    int id[32 * NG];               // vertex id by list position
-};
 
 // What the scan holds in registers for one vertex of its work list before it is that vertex's turn.
 struct ScanItem {
@@ -81,37 +59,6 @@ __device__ __forceinline__ void scan_gather(const int8_t *__restrict__ X, const 
     }
 }
 
-// Once per build: Xs <- X - 128 as int8 (n bytes, a multiple of 16).
-__global__ __launch_bounds__(256) void k_prepare_u8(const uint8_t *__restrict__ X, size_t n,
-                                                    int8_t *__restrict__ Xs)
-{
-    const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 16;
-    if (i < n) {
-        v4i x = *(const v4i *)(X + i);
-        x ^= (int)0x80808080;
-        *(v4i *)(Xs + i) = x;
-    }
-}
-
-// The same for rows the tiles do not fit: row u of Xs is dp bytes (dp >= d, a multiple of 4): the d bytes of x_u minus
-// 128, then zeros, which add nothing to a product of two rows.  X may have any alignment, so it is read by single
-// bytes, a wavefront taking 256 consecutive ones of a row.
-__global__ __launch_bounds__(256) void k_prepare_u8_rows(const uint8_t *__restrict__ X, long long N, int d, int dp,
-                                                         int8_t *__restrict__ Xs)
-{
-    const u32 words = (u32)dp / 4u;
-    for (u64 i = (u64)blockIdx.x * 256u + threadIdx.x; i < (u64)N * words; i += (u64)gridDim.x * 256u) {
-        const u64 u = i / words;
-        const int e = 4 * (int)(i - u * words);
-        const uint8_t *x = X + u * (u64)d + e;
-        u32 w = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (e + k < d) w |= ((u32)x[k] ^ 0x80u) << (8 * k);
-        *(u32 *)(Xs + 4 * i) = w;
-    }
-}
-
 // What a trip has in flight for the trips after it: the rows of the next vertex (or group) and the
 // list of the one after.  The memory counter of a wavefront is in order and counts stores as well, so a
 // wait for these loads that stood after the trip's stores would also wait for the stores to be
@@ -121,253 +68,112 @@ __device__ __forceinline__ void arrived(const v4i &x) { asm volatile("" ::"v"(x)
 __device__ __forceinline__ void arrived(u64 x) { asm volatile("" ::"v"(x)); }
 __device__ __forceinline__ void arrived(int x) { asm volatile("" ::"v"(x)); }
 
+// The same number, of which the compiler knows nothing: what a trip derives from it (masks, LDS addresses) is computed again in
+// every trip instead of waiting in registers, of which the streamed scans have none to spare (a spilled one is read back
+// through the same in-order memory counter as the rows in flight, which then have to arrive first).
+__device__ __forceinline__ int afresh(int x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 // Where a vertex's Gram tiles come from: formed on demand from rows that are held whole in registers (rows of 32 KS
 // bytes) ...
-template <int NG, int KS>
+template <typename OP, int NG, int KS>
 struct RowsGram {
     const v4i (&A)[NG][KS];
-    __device__ __forceinline__ v16i tile(int I, int J) const
+    __device__ __forceinline__ typename OP::tile_t tile(int I, int J) const
     {
-        v16i G = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+        typename OP::tile_t G = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-        for (int s = 0; s < KS; ++s) G = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[J][s], A[I][s], G, 0, 0, 0);
+        for (int s = 0; s < KS; ++s) G = OP::mac(A[J][s], A[I][s], G);
         return G;
     }
 };
 // ... or accumulated beforehand while longer rows were streamed through the registers (stream_gram)
-template <int NG>
+template <typename OP, int NG>
 struct StreamedGram {
-    const v16i (&G)[NG * (NG + 1) / 2];
-    __device__ __forceinline__ v16i tile(int I, int J) const { return G[I * (I + 1) / 2 + J]; }
+    const typename OP::tile_t (&G)[NG * (NG + 1) / 2];
+    __device__ __forceinline__ typename OP::tile_t tile(int I, int J) const { return G[I * (I + 1) / 2 + J]; }
 };
 
-// Rows of more than 128 bytes (padded with zeros to d = a multiple of 64) do not fit in registers whole: they are
-// streamed through them 32 CH bytes at a time, three buffers in rotation, while the accumulators of all the
-// vertex's tiles stay (16 registers per tile).  While the matrix cores work on one chunk the loads of the next two are
-// in flight; chunks past the end re-read the last one (a cache hit).  A list of this class fills all its NG groups,
-// and a tile costs 32 cycles per 32 bytes of its rows, a sixth of what its rows cost in memory time, so every tile is
-// formed, needed or not.  Measured on whole builds, S = 20, R = 96, 60 rounds, against the pair-at-a-time kernel these
-// rows went to before (bound by its dependent trips to memory): 60,000 x 784 36.1 -> 5.6 ms, 20,000 x 200 23.2 -> 3.0 ms.
-template <int NG, int CH>
-__device__ __forceinline__ void stream_fetch(const int8_t *const (&rp)[NG], int c, v4i (&x)[NG][CH])
+// Rows that registers do not hold whole are streamed, 128 bytes of every row (a chunk) at a time, while the accumulators of all
+// the vertex's tiles stay (16 registers per tile).  Loads in the operand layout would give every lane a piece of another row, and
+// such an instruction keeps the address unit busy for 64 cycles: at most 9.7 TB/s of lanes, used or not (measured on rows that sit in the
+// L2), which lists that fill 20 of 32 slots cannot afford next to 6.9 TB/s of memory.  So 8 neighbouring lanes take a row's 128 bytes (32
+// TB/s), and the chunk goes through LDS into the operand layout; piece q of row r lies in slot q ^ (r % 8) of its 128
+// bytes, which neither side's accesses conflict on.  A chunk of 64 bytes per row in flight, or one line in two instructions
+// a chunk apart, reaches 5.3 TB/s where 128 reach 6.9.  A wavefront's LDS traffic is in order, so one buffer serves every
+// chunk.  Rows of an odd number of 64 bytes end in half a chunk.
+// A tile costs 32 cycles per 32 bytes of its rows, a sixth of what its rows cost in memory time, so every tile is
+// formed, needed or not.
+template <int NG>
+__device__ __forceinline__ void stage_fetch(const int8_t *const (&rp)[4 * NG], int c, int rowbytes, int lane, v4i (&x)[4 * NG])
 {
+    int off = 128 * c;
+    if (off + 128 > rowbytes && (lane & 4)) off -= 64;      // half a chunk: its lanes twice
 #pragma unroll
-    for (int g = 0; g < NG; ++g)
-#pragma unroll
-        for (int s = 0; s < CH; ++s) x[g][s] = *(const v4i *)(rp[g] + (c * CH + s) * 32);
+    for (int i = 0; i < 4 * NG; ++i) x[i] = *(const v4i *)(rp[i] + off);
 }
 
-template <int NG, int CH>
-__device__ __forceinline__ void stream_tiles(const v4i (&x)[NG][CH], v16i (&G)[NG * (NG + 1) / 2])
+template <int NG>
+__device__ __forceinline__ void stage_store(char *stage, int lane, const v4i (&x)[4 * NG])
 {
+    char *p = stage + (lane >> 3) * 128 + (((lane & 7) ^ (lane >> 3)) << 4);
 #pragma unroll
-    for (int s = 0; s < CH; ++s)
+    for (int i = 0; i < 4 * NG; ++i) *(v4i *)(p + 1024 * i) = x[i];
+    wave_sync();
+}
+
+template <typename OP, int NG, int S0, int S1>
+__device__ __forceinline__ void stage_steps(const char *stage, int lane, typename OP::tile_t (&G)[NG * (NG + 1) / 2])
+{
+    const int l32 = lane & 31, half = lane >> 5;
+#pragma unroll
+    for (int s = S0; s < S1; ++s) {
+        v4i a[NG];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) a[g] = *(const v4i *)(stage + 4096 * g + l32 * 128 + (((2 * s + half) ^ (l32 & 7)) << 4));
 #pragma unroll
         for (int I = 0; I < NG; ++I)
 #pragma unroll
-            for (int J = 0; J <= I; ++J)
-                G[I * (I + 1) / 2 + J] = __builtin_amdgcn_mfma_i32_32x32x32_i8(x[J][s], x[I][s], G[I * (I + 1) / 2 + J], 0, 0, 0);
+            for (int J = 0; J <= I; ++J) G[I * (I + 1) / 2 + J] = OP::mac(a[J], a[I], G[I * (I + 1) / 2 + J]);
+    }
 }
 
-// Chunks 0 and 1 (in x0, x1) have been asked for; the buffers are free afterwards.
-template <int NG, int CH>
-__device__ __forceinline__ void stream_gram(const int8_t *const (&rp)[NG], int nchunk, v4i (&x0)[NG][CH], v4i (&x1)[NG][CH],
-                                            v16i (&G)[NG * (NG + 1) / 2])
+template <typename OP, int NG>
+__device__ __forceinline__ void stage_tiles(const char *stage, int c, int rowbytes, int lane, typename OP::tile_t (&G)[NG * (NG + 1) / 2])
 {
-    v4i x2[NG][CH];
-    const int last = nchunk - 1;
+    stage_steps<OP, NG, 0, 2>(stage, lane, G);
+    if (128 * c + 128 <= rowbytes) stage_steps<OP, NG, 2, 4>(stage, lane, G);      // wave-uniform
+    wave_sync();
+}
+
+// NBUF chunks are in flight: chunks 0 .. NBUF - 1 (in x0, x1) have been asked for; the buffers are free afterwards.  Loads past
+// the end re-read the last chunk.
+template <typename OP, int NG, int NBUF>
+__device__ __forceinline__ void stream_gram(const int8_t *const (&rp)[4 * NG], int rowbytes, int lane, char *stage, v4i (&x0)[4 * NG],
+                                            v4i (&x1)[4 * NG], typename OP::tile_t (&G)[NG * (NG + 1) / 2])
+{
+    const int nchunk = (rowbytes + 127) / 128, last = nchunk - 1;
 #pragma unroll
-    for (int t = 0; t < NG * (NG + 1) / 2; ++t) G[t] = (v16i)(0);
+    for (int t = 0; t < NG * (NG + 1) / 2; ++t) G[t] = (typename OP::tile_t)(0);
+    wave_sync();
 #pragma unroll 1
-    for (int c = 0; c < nchunk; c += 3) {
-        stream_fetch<NG, CH>(rp, c + 2 < last ? c + 2 : last, x2);
-        __builtin_amdgcn_sched_barrier(0);      // the loads first, then the matrix instructions they travel behind
-        stream_tiles<NG, CH>(x0, G);
+    for (int c = 0; c < nchunk; c += NBUF) {
+        stage_store<NG>(stage, lane, x0);
         __builtin_amdgcn_sched_barrier(0);
-        if (c + 1 < nchunk) {
-            stream_fetch<NG, CH>(rp, c + 3 < last ? c + 3 : last, x0);
+        stage_fetch<NG>(rp, c + NBUF < last ? c + NBUF : last, rowbytes, lane, x0);
+        __builtin_amdgcn_sched_barrier(0);
+        stage_tiles<OP, NG>(stage, c, rowbytes, lane, G);
+        if (NBUF == 2 && c + 1 < nchunk) {
+            stage_store<NG>(stage, lane, x1);
             __builtin_amdgcn_sched_barrier(0);
-            stream_tiles<NG, CH>(x1, G);
+            stage_fetch<NG>(rp, c + 3 < last ? c + 3 : last, rowbytes, lane, x1);
             __builtin_amdgcn_sched_barrier(0);
-        }
-        if (c + 2 < nchunk) {
-            stream_fetch<NG, CH>(rp, c + 4 < last ? c + 4 : last, x1);
-            __builtin_amdgcn_sched_barrier(0);
-            stream_tiles<NG, CH>(x2, G);
-            __builtin_amdgcn_sched_barrier(0);
+            stage_tiles<OP, NG>(stage, c + 1, rowbytes, lane, G);
         }
     }
-}
-
-// The body of Alg. 4's vertex loop for the vertex in `cur`, whose Gram tiles `gram` yields.  hold() names the
-// registers in flight for the trips after this one (see arrived).
-template <int NG, typename GRAM, typename HOLD>
-__device__ __forceinline__ void scan_vertex_u8(const ScanItem &cur, const GRAM &gram, MfmaScanSmem<NG> &sm, int R, u64 *__restrict__ keys,
-                                               int *__restrict__ deg, Prop *__restrict__ props,
-                                               int *__restrict__ nprop, int lane, u64 &tiles, u64 &rows,
-                                               u64 &nprops_total, u32 &ev_lane, HOLD hold)
-{
-    const int l32 = lane & 31, half = lane >> 5;
-    const int u = __builtin_amdgcn_readfirstlane(cur.u);      // same in every lane: keep it scalar
-    int m = __builtin_amdgcn_readfirstlane(cur.m);
-    if (m > 32 * NG) m = 32 * NG;   // cannot happen: the list is built per degree class
-    if (m > R) m = R;
-    u64 *row = keys + (size_t)u * R;
-    u64 kreg[2];
-    kreg[0] = lane < m ? cur.k[0] : KEY_PAD;
-    kreg[1] = (NG > 2 && lane + 64 < m) ? cur.k[1] : KEY_PAD;
-    u64 newm[2];
-    newm[0] = __builtin_amdgcn_ballot_w64(lane < m && (kreg[0] & 1ull));
-    newm[1] = __builtin_amdgcn_ballot_w64(NG > 2 && lane + 64 < m && (kreg[1] & 1ull));
-    const bool any_new = (newm[0] | newm[1]) != 0;   // else every pair was tested before
-    // what the scan leaves to be stored: per block one redirected edge per lane, and the kept set
-    u64 ekey[NG];
-    u32 etgt[NG];
-    int eslot[NG];
-    u32 Kw[NG];                             // U' as bit masks over list positions, 32 per word (uniform)
-#pragma unroll
-    for (int I = 0; I < NG; ++I) eslot[I] = -1, Kw[I] = 0, ekey[I] = 0, etgt[I] = 0;
-    int np_base = 0;
-    if (any_new) {
-    wave_sync();   // the previous vertex is done with the LDS tables
-    if (lane < 32 * NG) sm.id[lane] = (int)key_id(kreg[0]);
-    if (NG > 2 && lane + 64 < 32 * NG) sm.id[64 + lane] = (int)key_id(kreg[1]);
-    rows += m;
-    const u32 hm = 0x0F0F0F0Fu << (4 * half);   // the columns this half-wave holds
-
-#pragma unroll
-    for (int I = 0; I < NG; ++I) {
-        if (32 * I < m) {                   // wave-uniform
-            // the Gram tile of the block with itself; n of its rows is the diagonal, read back through
-            // LDS (rows past the list hold row 0 of X; no mask ever selects them)
-            const v16i G = gram.tile(I, I);
-            {
-                int4 *gt = (int4 *)(sm.gt + (32 * I + l32) * GT_STRIDE + 4 * half);
-                gt[0] = make_int4(G[0], G[1], G[2], G[3]);
-                gt[2] = make_int4(G[4], G[5], G[6], G[7]);
-                gt[4] = make_int4(G[8], G[9], G[10], G[11]);
-                gt[6] = make_int4(G[12], G[13], G[14], G[15]);
-            }
-            wave_sync();
-            const int nrI = sm.gt[(32 * I + l32) * GT_STRIDE + l32];
-            if (half == 0) sm.nrm[32 * I + l32] = nrI;
-            wave_sync();
-            // this block's rows in lane-per-row form (lane l32 <-> list position 32 I + l32), in both halves
-            const u64 kb = shfl_u64(kreg[I >> 1], 32 * (I & 1) + l32);
-            const int posi = 32 * I + l32;
-            const bool validi = posi < m;
-            const bool newi = kb & 1ull;
-            const int di = (int)key_dist(kb);
-            const int negt = di - nrI;
-            const u32 new_I = (u32)(newm[I >> 1] >> (32 * (I & 1)));
-            u32 F[NG], E[NG];
-#pragma unroll
-            for (int J = 0; J < NG; ++J) F[J] = E[J] = 0;
-#pragma unroll
-            for (int J = 0; J <= I; ++J) {
-                // a tile without a new row and without a new column holds only old/old pairs, which Alg. 4 skips
-                const u32 new_J = (u32)(newm[J >> 1] >> (32 * (J & 1)));
-                if ((new_I | new_J) == 0) continue;
-                tiles += 1;
-                // the old/old skip: a pair is tested only if v or w is new; only w before v count
-                u32 e = newi ? 0xFFFFFFFFu : new_J;
-                if (J == I) e &= (1u << l32) - 1u;
-                if (!validi) e = 0;
-                E[J] = e & hm;
-                // lane: row l32 of block I; acc[a]: column 8(a/4) + 4 half + a%4 of block J
-                v16i acc = G;
-                if (J < I) acc = gram.tile(I, J);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int4 nj = ((const int4 *)sm.nrm)[8 * J + 2 * q + half];
-                    acc[4 * q + 0] = (acc[4 * q + 0] << 1) + (negt - nj.x);
-                    acc[4 * q + 1] = (acc[4 * q + 1] << 1) + (negt - nj.y);
-                    acc[4 * q + 2] = (acc[4 * q + 2] << 1) + (negt - nj.z);
-                    acc[4 * q + 3] = (acc[4 * q + 3] << 1) + (negt - nj.w);
-                }
-                int4 *gt = (int4 *)(sm.gt + (32 * J + l32) * GT_STRIDE + 4 * half);
-                gt[0] = make_int4(acc[0], acc[1], acc[2], acc[3]);
-                gt[2] = make_int4(acc[4], acc[5], acc[6], acc[7]);
-                gt[4] = make_int4(acc[8], acc[9], acc[10], acc[11]);
-                gt[6] = make_int4(acc[12], acc[13], acc[14], acc[15]);
-                // bit a of ok: T < 0, v passes the prune test against column a
-                u32 ok = 0;
-#pragma unroll
-                for (int a = 15; a >= 0; --a) ok = __builtin_amdgcn_alignbit(ok, (u32)acc[a], 31);
-                // bit 4q + k  ->  column 8q + 4 half + k
-                ok = (ok | (ok << 8)) & 0x00FF00FFu;
-                ok = (ok | (ok << 4)) & 0x0F0F0F0Fu;
-                ok <<= 4 * half;
-                F[J] = E[J] & ~ok;
-            }
-            // the loop over v on masks; what the two half-waves find for a row is joined through ballots
-            bool pre = false;
-#pragma unroll
-            for (int J = 0; J < I; ++J) pre = pre || ((F[J] & Kw[J]) != 0);
-            const u64 preb = __builtin_amdgcn_ballot_w64(pre);
-            const u32 rem = (u32)(m - 32 * I);
-            const u32 vmask = rem >= 32u ? 0xFFFFFFFFu : ((1u << rem) - 1u);
-            const u32 Kmax = vmask & ~((u32)preb | (u32)(preb >> 32));
-            u32 Kcur = Kmax;
-            for (int sweep = 0; sweep < 33; ++sweep) {
-                const u64 hit = __builtin_amdgcn_ballot_w64((F[I] & Kcur) != 0);
-                const u32 Knew = Kmax & ~((u32)hit | (u32)(hit >> 32));
-                if (Knew == Kcur) break;
-                Kcur = Knew;
-            }
-            Kw[I] = Kcur;
-            const bool kept = (Kcur >> l32) & 1u;
-            const bool pruned = validi && !kept && half == 0;
-            // first failing w over both halves
-            int tgt = 0x7FFFFFFF;
-#pragma unroll
-            for (int J = I; J >= 0; --J) {
-                const u32 fk = F[J] & Kw[J];
-                if (fk) tgt = 32 * J + __builtin_ctz(fk);
-            }
-            {
-                const int other = __shfl_xor(tgt, 32);
-                tgt = other < tgt ? other : tgt;
-            }
-            // the evaluations Alg. 4 makes for this row: tested candidates up to and including w
-            int ev = 0;
-#pragma unroll
-            for (int J = 0; J <= I; ++J) {
-                const int rel = tgt - 32 * J;
-                const u32 upto = rel >= 31 ? 0xFFFFFFFFu : (rel < 0 ? 0u : ((2u << rel) - 1u));
-                ev += __popc(E[J] & Kw[J] & upto);
-            }
-            ev_lane += (u32)ev;
-            wave_sync();   // the tiles are in LDS
-            const u64 pm = __builtin_amdgcn_ballot_w64(pruned);
-            if (pruned) {
-                const int tv = sm.gt[((tgt & ~31) + l32) * GT_STRIDE + (tgt & 31)];
-                const u32 dvw = (u32)(di - tv);
-                // the redirect: v enters w's list
-                ekey[I] = make_key(dvw, key_id(kb), 1u);
-                etgt[I] = (u32)sm.id[tgt];
-                eslot[I] = np_base + __popcll(pm & lanes_below(lane));
-            }
-            np_base += __popcll(pm);
-            if (I + 1 < NG) wave_sync();   // before the next block overwrites the tiles
-        }
-    }
-    }
-    hold();     // every store of the trip comes after this point
-#pragma unroll
-    for (int I = 0; I < NG; ++I)
-        if (eslot[I] >= 0) emit_redirect(ekey[I], etgt[I], props + (size_t)u * R + eslot[I]);
-    // kept entries, flag old, compacted back into the row
-    const u64 K0 = (u64)Kw[0] | (NG > 1 ? ((u64)Kw[NG > 1 ? 1 : 0] << 32) : 0ull);
-    const u64 K1 = NG > 2 ? ((u64)Kw[NG > 2 ? 2 : 0] | (NG > 3 ? ((u64)Kw[NG > 3 ? 3 : 0] << 32) : 0ull)) : 0ull;
-    const int nk0 = __popcll(K0);
-    if ((K0 >> lane) & 1ull) row[__popcll(K0 & lanes_below(lane))] = kreg[0] & ~1ull;
-    if (NG > 2 && ((K1 >> lane) & 1ull)) row[nk0 + __popcll(K1 & lanes_below(lane))] = kreg[1] & ~1ull;
-    if (lane == 0) {
-        if (any_new) deg[u] = nk0 + __popcll(K1);
-        nprop[u] = np_base;
-    }
-    nprops_total += np_base;
 }
 
 // The work list is walked with a two-deep software pipeline: while vertex i is computed, the rows of
@@ -375,11 +181,11 @@ __device__ __forceinline__ void scan_vertex_u8(const ScanItem &cur, const GRAM &
 // list -> degree/list entries -> rows of X is paid once per wavefront, not once per vertex.  The loop
 // body is written out twice so that the two row buffers swap roles without being copied.
 // block `block` of `nblocks` walks the work list
-template <int NG, int KS>
-__device__ __forceinline__ void scan_list_body(const int8_t *__restrict__ X, int R, u64 *__restrict__ keys,
+template <typename OP, int NG, int KS>
+__device__ __forceinline__ void scan_list_body(const OP &op, const int8_t *__restrict__ X, int R, u64 *__restrict__ keys,
                                                int *__restrict__ deg, const int *__restrict__ list, u32 n_active,
                                                Prop *__restrict__ props, int *__restrict__ nprop,
-                                               RoundCtr *__restrict__ ctr, MfmaScanSmem<NG> &sm, u32 block, u32 nblocks)
+                                               RoundCtr *__restrict__ ctr, typename OP::template Smem<NG> &sm, u32 block, u32 nblocks)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar: the loop control stays on the scalar unit
     const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
@@ -417,7 +223,7 @@ __device__ __forceinline__ void scan_list_body(const int8_t *__restrict__ X, int
             const unsigned long long j = (unsigned long long)it + 3ull * nw;
             u_after = j < n_active ? list[j] : -1;
         }
-        scan_vertex_u8<NG>(cur, RowsGram<NG, KS>{A0}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total,
+        op.template list<NG>(cur, RowsGram<OP, NG, KS>{A0}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total,
                            ev_lane, [&] { hold(A1, aft); });
         cur = nxt;
         nxt = aft;
@@ -430,7 +236,7 @@ __device__ __forceinline__ void scan_list_body(const int8_t *__restrict__ X, int
             const unsigned long long j = (unsigned long long)it + 3ull * nw;
             u_after = j < n_active ? list[j] : -1;
         }
-        scan_vertex_u8<NG>(cur, RowsGram<NG, KS>{A1}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total,
+        op.template list<NG>(cur, RowsGram<OP, NG, KS>{A1}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total,
                            ev_lane, [&] { hold(A0, aft); });
         cur = nxt;
         nxt = aft;
@@ -445,56 +251,60 @@ __device__ __forceinline__ void scan_list_body(const int8_t *__restrict__ X, int
 
 // The same walk for rows of d > 128 bytes (d a multiple of 64).  The first two chunks of the next vertex's rows are
 // asked for as soon as the current one's matrix work is done, so they travel during its prune test and its stores.
-template <int NG>
-__device__ __forceinline__ void scan_list_stream_body(const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
+template <typename OP, int NG>
+__device__ __forceinline__ void scan_list_stream_body(const OP &op, const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
                                                       int *__restrict__ deg, const int *__restrict__ list, u32 n_active,
                                                       Prop *__restrict__ props, int *__restrict__ nprop,
-                                                      RoundCtr *__restrict__ ctr, MfmaScanSmem<NG> &sm, u32 block, u32 nblocks)
+                                                      RoundCtr *__restrict__ ctr, typename OP::template Smem<NG> &sm, u32 block, u32 nblocks)
 {
-    constexpr int CH = NG <= 2 ? 2 : 1;
+    constexpr int NBUF = NG == 1 ? 2 : 1;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+    int lane = threadIdx.x & 63;
     const u32 gw = block * 4 + wave, nw = nblocks * 4;
-    const int nchunk = d / (32 * CH);
+    const int last = (d + 127) / 128 - 1;
+    char *stage = (char *)sm.gt;
     u64 tiles = 0, rows = 0, nprops_total = 0;
     u32 ev_lane = 0;
 
     if (gw >= n_active) return;
-    auto row_pointers = [&](const ScanItem &it, const int8_t *(&rp)[NG]) {
+    // 16 bytes, piece lane % 8, of rows 8 i + lane / 8
+    auto row_pointers = [&](const ScanItem &it, const int8_t *(&rp)[4 * NG]) {
         const int m = it.m < 32 * NG ? it.m : 32 * NG;
 #pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            const int id = __shfl((int)key_id(it.k[g >> 1]), 32 * (g & 1) + l32);
-            const bool valid = it.u >= 0 && 32 * g + l32 < m;      // else row 0 (see scan_gather)
-            rp[g] = X + (size_t)(valid ? id : 0) * (size_t)d + half * 16;
+        for (int i = 0; i < 4 * NG; ++i) {
+            const int r = 8 * i + (lane >> 3), id = __shfl((int)key_id(it.k[i >> 3]), r & 63);
+            const bool valid = it.u >= 0 && r < m;      // else row 0 (see scan_gather)
+            rp[i] = X + (size_t)(valid ? id : 0) * (size_t)d + 16 * (lane & 7);
         }
     };
     ScanItem cur = scan_item_load<NG>(list[gw], keys, deg, R, lane);
     ScanItem nxt = scan_item_load<NG>(gw + nw < n_active ? list[gw + nw] : -1, keys, deg, R, lane);
     int u_after = gw + 2 * nw < n_active ? list[gw + 2 * nw] : -1;
-    const int8_t *rp[NG];
-    v4i x0[NG][CH], x1[NG][CH];
+    const int8_t *rp[4 * NG];
+    v4i x0[4 * NG], x1[4 * NG];
     row_pointers(cur, rp);
-    stream_fetch<NG, CH>(rp, 0, x0);
-    stream_fetch<NG, CH>(rp, 1, x1);
+    stage_fetch<NG>(rp, 0, d, lane, x0);
+    if (NBUF == 2) stage_fetch<NG>(rp, last < 1 ? last : 1, d, lane, x1);
 
     for (u32 it = gw;; it += nw) {
-        v16i G[NG * (NG + 1) / 2];
-        stream_gram<NG, CH>(rp, nchunk, x0, x1, G);
+        lane = afresh(lane);
+        typename OP::tile_t G[NG * (NG + 1) / 2];
+        stream_gram<OP, NG, NBUF>(rp, d, lane, stage, x0, x1, G);
         row_pointers(nxt, rp);
-        stream_fetch<NG, CH>(rp, 0, x0);
-        stream_fetch<NG, CH>(rp, 1, x1);
+        stage_fetch<NG>(rp, 0, d, lane, x0);
+        if (NBUF == 2) stage_fetch<NG>(rp, last < 1 ? last : 1, d, lane, x1);
         ScanItem aft = scan_item_load<NG>(u_after, keys, deg, R, lane);
         {
             const unsigned long long j = (unsigned long long)it + 3ull * nw;
             u_after = j < n_active ? list[j] : -1;
         }
-        scan_vertex_u8<NG>(cur, StreamedGram<NG>{G}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total,
+        op.template list<NG>(cur, StreamedGram<OP, NG>{G}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total,
                            ev_lane, [&] {
 #pragma unroll
-                               for (int g = 0; g < NG; ++g)
-#pragma unroll
-                                   for (int s = 0; s < CH; ++s) arrived(x0[g][s]), arrived(x1[g][s]);
+                               for (int i = 0; i < 4 * NG; ++i) {
+                                   arrived(x0[i]);
+                                   if (NBUF == 2) arrived(x1[i]);
+                               }
                                arrived(aft.k[0]), arrived(aft.m), arrived(u_after);
                                if (NG > 2) arrived(aft.k[1]);
                            });
@@ -509,25 +319,14 @@ __device__ __forceinline__ void scan_list_stream_body(const int8_t *__restrict__
 }
 
 // KS = 0: rows of d > 128 bytes, streamed
-template <int NG, int KS>
-__device__ __forceinline__ void scan_list_any(const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
+template <typename OP, int NG, int KS>
+__device__ __forceinline__ void scan_list_any(const OP &op, const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
                                               int *__restrict__ deg, const int *__restrict__ list, u32 n_active,
                                               Prop *__restrict__ props, int *__restrict__ nprop,
-                                              RoundCtr *__restrict__ ctr, MfmaScanSmem<NG> &sm, u32 block, u32 nblocks)
+                                              RoundCtr *__restrict__ ctr, typename OP::template Smem<NG> &sm, u32 block, u32 nblocks)
 {
-    if constexpr (KS == 0) scan_list_stream_body<NG>(X, d, R, keys, deg, list, n_active, props, nprop, ctr, sm, block, nblocks);
-    else scan_list_body<NG, KS>(X, R, keys, deg, list, n_active, props, nprop, ctr, sm, block, nblocks);
-}
-
-// (four groups of streamed rows: 160 accumulator registers, so one block per CU)
-template <int NG, int KS>
-__global__ __launch_bounds__(256, (NG == 1 ? 5 : NG == 2 ? 3 : KS == 0 && NG == 4 ? 1 : 2)) void k_update_scan_mfma_u8(
-    const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
-    int *__restrict__ deg, const int *__restrict__ list, const u32 *__restrict__ n_list,
-    Prop *__restrict__ props, int *__restrict__ nprop, RoundCtr *__restrict__ ctr)
-{
-    __shared__ MfmaScanSmem<NG> smem[4];
-    scan_list_any<NG, KS>(X, d, R, keys, deg, list, *n_list, props, nprop, ctr, smem[threadIdx.x >> 6], blockIdx.x, gridDim.x);
+    if constexpr (KS == 0) scan_list_stream_body<OP, NG>(op, X, d, R, keys, deg, list, n_active, props, nprop, ctr, sm, block, nblocks);
+    else scan_list_body<OP, NG, KS>(op, X, R, keys, deg, list, n_active, props, nprop, ctr, sm, block, nblocks);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -567,135 +366,14 @@ __device__ __forceinline__ void pack_gather(const int8_t *__restrict__ X, const 
     for (int s = 0; s < KS; ++s) A[0][s] = *(const v4i *)(p + s * 32);
 }
 
-template <int P, typename GRAM, typename HOLD>
-__device__ __forceinline__ void pack_vertices_u8(const PackItem &cur, const GRAM &gram, MfmaScanSmem<1> &sm, int R,
-                                                 u64 *__restrict__ keys, int *__restrict__ deg,
-                                                 Prop *__restrict__ props, int *__restrict__ nprop, int lane,
-                                                 u32 &tiles, u32 &rows, u32 &nprops_total, u32 &ev_lane, HOLD hold)
-{
-    constexpr int W = 32 / P;
-    const int l32 = lane & 31, half = lane >> 5, seg = l32 / W, pos = l32 % W;
-    const int u = cur.u;
-    int m = cur.m;
-    if (m > W) m = W;   // cannot happen: the list is built per degree class
-    if (m > R) m = R;
-    const bool valid = u >= 0 && pos < m;
-    const u64 kb = valid ? cur.k : KEY_PAD;
-    const bool newi = valid && (kb & 1ull);
-    const bool leader = u >= 0 && pos == 0 && half == 0;
-    const u32 new32 = (u32)__builtin_amdgcn_ballot_w64(newi && half == 0);
-    const bool any_new = new32 != 0;   // else nothing is new in any of the P lists: every pair was tested before
-    const u32 segmask = (W == 32 ? 0xFFFFFFFFu : ((1u << (W & 31)) - 1u) << (seg * W));
-    const u32 below = (1u << l32) - 1u;
-    // what the scan leaves to be stored
-    bool pruned = false, kept = false;
-    u32 Kcur = 0, pm = 0, dvw = 0, tgt_id = 0;
-    if (any_new) {
-        const u32 vmask = (u32)__builtin_amdgcn_ballot_w64(valid && half == 0);
-        wave_sync();   // the previous group is done with the LDS tables
-        if (half == 0) sm.id[l32] = (int)key_id(kb);
-        // n of every row: the diagonal of the Gram tile, through LDS (rows past a list hold row 0 of X;
-        // no mask ever selects them)
-        // lane: row l32; G[a]: <x_row, x_col> for column 8(a/4) + 4 half + a%4
-        const v16i G = gram.tile(0, 0);
-        {
-            int4 *gt = (int4 *)(sm.gt + l32 * GT_STRIDE + 4 * half);
-            gt[0] = make_int4(G[0], G[1], G[2], G[3]);
-            gt[2] = make_int4(G[4], G[5], G[6], G[7]);
-            gt[4] = make_int4(G[8], G[9], G[10], G[11]);
-            gt[6] = make_int4(G[12], G[13], G[14], G[15]);
-        }
-        wave_sync();
-        const int ni = sm.gt[l32 * GT_STRIDE + l32];
-        if (half == 0) sm.nrm[l32] = ni;
-        rows += __popc(vmask);
-        tiles += 1;
-        wave_sync();
-
-        const int di = (int)key_dist(kb);
-        const int negt = di - ni;
-        const u32 hm = 0x0F0F0F0Fu << (4 * half);   // the columns this half-wave holds
-        // the old/old skip: a pair is tested only if v or w is new; only w before v (in v's own list) count
-        u32 E = newi ? segmask : (new32 & segmask);
-        E &= below;
-        if (!valid) E = 0;
-        E &= hm;
-        // T = 2 G - n_j - t_i from the Gram tile that gave the norms
-        v16i acc;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int4 nj = ((const int4 *)sm.nrm)[2 * q + half];
-            acc[4 * q + 0] = (G[4 * q + 0] << 1) + (negt - nj.x);
-            acc[4 * q + 1] = (G[4 * q + 1] << 1) + (negt - nj.y);
-            acc[4 * q + 2] = (G[4 * q + 2] << 1) + (negt - nj.z);
-            acc[4 * q + 3] = (G[4 * q + 3] << 1) + (negt - nj.w);
-        }
-        {
-            int4 *gt = (int4 *)(sm.gt + l32 * GT_STRIDE + 4 * half);
-            gt[0] = make_int4(acc[0], acc[1], acc[2], acc[3]);
-            gt[2] = make_int4(acc[4], acc[5], acc[6], acc[7]);
-            gt[4] = make_int4(acc[8], acc[9], acc[10], acc[11]);
-            gt[6] = make_int4(acc[12], acc[13], acc[14], acc[15]);
-        }
-        // bit a of ok: T < 0, v passes the prune test against column a
-        u32 ok = 0;
-#pragma unroll
-        for (int a = 15; a >= 0; --a) ok = __builtin_amdgcn_alignbit(ok, (u32)acc[a], 31);
-        // bit 4q + k  ->  column 8q + 4 half + k
-        ok = (ok | (ok << 8)) & 0x00FF00FFu;
-        ok = (ok | (ok << 4)) & 0x0F0F0F0Fu;
-        ok <<= 4 * half;
-        const u32 F = E & ~ok;
-        // the loop over v on masks; what the two half-waves find for a row is joined through ballots
-        Kcur = vmask;
-        for (int sweep = 0; sweep < 33; ++sweep) {
-            const u64 hit = __builtin_amdgcn_ballot_w64((F & Kcur) != 0);
-            const u32 Knew = vmask & ~((u32)hit | (u32)(hit >> 32));
-            if (Knew == Kcur) break;
-            Kcur = Knew;
-        }
-        kept = (Kcur >> l32) & 1u;
-        pruned = valid && !kept && half == 0;
-        // first failing w over both halves
-        int tgt = 0x7FFFFFFF;
-        {
-            const u32 fk = F & Kcur;
-            if (fk) tgt = __builtin_ctz(fk);
-            const int other = __shfl_xor(tgt, 32);
-            tgt = other < tgt ? other : tgt;
-        }
-        // the evaluations Alg. 4 makes for this row: tested candidates up to and including w
-        {
-            const u32 upto = tgt >= 31 ? 0xFFFFFFFFu : ((2u << tgt) - 1u);
-            ev_lane += (u32)__popc(E & Kcur & upto);
-        }
-        wave_sync();   // the tile is in LDS
-        pm = (u32)__builtin_amdgcn_ballot_w64(pruned);
-        if (pruned) {
-            dvw = (u32)(di - sm.gt[l32 * GT_STRIDE + tgt]);
-            tgt_id = (u32)sm.id[tgt];
-        }
-        nprops_total += __popc(pm);
-    }
-    hold();     // every store of the trip comes after this point
-    // the redirect: v enters w's list
-    if (pruned) emit_redirect(make_key(dvw, key_id(kb), 1u), tgt_id, props + (size_t)u * R + __popc(pm & segmask & below));
-    // kept entries, flag old, compacted back into the row
-    if (kept && half == 0) keys[(size_t)u * R + __popc(Kcur & segmask & below)] = kb & ~1ull;
-    if (leader) {
-        if (any_new) deg[u] = __popc(Kcur & segmask);
-        nprop[u] = __popc(pm & segmask);
-    }
-}
-
 // Same two-deep software pipeline as k_update_scan_mfma_u8; trip g of a wavefront takes list entries
 // [P g, P g + P).
-template <int P, int KS>
-__device__ __forceinline__ void scan_packed_body(const int8_t *__restrict__ X, int R, u64 *__restrict__ keys,
+template <typename OP, int P, int KS>
+__device__ __forceinline__ void scan_packed_body(const OP &op, const int8_t *__restrict__ X, int R, u64 *__restrict__ keys,
                                                  int *__restrict__ deg, const int *__restrict__ list,
                                                  u32 n_active, Prop *__restrict__ props,
                                                  int *__restrict__ nprop, RoundCtr *__restrict__ ctr,
-                                                 MfmaScanSmem<1> &sm, u32 block, u32 nblocks)
+                                                 typename OP::template Smem<1> &sm, u32 block, u32 nblocks)
 {
     constexpr int W = 32 / P;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar: the loop control stays on the scalar unit
@@ -732,7 +410,7 @@ __device__ __forceinline__ void scan_packed_body(const int8_t *__restrict__ X, i
         pack_gather<P, KS>(X, nxt, pos, half, A1);
         PackItem aft = pack_item_load<P>(u_after, keys, deg, R, pos);
         u_after = vertex_of((unsigned long long)it + 3ull * nw);
-        pack_vertices_u8<P>(cur, RowsGram<1, KS>{A0}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total, ev_lane,
+        op.template pack<P>(cur, RowsGram<OP, 1, KS>{A0}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total, ev_lane,
                             [&] { hold(A1, aft); });
         cur = nxt;
         nxt = aft;
@@ -742,7 +420,7 @@ __device__ __forceinline__ void scan_packed_body(const int8_t *__restrict__ X, i
         pack_gather<P, KS>(X, nxt, pos, half, A0);
         aft = pack_item_load<P>(u_after, keys, deg, R, pos);
         u_after = vertex_of((unsigned long long)it + 3ull * nw);
-        pack_vertices_u8<P>(cur, RowsGram<1, KS>{A1}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total, ev_lane,
+        op.template pack<P>(cur, RowsGram<OP, 1, KS>{A1}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total, ev_lane,
                             [&] { hold(A0, aft); });
         cur = nxt;
         nxt = aft;
@@ -756,53 +434,57 @@ __device__ __forceinline__ void scan_packed_body(const int8_t *__restrict__ X, i
 }
 
 // The same for rows of d > 128 bytes (see scan_list_stream_body).
-template <int P>
-__device__ __forceinline__ void scan_packed_stream_body(const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
+template <typename OP, int P>
+__device__ __forceinline__ void scan_packed_stream_body(const OP &op, const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
                                                         int *__restrict__ deg, const int *__restrict__ list,
                                                         u32 n_active, Prop *__restrict__ props,
                                                         int *__restrict__ nprop, RoundCtr *__restrict__ ctr,
-                                                        MfmaScanSmem<1> &sm, u32 block, u32 nblocks)
+                                                        typename OP::template Smem<1> &sm, u32 block, u32 nblocks)
 {
-    constexpr int W = 32 / P, CH = 2;
+    constexpr int W = 32 / P;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
-    const int seg = l32 / W, pos = l32 % W;
+    int lane = threadIdx.x & 63;
     const u32 gw = block * 4 + wave, nw = nblocks * 4;
     const u32 n_groups = (n_active + (u32)P - 1u) / (u32)P;
-    const int nchunk = d / (32 * CH);
+    const int last = (d + 127) / 128 - 1;
+    char *stage = (char *)sm.gt;
     u32 tiles = 0, rows = 0, nprops_total = 0;
     u32 ev_lane = 0;
 
     if (gw >= n_groups) return;
     auto vertex_of = [&](unsigned long long g) -> int {
-        const unsigned long long idx = g * P + (unsigned)seg;
+        const unsigned long long idx = g * P + (unsigned)((lane & 31) / W);
         return (g < n_groups && idx < n_active) ? list[idx] : -1;
     };
-    auto row_pointer = [&](const PackItem &it, const int8_t *(&rp)[1]) {
-        const bool valid = it.u >= 0 && pos < (it.m < W ? it.m : W);      // else row 0 (see scan_gather)
-        rp[0] = X + (size_t)(valid ? key_id(it.k) : 0u) * (size_t)d + half * 16;
+    // lane l32 of either half holds the list entry of row l32; 16 bytes, piece lane % 8, of rows 8 i + lane / 8
+    auto row_pointers = [&](const PackItem &it, const int8_t *(&rp)[4]) {
+        const bool valid = it.u >= 0 && (lane & 31) % W < (it.m < W ? it.m : W);      // else row 0 (see scan_gather)
+        const int mine = valid ? (int)key_id(it.k) : 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) rp[i] = X + (size_t)__shfl(mine, 8 * i + (lane >> 3)) * (size_t)d + 16 * (lane & 7);
     };
-    PackItem cur = pack_item_load<P>(vertex_of(gw), keys, deg, R, pos);
-    PackItem nxt = pack_item_load<P>(vertex_of((unsigned long long)gw + nw), keys, deg, R, pos);
+    PackItem cur = pack_item_load<P>(vertex_of(gw), keys, deg, R, (lane & 31) % W);
+    PackItem nxt = pack_item_load<P>(vertex_of((unsigned long long)gw + nw), keys, deg, R, (lane & 31) % W);
     int u_after = vertex_of((unsigned long long)gw + 2ull * nw);
-    const int8_t *rp[1];
-    v4i x0[1][CH], x1[1][CH];
-    row_pointer(cur, rp);
-    stream_fetch<1, CH>(rp, 0, x0);
-    stream_fetch<1, CH>(rp, 1, x1);
+    const int8_t *rp[4];
+    v4i x0[4], x1[4];
+    row_pointers(cur, rp);
+    stage_fetch<1>(rp, 0, d, lane, x0);
+    stage_fetch<1>(rp, last < 1 ? last : 1, d, lane, x1);
 
     for (u32 it = gw;; it += nw) {
-        v16i G[1];
-        stream_gram<1, CH>(rp, nchunk, x0, x1, G);
-        row_pointer(nxt, rp);
-        stream_fetch<1, CH>(rp, 0, x0);
-        stream_fetch<1, CH>(rp, 1, x1);
-        PackItem aft = pack_item_load<P>(u_after, keys, deg, R, pos);
+        lane = afresh(lane);
+        typename OP::tile_t G[1];
+        stream_gram<OP, 1, 2>(rp, d, lane, stage, x0, x1, G);
+        row_pointers(nxt, rp);
+        stage_fetch<1>(rp, 0, d, lane, x0);
+        stage_fetch<1>(rp, last < 1 ? last : 1, d, lane, x1);
+        PackItem aft = pack_item_load<P>(u_after, keys, deg, R, (lane & 31) % W);
         u_after = vertex_of((unsigned long long)it + 3ull * nw);
-        pack_vertices_u8<P>(cur, StreamedGram<1>{G}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total, ev_lane,
+        op.template pack<P>(cur, StreamedGram<OP, 1>{G}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total, ev_lane,
                             [&] {
 #pragma unroll
-                                for (int s = 0; s < CH; ++s) arrived(x0[0][s]), arrived(x1[0][s]);
+                                for (int i = 0; i < 4; ++i) arrived(x0[i]), arrived(x1[i]);
                                 arrived(aft.k), arrived(aft.m), arrived(u_after);
                             });
         cur = nxt;
@@ -815,33 +497,14 @@ __device__ __forceinline__ void scan_packed_stream_body(const int8_t *__restrict
     if (lane == 0 && rows) add_round_stats(ctr, evals_algo, (u64)tiles * 1024ull, rows, nprops_total);
 }
 
-template <int P, int KS>
-__device__ __forceinline__ void scan_packed_any(const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
+template <typename OP, int P, int KS>
+__device__ __forceinline__ void scan_packed_any(const OP &op, const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
                                                 int *__restrict__ deg, const int *__restrict__ list, u32 n_active,
                                                 Prop *__restrict__ props, int *__restrict__ nprop,
-                                                RoundCtr *__restrict__ ctr, MfmaScanSmem<1> &sm, u32 block, u32 nblocks)
+                                                RoundCtr *__restrict__ ctr, typename OP::template Smem<1> &sm, u32 block, u32 nblocks)
 {
-    if constexpr (KS == 0) scan_packed_stream_body<P>(X, d, R, keys, deg, list, n_active, props, nprop, ctr, sm, block, nblocks);
-    else scan_packed_body<P, KS>(X, R, keys, deg, list, n_active, props, nprop, ctr, sm, block, nblocks);
-}
-
-// The three short-list classes in one launch: blockIdx.y = degree class (lists of at most 8, 16, 32
-// entries: 4, 2, 1 vertices per wavefront).  Each class is walked by the gridDim.x blocks of its row.
-template <int KS>
-__global__ __launch_bounds__(256, 4) void k_update_scan_mfma_u8_small(
-    const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
-    const int *__restrict__ lists, long long N, Prop *__restrict__ props, int *__restrict__ nprop,
-    RoundCtr *__restrict__ ctr)
-{
-    __shared__ MfmaScanSmem<1> smem[4];
-    MfmaScanSmem<1> &sm = smem[threadIdx.x >> 6];
-    const int y = blockIdx.y;
-    const int *list = lists + (size_t)y * N;
-    const u32 n = ctr->n_active[y];
-    stamp_scan_start(ctr);
-    if (y == 0) scan_packed_any<4, KS>(X, d, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
-    else if (y == 1) scan_packed_any<2, KS>(X, d, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
-    else scan_packed_any<1, KS>(X, d, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
+    if constexpr (KS == 0) scan_packed_stream_body<OP, P>(op, X, d, R, keys, deg, list, n_active, props, nprop, ctr, sm, block, nblocks);
+    else scan_packed_body<OP, P, KS>(op, X, R, keys, deg, list, n_active, props, nprop, ctr, sm, block, nblocks);
 }
 
 // Divides the grid's blocks among NC classes in proportion to their work, n[c] lists of weight[c] each; the grid has
@@ -881,48 +544,4 @@ __device__ __forceinline__ int share_blocks(const u32 (&n)[NC], const u32 (&weig
     }
     block = blockIdx.x - first;
     return cls;      // (-1 cannot happen here: the shares add up to the grid)
-}
-
-// Classes C0 .. NC - 1 in one launch, all of them resident together: the grid's blocks are divided among the
-// classes in proportion to their work (active lists x matrix tiles per list), one block at least for a class
-// that has any; every block derives the same division from the round's counters.  The classes then share the
-// start-up and the tail that each launch of its own pays.  NC classes: 3 short-list ones, then lists of at
-// most 64, 96, 128 entries.  Every block carries the registers and the LDS of the longest class (two blocks
-// per CU).  C0 = 0, every class: for inputs so small that no class alone has enough lists to fill the chip
-// (the short-list classes lose occupancy: with many active lists their own launch is faster).  C0 = 3, the
-// long-list classes only, next to k_update_scan_mfma_u8_small: for large inputs.
-template <int KS, int NC, int C0 = 0>
-__global__ __launch_bounds__(256, (KS == 0 && NC == 6 ? 1 : 2)) void k_update_scan_mfma_u8_all(
-    const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
-    const int *__restrict__ lists, long long N, Prop *__restrict__ props, int *__restrict__ nprop,
-    RoundCtr *__restrict__ ctr)
-{
-    constexpr int NGMAX = NC - 2;
-    static_assert(NC >= 4 && NC <= 6, "short lists plus one to three long-list classes");
-    __shared__ MfmaScanSmem<NGMAX> smem[4];
-    if (C0 == 0) stamp_scan_start(ctr);
-    // work per list: 4, 2, 1 lists share a tile; among the longer classes in proportion to their NG (NG + 1) / 2
-    // tiles (3 : 6 : 10; the division is sensitive there: 3 : 4.5 or 3 : 8 costs the 1M build 4 % of its scan time),
-    // and a 64-entry list weighted 2.25 short tiles (measured on 100,000 vertices: 1.5 -> 1.60 ms, 2 -> 1.51, 2.25 ->
-    // 1.49, 3 -> 1.53, 4 -> 1.70 ms of scan time per build)
-    // streamed rows (KS = 0): the rows' bytes dominate, and a list of a class holds 6, 12, 24, 46, 78, 112 of them or so
-    constexpr u32 weight[6] = {4u, 8u, 16u, KS ? 36u : 30u, KS ? 72u : 50u, KS ? 120u : 72u};
-    u32 n[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) n[c] = c >= C0 ? ctr->n_active[c] : 0u;
-    u32 block, mine;
-    const int cls = share_blocks<NC>(n, weight, block, mine);
-    if (cls < 0) return;
-    const int *list = lists + (size_t)cls * N;
-    const int wave = threadIdx.x >> 6;
-    MfmaScanSmem<1> &sm1 = *reinterpret_cast<MfmaScanSmem<1> *>(&smem[wave]);
-    if (C0 == 0 && cls == 0) scan_packed_any<4, KS>(X, d, R, keys, deg, list, n[0], props, nprop, ctr, sm1, block, mine);
-    else if (C0 == 0 && cls == 1) scan_packed_any<2, KS>(X, d, R, keys, deg, list, n[1], props, nprop, ctr, sm1, block, mine);
-    else if (C0 == 0 && cls == 2) scan_packed_any<1, KS>(X, d, R, keys, deg, list, n[2], props, nprop, ctr, sm1, block, mine);
-    else if (cls == 3)
-        scan_list_any<2, KS>(X, d, R, keys, deg, list, n[3], props, nprop, ctr, *reinterpret_cast<MfmaScanSmem<2> *>(&smem[wave]), block, mine);
-    else if (NC > 4 && cls == 4)
-        scan_list_any<3, KS>(X, d, R, keys, deg, list, n[NC > 4 ? 4 : 0], props, nprop, ctr, *reinterpret_cast<MfmaScanSmem<3> *>(&smem[wave]), block, mine);
-    else if (NC > 5 && cls == 5)
-        scan_list_any<4, KS>(X, d, R, keys, deg, list, n[NC > 5 ? 5 : 0], props, nprop, ctr, *reinterpret_cast<MfmaScanSmem<4> *>(&smem[wave]), block, mine);
 }

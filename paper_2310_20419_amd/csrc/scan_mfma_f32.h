@@ -26,7 +26,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "round.h"
 #include "scan_pairs.h"
+#include "scan_mfma.h"
 #include "wave_prims.h"
 
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -66,8 +68,6 @@ __device__ __forceinline__ u32 transpose16_bits(u32 w, int lane)
     return w & 0xFFFFu;
 }
 
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 template <bool FAST> struct GramAcc { typedef v4d type; typedef double norm; };
 template <> struct GramAcc<true> { typedef v4f type; typedef float norm; };
@@ -93,26 +93,6 @@ template <int DT> struct ChunkCoords { static constexpr int n = (DT == DT_F16 ||
 template <int NR, int CH, u32 TM, int DT, typename ACC, typename NRT>
 __device__ __forceinline__ void gram_chunk(const uint4 (&x)[NR][CH], ACC (&acc)[NR * (NR + 1) / 2], NRT (&nr)[NR], u32 need)
 {
-    if constexpr (sizeof(acc[0][0]) == 4 && (DT == DT_F16 || DT == DT_BF16)) {
-        // 16-bit rows, single-precision form: the 16 bytes a lane holds are 8 coordinates in the operand format of
-        // v_mfma_f32_16x16x32_{f16,bf16} as they are (products of two such numbers are exact in float); the norms
-        // come from the diagonal tiles afterwards, so `need` includes those
-#pragma unroll
-        for (int j = 0; j < CH; ++j)
-#pragma unroll
-            for (int I = 0; I < NR; ++I)
-#pragma unroll
-                for (int J = 0; J <= I; ++J)
-                    if (TM ? ((TM >> (I * (I + 1) / 2 + J)) & 1u) != 0 : ((need >> (I * (I + 1) / 2 + J)) & 1u) != 0) {   // wave-uniform
-                        if constexpr (DT == DT_F16)
-                            acc[I * (I + 1) / 2 + J] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                                __builtin_bit_cast(v8h, x[I][j]), __builtin_bit_cast(v8h, x[J][j]), acc[I * (I + 1) / 2 + J], 0, 0, 0);
-                        else
-                            acc[I * (I + 1) / 2 + J] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                __builtin_bit_cast(v8bf, x[I][j]), __builtin_bit_cast(v8bf, x[J][j]), acc[I * (I + 1) / 2 + J], 0, 0, 0);
-                    }
-        return;
-    }
 #pragma unroll
     for (int j = 0; j < CH; ++j)
 #pragma unroll
@@ -227,179 +207,6 @@ __device__ __forceinline__ void gram_f32_loop(const char *const (&rp)[NR], int n
     }
 }
 
-// Rows the matrix instructions cannot take as they lie in X (a length that is no multiple of 64 bytes, or an X that is
-// not 16-byte aligned): a copy with rows of rb bytes, a multiple of 128, zeros past the end of a row (they add nothing
-// to a product or to a squared difference).  A distance must come out with the same bits as from X itself, because
-// RandomGraph and the step-wise calls compute it there and equal edges must carry equal keys.  dist.h adds the
-// coordinates of lane s of 8 in the order of the lane's 16-byte pieces s, s + 8, ... where X can be read in such pieces:
-// then the copy keeps the order of the coordinates (permute = 0).  Otherwise lane s takes coordinates s, s + 8, ...
-// one by one, and the copy puts the next coordinates of that sequence into the lane's next piece: piece 8 b + s holds
-// coordinates V b + s, V b + s + 8, ... (V = 128 / size of a coordinate; permute = 1).  Distances and products do not
-// depend on the order of the coordinates otherwise.  The copy streams (200,000 x 100: about 60 us); the build it makes
-// possible: 200,000 x 100 float 95.7 -> 34.0 ms, S = 20, R = 96, 60 rounds.
-template <typename T>      // uint32_t: float rows, unsigned short: 16-bit rows
-__device__ __forceinline__ uint4 padded_piece(const T *x, int c, int d, int permute, u32 exponent, bool &odd)     // piece c of the copy of row x
-{
-    constexpr int V = 16 / (int)sizeof(T);      // coordinates per piece
-    const int e0 = permute ? 8 * V * (c >> 3) + (c & 7) : V * c, step = permute ? 8 : 1;
-    T t[V];
-#pragma unroll
-    for (int k = 0; k < V; ++k) {
-        const int e = e0 + k * step;
-        t[k] = e < d ? x[e] : (T)0;
-        odd = odd || ((u32)t[k] & exponent) == exponent;       // exponent bits all set: NaN or infinity
-    }
-    if constexpr (sizeof(T) == 4)
-        return make_uint4(t[0], t[1], t[2], t[3]);
-    else
-        return make_uint4((u32)t[0] | (u32)t[1] << 16, (u32)t[2] | (u32)t[3] << 16, (u32)t[V - 4] | (u32)t[V - 3] << 16,
-                          (u32)t[V - 2] | (u32)t[V - 1] << 16);
-}
-
-template <typename T>
-__device__ __forceinline__ bool pad_all_rows(const T *__restrict__ X, long long N, int d, u32 rb, int permute, u32 exponent, uint4 *__restrict__ Xp)
-{
-    const u32 pieces = rb / 16u;
-    bool odd = false;
-    for (u64 i = (u64)blockIdx.x * 256u + threadIdx.x; i < (u64)N * pieces; i += (u64)gridDim.x * 256u) {
-        const u64 u = i / pieces;
-        Xp[i] = padded_piece<T>(X + u * (u64)d, (int)(i - u * pieces), d, permute, exponent, odd);
-    }
-    return odd;
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_prepare_rows(const T *__restrict__ X, long long N, int d, u32 rb, int permute,
-                                                      u32 exponent, uint4 *__restrict__ Xp, u32 *__restrict__ nonfinite)
-{
-    if (pad_all_rows<T>(X, N, d, rb, permute, exponent, Xp)) *nonfinite = 1u;
-}
-
-
-// The half-precision copy of float32 rows that the first form's Gram block is computed from: row i is h_i, the binary16
-// rounding of (x_i - centre) 2^exponent, zeros up to rowbytes.  Distances do not depend on the centre, the mean of a
-// sample of rows, which keeps the rounding small for rows far from the origin; the exponent puts the sample's root mean
-// square near 2^-4, so that coordinates a million times larger still fit (what does not, or is not finite, becomes a NaN,
-// and every pair of its row is left to the exact routine).  With r_i = |(x_i - centre) 2^exponent - h_i|, a Euclidean norm
-// measured for every row in double precision, r_i <= share |h_i| + rest holds for all rows.
-struct HalfPar {
-    u32 share_bits, rest_bits;     // bits of non-negative floats order like the floats
-    int exponent, pad;
-};
-struct HalfRows {
-    const char *rows = nullptr;
-    u32 rowbytes = 0;
-    const HalfPar *par = nullptr;
-};
-#define HALF_SAMPLE 512          // rows the centre is the mean of
-
-// centre[c] = mean of coordinate c over the sample, square[b] = sum of the squared deviations of the 64 coordinates of block b.
-__global__ __launch_bounds__(256) void k_half_centre(const float *__restrict__ X, long long N, int d, float *__restrict__ centre,
-                                                     float *__restrict__ square, HalfPar *__restrict__ par)
-{
-    __shared__ float s[4][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int c = blockIdx.x * 64 + lane, n = (int)(N < HALF_SAMPLE ? N : HALF_SAMPLE);
-    const float *col = X + (c < d ? c : d - 1);
-    if (blockIdx.x == 0 && threadIdx.x == 0) par->share_bits = par->rest_bits = 0u;
-    float sum = 0.f;
-#pragma unroll 16
-    for (int i = wave; i < n; i += 4) {
-        const float x = col[(size_t)(i * N / n) * d];
-        sum += fabsf(x) <= 3.0e38f ? x * (1.f / HALF_SAMPLE) : 0.f;
-    }
-    s[wave][lane] = sum;
-    __syncthreads();
-    const float mean = (s[0][lane] + s[1][lane] + s[2][lane] + s[3][lane]) * ((float)HALF_SAMPLE / (float)n);
-    __syncthreads();
-    sum = 0.f;
-#pragma unroll 16
-    for (int i = wave; i < n; i += 4) {
-        const float x = col[(size_t)(i * N / n) * d] - mean;
-        sum += fabsf(x) <= 1.0e16f ? x * x : 0.f;
-    }
-    s[wave][lane] = c < d ? sum : 0.f;
-    __syncthreads();
-    if (wave == 0) {
-        if (c < d) centre[c] = mean;
-        sum = s[0][lane] + s[1][lane] + s[2][lane] + s[3][lane];
-        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-        if (lane == 0) square[blockIdx.x] = sum;
-    }
-}
-
-// L lanes per row, 8 coordinates (16 bytes of the copy) per lane and trip.
-template <int L>
-__global__ __launch_bounds__(256) void k_half_rows(const float *__restrict__ X, long long N, int d, int vec_ok, u32 rowbytes,
-                                                   const float *__restrict__ centre, const float *__restrict__ square,
-                                                   char *__restrict__ H, HalfPar *__restrict__ par)
-{
-    __shared__ float s[4][2];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = lane & (L - 1);
-    const int n = (int)(N < HALF_SAMPLE ? N : HALF_SAMPLE), nsq = (d + 63) / 64;
-    double tot = 0.0;
-    for (int k = lane; k < nsq; k += 64) tot += (double)square[k];
-    for (int o = 32; o > 0; o >>= 1) tot += __builtin_bit_cast(double, shfl_xor_u64(__builtin_bit_cast(u64, tot), o));
-    const float ms = (float)(tot / ((double)n * (double)d));
-    int e = ms > 0.f && ms < 3.0e38f ? -4 - (ilogbf(ms) >> 1) : 0;
-    e = e < -60 ? -60 : e > 60 ? 60 : e;
-    if (blockIdx.x == 0 && threadIdx.x == 0) par->exponent = e;
-    const float scale = ldexpf(1.f, e);
-    const int pieces = (int)(rowbytes / 16u);
-    const float small = (float)d * 0x1p-18f;
-    float share = 0.f, rest = 0.f;
-    for (u64 row = ((u64)blockIdx.x * 256u + threadIdx.x) / L; row < (u64)N; row += (u64)gridDim.x * (256u / L)) {
-        const float *x = X + row * (u64)d;
-        double err = 0.0;
-        float nrm = 0.f;
-        for (int p = sub; p < pieces; p += L) {
-            v8h h;
-            float v[8], m[8];
-            if (vec_ok && 8 * p + 8 <= d) {
-                *(float4 *)&v[0] = ((const float4 *)(x + 8 * p))[0];
-                *(float4 *)&v[4] = ((const float4 *)(x + 8 * p))[1];
-                *(float4 *)&m[0] = ((const float4 *)(centre + 8 * p))[0];
-                *(float4 *)&m[4] = ((const float4 *)(centre + 8 * p))[1];
-            } else {
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const int c = 8 * p + k;
-                    v[k] = c < d ? x[c] : 0.f;
-                    m[k] = c < d ? centre[c] : 0.f;
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const float t = (v[k] - m[k]) * scale;
-                h[k] = fabsf(t) <= 65504.f ? (_Float16)t : (_Float16)__uint_as_float(0x7FC00000u);
-                const float hf = (float)h[k];
-                const double r = ((double)v[k] - (double)m[k]) * (double)scale - (double)hf;
-                err = fma(r, r, err);
-                nrm = fmaf(hf, hf, nrm);
-            }
-            *(v8h *)(H + row * (u64)rowbytes + 16u * (u32)p) = h;
-        }
-#pragma unroll
-        for (int o = L / 2; o > 0; o >>= 1) {
-            err += __builtin_bit_cast(double, shfl_xor_u64(__builtin_bit_cast(u64, err), o));
-            nrm += __shfl_xor(nrm, o);
-        }
-        // a row of NaN compares false and counts for neither
-        if (nrm >= small) share = fmaxf(share, (float)sqrt(err / (double)nrm));
-        else if (nrm < small) rest = fmaxf(rest, (float)sqrt(err));
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        share = fmaxf(share, __shfl_xor(share, o));
-        rest = fmaxf(rest, __shfl_xor(rest, o));
-    }
-    if (lane == 0) { s[wave][0] = share; s[wave][1] = rest; }
-    __syncthreads();
-    if (threadIdx.x < 2) {
-        float m = fmaxf(fmaxf(s[0][threadIdx.x], s[1][threadIdx.x]), fmaxf(s[2][threadIdx.x], s[3][threadIdx.x]));
-        if (m > 0.f) atomicMax(threadIdx.x ? &par->rest_bits : &par->share_bits, __float_as_uint(m));
-    }
-}
-
 // bits [lo, hi) of a 96-bit mask, as word c (bits 32c .. 32c+31)
 __device__ __forceinline__ u32 range_word(int lo, int hi, int c)
 {
@@ -446,12 +253,6 @@ __device__ __forceinline__ int popc_below_w(u64 m0, u64 m1, int p)
 // with every pair resolved, 8.2 pair by pair, around 10^6 (few pairs each) 4.6 and 7.0.
 // (Without the bound 8,319 of 20,000 lists differed from the exact decisions for 100 coordinates of unit variance around
 // 10^6, 6,889 where every row occurs 100 times.)
-// FAST with 16-bit rows: the block comes from v_mfma_f32_16x16x32_{f16,bf16} on the rows as stored (exact
-// products), norms included (diagonals of the diagonal tiles).  One instruction sums 32 products and the
-// accumulator; taking its error as at most 8 x 2^-24 of the sum of their magnitudes (an in-bounds probe
-// against double precision stays below 2.3 x 2^-24 per instruction, also for operands spread over 20
-// binades, and shows that subnormal halves count), G and either norm are off by at most
-// (d / 4) 2^-24 of sqrt(n_i n_j) resp. n, hence eps_ij = (0.5 d + 20) 2^-24 (n_i + n_j).
 // Both: what falls below the smallest normal number, 2^-126, may be rounded coarsely or taken as zero, at each of the d
 // products and of the d sums of G and of either norm and in the evaluation, which eps_ij, a share of the norms, does not cover once the
 // norms are that small themselves: (8 d + 8) 2^-126 on top.  (Without it 18,669 of 20,000 lists of 100 coordinates
@@ -459,20 +260,15 @@ __device__ __forceinline__ int popc_below_w(u64 m0, u64 m1, int p)
 //
 // The work list: entries 0 .. n_first - 1 are list[0 ..], entries n_first .. n_active - 1 follow `skip` places further on
 // (a second degree class that the same shape serves).
-template <int NG, int CH, int NRC, bool FAST, int DT, bool HALF = false>
+template <int NG, int CH, int NRC, bool FAST, int DT>
 __device__ __forceinline__ void f32_scan_body(
-    const char *__restrict__ X, const HalfRows &half, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
+    const char *__restrict__ X, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
     const int *__restrict__ list, u32 n_first, size_t skip, u32 n_active, Prop *__restrict__ props, int *__restrict__ nprop,
     RoundCtr *__restrict__ ctr, int *__restrict__ redo, u32 *__restrict__ n_redo, F32ScanSmem<NRC> &sm, u32 block, u32 nblocks)
 {
     typedef typename GramAcc<FAST>::type acc_t;
-    // 16-bit rows in the single-precision form: the matrix instruction takes them as they are
-    static_assert(!HALF || (FAST && DT == DT_F32), "the half-precision copy serves the first form on float32 rows");
-    constexpr int GDT = HALF ? DT_F16 : DT;       // what the Gram block is computed from
-    constexpr bool NATIVE16 = FAST && (GDT == DT_F16 || GDT == DT_BF16);
-    const int dg = HALF ? (int)(half.rowbytes / 2u) : d;
-    const double epsk = NATIVE16 ? (0.5 * (double)dg + 20.0) * 5.9604644775390625e-08
-                                 : (1.5 * (double)dg + 20.0) * 5.9604644775390625e-08;
+    static_assert(!FAST || DT == DT_F32, "16-bit rows have a scan of their own");
+    const double epsk = (1.5 * (double)d + 20.0) * 5.9604644775390625e-08;
     const double epsk64 = (2.0 * (double)d + 24.0) * 1.1102230246251565e-16;      // double-precision form
     constexpr int NT = NRC * (NRC + 1) / 2;
     constexpr int NWD = (NRC + 1) / 2;        // 32-bit words of a mask over slots
@@ -482,12 +278,7 @@ __device__ __forceinline__ void f32_scan_body(
     const int r16 = lane & 15, q = lane >> 4, sub = lane & 7, grp = lane >> 3;
     const u32 gw = block * 4 + wave, nw = nblocks * 4;
     const u32 rowbytes = (u32)d * (u32)dt_size(DT);     // at most a few hundred KB
-    const char *__restrict__ G = HALF ? half.rows : X;      // rows of the Gram block
-    const u32 growbytes = HALF ? half.rowbytes : rowbytes;
-    const int nchunk = (int)(growbytes / (64u * CH));
-    // rounded up: what the sums of k_half_rows and the square roots here may have lost
-    const float gam = HALF ? 1.0001f * __uint_as_float(half.par->share_bits) : 0.f, bet = HALF ? 1.0001f * __uint_as_float(half.par->rest_bits) : 0.f;
-    const int e2 = HALF ? 2 * half.par->exponent : 0;
+    const int nchunk = (int)(rowbytes / (64u * CH));
     u64 tiles = 0, rows = 0, nprops_total = 0, pair_evals = 0;
     u32 ev_lane = 0;
 
@@ -533,8 +324,7 @@ __device__ __forceinline__ void f32_scan_body(
                     const int s = in ? (isnew ? sn : so) : p;
                     sm.key[s] = in ? kreg[h] : 0ull;
                     sm.pos[s] = p;
-                    const float du = in ? __uint_as_float(key_dist(kreg[h])) : 0.f;
-                    sm.distf[s] = HALF ? ldexpf(du, e2) : du;
+                    sm.distf[s] = in ? __uint_as_float(key_dist(kreg[h])) : 0.f;
                 }
             }
             rows += m;
@@ -546,7 +336,7 @@ __device__ __forceinline__ void f32_scan_body(
             for (int g = 0; g < NRC; ++g) {
                 const int s = 16 * g + r16;
                 const int id = s < m ? (int)key_id(sm.key[s]) : 0;      // lanes without a row read row 0
-                rp[g] = G + (size_t)id * growbytes + 16 * q;
+                rp[g] = X + (size_t)id * rowbytes + 16 * q;
             }
             // ---- Gram block over d in chunks of 16 dimensions: the tiles whose column group holds a new slot
             acc_t acc[NT];
@@ -562,23 +352,14 @@ __device__ __forceinline__ void f32_scan_body(
                 for (int J = 0; J <= I; ++J)
                     if (16 * I < m && J < g_new) need |= 1u << (I * (I + 1) / 2 + J);
             need = (u32)__builtin_amdgcn_readfirstlane((int)need);
-            // the tiles the Gram loop computes: those, and for 16-bit rows in the single-precision form the diagonal
-            // tile of every group in use (its diagonal is the group's norms)
-            u32 need_g = need;
-            if constexpr (NATIVE16) {
-#pragma unroll
-                for (int I = 0; I < NRC; ++I)
-                    if (16 * I < m) need_g |= 1u << (I * (I + 1) / 2 + I);
-                need_g = (u32)__builtin_amdgcn_readfirstlane((int)need_g);
-            }
             if constexpr (FAST) {
                 if (NRC == 1) {
-                    gram_f32_loop<NRC, CH, 1u, GDT>(rp, nchunk, acc, nr, need_g);
+                    gram_f32_loop<NRC, CH, 1u, DT>(rp, nchunk, acc, nr, need);
                 } else if (NRC == 2) {
-                    if (NATIVE16 || need == 7u) gram_f32_loop<NRC, CH, 7u, GDT>(rp, nchunk, acc, nr, need_g);
-                    else gram_f32_loop<NRC, CH, 3u, GDT>(rp, nchunk, acc, nr, need_g);
+                    if (need == 7u) gram_f32_loop<NRC, CH, 7u, DT>(rp, nchunk, acc, nr, need);
+                    else gram_f32_loop<NRC, CH, 3u, DT>(rp, nchunk, acc, nr, need);
                 } else {
-                    gram_f32_loop<NRC, CH, 0u, GDT>(rp, nchunk, acc, nr, need_g);
+                    gram_f32_loop<NRC, CH, 0u, DT>(rp, nchunk, acc, nr, need);
                 }
             } else {
                 if (NRC == 1) {
@@ -594,16 +375,8 @@ __device__ __forceinline__ void f32_scan_body(
             }
 #pragma unroll
             for (int g = 0; g < NRC; ++g) {
-                if constexpr (NATIVE16) {
-                    // entry (i, i) of the group's diagonal tile sits in lane (r16 = i, q = i / 4), accumulator i % 4
-                    const v4f dt = acc[g * (g + 1) / 2 + g];
-                    const int vs = r16 & 3;
-                    const float dv = vs == 0 ? dt[0] : vs == 1 ? dt[1] : vs == 2 ? dt[2] : dt[3];
-                    nr[g] = __shfl(dv, r16 + 16 * (r16 >> 2));
-                } else {
-                    nr[g] += __shfl_xor(nr[g], 16);
-                    nr[g] += __shfl_xor(nr[g], 32);     // n of slot 16 g + r16, in all four quarter-waves
-                }
+                nr[g] += __shfl_xor(nr[g], 16);
+                nr[g] += __shfl_xor(nr[g], 32);     // n of slot 16 g + r16, in all four quarter-waves
                 // all four quarter-waves hold the same sum and store it (no branch)
                 if (FAST) sm.nrmf[16 * g + r16] = (float)nr[g];
                 else sm.nrm[16 * g + r16] = (double)nr[g];
@@ -614,30 +387,24 @@ __device__ __forceinline__ void f32_scan_body(
             // group I as the tested row, bit c = column slot c of group J.  FB[t] (I != J): lane r16 = slot r16
             // of group J as the tested row, bit c = column slot c of group I.  (Same in all quarter-waves.)
             u32 FA[NT], FB[NT];
-            const float epskf = (float)epsk;
-            const float epsaf = HALF ? ldexpf(1.f, -120 + (e2 > 0 ? e2 : 0)) : (float)(8 * d + 8) * 1.17549435e-38f;
+            const float epskf = (float)epsk, epsaf = (float)(8 * d + 8) * 1.17549435e-38f;
 #pragma unroll
             for (int I = 0; I < NRC; ++I) {
                 // single-precision form: the rows of group I that this lane's accumulators stand for
                 float nIf[4], dIf[4], tIf[4];     // n, delta(u, .), n's part of the bound
-                float qIf[4], rIf[4];             // half-precision copy: 2 sqrt(delta(u, .)), distance of the row from its copy
                 if (FAST) {
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         nIf[v] = sm.nrmf[16 * I + 4 * q + v];
                         dIf[v] = sm.distf[16 * I + 4 * q + v];
                         tIf[v] = epskf * nIf[v];
-                        if constexpr (HALF) {
-                            qIf[v] = 2.000002f * __builtin_amdgcn_sqrtf(dIf[v]);
-                            rIf[v] = fmaf(gam, __builtin_amdgcn_sqrtf(nIf[v]), bet);
-                        }
                     }
                 }
 #pragma unroll
                 for (int J = 0; J <= I; ++J) {
                     const int t = I * (I + 1) / 2 + J;
                     FA[t] = FB[t] = 0;
-                    if (NRC == 1 || (NRC == 2 && (NATIVE16 || (need != 7u && t < 2))) || ((need_g >> t) & 1u)) tiles += 1;   // what the loop above computed
+                    if (NRC == 1 || (NRC == 2 && need != 7u && t < 2) || ((need >> t) & 1u)) tiles += 1;   // what the loop above computed
                     if ((need >> t) & 1u) {     // wave-uniform
                         // lane = slot r16 of group J; accumulator v = slot 4v + q of group I (4q + v in the
                         // single-precision instruction).  Low half of a word: the test fires; high half: undecided.
@@ -647,8 +414,6 @@ __device__ __forceinline__ void f32_scan_body(
                             // delta(v,w), which the bound's constant covers
                             const float dj = sm.distf[16 * J + r16];
                             const float nJf = (float)nr[J], tJf = fmaf(epskf, nJf, epsaf);
-                            const float qJf = HALF ? 2.000002f * __builtin_amdgcn_sqrtf(dj) : 0.f;
-                            const float rJf = HALF ? fmaf(gam, __builtin_amdgcn_sqrtf(nJf), bet) : 0.f;
                             // The outcomes with group I's slot as the tested row are taken as wavefront-wide masks:
                             // accumulator v of lane (r16, q) is (row 4q + v, column r16), so bit 16q + c of the mask
                             // of accumulator v is (row 4q + v, column c), and the row a lane stands for, r16, finds
@@ -659,18 +424,12 @@ __device__ __forceinline__ void f32_scan_body(
                                 const int rsel = 4 * q + v;
                                 const float nsum = nIf[v] + nJf;
                                 const float dvw = fmaf(-2.f, acc[t][v], nsum);
-                                float tol = tIf[v] + tJf, tolb = tol;
-                                if constexpr (HALF) {
-                                    const float rs = rIf[v] + rJf;
-                                    tol = fmaf(rs, rs, tol);
-                                    tolb = fmaf(qJf, rs, tol);
-                                    tol = fmaf(qIf[v], rs, tol);
-                                }
+                                const float tol = tIf[v] + tJf;
                                 const float ta = dIf[v] - dvw, tb = dj - dvw;
                                 fire_m[v] = __builtin_amdgcn_ballot_w64(ta >= 0.f);
                                 amb_m[v] = __builtin_amdgcn_ballot_w64(!(fabsf(ta) > tol));      // also when not finite
                                 fb |= (tb >= 0.f) ? (1u << rsel) : 0u;
-                                fb |= !(fabsf(tb) > tolb) ? (0x10000u << rsel) : 0u;
+                                fb |= !(fabsf(tb) > tol) ? (0x10000u << rsel) : 0u;
                             }
                             const int vs = r16 & 3, sh = 16 * (r16 >> 2);
                             const u64 mf = vs == 0 ? fire_m[0] : vs == 1 ? fire_m[1] : vs == 2 ? fire_m[2] : fire_m[3];
@@ -1011,7 +770,7 @@ __global__ __launch_bounds__(64 * 4, (NRC <= 2 ? 4 : NRC <= 5 ? 2 : 1)) void k_u
     __shared__ F32ScanSmem<NRC> smem[4];
     stamp_scan_start(ctr);
     const u32 n = *n_list;
-    f32_scan_body<NG, CH, NRC, false, DT>(X, HalfRows(), d, R, keys, deg, list, n, 0, n, props, nprop, ctr, nullptr, nullptr,
+    f32_scan_body<NG, CH, NRC, false, DT>(X, d, R, keys, deg, list, n, 0, n, props, nprop, ctr, nullptr, nullptr,
                                           smem[threadIdx.x >> 6], blockIdx.x, gridDim.x);
 }
 
@@ -1021,9 +780,9 @@ __global__ __launch_bounds__(64 * 4, (NRC <= 2 ? 4 : NRC <= 5 ? 2 : 1)) void k_u
 // block then has the registers of the longest shape.  Larger inputs take the classes that need about the same number
 // of registers together: up to 32 entries (C0 = 0), 33 .. 64 (C0 = 3), 65 .. 96 (C0 = 5); many long float32 rows the first of these
 // in two parts, up to 16 and (C0 = 2) 17 .. 32.
-template <int NRCMAX, int C0, int CH, int DT, bool HALF = false>
+template <int NRCMAX, int C0, int CH>
 __global__ __launch_bounds__(64 * 4, (NRCMAX <= 2 ? 4 : NRCMAX <= 4 ? 3 : 2)) void k_update_scan_mfma_f32_all(
-    const char *__restrict__ X, HalfRows half, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
+    const char *__restrict__ X, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
     const int *__restrict__ lists, long long N, Prop *__restrict__ props, int *__restrict__ nprop,
     RoundCtr *__restrict__ ctr, int *__restrict__ redo, u32 *__restrict__ n_redo)
 {
@@ -1051,7 +810,7 @@ __global__ __launch_bounds__(64 * 4, (NRCMAX <= 2 ? 4 : NRCMAX <= 4 ? 3 : 2)) vo
     if (k < 0) return;
     const int wave = threadIdx.x >> 6;
 #define RNND_F32_SHAPE(K_, NG_, CH_, NRC_)                                                                            \
-    f32_scan_body<NG_, CH_, NRC_, true, DT, HALF>(X, half, d, R, keys, deg, lists + (size_t)first_class[K_] * N, n1[K_],           \
+    f32_scan_body<NG_, CH_, NRC_, true, DT_F32>(X, d, R, keys, deg, lists + (size_t)first_class[K_] * N, n1[K_],           \
                                             (size_t)N - n1[K_], n[K_], props, nprop, ctr, redo, n_redo,                \
                                             *reinterpret_cast<F32ScanSmem<NRC_> *>(&smem[wave]), block, mine)
     if constexpr (C0 == 0)

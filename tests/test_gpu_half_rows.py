@@ -6,7 +6,7 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-N = 33_000      # past the size from which builds make the copy
+N = 33_000      # one scan launch for lists of 33 .. 96 slots, two otherwise
 KINDS = ["plain", "centre 1e3", "centre 1e6", "scale 1e-30", "scale 1e-20", "scale 1e15", "sizes", "outlier", "copies", "zeros", "nan", "inf"]
 
 
@@ -19,7 +19,7 @@ def rn():
     return m
 
 
-def _rows(kind, d):
+def _rows(kind, d, N=N):
     import torch
     g = np.random.default_rng(11)
     X = (g.normal(size=(64, d))[g.integers(0, 64, size=N)] + 0.5 * g.normal(size=(N, d))).astype(np.float32)
@@ -46,7 +46,60 @@ def _rows(kind, d):
 def test_same_as_the_pair_at_a_time_kernel(rn, kind, d):
     import torch
     X = _rows(kind, d)
-    for S, R, T1, T2 in ((20, 96, 2, 2), (8, 16, 1, 2), (40, 128, 1, 2)):
+    _compare(rn, X, ((20, 96, 2, 2), (8, 16, 1, 2), (40, 128, 1, 2)))
+
+
+@pytest.mark.parametrize("n,dtype", [(256, "f32"), (257, "f32"), (70_000, "f32"), (70_000, "f16"), (70_000, "bf16")])
+def test_sizes_where_the_launches_change(rn, n, dtype):
+    import torch
+    for d in (32, 100, 320):
+        X = _rows("plain", d, n).to({"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[dtype])
+        _compare(rn, X, ((20, 96, 2, 2), (40, 64, 1, 2)))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("R", [16, 96])
+def test_a_vertex_that_receives_thousands_of_edges(rn, dtype, R):
+    """Row 0 is nearer to every other row than any two of those are to each other, so whatever is pruned is redirected to it:
+    most of its edges arrive past its inbox, and past what its merge closes by itself."""
+    import torch
+    g = np.random.default_rng(3)
+    X = g.normal(size=(6000, 96))
+    X /= np.linalg.norm(X, axis=1, keepdims=True)
+    X[0] = 0
+    X = torch.from_numpy(X.astype(np.float32)).cuda().to({"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[dtype])
+    try:
+        rn.rnnd_set_kernel_variant(1)
+        keys, deg = rn.rnnd_random_graph(X, 8, R, 4)
+        ids = (keys[:, :8] >> 1) & 0x7FFFFFFF
+        assert int((ids == 0).sum()) < 600
+        # every list starts with row 0
+        d0 = (X.double() ** 2).sum(1).float()
+        own = (d0.view(torch.int32).long() << 32) | 1
+        has = (ids == 0).any(1)
+        keys[1:, 7][~has[1:]] = own[1:][~has[1:]]
+        keys[1:, :8] = keys[1:, :8].sort(dim=1).values
+    finally:
+        rn.rnnd_set_kernel_variant(0)
+    out = []
+    for v in (1, 0):
+        k, dg = keys.clone(), deg.clone()
+        try:
+            rn.rnnd_set_kernel_variant(v)
+            st = rn.rnnd_update_neighbors(X, k, dg, R, 2)
+            # a build in which row 0 is in one list of seven from the start
+            out.append((k, dg, rn.rnnd_build_ex(X[:700].contiguous(), R, R, 2, 2, 4), st.proposals[0]))
+        finally:
+            rn.rnnd_set_kernel_variant(0)
+    used = torch.arange(R, device="cuda")[None, :] < out[0][1][:, None]
+    assert torch.equal(out[0][1], out[1][1]) and torch.equal(out[0][0][used], out[1][0][used])
+    assert torch.equal(out[0][2][0], out[1][2][0]) and out[0][3] == out[1][3] > 30_000
+
+
+def _compare(rn, X, settings):
+    import torch
+    N = len(X)
+    for S, R, T1, T2 in settings:
         try:
             rn.rnnd_set_kernel_variant(1)
             want = rn.rnnd_build_ex(X, S, R, T1, T2, 5)
