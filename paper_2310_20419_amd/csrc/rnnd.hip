@@ -388,23 +388,23 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(long long N, int R, const int
     }
 }
 
-// Computes the open distances of the late edges of vertex x; group g of 8 lanes of the block walks list g.
+// Computes the open distances of the late edges of vertex x; each group of 8 lanes of the block walks its share of the lists.
 template <int DT>
 __device__ __attribute__((noinline)) void close_late(long long x, int late, LateHeads heads, Prop *props, const char *X, int d)
 {
-    const u32 l = threadIdx.x >> 3;
     const int sub = threadIdx.x & 7;
-    if (l >= LATE_LISTS) return;
     const size_t rb = (size_t)d * dt_size(DT);
-    u32 at = heads.base[(size_t)x * heads.stride + l];
-    for (int left = (late - (int)l + LATE_LISTS - 1) / LATE_LISTS; left > 0; --left) {
-        const u64 key = props[at].key;
-        const u32 next = props[at].next;
-        if (key_dist(key) == OPEN_DIST) {
-            const u32 db = group8_dist_bits<DT, 2>(X + (size_t)key_id(key) * rb, X + (size_t)x * rb, d, 1, sub);
-            if (sub == 0) props[at].key = make_key(db, key_id(key), 1u);
+    for (u32 l = threadIdx.x >> 3; l < LATE_LISTS; l += blockDim.x >> 3) {
+        u32 at = heads.base[(size_t)x * heads.stride + l];
+        for (int left = (late - (int)l + LATE_LISTS - 1) / LATE_LISTS; left > 0; --left) {
+            const u64 key = props[at].key;
+            const u32 next = props[at].next;
+            if (key_dist(key) == OPEN_DIST) {
+                const u32 db = group8_dist_bits<DT, 2>(X + (size_t)key_id(key) * rb, X + (size_t)x * rb, d, 1, sub);
+                if (sub == 0) props[at].key = make_key(db, key_id(key), 1u);
+            }
+            at = next;
         }
-        at = next;
     }
 }
 
@@ -522,18 +522,17 @@ __device__ __forceinline__ MergeItem merge_item_load(int x, int R, const u64 *ke
     return m;
 }
 
+// Wavefront `first` of `nwaves` that share the list tlist[0 .. n).
 template <int G, int DT>
-__device__ __forceinline__ void merge_group_body(int R, u64 *keys, int *deg, const int *tlist,
-                                                 const u32 *n_ptr, int *cnt, const u64 *inbox,
-                                                 int8_t *tcls, int use_classes, RoundCtr *ctr, OpenEdges *s_open,
-                                                 const char *__restrict__ X, int d)
+__device__ __forceinline__ void merge_group_body(int R, u64 *keys, int *deg, const int *tlist, u32 n, u32 first, u32 nwaves,
+                                                 int *cnt, const u64 *inbox, int8_t *tcls, int use_classes, RoundCtr *ctr,
+                                                 OpenEdges *s_open, const char *__restrict__ X, int d)
 {
     int dropped = 0;
     static_assert(G <= INBOX_CAP, "a group merge reads the received edges from the inbox only");
     int lane = threadIdx.x & 63, sub = lane & (G - 1), shift = lane & ~(G - 1);
     const u64 gmask = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1ull);
-    const u32 gid = (blockIdx.x * BLOCK + threadIdx.x) / G, ngrp = (gridDim.x * BLOCK) / G;
-    const u32 n = *n_ptr;
+    const u32 gid = first * (64 / G) + (u32)(lane / G), ngrp = nwaves * (64 / G);
     if (gid - (DT == DT_U8 ? 0u : (u32)(lane / G)) >= n) return;
     // list indices fit 32 bits with room to spare: n <= 2^31 and three strides of the grid are far below 2^31
     auto vertex_at = [&](u32 i) -> int { const int v = tlist[i < n ? i : n - 1u]; return i < n ? v : -1; };
@@ -620,8 +619,8 @@ __device__ __forceinline__ LateEdge late_edge(const Prop *props, u32 at, bool ha
 }
 
 template <int DT>
-__device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, const int *tlist,
-                                                   const u32 *n_ptr, int *cnt, const u64 *inbox,
+__device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, const int *tlist, u32 n, u32 first, u32 nwaves,
+                                                   int *cnt, const u64 *inbox,
                                                    LateHeads heads, const Prop *props, int8_t *tcls,
                                                    int use_classes, u64 (*s_stage)[RNND_MAX_R], RoundCtr *ctr,
                                                    OpenEdges *s_open, const char *__restrict__ X, int d)
@@ -631,8 +630,7 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
     const int cap = round_inbox(R);
     const int wave = threadIdx.x >> 6;
     int lane = threadIdx.x & 63;
-    const u32 gw = blockIdx.x * WAVES_PER_BLOCK + wave, nw = gridDim.x * WAVES_PER_BLOCK;
-    const u32 n = *n_ptr;
+    const u32 gw = first, nw = nwaves;
     if (gw >= n) return;
     auto vertex_at = [&](u32 i) -> int { const int v = tlist[i < n ? i : n - 1u]; return i < n ? v : -1; };
     WideItem cur = wide_item_load(vertex_at(gw), R, keys, deg, cnt, inbox, lane);
@@ -717,10 +715,74 @@ __global__ __launch_bounds__(BLOCK, (DT == DT_U8 ? 1 : 5)) void k_merge(long lon
     const int y = blockIdx.y;
     const int *tlist = tlists + (size_t)y * N;
     int8_t *tc = tcls + (size_t)y * N;
-    if (y == 0) merge_group_body<16, DT>(R, keys, deg, tlist, n_touched + 0, cnt, inbox, tc, use_classes, ctr, so, X, d);
-    else if (y == 1) merge_group_body<32, DT>(R, keys, deg, tlist, n_touched + 1, cnt, inbox, tc, use_classes, ctr, so, X, d);
-    else if (y == 2) merge_group_body<64, DT>(R, keys, deg, tlist, n_touched + 2, cnt, inbox, tc, use_classes, ctr, so, X, d);
-    else merge_general_body<DT>(R, keys, deg, tlist, n_touched + 3, cnt, inbox, heads, props, tc, use_classes, s_stage, ctr, so, X, d);
+    const u32 n = n_touched[y], first = blockIdx.x * WAVES_PER_BLOCK + (threadIdx.x >> 6), nwaves = gridDim.x * WAVES_PER_BLOCK;
+    if (y == 0) merge_group_body<16, DT>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, tc, use_classes, ctr, so, X, d);
+    else if (y == 1) merge_group_body<32, DT>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, tc, use_classes, ctr, so, X, d);
+    else if (y == 2) merge_group_body<64, DT>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, tc, use_classes, ctr, so, X, d);
+    else merge_general_body<DT>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, heads, props, tc, use_classes, s_stage, ctr, so, X, d);
+}
+
+// Classify, merge and compact of a round in one launch, for inputs whose rounds wait for launches (4-6 us each) rather than for
+// their work: a block takes `span` vertices (at most one per thread), sorts those that received edges into the merge classes in
+// LDS, merges them, and appends the ones that hold a "new" entry to the next active lists with one atomic per degree class.
+template <int DT>
+__global__ __launch_bounds__(BLOCK, (DT == DT_U8 ? 1 : 5)) void k_merge_blocks(long long N, int span, int R, u64 *keys, int *deg, int *cnt,
+                                                                               const u64 *inbox, LateHeads heads, Prop *props, int use_classes,
+                                                                               RoundCtr *ctr, int *lists, u32 *n_next,
+                                                                               const char *__restrict__ X, int d)
+{
+    __shared__ u64 s_stage[WAVES_PER_BLOCK][RNND_MAX_R];
+    __shared__ int s_list[NMRG][BLOCK];
+    __shared__ int8_t s_cls[NMRG][BLOCK];
+    __shared__ u32 s_n[NMRG], s_out[NDEG], s_base[NDEG];
+    const int wave = threadIdx.x >> 6;
+    OpenEdges *so = reinterpret_cast<OpenEdges *>(&s_stage[wave]);
+    const int cap = round_inbox(R);
+    if (threadIdx.x < NMRG) s_n[threadIdx.x] = 0;
+    if (threadIdx.x < NDEG) s_out[threadIdx.x] = 0;
+    __syncthreads();
+    const long long x = (long long)blockIdx.x * span + threadIdx.x;
+    int c = 0;
+    if ((int)threadIdx.x < span && x < N) c = cnt[x];
+    if (c > 0) {
+        const int q = merge_class(deg[x], c, cap);
+        s_list[q][atomicAdd(&s_n[q], 1u)] = (int)x;
+    }
+    __syncthreads();
+    if (DT != DT_U8) {
+        for (u32 i = 0; i < s_n[3]; ++i) {
+            const int v = s_list[3][i], late = cnt[v] - cap;
+            if (late > LATE_OPEN) close_late<DT>(v, late, heads, props, X, d);
+        }
+        __syncthreads();
+    }
+    // (the classes start with different wavefronts)
+    merge_group_body<16, DT>(R, keys, deg, s_list[0], s_n[0], wave, 4, cnt, inbox, s_cls[0], use_classes, ctr, so, X, d);
+    merge_group_body<32, DT>(R, keys, deg, s_list[1], s_n[1], (wave + 3) & 3, 4, cnt, inbox, s_cls[1], use_classes, ctr, so, X, d);
+    merge_group_body<64, DT>(R, keys, deg, s_list[2], s_n[2], (wave + 2) & 3, 4, cnt, inbox, s_cls[2], use_classes, ctr, so, X, d);
+    merge_general_body<DT>(R, keys, deg, s_list[3], s_n[3], (wave + 1) & 3, 4, cnt, inbox, heads, props, s_cls[3], use_classes, s_stage, ctr, so, X, d);
+    __syncthreads();
+    // at most `span` items in all: one per thread
+    int k = -1, item = 0;
+    u32 at = 0, i = threadIdx.x;
+#pragma unroll
+    for (int q = 0; q < NMRG; ++q) {
+        if (k == -1 && i < s_n[q]) {
+            item = s_list[q][i];
+            k = s_cls[q][i];
+            if (k < 0) k = -2;
+        } else if (k == -1) {
+            i -= s_n[q];
+        }
+    }
+    if (k >= 0) at = atomicAdd(&s_out[k], 1u);
+    __syncthreads();
+    if (threadIdx.x < NDEG) {
+        const u32 n = s_out[threadIdx.x];
+        s_base[threadIdx.x] = n ? atomicAdd(&n_next[threadIdx.x], n) : 0u;
+    }
+    __syncthreads();
+    if (k >= 0) lists[(size_t)k * N + s_base[k] + at] = item;
 }
 
 // Items i < n with cls[first + i] >= 0 are appended to list cls[first + i]; item i stands for vertex idx[i]
@@ -1560,9 +1622,9 @@ static int vec_ok_for(const void *X, int d, int dtype)
 //             fit the tiles, or rows padded to a length the tiles take (dp coordinates; see k_prepare_*_rows)
 // The first two are what a call needs; padded rows are an extra a call does without (generic kernel) where there is
 // no room for them.
-// Row length in bytes of the half-precision copy of d coordinates: a multiple of 128, so that no row shares a cache line; 192 for 65
-// .. 96 coordinates, where a third of 256 would be padding.
-static u32 half_row_bytes(int d) { return d <= 64 ? 128u : d <= 128 ? ((u32)d + 31u) / 32u * 64u : ((u32)d + 63u) / 64u * 128u; }
+// Row length in bytes of the half-precision copy of d coordinates: a multiple of 128, so that no row shares a cache line; 64 and 192
+// where a half or a third of 128 or 256 would be padding.
+static u32 half_row_bytes(int d) { return d <= 32 ? 64u : d <= 64 ? 128u : d <= 128 ? ((u32)d + 31u) / 32u * 64u : ((u32)d + 63u) / 64u * 128u; }
 // From how many vertices on a build's float32 scans take their Gram blocks from that copy: always but for the smallest inputs,
 // whose lists the two launches that make it would hold up (60-round builds without / with it, R = 96: 300 x 96 1.64 / 1.21 ms, 2,000 x 33
 // 1.60 / 1.55, 20,000 x 96 3.87 / 3.15, 1M x 960 915 / 526).
@@ -1718,7 +1780,7 @@ static void launch_half_rows(char *base, const void *X, long long N, int d, int 
 {
     HalfLayout l;
     half_layout(base, N, d, rb, &l);
-    hipLaunchKernelGGL(k_half_centre, dim3((unsigned)((d + 63) / 64)), dim3(256), 0, st, (const float *)X, N, d, l.centre, l.square, l.par);
+    hipLaunchKernelGGL(k_half_centre, dim3((unsigned)((d + 63) / 64)), dim3(1024), 0, st, (const float *)X, N, d, l.centre, l.square, l.par);
     const int lanes = rb <= 512 ? 16 : 64;
     const size_t need = ((size_t)N * lanes + 255) / 256, most = (size_t)persistent_blocks();
     const dim3 grid((unsigned)(need < most ? need : most));
@@ -1852,6 +1914,26 @@ static void launch_classify(int dt, hipStream_t st, long long N, int R, const Wo
     const auto go = dt == RNND_F32 ? launch_classify_dt<DT_F32> : dt == RNND_F16 ? launch_classify_dt<DT_F16> : dt == RNND_BF16 ? launch_classify_dt<DT_BF16> : launch_classify_dt<DT_U8>;
     go(st, N, R, w, deg, c, X, d);
 }
+// Up to here classify, merge and compact are one launch, of up to 128 vertices a block, fewer where that gives fewer than 512
+// blocks.  Three launches / one, ms: 5,000 x 32 uint8 0.355 / 0.302, 20,000 x 96 float32 3.14 / 2.92, 60,000 x 784 uint8 5.12 / 4.86,
+// 100,000 x 128 uint8 4.39 / 4.15, 200,000 x 100 float32 21.5 / 22.2, 300,000 x 768 bfloat16 103.0 / 103.6; 64 vertices a block
+// 3.08 ms at 20,000, 4.51 at 100,000, 256 vertices 3.05 and 4.30.
+#define MERGE_BLOCKS_MAX_N 131072
+#define MERGE_SPAN 128
+#define MERGE_BLOCKS_MIN 512
+template <int DT>
+static void launch_merge_blocks_dt(hipStream_t st, long long N, int R, const Workspace &w, u64 *keys, int *deg, int use_classes, RoundCtr *c, const void *X, int d)
+{
+    int span = MERGE_SPAN;
+    while (span > 16 && N / span < MERGE_BLOCKS_MIN) span >>= 1;
+    hipLaunchKernelGGL(k_merge_blocks<DT>, dim3((unsigned)((N + span - 1) / span)), dim3(BLOCK), 0, st, N, span, R, keys, deg, w.fill, w.inbox,
+                       late_heads(w.inbox, w.bins, R), w.props, use_classes, c, w.lists, (c + 1)->n_active, (const char *)X, d);
+}
+static void launch_merge_blocks(int dt, hipStream_t st, long long N, int R, const Workspace &w, u64 *keys, int *deg, int use_classes, RoundCtr *c, const void *X, int d)
+{
+    const auto go = dt == RNND_F32 ? launch_merge_blocks_dt<DT_F32> : dt == RNND_F16 ? launch_merge_blocks_dt<DT_F16> : dt == RNND_BF16 ? launch_merge_blocks_dt<DT_BF16> : launch_merge_blocks_dt<DT_U8>;
+    go(st, N, R, w, keys, deg, use_classes, c, X, d);
+}
 static void launch_merge(int dt, hipStream_t st, long long N, int R, const Workspace &w, u64 *keys, int *deg, int use_classes, RoundCtr *c, const void *X, int d)
 {
     const auto go = dt == RNND_F32 ? launch_merge_dt<DT_F32> : dt == RNND_F16 ? launch_merge_dt<DT_F16> : dt == RNND_BF16 ? launch_merge_dt<DT_BF16> : launch_merge_dt<DT_U8>;
@@ -1915,6 +1997,10 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
     const int open_dt = variant == 3 && use_classes == 2 ? dtype : RNND_U8;      // whose redirected edges come without distances
     hipLaunchKernelGGL(k_scatter, dim3(pb), dim3(BLOCK), 0, st, N, R, w.lists, ncl, c, w.props, (const int *)w.nprop, w.fill,
                        w.inbox, late_heads(w.inbox, w.bins, R));
+    if (!run && !re.round_stop && N <= MERGE_BLOCKS_MAX_N) {
+        launch_merge_blocks(open_dt, st, N, R, w, keys, deg, use_classes, c, X, d);
+        return hipGetLastError();
+    }
     launch_classify(open_dt, st, N, R, w, deg, c, X, d);
     launch_merge(open_dt, st, N, R, w, keys, deg, use_classes, c, X, d);
     if (run)

@@ -257,6 +257,7 @@ __device__ __forceinline__ void scan_list_stream_body(const OP &op, const int8_t
                                                       Prop *__restrict__ props, int *__restrict__ nprop,
                                                       RoundCtr *__restrict__ ctr, typename OP::template Smem<NG> &sm, u32 block, u32 nblocks)
 {
+    // (two chunks for longer lists as well: 60,000 x 784 uint8 4.60 -> 4.79 ms, 1M x 96 101 -> 119, whose registers spill)
     constexpr int NBUF = NG == 1 ? 2 : 1;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int lane = threadIdx.x & 63;
