@@ -55,6 +55,7 @@ struct ScanLaunch {
     int *redo;                  // [2 * N]
     hipStream_t st;
     hipEvent_t e_start, e_stop;
+    int round;                  // 0: no round before it in this call's counters
 };
 
 // float32 rows by degree classes 0 .. 6, single precision

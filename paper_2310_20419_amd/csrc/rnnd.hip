@@ -124,7 +124,7 @@ __global__ __launch_bounds__(BLOCK) void k_update_scan(const void *X, int d, int
         u64 *row = keys + (size_t)u * R;
         u64 k0 = lane < m ? row[lane] : KEY_PAD;
         u64 k1 = lane + 64 < m ? row[lane + 64] : KEY_PAD;
-        const int np = scan_vertex_pairs<DT>(X, d, vec_ok, R, u, m, k0, k1, row, deg, props, nprop, s_key[wave], s_pkey[wave], s_ptgt[wave],
+        const int np = scan_vertex_pairs<DT>(X, d, vec_ok, R, u, m, k0, k1, row, deg, props, nprop + u, s_key[wave], s_pkey[wave], s_ptgt[wave],
                                              lane, evals_algo, evals_exec);
         if (np < 0) continue;
         rows += m;
@@ -328,7 +328,7 @@ __device__ __forceinline__ u64 close_keys(u64 key, int x, bool have, OpenEdges *
 // group that share a target take their arrival numbers with one atomic (a vertex usually redirects
 // several entries to the same kept neighbour).  Arrivals below round_inbox(R) go to the target's inbox, later ones onto
 // one of its lists (see LATE_LISTS).
-__global__ __launch_bounds__(BLOCK) void k_scatter(long long N, int R, const int *lists, int ncl, RoundCtr *ctr,
+__device__ __forceinline__ void scatter_lists(long long N, int R, const int *lists, int ncl, RoundCtr *ctr,
                                                    Prop *props, const int *nprop, int *fill, u64 *inbox, LateHeads heads)
 {
     const int cap = round_inbox(R);
@@ -386,6 +386,57 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(long long N, int R, const int
         u = u_next; np = np_next; pr0 = pr_next;
         u_next = u_after;
     }
+}
+
+__global__ __launch_bounds__(BLOCK) void k_scatter(long long N, int R, const int *lists, int ncl, RoundCtr *ctr,
+                                                   Prop *props, const int *nprop, int *fill, u64 *inbox, LateHeads heads)
+{
+    scatter_lists(N, R, lists, ncl, ctr, props, nprop, fill, inbox, heads);
+}
+
+// The same where the float scan's redo lists have no launch of their own: their vertices, which have no edges to scatter
+// yet, are scanned pair by pair here and their edges scattered by the same wavefront.  For inputs whose rounds wait for launches: an
+// empty one of the double-precision form is 3.7 us.  (It scans many such vertices faster, and this kernel's registers
+// halve the scatter's occupancy, so larger inputs keep the two apart.)
+template <int DT>
+__global__ __launch_bounds__(BLOCK) void k_scatter_redo(long long N, int R, const int *lists, int ncl, RoundCtr *ctr,
+                                                        Prop *props, const int *nprop, int *fill, u64 *inbox, LateHeads heads,
+                                                        const int *redo, u64 *keys, int *deg, const void *X, int d, int vec_ok)
+{
+    __shared__ u64 s_key[WAVES_PER_BLOCK][RNND_MAX_R];
+    __shared__ u64 s_pkey[WAVES_PER_BLOCK][RNND_MAX_R];
+    __shared__ u32 s_ptgt[WAVES_PER_BLOCK][RNND_MAX_R];
+    __shared__ int s_np[WAVES_PER_BLOCK];
+    const u32 n0 = ctr->n_redo[0], n = n0 + ctr->n_redo[1];
+    if (n) {
+        const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, cap = round_inbox(R);
+        u64 evals_algo = 0, evals_exec = 0, rows = 0, edges = 0;
+        for (u32 it = blockIdx.x * WAVES_PER_BLOCK + wave; it < n; it += gridDim.x * WAVES_PER_BLOCK) {
+            const int u = redo[it < n0 ? (size_t)it : (size_t)N + (it - n0)];
+            int m = deg[u];
+            if (m > R) m = R;
+            u64 *row = keys + (size_t)u * R;
+            const u64 k0 = lane < m ? row[lane] : KEY_PAD, k1 = lane + 64 < m ? row[lane + 64] : KEY_PAD;
+            const int np = scan_vertex_pairs<DT>(X, d, vec_ok, R, u, m, k0, k1, row, deg, props, &s_np[wave], s_key[wave], s_pkey[wave],
+                                                 s_ptgt[wave], lane, evals_algo, evals_exec);
+            rows += m;
+            for (int p = lane; p < np; p += 64) {
+                const u32 tgt = s_ptgt[wave][p];
+                const int s = atomicAdd(&fill[tgt], 1);
+                if (s < cap) {
+                    inbox[(size_t)tgt * INBOX_CAP + s] = s_pkey[wave][p];
+                } else {
+                    const size_t slot = (size_t)u * R + p;      // emit_redirect has put the edge there
+                    props[slot].next = atomicExch(&heads.base[(size_t)tgt * heads.stride + ((u32)(s - cap) & (LATE_LISTS - 1u))], (u32)slot);
+                }
+                ++edges;
+            }
+            wave_sync();
+        }
+        for (int o = 32; o > 0; o >>= 1) edges += shfl_xor_u64(edges, o);
+        if (lane == 0 && rows) add_round_stats(ctr, evals_algo, evals_exec, rows, edges);
+    }
+    scatter_lists(N, R, lists, ncl, ctr, props, nprop, fill, inbox, heads);
 }
 
 // Computes the open distances of the late edges of vertex x; each group of 8 lanes of the block walks its share of the lists.
@@ -1934,6 +1985,22 @@ static void launch_merge_blocks(int dt, hipStream_t st, long long N, int R, cons
     const auto go = dt == RNND_F32 ? launch_merge_blocks_dt<DT_F32> : dt == RNND_F16 ? launch_merge_blocks_dt<DT_F16> : dt == RNND_BF16 ? launch_merge_blocks_dt<DT_BF16> : launch_merge_blocks_dt<DT_U8>;
     go(st, N, R, w, keys, deg, use_classes, c, X, d);
 }
+#ifndef REDO_IN_SCATTER_MAX_N
+#define REDO_IN_SCATTER_MAX_N 131072
+#endif
+template <int DT>
+static void launch_scatter_redo_dt(unsigned blocks, hipStream_t st, long long N, int R, const Workspace &w, int ncl, RoundCtr *c, u64 *keys, int *deg,
+                                   const void *X, int d, int vec_ok)
+{
+    hipLaunchKernelGGL(k_scatter_redo<DT>, dim3(blocks), dim3(BLOCK), 0, st, N, R, w.lists, ncl, c, w.props, (const int *)w.nprop, w.fill, w.inbox,
+                       late_heads(w.inbox, w.bins, R), (const int *)w.touched, keys, deg, X, d, vec_ok);
+}
+static void launch_scatter_redo(int dt, unsigned blocks, hipStream_t st, long long N, int R, const Workspace &w, int ncl, RoundCtr *c, u64 *keys, int *deg,
+                                const void *X, int d, int vec_ok)
+{
+    const auto go = dt == RNND_F32 ? launch_scatter_redo_dt<DT_F32> : dt == RNND_F16 ? launch_scatter_redo_dt<DT_F16> : launch_scatter_redo_dt<DT_BF16>;
+    go(blocks, st, N, R, w, ncl, c, keys, deg, X, d, vec_ok);
+}
 static void launch_merge(int dt, hipStream_t st, long long N, int R, const Workspace &w, u64 *keys, int *deg, int use_classes, RoundCtr *c, const void *X, int d)
 {
     const auto go = dt == RNND_F32 ? launch_merge_dt<DT_F32> : dt == RNND_F16 ? launch_merge_dt<DT_F16> : dt == RNND_BF16 ? launch_merge_dt<DT_BF16> : launch_merge_dt<DT_U8>;
@@ -1958,6 +2025,8 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
     const int variant = plan.variant, use_classes = plan.classes();
     const int d = variant == 2 ? plan.dp : rv.d, vec_ok = rv.vec_ok;
     RoundCtr *c = w.ctr + t;
+    const int open_dt = variant == 3 && use_classes == 2 ? dtype : RNND_U8;      // whose redirected edges come without distances
+    const bool redo_in_scatter = open_dt != RNND_U8 && !run && !re.scan_stop && N <= REDO_IN_SCATTER_MAX_N;
     if (run) {
         const unsigned cb = (run->count + 1023u) / 1024u;
         hipLaunchKernelGGL(k_compact_classes, dim3(cb < 256u ? cb : 256u, 1), dim3(1024), 0, st, (const u32 *)nullptr,
@@ -1971,13 +2040,15 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
         else launch_mfma_scan_classes<0>(w, d, R, keys, deg, N, c, st, re);
     } else if (variant == 3) {
         const bool generic_tail = R > 96;
-        ScanLaunch l = {X, d, R, keys, deg, N, w.lists, w.props, w.nprop, c, (int *)w.bins, st, re.scan_start, generic_tail ? (hipEvent_t) nullptr : re.scan_stop};
+        ScanLaunch l = {X, d, R, keys, deg, N, w.lists, w.props, w.nprop, c, w.touched, st, re.scan_start, generic_tail ? (hipEvent_t) nullptr : re.scan_stop, run ? 0 : t};
         if (use_classes == 2) {
             // lists of up to 128 entries; what the redo list of the longest holds goes to the generic kernel
             const bool copy = rv.half.rows != nullptr;
             launch_float_scan(l, dtype, copy ? rv.half.rows : X, copy ? rv.half.rowbytes : (u32)(d * dt_size(dtype)), rv.half.par);
-            launch_f64_redo(l, dtype);
-            if (generic_tail) launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, l.redo + N, &c->n_redo[1], pb, c, st, nullptr, re.scan_stop);
+            if (!redo_in_scatter) {
+                launch_f64_redo(l, dtype);
+                if (generic_tail) launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, l.redo + N, &c->n_redo[1], pb, c, st, nullptr, re.scan_stop);
+            }
         } else {
             // degree classes 0..6: lists of at most 8, 16, 32, 48, 64, 80, 96 entries = 1, 1, 2, 3, 4, 5, 6 groups of 16
             // rows; class 7 (97..128 entries: too many accumulator tiles) goes to the generic kernel
@@ -1994,8 +2065,9 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
     }
     // from here on `fill` plays the role of the per-target count of this round
     const int ncl = use_classes ? NDEG : 1;
-    const int open_dt = variant == 3 && use_classes == 2 ? dtype : RNND_U8;      // whose redirected edges come without distances
-    hipLaunchKernelGGL(k_scatter, dim3(pb), dim3(BLOCK), 0, st, N, R, w.lists, ncl, c, w.props, (const int *)w.nprop, w.fill,
+    if (redo_in_scatter) launch_scatter_redo(open_dt, pb, st, N, R, w, ncl, c, keys, deg, X, d, vec_ok);
+    else
+        hipLaunchKernelGGL(k_scatter, dim3(pb), dim3(BLOCK), 0, st, N, R, w.lists, ncl, c, w.props, (const int *)w.nprop, w.fill,
                        w.inbox, late_heads(w.inbox, w.bins, R));
     if (!run && !re.round_stop && N <= MERGE_BLOCKS_MAX_N) {
         launch_merge_blocks(open_dt, st, N, R, w, keys, deg, use_classes, c, X, d);

@@ -27,10 +27,12 @@
 #include "scan_mfma.h"
 #include "half_rows.h"
 #include "dist.h"
+#include "scan_mfma_f32.h"
 
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 #define FLOAT_PAIR_CAP 256
+#define OPEN_SAMPLE 32u
 
 template <int NG>
 struct alignas(16) FloatScanSmem {
@@ -68,6 +70,7 @@ struct FloatOp {
     typedef v16f tile_t;
     template <int NG> using Smem = FloatScanSmem<NG>;
     FloatRows fr;
+    mutable u32 n_open = 0;      // of this wavefront
     float eps, tiny, gam, bet;
     double spread;     // relative difference that two orders of summation in double precision may make
     int e2;
@@ -87,6 +90,12 @@ struct FloatOp {
         } else {
             tiny = DT == DT_F16 ? (float)rows.d * 0x1p-46f : (float)(8 * rows.d + 8) * 1.17549435e-38f;
         }
+    }
+
+    __device__ __forceinline__ void report(RoundCtr *ctr) const
+    {
+        // one wavefront in OPEN_SAMPLE (an add of each to one address takes 10 ns, 20 us a round)
+        if (HALF && n_open && threadIdx.x == 0 && (blockIdx.x & 7) == 0) atomicAdd(&ctr->n_open, n_open);
     }
 
     static __device__ __forceinline__ v16f mac(const v4i &a, const v4i &b, const v16f &c)
@@ -210,6 +219,7 @@ struct FloatOp {
             if (lane >= o) incl += up;
         }
         const int total = __builtin_amdgcn_readlane(incl, 63);
+        if (HALF) n_open += (u32)total;
         if (total > FLOAT_PAIR_CAP) return false;
         wave_sync();
         int at = incl - mine;
@@ -256,8 +266,9 @@ struct FloatOp {
         return true;
     }
 
-    __device__ __forceinline__ void leave(int u, int m) const
+    __device__ __forceinline__ void leave(int u, int m, int *nprop) const
     {
+        nprop[u] = 0;      // nothing to scatter until it is scanned again (see k_scatter_redo)
         const int longer = m > 96;
         fr.redo[(longer ? (size_t)fr.N : 0) + atomicAdd(fr.n_redo + longer, 1u)] = u;
     }
@@ -428,7 +439,7 @@ struct FloatOp {
         }
         hold();     // every store of the trip comes after this point
         if (left) {
-            if (lane == 0) leave(u, m);
+            if (lane == 0) leave(u, m, nprop);
             return;
         }
         ev_lane += ev_all;
@@ -541,7 +552,7 @@ struct FloatOp {
         }
         hold();     // every store of the trip comes after this point
         if (left) {
-            if (leader) leave(u, m);
+            if (leader) leave(u, m, nprop);
             return;
         }
         if (pruned) emit_redirect(make_key(OPEN_DIST, key_id(kb), 1u), tgt_id, props + (size_t)u * R + __popc(pm & segmask & below));
@@ -553,11 +564,31 @@ struct FloatOp {
     }
 };
 
+// Whether this round's scan of float32 rows reads whole rows, in single precision, instead of the half-precision copy.  Where
+// clusters are tight next to the distances between them, or rows differ in size by orders of magnitude, the copy leaves most pairs
+// to the exact distance.  So once a round has left more than WHOLE_OPEN per active vertex (0.3 on the average, 1.1 at most in the
+// builds of this repository's float workloads), the following ones take the form of scan_mfma_f32.h: every block finds the same from
+// the counters of the round before.
+#define WHOLE_OPEN 6
+__device__ __forceinline__ bool whole_rows(RoundCtr *ctr, int round)
+{
+    bool on = false;
+    if (round > 0) {
+        const RoundCtr *p = ctr - 1;
+        u32 active = 0;
+#pragma unroll
+        for (int k = 0; k < NDEG; ++k) active += p->n_active[k];
+        on = p->whole != 0u || (u64)p->n_open * OPEN_SAMPLE > (u64)WHOLE_OPEN * active || (u64)(p->n_redo[0] + p->n_redo[1]) * 16u > active;
+    }
+    if (on && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) ctr->whole = 1u;
+    return on;
+}
+
 // Lists of at most 8, 16, 32 entries (blockIdx.y = degree class): 4, 2, 1 vertices per wavefront.  
 template <int DT>
 __global__ __launch_bounds__(256, 4) void k_scan_float_small(
     const int8_t *__restrict__ G, u32 rowbytes, FloatRows fr, int R, u64 *__restrict__ keys, int *__restrict__ deg,
-    const int *__restrict__ lists, Prop *__restrict__ props, int *__restrict__ nprop, RoundCtr *__restrict__ ctr)
+    const int *__restrict__ lists, Prop *__restrict__ props, int *__restrict__ nprop, RoundCtr *ctr, int round)
 {
     typedef FloatOp<DT, DT == DT_F32> OP;
     __shared__ FloatScanSmem<1> smem[4];
@@ -566,23 +597,56 @@ __global__ __launch_bounds__(256, 4) void k_scan_float_small(
     const int *list = lists + (size_t)y * fr.N;
     const u32 n = ctr->n_active[y];
     stamp_scan_start(ctr);
+    if (DT == DT_F32 && round >= 0 && whole_rows(ctr, round)) return;      // (round < 0: no launch beside this one to take the lists)
     const OP op(fr, rowbytes);
     if (y == 0) scan_packed_stream_body<OP, 4>(op, G, (int)rowbytes, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
     else if (y == 1) scan_packed_stream_body<OP, 2>(op, G, (int)rowbytes, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
     else scan_packed_stream_body<OP, 1>(op, G, (int)rowbytes, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
+    op.report(ctr);
+}
+
+// The classes of a round that reads whole rows: shapes of 1, 2, 4, 6 groups of 16 rows.
+template <int SMEM>
+__device__ __forceinline__ void whole_row_classes(const FloatRows &fr, int R, u64 *keys, int *deg, const int *lists, Prop *props, int *nprop,
+                                                  RoundCtr *ctr, char (*smem)[SMEM])
+{
+    static_assert(sizeof(F32ScanSmem<6>) <= SMEM, "");
+    constexpr u32 weight[4] = {16u, 24u, 44u, 72u};
+    const u32 n1 = ctr->n_active[0], n[4] = {n1 + ctr->n_active[1], ctr->n_active[2], ctr->n_active[3], ctr->n_active[4]};
+    u32 block, mine;
+    const int k = share_blocks<4>(n, weight, block, mine);
+    char *sm = smem[threadIdx.x >> 6];
+    const size_t N = (size_t)fr.N;
+    if (k == 0)
+        f32_scan_body<1, 1, 1, true, DT_F32>(fr.X, fr.d, R, keys, deg, lists, n1, N - n1, n[0], props, nprop, ctr, fr.redo, fr.n_redo,
+                                             *reinterpret_cast<F32ScanSmem<1> *>(sm), block, mine);
+    else if (k == 1)
+        f32_scan_body<1, 1, 2, true, DT_F32>(fr.X, fr.d, R, keys, deg, lists + 2 * N, n[1], 0, n[1], props, nprop, ctr, fr.redo, fr.n_redo,
+                                             *reinterpret_cast<F32ScanSmem<2> *>(sm), block, mine);
+    else if (k == 2)
+        f32_scan_body<2, 1, 4, true, DT_F32>(fr.X, fr.d, R, keys, deg, lists + 3 * N, n[2], 0, n[2], props, nprop, ctr, fr.redo, fr.n_redo,
+                                             *reinterpret_cast<F32ScanSmem<4> *>(sm), block, mine);
+    else if (k == 3)
+        f32_scan_body<3, 1, 6, true, DT_F32>(fr.X, fr.d, R, keys, deg, lists + 4 * N, n[3], 0, n[3], props, nprop, ctr, fr.redo, fr.n_redo,
+                                             *reinterpret_cast<F32ScanSmem<6> *>(sm), block, mine);
 }
 
 // Classes C0 .. NC - 1 in one launch, the grid's blocks divided among them by their work (as k_update_scan_mfma_u8_all).
 template <int DT, int NC, int C0>
 __global__ __launch_bounds__(256, (NC == 6 ? 1 : 2)) void k_scan_float_all(
     const int8_t *__restrict__ G, u32 rowbytes, FloatRows fr, int R, u64 *__restrict__ keys, int *__restrict__ deg,
-    const int *__restrict__ lists, Prop *__restrict__ props, int *__restrict__ nprop, RoundCtr *__restrict__ ctr)
+    const int *__restrict__ lists, Prop *__restrict__ props, int *__restrict__ nprop, RoundCtr *ctr, int round)
 {
     typedef FloatOp<DT, DT == DT_F32> OP;
     constexpr int NGMAX = NC - 2;
     static_assert(NC == 5 || NC == 6, "short lists plus two or three long-list classes");
     __shared__ FloatScanSmem<NGMAX> smem[4];
     if (C0 == 0) stamp_scan_start(ctr);
+    if constexpr (DT == DT_F32 && NC == 5)
+        if (whole_rows(ctr, round)) {
+            whole_row_classes<sizeof(FloatScanSmem<NGMAX>)>(fr, R, keys, deg, lists, props, nprop, ctr, reinterpret_cast<char(*)[sizeof(FloatScanSmem<NGMAX>)]>(smem));
+            return;
+        }
     constexpr u32 weight[6] = {6u, 12u, 24u, 46u, 78u, 112u};
     u32 n[NC];
 #pragma unroll
@@ -603,4 +667,5 @@ __global__ __launch_bounds__(256, (NC == 6 ? 1 : 2)) void k_scan_float_all(
         scan_list_stream_body<OP, 3>(op, G, rb, R, keys, deg, list, n[4], props, nprop, ctr, *reinterpret_cast<FloatScanSmem<3> *>(&smem[wave]), block, mine);
     else if (NC > 5 && cls == 5)
         scan_list_stream_body<OP, NGMAX>(op, G, rb, R, keys, deg, list, n[NC > 5 ? 5 : 0], props, nprop, ctr, smem[wave], block, mine);
+    op.report(ctr);
 }

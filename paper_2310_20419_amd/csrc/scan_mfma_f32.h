@@ -582,10 +582,13 @@ __device__ __forceinline__ void f32_scan_body(
                 if (total > (FAST ? F32_AMB_CAP : F64_AMB_PER_ROW * m)) {
                     defer = true;
                     if (FAST) {
-                        if (lane == 0) redo[atomicAdd(n_redo, 1u)] = u;
+                        if (lane == 0) {
+                            nprop[u] = 0;      // nothing to scatter until it is scanned again
+                            redo[atomicAdd(n_redo, 1u)] = u;
+                        }
                     } else {
                         u64 ea = 0, ee = 0;
-                        nprops_total += scan_vertex_pairs<DT>(X, d, 1, R, u, m, kreg[0], kreg[1], row, deg, props, nprop, sm.key,
+                        nprops_total += scan_vertex_pairs<DT>(X, d, 1, R, u, m, kreg[0], kreg[1], row, deg, props, nprop + u, sm.key,
                                                               (u64 *)sm.nrm, sm.pv, lane, ea, ee);
                         ev_lane += lane == 0 ? (u32)ea : 0u;
                         pair_evals += ee;

@@ -11,11 +11,11 @@
 // entry lane + 64 in k1); the kept set U' so far is a bit mask; the delta(v,w) of up to 8 eligible w (kept,
 // not old/old) are evaluated at once by 8-lane groups in ascending w, and the first failing one
 // prunes v and redirects it.  Kept entries are written back in place with the flag cleared.
-// sk, pkey, ptgt: LDS of the wavefront's own, at least m entries each.  Returns the number of redirected edges, -1 for a
-// list without a new entry.
+// sk, pkey, ptgt: LDS of the wavefront's own, at least m entries each.  Returns the number of redirected edges (also in
+// *n_edges), -1 (0 there) for a list without a new entry.
 template <int DT>
 __device__ __forceinline__ int scan_vertex_pairs(const void *X, int d, int vec_ok, int R, int u, int m, u64 k0, u64 k1,
-                                                 u64 *row, int *deg, Prop *props, int *nprop, u64 *sk, u64 *pkey, u32 *ptgt,
+                                                 u64 *row, int *deg, Prop *props, int *n_edges, u64 *sk, u64 *pkey, u32 *ptgt,
                                                  int lane, u64 &evals_algo, u64 &evals_exec)
 {
     const int sub = lane & 7, grp = lane >> 3;
@@ -27,7 +27,7 @@ __device__ __forceinline__ int scan_vertex_pairs(const void *X, int d, int vec_o
     const u64 new1 = __builtin_amdgcn_ballot_w64(lane + 64 < m && (k1 & 1ull));
     wave_sync();
     if ((new0 | new1) == 0) {
-        if (lane == 0) nprop[u] = 0;
+        if (lane == 0) *n_edges = 0;
         return -1;
     }
     u64 K0 = 0, K1 = 0;   // U' as positions in the sorted list
@@ -81,7 +81,7 @@ __device__ __forceinline__ int scan_vertex_pairs(const void *X, int d, int vec_o
     if ((K1 >> lane) & 1ull) row[nk0 + __popcll(K1 & lanes_below(lane))] = k1 & ~1ull;
     if (lane == 0) {
         deg[u] = nk0 + __popcll(K1);
-        nprop[u] = np;
+        *n_edges = np;
     }
     wave_sync();
     for (int p = lane; p < np; p += 64) emit_redirect(pkey[p], ptgt[p], props + (size_t)u * R + p);

@@ -7,7 +7,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 N = 33_000      # one scan launch for lists of 33 .. 96 slots, two otherwise
-KINDS = ["plain", "centre 1e3", "centre 1e6", "scale 1e-30", "scale 1e-20", "scale 1e15", "sizes", "outlier", "copies", "zeros", "nan", "inf"]
+KINDS = ["plain", "centre 1e3", "centre 1e6", "scale 1e-30", "scale 1e-20", "scale 1e15", "sizes", "tight", "two places", "outlier", "copies", "zeros", "nan", "inf"]
 
 
 @pytest.fixture(scope="module")
@@ -29,6 +29,10 @@ def _rows(kind, d, N=N):
         X = X * np.float32(kind.split()[1])
     elif kind == "sizes":                          # norms over twelve binades
         X = X * np.exp2(g.integers(-6, 7, size=(N, 1))).astype(np.float32)
+    elif kind == "tight":                          # clusters far smaller than the distances between them: rounds that read whole rows
+        X = (g.normal(size=(512, d))[g.integers(0, 512, size=N)] + 0.003 * g.normal(size=(N, d))).astype(np.float32)
+    elif kind == "two places":
+        X[::2] += 1e4
     elif kind == "outlier":                        # rows the half-precision range does not hold
         X[::997] *= np.float32(1e12)
     elif kind == "copies":
@@ -52,8 +56,8 @@ def test_same_as_the_pair_at_a_time_kernel(rn, kind, d):
 @pytest.mark.parametrize("n,dtype", [(256, "f32"), (257, "f32"), (70_000, "f32"), (70_000, "f16"), (70_000, "bf16")])
 def test_sizes_where_the_launches_change(rn, n, dtype):
     import torch
-    for d in (32, 100, 320):
-        X = _rows("plain", d, n).to({"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[dtype])
+    for d, kind in ((32, "plain"), (100, "plain"), (320, "plain"), (48, "tight")):
+        X = _rows(kind, d, n).to({"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[dtype])
         _compare(rn, X, ((20, 96, 2, 2), (40, 64, 1, 2)))
 
 
