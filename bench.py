@@ -208,21 +208,22 @@ def measure(rn, cfg, X, Xd, esz, st16, steps, warmup, args, with_search=True, wi
     # Algorithmic bytes of one launch = rows of X it must gather (d*esz each) + the list entries it reads
     # (8 B) and writes back (8 B) + the redirected edges it emits (16 B); summed over the T1*T2 launches of
     # the last timed build, durations by HIP events on the build's stream.
-    scan_bytes = sum(g * (cfg.d * esz + 16) + 16 * p for g, p in zip(s["gathered_rows"], s["proposals"]))
+    # (float32 rows: the scan gathers the half-precision copy, 2 bytes a coordinate)
+    gather_esz = 2 if s["kernel_variant"] == 3 else esz
+    scan_bytes = sum(g * (cfg.d * gather_esz + 16) + 16 * p for g, p in zip(s["gathered_rows"], s["proposals"]))
     scan_ms = scan_ms_events if scan_ms_events else scan_ms_clock
     hbm_gbs = scan_bytes / (scan_ms * 1e-3) / 1e9 if scan_ms > 0 else 0.0
     kv = s["kernel_variant"]
     kname = {1: "k_update_scan",
              2: u8_scan_kernels(cfg),
-             3: "k_update_scan_mfma_f32_all<NRC,C0,CH,DT> (a round's scan launches, back to back; "
-                "%s MFMA Gram tiles, undecided pairs by exact distances)" % (st16 if half else "fp32")}[kv]
+             3: "k_scan_float_small<DT> + k_scan_float_all<DT,NC,C0> (a round's scan launches, back to back; "
+                "%s MFMA Gram tiles, undecided pairs by exact distances)" % (st16 if half else "f16 (half-precision copy)")}[kv]
     traffic = None if half or args.merge_cap or args.blocks else TRAFFIC_PER_LAUNCH.get((cfg.name, kv))
     if kv == 3:
-        # float rows: the Gram tiles run on the fp32 matrix cores (157.3 TFLOP/s dense; 16-bit rows: on the
-        # f16 ones, 2,500 TFLOP/s), the rows are gathered from HBM; the kernel is reported against whichever
+        # float rows: the Gram tiles run on the f16 matrix cores (2,500 TFLOP/s dense), the rows are gathered from HBM; the kernel is reported against whichever
         # of the two it sits closer to, with both fractions in the line.  executed flops = computed pair
         # distances * 2 d
-        mfma_peak = 2500.0 if half else 157.3
+        mfma_peak = 2500.0
         flops = sum(s["exec_evals"]) * 2.0 * cfg.d
         tflops = flops / (scan_ms * 1e-3) / 1e12 if scan_ms > 0 else 0.0
         extra = {"launches": rounds, "avg_launch_ms": scan_ms / max(1, rounds),

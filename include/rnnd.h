@@ -145,8 +145,9 @@ int rnnd_update_neighbors_blocks(const void *X, int64_t N, int32_t d, int dtype,
  * The library allocates it at the first call that needs it and keeps it, per device, for later calls (a
  * larger request replaces it); rnnd_release_workspace hands it back.  Not counted here: where the matrix-core scan needs
  * rows of another length than X has (see rnnd_set_kernel_variant), a call also keeps a padded copy of X in a block of its
- * own -- N rows of d coordinates rounded up to a multiple of 128 bytes (uint8: to 32, 64, 128 or a multiple of 64) -- if the
- * device has room for it.  Without room the call works on X itself, slower; the copy's block is given up where the
+ * own -- N rows of d coordinates rounded up to a multiple of 128 bytes (uint8: to 32, 64, 128 or a multiple of 64) -- and a build on
+ * float32 rows (256 vertices or more) a half-precision copy, N rows of 2 d bytes rounded up to a multiple of 64 or 128, next to it, if the
+ * device has room for them.  Without room the call works on X itself, slower; the copy's block is given up where the
  * workspace itself could not be had otherwise. */
 int rnnd_workspace_bytes(int64_t N, int32_t d, int dtype, int32_t R, int64_t rounds, size_t *bytes);
 
@@ -260,10 +261,10 @@ int rnnd_probe_gather_map(const void *X, int64_t n_rows, int64_t row_bytes, int6
  * throughout.  Automatic uses the dense Gram-block kernels on the matrix cores where they apply
  * and the generic kernel otherwise:
  *   uint8 rows: int8 MFMA (d = 32, 64 or 128 as they are, other lengths on a padded copy);
- *   float32 rows with d a multiple of 16, 16-bit rows with d a multiple of 32: a single-precision
- *   Gram block first (fp32 MFMA on float32 rows; f16 / bf16 MFMA on 16-bit rows as stored), every
- *   pair whose outcome lies within that block's error bound decided by the exact distance, and
- *   vertices with very many such pairs redone on the f64 MFMA.  Float rows of other lengths, or not 16-byte
+ *   float32 rows with d a multiple of 16, 16-bit rows with d a multiple of 32: a Gram block first (f16 / bf16 MFMA on
+ *   16-bit rows as stored and, in builds, on a half-precision copy of float32 rows; fp32 MFMA on float32 rows otherwise), every
+ *   pair whose outcome lies within that block's error bound and can matter decided by the exact distance, and
+ *   vertices with very many such pairs redone on the f64 MFMA or, on small inputs, pair by pair.  Float rows of other lengths, or not 16-byte
  *   aligned, on a padded copy if there are enough of them (256; 2,048 if d < 16) and every coordinate is finite
  *   (rnnd_update_neighbors: 2,048, finite or not).
  * All give identical graphs; this exists for testing and profiling.  Process-wide, not thread-safe. */

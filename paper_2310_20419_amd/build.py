@@ -9,7 +9,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librnnd.so")
-SOURCES = [os.path.join(CSRC, n + ".hip") for n in ("rnnd", "scan_float", "scan_f32")]
+SOURCES = [os.path.join(CSRC, n + ".hip") for n in ("rnnd", "scan_float", "scan_f32", "search")]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

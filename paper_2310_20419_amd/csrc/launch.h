@@ -65,3 +65,23 @@ void launch_f64_redo(const ScanLaunch &l, int dtype);
 void launch_f64_classes(const ScanLaunch &l, int dtype);
 // 16-bit rows, or the half-precision copy of float32 rows, by degree classes 0 .. 5
 void launch_float_scan(const ScanLaunch &l, int dtype, const void *rows, u32 rowbytes, const HalfPar *par);
+
+// A search as rnnd_search has planned it (search.hip): shape is an EvalShape, few = a team of wavefronts per query.
+struct SearchLaunch {
+    const void *X, *Q;
+    const int *graph, *degree;
+    long long N, nq;
+    int d, dtype, row_stride, L, K, k;
+    u64 seed;
+    u32 *bitmaps;
+    size_t bitmap_words;
+    u32 slots;
+    int *out_ids;
+    u32 *out_dist;
+    unsigned long long *counts;
+    unsigned blocks, dyn_lds;
+    int shape;
+    bool few;
+    hipStream_t st;
+};
+void launch_search(const SearchLaunch &l);

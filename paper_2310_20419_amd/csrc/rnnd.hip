@@ -10,6 +10,7 @@
 //   merge    every touched list becomes the first R distinct keys of (kept entries + inbox + later arrivals)
 //   compact  touched vertices whose new list holds a "new" entry form the next active lists,
 //            one per degree class (see degree_class)
+// (small inputs: the last three in one launch, see k_merge_blocks)
 // Between outer rounds AddReverseEdges (Alg. 5) uses the same inboxes and bins (launch_reverse).
 // Counters that many wavefronts would hit at one address are aggregated per block first.
 // search.h holds the graph search of Alg. 1 (rnnd_search).
@@ -1985,9 +1986,9 @@ static void launch_merge_blocks(int dt, hipStream_t st, long long N, int R, cons
     const auto go = dt == RNND_F32 ? launch_merge_blocks_dt<DT_F32> : dt == RNND_F16 ? launch_merge_blocks_dt<DT_F16> : dt == RNND_BF16 ? launch_merge_blocks_dt<DT_BF16> : launch_merge_blocks_dt<DT_U8>;
     go(st, N, R, w, keys, deg, use_classes, c, X, d);
 }
-#ifndef REDO_IN_SCATTER_MAX_N
+// 60-round builds with a launch of its own for the redo lists / without, ms: 1,000 x 96 float32 1.08 / 1.00, 20,000 x 96 2.88 / 2.82, 100,000
+// x 96 10.06 / 9.86, 100,000 x 304 19.16 / 19.12, 20,000 x 128 bfloat16 2.82 / 2.75, 20,000 x 320 float16 4.98 / 4.75.
 #define REDO_IN_SCATTER_MAX_N 131072
-#endif
 template <int DT>
 static void launch_scatter_redo_dt(unsigned blocks, hipStream_t st, long long N, int R, const Workspace &w, int ncl, RoundCtr *c, u64 *keys, int *deg,
                                    const void *X, int d, int vec_ok)
@@ -2855,37 +2856,9 @@ extern "C" int rnnd_search(const void *X, int64_t N, int32_t d, int dtype, int m
     {
         // (the bitmaps are cleared by the queries that need them)
         u32 *bitmaps = (u32 *)lease.base;
-#define RNND_SEARCH_TEAM(DT, E, SHAPE, TEAM)                                                                          \
-    hipLaunchKernelGGL((k_search<DT, E, SHAPE, TEAM>), dim3(blocks), dim3(64 * TEAM), dyn_lds, st, X, (long long)N, d, graph, \
-                       degree, row_stride, Q, (long long)nq, L, K, k, (u64)seed, bitmaps, bitmap_words, slots,        \
-                       out_ids, out_dist_bits, counts)
-#define RNND_SEARCH_ALONE(DT, E, SHAPE) RNND_SEARCH_TEAM(DT, E, SHAPE, 1)
-#define RNND_SEARCH_LAUNCH(DT, E, SHAPE)          \
-    if (few) RNND_SEARCH_TEAM(DT, E, SHAPE, 4);   \
-    else RNND_SEARCH_TEAM(DT, E, SHAPE, 1)
-#define RNND_SEARCH_E(DT, E)                                            \
-    if (shape == EVAL_SHORT) { RNND_SEARCH_ALONE(DT, E, EVAL_SHORT); }  \
-    else if (shape == EVAL_MID) { RNND_SEARCH_LAUNCH(DT, E, EVAL_MID); } \
-    else if (shape == EVAL_LONG) { RNND_SEARCH_LAUNCH(DT, E, EVAL_LONG); } \
-    else if (shape == EVAL_SINGLE) { RNND_SEARCH_LAUNCH(DT, E, EVAL_SINGLE); }
-#define RNND_SEARCH_FLOAT_E(DT, E)                                      \
-    RNND_SEARCH_E(DT, E)                                                \
-    else if (shape == EVAL_LONG_GLOBAL) { RNND_SEARCH_LAUNCH(DT, E, EVAL_LONG_GLOBAL); } \
-    else { RNND_SEARCH_LAUNCH(DT, E, EVAL_SINGLE_GLOBAL); }
-#define RNND_SEARCH_FLOAT(DT)                   \
-    if (L <= 64) { RNND_SEARCH_FLOAT_E(DT, 1) } \
-    else { RNND_SEARCH_FLOAT_E(DT, 2) }
-        if (dtype == RNND_U8 && L <= 64) { RNND_SEARCH_E(DT_U8, 1) }
-        else if (dtype == RNND_U8) { RNND_SEARCH_E(DT_U8, 2) }
-        else if (dtype == RNND_F16) { RNND_SEARCH_FLOAT(DT_F16) }
-        else if (dtype == RNND_BF16) { RNND_SEARCH_FLOAT(DT_BF16) }
-        else { RNND_SEARCH_FLOAT(DT_F32) }
-#undef RNND_SEARCH_FLOAT
-#undef RNND_SEARCH_FLOAT_E
-#undef RNND_SEARCH_E
-#undef RNND_SEARCH_ALONE
-#undef RNND_SEARCH_TEAM
-#undef RNND_SEARCH_LAUNCH
+        const SearchLaunch sl = {X, Q, graph, degree, (long long)N, (long long)nq, d, dtype, row_stride, L, K, k, (u64)seed, bitmaps, bitmap_words, slots,
+                                 out_ids, out_dist_bits, counts, (unsigned)blocks, (unsigned)dyn_lds, shape, few, st};
+        launch_search(sl);
         HIPCHK(hipGetLastError());
         HIPCHK(hipStreamSynchronize(st));
         int64_t sum = 0;

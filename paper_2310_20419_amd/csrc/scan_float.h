@@ -18,10 +18,15 @@
 //   - what falls below the smallest normal number.
 // Rows or distances that are not finite, or beyond 10^36, leave all their pairs undecided.
 //
-// An undecided pair is resolved by the exact routine (dist.h) only if its outcome can matter (see open_pairs); a vertex, or a
+// An undecided pair is resolved in double precision only if its outcome can matter: its column may be kept, and no column before it
+// prunes the row for certain; a vertex, or a
 // group of short-list vertices, with more than FLOAT_PAIR_CAP such pairs (ties in bulk) is left as it is and appended to
 // the redo list.  The redirected edges are stored without their delta(v,w): the merge at w computes it (close_keys), where the row
 // of w serves every edge w receives, at twice the scan's occupancy and next to a sort that leaves the memory idle.
+//
+// Measured on 60-round builds (scan kernels, ms; against 16-row groups of whole float32 rows, which also computed the redirected
+// distances: 119 and 871): 1M x 96 58 ms, vector units 0.57 busy, 6.0 TB/s fetched; 1M x 960 300 ms, 5.9 TB/s; 300,000 x 768 bfloat16
+// 70 ms, 6.2 TB/s.  Random rows in 128-byte chunks reach 6.9 TB/s.
 #pragma once
 #include "round.h"
 #include "scan_mfma.h"
@@ -353,7 +358,7 @@ struct FloatOp {
                     const u32 rem = (u32)(m - 32 * I);
                     const u32 vmask = rem >= 32u ? 0xFFFFFFFFu : ((1u << rem) - 1u);
                     if (__builtin_amdgcn_ballot_w64(some) != 0ull) {
-                        // open pairs (see the top of the file): hi = rows not pruned for certain, lo = rows kept for certain
+                        // the pairs that can matter (see the top of the file): hi = rows not pruned for certain, lo = rows kept for certain
                         bool sure = false, may = false;
 #pragma unroll
                         for (int J = 0; J < I; ++J) {

@@ -1,4 +1,4 @@
-// UpdateNeighbors scan (Alg. 4, the body of the vertex loop) for float32 rows on the double-precision matrix cores.
+// UpdateNeighbors scan (Alg. 4, the body of the vertex loop) for whole float32 rows on the matrix cores, and in double precision for all float rows.
 //
 // One wavefront owns one vertex u with m <= 16*NRC list entries, handled as NRC groups of 16 rows.
 // The rows are streamed through registers 16 dimensions (64 bytes per row) at a time: lane l loads 4
@@ -235,7 +235,7 @@ __device__ __forceinline__ int popc_below_w(u64 m0, u64 m1, int p)
 // degree class family; CH = 64-byte chunks of every row fetched per loop iteration (rows a multiple of
 // 64 CH bytes: a longer iteration gives the prefetch more matrix work to hide behind); DT = DT_F32 or
 // DT_F16 / DT_BF16 (16-bit storage of the same kind of rows).
-// FAST: the Gram block in single precision (gram_f32_loop).  A pair is then decided only if the outcome of
+// FAST: the Gram block of float32 rows in single precision (gram_f32_loop).  A pair is then decided only if the outcome of
 // the prune test is beyond the error bound of that block, eps_ij = (1.5 d + 20) 2^-24 (n_i + n_j), which
 // covers the accumulation of G (2 x 1.01 d 2^-24 sqrt(n_i n_j) <= 1.01 d 2^-24 (n_i + n_j)), the norms summed
 // in float (d / 4 + 2 roundings per norm), the evaluation of n_i + n_j - 2 G_ij in float and the roundings
