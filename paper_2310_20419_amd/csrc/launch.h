@@ -56,6 +56,7 @@ struct ScanLaunch {
     hipStream_t st;
     hipEvent_t e_start, e_stop;
     int round;                  // 0: no round before it in this call's counters
+    bool last;                  // launch_float_scan: no scan launch follows it (it carries e_stop)
 };
 
 // float32 rows by degree classes 0 .. 6, single precision

@@ -2027,7 +2027,7 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
     const int d = variant == 2 ? plan.dp : rv.d, vec_ok = rv.vec_ok;
     RoundCtr *c = w.ctr + t;
     const int open_dt = variant == 3 && use_classes == 2 ? dtype : RNND_U8;      // whose redirected edges come without distances
-    const bool redo_in_scatter = open_dt != RNND_U8 && !run && !re.scan_stop && N <= REDO_IN_SCATTER_MAX_N;
+    const bool redo_in_scatter = open_dt != RNND_U8 && !run && N <= REDO_IN_SCATTER_MAX_N;
     if (run) {
         const unsigned cb = (run->count + 1023u) / 1024u;
         hipLaunchKernelGGL(k_compact_classes, dim3(cb < 256u ? cb : 256u, 1), dim3(1024), 0, st, (const u32 *)nullptr,
@@ -2041,7 +2041,7 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
         else launch_mfma_scan_classes<0>(w, d, R, keys, deg, N, c, st, re);
     } else if (variant == 3) {
         const bool generic_tail = R > 96;
-        ScanLaunch l = {X, d, R, keys, deg, N, w.lists, w.props, w.nprop, c, w.touched, st, re.scan_start, generic_tail ? (hipEvent_t) nullptr : re.scan_stop, run ? 0 : t};
+        ScanLaunch l = {X, d, R, keys, deg, N, w.lists, w.props, w.nprop, c, w.touched, st, re.scan_start, generic_tail && !redo_in_scatter ? (hipEvent_t) nullptr : re.scan_stop, run ? 0 : t, redo_in_scatter};
         if (use_classes == 2) {
             // lists of up to 128 entries; what the redo list of the longest holds goes to the generic kernel
             const bool copy = rv.half.rows != nullptr;

@@ -14,27 +14,28 @@ template <int DT>
 static void launch(const ScanLaunch &l, const FloatRows &fr, const void *rows, u32 rowbytes)
 {
     const int8_t *G = (const int8_t *)rows;
+    const hipEvent_t e_stop = l.last ? l.e_stop : (hipEvent_t) nullptr;
     auto blocks = [&](int per_cu) {
         const unsigned gx = capped((long long)cu_count() * per_cu, l.N);
         return dim3(gx < 8 ? 8 : gx);      // a block at least for every class
     };
     if (l.R > 32 && l.R <= 96 && l.N <= FLOAT_SHARED_MAX_N) {
         static const int per_cu = resident_blocks_per_cu(k_scan_float_all<DT, 5, 0>, 2);
-        hipExtLaunchKernelGGL((k_scan_float_all<DT, 5, 0>), blocks(per_cu), dim3(256), 0, l.st, l.e_start, nullptr, 0, G, rowbytes, fr, l.R, l.keys, l.deg,
+        hipExtLaunchKernelGGL((k_scan_float_all<DT, 5, 0>), blocks(per_cu), dim3(256), 0, l.st, l.e_start, e_stop, 0, G, rowbytes, fr, l.R, l.keys, l.deg,
                               l.lists, l.props, l.nprop, l.c, l.round);
         return;
     }
     static const int per_s = resident_blocks_per_cu(k_scan_float_small<DT>, 4);
     const int ny = 1 + (l.R > 8) + (l.R > 16);
-    hipExtLaunchKernelGGL((k_scan_float_small<DT>), dim3(capped(cu_count() * per_s, l.N), ny), dim3(256), 0, l.st, l.e_start, nullptr, 0, G, rowbytes, fr,
+    hipExtLaunchKernelGGL((k_scan_float_small<DT>), dim3(capped(cu_count() * per_s, l.N), ny), dim3(256), 0, l.st, l.e_start, l.R <= 32 ? e_stop : (hipEvent_t) nullptr, 0, G, rowbytes, fr,
                           l.R, l.keys, l.deg, l.lists, l.props, l.nprop, l.c, l.R > 32 && l.R <= 96 ? l.round : -1);
     if (l.R <= 32) return;
     static const int per5 = resident_blocks_per_cu(k_scan_float_all<DT, 5, 3>, 2), per6 = resident_blocks_per_cu(k_scan_float_all<DT, 6, 3>, 1);
     if (l.R <= 96)
-        hipExtLaunchKernelGGL((k_scan_float_all<DT, 5, 3>), blocks(per5), dim3(256), 0, l.st, nullptr, nullptr, 0, G, rowbytes, fr, l.R, l.keys, l.deg, l.lists,
+        hipExtLaunchKernelGGL((k_scan_float_all<DT, 5, 3>), blocks(per5), dim3(256), 0, l.st, nullptr, e_stop, 0, G, rowbytes, fr, l.R, l.keys, l.deg, l.lists,
                               l.props, l.nprop, l.c, l.round);
     else
-        hipExtLaunchKernelGGL((k_scan_float_all<DT, 6, 3>), blocks(per6), dim3(256), 0, l.st, nullptr, nullptr, 0, G, rowbytes, fr, l.R, l.keys, l.deg, l.lists,
+        hipExtLaunchKernelGGL((k_scan_float_all<DT, 6, 3>), blocks(per6), dim3(256), 0, l.st, nullptr, e_stop, 0, G, rowbytes, fr, l.R, l.keys, l.deg, l.lists,
                               l.props, l.nprop, l.c, l.round);
 }
 
