@@ -338,7 +338,7 @@ __device__ __forceinline__ void scatter_lists(long long N, int R, const int *lis
     // the classes' lists as one: the grid is shared by their entries, however they are spread over the classes
     const ActiveLists al = active_lists(lists, N, ctr, ncl);
     const u32 n = al.start[NDEG];
-    stamp_scan_stop(ctr);
+    if (n < RNND_MAX_SLOTS) stamp_scan_stop(ctr);      // (always: the clock is read once the scan's counters are here)
     if (g >= n) return;
     // the loads of the next vertex (its count and its first 16 edges) are issued before the atomics
     // of the current one; the list entry of the vertex after that is fetched one trip earlier still
