@@ -242,7 +242,7 @@ struct FloatOp {
             const u32 pr = pair[p < total ? p : 0];
             const double e = wide_distance(fr.X + (size_t)id[(pr >> 8) & 127u] * rb, fr.X + (size_t)id[pr & 127u] * rb, pieces, sub, L);
             const float lo = (float)(e - e * spread), hi = (float)(e + e * spread);
-            const bool certain = __float_as_uint(lo) == __float_as_uint(hi);
+            const bool certain = lo == hi;      // (not where e is not a number: its sign depends on the order of the sum)
             if (sub == 0 && p < total) dd[p] = certain ? __float_as_uint(lo) : 0xFFFFFFFFu;
             unsure = unsure || !certain;
         }

@@ -76,3 +76,27 @@ def test_a_single_round_does_not_wait_for_the_rows(rn, dtype, d):
     X = _rows(dtype, d, "nan")
     keys, deg = rn.rnnd_random_graph(X, 20, 64, 4)
     assert rn.rnnd_update_neighbors(X, keys, deg, 64, 1).kernel_variant == 3
+
+
+@pytest.mark.parametrize("S,R", [(8, 16), (20, 64)])
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 320), ("f16", 64), ("f16", 512), ("bf16", 320)])
+def test_rows_of_nan_of_either_sign(rn, dtype, d, S, R):
+    """A distance that is not a number is stored, and compared, with the sign its sum happens to end with, which depends on the
+    order of the sum: only the routine that all stored distances come from may decide such a pair."""
+    import torch
+    g = np.random.default_rng(6)
+    X = (g.normal(size=(8, d))[g.integers(0, 8, size=N)] + 0.5 * g.normal(size=(N, d))).astype(np.float32)
+    t = torch.from_numpy(X).cuda().to({"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[dtype])
+    bits = t.view(torch.int32 if dtype == "f32" else torch.int16)
+    quiet = {"f32": 0x7FC00000, "f16": 0x7E00, "bf16": 0x7FC0}[dtype]
+    for k in range(6):      # a quarter of the rows holds one, of either sign
+        rows = torch.from_numpy(g.permutation(N)[:N // 16]).cuda()
+        bits[rows, int(g.integers(0, d))] = quiet if k % 2 else quiet - (1 << (31 if dtype == "f32" else 15))
+    assert int((bits[torch.isnan(t)] < 0).sum()) > 300 and int((bits[torch.isnan(t)] > 0).sum()) > 300
+
+    def build():
+        return rn.rnnd_build_ex(t, S, R, 2, 3, 4)
+    want = _variant(rn, 1, build)
+    used = torch.arange(R, device="cuda")[None, :] < want[1][:, None]
+    got = _variant(rn, 0, build)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and torch.equal(got[2][used], want[2][used])
