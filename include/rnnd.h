@@ -69,7 +69,9 @@ typedef struct {
     int32_t rounds;                         /* UpdateNeighbors rounds run (T1*T2) */
     int32_t reverse_calls;                  /* AddReverseEdges calls run (T1-1) */
     int32_t kernel_variant;                 /* UpdateNeighbors scan kernel used: 1 generic, 2 int8 MFMA, 3 float MFMA (fp32, then f64) */
-    int32_t reserved;
+    int32_t group_scans;                    /* scans (one per round; block-sequential: per run) of float rows that took the form of 16-row
+                                               groups because the 32-row tiles of the 16-bit matrix cores had left too many pairs
+                                               to the exact distance */
     float total_ms, init_ms;                /* GPU time of the whole call / of RandomGraph (HIP events) */
     float round_ms[RNND_MAX_ROUNDS];        /* GPU time of each UpdateNeighbors round (see rnnd_set_event_timing) */
     float scan_ms[RNND_MAX_ROUNDS];         /* of which: the scan kernels (Alg. 4's loop body) */

@@ -2184,6 +2184,7 @@ static hipError_t launch_reverse(const Workspace &w, long long N, int R, int use
 static void fill_round_stats(rnnd_stats *s, const RoundCtr *h, int rounds)
 {
     s->rounds = rounds;
+    for (int t = 0; t < rounds; ++t) s->group_scans += h[t].whole != 0u;
     for (int t = 0; t < rounds && t < RNND_MAX_ROUNDS; ++t) {
         s->active[t] = 0;
         for (int c = 0; c < NDEG; ++c) s->active[t] += h[t].n_active[c];
@@ -2446,6 +2447,7 @@ static void fill_pass_stats(rnnd_stats *s, const RoundCtr *h, int passes, int pe
         for (int k = 0; k < per_pass; ++k) {
             memset(&one, 0, sizeof one);
             fill_round_stats(&one, h + (size_t)p * per_pass + k, 1);
+            s->group_scans += one.group_scans;
             s->active[p] += one.active[0];
             s->algo_evals[p] += one.algo_evals[0];
             s->exec_evals[p] += one.exec_evals[0];
