@@ -56,6 +56,7 @@ struct ScanLaunch {
     hipStream_t st;
     hipEvent_t e_start, e_stop;
     int round;                  // 0: no round before it in this call's counters
+    long long vertices;         // of the round or run
     bool last;                  // launch_float_scan: no scan launch follows it (it carries e_stop)
 };
 

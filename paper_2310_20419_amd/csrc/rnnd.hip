@@ -2041,7 +2041,7 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
         else launch_mfma_scan_classes<0>(w, d, R, keys, deg, N, c, st, re);
     } else if (variant == 3) {
         const bool generic_tail = R > 96;
-        ScanLaunch l = {X, d, R, keys, deg, N, w.lists, w.props, w.nprop, c, w.touched, st, re.scan_start, generic_tail && !redo_in_scatter ? (hipEvent_t) nullptr : re.scan_stop, run ? 0 : t, redo_in_scatter};
+        ScanLaunch l = {X, d, R, keys, deg, N, w.lists, w.props, w.nprop, c, w.touched, st, re.scan_start, generic_tail && !redo_in_scatter ? (hipEvent_t) nullptr : re.scan_stop, run ? 0 : t, run ? (long long)run->count : N, redo_in_scatter};
         if (use_classes == 2) {
             // lists of up to 128 entries; what the redo list of the longest holds goes to the generic kernel
             const bool copy = rv.half.rows != nullptr;

@@ -54,6 +54,7 @@ struct FloatRows {
     int *redo;                     // vertices with lists of up to 96 entries, then (N further on) longer ones
     u32 *n_redo;
     long long N;
+    u32 enough;                    // active vertices from which a round decides about the form of the next
 };
 
 __device__ __forceinline__ u32 both_halves(u64 b) { return (u32)b | (u32)(b >> 32); }
@@ -573,9 +574,11 @@ struct FloatOp {
 // clusters are tight next to the distances between them, or rows differ in size by orders of magnitude, the copy leaves most pairs
 // to the exact distance.  So once a round has left more than WHOLE_OPEN per active vertex (0.3 on the average, 1.1 at most in the
 // builds of this repository's float workloads), the following ones take the form of scan_mfma_f32.h: every block finds the same from
-// the counters of the round before.
+// the counters of the round before.  A round decides this only if it has enough active vertices (see launch_float_scan): below, the
+// sample is not one (a few lists lie in wavefronts that are all sampled, or none), and the last rounds before an
+// AddReverseEdges call, of a handful of vertices, say nothing about the rounds after it.
 #define WHOLE_OPEN 6
-__device__ __forceinline__ bool whole_rows(RoundCtr *ctr, int round)
+__device__ __forceinline__ bool whole_rows(RoundCtr *ctr, int round, u32 enough)
 {
     bool on = false;
     if (round > 0) {
@@ -583,7 +586,8 @@ __device__ __forceinline__ bool whole_rows(RoundCtr *ctr, int round)
         u32 active = 0;
 #pragma unroll
         for (int k = 0; k < NDEG; ++k) active += p->n_active[k];
-        on = p->whole != 0u || (u64)p->n_open * OPEN_SAMPLE > (u64)WHOLE_OPEN * active || (u64)(p->n_redo[0] + p->n_redo[1]) * 16u > active;
+        on = p->whole != 0u || (active >= enough && ((u64)p->n_open * OPEN_SAMPLE > (u64)WHOLE_OPEN * active ||
+                                                     (u64)(p->n_redo[0] + p->n_redo[1]) * 16u > active));
     }
     if (on && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) ctr->whole = 1u;
     return on;
@@ -602,7 +606,7 @@ __global__ __launch_bounds__(256, 4) void k_scan_float_small(
     const int *list = lists + (size_t)y * fr.N;
     const u32 n = ctr->n_active[y];
     stamp_scan_start(ctr);
-    if (DT == DT_F32 && round >= 0 && whole_rows(ctr, round)) return;      // (round < 0: no launch beside this one to take the lists)
+    if (DT == DT_F32 && round >= 0 && whole_rows(ctr, round, fr.enough)) return;      // (round < 0: no launch beside this one to take the lists)
     const OP op(fr, rowbytes);
     if (y == 0) scan_packed_stream_body<OP, 4>(op, G, (int)rowbytes, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
     else if (y == 1) scan_packed_stream_body<OP, 2>(op, G, (int)rowbytes, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
@@ -648,7 +652,7 @@ __global__ __launch_bounds__(256, (NC == 6 ? 1 : 2)) void k_scan_float_all(
     __shared__ FloatScanSmem<NGMAX> smem[4];
     if (C0 == 0) stamp_scan_start(ctr);
     if constexpr (DT == DT_F32 && NC == 5)
-        if (whole_rows(ctr, round)) {
+        if (whole_rows(ctr, round, fr.enough)) {
             whole_row_classes<sizeof(FloatScanSmem<NGMAX>)>(fr, R, keys, deg, lists, props, nprop, ctr, reinterpret_cast<char(*)[sizeof(FloatScanSmem<NGMAX>)]>(smem));
             return;
         }

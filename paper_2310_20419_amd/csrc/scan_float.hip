@@ -39,9 +39,13 @@ static void launch(const ScanLaunch &l, const FloatRows &fr, const void *rows, u
                               l.props, l.nprop, l.c, l.round);
 }
 
+// A round of fewer active vertices than this does not decide which form the next one takes: 32 sampled wavefronts, or a sixteenth
+// of the vertices.
+#define DECIDE_MIN_ACTIVE 1024
 void launch_float_scan(const ScanLaunch &l, int dtype, const void *rows, u32 rowbytes, const HalfPar *par)
 {
-    const FloatRows fr = {(const char *)l.X, l.d, par, l.redo, &l.c->n_redo[0], l.N};
+    const u32 share = (u32)(l.vertices / 16);
+    const FloatRows fr = {(const char *)l.X, l.d, par, l.redo, &l.c->n_redo[0], l.N, share > DECIDE_MIN_ACTIVE ? share : DECIDE_MIN_ACTIVE};
     if (dtype == DT_F16) launch<DT_F16>(l, fr, rows, rowbytes);
     else if (dtype == DT_BF16) launch<DT_BF16>(l, fr, rows, rowbytes);
     else launch<DT_F32>(l, fr, rows, rowbytes);

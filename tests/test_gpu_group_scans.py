@@ -34,3 +34,12 @@ def test_rows_that_need_groups_get_them(rn, n, d):
     st = rn.rnnd_build_ex(rows("tight", n, d), 20, 96, 2, 4, 3)[3]
     assert 1 <= st.group_scans <= 7
     assert rn.rnnd_build_ex(rows("plain", n, d), 20, 96, 2, 4, 3)[3].group_scans == 0
+
+
+@pytest.mark.parametrize("n,d,R", [(1_200, 96, 96), (2_000, 96, 96), (5_000, 33, 48), (20_000, 96, 96)])
+def test_rounds_with_little_to_do_decide_nothing(rn, n, d, R):
+    """The last rounds before an AddReverseEdges call have a handful of active vertices: their few pairs say nothing about the
+    form that suits the thousands of the next round."""
+    for seed in range(4):
+        st = rn.rnnd_build_ex(rows("unit", n, d, seed), 20, R, 4, 15, seed)[3]
+        assert min(st.active[:60]) < 64 and st.group_scans == 0, (seed, list(st.active[:60]))
