@@ -2041,7 +2041,7 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
         else launch_mfma_scan_classes<0>(w, d, R, keys, deg, N, c, st, re);
     } else if (variant == 3) {
         const bool generic_tail = R > 96;
-        ScanLaunch l = {X, d, R, keys, deg, N, w.lists, w.props, w.nprop, c, w.touched, st, re.scan_start, generic_tail && !redo_in_scatter ? (hipEvent_t) nullptr : re.scan_stop, run ? 0 : t, run ? (long long)run->count : N, redo_in_scatter};
+        ScanLaunch l = {X, d, R, keys, deg, N, w.lists, w.props, w.nprop, c, w.touched, st, re.scan_start, generic_tail && !redo_in_scatter ? (hipEvent_t) nullptr : re.scan_stop, t, run ? (long long)run->count : N, redo_in_scatter};
         if (use_classes == 2) {
             // lists of up to 128 entries; what the redo list of the longest holds goes to the generic kernel
             const bool copy = rv.half.rows != nullptr;
@@ -2184,7 +2184,7 @@ static hipError_t launch_reverse(const Workspace &w, long long N, int R, int use
 static void fill_round_stats(rnnd_stats *s, const RoundCtr *h, int rounds)
 {
     s->rounds = rounds;
-    for (int t = 0; t < rounds; ++t) s->group_scans += h[t].whole != 0u;
+    for (int t = 0; t < rounds; ++t) s->group_scans += h[t].groups != 0u;
     for (int t = 0; t < rounds && t < RNND_MAX_ROUNDS; ++t) {
         s->active[t] = 0;
         for (int c = 0; c < NDEG; ++c) s->active[t] += h[t].n_active[c];

@@ -15,8 +15,8 @@ struct RoundCtr {
     u32 n_active[NDEG];   // lengths of this round's active lists
     u32 n_touched[NMRG];  // distinct targets of the redirected edges, by size of the merge they need
     u32 nonfinite;        // slot 0: k_prepare_rows met a coordinate that is NaN or infinite
-    u32 n_open;           // 16-bit matrix-core scan: pairs that its blocks left to the exact distance, by a sample of the wavefronts
-    u32 whole;            // ... of float32 rows: this round reads whole rows instead of the half-precision copy
+    u32 n_open;           // float scan by tiles: pairs left to the exact distance, by a sample of the wavefronts
+    u32 groups;           // float scan: this round (or run) takes groups of 16 rows instead of tiles (see group_form)
     u32 pad;
     u32 n_redo[NDEG];     // float scan: vertices the single-precision form left to the double-precision one
     // ticks of the device's constant-rate clock (0 = not taken): the round's first scan launch starts, its scatter

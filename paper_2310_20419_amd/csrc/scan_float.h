@@ -101,7 +101,7 @@ struct FloatOp {
     __device__ __forceinline__ void report(RoundCtr *ctr) const
     {
         // one wavefront in OPEN_SAMPLE (an add of each to one address takes 10 ns, 20 us a round)
-        if (HALF && n_open && threadIdx.x == 0 && (blockIdx.x & 7) == 0) atomicAdd(&ctr->n_open, n_open);
+        if (n_open && threadIdx.x == 0 && (blockIdx.x & 7) == 0) atomicAdd(&ctr->n_open, n_open);
     }
 
     static __device__ __forceinline__ v16f mac(const v4i &a, const v4i &b, const v16f &c)
@@ -225,7 +225,7 @@ struct FloatOp {
             if (lane >= o) incl += up;
         }
         const int total = __builtin_amdgcn_readlane(incl, 63);
-        if (HALF) n_open += (u32)total;
+        n_open += (u32)total;
         if (total > FLOAT_PAIR_CAP) return false;
         wave_sync();
         int at = incl - mine;
@@ -570,15 +570,16 @@ struct FloatOp {
     }
 };
 
-// Whether this round's scan of float32 rows reads whole rows, in single precision, instead of the half-precision copy.  Where
-// clusters are tight next to the distances between them, or rows differ in size by orders of magnitude, the copy leaves most pairs
-// to the exact distance.  So once a round has left more than WHOLE_OPEN per active vertex (0.3 on the average, 1.1 at most in the
-// builds of this repository's float workloads), the following ones take the form of scan_mfma_f32.h: every block finds the same from
-// the counters of the round before.  A round decides this only if it has enough active vertices (see launch_float_scan): below, the
+// Whether this round's scan takes the lists in groups of 16 rows, by scan_mfma_f32.h: float32 rows whole and in single precision,
+// 16-bit rows under the narrower error bound of that form.  Where clusters are tight next to the distances between them, rows differ
+// in size by orders of magnitude, or 16-bit rows lie far from the origin, the tiles leave most pairs to the exact distance.  So once
+// a round has left more than GROUP_OPEN per active vertex (0.3 on the average, 1.1 at most in the builds of this repository's float
+// workloads), the following ones take the other form: every block finds the same from the counters of the round before (block-sequential
+// passes: of the run before).  A round decides this only if it has enough active vertices (see launch_float_scan): below, the
 // sample is not one (a few lists lie in wavefronts that are all sampled, or none), and the last rounds before an
 // AddReverseEdges call, of a handful of vertices, say nothing about the rounds after it.
-#define WHOLE_OPEN 6
-__device__ __forceinline__ bool whole_rows(RoundCtr *ctr, int round, u32 enough)
+#define GROUP_OPEN 6
+__device__ __forceinline__ bool group_form(RoundCtr *ctr, int round, u32 enough)
 {
     bool on = false;
     if (round > 0) {
@@ -586,14 +587,25 @@ __device__ __forceinline__ bool whole_rows(RoundCtr *ctr, int round, u32 enough)
         u32 active = 0;
 #pragma unroll
         for (int k = 0; k < NDEG; ++k) active += p->n_active[k];
-        on = p->whole != 0u || (active >= enough && ((u64)p->n_open * OPEN_SAMPLE > (u64)WHOLE_OPEN * active ||
+        on = p->groups != 0u || (active >= enough && ((u64)p->n_open * OPEN_SAMPLE > (u64)GROUP_OPEN * active ||
                                                      (u64)(p->n_redo[0] + p->n_redo[1]) * 16u > active));
     }
-    if (on && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) ctr->whole = 1u;
+    if (on && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) ctr->groups = 1u;
     return on;
 }
 
-// Lists of at most 8, 16, 32 entries (blockIdx.y = degree class): 4, 2, 1 vertices per wavefront.  
+// One list of vertices with up to 16 NRC entries each, in groups of 16 rows; entry i < n_first of the list is list[i], the others
+// lie `skip` further on.
+template <int DT, int NG, int NRC, int SMEM>
+__device__ __forceinline__ void group_lists(const FloatRows &fr, int R, u64 *keys, int *deg, const int *list, u32 n_first, size_t skip, u32 n, Prop *props,
+                                            int *nprop, RoundCtr *ctr, char *sm, u32 block, u32 nblocks)
+{
+    static_assert(sizeof(F32ScanSmem<NRC>) <= SMEM, "the group form works in the LDS of the tile form");
+    f32_scan_body<NG, 1, NRC, true, DT>(fr.X, fr.d, R, keys, deg, list, n_first, skip, n, props, nprop, ctr, fr.redo, fr.n_redo,
+                                        *reinterpret_cast<F32ScanSmem<NRC> *>(sm), block, nblocks);
+}
+
+// Lists of at most 8, 16, 32 entries (blockIdx.y = degree class): 4, 2, 1 vertices per wavefront.
 template <int DT>
 __global__ __launch_bounds__(256, 4) void k_scan_float_small(
     const int8_t *__restrict__ G, u32 rowbytes, FloatRows fr, int R, u64 *__restrict__ keys, int *__restrict__ deg,
@@ -606,38 +618,17 @@ __global__ __launch_bounds__(256, 4) void k_scan_float_small(
     const int *list = lists + (size_t)y * fr.N;
     const u32 n = ctr->n_active[y];
     stamp_scan_start(ctr);
-    if (DT == DT_F32 && round >= 0 && whole_rows(ctr, round, fr.enough)) return;      // (round < 0: no launch beside this one to take the lists)
+    if (group_form(ctr, round, fr.enough)) {
+        constexpr int SMEM = sizeof(FloatScanSmem<1>);
+        if (y < 2) group_lists<DT, 1, 1, SMEM>(fr, R, keys, deg, list, n, 0, n, props, nprop, ctr, (char *)&sm, blockIdx.x, gridDim.x);
+        else group_lists<DT, 1, 2, SMEM>(fr, R, keys, deg, list, n, 0, n, props, nprop, ctr, (char *)&sm, blockIdx.x, gridDim.x);
+        return;
+    }
     const OP op(fr, rowbytes);
     if (y == 0) scan_packed_stream_body<OP, 4>(op, G, (int)rowbytes, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
     else if (y == 1) scan_packed_stream_body<OP, 2>(op, G, (int)rowbytes, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
     else scan_packed_stream_body<OP, 1>(op, G, (int)rowbytes, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
     op.report(ctr);
-}
-
-// The classes of a round that reads whole rows: shapes of 1, 2, 4, 6 groups of 16 rows.
-template <int SMEM>
-__device__ __forceinline__ void whole_row_classes(const FloatRows &fr, int R, u64 *keys, int *deg, const int *lists, Prop *props, int *nprop,
-                                                  RoundCtr *ctr, char (*smem)[SMEM])
-{
-    static_assert(sizeof(F32ScanSmem<6>) <= SMEM, "");
-    constexpr u32 weight[4] = {16u, 24u, 44u, 72u};
-    const u32 n1 = ctr->n_active[0], n[4] = {n1 + ctr->n_active[1], ctr->n_active[2], ctr->n_active[3], ctr->n_active[4]};
-    u32 block, mine;
-    const int k = share_blocks<4>(n, weight, block, mine);
-    char *sm = smem[threadIdx.x >> 6];
-    const size_t N = (size_t)fr.N;
-    if (k == 0)
-        f32_scan_body<1, 1, 1, true, DT_F32>(fr.X, fr.d, R, keys, deg, lists, n1, N - n1, n[0], props, nprop, ctr, fr.redo, fr.n_redo,
-                                             *reinterpret_cast<F32ScanSmem<1> *>(sm), block, mine);
-    else if (k == 1)
-        f32_scan_body<1, 1, 2, true, DT_F32>(fr.X, fr.d, R, keys, deg, lists + 2 * N, n[1], 0, n[1], props, nprop, ctr, fr.redo, fr.n_redo,
-                                             *reinterpret_cast<F32ScanSmem<2> *>(sm), block, mine);
-    else if (k == 2)
-        f32_scan_body<2, 1, 4, true, DT_F32>(fr.X, fr.d, R, keys, deg, lists + 3 * N, n[2], 0, n[2], props, nprop, ctr, fr.redo, fr.n_redo,
-                                             *reinterpret_cast<F32ScanSmem<4> *>(sm), block, mine);
-    else if (k == 3)
-        f32_scan_body<3, 1, 6, true, DT_F32>(fr.X, fr.d, R, keys, deg, lists + 4 * N, n[3], 0, n[3], props, nprop, ctr, fr.redo, fr.n_redo,
-                                             *reinterpret_cast<F32ScanSmem<6> *>(sm), block, mine);
 }
 
 // Classes C0 .. NC - 1 in one launch, the grid's blocks divided among them by their work (as k_update_scan_mfma_u8_all).
@@ -651,20 +642,32 @@ __global__ __launch_bounds__(256, (NC == 6 ? 1 : 2)) void k_scan_float_all(
     static_assert(NC == 5 || NC == 6, "short lists plus two or three long-list classes");
     __shared__ FloatScanSmem<NGMAX> smem[4];
     if (C0 == 0) stamp_scan_start(ctr);
-    if constexpr (DT == DT_F32 && NC == 5)
-        if (whole_rows(ctr, round, fr.enough)) {
-            whole_row_classes<sizeof(FloatScanSmem<NGMAX>)>(fr, R, keys, deg, lists, props, nprop, ctr, reinterpret_cast<char(*)[sizeof(FloatScanSmem<NGMAX>)]>(smem));
-            return;
-        }
-    constexpr u32 weight[6] = {6u, 12u, 24u, 46u, 78u, 112u};
-    u32 n[NC];
+    const int wave = threadIdx.x >> 6, rb = (int)rowbytes;
+    const size_t N = (size_t)fr.N;
+    const bool groups = group_form(ctr, round, fr.enough);
+    // (the group form takes lists of up to 96 entries, classes 0 and 1 as one; the longest stay with the tiles)
+    constexpr u32 tile_weight[6] = {6u, 12u, 24u, 46u, 78u, 112u}, group_weight[6] = {16u, 16u, 24u, 44u, 72u, 112u};
+    u32 n[NC], weight[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) n[c] = c >= C0 ? ctr->n_active[c] : 0u;
+    for (int c = 0; c < NC; ++c) {
+        n[c] = c >= C0 ? ctr->n_active[c] : 0u;
+        weight[c] = groups ? group_weight[c] : tile_weight[c];
+    }
+    const u32 n0 = n[0];
+    if (C0 == 0 && groups) n[1] += n0, n[0] = 0u;
     u32 block, mine;
     const int cls = share_blocks<NC>(n, weight, block, mine);
     if (cls < 0) return;
-    const int *list = lists + (size_t)cls * fr.N;
-    const int wave = threadIdx.x >> 6, rb = (int)rowbytes;
+    if (groups && cls < 5) {
+        constexpr int SMEM = sizeof(FloatScanSmem<NGMAX>);
+        char *sm = (char *)&smem[wave];
+        if (C0 == 0 && cls == 1) group_lists<DT, 1, 1, SMEM>(fr, R, keys, deg, lists, n0, N - n0, n[1], props, nprop, ctr, sm, block, mine);
+        else if (C0 == 0 && cls == 2) group_lists<DT, 1, 2, SMEM>(fr, R, keys, deg, lists + 2 * N, n[2], 0, n[2], props, nprop, ctr, sm, block, mine);
+        else if (cls == 3) group_lists<DT, 2, 4, SMEM>(fr, R, keys, deg, lists + 3 * N, n[3], 0, n[3], props, nprop, ctr, sm, block, mine);
+        else group_lists<DT, 3, 6, SMEM>(fr, R, keys, deg, lists + 4 * N, n[4], 0, n[4], props, nprop, ctr, sm, block, mine);
+        return;
+    }
+    const int *list = lists + (size_t)cls * N;
     const OP op(fr, rowbytes);
     FloatScanSmem<1> &sm1 = *reinterpret_cast<FloatScanSmem<1> *>(&smem[wave]);
     if (C0 == 0 && cls == 0) scan_packed_stream_body<OP, 4>(op, G, rb, R, keys, deg, list, n[0], props, nprop, ctr, sm1, block, mine);

@@ -28,7 +28,7 @@ static void launch(const ScanLaunch &l, const FloatRows &fr, const void *rows, u
     static const int per_s = resident_blocks_per_cu(k_scan_float_small<DT>, 4);
     const int ny = 1 + (l.R > 8) + (l.R > 16);
     hipExtLaunchKernelGGL((k_scan_float_small<DT>), dim3(capped(cu_count() * per_s, l.N), ny), dim3(256), 0, l.st, l.e_start, l.R <= 32 ? e_stop : (hipEvent_t) nullptr, 0, G, rowbytes, fr,
-                          l.R, l.keys, l.deg, l.lists, l.props, l.nprop, l.c, l.R > 32 && l.R <= 96 ? l.round : -1);
+                          l.R, l.keys, l.deg, l.lists, l.props, l.nprop, l.c, l.round);
     if (l.R <= 32) return;
     static const int per5 = resident_blocks_per_cu(k_scan_float_all<DT, 5, 3>, 2), per6 = resident_blocks_per_cu(k_scan_float_all<DT, 6, 3>, 1);
     if (l.R <= 96)

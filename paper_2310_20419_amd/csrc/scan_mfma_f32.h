@@ -1,4 +1,4 @@
-// UpdateNeighbors scan (Alg. 4, the body of the vertex loop) for whole float32 rows on the matrix cores, and in double precision for all float rows.
+// UpdateNeighbors scan (Alg. 4, the body of the vertex loop) in groups of 16 rows: whole float32 rows and 16-bit rows in single precision, all float rows in double.
 //
 // One wavefront owns one vertex u with m <= 16*NRC list entries, handled as NRC groups of 16 rows.
 // The rows are streamed through registers 16 dimensions (64 bytes per row) at a time: lane l loads 4
@@ -93,6 +93,26 @@ template <int DT> struct ChunkCoords { static constexpr int n = (DT == DT_F16 ||
 template <int NR, int CH, u32 TM, int DT, typename ACC, typename NRT>
 __device__ __forceinline__ void gram_chunk(const uint4 (&x)[NR][CH], ACC (&acc)[NR * (NR + 1) / 2], NRT (&nr)[NR], u32 need)
 {
+    if constexpr (sizeof(acc[0][0]) == 4 && (DT == DT_F16 || DT == DT_BF16)) {
+        // 16-bit rows, single-precision form: the 16 bytes a lane holds are 8 coordinates in the operand format of
+        // v_mfma_f32_16x16x32_{f16,bf16} as they are (products of two such numbers are exact in float); the norms
+        // come from the diagonal tiles afterwards, so `need` includes those
+#pragma unroll
+        for (int j = 0; j < CH; ++j)
+#pragma unroll
+            for (int I = 0; I < NR; ++I)
+#pragma unroll
+                for (int J = 0; J <= I; ++J)
+                    if (TM ? ((TM >> (I * (I + 1) / 2 + J)) & 1u) != 0 : ((need >> (I * (I + 1) / 2 + J)) & 1u) != 0) {   // wave-uniform
+                        if constexpr (DT == DT_F16)
+                            acc[I * (I + 1) / 2 + J] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                                __builtin_bit_cast(v8h, x[I][j]), __builtin_bit_cast(v8h, x[J][j]), acc[I * (I + 1) / 2 + J], 0, 0, 0);
+                        else
+                            acc[I * (I + 1) / 2 + J] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                __builtin_bit_cast(v8bf, x[I][j]), __builtin_bit_cast(v8bf, x[J][j]), acc[I * (I + 1) / 2 + J], 0, 0, 0);
+                    }
+        return;
+    }
 #pragma unroll
     for (int j = 0; j < CH; ++j)
 #pragma unroll
@@ -235,7 +255,7 @@ __device__ __forceinline__ int popc_below_w(u64 m0, u64 m1, int p)
 // degree class family; CH = 64-byte chunks of every row fetched per loop iteration (rows a multiple of
 // 64 CH bytes: a longer iteration gives the prefetch more matrix work to hide behind); DT = DT_F32 or
 // DT_F16 / DT_BF16 (16-bit storage of the same kind of rows).
-// FAST: the Gram block of float32 rows in single precision (gram_f32_loop).  A pair is then decided only if the outcome of
+// FAST: the Gram block in single precision (gram_f32_loop).  A pair is then decided only if the outcome of
 // the prune test is beyond the error bound of that block, eps_ij = (1.5 d + 20) 2^-24 (n_i + n_j), which
 // covers the accumulation of G (2 x 1.01 d 2^-24 sqrt(n_i n_j) <= 1.01 d 2^-24 (n_i + n_j)), the norms summed
 // in float (d / 4 + 2 roundings per norm), the evaluation of n_i + n_j - 2 G_ij in float and the roundings
@@ -253,6 +273,12 @@ __device__ __forceinline__ int popc_below_w(u64 m0, u64 m1, int p)
 // with every pair resolved, 8.2 pair by pair, around 10^6 (few pairs each) 4.6 and 7.0.
 // (Without the bound 8,319 of 20,000 lists differed from the exact decisions for 100 coordinates of unit variance around
 // 10^6, 6,889 where every row occurs 100 times.)
+// FAST with 16-bit rows: the block comes from v_mfma_f32_16x16x32_{f16,bf16} on the rows as stored (exact
+// products), norms included (diagonals of the diagonal tiles).  One instruction sums 32 products and the
+// accumulator; taking its error as at most 8 x 2^-24 of the sum of their magnitudes (an in-bounds probe
+// against double precision stays below 2.3 x 2^-24 per instruction, also for operands spread over 20
+// binades, and shows that subnormal halves count), G and either norm are off by at most
+// (d / 4) 2^-24 of sqrt(n_i n_j) resp. n, hence eps_ij = (0.5 d + 20) 2^-24 (n_i + n_j).
 // Both: what falls below the smallest normal number, 2^-126, may be rounded coarsely or taken as zero, at each of the d
 // products and of the d sums of G and of either norm and in the evaluation, which eps_ij, a share of the norms, does not cover once the
 // norms are that small themselves: (8 d + 8) 2^-126 on top.  (Without it 18,669 of 20,000 lists of 100 coordinates
@@ -267,8 +293,9 @@ __device__ __forceinline__ void f32_scan_body(
     RoundCtr *__restrict__ ctr, int *__restrict__ redo, u32 *__restrict__ n_redo, F32ScanSmem<NRC> &sm, u32 block, u32 nblocks)
 {
     typedef typename GramAcc<FAST>::type acc_t;
-    static_assert(!FAST || DT == DT_F32, "16-bit rows have a scan of their own");
-    const double epsk = (1.5 * (double)d + 20.0) * 5.9604644775390625e-08;
+    // 16-bit rows in the single-precision form: the matrix instruction takes them as they are
+    constexpr bool NATIVE16 = FAST && (DT == DT_F16 || DT == DT_BF16);
+    const double epsk = ((NATIVE16 ? 0.5 : 1.5) * (double)d + 20.0) * 5.9604644775390625e-08;
     const double epsk64 = (2.0 * (double)d + 24.0) * 1.1102230246251565e-16;      // double-precision form
     constexpr int NT = NRC * (NRC + 1) / 2;
     constexpr int NWD = (NRC + 1) / 2;        // 32-bit words of a mask over slots
@@ -352,14 +379,23 @@ __device__ __forceinline__ void f32_scan_body(
                 for (int J = 0; J <= I; ++J)
                     if (16 * I < m && J < g_new) need |= 1u << (I * (I + 1) / 2 + J);
             need = (u32)__builtin_amdgcn_readfirstlane((int)need);
+            // the tiles the Gram loop computes: those, and for 16-bit rows in the single-precision form the diagonal
+            // tile of every group in use (its diagonal is the group's norms)
+            u32 need_g = need;
+            if constexpr (NATIVE16) {
+#pragma unroll
+                for (int I = 0; I < NRC; ++I)
+                    if (16 * I < m) need_g |= 1u << (I * (I + 1) / 2 + I);
+                need_g = (u32)__builtin_amdgcn_readfirstlane((int)need_g);
+            }
             if constexpr (FAST) {
                 if (NRC == 1) {
-                    gram_f32_loop<NRC, CH, 1u, DT>(rp, nchunk, acc, nr, need);
+                    gram_f32_loop<NRC, CH, 1u, DT>(rp, nchunk, acc, nr, need_g);
                 } else if (NRC == 2) {
-                    if (need == 7u) gram_f32_loop<NRC, CH, 7u, DT>(rp, nchunk, acc, nr, need);
-                    else gram_f32_loop<NRC, CH, 3u, DT>(rp, nchunk, acc, nr, need);
+                    if (NATIVE16 || need == 7u) gram_f32_loop<NRC, CH, 7u, DT>(rp, nchunk, acc, nr, need_g);
+                    else gram_f32_loop<NRC, CH, 3u, DT>(rp, nchunk, acc, nr, need_g);
                 } else {
-                    gram_f32_loop<NRC, CH, 0u, DT>(rp, nchunk, acc, nr, need);
+                    gram_f32_loop<NRC, CH, 0u, DT>(rp, nchunk, acc, nr, need_g);
                 }
             } else {
                 if (NRC == 1) {
@@ -375,8 +411,16 @@ __device__ __forceinline__ void f32_scan_body(
             }
 #pragma unroll
             for (int g = 0; g < NRC; ++g) {
-                nr[g] += __shfl_xor(nr[g], 16);
-                nr[g] += __shfl_xor(nr[g], 32);     // n of slot 16 g + r16, in all four quarter-waves
+                if constexpr (NATIVE16) {
+                    // entry (i, i) of the group's diagonal tile sits in lane (r16 = i, q = i / 4), accumulator i % 4
+                    const v4f dt = acc[g * (g + 1) / 2 + g];
+                    const int vs = r16 & 3;
+                    const float dv = vs == 0 ? dt[0] : vs == 1 ? dt[1] : vs == 2 ? dt[2] : dt[3];
+                    nr[g] = __shfl(dv, r16 + 16 * (r16 >> 2));
+                } else {
+                    nr[g] += __shfl_xor(nr[g], 16);
+                    nr[g] += __shfl_xor(nr[g], 32);     // n of slot 16 g + r16, in all four quarter-waves
+                }
                 // all four quarter-waves hold the same sum and store it (no branch)
                 if (FAST) sm.nrmf[16 * g + r16] = (float)nr[g];
                 else sm.nrm[16 * g + r16] = (double)nr[g];
@@ -404,7 +448,7 @@ __device__ __forceinline__ void f32_scan_body(
                 for (int J = 0; J <= I; ++J) {
                     const int t = I * (I + 1) / 2 + J;
                     FA[t] = FB[t] = 0;
-                    if (NRC == 1 || (NRC == 2 && need != 7u && t < 2) || ((need >> t) & 1u)) tiles += 1;   // what the loop above computed
+                    if (NRC == 1 || (NRC == 2 && (NATIVE16 || (need != 7u && t < 2))) || ((need_g >> t) & 1u)) tiles += 1;   // what the loop above computed
                     if ((need >> t) & 1u) {     // wave-uniform
                         // lane = slot r16 of group J; accumulator v = slot 4v + q of group I (4q + v in the
                         // single-precision instruction).  Low half of a word: the test fires; high half: undecided.

@@ -26,14 +26,52 @@ def rows(kind, N, d, seed=1):
     X = normal(64, d)[torch.randint(0, 64, (N,), device="cuda", generator=g)] + 0.5 * normal(N, d)
     if kind == "unit":
         X = X / X.norm(dim=1, keepdim=True)
+    elif kind == "far":      # far from the origin, next to the distances
+        X = X + 200
+    elif kind == "sizes":    # norms over twelve binades
+        X = X * torch.exp2(torch.randint(-6, 7, (N, 1), device="cuda", generator=g).float())
     return X.contiguous()
 
 
-@pytest.mark.parametrize("n,d", [(20_000, 96), (70_000, 100), (140_000, 64)])
-def test_rows_that_need_groups_get_them(rn, n, d):
-    st = rn.rnnd_build_ex(rows("tight", n, d), 20, 96, 2, 4, 3)[3]
-    assert 1 <= st.group_scans <= 7
-    assert rn.rnnd_build_ex(rows("plain", n, d), 20, 96, 2, 4, 3)[3].group_scans == 0
+def DTYPES():
+    import torch
+    return {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
+
+
+def builds(rn, X, R):
+    """The statistics of a synchronous build and of one in four runs per pass, both checked against the pair-at-a-time kernel."""
+    import torch
+    S, out = min(20, R // 2), []
+    for f in (lambda: rn.rnnd_build_ex(X, S, R, 2, 4, 3), lambda: rn.rnnd_build_blocks(X, S, R, 2, 4, 3, 4)):
+        got = f()
+        try:
+            rn.rnnd_set_kernel_variant(1)
+            want = f()
+        finally:
+            rn.rnnd_set_kernel_variant(0)
+        used = torch.arange(R, device="cuda")[None, :] < want[1][:, None]
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and torch.equal(got[2][used], want[2][used])
+        assert list(got[3].algo_evals[:8]) == list(want[3].algo_evals[:8]) and want[3].group_scans == 0
+        out.append(got[3])
+    return out
+
+
+@pytest.mark.parametrize("R", [32, 96, 128])
+@pytest.mark.parametrize("kind,dtype", [("tight", "f32"), ("sizes", "f32"), ("far", "f16"), ("sizes", "f16"), ("far", "bf16"), ("sizes", "bf16")])
+@pytest.mark.parametrize("n,d", [(20_000, 96), (70_000, 160), (140_000, 64)])
+def test_rows_that_need_groups_get_them(rn, n, d, kind, dtype, R):
+    """Launches of every width: lists of up to 32, 96 and 128 entries, all classes in one launch (R = 96, 65,536 vertices) and in
+    two, undecided vertices redone in the scatter (131,072 vertices) and in launches of their own."""
+    X = rows(kind, n, d).to(DTYPES()[dtype])
+    whole, blocks = builds(rn, X, R)
+    assert 1 <= whole.group_scans <= 8 and 1 <= blocks.group_scans <= 32
+
+
+@pytest.mark.parametrize("R", [32, 96, 128])
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+def test_ordinary_rows_stay_with_the_tiles(rn, dtype, R):
+    for kind in ("plain", "unit"):
+        assert [s.group_scans for s in builds(rn, rows(kind, 20_000, 96).to(DTYPES()[dtype]), R)] == [0, 0]
 
 
 @pytest.mark.parametrize("n,d,R", [(1_200, 96, 96), (2_000, 96, 96), (5_000, 33, 48), (20_000, 96, 96)])
