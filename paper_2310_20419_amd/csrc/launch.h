@@ -52,17 +52,17 @@ struct ScanLaunch {
     Prop *props;
     int *nprop;
     RoundCtr *c;
-    int *redo;                  // [2 * N]
+    int *redo;                  // [2 * N] vertices that a first form leaves to another
     hipStream_t st;
     hipEvent_t e_start, e_stop;
     int round;                  // 0: no round before it in this call's counters
     long long vertices;         // of the round or run
-    bool last;                  // launch_float_scan: no scan launch follows it (it carries e_stop)
+    u32 enough;                 // active vertices from which a round decides about the form of the next
 };
 
 // float32 rows by degree classes 0 .. 6, single precision
 void launch_f32_scan(const ScanLaunch &l);
-// the double-precision form: the redo list (lists of up to 96 entries), or every class (R <= 96: e_stop after the last)
+// the double-precision form: l.redo[0 .. c->n_redo), or every class (R <= 96: e_stop after the last)
 void launch_f64_redo(const ScanLaunch &l, int dtype);
 void launch_f64_classes(const ScanLaunch &l, int dtype);
 // 16-bit rows, or the half-precision copy of float32 rows, by degree classes 0 .. 5

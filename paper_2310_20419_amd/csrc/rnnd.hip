@@ -104,10 +104,15 @@ __global__ __launch_bounds__(BLOCK) void k_random_graph(const void *X, long long
 
 // ------------------------------------------------- UpdateNeighbors: scan (generic kernel)
 // The body of Alg. 4's vertex loop (scan_vertex_pairs) for one vertex per wavefront.
+struct WorkList {
+    const int *list;
+    const u32 *n;
+    const int *list2 = nullptr;      // the list instead of it where *second is not 0
+    const u32 *n2 = nullptr, *second = nullptr;
+};
 template <int DT>
 __global__ __launch_bounds__(BLOCK) void k_update_scan(const void *X, int d, int vec_ok, int R,
-                                                       u64 *keys, int *deg, const int *list,
-                                                       const u32 *n_list, Prop *props, int *nprop,
+                                                       u64 *keys, int *deg, WorkList work, Prop *props, int *nprop,
                                                        RoundCtr *ctr)
 {
     __shared__ u64 s_key[WAVES_PER_BLOCK][RNND_MAX_R];
@@ -115,7 +120,9 @@ __global__ __launch_bounds__(BLOCK) void k_update_scan(const void *X, int d, int
     __shared__ u32 s_ptgt[WAVES_PER_BLOCK][RNND_MAX_R];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const u32 gw = blockIdx.x * WAVES_PER_BLOCK + wave, nw = gridDim.x * WAVES_PER_BLOCK;
-    const u32 n_active = *n_list;
+    const bool second = work.second && *work.second != 0u;
+    const int *list = second ? work.list2 : work.list;
+    const u32 n_active = second ? *work.n2 : *work.n;
     stamp_scan_start(ctr);
     u64 evals_algo = 0, evals_exec = 0, rows = 0, nprops_total = 0;
     for (u32 it = gw; it < n_active; it += nw) {
@@ -329,8 +336,8 @@ __device__ __forceinline__ u64 close_keys(u64 key, int x, bool have, OpenEdges *
 // group that share a target take their arrival numbers with one atomic (a vertex usually redirects
 // several entries to the same kept neighbour).  Arrivals below round_inbox(R) go to the target's inbox, later ones onto
 // one of its lists (see LATE_LISTS).
-__device__ __forceinline__ void scatter_lists(long long N, int R, const int *lists, int ncl, RoundCtr *ctr,
-                                                   Prop *props, const int *nprop, int *fill, u64 *inbox, LateHeads heads)
+__global__ __launch_bounds__(BLOCK) void k_scatter(long long N, int R, const int *lists, int ncl, RoundCtr *ctr,
+                                                   Prop *props, const int *nprop, int *fill, u64 *inbox, LateHeads heads, u32 enough)
 {
     const int cap = round_inbox(R);
     const int lane = threadIdx.x & 63, sub = lane & 15, gbase = lane & ~15;
@@ -339,6 +346,7 @@ __device__ __forceinline__ void scatter_lists(long long N, int R, const int *lis
     const ActiveLists al = active_lists(lists, N, ctr, ncl);
     const u32 n = al.start[NDEG];
     if (n < RNND_MAX_SLOTS) stamp_scan_stop(ctr);      // (always: the clock is read once the scan's counters are here)
+    if (enough && blockIdx.x == 0 && threadIdx.x == 0) decide_next_form(ctr, n, enough);
     if (g >= n) return;
     // the loads of the next vertex (its count and its first 16 edges) are issued before the atomics
     // of the current one; the list entry of the vertex after that is fetched one trip earlier still
@@ -387,57 +395,6 @@ __device__ __forceinline__ void scatter_lists(long long N, int R, const int *lis
         u = u_next; np = np_next; pr0 = pr_next;
         u_next = u_after;
     }
-}
-
-__global__ __launch_bounds__(BLOCK) void k_scatter(long long N, int R, const int *lists, int ncl, RoundCtr *ctr,
-                                                   Prop *props, const int *nprop, int *fill, u64 *inbox, LateHeads heads)
-{
-    scatter_lists(N, R, lists, ncl, ctr, props, nprop, fill, inbox, heads);
-}
-
-// The same where the float scan's redo lists have no launch of their own: their vertices, which have no edges to scatter
-// yet, are scanned pair by pair here and their edges scattered by the same wavefront.  For inputs whose rounds wait for launches: an
-// empty one of the double-precision form is 3.7 us.  (It scans many such vertices faster, and this kernel's registers
-// halve the scatter's occupancy, so larger inputs keep the two apart.)
-template <int DT>
-__global__ __launch_bounds__(BLOCK) void k_scatter_redo(long long N, int R, const int *lists, int ncl, RoundCtr *ctr,
-                                                        Prop *props, const int *nprop, int *fill, u64 *inbox, LateHeads heads,
-                                                        const int *redo, u64 *keys, int *deg, const void *X, int d, int vec_ok)
-{
-    __shared__ u64 s_key[WAVES_PER_BLOCK][RNND_MAX_R];
-    __shared__ u64 s_pkey[WAVES_PER_BLOCK][RNND_MAX_R];
-    __shared__ u32 s_ptgt[WAVES_PER_BLOCK][RNND_MAX_R];
-    __shared__ int s_np[WAVES_PER_BLOCK];
-    const u32 n0 = ctr->n_redo[0], n = n0 + ctr->n_redo[1];
-    if (n) {
-        const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, cap = round_inbox(R);
-        u64 evals_algo = 0, evals_exec = 0, rows = 0, edges = 0;
-        for (u32 it = blockIdx.x * WAVES_PER_BLOCK + wave; it < n; it += gridDim.x * WAVES_PER_BLOCK) {
-            const int u = redo[it < n0 ? (size_t)it : (size_t)N + (it - n0)];
-            int m = deg[u];
-            if (m > R) m = R;
-            u64 *row = keys + (size_t)u * R;
-            const u64 k0 = lane < m ? row[lane] : KEY_PAD, k1 = lane + 64 < m ? row[lane + 64] : KEY_PAD;
-            const int np = scan_vertex_pairs<DT>(X, d, vec_ok, R, u, m, k0, k1, row, deg, props, &s_np[wave], s_key[wave], s_pkey[wave],
-                                                 s_ptgt[wave], lane, evals_algo, evals_exec);
-            rows += m;
-            for (int p = lane; p < np; p += 64) {
-                const u32 tgt = s_ptgt[wave][p];
-                const int s = atomicAdd(&fill[tgt], 1);
-                if (s < cap) {
-                    inbox[(size_t)tgt * INBOX_CAP + s] = s_pkey[wave][p];
-                } else {
-                    const size_t slot = (size_t)u * R + p;      // emit_redirect has put the edge there
-                    props[slot].next = atomicExch(&heads.base[(size_t)tgt * heads.stride + ((u32)(s - cap) & (LATE_LISTS - 1u))], (u32)slot);
-                }
-                ++edges;
-            }
-            wave_sync();
-        }
-        for (int o = 32; o > 0; o >>= 1) edges += shfl_xor_u64(edges, o);
-        if (lane == 0 && rows) add_round_stats(ctr, evals_algo, evals_exec, rows, edges);
-    }
-    scatter_lists(N, R, lists, ncl, ctr, props, nprop, fill, inbox, heads);
 }
 
 // Computes the open distances of the late edges of vertex x; each group of 8 lanes of the block walks its share of the lists.
@@ -1923,21 +1880,21 @@ static void launch_mfma_scan_classes(const Workspace &w, int d, int R, u64 *keys
 
 template <int DT>
 static void launch_generic_scan_dt(const Workspace &w, const void *X, int d, int vec_ok, int R, u64 *keys, int *deg, long long N,
-                                   const int *list, const u32 *n_list, unsigned blocks, RoundCtr *c, hipStream_t st, hipEvent_t e_start, hipEvent_t e_stop)
+                                   const WorkList &work, unsigned blocks, RoundCtr *c, hipStream_t st, hipEvent_t e_start, hipEvent_t e_stop)
 {
     hipExtLaunchKernelGGL(k_update_scan<DT>, dim3(blocks), dim3(BLOCK), 0, st, e_start, e_stop, 0, X, d, vec_ok, R, keys, deg,
-                          list, n_list, w.props, w.nprop, c);
+                          work, w.props, w.nprop, c);
 }
 
 // The generic scan over one list.
 static void launch_generic_scan(const Workspace &w, const void *X, int d, int dtype, int vec_ok, int R, u64 *keys, int *deg,
-                                long long N, const int *list, const u32 *n_list, unsigned blocks, RoundCtr *c, hipStream_t st, hipEvent_t e_start,
+                                long long N, const WorkList &work, unsigned blocks, RoundCtr *c, hipStream_t st, hipEvent_t e_start,
                                 hipEvent_t e_stop)
 {
-    if (dtype == RNND_U8) launch_generic_scan_dt<DT_U8>(w, X, d, vec_ok, R, keys, deg, N, list, n_list, blocks, c, st, e_start, e_stop);
-    else if (dtype == RNND_F16) launch_generic_scan_dt<DT_F16>(w, X, d, vec_ok, R, keys, deg, N, list, n_list, blocks, c, st, e_start, e_stop);
-    else if (dtype == RNND_BF16) launch_generic_scan_dt<DT_BF16>(w, X, d, vec_ok, R, keys, deg, N, list, n_list, blocks, c, st, e_start, e_stop);
-    else launch_generic_scan_dt<DT_F32>(w, X, d, vec_ok, R, keys, deg, N, list, n_list, blocks, c, st, e_start, e_stop);
+    if (dtype == RNND_U8) launch_generic_scan_dt<DT_U8>(w, X, d, vec_ok, R, keys, deg, N, work, blocks, c, st, e_start, e_stop);
+    else if (dtype == RNND_F16) launch_generic_scan_dt<DT_F16>(w, X, d, vec_ok, R, keys, deg, N, work, blocks, c, st, e_start, e_stop);
+    else if (dtype == RNND_BF16) launch_generic_scan_dt<DT_BF16>(w, X, d, vec_ok, R, keys, deg, N, work, blocks, c, st, e_start, e_stop);
+    else launch_generic_scan_dt<DT_F32>(w, X, d, vec_ok, R, keys, deg, N, work, blocks, c, st, e_start, e_stop);
 }
 
 // dt (here and below): the type of the rows that open distances are computed from, DT_U8 where none are open
@@ -1986,22 +1943,6 @@ static void launch_merge_blocks(int dt, hipStream_t st, long long N, int R, cons
     const auto go = dt == RNND_F32 ? launch_merge_blocks_dt<DT_F32> : dt == RNND_F16 ? launch_merge_blocks_dt<DT_F16> : dt == RNND_BF16 ? launch_merge_blocks_dt<DT_BF16> : launch_merge_blocks_dt<DT_U8>;
     go(st, N, R, w, keys, deg, use_classes, c, X, d);
 }
-// 60-round builds with a launch of its own for the redo lists / without, ms: 1,000 x 96 float32 1.08 / 1.00, 20,000 x 96 2.88 / 2.82, 100,000
-// x 96 10.06 / 9.86, 100,000 x 304 19.16 / 19.12, 20,000 x 128 bfloat16 2.82 / 2.75, 20,000 x 320 float16 4.98 / 4.75.
-#define REDO_IN_SCATTER_MAX_N 131072
-template <int DT>
-static void launch_scatter_redo_dt(unsigned blocks, hipStream_t st, long long N, int R, const Workspace &w, int ncl, RoundCtr *c, u64 *keys, int *deg,
-                                   const void *X, int d, int vec_ok)
-{
-    hipLaunchKernelGGL(k_scatter_redo<DT>, dim3(blocks), dim3(BLOCK), 0, st, N, R, w.lists, ncl, c, w.props, (const int *)w.nprop, w.fill, w.inbox,
-                       late_heads(w.inbox, w.bins, R), (const int *)w.touched, keys, deg, X, d, vec_ok);
-}
-static void launch_scatter_redo(int dt, unsigned blocks, hipStream_t st, long long N, int R, const Workspace &w, int ncl, RoundCtr *c, u64 *keys, int *deg,
-                                const void *X, int d, int vec_ok)
-{
-    const auto go = dt == RNND_F32 ? launch_scatter_redo_dt<DT_F32> : dt == RNND_F16 ? launch_scatter_redo_dt<DT_F16> : launch_scatter_redo_dt<DT_BF16>;
-    go(blocks, st, N, R, w, ncl, c, keys, deg, X, d, vec_ok);
-}
 static void launch_merge(int dt, hipStream_t st, long long N, int R, const Workspace &w, u64 *keys, int *deg, int use_classes, RoundCtr *c, const void *X, int d)
 {
     const auto go = dt == RNND_F32 ? launch_merge_dt<DT_F32> : dt == RNND_F16 ? launch_merge_dt<DT_F16> : dt == RNND_BF16 ? launch_merge_dt<DT_BF16> : launch_merge_dt<DT_U8>;
@@ -2012,6 +1953,10 @@ static void launch_merge(int dt, hipStream_t st, long long N, int R, const Works
 struct VertexRun {
     u32 first = 0, count = 0;
 };
+
+// A round of fewer active vertices than this, or than a sixteenth of all, does not decide which form the float scan of the next
+// one takes (see decide_next_form): 32 sampled wavefronts.
+#define DECIDE_MIN_ACTIVE 1024u
 
 // One synchronous round over the active lists of counter slot t (run == nullptr), or one run of a
 // block-sequential pass: the run's active lists are taken from vcls[] first, and the classes of the
@@ -2027,7 +1972,8 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
     const int d = variant == 2 ? plan.dp : rv.d, vec_ok = rv.vec_ok;
     RoundCtr *c = w.ctr + t;
     const int open_dt = variant == 3 && use_classes == 2 ? dtype : RNND_U8;      // whose redirected edges come without distances
-    const bool redo_in_scatter = open_dt != RNND_U8 && !run && N <= REDO_IN_SCATTER_MAX_N;
+    const long long vertices = run ? (long long)run->count : N;
+    const u32 enough = vertices / 16 > DECIDE_MIN_ACTIVE ? (u32)(vertices / 16) : DECIDE_MIN_ACTIVE;
     if (run) {
         const unsigned cb = (run->count + 1023u) / 1024u;
         hipLaunchKernelGGL(k_compact_classes, dim3(cb < 256u ? cb : 256u, 1), dim3(1024), 0, st, (const u32 *)nullptr,
@@ -2041,15 +1987,15 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
         else launch_mfma_scan_classes<0>(w, d, R, keys, deg, N, c, st, re);
     } else if (variant == 3) {
         const bool generic_tail = R > 96;
-        ScanLaunch l = {X, d, R, keys, deg, N, w.lists, w.props, w.nprop, c, w.touched, st, re.scan_start, generic_tail && !redo_in_scatter ? (hipEvent_t) nullptr : re.scan_stop, t, run ? (long long)run->count : N, redo_in_scatter};
+        ScanLaunch l = {X, d, R, keys, deg, N, w.lists, w.props, w.nprop, c, w.touched, st, re.scan_start,
+                        generic_tail ? (hipEvent_t) nullptr : re.scan_stop, t, vertices, enough};
         if (use_classes == 2) {
-            // lists of up to 128 entries; what the redo list of the longest holds goes to the generic kernel
+            // lists of up to 128 entries; the generic kernel takes what the scan leaves of the longest, all of them where it takes groups
             const bool copy = rv.half.rows != nullptr;
             launch_float_scan(l, dtype, copy ? rv.half.rows : X, copy ? rv.half.rowbytes : (u32)(d * dt_size(dtype)), rv.half.par);
-            if (!redo_in_scatter) {
-                launch_f64_redo(l, dtype);
-                if (generic_tail) launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, l.redo + N, &c->n_redo[1], pb, c, st, nullptr, re.scan_stop);
-            }
+            if (generic_tail)
+                launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, WorkList{l.redo, &c->n_redo, w.lists + (size_t)5 * N, &c->n_active[5], &c->groups}, pb, c, st,
+                                    nullptr, re.scan_stop);
         } else {
             // degree classes 0..6: lists of at most 8, 16, 32, 48, 64, 80, 96 entries = 1, 1, 2, 3, 4, 5, 6 groups of 16
             // rows; class 7 (97..128 entries: too many accumulator tiles) goes to the generic kernel
@@ -2059,17 +2005,15 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
             } else {
                 launch_f64_classes(l, dtype);
             }
-            if (generic_tail) launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, w.lists + (size_t)7 * N, &c->n_active[7], pb, c, st, nullptr, re.scan_stop);
+            if (generic_tail) launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, WorkList{w.lists + (size_t)7 * N, &c->n_active[7]}, pb, c, st, nullptr, re.scan_stop);
         }
     } else {
-        launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, w.lists, &c->n_active[0], pb, c, st, re.scan_start, re.scan_stop);
+        launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, WorkList{w.lists, &c->n_active[0]}, pb, c, st, re.scan_start, re.scan_stop);
     }
     // from here on `fill` plays the role of the per-target count of this round
     const int ncl = use_classes ? NDEG : 1;
-    if (redo_in_scatter) launch_scatter_redo(open_dt, pb, st, N, R, w, ncl, c, keys, deg, X, d, vec_ok);
-    else
-        hipLaunchKernelGGL(k_scatter, dim3(pb), dim3(BLOCK), 0, st, N, R, w.lists, ncl, c, w.props, (const int *)w.nprop, w.fill,
-                       w.inbox, late_heads(w.inbox, w.bins, R));
+    hipLaunchKernelGGL(k_scatter, dim3(pb), dim3(BLOCK), 0, st, N, R, w.lists, ncl, c, w.props, (const int *)w.nprop, w.fill,
+                       w.inbox, late_heads(w.inbox, w.bins, R), open_dt != RNND_U8 ? enough : 0u);
     if (!run && !re.round_stop && N <= MERGE_BLOCKS_MAX_N) {
         launch_merge_blocks(open_dt, st, N, R, w, keys, deg, use_classes, c, X, d);
         return hipGetLastError();

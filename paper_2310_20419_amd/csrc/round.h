@@ -13,12 +13,13 @@
 #define STAT_SLOTS 64
 struct RoundCtr {
     u32 n_active[NDEG];   // lengths of this round's active lists
+    u32 groups;           // float scan: this round (or run) takes groups of 16 rows instead of tiles (see group_form)
+    u32 n_open;           // float scan by tiles: pairs left to the exact distance, by a sample of the wavefronts
     u32 n_touched[NMRG];  // distinct targets of the redirected edges, by size of the merge they need
     u32 nonfinite;        // slot 0: k_prepare_rows met a coordinate that is NaN or infinite
-    u32 n_open;           // float scan by tiles: pairs left to the exact distance, by a sample of the wavefronts
-    u32 groups;           // float scan: this round (or run) takes groups of 16 rows instead of tiles (see group_form)
-    u32 pad;
-    u32 n_redo[NDEG];     // float scan: vertices the single-precision form left to the double-precision one
+    u32 n_redo;           // float scan: vertices the first form leaves to another launch (the double-precision form; R > 96: lists
+                          // of more than 96 entries, the pair-at-a-time kernel)
+    u32 pad[4];
     // ticks of the device's constant-rate clock (0 = not taken): the round's first scan launch starts, its scatter
     // starts (= the scan has ended: launches of one stream run back to back), the round's last kernel has ended
     // (taken by k_stamp after the last round before an AddReverseEdges call or the export, only where statistics
@@ -49,6 +50,27 @@ __device__ __forceinline__ void stamp_scan_start(RoundCtr *ctr)
 __device__ __forceinline__ void stamp_scan_stop(RoundCtr *ctr)
 {
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) ctr->t_scan_stop = wall_clock64();
+}
+
+// Whether a float scan takes its lists in groups of 16 rows, by scan_mfma_f32.h, instead of tiles of 32 on the 16-bit matrix cores: float32
+// rows whole and in single precision, 16-bit rows under the narrower error bound of that form.  Where clusters are tight next to the
+// distances between them, rows differ in size by orders of magnitude, or 16-bit rows lie far from the origin, the tiles leave most
+// pairs to the exact distance.  So once a round has left more than GROUP_OPEN per active vertex (0.3 on the average, 1.1 at most in the
+// builds of this repository's float workloads), the following ones take the other form (block-sequential passes: the following runs).
+// A round decides this only if it has `enough` active vertices: below, the sample is not one (a few lists lie in wavefronts that are all
+// sampled, or none), and the last rounds before an AddReverseEdges call, of a handful of vertices, say nothing about
+// the rounds after it.  The scatter decides, so that the scan, whose first loads everything waits for, has none more.
+#define OPEN_SAMPLE 32u
+#define GROUP_OPEN 6u
+__device__ __forceinline__ void decide_next_form(RoundCtr *ctr, u32 active, u32 enough)
+{
+    if (ctr->groups != 0u || (active >= enough && (u64)ctr->n_open * OPEN_SAMPLE > (u64)GROUP_OPEN * active)) ctr[1].groups = 1u;
+}
+__device__ __forceinline__ bool group_form(RoundCtr *ctr)
+{
+    // (loaded next to the lists' lengths, before the kernel's first store: a trip to memory more costs 2 us in each block, 7 % of a scan of
+    // lists of up to 32 entries at 120,000 x 96)
+    return ctr->groups != 0u;
 }
 
 struct Prop {          // one redirected edge (Alg. 4, the edge update): `key` enters `tgt`'s list

@@ -33,7 +33,7 @@ static void launch_classes(const ScanLaunch &l, hipEvent_t e_start)
     unsigned gx = capped((long long)cu_count() * per_cu, l.N);
     if (gx < 8) gx = 8;      // a block at least for every class
     hipExtLaunchKernelGGL((k_update_scan_mfma_f32_all<NRCMAX, C0, CH>), dim3(gx), dim3(256), 0, l.st, e_start, nullptr, 0,
-                          (const char *)l.X, l.d, l.R, l.keys, l.deg, l.lists, l.N, l.props, l.nprop, l.c, l.redo, &l.c->n_redo[0]);
+                          (const char *)l.X, l.d, l.R, l.keys, l.deg, l.lists, l.N, l.props, l.nprop, l.c, l.redo, &l.c->n_redo);
 }
 
 void launch_f32_scan(const ScanLaunch &l)
@@ -77,7 +77,7 @@ static void launch_f64(const ScanLaunch &l, const int *list, const u32 *n_list, 
 
 void launch_f64_redo(const ScanLaunch &l, int dtype)
 {
-    const u32 *n = &l.c->n_redo[0];
+    const u32 *n = &l.c->n_redo;
     if (dtype == DT_F16) launch_f64<3, 1, 6, DT_F16>(l, l.redo, n, nullptr, l.e_stop);
     else if (dtype == DT_BF16) launch_f64<3, 1, 6, DT_BF16>(l, l.redo, n, nullptr, l.e_stop);
     else launch_f64<3, 1, 6, DT_F32>(l, l.redo, n, nullptr, l.e_stop);

@@ -20,8 +20,8 @@
 //
 // An undecided pair is resolved in double precision only if its outcome can matter: its column may be kept, and no column before it
 // prunes the row for certain; a vertex, or a
-// group of short-list vertices, with more than FLOAT_PAIR_CAP such pairs (ties in bulk) is left as it is and appended to
-// the redo list.  The redirected edges are stored without their delta(v,w): the merge at w computes it (close_keys), where the row
+// group of short-list vertices, with more than FLOAT_PAIR_CAP such pairs (ties in bulk) is left as it is, and scanned by the same
+// wavefront at the end of its walk on double-precision tiles.  The redirected edges are stored without their delta(v,w): the merge at w computes it (close_keys), where the row
 // of w serves every edge w receives, at twice the scan's occupancy and next to a sort that leaves the memory idle.
 //
 // Measured on 60-round builds (scan kernels, ms; against 16-row groups of whole float32 rows, which also computed the redirected
@@ -37,13 +37,13 @@
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 #define FLOAT_PAIR_CAP 256
-#define OPEN_SAMPLE 32u
 
 template <int NG>
 struct alignas(16) FloatScanSmem {
     float gt[NG > 1 ? 1024 * NG : 32 * GT_STRIDE];      // the rows on their way; a diagonal Gram tile; later the undecided pairs: row << 8 | column, then their distances
     float nrm[32 * NG];            // n_j by list position
     int id[32 * NG];               // vertex id by list position
+    int left;                      // see leave_vertex
 };
 
 // The rows of the exact routine and what the tolerance is made of; the same for every vertex of a launch.
@@ -51,11 +51,23 @@ struct FloatRows {
     const char *X;                 // rows of d coordinates, 16-byte pieces
     int d;
     const HalfPar *par;            // float32 rows
-    int *redo;                     // vertices with lists of up to 96 entries, then (N further on) longer ones
-    u32 *n_redo;
+    int *left;                     // [N] see leave_vertex; null: vertices go to `redo` instead
+    int *redo;                     // [N] vertices left to a launch that follows: all, or those with more than 96 entries ...
+    u32 *n_redo;                   // ... and how many
     long long N;
-    u32 enough;                    // active vertices from which a round decides about the form of the next
 };
+
+// The vertices that a wavefront leaves alone (lists of up to 96 entries), to be scanned in double precision at the end of its walk: a
+// chain from the last one to the first through an array by vertex.  Its head is in LDS, so that the walk keeps nothing for it.
+__device__ __forceinline__ void leave_vertex(int u, const FloatRows &fr, int *head, bool first_lane, bool longest)
+{
+    if (longest || !fr.left) {
+        if (first_lane) fr.redo[atomicAdd(fr.n_redo, 1u)] = u;
+    } else if (first_lane) {
+        fr.left[u] = *head;
+        *head = u;
+    }
+}
 
 __device__ __forceinline__ u32 both_halves(u64 b) { return (u32)b | (u32)(b >> 32); }
 
@@ -272,13 +284,6 @@ struct FloatOp {
         return true;
     }
 
-    __device__ __forceinline__ void leave(int u, int m, int *nprop) const
-    {
-        nprop[u] = 0;      // nothing to scatter until it is scanned again (see k_scatter_redo)
-        const int longer = m > 96;
-        fr.redo[(longer ? (size_t)fr.N : 0) + atomicAdd(fr.n_redo + longer, 1u)] = u;
-    }
-
     template <int NG, typename GRAM, typename HOLD>
     __device__ __forceinline__ void list(const ScanItem &cur, const GRAM &gram, FloatScanSmem<NG> &sm, int R, u64 *__restrict__ keys,
                                          int *__restrict__ deg, Prop *__restrict__ props, int *__restrict__ nprop, int lane,
@@ -445,7 +450,7 @@ struct FloatOp {
         }
         hold();     // every store of the trip comes after this point
         if (left) {
-            if (lane == 0) leave(u, m, nprop);
+            leave_vertex(u, fr, &sm.left, lane == 0, NG > 3);
             return;
         }
         ev_lane += ev_all;
@@ -558,7 +563,9 @@ struct FloatOp {
         }
         hold();     // every store of the trip comes after this point
         if (left) {
-            if (leader) leave(u, m, nprop);
+            for (u64 lm = __builtin_amdgcn_ballot_w64(leader); lm; lm &= lm - 1ull) {
+                leave_vertex(__builtin_amdgcn_readlane(u, __builtin_ctzll(lm)), fr, &sm.left, lane == 0, false);
+            }
             return;
         }
         if (pruned) emit_redirect(make_key(OPEN_DIST, key_id(kb), 1u), tgt_id, props + (size_t)u * R + __popc(pm & segmask & below));
@@ -570,114 +577,151 @@ struct FloatOp {
     }
 };
 
-// Whether this round's scan takes the lists in groups of 16 rows, by scan_mfma_f32.h: float32 rows whole and in single precision,
-// 16-bit rows under the narrower error bound of that form.  Where clusters are tight next to the distances between them, rows differ
-// in size by orders of magnitude, or 16-bit rows lie far from the origin, the tiles leave most pairs to the exact distance.  So once
-// a round has left more than GROUP_OPEN per active vertex (0.3 on the average, 1.1 at most in the builds of this repository's float
-// workloads), the following ones take the other form: every block finds the same from the counters of the round before (block-sequential
-// passes: of the run before).  A round decides this only if it has enough active vertices (see launch_float_scan): below, the
-// sample is not one (a few lists lie in wavefronts that are all sampled, or none), and the last rounds before an
-// AddReverseEdges call, of a handful of vertices, say nothing about the rounds after it.
-#define GROUP_OPEN 6
-__device__ __forceinline__ bool group_form(RoundCtr *ctr, int round, u32 enough)
-{
-    bool on = false;
-    if (round > 0) {
-        const RoundCtr *p = ctr - 1;
-        u32 active = 0;
-#pragma unroll
-        for (int k = 0; k < NDEG; ++k) active += p->n_active[k];
-        on = p->groups != 0u || (active >= enough && ((u64)p->n_open * OPEN_SAMPLE > (u64)GROUP_OPEN * active ||
-                                                     (u64)(p->n_redo[0] + p->n_redo[1]) * 16u > active));
-    }
-    if (on && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) ctr->groups = 1u;
-    return on;
-}
-
-// One list of vertices with up to 16 NRC entries each, in groups of 16 rows; entry i < n_first of the list is list[i], the others
-// lie `skip` further on.
-template <int DT, int NG, int NRC, int SMEM>
-__device__ __forceinline__ void group_lists(const FloatRows &fr, int R, u64 *keys, int *deg, const int *list, u32 n_first, size_t skip, u32 n, Prop *props,
-                                            int *nprop, RoundCtr *ctr, char *sm, u32 block, u32 nblocks)
+// This wavefront's vertices of a class, up to 16 NRC entries each, in groups of 16 rows; vertex i of the class is at(i).
+template <int DT, int NG, int NRC, int SMEM, typename AT>
+__device__ __forceinline__ void group_lists(const FloatRows &fr, int R, u64 *keys, int *deg, AT at, u32 gw, u32 nw, int &head, u32 n, Prop *props,
+                                            int *nprop, RoundCtr *ctr, char *sm)
 {
     static_assert(sizeof(F32ScanSmem<NRC>) <= SMEM, "the group form works in the LDS of the tile form");
-    f32_scan_body<NG, 1, NRC, true, DT>(fr.X, fr.d, R, keys, deg, list, n_first, skip, n, props, nprop, ctr, fr.redo, fr.n_redo,
-                                        *reinterpret_cast<F32ScanSmem<NRC> *>(sm), block, nblocks);
+    const bool first_lane = (threadIdx.x & 63) == 0;
+    f32_scan_body<NG, 1, NRC, true, DT>(fr.X, fr.d, R, keys, deg, at, gw, nw, n, props, nprop, ctr,
+                                        [&](int u) {
+                                            if (!fr.left) {
+                                                if (first_lane) fr.redo[atomicAdd(fr.n_redo, 1u)] = u;
+                                            } else {
+                                                if (first_lane) fr.left[u] = head;
+                                                head = u;
+                                            }
+                                        },
+                                        *reinterpret_cast<F32ScanSmem<NRC> *>(sm));
+}
+
+// ... and what it has left, in double precision.
+template <int DT, int NG, int NRC, int SMEM>
+__device__ __forceinline__ void finish_left(const FloatRows &fr, int R, u64 *keys, int *deg, int head, Prop *props, int *nprop, RoundCtr *ctr, char *sm)
+{
+    static_assert(sizeof(F32ScanSmem<NRC>) <= SMEM, "the group form works in the LDS of the tile form");
+    int next = __builtin_amdgcn_readfirstlane(head);
+    if (__builtin_expect(next < 0, 1)) return;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");      // the chain is read by other lanes than wrote it
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    u32 n = 0;
+    for (int u = next; u >= 0; u = fr.left[u]) ++n;
+    f32_scan_body<NG, 1, NRC, false, DT>(fr.X, fr.d, R, keys, deg,
+                                         [&](u32) {      // asked in order
+                                             const int u = next;
+                                             next = fr.left[u];
+                                             return u;
+                                         },
+                                         0, 1, n, props, nprop, ctr, [](int) {},
+                                         *reinterpret_cast<F32ScanSmem<NRC> *>(sm));
 }
 
 // Lists of at most 8, 16, 32 entries (blockIdx.y = degree class): 4, 2, 1 vertices per wavefront.
 template <int DT>
 __global__ __launch_bounds__(256, 4) void k_scan_float_small(
     const int8_t *__restrict__ G, u32 rowbytes, FloatRows fr, int R, u64 *__restrict__ keys, int *__restrict__ deg,
-    const int *__restrict__ lists, Prop *__restrict__ props, int *__restrict__ nprop, RoundCtr *ctr, int round)
+    const int *__restrict__ lists, Prop *__restrict__ props, int *__restrict__ nprop, RoundCtr *ctr)
 {
     typedef FloatOp<DT, DT == DT_F32> OP;
+    constexpr int SMEM = sizeof(FloatScanSmem<1>);
     __shared__ FloatScanSmem<1> smem[4];
-    FloatScanSmem<1> &sm = smem[threadIdx.x >> 6];
-    const int y = blockIdx.y;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    FloatScanSmem<1> &sm = smem[wave];
+    const int y = blockIdx.y, rb = (int)rowbytes;
     const int *list = lists + (size_t)y * fr.N;
     const u32 n = ctr->n_active[y];
-    stamp_scan_start(ctr);
-    if (group_form(ctr, round, fr.enough)) {
-        constexpr int SMEM = sizeof(FloatScanSmem<1>);
-        if (y < 2) group_lists<DT, 1, 1, SMEM>(fr, R, keys, deg, list, n, 0, n, props, nprop, ctr, (char *)&sm, blockIdx.x, gridDim.x);
-        else group_lists<DT, 1, 2, SMEM>(fr, R, keys, deg, list, n, 0, n, props, nprop, ctr, (char *)&sm, blockIdx.x, gridDim.x);
-        return;
-    }
     const OP op(fr, rowbytes);
-    if (y == 0) scan_packed_stream_body<OP, 4>(op, G, (int)rowbytes, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
-    else if (y == 1) scan_packed_stream_body<OP, 2>(op, G, (int)rowbytes, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
-    else scan_packed_stream_body<OP, 1>(op, G, (int)rowbytes, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
-    op.report(ctr);
+    const bool groups = group_form(ctr);
+    stamp_scan_start(ctr);
+    int head = -1;
+    if (__builtin_expect(groups, 0)) {
+        const auto at = [=](u32 i) { return list[i]; };
+        if (y < 2) group_lists<DT, 1, 1, SMEM>(fr, R, keys, deg, at, blockIdx.x * 4 + wave, gridDim.x * 4, head, n, props, nprop, ctr, (char *)&sm);
+        else group_lists<DT, 1, 2, SMEM>(fr, R, keys, deg, at, blockIdx.x * 4 + wave, gridDim.x * 4, head, n, props, nprop, ctr, (char *)&sm);
+    } else {
+        sm.left = -1;
+        wave_sync();
+        if (y == 0) scan_packed_stream_body<OP, 4>(op, G, rb, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
+        else if (y == 1) scan_packed_stream_body<OP, 2>(op, G, rb, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
+        else scan_packed_stream_body<OP, 1>(op, G, rb, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
+        op.report(ctr);
+        head = sm.left;
+    }
+    finish_left<DT, 1, 2, SMEM>(fr, R, keys, deg, head, props, nprop, ctr, (char *)&sm);
 }
 
 // Classes C0 .. NC - 1 in one launch, the grid's blocks divided among them by their work (as k_update_scan_mfma_u8_all).
-template <int DT, int NC, int C0>
+// FINISH: what is left is scanned at the end (see finish_left), else in a launch that follows (fr.left is null).
+template <int DT, int NC, int C0, bool FINISH>
 __global__ __launch_bounds__(256, (NC == 6 ? 1 : 2)) void k_scan_float_all(
     const int8_t *__restrict__ G, u32 rowbytes, FloatRows fr, int R, u64 *__restrict__ keys, int *__restrict__ deg,
-    const int *__restrict__ lists, Prop *__restrict__ props, int *__restrict__ nprop, RoundCtr *ctr, int round)
+    const int *__restrict__ lists, Prop *__restrict__ props, int *__restrict__ nprop, RoundCtr *ctr)
 {
     typedef FloatOp<DT, DT == DT_F32> OP;
-    constexpr int NGMAX = NC - 2;
+    constexpr int NGMAX = NC - 2, SMEM = sizeof(FloatScanSmem<NGMAX>);
     static_assert(NC == 5 || NC == 6, "short lists plus two or three long-list classes");
+    static_assert(C0 == 0 || C0 == 3, "with the short lists or without");
     __shared__ FloatScanSmem<NGMAX> smem[4];
-    if (C0 == 0) stamp_scan_start(ctr);
-    const int wave = threadIdx.x >> 6, rb = (int)rowbytes;
-    const size_t N = (size_t)fr.N;
-    const bool groups = group_form(ctr, round, fr.enough);
-    // (the group form takes lists of up to 96 entries, classes 0 and 1 as one; the longest stay with the tiles)
-    constexpr u32 tile_weight[6] = {6u, 12u, 24u, 46u, 78u, 112u}, group_weight[6] = {16u, 16u, 24u, 44u, 72u, 112u};
-    u32 n[NC], weight[NC];
+    u32 n[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        n[c] = c >= C0 ? ctr->n_active[c] : 0u;
-        weight[c] = groups ? group_weight[c] : tile_weight[c];
-    }
+    for (int c = 0; c < NC; ++c) n[c] = c >= C0 ? ctr->n_active[c] : 0u;
+    const OP op(fr, rowbytes);
+    const bool groups = group_form(ctr);
+    if (C0 == 0) stamp_scan_start(ctr);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rb = (int)rowbytes;
+    const size_t N = (size_t)fr.N;
+    constexpr u32 tile_weight[6] = {6u, 12u, 24u, 46u, 78u, 112u}, group_weight[6] = {16u, 16u, 24u, 44u, 72u, 0u};
+    u32 weight[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) weight[c] = groups ? group_weight[c] : tile_weight[c];
     const u32 n0 = n[0];
-    if (C0 == 0 && groups) n[1] += n0, n[0] = 0u;
+    if (groups) {
+        if (C0 == 0) n[1] += n0, n[0] = 0u;      // classes 0 and 1 as one
+        if (NC > 5) n[NC > 5 ? 5 : 0] = 0u;      // (the group form takes lists of up to 96 entries: see launch_float_scan)
+    }
     u32 block, mine;
     const int cls = share_blocks<NC>(n, weight, block, mine);
     if (cls < 0) return;
-    if (groups && cls < 5) {
-        constexpr int SMEM = sizeof(FloatScanSmem<NGMAX>);
-        char *sm = (char *)&smem[wave];
-        if (C0 == 0 && cls == 1) group_lists<DT, 1, 1, SMEM>(fr, R, keys, deg, lists, n0, N - n0, n[1], props, nprop, ctr, sm, block, mine);
-        else if (C0 == 0 && cls == 2) group_lists<DT, 1, 2, SMEM>(fr, R, keys, deg, lists + 2 * N, n[2], 0, n[2], props, nprop, ctr, sm, block, mine);
-        else if (cls == 3) group_lists<DT, 2, 4, SMEM>(fr, R, keys, deg, lists + 3 * N, n[3], 0, n[3], props, nprop, ctr, sm, block, mine);
-        else group_lists<DT, 3, 6, SMEM>(fr, R, keys, deg, lists + 4 * N, n[4], 0, n[4], props, nprop, ctr, sm, block, mine);
-        return;
+    int head = -1;
+    char *sm = (char *)&smem[wave];
+    if (__builtin_expect(groups, 0)) {
+        const int *list = lists + (size_t)cls * N;
+        const auto at = [=](u32 i) { return list[i]; };
+        if (C0 == 0 && cls == 1)
+            group_lists<DT, 1, 1, SMEM>(fr, R, keys, deg, [=](u32 i) { return i < n0 ? lists[i] : list[i - n0]; }, block * 4 + wave, mine * 4, head, n[1], props, nprop, ctr, sm);
+        else if (C0 == 0 && cls == 2) group_lists<DT, 1, 2, SMEM>(fr, R, keys, deg, at, block * 4 + wave, mine * 4, head, n[2], props, nprop, ctr, sm);
+        else if (cls == 3) group_lists<DT, 2, 4, SMEM>(fr, R, keys, deg, at, block * 4 + wave, mine * 4, head, n[3], props, nprop, ctr, sm);
+        else group_lists<DT, 3, 6, SMEM>(fr, R, keys, deg, at, block * 4 + wave, mine * 4, head, n[4], props, nprop, ctr, sm);
+    } else {
+        const int *list = lists + (size_t)cls * N;
+        FloatScanSmem<1> &sm1 = *reinterpret_cast<FloatScanSmem<1> *>(sm);
+        if (C0 == 0 && cls < 3) {
+            sm1.left = -1;
+            wave_sync();
+            if (cls == 0) scan_packed_stream_body<OP, 4>(op, G, rb, R, keys, deg, list, n[0], props, nprop, ctr, sm1, block, mine);
+            else if (cls == 1) scan_packed_stream_body<OP, 2>(op, G, rb, R, keys, deg, list, n[1], props, nprop, ctr, sm1, block, mine);
+            else scan_packed_stream_body<OP, 1>(op, G, rb, R, keys, deg, list, n[2], props, nprop, ctr, sm1, block, mine);
+            head = sm1.left;
+        } else if (cls == 3) {
+            FloatScanSmem<2> &sm2 = *reinterpret_cast<FloatScanSmem<2> *>(sm);
+            sm2.left = -1;
+            wave_sync();
+            scan_list_stream_body<OP, 2>(op, G, rb, R, keys, deg, list, n[3], props, nprop, ctr, sm2, block, mine);
+            head = sm2.left;
+        } else if (cls == 4) {
+            FloatScanSmem<3> &sm3 = *reinterpret_cast<FloatScanSmem<3> *>(sm);
+            sm3.left = -1;
+            wave_sync();
+            scan_list_stream_body<OP, 3>(op, G, rb, R, keys, deg, list, n[4], props, nprop, ctr, sm3, block, mine);
+            head = sm3.left;
+        } else if (NC > 5 && cls == 5) {
+            scan_list_stream_body<OP, NGMAX>(op, G, rb, R, keys, deg, list, n[NC > 5 ? 5 : 0], props, nprop, ctr, smem[wave], block, mine);
+        }
+        op.report(ctr);
     }
-    const int *list = lists + (size_t)cls * N;
-    const OP op(fr, rowbytes);
-    FloatScanSmem<1> &sm1 = *reinterpret_cast<FloatScanSmem<1> *>(&smem[wave]);
-    if (C0 == 0 && cls == 0) scan_packed_stream_body<OP, 4>(op, G, rb, R, keys, deg, list, n[0], props, nprop, ctr, sm1, block, mine);
-    else if (C0 == 0 && cls == 1) scan_packed_stream_body<OP, 2>(op, G, rb, R, keys, deg, list, n[1], props, nprop, ctr, sm1, block, mine);
-    else if (C0 == 0 && cls == 2) scan_packed_stream_body<OP, 1>(op, G, rb, R, keys, deg, list, n[2], props, nprop, ctr, sm1, block, mine);
-    else if (cls == 3)
-        scan_list_stream_body<OP, 2>(op, G, rb, R, keys, deg, list, n[3], props, nprop, ctr, *reinterpret_cast<FloatScanSmem<2> *>(&smem[wave]), block, mine);
-    else if (cls == 4)
-        scan_list_stream_body<OP, 3>(op, G, rb, R, keys, deg, list, n[4], props, nprop, ctr, *reinterpret_cast<FloatScanSmem<3> *>(&smem[wave]), block, mine);
-    else if (NC > 5 && cls == 5)
-        scan_list_stream_body<OP, NGMAX>(op, G, rb, R, keys, deg, list, n[NC > 5 ? 5 : 0], props, nprop, ctr, smem[wave], block, mine);
-    op.report(ctr);
+    if constexpr (!FINISH) return;
+    if (C0 == 0 && cls < 3) finish_left<DT, 1, 2, SMEM>(fr, R, keys, deg, head, props, nprop, ctr, sm);
+    else if (cls == 3) finish_left<DT, 2, 4, SMEM>(fr, R, keys, deg, head, props, nprop, ctr, sm);
+    else if (cls == 4) finish_left<DT, 3, 6, SMEM>(fr, R, keys, deg, head, props, nprop, ctr, sm);
 }

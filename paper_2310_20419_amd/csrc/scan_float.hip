@@ -10,42 +10,52 @@
 //   R = 128  float32 x 96     20,000 3.73 / 3.82            200,000 22.2 / 29.1     float16 x 320 20,000 4.98 / 5.10
 #define FLOAT_SHARED_MAX_N 65536
 
+// Up to here the vertices that a scan of lists of 33 .. 96 entries leaves are finished by the wavefronts that left them, above by a launch of
+// their own, which has the registers for it (at two wavefronts per SIMD that form spills 200).  float32 200,000 x 100, R = 96, 8
+// rounds, in the scan / in a launch, ms: rows 100 times each 17.7 / 15.4, clusters of radius 0.003 14.5 / 13.4, two places 10^4 apart
+// 24.8 / 24.1; an empty launch is 4.5 us, 3 % of a round at 70,000 x 96.
+#define FINISH_MAX_N 131072
+
 template <int DT>
-static void launch(const ScanLaunch &l, const FloatRows &fr, const void *rows, u32 rowbytes)
+static void launch(const ScanLaunch &l, FloatRows fr, const void *rows, u32 rowbytes)
 {
     const int8_t *G = (const int8_t *)rows;
-    const hipEvent_t e_stop = l.last ? l.e_stop : (hipEvent_t) nullptr;
+    const hipEvent_t e_stop = l.R <= 96 ? l.e_stop : (hipEvent_t) nullptr;      // (else the pair-at-a-time kernel follows)
     auto blocks = [&](int per_cu) {
         const unsigned gx = capped((long long)cu_count() * per_cu, l.N);
         return dim3(gx < 8 ? 8 : gx);      // a block at least for every class
     };
     if (l.R > 32 && l.R <= 96 && l.N <= FLOAT_SHARED_MAX_N) {
-        static const int per_cu = resident_blocks_per_cu(k_scan_float_all<DT, 5, 0>, 2);
-        hipExtLaunchKernelGGL((k_scan_float_all<DT, 5, 0>), blocks(per_cu), dim3(256), 0, l.st, l.e_start, e_stop, 0, G, rowbytes, fr, l.R, l.keys, l.deg,
-                              l.lists, l.props, l.nprop, l.c, l.round);
+        static const int per_cu = resident_blocks_per_cu(k_scan_float_all<DT, 5, 0, true>, 2);
+        hipExtLaunchKernelGGL((k_scan_float_all<DT, 5, 0, true>), blocks(per_cu), dim3(256), 0, l.st, l.e_start, e_stop, 0, G, rowbytes, fr, l.R, l.keys, l.deg,
+                              l.lists, l.props, l.nprop, l.c);
         return;
     }
     static const int per_s = resident_blocks_per_cu(k_scan_float_small<DT>, 4);
     const int ny = 1 + (l.R > 8) + (l.R > 16);
     hipExtLaunchKernelGGL((k_scan_float_small<DT>), dim3(capped(cu_count() * per_s, l.N), ny), dim3(256), 0, l.st, l.e_start, l.R <= 32 ? e_stop : (hipEvent_t) nullptr, 0, G, rowbytes, fr,
-                          l.R, l.keys, l.deg, l.lists, l.props, l.nprop, l.c, l.round);
+                          l.R, l.keys, l.deg, l.lists, l.props, l.nprop, l.c);
     if (l.R <= 32) return;
-    static const int per5 = resident_blocks_per_cu(k_scan_float_all<DT, 5, 3>, 2), per6 = resident_blocks_per_cu(k_scan_float_all<DT, 6, 3>, 1);
-    if (l.R <= 96)
-        hipExtLaunchKernelGGL((k_scan_float_all<DT, 5, 3>), blocks(per5), dim3(256), 0, l.st, nullptr, e_stop, 0, G, rowbytes, fr, l.R, l.keys, l.deg, l.lists,
-                              l.props, l.nprop, l.c, l.round);
-    else
-        hipExtLaunchKernelGGL((k_scan_float_all<DT, 6, 3>), blocks(per6), dim3(256), 0, l.st, nullptr, e_stop, 0, G, rowbytes, fr, l.R, l.keys, l.deg, l.lists,
-                              l.props, l.nprop, l.c, l.round);
+    if (l.R > 96) {
+        static const int per_cu = resident_blocks_per_cu(k_scan_float_all<DT, 6, 3, true>, 1);
+        hipExtLaunchKernelGGL((k_scan_float_all<DT, 6, 3, true>), blocks(per_cu), dim3(256), 0, l.st, nullptr, e_stop, 0, G, rowbytes, fr, l.R, l.keys, l.deg, l.lists,
+                              l.props, l.nprop, l.c);
+    } else if (l.N <= FINISH_MAX_N) {
+        static const int per_cu = resident_blocks_per_cu(k_scan_float_all<DT, 5, 3, true>, 2);
+        hipExtLaunchKernelGGL((k_scan_float_all<DT, 5, 3, true>), blocks(per_cu), dim3(256), 0, l.st, nullptr, e_stop, 0, G, rowbytes, fr, l.R, l.keys, l.deg, l.lists,
+                              l.props, l.nprop, l.c);
+    } else {
+        static const int per_cu = resident_blocks_per_cu(k_scan_float_all<DT, 5, 3, false>, 2);
+        fr.left = nullptr;
+        hipExtLaunchKernelGGL((k_scan_float_all<DT, 5, 3, false>), blocks(per_cu), dim3(256), 0, l.st, nullptr, nullptr, 0, G, rowbytes, fr, l.R, l.keys, l.deg, l.lists,
+                              l.props, l.nprop, l.c);
+        launch_f64_redo(l, DT);
+    }
 }
 
-// A round of fewer active vertices than this does not decide which form the next one takes: 32 sampled wavefronts, or a sixteenth
-// of the vertices.
-#define DECIDE_MIN_ACTIVE 1024
 void launch_float_scan(const ScanLaunch &l, int dtype, const void *rows, u32 rowbytes, const HalfPar *par)
 {
-    const u32 share = (u32)(l.vertices / 16);
-    const FloatRows fr = {(const char *)l.X, l.d, par, l.redo, &l.c->n_redo[0], l.N, share > DECIDE_MIN_ACTIVE ? share : DECIDE_MIN_ACTIVE};
+    const FloatRows fr = {(const char *)l.X, l.d, par, l.redo + l.N, l.redo, &l.c->n_redo, l.N};
     if (dtype == DT_F16) launch<DT_F16>(l, fr, rows, rowbytes);
     else if (dtype == DT_BF16) launch<DT_BF16>(l, fr, rows, rowbytes);
     else launch<DT_F32>(l, fr, rows, rowbytes);

@@ -284,13 +284,13 @@ __device__ __forceinline__ int popc_below_w(u64 m0, u64 m1, int p)
 // norms are that small themselves: (8 d + 8) 2^-126 on top.  (Without it 18,669 of 20,000 lists of 100 coordinates
 // around 1e-22 differed from the exact decisions, 3,487 around 1e-21; the distances themselves are sums in double.)
 //
-// The work list: entries 0 .. n_first - 1 are list[0 ..], entries n_first .. n_active - 1 follow `skip` places further on
-// (a second degree class that the same shape serves).
-template <int NG, int CH, int NRC, bool FAST, int DT>
+// The work list: vertex at(i), i = gw, gw + nw, ... below n_active, is this wavefront's.  FAST: vertices with more undecided pairs than
+// the form resolves are handed to leave(u), by the whole wavefront, with their rows, degrees and counts untouched.
+template <int NG, int CH, int NRC, bool FAST, int DT, typename AT, typename LEAVE>
 __device__ __forceinline__ void f32_scan_body(
     const char *__restrict__ X, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
-    const int *__restrict__ list, u32 n_first, size_t skip, u32 n_active, Prop *__restrict__ props, int *__restrict__ nprop,
-    RoundCtr *__restrict__ ctr, int *__restrict__ redo, u32 *__restrict__ n_redo, F32ScanSmem<NRC> &sm, u32 block, u32 nblocks)
+    AT at, u32 gw, u32 nw, u32 n_active, Prop *__restrict__ props, int *__restrict__ nprop,
+    RoundCtr *__restrict__ ctr, LEAVE leave, F32ScanSmem<NRC> &sm)
 {
     typedef typename GramAcc<FAST>::type acc_t;
     // 16-bit rows in the single-precision form: the matrix instruction takes them as they are
@@ -301,9 +301,8 @@ __device__ __forceinline__ void f32_scan_body(
     constexpr int NWD = (NRC + 1) / 2;        // 32-bit words of a mask over slots
     constexpr int NSET = NRC > 4 ? 2 : 1;     // lane (r16, q) owns rows 16 q + r16 and, if NRC > 4, 64 + 16 q + r16
     static_assert(NRC >= 1 && NRC <= 6 && (NRC == 2 * NG || NRC == 2 * NG - 1), "lists of at most 96 entries");
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63;
     const int r16 = lane & 15, q = lane >> 4, sub = lane & 7, grp = lane >> 3;
-    const u32 gw = block * 4 + wave, nw = nblocks * 4;
     const u32 rowbytes = (u32)d * (u32)dt_size(DT);     // at most a few hundred KB
     const int nchunk = (int)(rowbytes / (64u * CH));
     u64 tiles = 0, rows = 0, nprops_total = 0, pair_evals = 0;
@@ -311,7 +310,7 @@ __device__ __forceinline__ void f32_scan_body(
 
     if (gw >= n_active) return;
     auto vertex_at = [&](unsigned long long i) -> int {
-        return i < n_active ? list[i < n_first ? i : i + skip] : -1;
+        return i < n_active ? at((u32)i) : -1;
     };
     ScanItem cur = scan_item_load<NG>(vertex_at(gw), keys, deg, R, lane);
     ScanItem nxt = scan_item_load<NG>(vertex_at((unsigned long long)gw + nw), keys, deg, R, lane);
@@ -626,10 +625,7 @@ __device__ __forceinline__ void f32_scan_body(
                 if (total > (FAST ? F32_AMB_CAP : F64_AMB_PER_ROW * m)) {
                     defer = true;
                     if (FAST) {
-                        if (lane == 0) {
-                            nprop[u] = 0;      // nothing to scatter until it is scanned again
-                            redo[atomicAdd(n_redo, 1u)] = u;
-                        }
+                        leave(u);
                     } else {
                         u64 ea = 0, ee = 0;
                         nprops_total += scan_vertex_pairs<DT>(X, d, 1, R, u, m, kreg[0], kreg[1], row, deg, props, nprop + u, sm.key,
@@ -817,8 +813,8 @@ __global__ __launch_bounds__(64 * 4, (NRC <= 2 ? 4 : NRC <= 5 ? 2 : 1)) void k_u
     __shared__ F32ScanSmem<NRC> smem[4];
     stamp_scan_start(ctr);
     const u32 n = *n_list;
-    f32_scan_body<NG, CH, NRC, false, DT>(X, d, R, keys, deg, list, n, 0, n, props, nprop, ctr, nullptr, nullptr,
-                                          smem[threadIdx.x >> 6], blockIdx.x, gridDim.x);
+    f32_scan_body<NG, CH, NRC, false, DT>(X, d, R, keys, deg, [=](u32 i) { return list[i]; }, blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4, n, props,
+                                          nprop, ctr, [](int) {}, smem[threadIdx.x >> 6]);
 }
 
 // The single-precision form of the degree classes from C0 on, up to lists of 16 NRCMAX entries, in one launch, the
@@ -856,10 +852,13 @@ __global__ __launch_bounds__(64 * 4, (NRCMAX <= 2 ? 4 : NRCMAX <= 4 ? 3 : 2)) vo
     const int k = share_blocks<NS>(n, weight, block, mine);
     if (k < 0) return;
     const int wave = threadIdx.x >> 6;
+    auto leave = [=](int u) { if ((threadIdx.x & 63) == 0) redo[atomicAdd(n_redo, 1u)] = u; };
+    // (the second class of a shape that serves two follows the first one's)
 #define RNND_F32_SHAPE(K_, NG_, CH_, NRC_)                                                                            \
-    f32_scan_body<NG_, CH_, NRC_, true, DT_F32>(X, d, R, keys, deg, lists + (size_t)first_class[K_] * N, n1[K_],           \
-                                            (size_t)N - n1[K_], n[K_], props, nprop, ctr, redo, n_redo,                \
-                                            *reinterpret_cast<F32ScanSmem<NRC_> *>(&smem[wave]), block, mine)
+    f32_scan_body<NG_, CH_, NRC_, true, DT_F32>(X, d, R, keys, deg,                                                       \
+                                            [=](u32 i) { return lists[(size_t)first_class[K_] * N + (i < n1[K_] ? i : i + ((size_t)N - n1[K_]))]; }, \
+                                            block * 4 + wave, mine * 4, n[K_], props, nprop, ctr, leave,               \
+                                            *reinterpret_cast<F32ScanSmem<NRC_> *>(&smem[wave]))
     if constexpr (C0 == 0)
         if (k == 0) RNND_F32_SHAPE(0, 1, CH, 1);
     if constexpr (NRCMAX >= 2 && C0 <= 2)

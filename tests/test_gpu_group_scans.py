@@ -61,7 +61,7 @@ def builds(rn, X, R):
 @pytest.mark.parametrize("n,d", [(20_000, 96), (70_000, 160), (140_000, 64)])
 def test_rows_that_need_groups_get_them(rn, n, d, kind, dtype, R):
     """Launches of every width: lists of up to 32, 96 and 128 entries, all classes in one launch (R = 96, 65,536 vertices) and in
-    two, undecided vertices redone in the scatter (131,072 vertices) and in launches of their own."""
+    two, vertices with too many undecided pairs finished by the scan (131,072 vertices) and in a launch of their own."""
     X = rows(kind, n, d).to(DTYPES()[dtype])
     whole, blocks = builds(rn, X, R)
     assert 1 <= whole.group_scans <= 8 and 1 <= blocks.group_scans <= 32
