@@ -14,12 +14,13 @@
 struct RoundCtr {
     u32 n_active[NDEG];   // lengths of this round's active lists
     u32 groups;           // float scan: this round (or run) takes groups of 16 rows instead of tiles (see group_form)
+    u32 sample_pairs, sample_open;      // float scan, first round: pairs of a sample of the lists, and those the tiles would leave open
     u32 n_open;           // float scan by tiles: pairs left to the exact distance, by a sample of the wavefronts
     u32 n_touched[NMRG];  // distinct targets of the redirected edges, by size of the merge they need
     u32 nonfinite;        // slot 0: k_prepare_rows met a coordinate that is NaN or infinite
     u32 n_redo;           // float scan: vertices the first form leaves to another launch (the double-precision form; R > 96: lists
                           // of more than 96 entries, the pair-at-a-time kernel)
-    u32 pad[4];
+    u32 pad[2];
     // ticks of the device's constant-rate clock (0 = not taken): the round's first scan launch starts, its scatter
     // starts (= the scan has ended: launches of one stream run back to back), the round's last kernel has ended
     // (taken by k_stamp after the last round before an AddReverseEdges call or the export, only where statistics
@@ -60,8 +61,12 @@ __device__ __forceinline__ void stamp_scan_stop(RoundCtr *ctr)
 // A round decides this only if it has `enough` active vertices: below, the sample is not one (a few lists lie in wavefronts that are all
 // sampled, or none), and the last rounds before an AddReverseEdges call, of a handful of vertices, say nothing about
 // the rounds after it.  The scatter decides, so that the scan, whose first loads everything waits for, has none more.
+// The first round of a call has none before it; it takes groups if more than a GROUP_SHARE-th of the pairs of a sample of its lists
+// (k_float_sample) lie within the tiles' tolerance.
 #define OPEN_SAMPLE 32u
 #define GROUP_OPEN 6u
+#define GROUP_SHARE 12u
+#define SAMPLE_MIN_PAIRS 256u
 __device__ __forceinline__ void decide_next_form(RoundCtr *ctr, u32 active, u32 enough)
 {
     if (ctr->groups != 0u || (active >= enough && (u64)ctr->n_open * OPEN_SAMPLE > (u64)GROUP_OPEN * active)) ctr[1].groups = 1u;
@@ -70,7 +75,10 @@ __device__ __forceinline__ bool group_form(RoundCtr *ctr)
 {
     // (loaded next to the lists' lengths, before the kernel's first store: a trip to memory more costs 2 us in each block, 7 % of a scan of
     // lists of up to 32 entries at 120,000 x 96)
-    return ctr->groups != 0u;
+    const u32 was = ctr->groups, pairs = ctr->sample_pairs, open = ctr->sample_open;
+    const bool on = (was != 0u) | ((pairs >= SAMPLE_MIN_PAIRS) & (open * GROUP_SHARE > pairs));
+    if (on && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) ctr->groups = 1u;
+    return on;
 }
 
 struct Prop {          // one redirected edge (Alg. 4, the edge update): `key` enters `tgt`'s list

@@ -577,6 +577,75 @@ struct FloatOp {
     }
 };
 
+// One wavefront a list: eight pairs of eight of its entries, spread over it, against the tolerance that the tiles would have, 8 lanes a
+// pair.
+#define SAMPLE_BLOCKS 64
+template <int DT>
+__global__ __launch_bounds__(256) void k_float_sample(const char *__restrict__ G, u32 rowbytes, FloatRows fr, int R, const u64 *__restrict__ keys,
+                                                      const int *__restrict__ deg, const int *__restrict__ lists, u32 enough, RoundCtr *ctr)
+{
+    __shared__ u32 s_pairs, s_open;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, grp = lane >> 3, sub = lane & 7;
+    u32 active = 0, below[NDEG];
+#pragma unroll
+    for (int k = 0; k < NDEG; ++k) {
+        below[k] = active;
+        active += ctr->n_active[k];
+    }
+    if (active < enough) return;
+    if (threadIdx.x == 0) s_pairs = s_open = 0u;
+    // a vertex of the active lists, by a multiplicative hash of the wavefront's number
+    const u32 i = (u32)(((u64)((blockIdx.x * 4u + (u32)wave) * 0x9E3779B1u + 0x7F4A7C15u) * active) >> 32);
+    size_t at = i;
+#pragma unroll
+    for (int k = 1; k < NDEG; ++k)
+        if (i >= below[k]) at = (size_t)k * fr.N + (i - below[k]);
+    const int u = lists[at];
+    // the list is read without waiting for the degree; lane l holds slots l and 64 + l
+    const u64 *row = keys + (size_t)u * R;
+    const u64 k0 = row[lane < R ? lane : R - 1], k1 = row[lane + 64 < R ? lane + 64 : R - 1];
+    const int m = deg[u] < R ? deg[u] : R, t = m < 8 ? m : 8;
+    const int ti = (int)(0x77654321u >> (4 * grp)) & 15, tj = (int)(0x52302110u >> (4 * grp)) & 15;
+    const int ei = ti * (m - 1) / 7, ej = tj * (m - 1) / 7;      // (the farthest entry is one of them: rows far larger than the others are there)
+    const u64 ki = ei < 64 ? shfl_u64(k0, ei & 63) : shfl_u64(k1, ei & 63), kj = ej < 64 ? shfl_u64(k0, ej & 63) : shfl_u64(k1, ej & 63);
+    const FloatOp<DT, DT == DT_F32> op(fr, rowbytes);
+    const bool have = t == 8 && ((ki | kj) & 1ull);
+    float n = 0.f, delta = 0.f;
+    if (have) {
+        const char *g = G + (size_t)key_id(ki) * rowbytes;
+        for (u32 c = 16u * sub; c < rowbytes; c += 128u) {
+            const uint4 p = *(const uint4 *)(g + c);
+            const u32 x[4] = {p.x, p.y, p.z, p.w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                constexpr int T = DT == DT_BF16 ? DT_BF16 : DT_F16;
+                const float a = coord16_to_float<T>((unsigned short)x[k]), b = coord16_to_float<T>((unsigned short)(x[k] >> 16));
+                n = fmaf(a, a, n);
+                n = fmaf(b, b, n);
+            }
+        }
+        const size_t rb = (size_t)fr.d * dt_size(DT);
+        delta = op.scaled(group8_dist_bits<DT, 4>(fr.X + (size_t)key_id(ki) * rb, fr.X + (size_t)key_id(kj) * rb, fr.d, 1, sub));
+        n += __uint_as_float(xor_lane_u32<1>(__float_as_uint(n)));
+        n += __uint_as_float(xor_lane_u32<2>(__float_as_uint(n)));
+        n += __uint_as_float(xor_lane_u32<4>(__float_as_uint(n)));
+    }
+    __syncthreads();
+    const float nhalf = half_wave_max(n <= 1e36f ? n : 0.f), nmax = fmaxf(nhalf, __shfl_xor(nhalf, 32));
+    const float D = op.scaled(key_dist(ki));
+    const bool open = have && !(n <= 1e36f && fabsf(D - delta) > op.tolerance(D, n, nmax));
+    const u64 pairs = __builtin_amdgcn_ballot_w64(have && sub == 0), opens = __builtin_amdgcn_ballot_w64(open && sub == 0);
+    if (lane == 0 && pairs) {
+        atomicAdd(&s_pairs, (u32)__popcll(pairs));
+        atomicAdd(&s_open, (u32)__popcll(opens));
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && s_pairs) {
+        atomicAdd(&ctr->sample_pairs, s_pairs);
+        atomicAdd(&ctr->sample_open, s_open);
+    }
+}
+
 // This wavefront's vertices of a class, up to 16 NRC entries each, in groups of 16 rows; vertex i of the class is at(i).
 template <int DT, int NG, int NRC, int SMEM, typename AT>
 __device__ __forceinline__ void group_lists(const FloatRows &fr, int R, u64 *keys, int *deg, AT at, u32 gw, u32 nw, int &head, u32 n, Prop *props,

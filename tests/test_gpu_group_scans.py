@@ -28,6 +28,10 @@ def rows(kind, N, d, seed=1):
         X = X / X.norm(dim=1, keepdim=True)
     elif kind == "far":      # far from the origin, next to the distances
         X = X + 200
+    elif kind == "places":   # two of them, far apart
+        X[::2] += 1e4
+    elif kind == "outliers":
+        X[::97] *= 1e3
     elif kind == "sizes":    # norms over twelve binades
         X = X * torch.exp2(torch.randint(-6, 7, (N, 1), device="cuda", generator=g).float())
     return X.contiguous()
@@ -65,6 +69,25 @@ def test_rows_that_need_groups_get_them(rn, n, d, kind, dtype, R):
     X = rows(kind, n, d).to(DTYPES()[dtype])
     whole, blocks = builds(rn, X, R)
     assert 1 <= whole.group_scans <= 8 and 1 <= blocks.group_scans <= 32
+
+
+@pytest.mark.parametrize("R", [32, 96, 128])
+@pytest.mark.parametrize("kind,dtype", [("places", "f32"), ("sizes", "f32"), ("outliers", "f32"), ("far", "f16"), ("sizes", "bf16"), ("outliers", "bf16")])
+@pytest.mark.parametrize("n,d", [(8_192, 96), (140_000, 64)])
+def test_the_first_round_knows(rn, n, d, kind, dtype, R):
+    """A sample of the random graph's lists tells it: every round of the build takes groups, and every run."""
+    X = rows(kind, n, d).to(DTYPES()[dtype])
+    whole, blocks = builds(rn, X, R)
+    assert whole.group_scans == 8 and blocks.group_scans >= (32 if n >= 40_000 else 1)
+
+
+def test_the_first_round_of_a_step_call_knows(rn):
+    X = rows("far", 20_000, 96).to(DTYPES()["f16"])
+    keys, deg = rn.rnnd_random_graph(X, 20, 64, 4)
+    assert [rn.rnnd_update_neighbors(X, keys, deg, 64, 1).group_scans for _ in range(2)] == [1, 1]
+    X = rows("unit", 20_000, 96).to(DTYPES()["f16"])
+    keys, deg = rn.rnnd_random_graph(X, 20, 64, 4)
+    assert [rn.rnnd_update_neighbors(X, keys, deg, 64, 1).group_scans for _ in range(2)] == [0, 0]
 
 
 @pytest.mark.parametrize("R", [32, 96, 128])
