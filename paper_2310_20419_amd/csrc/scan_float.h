@@ -100,9 +100,11 @@ struct FloatOp {
         e2 = 0;
         spread = (2.0 * (double)rows.d + 32.0) * 1.1102230246251565e-16;
         if constexpr (HALF) {
-            // rounded up: what the sums of k_half_rows and the square roots here may have lost
-            gam = 1.0001f * __uint_as_float(rows.par->share_bits);
-            bet = 1.0001f * __uint_as_float(rows.par->rest_bits);
+            // rounded up: what the sums of k_half_rows and the square roots here may have lost, and the root of a norm n that comes from
+            // the tile, d 2^-24 n off at most (see above): d 2^-25
+            const float up = 1.0001f + (float)(rowbytes / 2u) * 0x1p-24f;
+            gam = up * __uint_as_float(rows.par->share_bits);
+            bet = up * __uint_as_float(rows.par->rest_bits);
             e2 = 2 * rows.par->exponent;
             tiny = (float)(rowbytes / 2u) * 0x1p-46f + ldexpf(1.f, -120 + (e2 > 0 ? e2 : 0));
         } else {

@@ -117,3 +117,10 @@ def _compare(rn, X, settings):
         n = T1 * T2
         assert list(got[3].algo_evals[:n]) == list(want[3].algo_evals[:n])
         assert list(got[3].proposals[:n]) == list(want[3].proposals[:n])
+
+
+@pytest.mark.parametrize("kind", ["plain", "centre 1e3", "tight"])
+@pytest.mark.parametrize("n,d", [(1500, 4096), (600, 20_000)])
+def test_long_rows(rn, n, d, kind):
+    """The error of the norms that the tiles form grows with the length of a row, and the bound with it."""
+    _compare(rn, _rows(kind, d, n), ((20, 96, 2, 3), (8, 16, 1, 2)))
