@@ -208,8 +208,9 @@ def measure(rn, cfg, X, Xd, esz, st16, steps, warmup, args, with_search=True, wi
     # Algorithmic bytes of one launch = rows of X it must gather (d*esz each) + the list entries it reads
     # (8 B) and writes back (8 B) + the redirected edges it emits (16 B); summed over the T1*T2 launches of
     # the last timed build, durations by HIP events on the build's stream.
-    # (float32 rows: the scan gathers the half-precision copy, 2 bytes a coordinate)
-    gather_esz = 2 if s["kernel_variant"] == 3 else esz
+    # (float32 rows: the scan gathers the half-precision copy, 2 bytes a coordinate; --variant 2 whole rows on the f64 matrix cores)
+    f64 = s["kernel_variant"] == 3 and args.variant == 2
+    gather_esz = 2 if s["kernel_variant"] == 3 and not f64 else esz
     scan_bytes = sum(g * (cfg.d * gather_esz + 16) + 16 * p for g, p in zip(s["gathered_rows"], s["proposals"]))
     scan_ms = scan_ms_events if scan_ms_events else scan_ms_clock
     hbm_gbs = scan_bytes / (scan_ms * 1e-3) / 1e9 if scan_ms > 0 else 0.0
@@ -218,12 +219,14 @@ def measure(rn, cfg, X, Xd, esz, st16, steps, warmup, args, with_search=True, wi
              2: u8_scan_kernels(cfg),
              3: "k_scan_float_small<DT> + k_scan_float_all<DT,NC,C0> (a round's scan launches, back to back; "
                 "%s MFMA Gram tiles, undecided pairs by exact distances)" % (st16 if half else "f16 (half-precision copy)")}[kv]
-    traffic = None if half or args.merge_cap or args.blocks else TRAFFIC_PER_LAUNCH.get((cfg.name, kv))
+    if f64:
+        kname = "k_update_scan_f64<NG,CH,NRC,DT> (a launch per degree class; f64 MFMA Gram tiles, undecided pairs by exact distances)"
+    traffic = None if half or args.merge_cap or args.blocks or f64 else TRAFFIC_PER_LAUNCH.get((cfg.name, kv))
     if kv == 3:
-        # float rows: the Gram tiles run on the f16 matrix cores (2,500 TFLOP/s dense), the rows are gathered from HBM; the kernel is reported against whichever
+        # float rows: the Gram tiles run on the f16 matrix cores (2,500 TFLOP/s dense; f64: 78.6), the rows are gathered from HBM; the kernel is reported against whichever
         # of the two it sits closer to, with both fractions in the line.  executed flops = computed pair
         # distances * 2 d
-        mfma_peak = 2500.0
+        mfma_peak = 78.6 if f64 else 2500.0
         flops = sum(s["exec_evals"]) * 2.0 * cfg.d
         tflops = flops / (scan_ms * 1e-3) / 1e12 if scan_ms > 0 else 0.0
         extra = {"launches": rounds, "avg_launch_ms": scan_ms / max(1, rounds),

@@ -64,7 +64,8 @@ typedef enum {
 
 /* Counters of one build, filled on the host.  "algo" evaluations are the delta(v,w)
  * evaluations the prune test of Alg. 4 performs (with its old/old skip and its break at the
- * first failure); "exec" are the distances the kernels actually computed. */
+ * first failure); "exec" are the pair distances of the scans: every pair of a Gram tile they formed, or, pair at a time, every
+ * one evaluated (float rows on 16-bit tiles: without the exact distances of undecided pairs and of redirected edges). */
 typedef struct {
     int32_t rounds;                         /* UpdateNeighbors rounds run (T1*T2) */
     int32_t reverse_calls;                  /* AddReverseEdges calls run (T1-1) */
@@ -266,7 +267,9 @@ int rnnd_probe_gather_map(const void *X, int64_t n_rows, int64_t row_bytes, int6
  *   float32 rows with d a multiple of 16, 16-bit rows with d a multiple of 32: a Gram block first (f16 / bf16 MFMA on
  *   16-bit rows as stored and, in builds, on a half-precision copy of float32 rows; fp32 MFMA on float32 rows otherwise), every
  *   pair whose outcome lies within that block's error bound and can matter decided by the exact distance, and
- *   vertices with very many such pairs redone on the f64 MFMA or, on small inputs, pair by pair.  Float rows of other lengths, or not 16-byte
+ *   vertices with very many such pairs redone on the f64 MFMA (lists of more than 96 entries: pair by pair).  Rounds whose
+ *   lists those Gram blocks would leave mostly undecided take fp32 MFMA on whole float32 rows, or the narrower bound of smaller f16 / bf16
+ *   MFMA tiles, instead (rnnd_stats.group_scans; chosen on the device, from 8,192 vertices on in the first round too).  Float rows of other lengths, or not 16-byte
  *   aligned, on a padded copy if there are enough of them (256; 2,048 if d < 16) and every coordinate is finite
  *   (rnnd_update_neighbors: 2,048, finite or not).
  * All give identical graphs; this exists for testing and profiling.  Process-wide, not thread-safe. */

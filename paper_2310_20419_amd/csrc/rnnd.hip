@@ -1526,9 +1526,10 @@ struct Workspace {
     int *deg = nullptr;     // [N]
     Prop *props = nullptr;  // [N*R]   slot u*R.. holds the edges vertex u redirected this round
     u64 *inbox = nullptr;   // [N*INBOX_CAP] redirected edges received this round, by target
-    u64 *bins = nullptr;    // [N*R]   a round's heads of late edges, the float scan's redo list; AddReverseEdges' bins
+    u64 *bins = nullptr;    // [N*R]   a round's heads of late edges; AddReverseEdges' bins
     u64 *thr = nullptr;     // [N]
     int *cnt = nullptr, *binoff = nullptr, *fill = nullptr, *touched = nullptr, *hubs = nullptr, *nprop = nullptr;
+    // (touched: [NMRG*N]; until the scatter, the vertices that a float scan leaves)
     char *half = nullptr;     // half-precision copy of float32 rows
     int8_t *xs = nullptr;     // copy of X (see ScanPlan): X - 128 as int8 for the uint8 MFMA scan, or padded rows
     int *lists = nullptr;   // [NDEG*N] active lists by degree class

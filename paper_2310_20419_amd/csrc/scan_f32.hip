@@ -2,6 +2,8 @@
 #include "launch.h"
 #include "scan_mfma_f32.h"
 
+// (The times of the launch rules here are of builds that worked by these kernels throughout: float32 builds, and 16-bit ones, before they had the
+// tiles of scan_float.h.  Static builds and step-wise calls on float32 rows still do.)
 // Float scan: up to here one launch for all classes, which costs the shorter lists their occupancy; above, a launch for each of
 // lists of up to 32, 64 and 96 entries.  Whole builds, S = 20, 60 rounds, three launches / one, ms:
 //   R = 96          20,000        32,000        50,000         70,000         100,000         200,000

@@ -390,7 +390,7 @@ struct FloatOp {
                         const u32 lmax = vmask & ~both_halves(__builtin_amdgcn_ballot_w64(may));
                         u32 hi = hmax, lo = 0;
 #pragma unroll 1
-                    for (int sweep = 0; sweep < 33; ++sweep) {
+                        for (int sweep = 0; sweep < 33; ++sweep) {
                             lo = lmax & ~both_halves(__builtin_amdgcn_ballot_w64(((F[I] | U[I]) & hi) != 0));
                             const u32 h = hmax & ~both_halves(__builtin_amdgcn_ballot_w64((F[I] & lo) != 0));
                             if (h == hi) break;
@@ -427,7 +427,7 @@ struct FloatOp {
                         const u32 Kmax = vmask & ~both_halves(__builtin_amdgcn_ballot_w64(pre));
                         u32 Kcur = Kmax;
 #pragma unroll 1
-                    for (int sweep = 0; sweep < 33; ++sweep) {
+                        for (int sweep = 0; sweep < 33; ++sweep) {
                             const u32 Knew = Kmax & ~both_halves(__builtin_amdgcn_ballot_w64((F[I] & Kcur) != 0));
                             if (Knew == Kcur) break;
                             Kcur = Knew;

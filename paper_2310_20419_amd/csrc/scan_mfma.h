@@ -249,8 +249,8 @@ __device__ __forceinline__ void scan_list_body(const OP &op, const int8_t *__res
     if (lane == 0 && rows) add_round_stats(ctr, evals_algo, tiles * 1024ull, rows, nprops_total);
 }
 
-// The same walk for rows of d > 128 bytes (d a multiple of 64).  The first two chunks of the next vertex's rows are
-// asked for as soon as the current one's matrix work is done, so they travel during its prune test and its stores.
+// The same walk for rows of d > 128 bytes (d a multiple of 64).  The first chunk of the next vertex's rows (of lists of up to 32 entries:
+// the first two) is asked for as soon as the current one's matrix work is done, so it travels during its prune test and its stores.
 template <typename OP, int NG>
 __device__ __forceinline__ void scan_list_stream_body(const OP &op, const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
                                                       int *__restrict__ deg, const int *__restrict__ list, u32 n_active,

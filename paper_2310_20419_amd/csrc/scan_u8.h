@@ -1,7 +1,7 @@
 // UpdateNeighbors scan (Alg. 4, the body of the vertex loop) for uint8 rows on the matrix cores.
 //
 // One wavefront owns one vertex u with m <= 32*NG list entries.  The rows x_v of its whole list are
-// gathered straight into MFMA operand registers (lane l: row l%32 of a 32-row group, bytes
+// gathered straight into MFMA operand registers, rows of more than 128 bytes through LDS (lane l: row l%32 of a 32-row group, bytes
 // [32s + 16(l/32), +16) of K-step s) from a copy of X made once per build in which every byte is
 // the int8 x-128 (this leaves every difference, hence every delta, unchanged).  n_v = |x_v - 128|^2
 // is read off the diagonal of the Gram tile of v's block with itself.
