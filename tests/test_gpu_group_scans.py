@@ -31,7 +31,7 @@ def rows(kind, N, d, seed=1):
     elif kind == "places":   # two of them, far apart
         X[::2] += 1e4
     elif kind == "outliers":
-        X[::97] *= 1e3
+        X[::23] *= 1e3
     elif kind == "sizes":    # norms over twelve binades
         X = X * torch.exp2(torch.randint(-6, 7, (N, 1), device="cuda", generator=g).float())
     return X.contiguous()
@@ -88,6 +88,19 @@ def test_the_first_round_of_a_step_call_knows(rn):
     X = rows("unit", 20_000, 96).to(DTYPES()["f16"])
     keys, deg = rn.rnnd_random_graph(X, 20, 64, 4)
     assert [rn.rnnd_update_neighbors(X, keys, deg, 64, 1).group_scans for _ in range(2)] == [0, 0]
+
+
+@pytest.mark.parametrize("R", [32, 96, 128])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [20_000, 140_000])
+def test_rows_that_repeat(rn, n, dtype, R):
+    """Ties in bulk: whatever form a scan takes it leaves vertices to the next one, in the scan or (140,000) in a launch of its own, lists of more
+    than 96 entries to the pair-at-a-time kernel."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(2)
+    X = rows("plain", n // 50, 64).repeat_interleave(50, 0)[torch.randperm(n // 50 * 50, device="cuda", generator=g)]
+    builds(rn, X.contiguous().to(DTYPES()[dtype]), R)
 
 
 @pytest.mark.parametrize("R", [32, 96, 128])

@@ -91,13 +91,19 @@ def test_a_vertex_that_receives_thousands_of_edges(rn, dtype, R):
         try:
             rn.rnnd_set_kernel_variant(v)
             st = rn.rnnd_update_neighbors(X, k, dg, R, 2)
+            # one run per pass is the same round, through the launches of large inputs: classify, merge, compact
+            k1, dg1 = keys.clone(), deg.clone()
+            rn.rnnd_update_neighbors_blocks(X, k1, dg1, R, 1, 2)
             # a build in which row 0 is in one list of seven from the start
-            out.append((k, dg, rn.rnnd_build_ex(X[:700].contiguous(), R, R, 2, 2, 4), st.proposals[0]))
+            small = X[:700].contiguous()
+            out.append((k, dg, rn.rnnd_build_ex(small, R, R, 2, 2, 4), st.proposals[0], k1, dg1, rn.rnnd_build_blocks(small, R, R, 2, 2, 4, 1)))
         finally:
             rn.rnnd_set_kernel_variant(0)
     used = torch.arange(R, device="cuda")[None, :] < out[0][1][:, None]
     assert torch.equal(out[0][1], out[1][1]) and torch.equal(out[0][0][used], out[1][0][used])
     assert torch.equal(out[0][2][0], out[1][2][0]) and out[0][3] == out[1][3] > 30_000
+    assert torch.equal(out[0][1], out[1][5]) and torch.equal(out[0][0][used], out[1][4][used])
+    assert torch.equal(out[0][2][0], out[1][6][0]) and torch.equal(out[0][2][1], out[1][6][1])
 
 
 def _compare(rn, X, settings):
