@@ -5,6 +5,7 @@
 
 #include "half_rows.h"
 #include "round.h"
+#include "scatter.h"
 
 static inline int cu_count()
 {
@@ -49,8 +50,7 @@ struct ScanLaunch {
     int *deg;
     long long N;
     const int *lists;           // [NDEG * N], by degree class
-    Prop *props;
-    int *nprop;
+    EdgeSink sink;
     RoundCtr *c;
     int *redo;                  // [2 * N] vertices that a first form leaves to another
     hipStream_t st;

@@ -5,7 +5,8 @@
 //   scan     every active vertex (one holding a "new" entry) runs the body of Alg. 4's vertex loop on its own list,
 //            writes its kept entries back in place and leaves its redirected edges in its slot of `props`
 //   scatter  every redirected edge takes an arrival number at its target (the round's only atomic per
-//            edge) and moves into the target's inbox (up to INBOX_CAP slots per vertex); later arrivals are chained
+//            edge) and moves into the target's inbox (up to INBOX_CAP slots per vertex); later arrivals are chained.
+//            The scans by tiles do it themselves, in their trips (see EdgeOut); a kernel of its own serves the others
 //   classify vertices that received edges form the `touched` lists, by the size of the merge they need
 //   merge    every touched list becomes the first R distinct keys of (kept entries + inbox + later arrivals)
 //   compact  touched vertices whose new list holds a "new" entry form the next active lists,
@@ -30,11 +31,9 @@
 #define GOLDEN64 0x9E3779B97F4A7C15ull
 #define RNND_MAX_SLOTS 0x7FFFFF00ull   // N * (slots per row): bin offsets are ints, -1 = no bin
 #define RNND_MAX_RUN_SLOTS 131072      // rounds (x runs per pass): one small counter block each
-#ifndef INBOX_CAP
-#define INBOX_CAP 64   // redirected edges a vertex can receive per round without the overflow path
-#endif
 
 #include "dist.h"
+#include "scatter.h"
 #include "scan_u8.h"
 #include "scan_pairs.h"
 #include "padded_rows.h"
@@ -112,8 +111,7 @@ struct WorkList {
 };
 template <int DT>
 __global__ __launch_bounds__(BLOCK) void k_update_scan(const void *X, int d, int vec_ok, int R,
-                                                       u64 *keys, int *deg, WorkList work, Prop *props, int *nprop,
-                                                       RoundCtr *ctr)
+                                                       u64 *keys, int *deg, WorkList work, EdgeSink sink, RoundCtr *ctr)
 {
     __shared__ u64 s_key[WAVES_PER_BLOCK][RNND_MAX_R];
     __shared__ u64 s_pkey[WAVES_PER_BLOCK][RNND_MAX_R];
@@ -132,13 +130,14 @@ __global__ __launch_bounds__(BLOCK) void k_update_scan(const void *X, int d, int
         u64 *row = keys + (size_t)u * R;
         u64 k0 = lane < m ? row[lane] : KEY_PAD;
         u64 k1 = lane + 64 < m ? row[lane + 64] : KEY_PAD;
-        const int np = scan_vertex_pairs<DT>(X, d, vec_ok, R, u, m, k0, k1, row, deg, props, nprop + u, s_key[wave], s_pkey[wave], s_ptgt[wave],
+        const int np = scan_vertex_pairs<DT>(X, d, vec_ok, R, u, m, k0, k1, row, deg, sink.props, sink.nprop + u, s_key[wave], s_pkey[wave], s_ptgt[wave],
                                              lane, evals_algo, evals_exec);
         if (np < 0) continue;
         rows += m;
         nprops_total += np;
     }
     if (lane == 0 && rows) add_round_stats(ctr, evals_algo, evals_exec, rows, nprops_total);
+    scatter_walk(sink, [=](u32 i) { return list[i]; }, gw, nw, n_active, R);
 }
 
 // ------------------------------------------------------ UpdateNeighbors: merge
@@ -257,46 +256,6 @@ __global__ __launch_bounds__(256) void k_prepare_listed_rows(const T *__restrict
     }
 }
 
-// Bit j set iff lane j of this lane's row of 16 holds the same value, for the lanes reached by rotations R .. 15.
-template <int R>
-__device__ __forceinline__ u32 same_target_mask(u32 tgt, int sub)
-{
-    if constexpr (R >= 16) {
-        return 0u;
-    } else {
-        const u32 t = (u32)__builtin_amdgcn_update_dpp(0, (int)tgt, 0x120 + R, 0xF, 0xF, true);     // row_ror:R
-        const u32 here = (t == tgt ? 1u : 0u) << ((sub - R) & 15);
-        return here | same_target_mask<R + 1>(tgt, sub);
-    }
-}
-
-// Redirected edges that arrive past their target's inbox ("late") stay where they are, in props, and are chained: a
-// target has LATE_LISTS lists, arrival number a is on list (a - inbox) mod LATE_LISTS, so the lists are of equal
-// length and a wavefront walks all of them at once.  The heads need no clearing: how many edges are on a list follows
-// from the target's count.  They lie in the bin array (8 R bytes per vertex, 4 LATE_LISTS needed); rows of fewer than 32
-// slots have no room for them there and receive fewer edges, so they use 32 of their 64 inbox slots and keep the heads in the
-// other 32.  (A second pass over all active vertices, once bins had been handed out, used to move them: one launch more
-// per round and 1.06 of 26 ms at 1M x 128.  Whole builds: 5,000 x 32 381 -> 354 us, 100,000 x 128 4.61 -> 4.33
-// ms, 1M x 128 26.0 -> 25.5 ms.  A round in which one vertex receives 700,000 edges, second pass / as many lists as fit 4 R
-// bytes / now: rows of 8 slots 19.5 / 78.6 / 19.7 ms, of 16 19.5 / 40.4 / 19.7, of 96 19.5 / 20.8 / 19.8, the last because the links
-// of a chunk are asked for while the one before it is sorted; 7,000 edges, 8 slots: 0.29 / 0.87 / 0.28.)
-#define LATE_LISTS 64
-#define LATE_OPEN 512     // float rows: late edges of a vertex whose distances its merge computes
-static __host__ __device__ inline int round_inbox(int R) { return R < 32 ? 32 : INBOX_CAP; }
-
-// list head l of vertex x is at [x * stride + l]
-struct LateHeads {
-    u32 *base;
-    u32 stride;
-};
-static __host__ __device__ inline LateHeads late_heads(u64 *inbox, u64 *bins, int R)
-{
-    LateHeads h;
-    h.base = R < 32 ? (u32 *)(inbox + 32) : (u32 *)bins;
-    h.stride = R < 32 ? 2u * INBOX_CAP : (u32)LATE_LISTS;
-    return h;
-}
-
 // Redirected edges of the float scans arrive without their distances (OPEN_DIST).  Computes them for the lanes whose key (of a
 // vertex in the list of vertex x) is open, in 8-lane groups, in the order the wavefront holds them; every lane of the
 // wavefront takes part.  DT_U8: nothing is ever open.
@@ -332,7 +291,7 @@ __device__ __forceinline__ u64 close_keys(u64 key, int x, bool have, OpenEdges *
     }
 }
 
-// Every active vertex moves its redirected edges to their targets, 16 lanes per vertex.  Lanes of a
+// For scans that leave their edges in props (see scan_scatters): every active vertex moves its redirected edges to their targets, 16 lanes per vertex.  Lanes of a
 // group that share a target take their arrival numbers with one atomic (a vertex usually redirects
 // several entries to the same kept neighbour).  Arrivals below round_inbox(R) go to the target's inbox, later ones onto
 // one of its lists (see LATE_LISTS).
@@ -397,6 +356,16 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(long long N, int R, const int
     }
 }
 
+// What k_scatter does besides scattering, for a round whose scan has scattered: by one thread.
+__device__ __forceinline__ void end_scan(RoundCtr *ctr, u32 enough)
+{
+    u32 active = 0;
+#pragma unroll
+    for (int k = 0; k < NDEG; ++k) active += ctr->n_active[k];
+    if (active < RNND_MAX_SLOTS) ctr->t_scan_stop = wall_clock64();      // (always: the clock is read once the scan's counters are here)
+    if (enough) decide_next_form(ctr, active, enough);
+}
+
 // Computes the open distances of the late edges of vertex x; each group of 8 lanes of the block walks its share of the lists.
 template <int DT>
 __device__ __attribute__((noinline)) void close_late(long long x, int late, LateHeads heads, Prop *props, const char *X, int d)
@@ -433,8 +402,9 @@ __device__ __forceinline__ int merge_class(int nb, int c, int cap)
 // of more than LATE_OPEN late edges the block does that here, 8 lanes for each of the hub's lists.
 template <int TC_TILES, int DT>
 __global__ __launch_bounds__(1024) void k_touch_classify(long long N, int cap, const int *cnt, const int *deg, RoundCtr *ctr, int *tlists,
-                                                         LateHeads heads, Prop *props, const char *__restrict__ X, int d)
+                                                         LateHeads heads, Prop *props, const char *__restrict__ X, int d, int scattered, u32 enough)
 {
+    if (scattered && blockIdx.x == 0 && threadIdx.x == 0) end_scan(ctr, enough);
     __shared__ u32 s_cnt[TC_TILES][16][NMRG], s_base[NMRG];
     bool hub = false;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -738,12 +708,13 @@ template <int DT>
 __global__ __launch_bounds__(BLOCK, (DT == DT_U8 ? 1 : 5)) void k_merge_blocks(long long N, int span, int R, u64 *keys, int *deg, int *cnt,
                                                                                const u64 *inbox, LateHeads heads, Prop *props, int use_classes,
                                                                                RoundCtr *ctr, int *lists, u32 *n_next,
-                                                                               const char *__restrict__ X, int d)
+                                                                               const char *__restrict__ X, int d, int scattered, u32 enough)
 {
     __shared__ u64 s_stage[WAVES_PER_BLOCK][RNND_MAX_R];
     __shared__ int s_list[NMRG][BLOCK];
     __shared__ int8_t s_cls[NMRG][BLOCK];
     __shared__ u32 s_n[NMRG], s_out[NDEG], s_base[NDEG];
+    if (scattered && blockIdx.x == 0 && threadIdx.x == 0) end_scan(ctr, enough);
     const int wave = threadIdx.x >> 6;
     OpenEdges *so = reinterpret_cast<OpenEdges *>(&s_stage[wave]);
     const int cap = round_inbox(R);
@@ -1715,14 +1686,16 @@ struct RoundEvents {
     hipEvent_t round_stop = nullptr;   // end of the round's last kernel
 };
 
+static EdgeSink edge_sink(const Workspace &w, int R) { return EdgeSink{w.fill, w.inbox, late_heads(w.inbox, w.bins, R), w.props, w.nprop}; }
+
 template <int NG, int KS>
 static void launch_mfma_scan(const Workspace &w, int d, int R, u64 *keys, int *deg, long long N, RoundCtr *c,
-                             hipStream_t st, hipEvent_t e_stop)
+                             hipStream_t st, hipEvent_t e_stop, const EdgeSink &sink)
 {
     static const int per_cu = resident_blocks_per_cu(k_update_scan_mfma_u8<NG, KS>, NG == 2 ? 3 : 2);
     hipExtLaunchKernelGGL((k_update_scan_mfma_u8<NG, KS>), dim3(capped(cu_count() * per_cu, N)), dim3(256), 0, st, nullptr,
                           e_stop, 0, (const int8_t *)w.xs, d, R, keys, deg, w.lists + (size_t)(NG + 1) * N,
-                          &c->n_active[NG + 1], w.props, w.nprop, c);
+                          &c->n_active[NG + 1], sink, c);
 }
 
 // Fills w.xs, the copy of X the plan asks for.
@@ -1839,7 +1812,7 @@ static hipError_t prepare_rows(const Workspace &w, ScanPlan &p, const void *X, l
 
 template <int KS>
 static void launch_mfma_scan_classes(const Workspace &w, int d, int R, u64 *keys, int *deg, long long N, RoundCtr *c,
-                                     hipStream_t st, const RoundEvents &re)
+                                     hipStream_t st, const RoundEvents &re, const EdgeSink &sink)
 {
     static const int per_cu = resident_blocks_per_cu(k_update_scan_mfma_u8_small<KS>, 4);
     const int n_big = (R > 32) + (R > 64) + (R > 96);   // launches after the short-list kernel
@@ -1849,66 +1822,66 @@ static void launch_mfma_scan_classes(const Workspace &w, int d, int R, u64 *keys
         if (gx < 8) gx = 8;      // a block at least for every class
         if (n_big == 1)
             hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, 4>), dim3(gx), dim3(256), 0, st, re.scan_start, re.scan_stop, 0,
-                                  (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, w.props, w.nprop, c);
+                                  (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, sink, c);
         else if (n_big == 2)
             hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, 5>), dim3(gx), dim3(256), 0, st, re.scan_start, re.scan_stop, 0,
-                                  (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, w.props, w.nprop, c);
+                                  (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, sink, c);
         else
             hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, 6>), dim3(gx), dim3(256), 0, st, re.scan_start, re.scan_stop, 0,
-                                  (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, w.props, w.nprop, c);
+                                  (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, sink, c);
         return;
     }
     const int ny = 1 + (R > 8) + (R > 16);
     hipExtLaunchKernelGGL((k_update_scan_mfma_u8_small<KS>), dim3(capped(cu_count() * per_cu, N), ny), dim3(256), 0, st,
                           re.scan_start, n_big == 0 ? re.scan_stop : nullptr, 0, (const int8_t *)w.xs, d, R, keys, deg,
-                          w.lists, N, w.props, w.nprop, c);
+                          w.lists, N, sink, c);
     // large inputs: the short-list launch above, then the longer classes in one launch
     if (n_big >= 2 && (g_scan_launches == 3 || (g_scan_launches == 0 && N <= LONG_SHARED_MAX_N))) {
         unsigned gx = capped((long long)cu_count() * 2, N);
         if (gx < 8) gx = 8;      // a block at least for every class
         if (n_big == 2)
             hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, 5, 3>), dim3(gx), dim3(256), 0, st, nullptr, re.scan_stop, 0,
-                                  (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, w.props, w.nprop, c);
+                                  (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, sink, c);
         else
             hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, 6, 3>), dim3(gx), dim3(256), 0, st, nullptr, re.scan_stop, 0,
-                                  (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, w.props, w.nprop, c);
+                                  (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, sink, c);
         return;
     }
-    if (R > 32) launch_mfma_scan<2, KS>(w, d, R, keys, deg, N, c, st, n_big == 1 ? re.scan_stop : nullptr);
-    if (R > 64) launch_mfma_scan<3, KS>(w, d, R, keys, deg, N, c, st, n_big == 2 ? re.scan_stop : nullptr);
-    if (R > 96) launch_mfma_scan<4, KS>(w, d, R, keys, deg, N, c, st, n_big == 3 ? re.scan_stop : nullptr);
+    if (R > 32) launch_mfma_scan<2, KS>(w, d, R, keys, deg, N, c, st, n_big == 1 ? re.scan_stop : nullptr, sink);
+    if (R > 64) launch_mfma_scan<3, KS>(w, d, R, keys, deg, N, c, st, n_big == 2 ? re.scan_stop : nullptr, sink);
+    if (R > 96) launch_mfma_scan<4, KS>(w, d, R, keys, deg, N, c, st, n_big == 3 ? re.scan_stop : nullptr, sink);
 }
 
 template <int DT>
 static void launch_generic_scan_dt(const Workspace &w, const void *X, int d, int vec_ok, int R, u64 *keys, int *deg, long long N,
-                                   const WorkList &work, unsigned blocks, RoundCtr *c, hipStream_t st, hipEvent_t e_start, hipEvent_t e_stop)
+                                   const WorkList &work, const EdgeSink &sink, unsigned blocks, RoundCtr *c, hipStream_t st, hipEvent_t e_start, hipEvent_t e_stop)
 {
     hipExtLaunchKernelGGL(k_update_scan<DT>, dim3(blocks), dim3(BLOCK), 0, st, e_start, e_stop, 0, X, d, vec_ok, R, keys, deg,
-                          work, w.props, w.nprop, c);
+                          work, sink, c);
 }
 
 // The generic scan over one list.
 static void launch_generic_scan(const Workspace &w, const void *X, int d, int dtype, int vec_ok, int R, u64 *keys, int *deg,
-                                long long N, const WorkList &work, unsigned blocks, RoundCtr *c, hipStream_t st, hipEvent_t e_start,
+                                long long N, const WorkList &work, const EdgeSink &sink, unsigned blocks, RoundCtr *c, hipStream_t st, hipEvent_t e_start,
                                 hipEvent_t e_stop)
 {
-    if (dtype == RNND_U8) launch_generic_scan_dt<DT_U8>(w, X, d, vec_ok, R, keys, deg, N, work, blocks, c, st, e_start, e_stop);
-    else if (dtype == RNND_F16) launch_generic_scan_dt<DT_F16>(w, X, d, vec_ok, R, keys, deg, N, work, blocks, c, st, e_start, e_stop);
-    else if (dtype == RNND_BF16) launch_generic_scan_dt<DT_BF16>(w, X, d, vec_ok, R, keys, deg, N, work, blocks, c, st, e_start, e_stop);
-    else launch_generic_scan_dt<DT_F32>(w, X, d, vec_ok, R, keys, deg, N, work, blocks, c, st, e_start, e_stop);
+    if (dtype == RNND_U8) launch_generic_scan_dt<DT_U8>(w, X, d, vec_ok, R, keys, deg, N, work, sink, blocks, c, st, e_start, e_stop);
+    else if (dtype == RNND_F16) launch_generic_scan_dt<DT_F16>(w, X, d, vec_ok, R, keys, deg, N, work, sink, blocks, c, st, e_start, e_stop);
+    else if (dtype == RNND_BF16) launch_generic_scan_dt<DT_BF16>(w, X, d, vec_ok, R, keys, deg, N, work, sink, blocks, c, st, e_start, e_stop);
+    else launch_generic_scan_dt<DT_F32>(w, X, d, vec_ok, R, keys, deg, N, work, sink, blocks, c, st, e_start, e_stop);
 }
 
 // dt (here and below): the type of the rows that open distances are computed from, DT_U8 where none are open
 template <int DT>
-static void launch_classify_dt(hipStream_t st, long long N, int R, const Workspace &w, const int *deg, RoundCtr *c, const void *X, int d)
+static void launch_classify_dt(hipStream_t st, long long N, int R, const Workspace &w, const int *deg, RoundCtr *c, const void *X, int d, bool scattered, u32 enough)
 {
     const LateHeads heads = late_heads(w.inbox, w.bins, R);
     if (N <= SMALL_INPUT_MAX_N)
         hipLaunchKernelGGL((k_touch_classify<2, DT>), dim3((unsigned)((N + 2047) / 2048)), dim3(1024), 0, st, N, round_inbox(R), w.fill, deg, c,
-                           w.touched, heads, w.props, (const char *)X, d);
+                           w.touched, heads, w.props, (const char *)X, d, scattered ? 1 : 0, enough);
     else
         hipLaunchKernelGGL((k_touch_classify<4, DT>), dim3((unsigned)((N + 4095) / 4096)), dim3(1024), 0, st, N, round_inbox(R), w.fill, deg, c,
-                           w.touched, heads, w.props, (const char *)X, d);
+                           w.touched, heads, w.props, (const char *)X, d, scattered ? 1 : 0, enough);
 }
 
 template <int DT>
@@ -1919,10 +1892,10 @@ static void launch_merge_dt(hipStream_t st, long long N, int R, const Workspace 
                        w.fill, w.inbox, late_heads(w.inbox, w.bins, R), (const Prop *)w.props, w.tcls, use_classes, c, (const char *)X, d);
 }
 
-static void launch_classify(int dt, hipStream_t st, long long N, int R, const Workspace &w, const int *deg, RoundCtr *c, const void *X, int d)
+static void launch_classify(int dt, hipStream_t st, long long N, int R, const Workspace &w, const int *deg, RoundCtr *c, const void *X, int d, bool scattered, u32 enough)
 {
     const auto go = dt == RNND_F32 ? launch_classify_dt<DT_F32> : dt == RNND_F16 ? launch_classify_dt<DT_F16> : dt == RNND_BF16 ? launch_classify_dt<DT_BF16> : launch_classify_dt<DT_U8>;
-    go(st, N, R, w, deg, c, X, d);
+    go(st, N, R, w, deg, c, X, d, scattered, enough);
 }
 // Up to here classify, merge and compact are one launch, of up to 128 vertices a block, fewer where that gives fewer than 512
 // blocks.  Three launches / one, ms: 5,000 x 32 uint8 0.355 / 0.302, 20,000 x 96 float32 3.14 / 2.92, 60,000 x 784 uint8 5.12 / 4.86,
@@ -1932,17 +1905,19 @@ static void launch_classify(int dt, hipStream_t st, long long N, int R, const Wo
 #define MERGE_SPAN 128
 #define MERGE_BLOCKS_MIN 512
 template <int DT>
-static void launch_merge_blocks_dt(hipStream_t st, long long N, int R, const Workspace &w, u64 *keys, int *deg, int use_classes, RoundCtr *c, const void *X, int d)
+static void launch_merge_blocks_dt(hipStream_t st, long long N, int R, const Workspace &w, u64 *keys, int *deg, int use_classes, RoundCtr *c, const void *X, int d,
+                                   bool scattered, u32 enough)
 {
     int span = MERGE_SPAN;
     while (span > 16 && N / span < MERGE_BLOCKS_MIN) span >>= 1;
     hipLaunchKernelGGL(k_merge_blocks<DT>, dim3((unsigned)((N + span - 1) / span)), dim3(BLOCK), 0, st, N, span, R, keys, deg, w.fill, w.inbox,
-                       late_heads(w.inbox, w.bins, R), w.props, use_classes, c, w.lists, (c + 1)->n_active, (const char *)X, d);
+                       late_heads(w.inbox, w.bins, R), w.props, use_classes, c, w.lists, (c + 1)->n_active, (const char *)X, d, scattered ? 1 : 0, enough);
 }
-static void launch_merge_blocks(int dt, hipStream_t st, long long N, int R, const Workspace &w, u64 *keys, int *deg, int use_classes, RoundCtr *c, const void *X, int d)
+static void launch_merge_blocks(int dt, hipStream_t st, long long N, int R, const Workspace &w, u64 *keys, int *deg, int use_classes, RoundCtr *c, const void *X, int d,
+                                bool scattered, u32 enough)
 {
     const auto go = dt == RNND_F32 ? launch_merge_blocks_dt<DT_F32> : dt == RNND_F16 ? launch_merge_blocks_dt<DT_F16> : dt == RNND_BF16 ? launch_merge_blocks_dt<DT_BF16> : launch_merge_blocks_dt<DT_U8>;
-    go(st, N, R, w, keys, deg, use_classes, c, X, d);
+    go(st, N, R, w, keys, deg, use_classes, c, X, d, scattered, enough);
 }
 static void launch_merge(int dt, hipStream_t st, long long N, int R, const Workspace &w, u64 *keys, int *deg, int use_classes, RoundCtr *c, const void *X, int d)
 {
@@ -1958,6 +1933,19 @@ struct VertexRun {
 // A round of fewer active vertices than this, or than a sixteenth of all, does not decide which form the float scan of the next
 // one takes (see decide_next_form): 32 sampled wavefronts.
 #define DECIDE_MIN_ACTIVE 1024u
+
+// Whether the scan by tiles (and what follows it) scatters the edges itself (see EdgeOut).  Scans that hold rows whole always do: 1M x 128
+// uint8 25.5 -> 23.5 ms, 20M (6 rounds) 116 -> 106, 1M x 64 (15 rounds) 5.05 -> 4.26.  Streamed rows: as long as they and the inboxes stay below
+// this many bytes; beyond, an arrival number takes longer to come than the next rows, which wait behind it.  k_scatter / in the scan, 15 rounds, ms: float32
+// 1M x 96 31.3 / 29.0, x 256 59.3 / 57.6, x 512 115.3 / 114.2, x 960 212.0 / 214.1; 300,000 x 960 56.0 / 55.6; bfloat16 1M x 256 43.7 / 42.4, x 768
+// 121.9 / 122.5; uint8 1M x 784 28.6 / 27.7, 2M x 784 (6 rounds) 34.1 / 38.0; float32 4M x 128 (6 rounds) 76.3 / 78.4.
+#define OWN_SCATTER_MAX_BYTES 1750000000ll
+static bool scan_scatters(const ScanPlan &plan, const RowsView &rv, long long N, int dtype)
+{
+    if (plan.variant == 2 && plan.dp <= 128) return true;
+    const long long rowbytes = plan.variant == 2 ? plan.dp : rv.half.rows ? rv.half.rowbytes : (long long)rv.d * dt_size(dtype);
+    return N * (rowbytes + 8 * INBOX_CAP) <= OWN_SCATTER_MAX_BYTES;
+}
 
 // One synchronous round over the active lists of counter slot t (run == nullptr), or one run of a
 // block-sequential pass: the run's active lists are taken from vcls[] first, and the classes of the
@@ -1975,6 +1963,9 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
     const int open_dt = variant == 3 && use_classes == 2 ? dtype : RNND_U8;      // whose redirected edges come without distances
     const long long vertices = run ? (long long)run->count : N;
     const u32 enough = vertices / 16 > DECIDE_MIN_ACTIVE ? (u32)(vertices / 16) : DECIDE_MIN_ACTIVE;
+    const bool own_scatter = use_classes == 2 && scan_scatters(plan, rv, N, dtype);
+    EdgeSink sink = edge_sink(w, R);
+    if (!own_scatter) sink.count = nullptr;
     if (run) {
         const unsigned cb = (run->count + 1023u) / 1024u;
         hipLaunchKernelGGL(k_compact_classes, dim3(cb < 256u ? cb : 256u, 1), dim3(1024), 0, st, (const u32 *)nullptr,
@@ -1982,20 +1973,20 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
                            run->first, w.vcls);
     }
     if (variant == 2) {
-        if (d == 32) launch_mfma_scan_classes<1>(w, d, R, keys, deg, N, c, st, re);
-        else if (d == 64) launch_mfma_scan_classes<2>(w, d, R, keys, deg, N, c, st, re);
-        else if (d == 128) launch_mfma_scan_classes<4>(w, d, R, keys, deg, N, c, st, re);
-        else launch_mfma_scan_classes<0>(w, d, R, keys, deg, N, c, st, re);
+        if (d == 32) launch_mfma_scan_classes<1>(w, d, R, keys, deg, N, c, st, re, sink);
+        else if (d == 64) launch_mfma_scan_classes<2>(w, d, R, keys, deg, N, c, st, re, sink);
+        else if (d == 128) launch_mfma_scan_classes<4>(w, d, R, keys, deg, N, c, st, re, sink);
+        else launch_mfma_scan_classes<0>(w, d, R, keys, deg, N, c, st, re, sink);
     } else if (variant == 3) {
         const bool generic_tail = R > 96;
-        ScanLaunch l = {X, d, R, keys, deg, N, w.lists, w.props, w.nprop, c, w.touched, st, re.scan_start,
+        ScanLaunch l = {X, d, R, keys, deg, N, w.lists, sink, c, w.touched, st, re.scan_start,
                         generic_tail ? (hipEvent_t) nullptr : re.scan_stop, t, vertices, enough};
         if (use_classes == 2) {
             // lists of up to 128 entries; the generic kernel takes what the scan leaves of the longest, all of them where it takes groups
             const bool copy = rv.half.rows != nullptr;
             launch_float_scan(l, dtype, copy ? rv.half.rows : X, copy ? rv.half.rowbytes : (u32)(d * dt_size(dtype)), rv.half.par);
             if (generic_tail)
-                launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, WorkList{l.redo, &c->n_redo, w.lists + (size_t)5 * N, &c->n_active[5], &c->groups}, pb, c, st,
+                launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, WorkList{l.redo, &c->n_redo, w.lists + (size_t)5 * N, &c->n_active[5], &c->groups}, sink, pb, c, st,
                                     nullptr, re.scan_stop);
         } else {
             // degree classes 0..6: lists of at most 8, 16, 32, 48, 64, 80, 96 entries = 1, 1, 2, 3, 4, 5, 6 groups of 16
@@ -2006,20 +1997,22 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
             } else {
                 launch_f64_classes(l, dtype);
             }
-            if (generic_tail) launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, WorkList{w.lists + (size_t)7 * N, &c->n_active[7]}, pb, c, st, nullptr, re.scan_stop);
+            if (generic_tail) launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, WorkList{w.lists + (size_t)7 * N, &c->n_active[7]}, sink, pb, c, st, nullptr, re.scan_stop);
         }
     } else {
-        launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, WorkList{w.lists, &c->n_active[0]}, pb, c, st, re.scan_start, re.scan_stop);
+        launch_generic_scan(w, X, d, dtype, vec_ok, R, keys, deg, N, WorkList{w.lists, &c->n_active[0]}, sink, pb, c, st, re.scan_start, re.scan_stop);
     }
     // from here on `fill` plays the role of the per-target count of this round
     const int ncl = use_classes ? NDEG : 1;
-    hipLaunchKernelGGL(k_scatter, dim3(pb), dim3(BLOCK), 0, st, N, R, w.lists, ncl, c, w.props, (const int *)w.nprop, w.fill,
-                       w.inbox, late_heads(w.inbox, w.bins, R), open_dt != RNND_U8 ? enough : 0u);
+    const u32 decide = open_dt != RNND_U8 ? enough : 0u;
+    if (!own_scatter)
+        hipLaunchKernelGGL(k_scatter, dim3(pb), dim3(BLOCK), 0, st, N, R, w.lists, ncl, c, w.props, (const int *)w.nprop, w.fill,
+                           w.inbox, late_heads(w.inbox, w.bins, R), decide);
     if (!run && !re.round_stop && N <= MERGE_BLOCKS_MAX_N) {
-        launch_merge_blocks(open_dt, st, N, R, w, keys, deg, use_classes, c, X, d);
+        launch_merge_blocks(open_dt, st, N, R, w, keys, deg, use_classes, c, X, d, own_scatter, decide);
         return hipGetLastError();
     }
-    launch_classify(open_dt, st, N, R, w, deg, c, X, d);
+    launch_classify(open_dt, st, N, R, w, deg, c, X, d, own_scatter, decide);
     launch_merge(open_dt, st, N, R, w, keys, deg, use_classes, c, X, d);
     if (run)
         hipLaunchKernelGGL(k_store_classes, dim3(64, NMRG), dim3(256), 0, st, (const u32 *)c->n_touched,

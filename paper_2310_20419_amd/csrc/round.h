@@ -45,8 +45,11 @@ __device__ __forceinline__ void add_round_stats(RoundCtr *ctr, u64 algo, u64 exe
 // Statistics take the scan time of a round from the device's own clock instead of events attached to the launches:
 // an event costs 4-7 microseconds of idle queue after its kernel, three per round used to add 1 ms to a 27 ms build.
 __device__ __forceinline__ void stamp_scan_start(RoundCtr *ctr)
-{   // the first scan launch of a round that comes by fills the field
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && ctr->t_scan_start == 0ull) ctr->t_scan_start = wall_clock64();
+{   // the first scan launch of a round that comes by fills the field (the clock is read before the field is, which takes a microsecond)
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+        const u64 now = wall_clock64();
+        if (ctr->t_scan_start == 0ull) ctr->t_scan_start = now;
+    }
 }
 __device__ __forceinline__ void stamp_scan_stop(RoundCtr *ctr)
 {

@@ -35,7 +35,7 @@ static void launch_classes(const ScanLaunch &l, hipEvent_t e_start)
     unsigned gx = capped((long long)cu_count() * per_cu, l.N);
     if (gx < 8) gx = 8;      // a block at least for every class
     hipExtLaunchKernelGGL((k_update_scan_mfma_f32_all<NRCMAX, C0, CH>), dim3(gx), dim3(256), 0, l.st, e_start, nullptr, 0,
-                          (const char *)l.X, l.d, l.R, l.keys, l.deg, l.lists, l.N, l.props, l.nprop, l.c, l.redo, &l.c->n_redo);
+                          (const char *)l.X, l.d, l.R, l.keys, l.deg, l.lists, l.N, l.sink.props, l.sink.nprop, l.c, l.redo, &l.c->n_redo);
 }
 
 void launch_f32_scan(const ScanLaunch &l)
@@ -68,18 +68,24 @@ void launch_f32_scan(const ScanLaunch &l)
     if (R > 64) launch_classes<6, 5, 1>(l, nullptr);
 }
 
-template <int NG, int CH, int NRC, int DT>
+template <int NG, int CH, int NRC, int DT, bool SCATTER = false>
 static void launch_f64(const ScanLaunch &l, const int *list, const u32 *n_list, hipEvent_t e_start, hipEvent_t e_stop)
 {
     // wavefronts that fit per SIMD: about 4 for NG = 1, 2 for NG = 2, 1 for NG = 3 (21 accumulator tiles)
-    static const int per_cu = resident_blocks_per_cu(k_update_scan_f64<NG, CH, NRC, DT>, NG == 1 ? 4 : NG == 2 ? 2 : 1);
-    hipExtLaunchKernelGGL((k_update_scan_f64<NG, CH, NRC, DT>), dim3(capped(cu_count() * per_cu, l.N)), dim3(256), 0,
-                          l.st, e_start, e_stop, 0, (const char *)l.X, l.d, l.R, l.keys, l.deg, list, n_list, l.props, l.nprop, l.c);
+    static const int per_cu = resident_blocks_per_cu(k_update_scan_f64<NG, CH, NRC, DT, SCATTER>, NG == 1 ? 4 : NG == 2 ? 2 : 1);
+    hipExtLaunchKernelGGL((k_update_scan_f64<NG, CH, NRC, DT, SCATTER>), dim3(capped(cu_count() * per_cu, l.N)), dim3(256), 0,
+                          l.st, e_start, e_stop, 0, (const char *)l.X, l.d, l.R, l.keys, l.deg, list, n_list, l.sink, l.c);
 }
 
 void launch_f64_redo(const ScanLaunch &l, int dtype)
 {
     const u32 *n = &l.c->n_redo;
+    if (l.sink.count) {      // the scan before it has scattered
+        if (dtype == DT_F16) launch_f64<3, 1, 6, DT_F16, true>(l, l.redo, n, nullptr, l.e_stop);
+        else if (dtype == DT_BF16) launch_f64<3, 1, 6, DT_BF16, true>(l, l.redo, n, nullptr, l.e_stop);
+        else launch_f64<3, 1, 6, DT_F32, true>(l, l.redo, n, nullptr, l.e_stop);
+        return;
+    }
     if (dtype == DT_F16) launch_f64<3, 1, 6, DT_F16>(l, l.redo, n, nullptr, l.e_stop);
     else if (dtype == DT_BF16) launch_f64<3, 1, 6, DT_BF16>(l, l.redo, n, nullptr, l.e_stop);
     else launch_f64<3, 1, 6, DT_F32>(l, l.redo, n, nullptr, l.e_stop);

@@ -301,7 +301,7 @@ struct FloatOp {
 
     template <int NG, typename GRAM, typename HOLD>
     __device__ __forceinline__ void list(const ScanItem &cur, const GRAM &gram, FloatScanSmem<NG> &sm, int R, u64 *__restrict__ keys,
-                                         int *__restrict__ deg, Prop *__restrict__ props, int *__restrict__ nprop, int lane,
+                                         int *__restrict__ deg, EdgeOut &out, int lane,
                                          u64 &tiles, u64 &rows, u64 &nprops_total, u32 &ev_lane, HOLD hold) const
     {
         const int l32 = lane & 31, half = lane >> 5;
@@ -319,10 +319,10 @@ struct FloatOp {
         const bool any_new = (newm[0] | newm[1]) != 0;
         bool left = false;
         u32 eid[NG], etgt[NG];
-        int eslot[NG];
+        int eplace[NG];
         u32 Kw[NG], badc[NG];
 #pragma unroll
-        for (int I = 0; I < NG; ++I) eslot[I] = -1, Kw[I] = 0, badc[I] = 0, eid[I] = 0, etgt[I] = 0;
+        for (int I = 0; I < NG; ++I) eplace[I] = -1, Kw[I] = 0, badc[I] = 0, eid[I] = 0, etgt[I] = 0;
         int np_base = 0;
         u32 ev_all = 0;
         float nmax = 0.f;
@@ -455,7 +455,7 @@ struct FloatOp {
                         if (pruned) {
                             eid[I] = key_id(kb);
                             etgt[I] = (u32)sm.id[tgt];
-                            eslot[I] = np_base + __popcll(pm & lanes_below(lane));
+                            eplace[I] = (np_base + __popcll(pm & lanes_below(lane))) | tgt << 8;
                         }
                         np_base += __popcll(pm);
                         if (I + 1 < NG) wave_sync();   // before the next block overwrites the tile
@@ -464,29 +464,28 @@ struct FloatOp {
             }
         }
         hold();     // every store of the trip comes after this point
+        out.flush(lane);
         if (left) {
             leave_vertex(u, fr, &sm.left, lane == 0, NG > 3);
             return;
         }
         ev_lane += ev_all;
+        u64 ekey[NG];
 #pragma unroll
-        for (int I = 0; I < NG; ++I)
-            if (eslot[I] >= 0) emit_redirect(make_key(OPEN_DIST, eid[I], 1u), etgt[I], props + (size_t)u * R + eslot[I]);
+        for (int I = 0; I < NG; ++I) ekey[I] = make_key(OPEN_DIST, eid[I], 1u);
+        out.template list<NG>(ekey, etgt, eplace, np_base, u, lane, sm.gt);
         const u64 K0 = (u64)Kw[0] | (NG > 1 ? ((u64)Kw[NG > 1 ? 1 : 0] << 32) : 0ull);
         const u64 K1 = NG > 2 ? ((u64)Kw[NG > 2 ? 2 : 0] | (NG > 3 ? ((u64)Kw[NG > 3 ? 3 : 0] << 32) : 0ull)) : 0ull;
         const int nk0 = __popcll(K0);
         if ((K0 >> lane) & 1ull) row[__popcll(K0 & lanes_below(lane))] = kreg[0] & ~1ull;
         if (NG > 2 && ((K1 >> lane) & 1ull)) row[nk0 + __popcll(K1 & lanes_below(lane))] = kreg[1] & ~1ull;
-        if (lane == 0) {
-            if (any_new) deg[u] = nk0 + __popcll(K1);
-            nprop[u] = np_base;
-        }
+        if (lane == 0 && any_new) deg[u] = nk0 + __popcll(K1);
         nprops_total += np_base;
     }
 
     template <int P, typename GRAM, typename HOLD>
     __device__ __forceinline__ void pack(const PackItem &cur, const GRAM &gram, FloatScanSmem<1> &sm, int R, u64 *__restrict__ keys,
-                                         int *__restrict__ deg, Prop *__restrict__ props, int *__restrict__ nprop, int lane,
+                                         int *__restrict__ deg, EdgeOut &out, int lane,
                                          u32 &tiles, u32 &rows, u32 &nprops_total, u32 &ev_lane, HOLD hold) const
     {
         constexpr int W = 32 / P;
@@ -505,6 +504,7 @@ struct FloatOp {
         const u32 below = (1u << l32) - 1u;
         bool pruned = false, kept = false, left = false;
         u32 Kcur = 0, pm = 0, tgt_id = 0;
+        int tgt_pos = 0;
         if (any_new) {
             const u32 vmask = (u32)__builtin_amdgcn_ballot_w64(valid && half == 0);
             wave_sync();
@@ -572,23 +572,24 @@ struct FloatOp {
                     ev_lane += (u32)__popc(E & Kcur & upto);
                 }
                 pm = (u32)__builtin_amdgcn_ballot_w64(pruned);
-                if (pruned) tgt_id = (u32)sm.id[tgt];
+                if (pruned) {
+                    tgt_id = (u32)sm.id[tgt];
+                    tgt_pos = tgt;
+                }
                 nprops_total += __popc(pm);
             }
         }
         hold();     // every store of the trip comes after this point
+        out.flush(lane);
         if (left) {
             for (u64 lm = __builtin_amdgcn_ballot_w64(leader); lm; lm &= lm - 1ull) {
                 leave_vertex(__builtin_amdgcn_readlane(u, __builtin_ctzll(lm)), fr, &sm.left, lane == 0, false);
             }
             return;
         }
-        if (pruned) emit_redirect(make_key(OPEN_DIST, key_id(kb), 1u), tgt_id, props + (size_t)u * R + __popc(pm & segmask & below));
+        out.pack(make_key(OPEN_DIST, key_id(kb), 1u), tgt_id, tgt_pos, u, __popc(pm & segmask & below), pm, leader, segmask, lane, sm.gt);
         if (kept && half == 0) keys[(size_t)u * R + __popc(Kcur & segmask & below)] = kb & ~1ull;
-        if (leader) {
-            if (any_new) deg[u] = __popc(Kcur & segmask);
-            nprop[u] = __popc(pm & segmask);
-        }
+        if (leader && any_new) deg[u] = __popc(Kcur & segmask);
     }
 };
 
@@ -663,15 +664,18 @@ __global__ __launch_bounds__(256) void k_float_sample(const char *__restrict__ G
 
 // This wavefront's vertices of a class, up to 16 NRC entries each, in groups of 16 rows; vertex i of the class is at(i).
 template <int DT, int NG, int NRC, int SMEM, typename AT>
-__device__ __forceinline__ void group_lists(const FloatRows &fr, int R, u64 *keys, int *deg, AT at, u32 gw, u32 nw, int &head, u32 n, Prop *props,
-                                            int *nprop, RoundCtr *ctr, char *sm)
+__device__ __forceinline__ void group_lists(const FloatRows &fr, int R, u64 *keys, int *deg, AT at, u32 gw, u32 nw, int &head, u32 n, const EdgeSink &sink,
+                                            RoundCtr *ctr, char *sm)
 {
     static_assert(sizeof(F32ScanSmem<NRC>) <= SMEM, "the group form works in the LDS of the tile form");
     const bool first_lane = (threadIdx.x & 63) == 0;
-    f32_scan_body<NG, 1, NRC, true, DT>(fr.X, fr.d, R, keys, deg, at, gw, nw, n, props, nprop, ctr,
+    f32_scan_body<NG, 1, NRC, true, DT>(fr.X, fr.d, R, keys, deg, at, gw, nw, n, sink.props, sink.nprop, ctr,
                                         [&](int u) {
                                             if (!fr.left) {
-                                                if (first_lane) fr.redo[atomicAdd(fr.n_redo, 1u)] = u;
+                                                if (first_lane) {
+                                                    sink.nprop[u] = 0;
+                                                    fr.redo[atomicAdd(fr.n_redo, 1u)] = u;
+                                                }
                                             } else {
                                                 if (first_lane) fr.left[u] = head;
                                                 head = u;
@@ -680,9 +684,10 @@ __device__ __forceinline__ void group_lists(const FloatRows &fr, int R, u64 *key
                                         *reinterpret_cast<F32ScanSmem<NRC> *>(sm));
 }
 
-// ... and what it has left, in double precision.
+// ... and what it has left, in double precision.  scatter: with the edges of these vertices.
 template <int DT, int NG, int NRC, int SMEM>
-__device__ __forceinline__ void finish_left(const FloatRows &fr, int R, u64 *keys, int *deg, int head, Prop *props, int *nprop, RoundCtr *ctr, char *sm)
+__device__ __forceinline__ void finish_left(const FloatRows &fr, int R, u64 *keys, int *deg, int head, const EdgeSink &sink, RoundCtr *ctr, char *sm,
+                                            bool scatter)
 {
     static_assert(sizeof(F32ScanSmem<NRC>) <= SMEM, "the group form works in the LDS of the tile form");
     int next = __builtin_amdgcn_readfirstlane(head);
@@ -691,25 +696,26 @@ __device__ __forceinline__ void finish_left(const FloatRows &fr, int R, u64 *key
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     u32 n = 0;
     for (int u = next; u >= 0; u = fr.left[u]) ++n;
-    f32_scan_body<NG, 1, NRC, false, DT>(fr.X, fr.d, R, keys, deg,
-                                         [&](u32) {      // asked in order
-                                             const int u = next;
-                                             next = fr.left[u];
-                                             return u;
-                                         },
-                                         0, 1, n, props, nprop, ctr, [](int) {},
-                                         *reinterpret_cast<F32ScanSmem<NRC> *>(sm));
+    const auto at = [&](u32) {      // asked in order
+        const int u = next;
+        next = fr.left[u];
+        return u;
+    };
+    f32_scan_body<NG, 1, NRC, false, DT>(fr.X, fr.d, R, keys, deg, at, 0, 1, n, sink.props, sink.nprop, ctr, [](int) {}, *reinterpret_cast<F32ScanSmem<NRC> *>(sm));
+    next = __builtin_amdgcn_readfirstlane(head);
+    if (scatter) scatter_walk(sink, at, 0, 1, n, R);
 }
 
 // Lists of at most 8, 16, 32 entries (blockIdx.y = degree class): 4, 2, 1 vertices per wavefront.
 template <int DT>
 __global__ __launch_bounds__(256, 4) void k_scan_float_small(
     const int8_t *__restrict__ G, u32 rowbytes, FloatRows fr, int R, u64 *__restrict__ keys, int *__restrict__ deg,
-    const int *__restrict__ lists, Prop *__restrict__ props, int *__restrict__ nprop, RoundCtr *ctr)
+    const int *__restrict__ lists, EdgeSink sink, RoundCtr *ctr)
 {
     typedef FloatOp<DT, DT == DT_F32> OP;
     constexpr int SMEM = sizeof(FloatScanSmem<1>);
     __shared__ FloatScanSmem<1> smem[4];
+    __shared__ PendingEdges pend[4];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     FloatScanSmem<1> &sm = smem[wave];
     const int y = blockIdx.y, rb = (int)rowbytes;
@@ -721,18 +727,20 @@ __global__ __launch_bounds__(256, 4) void k_scan_float_small(
     int head = -1;
     if (__builtin_expect(groups, 0)) {
         const auto at = [=](u32 i) { return list[i]; };
-        if (y < 2) group_lists<DT, 1, 1, SMEM>(fr, R, keys, deg, at, blockIdx.x * 4 + wave, gridDim.x * 4, head, n, props, nprop, ctr, (char *)&sm);
-        else group_lists<DT, 1, 2, SMEM>(fr, R, keys, deg, at, blockIdx.x * 4 + wave, gridDim.x * 4, head, n, props, nprop, ctr, (char *)&sm);
+        if (y < 2) group_lists<DT, 1, 1, SMEM>(fr, R, keys, deg, at, blockIdx.x * 4 + wave, gridDim.x * 4, head, n, sink, ctr, (char *)&sm);
+        else group_lists<DT, 1, 2, SMEM>(fr, R, keys, deg, at, blockIdx.x * 4 + wave, gridDim.x * 4, head, n, sink, ctr, (char *)&sm);
     } else {
+        EdgeOut out(sink, pend[wave], R);
         sm.left = -1;
         wave_sync();
-        if (y == 0) scan_packed_stream_body<OP, 4>(op, G, rb, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
-        else if (y == 1) scan_packed_stream_body<OP, 2>(op, G, rb, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
-        else scan_packed_stream_body<OP, 1>(op, G, rb, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
+        if (y == 0) scan_packed_stream_body<OP, 4>(op, G, rb, R, keys, deg, list, n, out, ctr, sm, blockIdx.x, gridDim.x);
+        else if (y == 1) scan_packed_stream_body<OP, 2>(op, G, rb, R, keys, deg, list, n, out, ctr, sm, blockIdx.x, gridDim.x);
+        else scan_packed_stream_body<OP, 1>(op, G, rb, R, keys, deg, list, n, out, ctr, sm, blockIdx.x, gridDim.x);
         op.report(ctr);
         head = sm.left;
     }
-    finish_left<DT, 1, 2, SMEM>(fr, R, keys, deg, head, props, nprop, ctr, (char *)&sm);
+    finish_left<DT, 1, 2, SMEM>(fr, R, keys, deg, head, sink, ctr, (char *)&sm, !groups);
+    if (__builtin_expect(groups, 0)) scatter_walk(sink, [=](u32 i) { return list[i]; }, blockIdx.x * 4 + wave, gridDim.x * 4, n, R);
 }
 
 // Classes C0 .. NC - 1 in one launch, the grid's blocks divided among them by their work (as k_update_scan_mfma_u8_all).
@@ -740,9 +748,10 @@ __global__ __launch_bounds__(256, 4) void k_scan_float_small(
 template <int DT, int NC, int C0, bool FINISH>
 __global__ __launch_bounds__(256, (NC == 6 ? 1 : 2)) void k_scan_float_all(
     const int8_t *__restrict__ G, u32 rowbytes, FloatRows fr, int R, u64 *__restrict__ keys, int *__restrict__ deg,
-    const int *__restrict__ lists, Prop *__restrict__ props, int *__restrict__ nprop, RoundCtr *ctr)
+    const int *__restrict__ lists, EdgeSink sink, RoundCtr *ctr)
 {
     typedef FloatOp<DT, DT == DT_F32> OP;
+    __shared__ PendingEdges pend[4];
     constexpr int NGMAX = NC - 2, SMEM = sizeof(FloatScanSmem<NGMAX>);
     static_assert(NC == 5 || NC == 6, "short lists plus two or three long-list classes");
     static_assert(C0 == 0 || C0 == 3, "with the short lists or without");
@@ -773,39 +782,49 @@ __global__ __launch_bounds__(256, (NC == 6 ? 1 : 2)) void k_scan_float_all(
         const int *list = lists + (size_t)cls * N;
         const auto at = [=](u32 i) { return list[i]; };
         if (C0 == 0 && cls == 1)
-            group_lists<DT, 1, 1, SMEM>(fr, R, keys, deg, [=](u32 i) { return i < n0 ? lists[i] : list[i - n0]; }, block * 4 + wave, mine * 4, head, n[1], props, nprop, ctr, sm);
-        else if (C0 == 0 && cls == 2) group_lists<DT, 1, 2, SMEM>(fr, R, keys, deg, at, block * 4 + wave, mine * 4, head, n[2], props, nprop, ctr, sm);
-        else if (cls == 3) group_lists<DT, 2, 4, SMEM>(fr, R, keys, deg, at, block * 4 + wave, mine * 4, head, n[3], props, nprop, ctr, sm);
-        else group_lists<DT, 3, 6, SMEM>(fr, R, keys, deg, at, block * 4 + wave, mine * 4, head, n[4], props, nprop, ctr, sm);
+            group_lists<DT, 1, 1, SMEM>(fr, R, keys, deg, [=](u32 i) { return i < n0 ? lists[i] : list[i - n0]; }, block * 4 + wave, mine * 4, head, n[1], sink, ctr, sm);
+        else if (C0 == 0 && cls == 2) group_lists<DT, 1, 2, SMEM>(fr, R, keys, deg, at, block * 4 + wave, mine * 4, head, n[2], sink, ctr, sm);
+        else if (cls == 3) group_lists<DT, 2, 4, SMEM>(fr, R, keys, deg, at, block * 4 + wave, mine * 4, head, n[3], sink, ctr, sm);
+        else group_lists<DT, 3, 6, SMEM>(fr, R, keys, deg, at, block * 4 + wave, mine * 4, head, n[4], sink, ctr, sm);
     } else {
         const int *list = lists + (size_t)cls * N;
+        EdgeOut out(sink, pend[wave], R);
         FloatScanSmem<1> &sm1 = *reinterpret_cast<FloatScanSmem<1> *>(sm);
         if (C0 == 0 && cls < 3) {
             sm1.left = -1;
             wave_sync();
-            if (cls == 0) scan_packed_stream_body<OP, 4>(op, G, rb, R, keys, deg, list, n[0], props, nprop, ctr, sm1, block, mine);
-            else if (cls == 1) scan_packed_stream_body<OP, 2>(op, G, rb, R, keys, deg, list, n[1], props, nprop, ctr, sm1, block, mine);
-            else scan_packed_stream_body<OP, 1>(op, G, rb, R, keys, deg, list, n[2], props, nprop, ctr, sm1, block, mine);
+            if (cls == 0) scan_packed_stream_body<OP, 4>(op, G, rb, R, keys, deg, list, n[0], out, ctr, sm1, block, mine);
+            else if (cls == 1) scan_packed_stream_body<OP, 2>(op, G, rb, R, keys, deg, list, n[1], out, ctr, sm1, block, mine);
+            else scan_packed_stream_body<OP, 1>(op, G, rb, R, keys, deg, list, n[2], out, ctr, sm1, block, mine);
             head = sm1.left;
         } else if (cls == 3) {
             FloatScanSmem<2> &sm2 = *reinterpret_cast<FloatScanSmem<2> *>(sm);
             sm2.left = -1;
             wave_sync();
-            scan_list_stream_body<OP, 2>(op, G, rb, R, keys, deg, list, n[3], props, nprop, ctr, sm2, block, mine);
+            scan_list_stream_body<OP, 2>(op, G, rb, R, keys, deg, list, n[3], out, ctr, sm2, block, mine);
             head = sm2.left;
         } else if (cls == 4) {
             FloatScanSmem<3> &sm3 = *reinterpret_cast<FloatScanSmem<3> *>(sm);
             sm3.left = -1;
             wave_sync();
-            scan_list_stream_body<OP, 3>(op, G, rb, R, keys, deg, list, n[4], props, nprop, ctr, sm3, block, mine);
+            scan_list_stream_body<OP, 3>(op, G, rb, R, keys, deg, list, n[4], out, ctr, sm3, block, mine);
             head = sm3.left;
         } else if (NC > 5 && cls == 5) {
-            scan_list_stream_body<OP, NGMAX>(op, G, rb, R, keys, deg, list, n[NC > 5 ? 5 : 0], props, nprop, ctr, smem[wave], block, mine);
+            scan_list_stream_body<OP, NGMAX>(op, G, rb, R, keys, deg, list, n[NC > 5 ? 5 : 0], out, ctr, smem[wave], block, mine);
         }
         op.report(ctr);
     }
-    if constexpr (!FINISH) return;
-    if (C0 == 0 && cls < 3) finish_left<DT, 1, 2, SMEM>(fr, R, keys, deg, head, props, nprop, ctr, sm);
-    else if (cls == 3) finish_left<DT, 2, 4, SMEM>(fr, R, keys, deg, head, props, nprop, ctr, sm);
-    else if (cls == 4) finish_left<DT, 3, 6, SMEM>(fr, R, keys, deg, head, props, nprop, ctr, sm);
+    if constexpr (FINISH) {
+        if (C0 == 0 && cls < 3) finish_left<DT, 1, 2, SMEM>(fr, R, keys, deg, head, sink, ctr, sm, !groups);
+        else if (cls == 3) finish_left<DT, 2, 4, SMEM>(fr, R, keys, deg, head, sink, ctr, sm, !groups);
+        else if (cls == 4) finish_left<DT, 3, 6, SMEM>(fr, R, keys, deg, head, sink, ctr, sm, !groups);
+    }
+    if (__builtin_expect(groups, 0)) {
+        u32 nc = 0;
+#pragma unroll
+        for (int c = C0; c < NC; ++c) nc = c == cls ? n[c] : nc;
+        const int *list = lists + (size_t)cls * N;
+        const u32 joined = C0 == 0 && cls == 1 ? n0 : 0u;      // (classes 0 and 1 as one)
+        scatter_walk(sink, [=](u32 i) { return i < joined ? lists[i] : list[i - joined]; }, block * 4 + wave, mine * 4, nc, R);
+    }
 }

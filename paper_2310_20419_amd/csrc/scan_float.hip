@@ -34,27 +34,27 @@ static void launch(const ScanLaunch &l, FloatRows fr, const void *rows, u32 rowb
     if (l.R > 32 && l.R <= 96 && l.N <= FLOAT_SHARED_MAX_N) {
         static const int per_cu = resident_blocks_per_cu(k_scan_float_all<DT, 5, 0, true>, 2);
         hipExtLaunchKernelGGL((k_scan_float_all<DT, 5, 0, true>), blocks(per_cu), dim3(256), 0, l.st, l.e_start, e_stop, 0, G, rowbytes, fr, l.R, l.keys, l.deg,
-                              l.lists, l.props, l.nprop, l.c);
+                              l.lists, l.sink, l.c);
         return;
     }
     static const int per_s = resident_blocks_per_cu(k_scan_float_small<DT>, 4);
     const int ny = 1 + (l.R > 8) + (l.R > 16);
     hipExtLaunchKernelGGL((k_scan_float_small<DT>), dim3(capped(cu_count() * per_s, l.N), ny), dim3(256), 0, l.st, l.e_start, l.R <= 32 ? e_stop : (hipEvent_t) nullptr, 0, G, rowbytes, fr,
-                          l.R, l.keys, l.deg, l.lists, l.props, l.nprop, l.c);
+                          l.R, l.keys, l.deg, l.lists, l.sink, l.c);
     if (l.R <= 32) return;
     if (l.R > 96) {
         static const int per_cu = resident_blocks_per_cu(k_scan_float_all<DT, 6, 3, true>, 1);
         hipExtLaunchKernelGGL((k_scan_float_all<DT, 6, 3, true>), blocks(per_cu), dim3(256), 0, l.st, nullptr, e_stop, 0, G, rowbytes, fr, l.R, l.keys, l.deg, l.lists,
-                              l.props, l.nprop, l.c);
+                              l.sink, l.c);
     } else if (l.N <= FINISH_MAX_N) {
         static const int per_cu = resident_blocks_per_cu(k_scan_float_all<DT, 5, 3, true>, 2);
         hipExtLaunchKernelGGL((k_scan_float_all<DT, 5, 3, true>), blocks(per_cu), dim3(256), 0, l.st, nullptr, e_stop, 0, G, rowbytes, fr, l.R, l.keys, l.deg, l.lists,
-                              l.props, l.nprop, l.c);
+                              l.sink, l.c);
     } else {
         static const int per_cu = resident_blocks_per_cu(k_scan_float_all<DT, 5, 3, false>, 2);
         fr.left = nullptr;
         hipExtLaunchKernelGGL((k_scan_float_all<DT, 5, 3, false>), blocks(per_cu), dim3(256), 0, l.st, nullptr, nullptr, 0, G, rowbytes, fr, l.R, l.keys, l.deg, l.lists,
-                              l.props, l.nprop, l.c);
+                              l.sink, l.c);
         launch_f64_redo(l, DT);
     }
 }

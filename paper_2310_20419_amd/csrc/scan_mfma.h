@@ -4,12 +4,14 @@
 // scan_u8.h, float rows: scan_float.h):
 //     tile_t, mac           accumulator of a 32 x 32 tile and the matrix instruction
 //     Smem<NG>              LDS of a wavefront; its gt, of 4 KB per 32 rows at least, is free until the Gram tiles are complete
-//     list<NG>, pack<P>     the body of Alg. 4's vertex loop for one vertex of up to 32 NG entries, for P vertices of up to 32 / P
+//     list<NG>, pack<P>     the body of Alg. 4's vertex loop for one vertex of up to 32 NG entries, for P vertices of up to 32 / P; its
+//                           edges go to an EdgeOut, which has delivered those of the trip before once hold() has been called
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "round.h"
+#include "scatter.h"
 #include "wave_prims.h"
 
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -184,7 +186,7 @@ __device__ __forceinline__ void stream_gram(const int8_t *const (&rp)[4 * NG], i
 template <typename OP, int NG, int KS>
 __device__ __forceinline__ void scan_list_body(const OP &op, const int8_t *__restrict__ X, int R, u64 *__restrict__ keys,
                                                int *__restrict__ deg, const int *__restrict__ list, u32 n_active,
-                                               Prop *__restrict__ props, int *__restrict__ nprop,
+                                               EdgeOut &out,
                                                RoundCtr *__restrict__ ctr, typename OP::template Smem<NG> &sm, u32 block, u32 nblocks)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar: the loop control stays on the scalar unit
@@ -223,7 +225,7 @@ __device__ __forceinline__ void scan_list_body(const OP &op, const int8_t *__res
             const unsigned long long j = (unsigned long long)it + 3ull * nw;
             u_after = j < n_active ? list[j] : -1;
         }
-        op.template list<NG>(cur, RowsGram<OP, NG, KS>{A0}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total,
+        op.template list<NG>(cur, RowsGram<OP, NG, KS>{A0}, sm, R, keys, deg, out, lane, tiles, rows, nprops_total,
                            ev_lane, [&] { hold(A1, aft); });
         cur = nxt;
         nxt = aft;
@@ -236,13 +238,14 @@ __device__ __forceinline__ void scan_list_body(const OP &op, const int8_t *__res
             const unsigned long long j = (unsigned long long)it + 3ull * nw;
             u_after = j < n_active ? list[j] : -1;
         }
-        op.template list<NG>(cur, RowsGram<OP, NG, KS>{A1}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total,
+        op.template list<NG>(cur, RowsGram<OP, NG, KS>{A1}, sm, R, keys, deg, out, lane, tiles, rows, nprops_total,
                            ev_lane, [&] { hold(A0, aft); });
         cur = nxt;
         nxt = aft;
         if ((unsigned long long)it + nw >= n_active) break;
         it += nw;
     }
+    out.flush(lane);
     u64 evals_algo = ev_lane;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) evals_algo += shfl_xor_u64(evals_algo, o);
@@ -254,7 +257,7 @@ __device__ __forceinline__ void scan_list_body(const OP &op, const int8_t *__res
 template <typename OP, int NG>
 __device__ __forceinline__ void scan_list_stream_body(const OP &op, const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
                                                       int *__restrict__ deg, const int *__restrict__ list, u32 n_active,
-                                                      Prop *__restrict__ props, int *__restrict__ nprop,
+                                                      EdgeOut &out,
                                                       RoundCtr *__restrict__ ctr, typename OP::template Smem<NG> &sm, u32 block, u32 nblocks)
 {
     // (two chunks for longer lists as well: 60,000 x 784 uint8 4.60 -> 4.79 ms, 1M x 96 101 -> 119, whose registers spill)
@@ -299,7 +302,7 @@ __device__ __forceinline__ void scan_list_stream_body(const OP &op, const int8_t
             const unsigned long long j = (unsigned long long)it + 3ull * nw;
             u_after = j < n_active ? list[j] : -1;
         }
-        op.template list<NG>(cur, StreamedGram<OP, NG>{G}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total,
+        op.template list<NG>(cur, StreamedGram<OP, NG>{G}, sm, R, keys, deg, out, lane, tiles, rows, nprops_total,
                            ev_lane, [&] {
 #pragma unroll
                                for (int i = 0; i < 4 * NG; ++i) {
@@ -313,6 +316,7 @@ __device__ __forceinline__ void scan_list_stream_body(const OP &op, const int8_t
         nxt = aft;
         if ((unsigned long long)it + nw >= n_active) break;
     }
+    out.flush(lane);
     u64 evals_algo = ev_lane;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) evals_algo += shfl_xor_u64(evals_algo, o);
@@ -323,11 +327,11 @@ __device__ __forceinline__ void scan_list_stream_body(const OP &op, const int8_t
 template <typename OP, int NG, int KS>
 __device__ __forceinline__ void scan_list_any(const OP &op, const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
                                               int *__restrict__ deg, const int *__restrict__ list, u32 n_active,
-                                              Prop *__restrict__ props, int *__restrict__ nprop,
+                                              EdgeOut &out,
                                               RoundCtr *__restrict__ ctr, typename OP::template Smem<NG> &sm, u32 block, u32 nblocks)
 {
-    if constexpr (KS == 0) scan_list_stream_body<OP, NG>(op, X, d, R, keys, deg, list, n_active, props, nprop, ctr, sm, block, nblocks);
-    else scan_list_body<OP, NG, KS>(op, X, R, keys, deg, list, n_active, props, nprop, ctr, sm, block, nblocks);
+    if constexpr (KS == 0) scan_list_stream_body<OP, NG>(op, X, d, R, keys, deg, list, n_active, out, ctr, sm, block, nblocks);
+    else scan_list_body<OP, NG, KS>(op, X, R, keys, deg, list, n_active, out, ctr, sm, block, nblocks);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -372,8 +376,7 @@ __device__ __forceinline__ void pack_gather(const int8_t *__restrict__ X, const 
 template <typename OP, int P, int KS>
 __device__ __forceinline__ void scan_packed_body(const OP &op, const int8_t *__restrict__ X, int R, u64 *__restrict__ keys,
                                                  int *__restrict__ deg, const int *__restrict__ list,
-                                                 u32 n_active, Prop *__restrict__ props,
-                                                 int *__restrict__ nprop, RoundCtr *__restrict__ ctr,
+                                                 u32 n_active, EdgeOut &out, RoundCtr *__restrict__ ctr,
                                                  typename OP::template Smem<1> &sm, u32 block, u32 nblocks)
 {
     constexpr int W = 32 / P;
@@ -411,7 +414,7 @@ __device__ __forceinline__ void scan_packed_body(const OP &op, const int8_t *__r
         pack_gather<P, KS>(X, nxt, pos, half, A1);
         PackItem aft = pack_item_load<P>(u_after, keys, deg, R, pos);
         u_after = vertex_of((unsigned long long)it + 3ull * nw);
-        op.template pack<P>(cur, RowsGram<OP, 1, KS>{A0}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total, ev_lane,
+        op.template pack<P>(cur, RowsGram<OP, 1, KS>{A0}, sm, R, keys, deg, out, lane, tiles, rows, nprops_total, ev_lane,
                             [&] { hold(A1, aft); });
         cur = nxt;
         nxt = aft;
@@ -421,13 +424,14 @@ __device__ __forceinline__ void scan_packed_body(const OP &op, const int8_t *__r
         pack_gather<P, KS>(X, nxt, pos, half, A0);
         aft = pack_item_load<P>(u_after, keys, deg, R, pos);
         u_after = vertex_of((unsigned long long)it + 3ull * nw);
-        op.template pack<P>(cur, RowsGram<OP, 1, KS>{A1}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total, ev_lane,
+        op.template pack<P>(cur, RowsGram<OP, 1, KS>{A1}, sm, R, keys, deg, out, lane, tiles, rows, nprops_total, ev_lane,
                             [&] { hold(A0, aft); });
         cur = nxt;
         nxt = aft;
         if ((unsigned long long)it + nw >= n_groups) break;
         it += nw;
     }
+    out.flush(lane);
     u64 evals_algo = ev_lane;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) evals_algo += shfl_xor_u64(evals_algo, o);
@@ -438,8 +442,7 @@ __device__ __forceinline__ void scan_packed_body(const OP &op, const int8_t *__r
 template <typename OP, int P>
 __device__ __forceinline__ void scan_packed_stream_body(const OP &op, const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
                                                         int *__restrict__ deg, const int *__restrict__ list,
-                                                        u32 n_active, Prop *__restrict__ props,
-                                                        int *__restrict__ nprop, RoundCtr *__restrict__ ctr,
+                                                        u32 n_active, EdgeOut &out, RoundCtr *__restrict__ ctr,
                                                         typename OP::template Smem<1> &sm, u32 block, u32 nblocks)
 {
     constexpr int W = 32 / P;
@@ -482,7 +485,7 @@ __device__ __forceinline__ void scan_packed_stream_body(const OP &op, const int8
         stage_fetch<1>(rp, last < 1 ? last : 1, d, lane, x1);
         PackItem aft = pack_item_load<P>(u_after, keys, deg, R, (lane & 31) % W);
         u_after = vertex_of((unsigned long long)it + 3ull * nw);
-        op.template pack<P>(cur, StreamedGram<OP, 1>{G}, sm, R, keys, deg, props, nprop, lane, tiles, rows, nprops_total, ev_lane,
+        op.template pack<P>(cur, StreamedGram<OP, 1>{G}, sm, R, keys, deg, out, lane, tiles, rows, nprops_total, ev_lane,
                             [&] {
 #pragma unroll
                                 for (int i = 0; i < 4; ++i) arrived(x0[i]), arrived(x1[i]);
@@ -492,6 +495,7 @@ __device__ __forceinline__ void scan_packed_stream_body(const OP &op, const int8
         nxt = aft;
         if ((unsigned long long)it + nw >= n_groups) break;
     }
+    out.flush(lane);
     u64 evals_algo = ev_lane;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) evals_algo += shfl_xor_u64(evals_algo, o);
@@ -501,11 +505,11 @@ __device__ __forceinline__ void scan_packed_stream_body(const OP &op, const int8
 template <typename OP, int P, int KS>
 __device__ __forceinline__ void scan_packed_any(const OP &op, const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
                                                 int *__restrict__ deg, const int *__restrict__ list, u32 n_active,
-                                                Prop *__restrict__ props, int *__restrict__ nprop,
+                                                EdgeOut &out,
                                                 RoundCtr *__restrict__ ctr, typename OP::template Smem<1> &sm, u32 block, u32 nblocks)
 {
-    if constexpr (KS == 0) scan_packed_stream_body<OP, P>(op, X, d, R, keys, deg, list, n_active, props, nprop, ctr, sm, block, nblocks);
-    else scan_packed_body<OP, P, KS>(op, X, R, keys, deg, list, n_active, props, nprop, ctr, sm, block, nblocks);
+    if constexpr (KS == 0) scan_packed_stream_body<OP, P>(op, X, d, R, keys, deg, list, n_active, out, ctr, sm, block, nblocks);
+    else scan_packed_body<OP, P, KS>(op, X, R, keys, deg, list, n_active, out, ctr, sm, block, nblocks);
 }
 
 // Divides the grid's blocks among NC classes in proportion to their work, n[c] lists of weight[c] each; the grid has

@@ -803,18 +803,19 @@ __device__ __forceinline__ void f32_scan_body(
     if (lane == 0 && rows) add_round_stats(ctr, evals_algo, tiles * 256ull + pair_evals, rows, nprops_total);
 }
 
-// The double-precision form over one list: the redo list, or (kernel variant 2) the active list of a degree class.
-template <int NG, int CH, int NRC, int DT>
+// The double-precision form over one list: the redo list, or (kernel variant 2) the active list of a degree class.  SCATTER: and the scatter of its edges.
+template <int NG, int CH, int NRC, int DT, bool SCATTER>
 __global__ __launch_bounds__(64 * 4, (NRC <= 2 ? 4 : NRC <= 5 ? 2 : 1)) void k_update_scan_f64(
     const char *__restrict__ X, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
-    const int *__restrict__ list, const u32 *__restrict__ n_list, Prop *__restrict__ props,
-    int *__restrict__ nprop, RoundCtr *__restrict__ ctr)
+    const int *__restrict__ list, const u32 *__restrict__ n_list, EdgeSink sink,
+    RoundCtr *__restrict__ ctr)
 {
     __shared__ F32ScanSmem<NRC> smem[4];
     stamp_scan_start(ctr);
     const u32 n = *n_list;
-    f32_scan_body<NG, CH, NRC, false, DT>(X, d, R, keys, deg, [=](u32 i) { return list[i]; }, blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4, n, props,
-                                          nprop, ctr, [](int) {}, smem[threadIdx.x >> 6]);
+    f32_scan_body<NG, CH, NRC, false, DT>(X, d, R, keys, deg, [=](u32 i) { return list[i]; }, blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4, n, sink.props,
+                                          sink.nprop, ctr, [](int) {}, smem[threadIdx.x >> 6]);
+    if constexpr (SCATTER) scatter_walk(sink, [=](u32 i) { return list[i]; }, blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4, n, R);
 }
 
 // The single-precision form of the degree classes from C0 on, up to lists of 16 NRCMAX entries, in one launch, the

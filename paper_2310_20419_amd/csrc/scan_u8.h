@@ -67,8 +67,7 @@ __global__ __launch_bounds__(256) void k_prepare_u8_rows(const uint8_t *__restri
 // registers in flight for the trips after this one (see arrived).
 template <int NG, typename GRAM, typename HOLD>
 __device__ __forceinline__ void scan_vertex_u8(const ScanItem &cur, const GRAM &gram, MfmaScanSmem<NG> &sm, int R, u64 *__restrict__ keys,
-                                               int *__restrict__ deg, Prop *__restrict__ props,
-                                               int *__restrict__ nprop, int lane, u64 &tiles, u64 &rows,
+                                               int *__restrict__ deg, EdgeOut &out, int lane, u64 &tiles, u64 &rows,
                                                u64 &nprops_total, u32 &ev_lane, HOLD hold)
 {
     const int l32 = lane & 31, half = lane >> 5;
@@ -87,10 +86,10 @@ __device__ __forceinline__ void scan_vertex_u8(const ScanItem &cur, const GRAM &
     // what the scan leaves to be stored: per block one redirected edge per lane, and the kept set
     u64 ekey[NG];
     u32 etgt[NG];
-    int eslot[NG];
+    int eplace[NG];
     u32 Kw[NG];                             // U' as bit masks over list positions, 32 per word (uniform)
 #pragma unroll
-    for (int I = 0; I < NG; ++I) eslot[I] = -1, Kw[I] = 0, ekey[I] = 0, etgt[I] = 0;
+    for (int I = 0; I < NG; ++I) eplace[I] = -1, Kw[I] = 0, ekey[I] = 0, etgt[I] = 0;
     int np_base = 0;
     if (any_new) {
     wave_sync();   // the previous vertex is done with the LDS tables
@@ -210,7 +209,7 @@ __device__ __forceinline__ void scan_vertex_u8(const ScanItem &cur, const GRAM &
                 // the redirect: v enters w's list
                 ekey[I] = make_key(dvw, key_id(kb), 1u);
                 etgt[I] = (u32)sm.id[tgt];
-                eslot[I] = np_base + __popcll(pm & lanes_below(lane));
+                eplace[I] = (np_base + __popcll(pm & lanes_below(lane))) | tgt << 8;
             }
             np_base += __popcll(pm);
             if (I + 1 < NG) wave_sync();   // before the next block overwrites the tiles
@@ -218,26 +217,21 @@ __device__ __forceinline__ void scan_vertex_u8(const ScanItem &cur, const GRAM &
     }
     }
     hold();     // every store of the trip comes after this point
-#pragma unroll
-    for (int I = 0; I < NG; ++I)
-        if (eslot[I] >= 0) emit_redirect(ekey[I], etgt[I], props + (size_t)u * R + eslot[I]);
+    out.flush(lane);
+    out.template list<NG>(ekey, etgt, eplace, np_base, u, lane, sm.gt);
     // kept entries, flag old, compacted back into the row
     const u64 K0 = (u64)Kw[0] | (NG > 1 ? ((u64)Kw[NG > 1 ? 1 : 0] << 32) : 0ull);
     const u64 K1 = NG > 2 ? ((u64)Kw[NG > 2 ? 2 : 0] | (NG > 3 ? ((u64)Kw[NG > 3 ? 3 : 0] << 32) : 0ull)) : 0ull;
     const int nk0 = __popcll(K0);
     if ((K0 >> lane) & 1ull) row[__popcll(K0 & lanes_below(lane))] = kreg[0] & ~1ull;
     if (NG > 2 && ((K1 >> lane) & 1ull)) row[nk0 + __popcll(K1 & lanes_below(lane))] = kreg[1] & ~1ull;
-    if (lane == 0) {
-        if (any_new) deg[u] = nk0 + __popcll(K1);
-        nprop[u] = np_base;
-    }
+    if (lane == 0 && any_new) deg[u] = nk0 + __popcll(K1);
     nprops_total += np_base;
 }
 
 template <int P, typename GRAM, typename HOLD>
 __device__ __forceinline__ void pack_vertices_u8(const PackItem &cur, const GRAM &gram, MfmaScanSmem<1> &sm, int R,
-                                                 u64 *__restrict__ keys, int *__restrict__ deg,
-                                                 Prop *__restrict__ props, int *__restrict__ nprop, int lane,
+                                                 u64 *__restrict__ keys, int *__restrict__ deg, EdgeOut &out, int lane,
                                                  u32 &tiles, u32 &rows, u32 &nprops_total, u32 &ev_lane, HOLD hold)
 {
     constexpr int W = 32 / P;
@@ -257,6 +251,7 @@ __device__ __forceinline__ void pack_vertices_u8(const PackItem &cur, const GRAM
     // what the scan leaves to be stored
     bool pruned = false, kept = false;
     u32 Kcur = 0, pm = 0, dvw = 0, tgt_id = 0;
+    int tgt_pos = 0;
     if (any_new) {
         const u32 vmask = (u32)__builtin_amdgcn_ballot_w64(valid && half == 0);
         wave_sync();   // the previous group is done with the LDS tables
@@ -341,18 +336,17 @@ __device__ __forceinline__ void pack_vertices_u8(const PackItem &cur, const GRAM
         if (pruned) {
             dvw = (u32)(di - sm.gt[l32 * GT_STRIDE + tgt]);
             tgt_id = (u32)sm.id[tgt];
+            tgt_pos = tgt;
         }
         nprops_total += __popc(pm);
     }
     hold();     // every store of the trip comes after this point
     // the redirect: v enters w's list
-    if (pruned) emit_redirect(make_key(dvw, key_id(kb), 1u), tgt_id, props + (size_t)u * R + __popc(pm & segmask & below));
+    out.flush(lane);
+    out.pack(make_key(dvw, key_id(kb), 1u), tgt_id, tgt_pos, u, __popc(pm & segmask & below), pm, leader, segmask, lane, sm.gt);
     // kept entries, flag old, compacted back into the row
     if (kept && half == 0) keys[(size_t)u * R + __popc(Kcur & segmask & below)] = kb & ~1ull;
-    if (leader) {
-        if (any_new) deg[u] = __popc(Kcur & segmask);
-        nprop[u] = __popc(pm & segmask);
-    }
+    if (leader && any_new) deg[u] = __popc(Kcur & segmask);
 }
 
 // What the walks below do with the rows of a vertex: uint8 rows.
@@ -374,10 +368,12 @@ template <int NG, int KS>
 __global__ __launch_bounds__(256, (NG == 1 ? 5 : NG == 2 ? 3 : KS == 0 && NG == 4 ? 1 : 2)) void k_update_scan_mfma_u8(
     const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
     int *__restrict__ deg, const int *__restrict__ list, const u32 *__restrict__ n_list,
-    Prop *__restrict__ props, int *__restrict__ nprop, RoundCtr *__restrict__ ctr)
+    EdgeSink sink, RoundCtr *__restrict__ ctr)
 {
     __shared__ MfmaScanSmem<NG> smem[4];
-    scan_list_any<U8Op, NG, KS>(U8Op(), X, d, R, keys, deg, list, *n_list, props, nprop, ctr, smem[threadIdx.x >> 6], blockIdx.x, gridDim.x);
+    __shared__ PendingEdges pend[4];
+    EdgeOut out(sink, pend[threadIdx.x >> 6], R);
+    scan_list_any<U8Op, NG, KS>(U8Op(), X, d, R, keys, deg, list, *n_list, out, ctr, smem[threadIdx.x >> 6], blockIdx.x, gridDim.x);
 }
 
 // The three short-list classes in one launch: blockIdx.y = degree class (lists of at most 8, 16, 32
@@ -385,18 +381,19 @@ __global__ __launch_bounds__(256, (NG == 1 ? 5 : NG == 2 ? 3 : KS == 0 && NG == 
 template <int KS>
 __global__ __launch_bounds__(256, 4) void k_update_scan_mfma_u8_small(
     const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
-    const int *__restrict__ lists, long long N, Prop *__restrict__ props, int *__restrict__ nprop,
-    RoundCtr *__restrict__ ctr)
+    const int *__restrict__ lists, long long N, EdgeSink sink, RoundCtr *__restrict__ ctr)
 {
     __shared__ MfmaScanSmem<1> smem[4];
+    __shared__ PendingEdges pend[4];
+    EdgeOut out(sink, pend[threadIdx.x >> 6], R);
     MfmaScanSmem<1> &sm = smem[threadIdx.x >> 6];
     const int y = blockIdx.y;
     const int *list = lists + (size_t)y * N;
     const u32 n = ctr->n_active[y];
     stamp_scan_start(ctr);
-    if (y == 0) scan_packed_any<U8Op, 4, KS>(U8Op(), X, d, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
-    else if (y == 1) scan_packed_any<U8Op, 2, KS>(U8Op(), X, d, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
-    else scan_packed_any<U8Op, 1, KS>(U8Op(), X, d, R, keys, deg, list, n, props, nprop, ctr, sm, blockIdx.x, gridDim.x);
+    if (y == 0) scan_packed_any<U8Op, 4, KS>(U8Op(), X, d, R, keys, deg, list, n, out, ctr, sm, blockIdx.x, gridDim.x);
+    else if (y == 1) scan_packed_any<U8Op, 2, KS>(U8Op(), X, d, R, keys, deg, list, n, out, ctr, sm, blockIdx.x, gridDim.x);
+    else scan_packed_any<U8Op, 1, KS>(U8Op(), X, d, R, keys, deg, list, n, out, ctr, sm, blockIdx.x, gridDim.x);
 }
 
 // Classes C0 .. NC - 1 in one launch, all of them resident together: the grid's blocks are divided among the
@@ -410,12 +407,13 @@ __global__ __launch_bounds__(256, 4) void k_update_scan_mfma_u8_small(
 template <int KS, int NC, int C0 = 0>
 __global__ __launch_bounds__(256, (KS == 0 && NC == 6 ? 1 : 2)) void k_update_scan_mfma_u8_all(
     const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
-    const int *__restrict__ lists, long long N, Prop *__restrict__ props, int *__restrict__ nprop,
-    RoundCtr *__restrict__ ctr)
+    const int *__restrict__ lists, long long N, EdgeSink sink, RoundCtr *__restrict__ ctr)
 {
     constexpr int NGMAX = NC - 2;
     static_assert(NC >= 4 && NC <= 6, "short lists plus one to three long-list classes");
     __shared__ MfmaScanSmem<NGMAX> smem[4];
+    __shared__ PendingEdges pend[4];
+    EdgeOut out(sink, pend[threadIdx.x >> 6], R);
     if (C0 == 0) stamp_scan_start(ctr);
     // work per list: 4, 2, 1 lists share a tile; among the longer classes in proportion to their NG (NG + 1) / 2
     // tiles (3 : 6 : 10; the division is sensitive there: 3 : 4.5 or 3 : 8 costs the 1M build 4 % of its scan time),
@@ -432,13 +430,13 @@ __global__ __launch_bounds__(256, (KS == 0 && NC == 6 ? 1 : 2)) void k_update_sc
     const int *list = lists + (size_t)cls * N;
     const int wave = threadIdx.x >> 6;
     MfmaScanSmem<1> &sm1 = *reinterpret_cast<MfmaScanSmem<1> *>(&smem[wave]);
-    if (C0 == 0 && cls == 0) scan_packed_any<U8Op, 4, KS>(U8Op(), X, d, R, keys, deg, list, n[0], props, nprop, ctr, sm1, block, mine);
-    else if (C0 == 0 && cls == 1) scan_packed_any<U8Op, 2, KS>(U8Op(), X, d, R, keys, deg, list, n[1], props, nprop, ctr, sm1, block, mine);
-    else if (C0 == 0 && cls == 2) scan_packed_any<U8Op, 1, KS>(U8Op(), X, d, R, keys, deg, list, n[2], props, nprop, ctr, sm1, block, mine);
+    if (C0 == 0 && cls == 0) scan_packed_any<U8Op, 4, KS>(U8Op(), X, d, R, keys, deg, list, n[0], out, ctr, sm1, block, mine);
+    else if (C0 == 0 && cls == 1) scan_packed_any<U8Op, 2, KS>(U8Op(), X, d, R, keys, deg, list, n[1], out, ctr, sm1, block, mine);
+    else if (C0 == 0 && cls == 2) scan_packed_any<U8Op, 1, KS>(U8Op(), X, d, R, keys, deg, list, n[2], out, ctr, sm1, block, mine);
     else if (cls == 3)
-        scan_list_any<U8Op, 2, KS>(U8Op(), X, d, R, keys, deg, list, n[3], props, nprop, ctr, *reinterpret_cast<MfmaScanSmem<2> *>(&smem[wave]), block, mine);
+        scan_list_any<U8Op, 2, KS>(U8Op(), X, d, R, keys, deg, list, n[3], out, ctr, *reinterpret_cast<MfmaScanSmem<2> *>(&smem[wave]), block, mine);
     else if (NC > 4 && cls == 4)
-        scan_list_any<U8Op, 3, KS>(U8Op(), X, d, R, keys, deg, list, n[NC > 4 ? 4 : 0], props, nprop, ctr, *reinterpret_cast<MfmaScanSmem<3> *>(&smem[wave]), block, mine);
+        scan_list_any<U8Op, 3, KS>(U8Op(), X, d, R, keys, deg, list, n[NC > 4 ? 4 : 0], out, ctr, *reinterpret_cast<MfmaScanSmem<3> *>(&smem[wave]), block, mine);
     else if (NC > 5 && cls == 5)
-        scan_list_any<U8Op, 4, KS>(U8Op(), X, d, R, keys, deg, list, n[NC > 5 ? 5 : 0], props, nprop, ctr, *reinterpret_cast<MfmaScanSmem<4> *>(&smem[wave]), block, mine);
+        scan_list_any<U8Op, 4, KS>(U8Op(), X, d, R, keys, deg, list, n[NC > 5 ? 5 : 0], out, ctr, *reinterpret_cast<MfmaScanSmem<4> *>(&smem[wave]), block, mine);
 }

@@ -1,0 +1,221 @@
+// How redirected edges reach their targets: inboxes, and the chains of what arrives past them.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "round.h"
+#include "wave_prims.h"
+
+#define INBOX_CAP 64   // redirected edges a vertex can receive per round without the overflow path
+
+// Bit j set iff lane j of this lane's row of 16 holds the same value, for the lanes reached by rotations R .. 15.
+template <int R>
+__device__ __forceinline__ u32 same_target_mask(u32 tgt, int sub)
+{
+    if constexpr (R >= 16) {
+        return 0u;
+    } else {
+        const u32 t = (u32)__builtin_amdgcn_update_dpp(0, (int)tgt, 0x120 + R, 0xF, 0xF, true);     // row_ror:R
+        const u32 here = (t == tgt ? 1u : 0u) << ((sub - R) & 15);
+        return here | same_target_mask<R + 1>(tgt, sub);
+    }
+}
+
+// Redirected edges that arrive past their target's inbox ("late") stay where they are, in props, and are chained: a
+// target has LATE_LISTS lists, arrival number a is on list (a - inbox) mod LATE_LISTS, so the lists are of equal
+// length and a wavefront walks all of them at once.  The heads need no clearing: how many edges are on a list follows
+// from the target's count.  They lie in the bin array (8 R bytes per vertex, 4 LATE_LISTS needed); rows of fewer than 32
+// slots have no room for them there and receive fewer edges, so they use 32 of their 64 inbox slots and keep the heads in the
+// other 32.  (A second pass over all active vertices, once bins had been handed out, used to move them: one launch more
+// per round and 1.06 of 26 ms at 1M x 128.  Whole builds: 5,000 x 32 381 -> 354 us, 100,000 x 128 4.61 -> 4.33
+// ms, 1M x 128 26.0 -> 25.5 ms.  A round in which one vertex receives 700,000 edges, second pass / as many lists as fit 4 R
+// bytes / now: rows of 8 slots 19.5 / 78.6 / 19.7 ms, of 16 19.5 / 40.4 / 19.7, of 96 19.5 / 20.8 / 19.8, the last because the links
+// of a chunk are asked for while the one before it is sorted; 7,000 edges, 8 slots: 0.29 / 0.87 / 0.28.)
+#define LATE_LISTS 64
+#define LATE_OPEN 512     // float rows: late edges of a vertex whose distances its merge computes
+static __host__ __device__ inline int round_inbox(int R) { return R < 32 ? 32 : INBOX_CAP; }
+
+// list head l of vertex x is at [x * stride + l]
+struct LateHeads {
+    u32 *base;
+    u32 stride;
+};
+static __host__ __device__ inline LateHeads late_heads(u64 *inbox, u64 *bins, int R)
+{
+    LateHeads h;
+    h.base = R < 32 ? (u32 *)(inbox + 32) : (u32 *)bins;
+    h.stride = R < 32 ? 2u * INBOX_CAP : (u32)LATE_LISTS;
+    return h;
+}
+
+// Where the edges of a round go.
+struct EdgeSink {
+    int *count;        // [N] edges received; null: the scan leaves its edges in props, how many in nprop, for k_scatter
+    u64 *inbox;
+    LateHeads heads;
+    Prop *props;       // [N * R] slots u * R .. are vertex u's
+    int *nprop;        // [N]
+};
+
+// The edge numbered `place` among those its target receives; `slot` is a place in props that no other edge has.
+__device__ __forceinline__ void deliver(const EdgeSink &s, int cap, u64 key, u32 tgt, int place, u32 slot)
+{
+    if (place < cap) {
+        s.inbox[(size_t)tgt * INBOX_CAP + place] = key;
+    } else {
+        s.props[slot].key = key;
+        s.props[slot].next = atomicExch(&s.heads.base[(size_t)tgt * s.heads.stride + ((u32)(place - cap) & (LATE_LISTS - 1u))], slot);
+    }
+}
+
+struct PendingEdges {
+    u64 key[64];
+    u32 tgt[64];       // (groups of short lists: slots in the upper half)
+    uint8_t pos[64];
+};
+
+// The scatter of the tile scans.  At the end of a trip a wavefront asks for the arrival numbers of the edges it has redirected, lanes that share
+// a target with one atomic, and at the end of the next one, when they have long been there, it writes the edges to their inboxes: the atomics, of which the part does 2.7 x
+// 10^10 a second and no more, run under the gathers, and no edge is stored and read again.  (The same work as a kernel of its own after the scan was bound by
+// them: 1M x 128 uint8 3.7 of 25.2 ms, 1M x 96 float32 8.1 of 102; at the end of a wavefront's walk it kept too few in flight: 100,000 x 128 a heavy round 63 + 23 -> 94 us.)
+// What waits from trip to trip is the key and the target of an edge in LDS, one edge per lane, and two registers.
+struct EdgeOut {
+    const EdgeSink &s;
+    PendingEdges &pend;
+    int R, cap;
+    u64 waiting = 0;    // lanes with an edge that waits (uniform)
+    u32 slot0 = 0;      // slot of the edge of lane 0, the others follow; all ones: slots in pend.tgt[32 ..]
+    int first = 0;      // the arrival number that the lane got for all edges that share its target
+    u32 how = 0;        // place among those | lane that has the number << 8
+
+    __device__ __forceinline__ EdgeOut(const EdgeSink &sink, PendingEdges &p, int R_) : s(sink), pend(p), R(R_), cap(round_inbox(R_)) {}
+
+    // All lanes.  No edge waits afterwards.
+    __device__ __forceinline__ void flush(int lane)
+    {
+        if (waiting == 0ull) return;
+        const int place = __shfl(first, (int)(how >> 8)) + (int)(how & 255u);
+        if ((waiting >> lane) & 1ull) {
+            u32 slot = slot0 + (u32)lane;
+            if (slot0 == 0xFFFFFFFFu) slot = pend.tgt[32 + (lane & 31)];
+            deliver(s, cap, pend.key[lane], pend.tgt[lane], place, slot);
+        }
+        waiting = 0ull;
+    }
+
+    // The edges of one vertex u: the lane holds those with place[I] >= 0, `np` in all, their targets by id, and as place their number and the target's
+    // position in the list << 8.
+    // scratch: 256 bytes per 32 entries.
+    template <int NG>
+    __device__ __forceinline__ void list(const u64 (&key)[NG], const u32 (&tgt)[NG], const int (&place)[NG], int np, int u, int lane, void *scratch)
+    {
+        if (!s.count) {
+#pragma unroll
+            for (int I = 0; I < NG; ++I)
+                if (place[I] >= 0) emit_redirect(key[I], tgt[I], s.props + (size_t)u * R + (place[I] & 255));
+            if (lane == 0) s.nprop[u] = np;
+            return;
+        }
+        if (np == 0) return;
+        u32 *cnt = (u32 *)scratch, *lead = cnt + 32 * NG;
+        if (NG > 2 && np > 64) {      // more edges than lanes: not worth a second round of registers, so these numbers are waited for
+            wave_sync();
+            if (lane < 32 * NG) cnt[lane] = 0u;
+            if (lane + 64 < 32 * NG) cnt[lane + 64] = 0u;
+            wave_sync();
+            u32 rank[NG];
+#pragma unroll
+            for (int I = 0; I < NG; ++I) rank[I] = place[I] >= 0 ? atomicAdd(&cnt[place[I] >> 8], 1u) : 1u;
+            wave_sync();
+#pragma unroll
+            for (int I = 0; I < NG; ++I)
+                if (rank[I] == 0u) lead[place[I] >> 8] = (u32)atomicAdd(&s.count[tgt[I]], (int)cnt[place[I] >> 8]);
+            wave_sync();
+#pragma unroll
+            for (int I = 0; I < NG; ++I)
+                if (place[I] >= 0) deliver(s, cap, key[I], tgt[I], (int)(lead[place[I] >> 8] + rank[I]), (u32)u * (u32)R + (u32)(place[I] & 255));
+            return;
+        }
+        wave_sync();
+#pragma unroll
+        for (int I = 0; I < NG; ++I)
+            if (place[I] >= 0) {
+                const int e = place[I] & 255;
+                pend.key[e] = key[I];
+                pend.tgt[e] = tgt[I];
+                pend.pos[e] = (uint8_t)(place[I] >> 8);
+            }
+        if (lane < 32 * NG) cnt[lane] = 0u;
+        if (NG > 2 && lane + 64 < 32 * NG) cnt[lane + 64] = 0u;
+        wave_sync();
+        const u32 t = pend.tgt[lane];
+        const u32 q = lane < np ? pend.pos[lane] : 0u;
+        u32 rank = 0u;
+        if (lane < np) {
+            rank = atomicAdd(&cnt[q], 1u);
+            if (rank == 0u) lead[q] = (u32)lane;
+        }
+        wave_sync();
+        const u32 l = lead[q], together = cnt[q];
+        if (lane < np && rank == 0u) first = atomicAdd(&s.count[t], (int)together);
+        how = rank | l << 8;
+        waiting = np < 64 ? (1ull << np) - 1ull : ~0ull;
+        slot0 = (u32)u * (u32)R;
+    }
+
+    // The edges of a group of short lists: at most one per lane, those of the lanes in `pm` (below 32), slot: in the vertex's own; `leader`: a lane
+    // for each vertex, all its lanes in segmask.  scratch: 256 bytes.
+    __device__ __forceinline__ void pack(u64 key, u32 tgt, int pos, int u, int slot, u32 pm, bool leader, u32 segmask, int lane, void *scratch)
+    {
+        const bool have = lane < 32 && ((pm >> (lane & 31)) & 1u);
+        if (!s.count) {
+            if (have) emit_redirect(key, tgt, s.props + (size_t)u * R + slot);
+            if (leader) s.nprop[u] = __popc(pm & segmask);
+            return;
+        }
+        if (pm == 0u) return;
+        u32 *cnt = (u32 *)scratch, *lead = cnt + 32;
+        wave_sync();
+        if (lane < 32) cnt[lane] = 0u;
+        wave_sync();
+        u32 rank = 0u;
+        if (have) {
+            pend.key[lane] = key;
+            pend.tgt[lane] = tgt;
+            pend.tgt[32 + lane] = (u32)u * (u32)R + (u32)slot;
+            rank = atomicAdd(&cnt[pos], 1u);
+            if (rank == 0u) lead[pos] = (u32)lane;
+        }
+        wave_sync();
+        const u32 l = lead[pos], together = cnt[pos];
+        if (have && rank == 0u) first = atomicAdd(&s.count[tgt], (int)together);
+        how = rank | l << 8;
+        waiting = (u64)pm;
+        slot0 = 0xFFFFFFFFu;
+    }
+};
+
+// The edges that a form without tiles has left in props[u * R ..], nprop[u] of them, for the vertices at(gw), at(gw + nw), ... below `end`: one wavefront each.
+template <typename AT>
+__device__ __forceinline__ void scatter_walk(const EdgeSink &s, AT at, u32 gw, u32 nw, u32 end, int R)
+{
+    if (!s.count) return;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");      // the edges are read by other lanes than wrote them
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    const int cap = round_inbox(R), lane = threadIdx.x & 63, sub = lane & 15, gbase = lane & ~15;
+    for (u32 i = gw; i < end; i += nw) {
+        const int u = at(i), np = s.nprop[u];
+        for (int p0 = 0; p0 < np; p0 += 64) {
+            const int p = p0 + lane;
+            const u32 slot = (u32)u * (u32)R + (u32)(p < np ? p : 0);
+            const u64 key = s.props[slot].key;
+            const u32 tgt = p < np ? s.props[slot].tgt : 0xFFFFFFFFu;
+            const u32 same = (1u << sub) | same_target_mask<1>(tgt, sub);
+            const int leader = __builtin_ctz(same);
+            int first = 0;
+            if (p < np && sub == leader) first = atomicAdd(&s.count[tgt], __popc(same));
+            first = __shfl(first, gbase + leader);
+            if (p < np) deliver(s, cap, key, tgt, first + __popc(same & ((1u << sub) - 1u)), slot);
+        }
+    }
+}
