@@ -260,19 +260,46 @@ __global__ __launch_bounds__(256) void k_prepare_listed_rows(const T *__restrict
 // vertex in the list of vertex x) is open, in 8-lane groups, in the order the wavefront holds them; every lane of the
 // wavefront takes part.  DT_U8: nothing is ever open.
 struct OpenEdges {
-    uint2 edge[64];
+    union {
+        uint2 edge[64];
+        uint8_t lane[128];      // see repeats
+    };
     u32 dist[64];
 };
-template <int DT>
-__device__ __forceinline__ u64 close_keys(u64 key, int x, bool have, OpenEdges *s, const char *__restrict__ X, int d, int lane)
+// From the second pass on 15-40 % of the redirected edges name an edge that another vertex redirects in the same round or that the list holds already;
+// their distances need not be computed, the merge would drop the second of two equal keys.  Lanes whose open key names the vertex of a key that some lane of
+// the same G holds in `list` or, of several open ones, all but one: found through a table of 128 lanes by vertex, in which the last one to write wins (a lane that loses its place to
+// another vertex counts as no repeat).  Merge with / without: 1M x 96 float32 25.6 / 26.3 ms, 1M x 960 182 / 188, 300,000 x 768 bfloat16 (whole build) 98.0 / 100.6; not in
+// k_merge_blocks, whose rounds wait for latency: 20,000 x 96 0.935 / 0.890.
+template <int G>
+__device__ __forceinline__ bool repeats(u64 key, bool open, u64 list, bool listed, OpenEdges *s, int lane)
+{
+    constexpr u32 SLOTS = 2 * G;
+    const u32 base = (u32)(lane / G) * SLOTS;
+    const u32 at = base + ((key_id(key) * 0x9E3779B1u) >> 16) % SLOTS, lat = base + ((key_id(list) * 0x9E3779B1u) >> 16) % SLOTS;
+    wave_sync();
+    if (open) s->lane[at] = (uint8_t)lane;
+    wave_sync();
+    if (listed) s->lane[lat] = (uint8_t)(64 + lane);
+    wave_sync();
+    const u32 w = open ? s->lane[at] : (u32)lane;
+    const u32 of_open = (u32)__shfl((int)key_id(key), (int)(w & 63u)), of_list = (u32)__shfl((int)key_id(list), (int)(w & 63u));
+    return open && w != (u32)lane && (w >= 64u ? of_list : of_open) == key_id(key);
+}
+template <int DT, int G, bool SEEK>
+__device__ __forceinline__ u64 close_keys(u64 key, int x, bool have, u64 list, bool listed, OpenEdges *s, const char *__restrict__ X, int d, int lane)
 {
     if constexpr (DT == DT_U8) {
         return key;
     } else {
-        const bool open = have && key_dist(key) == OPEN_DIST;
+        bool open = have && key_dist(key) == OPEN_DIST;
+        if (__builtin_amdgcn_ballot_w64(open) == 0ull) return key;
+        if (SEEK && repeats<G>(key, open, list, listed, s, lane)) {
+            key = KEY_PAD;
+            open = false;
+        }
         const u64 om = __builtin_amdgcn_ballot_w64(open);
         const int total = __popcll(om);
-        if (total == 0) return key;
         const size_t rb = (size_t)d * dt_size(DT);
         const int mine = __popcll(om & lanes_below(lane)), grp = lane >> 3, sub = lane & 7;
         wave_sync();
@@ -502,7 +529,7 @@ __device__ __forceinline__ MergeItem merge_item_load(int x, int R, const u64 *ke
 }
 
 // Wavefront `first` of `nwaves` that share the list tlist[0 .. n).
-template <int G, int DT>
+template <int G, int DT, bool SEEK>
 __device__ __forceinline__ void merge_group_body(int R, u64 *keys, int *deg, const int *tlist, u32 n, u32 first, u32 nwaves,
                                                  int *cnt, const u64 *inbox, int8_t *tcls, int use_classes, RoundCtr *ctr,
                                                  OpenEdges *s_open, const char *__restrict__ X, int d)
@@ -535,7 +562,7 @@ __device__ __forceinline__ void merge_group_body(int R, u64 *keys, int *deg, con
         u64 k = KEY_PAD;
         if (sub < nb) k = cur.kr;
         else if (G - 1 - sub < c) k = cur.ki;
-        k = close_keys<DT>(k, x, sub >= nb && G - 1 - sub < c, s_open, X, d, lane);
+        k = close_keys<DT, G, SEEK>(k, x, sub >= nb && G - 1 - sub < c, k, sub < nb, s_open, X, d, lane);
         k = group_sort<G>(k, lane);
         u64 prev = shfl_up1_u64(k);
         if (sub == 0) prev = KEY_PAD;
@@ -597,7 +624,7 @@ __device__ __forceinline__ LateEdge late_edge(const Prop *props, u32 at, bool ha
     return e;
 }
 
-template <int DT>
+template <int DT, bool SEEK>
 __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, const int *tlist, u32 n, u32 first, u32 nwaves,
                                                    int *cnt, const u64 *inbox,
                                                    LateHeads heads, const Prop *props, int8_t *tcls,
@@ -623,7 +650,7 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
 
         const int x = __builtin_amdgcn_readfirstlane(cur.x);
         const int nb = __builtin_amdgcn_readfirstlane(cur.nb), c = __builtin_amdgcn_readfirstlane(cur.c);
-        cur.in = close_keys<DT>(cur.in, x, 63 - lane < (c < cap ? c : cap), s_open, X, d, lane);
+        cur.in = close_keys<DT, 64, SEEK>(cur.in, x, 63 - lane < (c < cap ? c : cap), cur.r0, lane < nb, s_open, X, d, lane);
         bool any_new = false;
         int nd;
         if (c <= cap && nb + c <= 128) {
@@ -640,7 +667,7 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
                 // a full inbox, and at most one late edge per list: the lists from the top lane down, above the kept entries
                 u64 k[2];
                 k[0] = lane < nb ? cur.r0 : late_edge(props, 63 - lane < late ? head[63 - lane] : 0u, 63 - lane < late).key;
-                k[0] = close_keys<DT>(k[0], x, lane >= nb && 63 - lane < late, s_open, X, d, lane);
+                k[0] = close_keys<DT, 64, SEEK>(k[0], x, lane >= nb && 63 - lane < late, k[0], lane < nb, s_open, X, d, lane);
                 k[1] = 63 - lane < ca ? cur.in : KEY_PAD;
                 wave_sort<2>(k, lane);
                 nd = wave_unique_prefix<2>(k, lane, R, row, &any_new, &dropped);
@@ -652,7 +679,7 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
                 k[0] = lane < nb ? cur.r0 : KEY_PAD;
                 k[1] = lane + 64 < nb ? cur.r1 : KEY_PAD;
                 k[2] = 63 - lane < ca ? cur.in : KEY_PAD;
-                k[3] = close_keys<DT>(first.key, x, lane < late, s_open, X, d, lane);
+                k[3] = close_keys<DT, 64, SEEK>(first.key, x, lane < late, k[0], lane < nb, s_open, X, d, lane);
                 LateEdge a = late_edge(props, first.next, LATE_LISTS + lane < late);
                 for (int at = LATE_LISTS;; at += 2 * LATE_LISTS) {      // edges taken so far; `a` is the next one of my list
                     wave_sort<4>(k, lane);
@@ -663,8 +690,8 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
                     k[1] = lane + 64 < nd ? s_stage[wave][lane + 64] : KEY_PAD;
                     wave_sync();
                     if (at >= late) break;
-                    k[2] = close_keys<DT>(a.key, x, at + lane < late, s_open, X, d, lane);
-                    k[3] = close_keys<DT>(b.key, x, at + LATE_LISTS + lane < late, s_open, X, d, lane);
+                    k[2] = close_keys<DT, 64, SEEK>(a.key, x, at + lane < late, k[0], lane < nd, s_open, X, d, lane);
+                    k[3] = close_keys<DT, 64, SEEK>(b.key, x, at + LATE_LISTS + lane < late, k[0], lane < nd, s_open, X, d, lane);
                     a = late_edge(props, b.next, at + 2 * LATE_LISTS + lane < late);
                 }
                 if (lane < nd) row[lane] = k[0];
@@ -695,10 +722,10 @@ __global__ __launch_bounds__(BLOCK, (DT == DT_U8 ? 1 : 5)) void k_merge(long lon
     const int *tlist = tlists + (size_t)y * N;
     int8_t *tc = tcls + (size_t)y * N;
     const u32 n = n_touched[y], first = blockIdx.x * WAVES_PER_BLOCK + (threadIdx.x >> 6), nwaves = gridDim.x * WAVES_PER_BLOCK;
-    if (y == 0) merge_group_body<16, DT>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, tc, use_classes, ctr, so, X, d);
-    else if (y == 1) merge_group_body<32, DT>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, tc, use_classes, ctr, so, X, d);
-    else if (y == 2) merge_group_body<64, DT>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, tc, use_classes, ctr, so, X, d);
-    else merge_general_body<DT>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, heads, props, tc, use_classes, s_stage, ctr, so, X, d);
+    if (y == 0) merge_group_body<16, DT, true>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, tc, use_classes, ctr, so, X, d);
+    else if (y == 1) merge_group_body<32, DT, true>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, tc, use_classes, ctr, so, X, d);
+    else if (y == 2) merge_group_body<64, DT, true>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, tc, use_classes, ctr, so, X, d);
+    else merge_general_body<DT, true>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, heads, props, tc, use_classes, s_stage, ctr, so, X, d);
 }
 
 // Classify, merge and compact of a round in one launch, for inputs whose rounds wait for launches (4-6 us each) rather than for
@@ -737,10 +764,10 @@ __global__ __launch_bounds__(BLOCK, (DT == DT_U8 ? 1 : 5)) void k_merge_blocks(l
         __syncthreads();
     }
     // (the classes start with different wavefronts)
-    merge_group_body<16, DT>(R, keys, deg, s_list[0], s_n[0], wave, 4, cnt, inbox, s_cls[0], use_classes, ctr, so, X, d);
-    merge_group_body<32, DT>(R, keys, deg, s_list[1], s_n[1], (wave + 3) & 3, 4, cnt, inbox, s_cls[1], use_classes, ctr, so, X, d);
-    merge_group_body<64, DT>(R, keys, deg, s_list[2], s_n[2], (wave + 2) & 3, 4, cnt, inbox, s_cls[2], use_classes, ctr, so, X, d);
-    merge_general_body<DT>(R, keys, deg, s_list[3], s_n[3], (wave + 1) & 3, 4, cnt, inbox, heads, props, s_cls[3], use_classes, s_stage, ctr, so, X, d);
+    merge_group_body<16, DT, false>(R, keys, deg, s_list[0], s_n[0], wave, 4, cnt, inbox, s_cls[0], use_classes, ctr, so, X, d);
+    merge_group_body<32, DT, false>(R, keys, deg, s_list[1], s_n[1], (wave + 3) & 3, 4, cnt, inbox, s_cls[1], use_classes, ctr, so, X, d);
+    merge_group_body<64, DT, false>(R, keys, deg, s_list[2], s_n[2], (wave + 2) & 3, 4, cnt, inbox, s_cls[2], use_classes, ctr, so, X, d);
+    merge_general_body<DT, false>(R, keys, deg, s_list[3], s_n[3], (wave + 1) & 3, 4, cnt, inbox, heads, props, s_cls[3], use_classes, s_stage, ctr, so, X, d);
     __syncthreads();
     // at most `span` items in all: one per thread
     int k = -1, item = 0;
