@@ -143,14 +143,14 @@ __global__ __launch_bounds__(BLOCK) void k_update_scan(const void *X, int d, int
 // ------------------------------------------------------ UpdateNeighbors: merge
 // Vertices x with cnt[x] > list_min are appended to `list`; those with cnt[x] > bin_min get a bin of
 // cnt[x] - bin_sub keys starting at binoff[x] (others: binoff = -1).  One pair of atomics per 1024
-// vertices.  Optionally clears zero_a[] and zero_b[], sets thr[] to "keep all", and marks in cand[]
-// the vertices with deg[x] + cnt[x] > cand_R.
+// vertices.  Optionally clears zero_a[] and zero_b[], sets thr[] to "keep all", marks in cand[]
+// the vertices with deg[x] + cnt[x] > cand_R, and lists in flagged[] those with flag[x] >= 0.
 __global__ __launch_bounds__(1024) void k_assign_bins(long long N, const int *cnt, int list_min, int bin_min,
                                                       int bin_sub, int *binoff, u32 *bin_cursor, int *list,
                                                       u32 *n_list, int *zero_a, int *zero_b, u64 *thr,
-                                                      const int *deg, int cand_R, int8_t *cand)
+                                                      const int *deg, int cand_R, int8_t *cand, const int8_t *flag, int *flagged, u32 *n_flagged)
 {
-    __shared__ u32 s_sum[16], s_num[16], s_base[2];
+    __shared__ u32 s_sum[16], s_num[16], s_flag[16], s_base[3];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long long x = (long long)blockIdx.x * 1024 + threadIdx.x;
     int c = 0;
@@ -170,18 +170,25 @@ __global__ __launch_bounds__(1024) void k_assign_bins(long long N, const int *cn
         if (lane >= o) incl += v;
     }
     const u64 hb = __builtin_amdgcn_ballot_w64(in_list);
-    if (lane == 63) { s_sum[wave] = incl; s_num[wave] = (u32)__popcll(hb); }
+    const bool is_flagged = flag && x < N && flag[x] >= 0;
+    const u64 fb = __builtin_amdgcn_ballot_w64(is_flagged);
+    if (lane == 63) { s_sum[wave] = incl; s_num[wave] = (u32)__popcll(hb); s_flag[wave] = (u32)__popcll(fb); }
     __syncthreads();
     if (threadIdx.x == 0) {
-        u32 ts = 0, tn = 0;
-        for (int w = 0; w < 16; ++w) { u32 a = s_sum[w], b = s_num[w]; s_sum[w] = ts; s_num[w] = tn; ts += a; tn += b; }
-        s_base[0] = ts ? atomicAdd(bin_cursor, ts) : 0u;
-        s_base[1] = tn ? atomicAdd(n_list, tn) : 0u;
+        u32 ts = 0, tn = 0, tf = 0;
+        for (int w = 0; w < 16; ++w) {
+            const u32 a = s_sum[w], b = s_num[w], c = s_flag[w];
+            s_sum[w] = ts; s_num[w] = tn; s_flag[w] = tf;
+            ts += a; tn += b; tf += c;
+        }
+        const u32 b0 = ts ? atomicAdd(bin_cursor, ts) : 0u, b1 = tn ? atomicAdd(n_list, tn) : 0u, b2 = tf ? atomicAdd(n_flagged, tf) : 0u;
+        s_base[0] = b0; s_base[1] = b1; s_base[2] = b2;
     }
     __syncthreads();
     if (x < N) {
         binoff[x] = mine ? (int)(s_base[0] + s_sum[wave] + incl - mine) : -1;
         if (in_list) list[s_base[1] + s_num[wave] + __popcll(hb & lanes_below(lane))] = (int)x;
+        if (is_flagged) flagged[s_base[2] + s_flag[wave] + __popcll(fb & lanes_below(lane))] = (int)x;
     }
 }
 
@@ -845,6 +852,15 @@ __global__ __launch_bounds__(256) void k_store_classes(const u32 *n_touched, con
 }
 
 // ------------------------------------------------------------ AddReverseEdges
+// The first kernel of a call clears the call's cursors and the lengths of the next round's lists (n_next may be null), which only kernels after it use.
+__device__ __forceinline__ void clear_cursors(u32 *misc, u32 *n_next)
+{
+    if (blockIdx.x == 0 && threadIdx.x < 16) {
+        misc[threadIdx.x] = 0u;
+        if (n_next && threadIdx.x < NDEG) n_next[threadIdx.x] = 0u;
+    }
+}
+
 // The union and the out-degree cut of Alg. 5 need, for every x, the edges that point to x.  Every edge (u, v) takes an arrival
 // number at v (one atomic on fill[v]); the first INBOX_CAP arrivals are written to v's inbox as
 // key(delta, u, new).  A later arrival is remembered with its edge (late[] holds its number, over[u]
@@ -854,8 +870,9 @@ __global__ __launch_bounds__(256) void k_store_classes(const u32 *n_touched, con
 // kernel is bound by its three dependent trips to memory: degree, list entry, arrival number).
 __global__ __launch_bounds__(BLOCK) void k_reverse_scatter(long long N, int R, const u64 *keys, const int *deg,
                                                            int *fill, u64 *inbox, u32 *late, u64 *over,
-                                                           int8_t *mark)
+                                                           int8_t *mark, u32 *misc, u32 *n_next)
 {
+    clear_cursors(misc, n_next);
     const int lane = threadIdx.x & 63, sub = lane & 15, gsh = lane & ~15;
     const long long u = ((long long)blockIdx.x * BLOCK + threadIdx.x) >> 4;
     const bool valid = u < N;
@@ -956,9 +973,11 @@ __device__ __forceinline__ void for_each_edge_of_chunk(long long N, int W, const
 }
 
 __global__ __launch_bounds__(BIN_THREADS) void k_bin_count(long long N, int W, const u64 *__restrict__ keys,
-                                                           const int *__restrict__ deg, u32 nranges, u32 *__restrict__ blockhist)
+                                                           const int *__restrict__ deg, u32 nranges, u32 *__restrict__ blockhist,
+                                                           u32 *misc, u32 *n_next)
 {
     __shared__ u32 hist[RANGE_MAX];
+    clear_cursors(misc, n_next);
     for (u32 r = threadIdx.x; r < nranges; r += BIN_THREADS) hist[r] = 0;
     __syncthreads();
     for_each_edge_of_chunk(N, W, keys, deg, [&](long long, u64 k) { atomicAdd(&hist[key_id(k) >> RANGE_BITS], 1u); });
@@ -2090,7 +2109,7 @@ static void launch_compact_all(const Workspace &w, long long N, int t_next, hipS
 // AddReverseEdges; the active lists for round t_next are rebuilt from scratch (t_next < 0: only vcls[], the
 // class of every vertex that holds a "new" entry, is written).  Expects fill[] == 0
 // and leaves it so.  Between rounds nprop[], tcls[], props[] and touched[] are free: they serve as the
-// second in-edge count, the per-vertex marks, the late arrival numbers and their position masks.  misc: [0] bin cursor, [1] vertices with a bin (union and out-degree cut), [4..11] lengths of the compaction of rowflag[] ([4]: the flagged lists),
+// second in-edge count, the per-vertex marks, the late arrival numbers and their position masks.  misc: [0] bin cursor, [1] vertices with a bin (union and out-degree cut), [4] flagged lists,
 // [2] bin cursor, [3] vertices with more than R incoming edges (in-degree cut).
 static hipError_t launch_reverse(const Workspace &w, long long N, int R, int use_classes, u64 *keys, int *deg,
                                  int t_next, hipStream_t st, hipEvent_t e_stop = nullptr, int W = 0)
@@ -2101,14 +2120,13 @@ static hipError_t launch_reverse(const Workspace &w, long long N, int R, int use
     int8_t *cand = w.tcls, *rowflag = w.tcls + N, *mark = w.tcls + 2 * N;
     u32 *late = (u32 *)w.props;          // one word per list slot (props is 16 bytes per slot)
     u64 *over = (u64 *)w.touched;        // two words per vertex (touched is 16 bytes per vertex)
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, w.misc, (size_t)16);
-    if (t_next >= 0) hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, w.ctr[t_next].n_active, (size_t)NDEG);
+    u32 *n_next = t_next >= 0 ? w.ctr[t_next].n_active : nullptr;
     // union with reversed edges, out-lists cut to R
     // the transposition: one arrival-number atomic per edge, or (large N, see k_bin_count) binned by target range
     const bool binned = w.blockhist && g_transpose_path != 1 && (g_transpose_path == 2 || N >= BIN_MIN_N);
     if (binned) {
         const unsigned nb = (unsigned)bin_blocks(N), nr = (unsigned)bin_ranges(N);
-        hipLaunchKernelGGL(k_bin_count, dim3(nb), dim3(BIN_THREADS), 0, st, N, W, (const u64 *)keys, (const int *)deg, nr, w.blockhist);
+        hipLaunchKernelGGL(k_bin_count, dim3(nb), dim3(BIN_THREADS), 0, st, N, W, (const u64 *)keys, (const int *)deg, nr, w.blockhist, w.misc, n_next);
         hipLaunchKernelGGL(k_bin_offsets, dim3((nr + 63) / 64), dim3(1024), 0, st, nb, nr, w.blockhist, w.range_tot);
         hipLaunchKernelGGL(k_bin_bases, dim3(1), dim3(1024), 0, st, nr, (const u32 *)w.range_tot, w.range_base);
         hipLaunchKernelGGL(k_bin_partition, dim3(nb), dim3(BIN_THREADS), 0, st, N, W, (const u64 *)keys, (const int *)deg, nr,
@@ -2117,9 +2135,10 @@ static hipError_t launch_reverse(const Workspace &w, long long N, int R, int use
                            (const int *)deg, w.fill, w.inbox, w.binoff, w.bins, w.misc + 0, w.cnt, cnt_in, cand);
     } else {
         hipLaunchKernelGGL(k_reverse_scatter, dim3((unsigned)((N * 16 + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0, st, N, W, keys, deg,
-                           w.fill, w.inbox, late, over, mark);
+                           w.fill, w.inbox, late, over, mark, w.misc, n_next);
         hipLaunchKernelGGL(k_assign_bins, dim3(tb), dim3(1024), 0, st, N, w.fill, INBOX_CAP, INBOX_CAP, INBOX_CAP,
-                           w.binoff, w.misc + 0, w.hubs, w.misc + 1, w.cnt, cnt_in, (u64 *)nullptr, deg, R, cand);
+                           w.binoff, w.misc + 0, w.hubs, w.misc + 1, w.cnt, cnt_in, (u64 *)nullptr, deg, R, cand,
+                           (const int8_t *)nullptr, (int *)nullptr, (u32 *)nullptr);
         hipLaunchKernelGGL(k_reverse_surplus, dim3(vb), dim3(BLOCK), 0, st, N, W, keys, late, over, mark, w.binoff,
                            w.bins, w.misc + 1);
     }
@@ -2128,13 +2147,11 @@ static hipError_t launch_reverse(const Workspace &w, long long N, int R, int use
     hipLaunchKernelGGL(k_reverse_merge, dim3(rm_blocks < (vb + 1) / 2 ? rm_blocks : (vb + 1) / 2), dim3(BLOCK), 0, st, N, W, R, keys,
                        deg, w.fill, w.inbox, w.binoff, w.bins, cand, cnt_in, rowflag, w.vcls, use_classes);
     // in-lists cut to R; only vertices with more than R incoming edges need a bin, and only the flagged lists
-    // (class 0 of rowflag[]) are walked: they are compacted into the first active list, which is free until
+    // (class 0 of rowflag[]) are walked: the launch that hands out the bins lists them in the first active list, which is free until
     // the lists of the next round are rebuilt at the end
     int *flagged = w.lists;
-    hipLaunchKernelGGL(k_compact_classes, dim3(256, 1), dim3(1024), 0, st, (const u32 *)nullptr, (u32)N, (const int *)nullptr,
-                       (const int8_t *)rowflag, flagged, N, w.misc + 4, 0u, (int8_t *)nullptr);
     hipLaunchKernelGGL(k_assign_bins, dim3(tb), dim3(1024), 0, st, N, cnt_in, R, R, 0, w.binoff, w.misc + 2, w.hubs,
-                       w.misc + 3, w.cnt, (int *)nullptr, w.thr, (const int *)nullptr, 0, (int8_t *)nullptr);
+                       w.misc + 3, w.cnt, (int *)nullptr, w.thr, (const int *)nullptr, 0, (int8_t *)nullptr, (const int8_t *)rowflag, flagged, w.misc + 4);
     hipLaunchKernelGGL(k_fill_bins, dim3(capped(persistent_blocks(), N)), dim3(BLOCK), 0, st, W, (const u64 *)keys, (const int *)deg,
                        (const int *)flagged, (const u32 *)(w.misc + 4), w.binoff, w.cnt, w.bins, 0u, w.misc + 3);
     hipLaunchKernelGGL(k_incap_threshold, dim3(capped(persistent_blocks(), N)), dim3(BLOCK), 0, st, R, w.hubs, w.misc + 3,
