@@ -77,12 +77,12 @@ __global__ __launch_bounds__(BLOCK) void k_random_graph(const void *X, long long
     u64 *row = keys + (size_t)u * R;
     if (S <= 32) {     // the upper half of the wavefront sorts padding
         u64 k = lane < S ? make_key(s_tab[wave].dist[lane], (u32)ids[lane], 1u) : KEY_PAD;
-        k = group_sort<32>(k, lane);
+        k = group_sort<32>(k);
         if (lane < S) row[lane] = k;
     } else if (S <= 64) {
         u64 k[1];
         k[0] = lane < S ? make_key(s_tab[wave].dist[lane], (u32)ids[lane], 1u) : KEY_PAD;
-        wave_sort<1>(k, lane);
+        wave_sort<1>(k);
         if (lane < S) row[lane] = k[0];
     } else {
         u64 k[2];
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(BLOCK) void k_random_graph(const void *X, long long
             int e = r * 64 + lane;
             k[r] = e < S ? make_key(s_tab[wave].dist[e], (u32)ids[e], 1u) : KEY_PAD;
         }
-        wave_sort<2>(k, lane);
+        wave_sort<2>(k);
         if (lane < S) row[lane] = k[0];
         if (lane + 64 < S) row[lane + 64] = k[1];
     }
@@ -570,7 +570,7 @@ __device__ __forceinline__ void merge_group_body(int R, u64 *keys, int *deg, con
         if (sub < nb) k = cur.kr;
         else if (G - 1 - sub < c) k = cur.ki;
         k = close_keys<DT, G, SEEK>(k, x, sub >= nb && G - 1 - sub < c, k, sub < nb, s_open, X, d, lane);
-        k = group_sort<G>(k, lane);
+        k = group_sort<G>(k);
         u64 prev = shfl_up1_u64(k);
         if (sub == 0) prev = KEY_PAD;
         const bool keep = (k != KEY_PAD) && ((k >> 1) != (prev >> 1));
@@ -664,7 +664,7 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
             u64 k[2];
             k[0] = lane < nb ? cur.r0 : KEY_PAD;
             k[1] = lane + 64 < nb ? cur.r1 : (63 - lane < c ? cur.in : KEY_PAD);
-            wave_sort<2>(k, lane);
+            wave_sort<2>(k);
             nd = wave_unique_prefix<2>(k, lane, R, keys + (size_t)x * R, &any_new, &dropped);
         } else {
             const int ca = c < cap ? c : cap, late = c - ca;
@@ -676,7 +676,7 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
                 k[0] = lane < nb ? cur.r0 : late_edge(props, 63 - lane < late ? head[63 - lane] : 0u, 63 - lane < late).key;
                 k[0] = close_keys<DT, 64, SEEK>(k[0], x, lane >= nb && 63 - lane < late, k[0], lane < nb, s_open, X, d, lane);
                 k[1] = 63 - lane < ca ? cur.in : KEY_PAD;
-                wave_sort<2>(k, lane);
+                wave_sort<2>(k);
                 nd = wave_unique_prefix<2>(k, lane, R, row, &any_new, &dropped);
             } else {
                 // inbox and late edges in chunks of 128 against the best R found so far; lane l walks list l, and the two
@@ -689,7 +689,7 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
                 k[3] = close_keys<DT, 64, SEEK>(first.key, x, lane < late, k[0], lane < nb, s_open, X, d, lane);
                 LateEdge a = late_edge(props, first.next, LATE_LISTS + lane < late);
                 for (int at = LATE_LISTS;; at += 2 * LATE_LISTS) {      // edges taken so far; `a` is the next one of my list
-                    wave_sort<4>(k, lane);
+                    wave_sort<4>(k);
                     const LateEdge b = late_edge(props, a.next, at + LATE_LISTS + lane < late);
                     nd = wave_unique_prefix<4>(k, lane, R, s_stage[wave], &any_new, &dropped);
                     wave_sync();
@@ -1264,7 +1264,7 @@ __global__ __launch_bounds__(BLOCK) void k_reverse_merge(long long N, int W, int
                 if (l32 < nbh) k = cur.kr;
                 else if (31 - l32 < ch) k = cur.ki;
             }
-            k = group_sort<32>(k, lane);
+            k = group_sort<32>(k);
             u64 prev = shfl_up1_u64(k);
             if (l32 == 0) prev = KEY_PAD;
             const bool keep = (k != KEY_PAD) && ((k >> 1) != (prev >> 1));

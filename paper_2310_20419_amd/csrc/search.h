@@ -372,11 +372,7 @@ __device__ __forceinline__ void merge_into_candidates(u64 (&C)[E], u64 kn, int l
         C[1] = a < b ? b : a;
     }
 #pragma unroll
-    for (int stride = 32; stride > 0; stride >>= 1) {
-        const bool lower = (lane & stride) == 0;
-#pragma unroll
-        for (int r = 0; r < E; ++r) C[r] = keep_of_pair(C[r], xor_lane_u64(C[r], stride), lower);
-    }
+    for (int r = 0; r < E; ++r) merge_ascending<32>(C[r]);
 }
 
 __device__ __forceinline__ u64 read_lane_u64(u64 v, int src)      // src the same in every lane
@@ -649,9 +645,9 @@ __global__ __launch_bounds__(64 * TEAM, 4) void k_search(const void *X, long lon
             const int na = __popcll(__builtin_amdgcn_ballot_w64(kn != KEY_PAD));
             if (na == 0) continue;
             // a group of lanes without a new key has nothing to sort
-            if (span <= 16) kn = group_sort<16>(kn, lane);
-            else if (span <= 32) kn = group_sort<32>(kn, lane);
-            else kn = group_sort<64>(kn, lane);
+            if (span <= 16) kn = group_sort<16>(kn);
+            else if (span <= 32) kn = group_sort<32>(kn);
+            else kn = group_sort<64>(kn);
             merge_into_candidates<E>(C, kn, lane);
             m = m + na < L ? m + na : L;
             // the registers hold 64 E keys; C is its first L

@@ -52,9 +52,9 @@ __device__ __forceinline__ u64 shfl_up1_u64(u64 v)
     return ((u64)hi << 32) | lo;
 }
 
-// Value of lane (l xor S), S a power of two below 64.  Within rows of 16 lanes the exchange is a
-// DPP move (no LDS round trip) where the ISA has one: quad permutations for S = 1, 2 and a rotation
-// by 8 for S = 8; S = 4 and 16 use the LDS swizzle unit, S = 32 the permute unit.  Every lane of these
+// Value of lane (l xor S), S a power of two below 64, or one less.  Within rows of 16 lanes the exchange is a
+// DPP move (no LDS round trip) where the ISA has one: quad permutations for S = 1, 2, 3, mirrors for S = 7, 15 and a rotation
+// by 8 for S = 8; S = 4, 16 and 31 use the LDS swizzle unit, S = 32 and 63 the permute unit.  Every lane of these
 // DPP patterns has a source lane, so bound_ctrl changes no value: it only tells the compiler that the
 // destination needs no initial value (two moves less per 64-bit exchange).
 template <int S>
@@ -62,9 +62,13 @@ __device__ __forceinline__ u32 xor_lane_u32(u32 v)
 {
     if constexpr (S == 1) return (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);        // quad_perm [1,0,3,2]
     else if constexpr (S == 2) return (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
+    else if constexpr (S == 3) return (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x1B, 0xF, 0xF, true);   // quad_perm [3,2,1,0]
+    else if constexpr (S == 7) return (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);  // row_half_mirror
+    else if constexpr (S == 15) return (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true); // row_mirror
     else if constexpr (S == 8) return (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true);  // row_ror:8
     else if constexpr (S == 4) return (u32)__builtin_amdgcn_ds_swizzle((int)v, 0x101F);                     // xor 4, and 0x1F
     else if constexpr (S == 16) return (u32)__builtin_amdgcn_ds_swizzle((int)v, 0x401F);                    // xor 16, and 0x1F
+    else if constexpr (S == 31) return (u32)__builtin_amdgcn_ds_swizzle((int)v, 0x7C1F);                    // xor 31, and 0x1F
     else return (u32)__shfl_xor((int)v, S);
 }
 
@@ -82,59 +86,91 @@ __device__ __forceinline__ u64 xor_lane_u64(u64 v, int stride)
     return ((u64)hi << 32) | lo;
 }
 
-// One compare-exchange of a bitonic network from the point of view of one side: keeps the smaller
-// of (mine, other) if take_min, else the larger.
-__device__ __forceinline__ u64 keep_of_pair(u64 mine, u64 other, bool take_min)
+// Lanes l (of element r * 64 + l) that keep the smaller key when elements `stride` apart are exchanged in a bitonic stage
+// whose runs of `size` ascend and descend in turn.
+static constexpr u64 min_lanes(int r, int size, int stride)
 {
-    return ((mine < other) == take_min) ? mine : other;
+    u64 m = 0;
+    for (int l = 0; l < 64; ++l)
+        if ((((r * 64 + l) & size) == 0) == ((l & stride) == 0)) m |= 1ull << l;
+    return m;
+}
+
+// One compare-exchange of a sorting network: a lane meets lane (l xor X) and keeps the smaller of the two keys if it is in MIN, else the larger.
+// Which side a lane is on is a constant of the scalar unit: as a comparison of lane numbers it was a vector instruction made again in every trip (float
+// merges), or sat in scalar registers that ran out and came back lane by lane (search: 196 lane reads, now 88).  Two moves, a comparison, two selections.
+// (The comparison as the borrow of a subtraction that reads through DPP, four vector instructions in all, is slower: the carry and its wait
+// states lie in every stage's chain; 100,000 x 128 uint8 3.78 -> 4.00 ms.)  With the mirrors of group_sort: 10,000 uint8 queries on 1M x 128
+// 913 -> 871 us, one float query on 100,000 x 96 142.8 -> 139.4, builds of 200,000 x 100 float32 20.5 -> 20.3 ms, 20,000 x 96 2.70 -> 2.69,
+// uint8 the same.
+template <int X, u64 MIN>
+__device__ __forceinline__ void exchange(u64 &k)
+{
+    const u32 lo = xor_lane_u32<X>((u32)k), hi = xor_lane_u32<X>((u32)(k >> 32));
+    const u64 other = ((u64)hi << 32) | lo;
+    k = __builtin_amdgcn_inverse_ballot_w64(__builtin_amdgcn_ballot_w64(other < k) ^ MIN) ? k : other;
+}
+
+// The stages STRIDE, STRIDE / 2, ... 1 that sort bitonic runs of 2 STRIDE lanes, all ascending.
+template <int STRIDE>
+__device__ __forceinline__ void merge_ascending(u64 &k)
+{
+    if constexpr (STRIDE > 0) {
+        exchange<STRIDE, min_lanes(0, 1 << 16, STRIDE)>(k);
+        merge_ascending<STRIDE / 2>(k);
+    }
 }
 
 // Ascending bitonic sort of 64*E keys held as k[r] in lane l  <->  element index r*64 + l.
-template <int E>
-__device__ __forceinline__ void wave_sort(u64 (&k)[E], int lane)
+template <int E, int R, int SIZE, int STRIDE>
+__device__ __forceinline__ void sort_stage(u64 (&k)[E])
 {
-#pragma unroll
-    for (int size = 2; size <= 64 * E; size <<= 1) {
-#pragma unroll
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            if (stride >= 64) {
-                const int rs = stride / 64;
-#pragma unroll
-                for (int r = 0; r < E; ++r) {
-                    if ((r & rs) == 0) {
-                        const bool up = (((r * 64) & size) == 0);
-                        const u64 a = k[r], b = k[r | rs];
-                        const bool swap = (b < a) == up;      // up: smaller first
-                        k[r] = swap ? b : a;
-                        k[r | rs] = swap ? a : b;
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int r = 0; r < E; ++r) {
-                    const bool up = ((((r * 64) + lane) & size) == 0);
-                    const bool lower = (lane & stride) == 0;
-                    k[r] = keep_of_pair(k[r], xor_lane_u64(k[r], stride), lower == up);
-                }
-            }
-        }
+    if constexpr (R < E) {
+        exchange<STRIDE, min_lanes(R, SIZE, STRIDE)>(k[R]);
+        sort_stage<E, R + 1, SIZE, STRIDE>(k);
     }
 }
-
-// Ascending bitonic sort inside every group of G consecutive lanes (G = 16, 32 or 64), one key per lane.
-template <int G>
-__device__ __forceinline__ u64 group_sort(u64 k, int lane)
+template <int E, int SIZE, int STRIDE>
+__device__ __forceinline__ void sort_stages(u64 (&k)[E])
 {
-    const int sub = lane & (G - 1);
+    if constexpr (STRIDE >= 64) {
+        constexpr int rs = STRIDE / 64;
 #pragma unroll
-    for (int size = 2; size <= G; size <<= 1) {
-#pragma unroll
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            const bool up = (sub & size) == 0;      // for size == G: always ascending
-            const bool lower = (lane & stride) == 0;
-            k = keep_of_pair(k, xor_lane_u64(k, stride), lower == up);
+        for (int r = 0; r < E; ++r) {
+            if ((r & rs) == 0) {
+                const bool up = (((r * 64) & SIZE) == 0);
+                const u64 a = k[r], b = k[r | rs];
+                const bool swap = (b < a) == up;      // up: smaller first
+                k[r] = swap ? b : a;
+                k[r | rs] = swap ? a : b;
+            }
         }
+    } else {
+        sort_stage<E, 0, SIZE, STRIDE>(k);
     }
+    if constexpr (STRIDE > 1) sort_stages<E, SIZE, STRIDE / 2>(k);
+    else if constexpr (SIZE < 64 * E) sort_stages<E, SIZE * 2, SIZE>(k);
+}
+template <int E>
+__device__ __forceinline__ void wave_sort(u64 (&k)[E])
+{
+    sort_stages<E, 2, 1>(k);
+}
+
+// Ascending sort inside every group of G consecutive lanes (G = 16, 32 or 64), one key per lane.  Runs of SIZE / 2 are merged by
+// first meeting end to end (lane xor SIZE - 1), after which every stage ascends: up to 16 lanes that is a mirror, which DPP has, where the
+// alternating network has one more exchange over 4 lanes, which it has not.
+template <int G, int SIZE = 2>
+__device__ __forceinline__ void sort_runs(u64 &k)
+{
+    exchange<SIZE - 1, min_lanes(0, 1 << 16, SIZE / 2)>(k);
+    merge_ascending<SIZE / 4>(k);
+    if constexpr (SIZE < G) sort_runs<G, SIZE * 2>(k);
+}
+template <int G>
+__device__ __forceinline__ u64 group_sort(u64 k)
+{
+    sort_runs<G>(k);
     return k;
 }
 
@@ -184,7 +220,7 @@ __device__ __forceinline__ int wave_merge_row(u64 *row, int nb, const u64 *binA,
     if (total <= 64) {
         u64 k[1];
         k[0] = lane < nb ? row[lane] : (lane < total ? bin_at(lane - nb) : KEY_PAD);
-        wave_sort<1>(k, lane);
+        wave_sort<1>(k);
         n = wave_unique_prefix<1>(k, lane, R, row, any_new, dropped);
     } else if (total <= 128) {
         u64 k[2];
@@ -193,7 +229,7 @@ __device__ __forceinline__ int wave_merge_row(u64 *row, int nb, const u64 *binA,
             int e = r * 64 + lane;
             k[r] = e < nb ? row[e] : (e < total ? bin_at(e - nb) : KEY_PAD);
         }
-        wave_sort<2>(k, lane);
+        wave_sort<2>(k);
         n = wave_unique_prefix<2>(k, lane, R, row, any_new, dropped);
     } else {
         // stream the bin through in chunks of 128 against the best R found so far
@@ -205,7 +241,7 @@ __device__ __forceinline__ int wave_merge_row(u64 *row, int nb, const u64 *binA,
             int e0 = done + lane, e1 = done + 64 + lane;
             k[2] = e0 < c ? bin_at(e0) : KEY_PAD;
             k[3] = e1 < c ? bin_at(e1) : KEY_PAD;
-            wave_sort<4>(k, lane);
+            wave_sort<4>(k);
             n = wave_unique_prefix<4>(k, lane, R, stage, any_new, dropped);
             wave_sync();
             k[0] = lane < n ? stage[lane] : KEY_PAD;
