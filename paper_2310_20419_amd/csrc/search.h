@@ -136,10 +136,7 @@ template <int DT>
 __device__ __forceinline__ void add_piece(typename EvalAcc<DT>::type &acc, const uint4 &a, const uint4 &b)
 {
     if constexpr (DT == DT_U8) {
-        acc = sqdiff_word_u8(a.x, b.x, acc);
-        acc = sqdiff_word_u8(a.y, b.y, acc);
-        acc = sqdiff_word_u8(a.z, b.z, acc);
-        acc = sqdiff_word_u8(a.w, b.w, acc);
+        acc = sqdiff_piece_u8(a, b, acc);
     } else {
 #pragma unroll
         for (int i = 0; i < PieceCoords<DT>::n; ++i) {
@@ -169,8 +166,9 @@ __device__ __forceinline__ void add_pieces(typename EvalAcc<DT>::type (&acc)[RB]
         }
     }
 }
-__device__ __forceinline__ u32 eval_bits(int acc) { return (u32)group8_sum(acc); }
-__device__ __forceinline__ u32 eval_bits(double acc) { return __float_as_uint((float)group8_sum(acc)); }
+// (in the first four lanes of a group)
+__device__ __forceinline__ u32 eval_bits(int acc) { return (u32)group8_sum_low(acc); }
+__device__ __forceinline__ u32 eval_bits(double acc) { return __float_as_uint((float)group8_sum_low(acc)); }
 
 // UF pieces per lane, from piece c0 on, of RB rows.  The loads are unconditional (a lane past the end of the row reads
 // its last piece and drops the outcome): a branch around each would make the wavefront wait for one load after the other.
