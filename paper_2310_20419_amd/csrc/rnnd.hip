@@ -274,9 +274,12 @@ struct OpenEdges {
     u32 dist[64];
 };
 // From the second pass on 15-40 % of the redirected edges name an edge that another vertex redirects in the same round or that the list holds already;
-// their distances need not be computed, the merge would drop the second of two equal keys.  Lanes whose open key names the vertex of a key that some lane of
+// their distances need not be computed where the merge would drop the second of two equal keys.  Lanes whose open key names the vertex of a key that some lane of
 // the same G holds in `list` or, of several open ones, all but one: found through a table of 128 lanes by vertex, in which the last one to write wins (a lane that loses its place to
-// another vertex counts as no repeat).  Merge with / without: 1M x 96 float32 25.6 / 26.3 ms, 1M x 960 182 / 188, 300,000 x 768 bfloat16 (whole build) 98.0 / 100.6; not in
+// another vertex counts as no repeat).  Equal vertices are equal keys only if the distances have the same bits.  Those of open keys do: one routine forms them, operands in the same order.
+// A listed one does (same_bits) where this library has formed it on the same rows, in either order, unless it is a NaN, whose sign is that of the operand it came
+// with or the other; a caller's snapshot may hold distances summed in another order, so there lists are not looked at.  Merge with / without: 1M x 96 float32 25.6 / 26.3 ms, 1M x 960 182 / 188; whole builds 1M x 960 513 / 524,
+// 300,000 x 768 bfloat16 97.6 / 99.8, 200,000 x 960 84.7 / 86.7, 200,000 x 16 10.83 / 10.84 (open keys only: 523, 99.3, 86.5, 10.92); not in
 // k_merge_blocks, whose rounds wait for latency: 20,000 x 96 0.935 / 0.890.
 template <int G>
 __device__ __forceinline__ bool repeats(u64 key, bool open, u64 list, bool listed, OpenEdges *s, int lane)
@@ -294,14 +297,14 @@ __device__ __forceinline__ bool repeats(u64 key, bool open, u64 list, bool liste
     return open && w != (u32)lane && (w >= 64u ? of_list : of_open) == key_id(key);
 }
 template <int DT, int G, bool SEEK>
-__device__ __forceinline__ u64 close_keys(u64 key, int x, bool have, u64 list, bool listed, OpenEdges *s, const char *__restrict__ X, int d, int lane)
+__device__ __forceinline__ u64 close_keys(u64 key, int x, bool have, u64 list, bool listed, int same_bits, OpenEdges *s, const char *__restrict__ X, int d, int lane)
 {
     if constexpr (DT == DT_U8) {
         return key;
     } else {
         bool open = have && key_dist(key) == OPEN_DIST;
         if (__builtin_amdgcn_ballot_w64(open) == 0ull) return key;
-        if (SEEK && repeats<G>(key, open, list, listed, s, lane)) {
+        if (SEEK && repeats<G>(key, open, list, same_bits && listed && key_dist(list) <= INFINITE_DIST, s, lane)) {
             key = KEY_PAD;
             open = false;
         }
@@ -539,7 +542,7 @@ __device__ __forceinline__ MergeItem merge_item_load(int x, int R, const u64 *ke
 template <int G, int DT, bool SEEK>
 __device__ __forceinline__ void merge_group_body(int R, u64 *keys, int *deg, const int *tlist, u32 n, u32 first, u32 nwaves,
                                                  int *cnt, const u64 *inbox, int8_t *tcls, int use_classes, RoundCtr *ctr,
-                                                 OpenEdges *s_open, const char *__restrict__ X, int d)
+                                                 int same_bits, OpenEdges *s_open, const char *__restrict__ X, int d)
 {
     int dropped = 0;
     static_assert(G <= INBOX_CAP, "a group merge reads the received edges from the inbox only");
@@ -569,7 +572,7 @@ __device__ __forceinline__ void merge_group_body(int R, u64 *keys, int *deg, con
         u64 k = KEY_PAD;
         if (sub < nb) k = cur.kr;
         else if (G - 1 - sub < c) k = cur.ki;
-        k = close_keys<DT, G, SEEK>(k, x, sub >= nb && G - 1 - sub < c, k, sub < nb, s_open, X, d, lane);
+        k = close_keys<DT, G, SEEK>(k, x, sub >= nb && G - 1 - sub < c, k, sub < nb, same_bits, s_open, X, d, lane);
         k = group_sort<G>(k);
         u64 prev = shfl_up1_u64(k);
         if (sub == 0) prev = KEY_PAD;
@@ -636,7 +639,7 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
                                                    int *cnt, const u64 *inbox,
                                                    LateHeads heads, const Prop *props, int8_t *tcls,
                                                    int use_classes, u64 (*s_stage)[RNND_MAX_R], RoundCtr *ctr,
-                                                   OpenEdges *s_open, const char *__restrict__ X, int d)
+                                                   int same_bits, OpenEdges *s_open, const char *__restrict__ X, int d)
 {
     int dropped = 0;
     static_assert(INBOX_CAP == 64 && LATE_LISTS == 64, "lane l prefetches inbox slot 63 - l and walks list l");
@@ -657,7 +660,7 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
 
         const int x = __builtin_amdgcn_readfirstlane(cur.x);
         const int nb = __builtin_amdgcn_readfirstlane(cur.nb), c = __builtin_amdgcn_readfirstlane(cur.c);
-        cur.in = close_keys<DT, 64, SEEK>(cur.in, x, 63 - lane < (c < cap ? c : cap), cur.r0, lane < nb, s_open, X, d, lane);
+        cur.in = close_keys<DT, 64, SEEK>(cur.in, x, 63 - lane < (c < cap ? c : cap), cur.r0, lane < nb, same_bits, s_open, X, d, lane);
         bool any_new = false;
         int nd;
         if (c <= cap && nb + c <= 128) {
@@ -674,7 +677,7 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
                 // a full inbox, and at most one late edge per list: the lists from the top lane down, above the kept entries
                 u64 k[2];
                 k[0] = lane < nb ? cur.r0 : late_edge(props, 63 - lane < late ? head[63 - lane] : 0u, 63 - lane < late).key;
-                k[0] = close_keys<DT, 64, SEEK>(k[0], x, lane >= nb && 63 - lane < late, k[0], lane < nb, s_open, X, d, lane);
+                k[0] = close_keys<DT, 64, SEEK>(k[0], x, lane >= nb && 63 - lane < late, k[0], lane < nb, same_bits, s_open, X, d, lane);
                 k[1] = 63 - lane < ca ? cur.in : KEY_PAD;
                 wave_sort<2>(k);
                 nd = wave_unique_prefix<2>(k, lane, R, row, &any_new, &dropped);
@@ -686,7 +689,7 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
                 k[0] = lane < nb ? cur.r0 : KEY_PAD;
                 k[1] = lane + 64 < nb ? cur.r1 : KEY_PAD;
                 k[2] = 63 - lane < ca ? cur.in : KEY_PAD;
-                k[3] = close_keys<DT, 64, SEEK>(first.key, x, lane < late, k[0], lane < nb, s_open, X, d, lane);
+                k[3] = close_keys<DT, 64, SEEK>(first.key, x, lane < late, k[0], lane < nb, same_bits, s_open, X, d, lane);
                 LateEdge a = late_edge(props, first.next, LATE_LISTS + lane < late);
                 for (int at = LATE_LISTS;; at += 2 * LATE_LISTS) {      // edges taken so far; `a` is the next one of my list
                     wave_sort<4>(k);
@@ -697,8 +700,8 @@ __device__ __forceinline__ void merge_general_body(int R, u64 *keys, int *deg, c
                     k[1] = lane + 64 < nd ? s_stage[wave][lane + 64] : KEY_PAD;
                     wave_sync();
                     if (at >= late) break;
-                    k[2] = close_keys<DT, 64, SEEK>(a.key, x, at + lane < late, k[0], lane < nd, s_open, X, d, lane);
-                    k[3] = close_keys<DT, 64, SEEK>(b.key, x, at + LATE_LISTS + lane < late, k[0], lane < nd, s_open, X, d, lane);
+                    k[2] = close_keys<DT, 64, SEEK>(a.key, x, at + lane < late, k[0], lane < nd, same_bits, s_open, X, d, lane);
+                    k[3] = close_keys<DT, 64, SEEK>(b.key, x, at + LATE_LISTS + lane < late, k[0], lane < nd, same_bits, s_open, X, d, lane);
                     a = late_edge(props, b.next, at + 2 * LATE_LISTS + lane < late);
                 }
                 if (lane < nd) row[lane] = k[0];
@@ -720,7 +723,7 @@ template <int DT>
 __global__ __launch_bounds__(BLOCK, (DT == DT_U8 ? 1 : 5)) void k_merge(long long N, int R, u64 *keys, int *deg, const int *tlists,
                                                  const u32 *n_touched, int *cnt, const u64 *inbox,
                                                  LateHeads heads, const Prop *props, int8_t *tcls,
-                                                 int use_classes, RoundCtr *ctr, const char *__restrict__ X, int d)
+                                                 int use_classes, int same_bits, RoundCtr *ctr, const char *__restrict__ X, int d)
 {
     __shared__ u64 s_stage[WAVES_PER_BLOCK][RNND_MAX_R];
     static_assert(sizeof(OpenEdges) <= sizeof(u64) * RNND_MAX_R, "the open edges lie in the stage, which is free until they are closed");
@@ -729,10 +732,10 @@ __global__ __launch_bounds__(BLOCK, (DT == DT_U8 ? 1 : 5)) void k_merge(long lon
     const int *tlist = tlists + (size_t)y * N;
     int8_t *tc = tcls + (size_t)y * N;
     const u32 n = n_touched[y], first = blockIdx.x * WAVES_PER_BLOCK + (threadIdx.x >> 6), nwaves = gridDim.x * WAVES_PER_BLOCK;
-    if (y == 0) merge_group_body<16, DT, true>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, tc, use_classes, ctr, so, X, d);
-    else if (y == 1) merge_group_body<32, DT, true>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, tc, use_classes, ctr, so, X, d);
-    else if (y == 2) merge_group_body<64, DT, true>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, tc, use_classes, ctr, so, X, d);
-    else merge_general_body<DT, true>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, heads, props, tc, use_classes, s_stage, ctr, so, X, d);
+    if (y == 0) merge_group_body<16, DT, true>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, tc, use_classes, ctr, same_bits, so, X, d);
+    else if (y == 1) merge_group_body<32, DT, true>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, tc, use_classes, ctr, same_bits, so, X, d);
+    else if (y == 2) merge_group_body<64, DT, true>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, tc, use_classes, ctr, same_bits, so, X, d);
+    else merge_general_body<DT, true>(R, keys, deg, tlist, n, first, nwaves, cnt, inbox, heads, props, tc, use_classes, s_stage, ctr, same_bits, so, X, d);
 }
 
 // Classify, merge and compact of a round in one launch, for inputs whose rounds wait for launches (4-6 us each) rather than for
@@ -771,10 +774,10 @@ __global__ __launch_bounds__(BLOCK, (DT == DT_U8 ? 1 : 5)) void k_merge_blocks(l
         __syncthreads();
     }
     // (the classes start with different wavefronts)
-    merge_group_body<16, DT, false>(R, keys, deg, s_list[0], s_n[0], wave, 4, cnt, inbox, s_cls[0], use_classes, ctr, so, X, d);
-    merge_group_body<32, DT, false>(R, keys, deg, s_list[1], s_n[1], (wave + 3) & 3, 4, cnt, inbox, s_cls[1], use_classes, ctr, so, X, d);
-    merge_group_body<64, DT, false>(R, keys, deg, s_list[2], s_n[2], (wave + 2) & 3, 4, cnt, inbox, s_cls[2], use_classes, ctr, so, X, d);
-    merge_general_body<DT, false>(R, keys, deg, s_list[3], s_n[3], (wave + 1) & 3, 4, cnt, inbox, heads, props, s_cls[3], use_classes, s_stage, ctr, so, X, d);
+    merge_group_body<16, DT, false>(R, keys, deg, s_list[0], s_n[0], wave, 4, cnt, inbox, s_cls[0], use_classes, ctr, 0, so, X, d);
+    merge_group_body<32, DT, false>(R, keys, deg, s_list[1], s_n[1], (wave + 3) & 3, 4, cnt, inbox, s_cls[1], use_classes, ctr, 0, so, X, d);
+    merge_group_body<64, DT, false>(R, keys, deg, s_list[2], s_n[2], (wave + 2) & 3, 4, cnt, inbox, s_cls[2], use_classes, ctr, 0, so, X, d);
+    merge_general_body<DT, false>(R, keys, deg, s_list[3], s_n[3], (wave + 1) & 3, 4, cnt, inbox, heads, props, s_cls[3], use_classes, s_stage, ctr, 0, so, X, d);
     __syncthreads();
     // at most `span` items in all: one per thread
     int k = -1, item = 0;
@@ -1788,6 +1791,7 @@ struct RowsView {
     const void *X = nullptr;
     int d = 0, vec_ok = 0;
     HalfRows half;
+    bool own_lists = false;     // the lists hold distances that this library has formed on these rows, and no others
 };
 
 // Where the parts of a half-precision copy lie.
@@ -1836,6 +1840,7 @@ static hipError_t prepare_rows(const Workspace &w, ScanPlan &p, const void *X, l
     rv->X = X;
     rv->d = d;
     rv->vec_ok = vec_ok_for(X, d, dtype);
+    rv->own_lists = !step;
     if (p.half_rb) launch_half_rows(w.half, X, N, d, rv->vec_ok, p.half_rb, st, &rv->half);
     launch_prepare(w, p, X, N, d, dtype, round, st);
     if (p.copy != COPY_ROWS && p.copy != COPY_ROWS_PERMUTED) return hipGetLastError();
@@ -1931,11 +1936,11 @@ static void launch_classify_dt(hipStream_t st, long long N, int R, const Workspa
 }
 
 template <int DT>
-static void launch_merge_dt(hipStream_t st, long long N, int R, const Workspace &w, u64 *keys, int *deg, int use_classes, RoundCtr *c, const void *X, int d)
+static void launch_merge_dt(hipStream_t st, long long N, int R, const Workspace &w, u64 *keys, int *deg, int use_classes, bool same_bits, RoundCtr *c, const void *X, int d)
 {
     static const int per_cu = resident_blocks_per_cu(k_merge<DT>, 6);
     hipLaunchKernelGGL(k_merge<DT>, dim3(capped(cu_count() * per_cu, N), NMRG), dim3(BLOCK), 0, st, N, R, keys, deg, w.touched, c->n_touched,
-                       w.fill, w.inbox, late_heads(w.inbox, w.bins, R), (const Prop *)w.props, w.tcls, use_classes, c, (const char *)X, d);
+                       w.fill, w.inbox, late_heads(w.inbox, w.bins, R), (const Prop *)w.props, w.tcls, use_classes, same_bits ? 1 : 0, c, (const char *)X, d);
 }
 
 static void launch_classify(int dt, hipStream_t st, long long N, int R, const Workspace &w, const int *deg, RoundCtr *c, const void *X, int d, bool scattered, u32 enough)
@@ -1965,10 +1970,10 @@ static void launch_merge_blocks(int dt, hipStream_t st, long long N, int R, cons
     const auto go = dt == RNND_F32 ? launch_merge_blocks_dt<DT_F32> : dt == RNND_F16 ? launch_merge_blocks_dt<DT_F16> : dt == RNND_BF16 ? launch_merge_blocks_dt<DT_BF16> : launch_merge_blocks_dt<DT_U8>;
     go(st, N, R, w, keys, deg, use_classes, c, X, d, scattered, enough);
 }
-static void launch_merge(int dt, hipStream_t st, long long N, int R, const Workspace &w, u64 *keys, int *deg, int use_classes, RoundCtr *c, const void *X, int d)
+static void launch_merge(int dt, hipStream_t st, long long N, int R, const Workspace &w, u64 *keys, int *deg, int use_classes, bool same_bits, RoundCtr *c, const void *X, int d)
 {
     const auto go = dt == RNND_F32 ? launch_merge_dt<DT_F32> : dt == RNND_F16 ? launch_merge_dt<DT_F16> : dt == RNND_BF16 ? launch_merge_dt<DT_BF16> : launch_merge_dt<DT_U8>;
-    go(st, N, R, w, keys, deg, use_classes, c, X, d);
+    go(st, N, R, w, keys, deg, use_classes, same_bits, c, X, d);
 }
 
 // One run of consecutive vertex ids of a block-sequential pass: ids first .. first + count - 1.
@@ -2059,7 +2064,7 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
         return hipGetLastError();
     }
     launch_classify(open_dt, st, N, R, w, deg, c, X, d, own_scatter, decide);
-    launch_merge(open_dt, st, N, R, w, keys, deg, use_classes, c, X, d);
+    launch_merge(open_dt, st, N, R, w, keys, deg, use_classes, rv.own_lists, c, X, d);
     if (run)
         hipLaunchKernelGGL(k_store_classes, dim3(64, NMRG), dim3(256), 0, st, (const u32 *)c->n_touched,
                            (const int *)w.touched, (const int8_t *)w.tcls, N, w.vcls);

@@ -93,6 +93,7 @@ struct Prop {          // one redirected edge (Alg. 4, the edge update): `key` e
 // A key whose distance is still to be computed (by the merge, see close_keys): these bits in place of the distance.  A NaN can
 // have them too; computing it once more gives the same bits.
 #define OPEN_DIST 0xFFFFFFFFu
+#define INFINITE_DIST 0x7F800000u     // float rows: greater bits are a NaN's
 
 // The edge update of Alg. 4: (w, v) enters E.  Recorded in the scanning vertex's own slot.
 __device__ __forceinline__ void emit_redirect(u64 key, u32 tgt, Prop *slot)
