@@ -1986,16 +1986,18 @@ struct VertexRun {
 #define DECIDE_MIN_ACTIVE 1024u
 
 // Whether the scan by tiles (and what follows it) scatters the edges itself (see EdgeOut).  Scans that hold rows whole always do: 1M x 128
-// uint8 25.5 -> 23.5 ms, 20M (6 rounds) 116 -> 106, 1M x 64 (15 rounds) 5.05 -> 4.26.  Streamed rows: as long as they and the inboxes stay below
-// this many bytes; beyond, an arrival number takes longer to come than the next rows, which wait behind it.  k_scatter / in the scan, 15 rounds, ms: float32
-// 1M x 96 31.3 / 29.0, x 256 59.3 / 57.6, x 512 115.3 / 114.2, x 960 212.0 / 214.1; 300,000 x 960 56.0 / 55.6; bfloat16 1M x 256 43.7 / 42.4, x 768
-// 121.9 / 122.5; uint8 1M x 784 28.6 / 27.7, 2M x 784 (6 rounds) 34.1 / 38.0; float32 4M x 128 (6 rounds) 76.3 / 78.4.
+// uint8 25.6 -> 23.6 ms, 3M x 128 (16 rounds) 36.5 -> 32.2, 1M x 64 (16 rounds, R = 64) 11.2 -> 9.3.  Streamed rows of up to OWN_SCATTER_ROW_BYTES do as well, longer ones
+// as long as rows and inboxes stay below OWN_SCATTER_MAX_BYTES: beyond, an arrival number takes longer to come than the next rows, which wait behind it.  k_scatter after
+// scans that have no scatter in them / k_scatter / in the scan, ms (60 rounds, * 15): float32 1M x 96 102.6 / 106.4 / 100.6, x 256 190.1 / 190.9 / 186.0, x 512 300.5 / 295.6 / 292.1, x 960 523.1 / 514.0 / 519.3;
+// 3M x 128 396 / 407 / 394; 6M x 32 548 / 583 / 538; 2M x 512 * 244.8 / 245.5 / 245.3; 300,000 x 960 134.0 / 130.9 / 128.7; bfloat16 1M x 256 149.3 / 148.4 / 144.4, x 512 275.6 / 272.8 / 270.9,
+// x 768 408.8 / 404.2 / 408.2; uint8 1M x 784 52.3 / 52.5 / 50.6, 2M x 784 112.0 / 112.1 / 109.7, 2M x 1024 * 67.1 / 66.9 / 66.3, 2M x 1536 * 98.1 / 96.4 / 98.0, 4M x 256 113.5 / 117.4 / 111.9,
+// 1.2M x 2048 * 71.1 / 71.2 / 71.7.  (The device's placement of a buffer moves such a figure by up to 2 %, at 2M rows.)
+#define OWN_SCATTER_ROW_BYTES 1024
 #define OWN_SCATTER_MAX_BYTES 1750000000ll
 static bool scan_scatters(const ScanPlan &plan, const RowsView &rv, long long N, int dtype)
 {
-    if (plan.variant == 2 && plan.dp <= 128) return true;
     const long long rowbytes = plan.variant == 2 ? plan.dp : rv.half.rows ? rv.half.rowbytes : (long long)rv.d * dt_size(dtype);
-    return N * (rowbytes + 8 * INBOX_CAP) <= OWN_SCATTER_MAX_BYTES;
+    return rowbytes <= OWN_SCATTER_ROW_BYTES || N * (rowbytes + 8 * INBOX_CAP) <= OWN_SCATTER_MAX_BYTES;
 }
 
 // One synchronous round over the active lists of counter slot t (run == nullptr), or one run of a

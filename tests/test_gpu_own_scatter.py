@@ -1,5 +1,5 @@
-"""The scans by tiles send the edges they redirect to their targets themselves, beyond a size (rows and inboxes of more than 1.75 GB,
-rows streamed) a kernel after the scan does.  The pair-at-a-time kernel always leaves them to that kernel, and every form decides alike: the
+"""The scans by tiles send the edges they redirect to their targets themselves, beyond a size (rows of more than 1,024 bytes, with the inboxes more
+than 1.75 GB) a kernel after the scan does.  The pair-at-a-time kernel always leaves them to that kernel, and every form decides alike: the
 graphs, the degrees and the number of redirected edges must be the same."""
 import pytest
 
@@ -28,13 +28,31 @@ def rows(n, d, dtype, seed):
     return x
 
 
-def compare(rn, X, S, R, T1, T2):
+def launches_of(f):
+    """f's result, and the names of the kernels it launched."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        out = f()
+        torch.cuda.synchronize()
+    return out, [e.name for e in p.events()]
+
+
+def compare(rn, X, S, R, T1, T2, own=None):
+    """own: whether the edges must have been scattered by the scans."""
     import torch
     out = []
     try:
         for variant in (0, 1):
             rn.rnnd_set_kernel_variant(variant)
-            g, dg, _, st = rn.rnnd_build_ex(X, S, R, T1, T2, 5, want_keys=False)
+            def build():
+                return rn.rnnd_build_ex(X, S, R, T1, T2, 5, want_keys=False)
+            if own is None:
+                g, dg, _, st = build()
+            else:
+                (g, dg, _, st), names = launches_of(build)
+                assert any("k_random_graph" in k for k in names), names
+                assert any("k_scatter" in k for k in names) == (variant == 1 or not own), names
             out.append((g, dg, list(st.proposals[:T1 * T2])))
     finally:
         rn.rnnd_set_kernel_variant(0)
@@ -49,7 +67,17 @@ def test_edges_arrive_whatever_the_width_of_the_lists(rn, dtype, d, S, R):
     compare(rn, rows(1500, d, dtype, S), S, R, 2, 3)
 
 
-# 1.75e9 / (832 + 512) = 1,302,083 rows of 784 bytes
-@pytest.mark.parametrize("n", [1_302_083, 1_302_084])
-def test_either_side_of_the_line(rn, n):
-    compare(rn, rows(n, 784, "uint8", 3), 6, 32, 1, 2)
+# rows of up to 1,024 bytes: always; longer ones up to 1.75e9 / (1088 + 512) = 1,093,750 rows of 1,088 bytes, / (16384 + 512) = 103,574 of 16,384
+@pytest.mark.parametrize("dtype,n,d,own", [("uint8", 1_302_084, 784, True), ("uint8", 1_200_000, 1024, True),
+                                           ("uint8", 1_093_750, 1025, True), ("uint8", 1_093_751, 1025, False),
+                                           ("float32", 1_150_000, 512, True), ("bfloat16", 1_093_751, 544, False),
+                                           ("float16", 103_574, 8192, True), ("float16", 103_575, 8192, False), ("float32", 103_575, 8192, False)])
+def test_either_side_of_the_line(rn, dtype, n, d, own):
+    compare(rn, rows(n, d, dtype, 3), 6, 32, 1, 2, own)
+
+
+# beyond the line: what the scans leave in props, for every width of the lists
+@pytest.mark.parametrize("S,R", [(7, 8), (30, 32), (60, 64), (90, 96), (120, 128)])
+@pytest.mark.parametrize("dtype,n,d", [("uint8", 106_000, 16000), ("float32", 103_600, 8192), ("bfloat16", 103_600, 8192)])
+def test_edges_left_to_the_kernel_after_the_scan(rn, dtype, n, d, S, R):
+    compare(rn, rows(n, d, dtype, S), S, R, 1, 2, False)
