@@ -1737,12 +1737,12 @@ struct RoundEvents {
 
 static EdgeSink edge_sink(const Workspace &w, int R) { return EdgeSink{w.fill, w.inbox, late_heads(w.inbox, w.bins, R), w.props, w.nprop}; }
 
-template <int NG, int KS>
+template <int NG, int KS, typename OUT>
 static void launch_mfma_scan(const Workspace &w, int d, int R, u64 *keys, int *deg, long long N, RoundCtr *c,
                              hipStream_t st, hipEvent_t e_stop, const EdgeSink &sink)
 {
-    static const int per_cu = resident_blocks_per_cu(k_update_scan_mfma_u8<NG, KS>, NG == 2 ? 3 : 2);
-    hipExtLaunchKernelGGL((k_update_scan_mfma_u8<NG, KS>), dim3(capped(cu_count() * per_cu, N)), dim3(256), 0, st, nullptr,
+    static const int per_cu = resident_blocks_per_cu(k_update_scan_mfma_u8<NG, KS, OUT>, NG == 2 ? 3 : 2);
+    hipExtLaunchKernelGGL((k_update_scan_mfma_u8<NG, KS, OUT>), dim3(capped(cu_count() * per_cu, N)), dim3(256), 0, st, nullptr,
                           e_stop, 0, (const int8_t *)w.xs, d, R, keys, deg, w.lists + (size_t)(NG + 1) * N,
                           &c->n_active[NG + 1], sink, c);
 }
@@ -1861,29 +1861,29 @@ static hipError_t prepare_rows(const Workspace &w, ScanPlan &p, const void *X, l
     return hipSuccess;
 }
 
-template <int KS>
+template <int KS, typename OUT>
 static void launch_mfma_scan_classes(const Workspace &w, int d, int R, u64 *keys, int *deg, long long N, RoundCtr *c,
                                      hipStream_t st, const RoundEvents &re, const EdgeSink &sink)
 {
-    static const int per_cu = resident_blocks_per_cu(k_update_scan_mfma_u8_small<KS>, 4);
+    static const int per_cu = resident_blocks_per_cu(k_update_scan_mfma_u8_small<KS, OUT>, 4);
     const int n_big = (R > 32) + (R > 64) + (R > 96);   // launches after the short-list kernel
     // small inputs: every class in one launch (see k_update_scan_mfma_u8_all)
     if (n_big > 0 && (g_scan_launches == 2 || (g_scan_launches == 0 && N <= SMALL_INPUT_MAX_N))) {
         unsigned gx = capped((long long)cu_count() * 2, N);
         if (gx < 8) gx = 8;      // a block at least for every class
         if (n_big == 1)
-            hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, 4>), dim3(gx), dim3(256), 0, st, re.scan_start, re.scan_stop, 0,
+            hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, OUT, 4>), dim3(gx), dim3(256), 0, st, re.scan_start, re.scan_stop, 0,
                                   (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, sink, c);
         else if (n_big == 2)
-            hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, 5>), dim3(gx), dim3(256), 0, st, re.scan_start, re.scan_stop, 0,
+            hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, OUT, 5>), dim3(gx), dim3(256), 0, st, re.scan_start, re.scan_stop, 0,
                                   (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, sink, c);
         else
-            hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, 6>), dim3(gx), dim3(256), 0, st, re.scan_start, re.scan_stop, 0,
+            hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, OUT, 6>), dim3(gx), dim3(256), 0, st, re.scan_start, re.scan_stop, 0,
                                   (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, sink, c);
         return;
     }
     const int ny = 1 + (R > 8) + (R > 16);
-    hipExtLaunchKernelGGL((k_update_scan_mfma_u8_small<KS>), dim3(capped(cu_count() * per_cu, N), ny), dim3(256), 0, st,
+    hipExtLaunchKernelGGL((k_update_scan_mfma_u8_small<KS, OUT>), dim3(capped(cu_count() * per_cu, N), ny), dim3(256), 0, st,
                           re.scan_start, n_big == 0 ? re.scan_stop : nullptr, 0, (const int8_t *)w.xs, d, R, keys, deg,
                           w.lists, N, sink, c);
     // large inputs: the short-list launch above, then the longer classes in one launch
@@ -1891,16 +1891,16 @@ static void launch_mfma_scan_classes(const Workspace &w, int d, int R, u64 *keys
         unsigned gx = capped((long long)cu_count() * 2, N);
         if (gx < 8) gx = 8;      // a block at least for every class
         if (n_big == 2)
-            hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, 5, 3>), dim3(gx), dim3(256), 0, st, nullptr, re.scan_stop, 0,
+            hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, OUT, 5, 3>), dim3(gx), dim3(256), 0, st, nullptr, re.scan_stop, 0,
                                   (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, sink, c);
         else
-            hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, 6, 3>), dim3(gx), dim3(256), 0, st, nullptr, re.scan_stop, 0,
+            hipExtLaunchKernelGGL((k_update_scan_mfma_u8_all<KS, OUT, 6, 3>), dim3(gx), dim3(256), 0, st, nullptr, re.scan_stop, 0,
                                   (const int8_t *)w.xs, d, R, keys, deg, w.lists, N, sink, c);
         return;
     }
-    if (R > 32) launch_mfma_scan<2, KS>(w, d, R, keys, deg, N, c, st, n_big == 1 ? re.scan_stop : nullptr, sink);
-    if (R > 64) launch_mfma_scan<3, KS>(w, d, R, keys, deg, N, c, st, n_big == 2 ? re.scan_stop : nullptr, sink);
-    if (R > 96) launch_mfma_scan<4, KS>(w, d, R, keys, deg, N, c, st, n_big == 3 ? re.scan_stop : nullptr, sink);
+    if (R > 32) launch_mfma_scan<2, KS, OUT>(w, d, R, keys, deg, N, c, st, n_big == 1 ? re.scan_stop : nullptr, sink);
+    if (R > 64) launch_mfma_scan<3, KS, OUT>(w, d, R, keys, deg, N, c, st, n_big == 2 ? re.scan_stop : nullptr, sink);
+    if (R > 96) launch_mfma_scan<4, KS, OUT>(w, d, R, keys, deg, N, c, st, n_big == 3 ? re.scan_stop : nullptr, sink);
 }
 
 template <int DT>
@@ -1994,8 +1994,14 @@ struct VertexRun {
 // 1.2M x 2048 * 71.1 / 71.2 / 71.7.  (The device's placement of a buffer moves such a figure by up to 2 %, at 2M rows.)
 #define OWN_SCATTER_ROW_BYTES 1024
 #define OWN_SCATTER_MAX_BYTES 1750000000ll
-static bool scan_scatters(const ScanPlan &plan, const RowsView &rv, long long N, int dtype)
+// Streamed uint8 rows in lists of up to 128 entries: that scan has the registers of one block per CU, and the scatter costs it more than k_scatter takes once the launch saved
+// (4 of about 40 us a round) counts for less.  R = 128, left to k_scatter / in the scan, 16 rounds, 60 rounds, ms: 5,000 x 320 0.897 / 0.789, 2.25 / 1.97; 20,000 x 320 1.319 / 1.261, 3.21 / 2.97;
+// 40,000 x 320 1.796 / 1.802, 4.06 / 3.90; 60,000 x 200 2.37 / 2.43, 5.13 / 5.10; 60,000 x 784 3.01 / 3.05, 6.12 / 6.04; 100,000 x 200 3.47 / 3.64, 7.13 / 7.31;
+// 300,000 x 320 8.49 / 9.08, 16.1 / 17.0; 3M x 200 72.9 / 74.8, -.
+#define OWN_SCATTER_WIDE_U8_MAX_N 49152
+static bool scan_scatters(const ScanPlan &plan, const RowsView &rv, long long N, int dtype, int R)
 {
+    if (plan.variant == 2 && plan.dp > 128 && R > 96 && N > OWN_SCATTER_WIDE_U8_MAX_N) return false;
     const long long rowbytes = plan.variant == 2 ? plan.dp : rv.half.rows ? rv.half.rowbytes : (long long)rv.d * dt_size(dtype);
     return rowbytes <= OWN_SCATTER_ROW_BYTES || N * (rowbytes + 8 * INBOX_CAP) <= OWN_SCATTER_MAX_BYTES;
 }
@@ -2016,7 +2022,7 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
     const int open_dt = variant == 3 && use_classes == 2 ? dtype : RNND_U8;      // whose redirected edges come without distances
     const long long vertices = run ? (long long)run->count : N;
     const u32 enough = vertices / 16 > DECIDE_MIN_ACTIVE ? (u32)(vertices / 16) : DECIDE_MIN_ACTIVE;
-    const bool own_scatter = use_classes == 2 && scan_scatters(plan, rv, N, dtype);
+    const bool own_scatter = use_classes == 2 && scan_scatters(plan, rv, N, dtype, R);
     EdgeSink sink = edge_sink(w, R);
     if (!own_scatter) sink.count = nullptr;
     if (run) {
@@ -2026,10 +2032,11 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
                            run->first, w.vcls);
     }
     if (variant == 2) {
-        if (d == 32) launch_mfma_scan_classes<1>(w, d, R, keys, deg, N, c, st, re, sink);
-        else if (d == 64) launch_mfma_scan_classes<2>(w, d, R, keys, deg, N, c, st, re, sink);
-        else if (d == 128) launch_mfma_scan_classes<4>(w, d, R, keys, deg, N, c, st, re, sink);
-        else launch_mfma_scan_classes<0>(w, d, R, keys, deg, N, c, st, re, sink);
+        if (d == 32) launch_mfma_scan_classes<1, EdgeOut>(w, d, R, keys, deg, N, c, st, re, sink);
+        else if (d == 64) launch_mfma_scan_classes<2, EdgeOut>(w, d, R, keys, deg, N, c, st, re, sink);
+        else if (d == 128) launch_mfma_scan_classes<4, EdgeOut>(w, d, R, keys, deg, N, c, st, re, sink);
+        else if (own_scatter) launch_mfma_scan_classes<0, EdgeOut>(w, d, R, keys, deg, N, c, st, re, sink);
+        else launch_mfma_scan_classes<0, EdgesLeft>(w, d, R, keys, deg, N, c, st, re, sink);
     } else if (variant == 3) {
         const bool generic_tail = R > 96;
         ScanLaunch l = {X, d, R, keys, deg, N, w.lists, sink, c, w.touched, st, re.scan_start,

@@ -5,7 +5,7 @@
 //     tile_t, mac           accumulator of a 32 x 32 tile and the matrix instruction
 //     Smem<NG>              LDS of a wavefront; its gt, of 4 KB per 32 rows at least, is free until the Gram tiles are complete
 //     list<NG>, pack<P>     the body of Alg. 4's vertex loop for one vertex of up to 32 NG entries, for P vertices of up to 32 / P; its
-//                           edges go to an EdgeOut, which has delivered those of the trip before once hold() has been called
+//                           edges go to an EdgeOut, which has delivered those of the trip before once hold() has been called, or an EdgesLeft
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -183,10 +183,10 @@ __device__ __forceinline__ void stream_gram(const int8_t *const (&rp)[4 * NG], i
 // list -> degree/list entries -> rows of X is paid once per wavefront, not once per vertex.  The loop
 // body is written out twice so that the two row buffers swap roles without being copied.
 // block `block` of `nblocks` walks the work list
-template <typename OP, int NG, int KS>
+template <typename OP, int NG, int KS, typename OUT>
 __device__ __forceinline__ void scan_list_body(const OP &op, const int8_t *__restrict__ X, int R, u64 *__restrict__ keys,
                                                int *__restrict__ deg, const int *__restrict__ list, u32 n_active,
-                                               EdgeOut &out,
+                                               OUT &out,
                                                RoundCtr *__restrict__ ctr, typename OP::template Smem<NG> &sm, u32 block, u32 nblocks)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar: the loop control stays on the scalar unit
@@ -254,10 +254,10 @@ __device__ __forceinline__ void scan_list_body(const OP &op, const int8_t *__res
 
 // The same walk for rows of d > 128 bytes (d a multiple of 64).  The first chunk of the next vertex's rows (of lists of up to 32 entries:
 // the first two) is asked for as soon as the current one's matrix work is done, so it travels during its prune test and its stores.
-template <typename OP, int NG>
+template <typename OP, int NG, typename OUT>
 __device__ __forceinline__ void scan_list_stream_body(const OP &op, const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
                                                       int *__restrict__ deg, const int *__restrict__ list, u32 n_active,
-                                                      EdgeOut &out,
+                                                      OUT &out,
                                                       RoundCtr *__restrict__ ctr, typename OP::template Smem<NG> &sm, u32 block, u32 nblocks)
 {
     // (two chunks for longer lists as well: 60,000 x 784 uint8 4.60 -> 4.79 ms, 1M x 96 101 -> 119, whose registers spill)
@@ -324,10 +324,10 @@ __device__ __forceinline__ void scan_list_stream_body(const OP &op, const int8_t
 }
 
 // KS = 0: rows of d > 128 bytes, streamed
-template <typename OP, int NG, int KS>
+template <typename OP, int NG, int KS, typename OUT>
 __device__ __forceinline__ void scan_list_any(const OP &op, const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
                                               int *__restrict__ deg, const int *__restrict__ list, u32 n_active,
-                                              EdgeOut &out,
+                                              OUT &out,
                                               RoundCtr *__restrict__ ctr, typename OP::template Smem<NG> &sm, u32 block, u32 nblocks)
 {
     if constexpr (KS == 0) scan_list_stream_body<OP, NG>(op, X, d, R, keys, deg, list, n_active, out, ctr, sm, block, nblocks);
@@ -373,10 +373,10 @@ __device__ __forceinline__ void pack_gather(const int8_t *__restrict__ X, const 
 
 // Same two-deep software pipeline as k_update_scan_mfma_u8; trip g of a wavefront takes list entries
 // [P g, P g + P).
-template <typename OP, int P, int KS>
+template <typename OP, int P, int KS, typename OUT>
 __device__ __forceinline__ void scan_packed_body(const OP &op, const int8_t *__restrict__ X, int R, u64 *__restrict__ keys,
                                                  int *__restrict__ deg, const int *__restrict__ list,
-                                                 u32 n_active, EdgeOut &out, RoundCtr *__restrict__ ctr,
+                                                 u32 n_active, OUT &out, RoundCtr *__restrict__ ctr,
                                                  typename OP::template Smem<1> &sm, u32 block, u32 nblocks)
 {
     constexpr int W = 32 / P;
@@ -439,10 +439,10 @@ __device__ __forceinline__ void scan_packed_body(const OP &op, const int8_t *__r
 }
 
 // The same for rows of d > 128 bytes (see scan_list_stream_body).
-template <typename OP, int P>
+template <typename OP, int P, typename OUT>
 __device__ __forceinline__ void scan_packed_stream_body(const OP &op, const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
                                                         int *__restrict__ deg, const int *__restrict__ list,
-                                                        u32 n_active, EdgeOut &out, RoundCtr *__restrict__ ctr,
+                                                        u32 n_active, OUT &out, RoundCtr *__restrict__ ctr,
                                                         typename OP::template Smem<1> &sm, u32 block, u32 nblocks)
 {
     constexpr int W = 32 / P;
@@ -502,10 +502,10 @@ __device__ __forceinline__ void scan_packed_stream_body(const OP &op, const int8
     if (lane == 0 && rows) add_round_stats(ctr, evals_algo, (u64)tiles * 1024ull, rows, nprops_total);
 }
 
-template <typename OP, int P, int KS>
+template <typename OP, int P, int KS, typename OUT>
 __device__ __forceinline__ void scan_packed_any(const OP &op, const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
                                                 int *__restrict__ deg, const int *__restrict__ list, u32 n_active,
-                                                EdgeOut &out,
+                                                OUT &out,
                                                 RoundCtr *__restrict__ ctr, typename OP::template Smem<1> &sm, u32 block, u32 nblocks)
 {
     if constexpr (KS == 0) scan_packed_stream_body<OP, P>(op, X, d, R, keys, deg, list, n_active, out, ctr, sm, block, nblocks);

@@ -65,9 +65,9 @@ __global__ __launch_bounds__(256) void k_prepare_u8_rows(const uint8_t *__restri
 
 // The body of Alg. 4's vertex loop for the vertex in `cur`, whose Gram tiles `gram` yields.  hold() names the
 // registers in flight for the trips after this one (see arrived).
-template <int NG, typename GRAM, typename HOLD>
+template <int NG, typename GRAM, typename OUT, typename HOLD>
 __device__ __forceinline__ void scan_vertex_u8(const ScanItem &cur, const GRAM &gram, MfmaScanSmem<NG> &sm, int R, u64 *__restrict__ keys,
-                                               int *__restrict__ deg, EdgeOut &out, int lane, u64 &tiles, u64 &rows,
+                                               int *__restrict__ deg, OUT &out, int lane, u64 &tiles, u64 &rows,
                                                u64 &nprops_total, u32 &ev_lane, HOLD hold)
 {
     const int l32 = lane & 31, half = lane >> 5;
@@ -229,9 +229,9 @@ __device__ __forceinline__ void scan_vertex_u8(const ScanItem &cur, const GRAM &
     nprops_total += np_base;
 }
 
-template <int P, typename GRAM, typename HOLD>
+template <int P, typename GRAM, typename OUT, typename HOLD>
 __device__ __forceinline__ void pack_vertices_u8(const PackItem &cur, const GRAM &gram, MfmaScanSmem<1> &sm, int R,
-                                                 u64 *__restrict__ keys, int *__restrict__ deg, EdgeOut &out, int lane,
+                                                 u64 *__restrict__ keys, int *__restrict__ deg, OUT &out, int lane,
                                                  u32 &tiles, u32 &rows, u32 &nprops_total, u32 &ev_lane, HOLD hold)
 {
     constexpr int W = 32 / P;
@@ -364,28 +364,28 @@ struct U8Op {
 };
 
 // (four groups of streamed rows: 160 accumulator registers, so one block per CU)
-template <int NG, int KS>
+template <int NG, int KS, typename OUT>
 __global__ __launch_bounds__(256, (NG == 1 ? 5 : NG == 2 ? 3 : KS == 0 && NG == 4 ? 1 : 2)) void k_update_scan_mfma_u8(
     const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys,
     int *__restrict__ deg, const int *__restrict__ list, const u32 *__restrict__ n_list,
     EdgeSink sink, RoundCtr *__restrict__ ctr)
 {
     __shared__ MfmaScanSmem<NG> smem[4];
-    __shared__ PendingEdges pend[4];
-    EdgeOut out(sink, pend[threadIdx.x >> 6], R);
+    __shared__ typename OUT::Pending pend[4];
+    OUT out(sink, pend[threadIdx.x >> 6], R);
     scan_list_any<U8Op, NG, KS>(U8Op(), X, d, R, keys, deg, list, *n_list, out, ctr, smem[threadIdx.x >> 6], blockIdx.x, gridDim.x);
 }
 
 // The three short-list classes in one launch: blockIdx.y = degree class (lists of at most 8, 16, 32
 // entries: 4, 2, 1 vertices per wavefront).  Each class is walked by the gridDim.x blocks of its row.
-template <int KS>
+template <int KS, typename OUT>
 __global__ __launch_bounds__(256, 4) void k_update_scan_mfma_u8_small(
     const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
     const int *__restrict__ lists, long long N, EdgeSink sink, RoundCtr *__restrict__ ctr)
 {
     __shared__ MfmaScanSmem<1> smem[4];
-    __shared__ PendingEdges pend[4];
-    EdgeOut out(sink, pend[threadIdx.x >> 6], R);
+    __shared__ typename OUT::Pending pend[4];
+    OUT out(sink, pend[threadIdx.x >> 6], R);
     MfmaScanSmem<1> &sm = smem[threadIdx.x >> 6];
     const int y = blockIdx.y;
     const int *list = lists + (size_t)y * N;
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(256, 4) void k_update_scan_mfma_u8_small(
 // per CU).  C0 = 0, every class: for inputs so small that no class alone has enough lists to fill the chip
 // (the short-list classes lose occupancy: with many active lists their own launch is faster).  C0 = 3, the
 // long-list classes only, next to k_update_scan_mfma_u8_small: for large inputs.
-template <int KS, int NC, int C0 = 0>
+template <int KS, typename OUT, int NC, int C0 = 0>
 __global__ __launch_bounds__(256, (KS == 0 && NC == 6 ? 1 : 2)) void k_update_scan_mfma_u8_all(
     const int8_t *__restrict__ X, int d, int R, u64 *__restrict__ keys, int *__restrict__ deg,
     const int *__restrict__ lists, long long N, EdgeSink sink, RoundCtr *__restrict__ ctr)
@@ -412,8 +412,8 @@ __global__ __launch_bounds__(256, (KS == 0 && NC == 6 ? 1 : 2)) void k_update_sc
     constexpr int NGMAX = NC - 2;
     static_assert(NC >= 4 && NC <= 6, "short lists plus one to three long-list classes");
     __shared__ MfmaScanSmem<NGMAX> smem[4];
-    __shared__ PendingEdges pend[4];
-    EdgeOut out(sink, pend[threadIdx.x >> 6], R);
+    __shared__ typename OUT::Pending pend[4];
+    OUT out(sink, pend[threadIdx.x >> 6], R);
     if (C0 == 0) stamp_scan_start(ctr);
     // work per list: 4, 2, 1 lists share a tile; among the longer classes in proportion to their NG (NG + 1) / 2
     // tiles (3 : 6 : 10; the division is sensitive there: 3 : 4.5 or 3 : 8 costs the 1M build 4 % of its scan time),

@@ -80,6 +80,7 @@ struct PendingEdges {
 // them: 1M x 128 uint8 3.7 of 25.2 ms, 1M x 96 float32 8.1 of 102; at the end of a wavefront's walk it kept too few in flight: 100,000 x 128 a heavy round 63 + 23 -> 94 us.)
 // What waits from trip to trip is the key and the target of an edge in LDS, one edge per lane, and two registers.
 struct EdgeOut {
+    typedef PendingEdges Pending;
     const EdgeSink &s;
     PendingEdges &pend;
     int R, cap;
@@ -192,6 +193,30 @@ struct EdgeOut {
         how = rank | l << 8;
         waiting = (u64)pm;
         slot0 = 0xFFFFFFFFu;
+    }
+};
+
+// What a tile scan takes in place of an EdgeOut to leave all its edges in props: a kernel that has the registers of one block per CU (uint8 rows streamed, lists of
+// up to 128 entries) pays for the other's code even where it does not scatter.
+struct EdgesLeft {
+    struct Pending {};
+    const EdgeSink &s;
+    int R;
+
+    __device__ __forceinline__ EdgesLeft(const EdgeSink &sink, Pending &, int R_) : s(sink), R(R_) {}
+    __device__ __forceinline__ void flush(int) {}
+    template <int NG>
+    __device__ __forceinline__ void list(const u64 (&key)[NG], const u32 (&tgt)[NG], const int (&place)[NG], int np, int u, int lane, void *)
+    {
+#pragma unroll
+        for (int I = 0; I < NG; ++I)
+            if (place[I] >= 0) emit_redirect(key[I], tgt[I], s.props + (size_t)u * R + (place[I] & 255));
+        if (lane == 0) s.nprop[u] = np;
+    }
+    __device__ __forceinline__ void pack(u64 key, u32 tgt, int, int u, int slot, u32 pm, bool leader, u32 segmask, int lane, void *)
+    {
+        if (lane < 32 && ((pm >> (lane & 31)) & 1u)) emit_redirect(key, tgt, s.props + (size_t)u * R + slot);
+        if (leader) s.nprop[u] = __popc(pm & segmask);
     }
 };
 

@@ -76,6 +76,14 @@ def test_either_side_of_the_line(rn, dtype, n, d, own):
     compare(rn, rows(n, d, dtype, 3), 6, 32, 1, 2, own)
 
 
+# streamed uint8 rows, lists of up to 128 entries: up to 49,152 rows; and each launch that leaves its edges, of all classes (up to 524,288 rows), of the short
+# and the longer lists (up to 2,097,152), of every class
+@pytest.mark.parametrize("n,d,S,R,own", [(49_152, 129, 120, 128, True), (49_153, 129, 120, 128, False), (524_289, 129, 100, 128, False),
+                                         (2_097_153, 129, 20, 128, False), (1_093_751, 1025, 40, 64, False), (1_093_751, 1025, 70, 96, False)])
+def test_streamed_bytes_in_long_lists(rn, n, d, S, R, own):
+    compare(rn, rows(n, d, "uint8", 4), S, R, 1, 2, own)
+
+
 # beyond the line: what the scans leave in props, for every width of the lists
 @pytest.mark.parametrize("S,R", [(7, 8), (30, 32), (60, 64), (90, 96), (120, 128)])
 @pytest.mark.parametrize("dtype,n,d", [("uint8", 106_000, 16000), ("float32", 103_600, 8192), ("bfloat16", 103_600, 8192)])
