@@ -328,69 +328,17 @@ __device__ __forceinline__ u64 close_keys(u64 key, int x, bool have, u64 list, b
     }
 }
 
-// For scans that leave their edges in props (see scan_scatters): every active vertex moves its redirected edges to their targets, 16 lanes per vertex.  Lanes of a
-// group that share a target take their arrival numbers with one atomic (a vertex usually redirects
-// several entries to the same kept neighbour).  Arrivals below round_inbox(R) go to the target's inbox, later ones onto
-// one of its lists (see LATE_LISTS).
-__global__ __launch_bounds__(BLOCK) void k_scatter(long long N, int R, const int *lists, int ncl, RoundCtr *ctr,
-                                                   Prop *props, const int *nprop, int *fill, u64 *inbox, LateHeads heads, u32 enough)
+// For scans that leave their edges in props (see scan_scatters): every active vertex moves its redirected edges to their targets.  Arrivals below round_inbox(R) go to
+// the target's inbox, later ones onto one of its lists (see LATE_LISTS).
+__global__ __launch_bounds__(BLOCK) void k_scatter(long long N, const int *lists, int ncl, RoundCtr *ctr, EdgeSink sink, int R, u32 enough)
 {
-    const int cap = round_inbox(R);
-    const int lane = threadIdx.x & 63, sub = lane & 15, gbase = lane & ~15;
     const u32 g = (blockIdx.x * BLOCK + threadIdx.x) >> 4, ng = (gridDim.x * BLOCK) >> 4;
     // the classes' lists as one: the grid is shared by their entries, however they are spread over the classes
     const ActiveLists al = active_lists(lists, N, ctr, ncl);
     const u32 n = al.start[NDEG];
     if (n < RNND_MAX_SLOTS) stamp_scan_stop(ctr);      // (always: the clock is read once the scan's counters are here)
     if (enough && blockIdx.x == 0 && threadIdx.x == 0) decide_next_form(ctr, n, enough);
-    if (g >= n) return;
-    // the loads of the next vertex (its count and its first 16 edges) are issued before the atomics
-    // of the current one; the list entry of the vertex after that is fetched one trip earlier still
-    auto vertex_at = [&](unsigned long long i) -> int { return i < n ? active_vertex(al, (u32)i) : -1; };
-    auto first_edges = [&](int u, int &np, Prop &pr) {
-        np = 0;
-        pr.key = 0; pr.tgt = 0xFFFFFFFFu; pr.next = 0;
-        if (u >= 0) {
-            np = nprop[u];
-            if (sub < R) pr = props[(size_t)u * R + sub];   // slots past np exist; masked below
-        }
-    };
-    int u = vertex_at(g), np;
-    Prop pr0;
-    first_edges(u, np, pr0);
-    int u_next = vertex_at((unsigned long long)g + ng);
-    for (unsigned long long it = g; it < n; it += ng) {
-        int np_next;
-        Prop pr_next;
-        first_edges(u_next, np_next, pr_next);
-        const int u_after = vertex_at(it + 2ull * ng);
-
-        for (int p0 = 0; p0 < np; p0 += 16) {      // same trip count for the whole group
-            const int p = p0 + sub;
-            const bool have = p < np;
-            Prop pr = pr0;
-            if (p0 > 0 && have) pr = props[(size_t)u * R + p];
-            if (!have) pr.tgt = 0xFFFFFFFFu;
-            // lanes of my group with my target
-            // rotation r of the group's row brings the target of lane (sub - r) mod 16
-            const u32 same = (1u << sub) | same_target_mask<1>(pr.tgt, sub);
-            const int leader = __builtin_ctz(same), rank = __popc(same & ((1u << sub) - 1u));
-            int base = 0;
-            if (have && sub == leader) base = atomicAdd(&fill[pr.tgt], __popc(same));
-            base = __shfl(base, gbase + leader);
-            if (have) {
-                const int s = base + rank;
-                if (s < cap) {
-                    inbox[(size_t)pr.tgt * INBOX_CAP + s] = pr.key;
-                } else {
-                    const size_t slot = (size_t)u * R + p;
-                    props[slot].next = atomicExch(&heads.base[(size_t)pr.tgt * heads.stride + ((u32)(s - cap) & (LATE_LISTS - 1u))], (u32)slot);
-                }
-            }
-        }
-        u = u_next; np = np_next; pr0 = pr_next;
-        u_next = u_after;
-    }
+    scatter_vertices<16, 1>(sink, [&](u32 i) { return active_vertex(al, i); }, g, ng, n, R);
 }
 
 // What k_scatter does besides scattering, for a round whose scan has scattered: by one thread.
@@ -2023,7 +1971,8 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
     const long long vertices = run ? (long long)run->count : N;
     const u32 enough = vertices / 16 > DECIDE_MIN_ACTIVE ? (u32)(vertices / 16) : DECIDE_MIN_ACTIVE;
     const bool own_scatter = use_classes == 2 && scan_scatters(plan, rv, N, dtype, R);
-    EdgeSink sink = edge_sink(w, R);
+    const EdgeSink all = edge_sink(w, R);
+    EdgeSink sink = all;
     if (!own_scatter) sink.count = nullptr;
     if (run) {
         const unsigned cb = (run->count + 1023u) / 1024u;
@@ -2066,8 +2015,7 @@ static hipError_t launch_update_round(const Workspace &w, const RowsView &rv, lo
     const int ncl = use_classes ? NDEG : 1;
     const u32 decide = open_dt != RNND_U8 ? enough : 0u;
     if (!own_scatter)
-        hipLaunchKernelGGL(k_scatter, dim3(pb), dim3(BLOCK), 0, st, N, R, w.lists, ncl, c, w.props, (const int *)w.nprop, w.fill,
-                           w.inbox, late_heads(w.inbox, w.bins, R), decide);
+        hipLaunchKernelGGL(k_scatter, dim3(pb), dim3(BLOCK), 0, st, N, (const int *)w.lists, ncl, c, all, R, decide);
     if (!run && !re.round_stop && N <= MERGE_BLOCKS_MAX_N) {
         launch_merge_blocks(open_dt, st, N, R, w, keys, deg, use_classes, c, X, d, own_scatter, decide);
         return hipGetLastError();

@@ -703,7 +703,7 @@ __device__ __forceinline__ void finish_left(const FloatRows &fr, int R, u64 *key
     };
     f32_scan_body<NG, 1, NRC, false, DT>(fr.X, fr.d, R, keys, deg, at, 0, 1, n, sink.props, sink.nprop, ctr, [](int) {}, *reinterpret_cast<F32ScanSmem<NRC> *>(sm));
     next = __builtin_amdgcn_readfirstlane(head);
-    if (scatter) scatter_walk(sink, at, 0, 1, n, R);
+    if (scatter) scatter_chain(sink, at, n, R);
 }
 
 // Lists of at most 8, 16, 32 entries (blockIdx.y = degree class): 4, 2, 1 vertices per wavefront.

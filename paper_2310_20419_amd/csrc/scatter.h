@@ -220,27 +220,96 @@ struct EdgesLeft {
     }
 };
 
-// The edges that a form without tiles has left in props[u * R ..], nprop[u] of them, for the vertices at(gw), at(gw + nw), ... below `end`: one wavefront each.
+// The edges in props[u * R ..], nprop[u] of them, of the vertices at(i), i = first, first + step, ... below `end`, LANES (16 or 64) lanes per vertex.  Lanes of a row of 16 that share a
+// target take their arrival numbers with one atomic (a vertex usually redirects several entries to the same kept neighbour).  The loads of the next vertex (its count and its first
+// LANES edges) are issued before the atomics of the current one; the list entry of the vertex after that is fetched one trip earlier still.  The atomics of C times LANES edges are on
+// their way together.
+template <int LANES, int C, typename AT>
+__device__ __forceinline__ void scatter_vertices(const EdgeSink &s, AT at, unsigned long long first, unsigned long long step, u32 end, int R)
+{
+    const int cap = round_inbox(R), lane = threadIdx.x & 63, e = lane & (LANES - 1), sub = lane & 15, gbase = lane & ~15;
+    if (first >= end) return;
+    auto vertex_at = [&](unsigned long long i) -> int { return i < end ? at((u32)i) : -1; };
+    auto first_edges = [&](int u, int &np, Prop &pr) {
+        np = 0;
+        pr.key = 0; pr.tgt = 0xFFFFFFFFu; pr.next = 0;
+        if (u >= 0) {
+            np = s.nprop[u];
+            if (e < R) pr = s.props[(size_t)u * R + e];   // slots past np exist; masked below
+        }
+    };
+    int u = vertex_at(first), np;
+    Prop pr0;
+    first_edges(u, np, pr0);
+    int u_next = vertex_at(first + step);
+    for (unsigned long long it = first; it < end; it += step) {
+        int np_next;
+        Prop pr_next;
+        first_edges(u_next, np_next, pr_next);
+        const int u_after = vertex_at(it + 2ull * step);
+
+        for (int p0 = 0; p0 < np; p0 += LANES * C) {      // same trip count for all lanes of a vertex
+            Prop pr[C];
+            u32 same[C];
+            int base[C];
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const int p = p0 + LANES * c + e;
+                pr[c] = pr0;
+                if ((c > 0 || p0 > 0) && p < np) pr[c] = s.props[(size_t)u * R + p];
+                if (p >= np) pr[c].tgt = 0xFFFFFFFFu;
+            }
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                // lanes of my row with my target: rotation r of the row brings the target of lane (sub - r) mod 16
+                same[c] = (1u << sub) | same_target_mask<1>(pr[c].tgt, sub);
+                base[c] = 0;
+                if (p0 + LANES * c + e < np && sub == __builtin_ctz(same[c])) base[c] = atomicAdd(&s.count[pr[c].tgt], __popc(same[c]));
+            }
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const int p = p0 + LANES * c + e, place = __shfl(base[c], gbase + __builtin_ctz(same[c])) + __popc(same[c] & ((1u << sub) - 1u));
+                if (p < np) {
+                    if (place < cap) {
+                        s.inbox[(size_t)pr[c].tgt * INBOX_CAP + place] = pr[c].key;
+                    } else {
+                        const size_t slot = (size_t)u * R + p;
+                        s.props[slot].next = atomicExch(&s.heads.base[(size_t)pr[c].tgt * s.heads.stride + ((u32)(place - cap) & (LATE_LISTS - 1u))], (u32)slot);
+                    }
+                }
+            }
+        }
+        u = u_next; np = np_next; pr0 = pr_next;
+        u_next = u_after;
+    }
+}
+
+// The edges that a form without tiles has left in props, for its vertices at(gw), at(gw + nw), ... below `end`.  These kernels keep fewer wavefronts in flight than k_scatter, so each
+// takes four vertices and 32 edges of them at once, unless it has no more than two.  8 rounds, k_scatter / a vertex at a time / now, ms, float32 with norms over 12 binades: 1M x 96
+// 23.6 / 24.8 / 23.8, 1M x 32, R = 32, 9.21 / 10.56 / 9.41, 200,000 x 100, R = 32, 3.85 / 4.01 / 3.83, R = 128 14.3 / 14.4 / 14.2 (16 edges of each: 9.41, 3.82, 14.3; 64: 9.55, 3.86, 14.2).
 template <typename AT>
 __device__ __forceinline__ void scatter_walk(const EdgeSink &s, AT at, u32 gw, u32 nw, u32 end, int R)
 {
-    if (!s.count) return;
+    if (!s.count || gw >= end) return;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");      // the edges are read by other lanes than wrote them
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    const int cap = round_inbox(R), lane = threadIdx.x & 63, sub = lane & 15, gbase = lane & ~15;
-    for (u32 i = gw; i < end; i += nw) {
-        const int u = at(i), np = s.nprop[u];
-        for (int p0 = 0; p0 < np; p0 += 64) {
-            const int p = p0 + lane;
-            const u32 slot = (u32)u * (u32)R + (u32)(p < np ? p : 0);
-            const u64 key = s.props[slot].key;
-            const u32 tgt = p < np ? s.props[slot].tgt : 0xFFFFFFFFu;
-            const u32 same = (1u << sub) | same_target_mask<1>(tgt, sub);
-            const int leader = __builtin_ctz(same);
-            int first = 0;
-            if (p < np && sub == leader) first = atomicAdd(&s.count[tgt], __popc(same));
-            first = __shfl(first, gbase + leader);
-            if (p < np) deliver(s, cap, key, tgt, first + __popc(same & ((1u << sub) - 1u)), slot);
+    if (end - gw <= 2u * nw) scatter_vertices<64, 1>(s, at, gw, nw, end, R);
+    else scatter_vertices<16, 2>(s, at, gw + (unsigned long long)((threadIdx.x & 63) >> 4) * nw, 4ull * nw, end, R);
+}
+// ... and for n of them that are asked in order, by all lanes together.
+template <typename AT>
+__device__ __forceinline__ void scatter_chain(const EdgeSink &s, AT at, u32 n, int R)
+{
+    if (!s.count) return;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    const int group = (threadIdx.x & 63) >> 4;
+    for (u32 i = 0; i < n; i += 4u) {
+        int mine = -1;
+        for (int q = 0; q < 4 && i + (u32)q < n; ++q) {
+            const int u = at(i + (u32)q);
+            if (group == q) mine = u;
         }
+        scatter_vertices<16, 2>(s, [=](u32) { return mine; }, 0ull, 1ull, mine >= 0 ? 1u : 0u, R);
     }
 }

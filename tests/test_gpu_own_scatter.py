@@ -67,6 +67,19 @@ def test_edges_arrive_whatever_the_width_of_the_lists(rn, dtype, d, S, R):
     compare(rn, rows(1500, d, dtype, S), S, R, 2, 3)
 
 
+# rows whose norms lie over twelve binades take groups of 16 rows, from the first or the second round on, whose edges are walked after the scan: a wavefront has one or two
+# vertices of 8,192, whatever the class, more of 60,000
+@pytest.mark.parametrize("n", [8_192, 60_000])
+@pytest.mark.parametrize("S,R", [(30, 32), (60, 64), (90, 96), (120, 128)])
+@pytest.mark.parametrize("dtype", ["float32", "bfloat16"])
+def test_edges_of_groups_arrive(rn, dtype, n, S, R):
+    import torch
+    X = rows(n, 64, dtype, S)
+    X = (X.float() * torch.exp2((torch.arange(n, device="cuda") % 13 - 6).float())[:, None]).to(X.dtype)
+    compare(rn, X, S, R, 1, 3)
+    assert rn.rnnd_build_ex(X, S, R, 1, 3, 5, want_keys=False)[3].group_scans >= 2
+
+
 # rows of up to 1,024 bytes: always; longer ones up to 1.75e9 / (1088 + 512) = 1,093,750 rows of 1,088 bytes, / (16384 + 512) = 103,574 of 16,384
 @pytest.mark.parametrize("dtype,n,d,own", [("uint8", 1_302_084, 784, True), ("uint8", 1_200_000, 1024, True),
                                            ("uint8", 1_093_750, 1025, True), ("uint8", 1_093_751, 1025, False),
