@@ -39,8 +39,11 @@ static void launch(const ScanLaunch &l, FloatRows fr, const void *rows, u32 rowb
     }
     static const int per_s = resident_blocks_per_cu(k_scan_float_small<DT>, 4);
     const int ny = 1 + (l.R > 8) + (l.R > 16);
-    // (half the blocks that a vertex per wavefront would take, for each of three classes: 5,000 x 96, R = 32, 1.39 -> 1.33 ms)
-    hipExtLaunchKernelGGL((k_scan_float_small<DT>), dim3(capped(cu_count() * per_s, l.N / 2), ny), dim3(256), 0, l.st, l.e_start, l.R <= 32 ? e_stop : (hipEvent_t) nullptr, 0, G, rowbytes, fr,
+    // Half the blocks that a vertex per wavefront would take, for each of three classes, where a round waits for its launches more than for its rows.  R = 32, a vertex per wavefront / half, ms: rows of 192
+    // bytes 300 0.749 / 0.678, 4,000 1.235 / 1.197; 256 bytes 1,000 0.866 / 0.870, 6,000 1.568 / 1.507; 768 bytes 1,000 1.046 / 1.054, 2,000 1.319 / 1.337, 4,000 1.707 / 1.683; 1,920 bytes 2,000 2.02 / 2.11,
+    // 4,000 2.48 / 2.52, 8,000 3.544 / 3.526; 4,000 bytes 2,000 3.35 / 3.55, 6,000 5.54 / 5.58.
+    const bool halve = rowbytes <= 256u || l.N >= 4ll * rowbytes;
+    hipExtLaunchKernelGGL((k_scan_float_small<DT>), dim3(capped(cu_count() * per_s, halve ? l.N / 2 : l.N), ny), dim3(256), 0, l.st, l.e_start, l.R <= 32 ? e_stop : (hipEvent_t) nullptr, 0, G, rowbytes, fr,
                           l.R, l.keys, l.deg, l.lists, l.sink, l.c);
     if (l.R <= 32) return;
     if (l.R > 96) {

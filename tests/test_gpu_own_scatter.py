@@ -67,6 +67,13 @@ def test_edges_arrive_whatever_the_width_of_the_lists(rn, dtype, d, S, R):
     compare(rn, rows(1500, d, dtype, S), S, R, 2, 3)
 
 
+# lists of up to 32 entries of few rows: half the blocks for rows of up to 256 bytes, and from 4 rows for each byte on
+@pytest.mark.parametrize("n,d", [(700, 128), (700, 129), (1_535, 192), (1_536, 192), (9, 4000)])
+@pytest.mark.parametrize("R", [32, 128])
+def test_short_lists_of_few_rows(rn, n, d, R):
+    compare(rn, rows(n, d, "float32", 5), min(30, n - 1), R, 2, 3)
+
+
 # rows whose norms lie over twelve binades take groups of 16 rows, from the first or the second round on, whose edges are walked after the scan: a wavefront has one or two
 # vertices of 8,192, whatever the class, more of 60,000
 @pytest.mark.parametrize("n", [8_192, 60_000])
