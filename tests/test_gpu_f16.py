@@ -80,6 +80,17 @@ def test_build_on_half_rows(rn, oracle_mod, variant, kind, N, d, S, R, T1, T2):
         assert (found.cpu().numpy() == wfound).all() and evals == wevals
 
 
+# a trip of an exact distance takes 2, 3, 4, 5 or 8 pieces of 8 coordinates in each of 8 lanes: around each of these lengths, and two trips of the merge's
+@pytest.mark.parametrize("d", [120, 128, 136, 184, 192, 200, 256, 264, 320, 328, 384, 392, 512, 520])
+def test_rows_of_whole_and_partial_trips(rn, oracle_mod, variant, d):
+    X16 = _half("gauss", 500, d, d)
+    want = oracle_mod.build_sync(X16.astype(np.float32), 12, 40, 2, 3, 21)
+    graph, degree, keys, _ = rn.rnnd_build_ex(cuda(X16), 12, 40, 2, 3, 21)
+    assert_snapshot_equal(want.snap, True, keys, degree, "d %d" % d)
+    graph, degree, keys, _ = rn.rnnd_build_blocks(cuda(X16), 12, 40, 2, 3, 21, 1)      # the merge in a launch of its own
+    assert_snapshot_equal(want.snap, True, keys, degree, "d %d, one run" % d)
+
+
 def test_blocks_and_steps_on_half_rows(rn, oracle_mod):
     X16 = _half("unit", 1500, 96, 5)
     X = X16.astype(np.float32)
