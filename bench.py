@@ -25,8 +25,8 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 # HBM bytes per scan launch (one round's scan kernels together) measured with rocprofv3 --pmc FETCH_SIZE /
 # WRITE_SIZE (two runs, each scaled by what the same counter reads for a plain 1 GiB copy in the same run);
 # see profiles/update_scan_cfg{3,4,5}_hbm_traffic.txt.  Keyed by (workload, kernel variant); None where it
-# has not been measured.
-TRAFFIC_PER_LAUNCH = {("cfg3", 2): 1.0224e9, ("cfg4", 3): 5.2354e9, ("cfg5", 3): 2.8962e10}
+# has not been measured.  (cfg3, cfg4: with the scatter of the redirected edges, which those scans do themselves.)
+TRAFFIC_PER_LAUNCH = {("cfg3", 2): 1.0426e9, ("cfg4", 3): 5.4336e9, ("cfg5", 3): 2.8979e10}
 
 
 def host_cpu():
@@ -82,14 +82,24 @@ def u8_scan_kernels(cfg):
     """The launches that make up one round's uint8 matrix-core scan (the library's rule: by R and N)."""
     ks = cfg.d // 32
     if cfg.R <= 32:
-        return "k_update_scan_mfma_u8_small<%d> (one launch per round)" % ks
+        return "k_update_scan_mfma_u8_small<%d,OUT> (one launch per round)" % ks
     if cfg.N <= 524288:
-        return "k_update_scan_mfma_u8_all<%d,NC> (one launch per round for all degree classes)" % ks
+        return "k_update_scan_mfma_u8_all<%d,OUT,NC> (one launch per round for all degree classes)" % ks
     if cfg.R <= 64 or cfg.N > 2097152:
-        return ("k_update_scan_mfma_u8_small<%d> + k_update_scan_mfma_u8<NG,%d>, NG = 2 .. %d (one round's scan launches, back "
+        return ("k_update_scan_mfma_u8_small<%d,OUT> + k_update_scan_mfma_u8<NG,%d,OUT>, NG = 2 .. %d (one round's scan launches, back "
                 "to back)" % (ks, ks, (cfg.R + 31) // 32))
-    return ("k_update_scan_mfma_u8_small<%d> + k_update_scan_mfma_u8_all<%d,NC,3> (one round's scan launches: lists of at "
+    return ("k_update_scan_mfma_u8_small<%d,OUT> + k_update_scan_mfma_u8_all<%d,OUT,NC,3> (one round's scan launches: lists of at "
             "most 32 entries, then the longer classes; back to back)" % (ks, ks))
+
+
+def scan_scatters(cfg, kv, width, rowbytes):
+    """Whether the scan by tiles sends its redirected edges to their targets itself (the library's rule, by the bytes it
+    gathers per row, N and the width of the lists); a kernel after it does otherwise, and scan_ms is without that."""
+    if kv == 2 and cfg.d <= 128:
+        return True
+    if kv == 2 and width > 96 and cfg.N > 49152:
+        return False
+    return rowbytes <= 1024 or cfg.N * (rowbytes + 512) <= 1750000000
 
 
 def exact_top10(Xd, Qd):
@@ -206,12 +216,15 @@ def measure(rn, cfg, X, Xd, esz, st16, steps, warmup, args, with_search=True, wi
             rn.rnnd_set_event_timing(False)
     # dominant kernel: the UpdateNeighbors scan (the class launches of one round taken together).
     # Algorithmic bytes of one launch = rows of X it must gather (d*esz each) + the list entries it reads
-    # (8 B) and writes back (8 B) + the redirected edges it emits (16 B); summed over the T1*T2 launches of
-    # the last timed build, durations by HIP events on the build's stream.
+    # (8 B) and writes back (8 B) + the redirected edges: 8 B each where the scan writes them to their targets' inboxes (the
+    # time then includes that scatter and its atomics), 16 B where it leaves them to a kernel after it; summed over the
+    # T1*T2 launches of the last timed build, durations by HIP events on the build's stream.
     # (float32 rows: the scan gathers the half-precision copy, 2 bytes a coordinate; --variant 2 whole rows on the f64 matrix cores)
     f64 = s["kernel_variant"] == 3 and args.variant == 2
     gather_esz = 2 if s["kernel_variant"] == 3 and not f64 else esz
-    scan_bytes = sum(g * (cfg.d * gather_esz + 16) + 16 * p for g, p in zip(s["gathered_rows"], s["proposals"]))
+    own_scatter = s["kernel_variant"] in (2, 3) and not f64 and scan_scatters(cfg, s["kernel_variant"], args.merge_cap or cfg.R, cfg.d * gather_esz)
+    edge_bytes = 8 if own_scatter else 16
+    scan_bytes = sum(g * (cfg.d * gather_esz + 16) + edge_bytes * p for g, p in zip(s["gathered_rows"], s["proposals"]))
     scan_ms = scan_ms_events if scan_ms_events else scan_ms_clock
     hbm_gbs = scan_bytes / (scan_ms * 1e-3) / 1e9 if scan_ms > 0 else 0.0
     kv = s["kernel_variant"]
@@ -246,6 +259,7 @@ def measure(rn, cfg, X, Xd, esz, st16, steps, warmup, args, with_search=True, wi
                 "algorithmic_bytes_per_launch": scan_bytes / max(1, rounds)}
     roof["launch_timing"] = ("HIP events attached to the first and last scan launch of every round, %d extra build(s) after "
                              "the timed ones" % args.event_steps) if scan_ms_events else "device clock, the timed builds"
+    roof["includes_scatter"] = own_scatter
     roof["avg_launch_ms_device_clock"] = scan_ms_clock / max(1, rounds)    # over the timed builds (last one)
     if traffic:
         roof["traffic_over_algorithmic"] = traffic / (scan_bytes / max(1, rounds))

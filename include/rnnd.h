@@ -75,7 +75,11 @@ typedef struct {
                                                to the exact distance */
     float total_ms, init_ms;                /* GPU time of the whole call / of RandomGraph (HIP events) */
     float round_ms[RNND_MAX_ROUNDS];        /* GPU time of each UpdateNeighbors round (see rnnd_set_event_timing) */
-    float scan_ms[RNND_MAX_ROUNDS];         /* of which: the scan kernels (Alg. 4's loop body) */
+    float scan_ms[RNND_MAX_ROUNDS];         /* of which: the scan kernels (Alg. 4's loop body).  Scans by tiles also send the
+                                               edges they redirect to their targets, unless rows of more than 1,024 bytes as gathered
+                                               (float32 in builds: 2 a coordinate) take more than 1.75 GB, with 512 for each, or
+                                               N > 49,152 uint8 rows of more than 128 bytes have lists of more than 96 slots: then, and
+                                               in the other forms, a kernel after the scan does, and is not counted */
     float reverse_ms[RNND_MAX_ROUNDS];      /* GPU time of each AddReverseEdges call */
     int64_t init_evals;                     /* N*S */
     int64_t active[RNND_MAX_ROUNDS];        /* vertices with at least one "new" entry */
@@ -180,7 +184,7 @@ int rnnd_set_workspace_poison(int on);
 
 /* Where the per-round times of rnnd_stats (round_ms, scan_ms, reverse_ms) come from.  Process-wide.
  *   0 (default)  the device's constant-rate clock, read by the kernels themselves (the first workgroup of a round's
- *                first scan launch, of its scatter launch, ...): costs nothing, so a build with statistics takes as
+ *                first scan launch, of the launch after its scans, ...): costs nothing, so a build with statistics takes as
  *                long as one without; a scan's time then includes the dispatch of the kernel that follows it
  *   1            HIP events attached to the launches (hipExtLaunchKernelGGL): each holds the queue for 4-7
  *                microseconds after its kernel, three per round

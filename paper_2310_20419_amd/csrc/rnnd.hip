@@ -279,8 +279,9 @@ struct OpenEdges {
 // another vertex counts as no repeat).  Equal vertices are equal keys only if the distances have the same bits.  Those of open keys do: one routine forms them, operands in the same order.
 // A listed one does (same_bits) where this library has formed it on the same rows, in either order, unless it is a NaN, whose sign is that of the operand it came
 // with or the other; a caller's snapshot may hold distances summed in another order, so there lists are not looked at.  Merge with / without: 1M x 96 float32 25.6 / 26.3 ms, 1M x 960 182 / 188; whole builds 1M x 960 513 / 524,
-// 300,000 x 768 bfloat16 97.6 / 99.8, 200,000 x 960 84.7 / 86.7, 200,000 x 16 10.83 / 10.84 (open keys only: 523, 99.3, 86.5, 10.92); not in
-// k_merge_blocks, whose rounds wait for latency: 20,000 x 96 0.935 / 0.890.
+// 300,000 x 768 bfloat16 97.6 / 99.8, 200,000 x 960 84.7 / 86.7, 200,000 x 16 10.83 / 10.84 (open keys only: 523, 99.3, 86.5, 10.92). Not in
+// k_merge_blocks (merge of 20,000 x 96 float32 0.935 / 0.890, whole builds of 96 bfloat16 20,000 2.51 / 2.47, 60,000 5.92 / 5.87), although long rows would gain there too: float32 20,000 x 960
+// 8.74 / 9.16, 60,000 x 384 12.2 / 12.5, 130,000 x 960 67.4 / 69.9, bfloat16 130,000 x 768 40.7 / 41.7.
 template <int G>
 __device__ __forceinline__ bool repeats(u64 key, bool open, u64 list, bool listed, OpenEdges *s, int lane)
 {

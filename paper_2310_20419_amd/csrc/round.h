@@ -21,8 +21,8 @@ struct RoundCtr {
     u32 n_redo;           // float scan: vertices the first form leaves to another launch (the double-precision form; R > 96: lists
                           // of more than 96 entries, the pair-at-a-time kernel)
     u32 pad[2];
-    // ticks of the device's constant-rate clock (0 = not taken): the round's first scan launch starts, its scatter
-    // starts (= the scan has ended: launches of one stream run back to back), the round's last kernel has ended
+    // ticks of the device's constant-rate clock (0 = not taken): the round's first scan launch starts, the launch after
+    // its scans starts (= they have ended: launches of one stream run back to back), the round's last kernel has ended
     // (taken by k_stamp after the last round before an AddReverseEdges call or the export, only where statistics
     // ask for it; every other round, and an AddReverseEdges call, ends where the next round's scan starts)
     u64 t_scan_start, t_scan_stop, t_round_stop;
@@ -63,7 +63,8 @@ __device__ __forceinline__ void stamp_scan_stop(RoundCtr *ctr)
 // builds of this repository's float workloads), the following ones take the other form (block-sequential passes: the following runs).
 // A round decides this only if it has `enough` active vertices: below, the sample is not one (a few lists lie in wavefronts that are all
 // sampled, or none), and the last rounds before an AddReverseEdges call, of a handful of vertices, say nothing about
-// the rounds after it.  The scatter decides, so that the scan, whose first loads everything waits for, has none more.
+// the rounds after it.  The launch after the scan decides (the scatter or, where the scan has scattered, the merge: end_scan), so that the scan, whose first loads
+// everything waits for, has none more.
 // The first round of a call has none before it; it takes groups if more than a GROUP_SHARE-th of the pairs of a sample of its lists
 // (k_float_sample) lie within the tiles' tolerance.
 #define OPEN_SAMPLE 32u
@@ -87,7 +88,7 @@ __device__ __forceinline__ bool group_form(RoundCtr *ctr)
 struct Prop {          // one redirected edge (Alg. 4, the edge update): `key` enters `tgt`'s list
     u64 key;
     u32 tgt;
-    u32 next;          // set by the scatter for edges past the inbox: the edge (its place in props) that was on tgt's list before
+    u32 next;          // set by whoever scatters, for edges past the inbox: the edge (its place in props) that was on tgt's list before
 };
 
 // A key whose distance is still to be computed (by the merge, see close_keys): these bits in place of the distance.  A NaN can

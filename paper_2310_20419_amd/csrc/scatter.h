@@ -75,9 +75,10 @@ struct PendingEdges {
 };
 
 // The scatter of the tile scans.  At the end of a trip a wavefront asks for the arrival numbers of the edges it has redirected, lanes that share
-// a target with one atomic, and at the end of the next one, when they have long been there, it writes the edges to their inboxes: the atomics, of which the part does 2.7 x
-// 10^10 a second and no more, run under the gathers, and no edge is stored and read again.  (The same work as a kernel of its own after the scan was bound by
-// them: 1M x 128 uint8 3.7 of 25.2 ms, 1M x 96 float32 8.1 of 102; at the end of a wavefront's walk it kept too few in flight: 100,000 x 128 a heavy round 63 + 23 -> 94 us.)
+// a target with one atomic, and at the end of the next one, when they have long been there, it writes the edges to their inboxes, so no edge is stored and read again.  (As a
+// kernel of its own after the scan the same work was bound by the atomics, of which the part does 2.7 x 10^10 a second and no more.  uint8 rows: they run under the gathers in part,
+// 1M x 128 scans 12.2 + scatter 3.7 ms as two kernels, 14.3 as one.  1M x 96 float32: hardly, 59.3 + 8.2 ms against 67.4, whole builds
+// 102.6 against 100.6.  At the end of a wavefront's walk it kept too few in flight: 100,000 x 128 a heavy round 63 + 23 -> 94 us.)
 // What waits from trip to trip is the key and the target of an edge in LDS, one edge per lane, and two registers.
 struct EdgeOut {
     typedef PendingEdges Pending;
