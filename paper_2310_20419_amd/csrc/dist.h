@@ -90,10 +90,11 @@ __device__ __forceinline__ int sqdiff_piece_u8(const uint4 &a, const uint4 &b, i
 
 // UF (float rows): 16-byte chunks per lane whose loads are issued together before the (ordered)
 // accumulation; it changes how many loads are in flight, never the order of the arithmetic.  UF >= 2.
-// TOGETHER, float16 rows: inside the large kernels the scheduler would wait for one piece after the other, so that the conversions take fewer registers; a barrier keeps
-// the loads before the arithmetic: 1M x 640, R = 32, 5 rounds 45.7 -> 39.5 ms, 20,000 x 768, R = 96, 60 rounds 8.3 -> 6.1.  (Not in RandomGraph, whose loads are together as it
-// is: with the registers that it then gives up, 300,000 x 768 takes 2.06 ms instead of 2.01.)
-template <int DT, int UF = 4, bool TOGETHER = true>
+// TOGETHER (16-bit rows): inside the float16 merges the scheduler waits for one piece after the other, so that the conversions take fewer registers.  Rows of more than 128
+// coordinates, which take several trips, there have a loop of their own in which a barrier keeps the loads before the arithmetic.  With two pieces a trip nothing spills (three: the same
+// within 8 % either way); in that loop rows of up to 128 took 1-4 % longer.  8 rounds, R = 96, before / now, ms: 300,000 x 160 6.83 / 5.88, x 320 8.84 / 8.43, x 960 27.8 / 22.9,
+// 20,000 x 768 2.08 / 1.51; 1M x 640, R = 32, 5 rounds 45.9 / 39.8.
+template <int DT, int UF = 4, bool TOGETHER = false>
 __device__ __forceinline__ uint32_t group8_dist_bits(const void *pa, const void *pb, int d,
                                                      int vec_ok, int sub)
 {
@@ -122,31 +123,56 @@ __device__ __forceinline__ uint32_t group8_dist_bits(const void *pa, const void 
             const int nchunk = d >> 3;
             const us8 *pa8 = (const us8 *)a, *pb8 = (const us8 *)b;
             int c = sub;
-            for (; c + 8 * (UF - 1) < nchunk; c += 8 * UF) {
-                us8 va[UF], vb[UF];
+            constexpr int TAIL = TOGETHER ? 2 : UF - 1;
+            if (TOGETHER) {
+                for (; nchunk > 8 * TAIL && c - sub < nchunk; c += 8 * UF) {
+                    us8 va[UF], vb[UF];
+                    if (c - sub + 8 * UF <= nchunk) {
 #pragma unroll
-                for (int k = 0; k < UF; ++k) { va[k] = pa8[c + 8 * k]; vb[k] = pb8[c + 8 * k]; }
-                if (DT == DT_F16 && TOGETHER) __builtin_amdgcn_sched_barrier(0);
+                        for (int k = 0; k < UF; ++k) { va[k] = pa8[c + 8 * k]; vb[k] = pb8[c + 8 * k]; }
+                    } else {
 #pragma unroll
-                for (int k = 0; k < UF; ++k)
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const double t = (double)coord16_to_float<DT>(va[k][e]) - (double)coord16_to_float<DT>(vb[k][e]);
-                        acc = fma(t, t, acc);
+                        for (int k = 0; k < UF; ++k) {      // (as below)
+                            const bool in = c + 8 * k < nchunk;
+                            va[k] = in ? pa8[c + 8 * k] : (us8)(0);
+                            vb[k] = in ? pb8[c + 8 * k] : (us8)(0);
+                        }
                     }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int k = 0; k < UF; ++k)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const double t = (double)coord16_to_float<DT>(va[k][e]) - (double)coord16_to_float<DT>(vb[k][e]);
+                            acc = fma(t, t, acc);
+                        }
+                }
+            } else {
+                for (; c + 8 * (UF - 1) < nchunk; c += 8 * UF) {
+                    us8 va[UF], vb[UF];
+#pragma unroll
+                    for (int k = 0; k < UF; ++k) { va[k] = pa8[c + 8 * k]; vb[k] = pb8[c + 8 * k]; }
+#pragma unroll
+                    for (int k = 0; k < UF; ++k)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const double t = (double)coord16_to_float<DT>(va[k][e]) - (double)coord16_to_float<DT>(vb[k][e]);
+                            acc = fma(t, t, acc);
+                        }
+                }
             }
             if (c < nchunk) {
                 // the last, shorter trip: its loads are issued together as well; a chunk past the end reads as zeros,
                 // and adding the square of 0 - 0 leaves the sum as it is, so the arithmetic is that of the short loop
-                us8 va[UF - 1 > 0 ? UF - 1 : 1], vb[UF - 1 > 0 ? UF - 1 : 1];
+                us8 va[TAIL > 0 ? TAIL : 1], vb[TAIL > 0 ? TAIL : 1];
 #pragma unroll
-                for (int k = 0; k < UF - 1; ++k) {
+                for (int k = 0; k < TAIL; ++k) {
                     const bool in = c + 8 * k < nchunk;
                     va[k] = in ? pa8[c + 8 * k] : (us8)(0);
                     vb[k] = in ? pb8[c + 8 * k] : (us8)(0);
                 }
 #pragma unroll
-                for (int k = 0; k < UF - 1; ++k)
+                for (int k = 0; k < TAIL; ++k)
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
                         const double t = (double)coord16_to_float<DT>(va[k][e]) - (double)coord16_to_float<DT>(vb[k][e]);

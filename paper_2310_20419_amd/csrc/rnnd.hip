@@ -320,7 +320,7 @@ __device__ __forceinline__ u64 close_keys(u64 key, int x, bool have, u64 list, b
             const int e = b + grp;
             if (e < total) {
                 const uint2 vw = s->edge[e];
-                const u32 db = group8_dist_bits<DT, 3>(X + (size_t)vw.x * rb, X + (size_t)vw.y * rb, d, 1, sub);
+                const u32 db = group8_dist_bits<DT, DT == DT_F16 ? 2 : 3, DT == DT_F16>(X + (size_t)vw.x * rb, X + (size_t)vw.y * rb, d, 1, sub);
                 if (sub == 0) s->dist[e] = db;
             }
         }

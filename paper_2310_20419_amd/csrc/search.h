@@ -350,7 +350,7 @@ __device__ __forceinline__ void search_eval(const void *X, const void *qv, int d
     for (int b = 0; b < cnt; b += 8) {
         const int p = b + grp;
         const int id = sm.id[p < cnt ? p : cnt - 1];
-        const u32 db = group8_dist_bits<DT, 4, false>(qv, (const char *)X + (size_t)id * rowbytes, d, vec_ok, sub);
+        const u32 db = group8_dist_bits<DT>(qv, (const char *)X + (size_t)id * rowbytes, d, vec_ok, sub);
         if (p < cnt && sub == 0) sm.dist[p] = db;
     }
 }

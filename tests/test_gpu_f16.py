@@ -81,7 +81,7 @@ def test_build_on_half_rows(rn, oracle_mod, variant, kind, N, d, S, R, T1, T2):
 
 
 # a trip of an exact distance takes 2, 3, 4, 5 or 8 pieces of 8 coordinates in each of 8 lanes: around each of these lengths, and two trips of the merge's
-@pytest.mark.parametrize("d", [120, 128, 136, 184, 192, 200, 256, 264, 320, 328, 384, 392, 512, 520])
+@pytest.mark.parametrize("d", [64, 96, 120, 128, 136, 160, 184, 192, 200, 256, 264, 320, 328, 384, 392, 512, 520])
 def test_rows_of_whole_and_partial_trips(rn, oracle_mod, variant, d):
     X16 = _half("gauss", 500, d, d)
     want = oracle_mod.build_sync(X16.astype(np.float32), 12, 40, 2, 3, 21)
